@@ -120,9 +120,11 @@ static bool is_device_ptr(const void *p) {
     return at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged;
 }
 
+// every array has 16 bytes behind its end: the row transforms read rows in groups of four numbers
+#define ARRAY_PAD 16
 template <typename T>
 static ripple_status dev_alloc(ripple_ctx *c, T **p, size_t count, bool zero) {
-    size_t bytes = (count ? count : 1) * sizeof(T);
+    size_t bytes = (count ? count : 1) * sizeof(T) + ARRAY_PAD;
     hipError_t e = hipMalloc((void **)p, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -204,7 +206,7 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     {   // features
         void *h0 = nullptr;
         size_t bytes = n * d0 * elem_size(c);
-        hipError_t e = hipMalloc(&h0, bytes ? bytes : 4);
+        hipError_t e = hipMalloc(&h0, bytes + ARRAY_PAD);
         if (e != hipSuccess) return fail(c, RIPPLE_ENOMEM, "device allocation of the feature matrix failed");
         c->H[0] = h0;
         RP_HIP(c, hipMemsetAsync(h0, 0, bytes, c->stream));
@@ -447,7 +449,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
     for (uint32_t l = 1; l <= c->L; ++l) {
         void *h = nullptr;
         size_t bytes = n * c->d[l] * elem_size(c);
-        if (hipMalloc(&h, bytes) != hipSuccess) return fail(c, RIPPLE_ENOMEM, "device allocation of H failed");
+        if (hipMalloc(&h, bytes + ARRAY_PAD) != hipSuccess) return fail(c, RIPPLE_ENOMEM, "device allocation of H failed");
         c->H[l] = h;
         RP_HIP(c, hipMemsetAsync(h, 0, bytes, c->stream));
         c->xw[l] = (c->layers[l - 1].proj || rp_layer_attn(c, l)) ? c->d[l] : c->d[l - 1];
@@ -572,7 +574,7 @@ extern "C" ripple_status ripple_full_infer(ripple_ctx *c) {
     hipLaunchKernelGGL(k_or_words, dim3(rp_div_up(c->n_words, 256)), dim3(256), 0, c->stream, c->bm[0], c->alive,
                        c->n_words);
     rp_launch_bitmap_to_list(c, c->bm[0], c->all_list, &c->ctr->a[0]);
-    if (c->opt_deterministic) rp_launch_alive_list(c);     // the same list once more, with its in-degree prefix
+    rp_launch_alive_list(c);                               // the same list once more, with its in-degree prefix
     for (uint32_t l = 1; l <= c->L; ++l) {
         if (rp_layer_attn(c, l)) {
             rp_launch_gat_project(c, l, c->all_list, &c->ctr->a[0]);

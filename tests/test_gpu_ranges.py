@@ -1,0 +1,35 @@
+"""Small cases at the edges of what single kernels and dispatch rules take, each against the oracle."""
+import numpy as np
+import pytest
+
+import paper_2601_12347_amd as rp
+import ripple_inputs as ri
+from harness import Pair, make_pair, make_stream
+
+pytestmark = pytest.mark.gpu
+
+MIX = {"edge_add": 0.5, "edge_del": 0.3, "feat": 0.2, "vadd": 0.0, "vdel": 0.0}
+
+
+@pytest.mark.parametrize("kind,weighted", [("gcn_sum", False), ("gcn_wsum", True), ("gcn_max", False), ("gcn_min", False)])
+@pytest.mark.parametrize("edges", [0, 1, 255, 256, 257, 5000])
+def test_bootstrap_sums_of_rows_that_span_runs(kind, weighted, edges):
+    """The in-edge space is cut into runs: a vertex whose in-edges lie in several (vertex 0, up to 5,000 in-edges), a few
+    short rows after it and vertices without any."""
+    print("case runs", kind, edges, flush=True)
+    n = 6000
+    src = np.arange(1, edges + 1, dtype=np.uint32)
+    dst = np.zeros(edges, np.uint32)
+    if edges > 1000:
+        src = np.concatenate([src, np.arange(100, 160, dtype=np.uint32)])
+        dst = np.concatenate([dst, np.repeat(np.arange(1, 21, dtype=np.uint32), 3)])
+    model = ri.make_model(kind, (7, 70, 9), 3)
+    weights = ri.edge_weights(len(src), 4) if weighted else None
+    pair = Pair(n, n + 5, src, dst, ri.features(n, 7, 1), model, weights=weights)
+    try:
+        pair.check_embeddings()
+        pair.check_aggregates()
+        rp.ripple_full_infer(pair.ctx)                     # a second time, over the sums of the first
+        pair.check_embeddings()
+    finally:
+        pair.close()
