@@ -35,43 +35,46 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {     // rou
     return (uint32_t)__builtin_bit_cast(unsigned short, a) | ((uint32_t)__builtin_bit_cast(unsigned short, b) << 16);
 }
 
+// Rows of any width: a row of 190 or 47 floats starts at a multiple of 4 bytes only, which a 16-byte global load takes all
+// the same. The last group of a row may read up to three numbers past its end (the next row's, or, behind the last row,
+// the padding dev_alloc puts behind every array); they are zeroed or dropped later.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uintx2u __attribute__((ext_vector_type(2), aligned(2)));    // four bf16 numbers
+__device__ __forceinline__ uint32_t last_group(uint32_t n) { return (n - 1u) & ~3u; }   // first column of a row's last group of four
+
 // Raw 16 (or 8) bytes for four consecutive k of one gathered row; no arithmetic on the data.
-// MODE 1 with bf16 embeddings and MODE 2 need two sources (p: own embedding, q: aggregate).
+// MODE 1 with bf16 embeddings and MODE 2 need two sources (p: own embedding, q: aggregate). MODE 1 takes rows whose width
+// is a multiple of four only (a group must not straddle the two halves).
 template <int MODE, int STORE>
 __device__ __forceinline__ void fetch_raw(const TArgs &a, uint32_t v, uint32_t slot, uint32_t k, floatx4 &p, floatx4 &q) {
-    const uint32_t kc = min(k, a.K - 4u);                     // stay inside the row; padding is zeroed later
+    const uint32_t kc = min(k, last_group(a.K));
     const size_t row = (size_t)v * a.d_in;
+    auto bf4 = [](const void *h, size_t i) {
+        const uintx2u r = *(const uintx2u *)((const __hip_bfloat16 *)h + i);
+        floatx4 f = (floatx4)(0.0f);
+        f.x = __uint_as_float(r.x);
+        f.y = __uint_as_float(r.y);
+        return f;
+    };
     if (MODE == 0) {
-        p = *(const floatx4 *)(a.X + row + kc);
+        p = *(const floatx4u *)(a.X + row + kc);
     } else if (MODE == 3) {
-        p = *(const floatx4 *)(a.tmp_in + (size_t)slot * a.tmp_ld + kc);
+        p = *(const floatx4u *)(a.tmp_in + (size_t)slot * a.tmp_ld + kc);
     } else if (MODE == 4) {
-        if (STORE) {
-            const uint2 r = *(const uint2 *)((const __hip_bfloat16 *)a.Hprev + row + kc);
-            p.x = __uint_as_float(r.x);
-            p.y = __uint_as_float(r.y);
-        } else {
-            p = *(const floatx4 *)((const float *)a.Hprev + row + kc);
-        }
+        if (STORE) p = bf4(a.Hprev, row + kc);
+        else p = *(const floatx4u *)((const float *)a.Hprev + row + kc);
     } else if (MODE == 2) {
-        q = *(const floatx4 *)(a.X + row + kc);
-        if (STORE) {
-            const uint2 r = *(const uint2 *)((const __hip_bfloat16 *)a.Hprev + row + kc);
-            p.x = __uint_as_float(r.x);
-            p.y = __uint_as_float(r.y);
-        } else {
-            p = *(const floatx4 *)((const float *)a.Hprev + row + kc);
-        }
+        q = *(const floatx4u *)(a.X + row + kc);
+        if (STORE) p = bf4(a.Hprev, row + kc);
+        else p = *(const floatx4u *)((const float *)a.Hprev + row + kc);
     } else {                                                  // MODE 1: k < d_in own embedding, else aggregate
         if (STORE) {
             const uint32_t kh = min(kc, a.d_in - 4u), kx = kc >= a.d_in ? kc - a.d_in : 0u;
-            const uint2 r = *(const uint2 *)((const __hip_bfloat16 *)a.Hprev + row + kh);
-            p.x = __uint_as_float(r.x);
-            p.y = __uint_as_float(r.y);
-            q = *(const floatx4 *)(a.X + row + kx);
+            p = bf4(a.Hprev, row + kh);
+            q = *(const floatx4u *)(a.X + row + kx);
         } else {
             const float *src = (kc < a.d_in) ? (const float *)a.Hprev + row + kc : a.X + row + (kc - a.d_in);
-            p = *(const floatx4 *)src;
+            p = *(const floatx4u *)src;
         }
     }
 }
@@ -99,7 +102,12 @@ __device__ __forceinline__ floatx4 finish_raw(const TArgs &a, floatx4 p, floatx4
         const floatx4 x = STORE ? q : p;
         r = (k < a.d_in) ? h : x * scale;
     }
-    if (k >= a.K) r = (floatx4)(0.0f);
+    if (k + 4u > a.K) {                                       // padding, and what was read past the row's end
+        r.x = k < a.K ? r.x : 0.0f;
+        r.y = k + 1u < a.K ? r.y : 0.0f;
+        r.z = k + 2u < a.K ? r.z : 0.0f;
+        r.w = k + 3u < a.K ? r.w : 0.0f;
+    }
     return r;
 }
 
@@ -163,19 +171,12 @@ __device__ __forceinline__ void epilogue(const TArgs &a, floatx16 (&acc)[TM][TN]
     }
 }
 
-// 16-byte (or element-wise, for rows whose width is not a multiple of four) accesses of the epilogues
-__device__ __forceinline__ floatx4 ld4(const float *p, bool vec, uint32_t n_valid) {
-    if (vec) return *(const floatx4 *)p;
-    floatx4 r = (floatx4)(0.0f);
-    if (n_valid > 0) r.x = p[0];
-    if (n_valid > 1) r.y = p[1];
-    if (n_valid > 2) r.z = p[2];
-    if (n_valid > 3) r.w = p[3];
-    return r;
-}
-__device__ __forceinline__ void st4(float *p, floatx4 v, bool vec, uint32_t n_valid) {
-    if (vec) {
-        *(floatx4 *)p = v;
+// 16-byte (bf16: 8-byte) accesses of the epilogues. full = false: a row's last group when the width is not a multiple of
+// four; a load takes the whole group all the same (see floatx4u), a store the valid numbers.
+__device__ __forceinline__ floatx4 ld4(const float *p) { return *(const floatx4u *)p; }
+__device__ __forceinline__ void st4(float *p, floatx4 v, bool full, uint32_t n_valid) {
+    if (full) {
+        *(floatx4u *)p = v;
         return;
     }
     if (n_valid > 0) p[0] = v.x;
@@ -183,20 +184,13 @@ __device__ __forceinline__ void st4(float *p, floatx4 v, bool vec, uint32_t n_va
     if (n_valid > 2) p[2] = v.z;
     if (n_valid > 3) p[3] = v.w;
 }
-__device__ __forceinline__ floatx4 ld4_bf16(const __hip_bfloat16 *p, bool vec, uint32_t n_valid) {
-    floatx4 r = (floatx4)(0.0f);
-    if (vec) {
-        const uint2 w = *(const uint2 *)p;
-        r.x = bf_lo(w.x);
-        r.y = bf_hi(w.x);
-        r.z = bf_lo(w.y);
-        r.w = bf_hi(w.y);
-        return r;
-    }
-    if (n_valid > 0) r.x = __bfloat162float(p[0]);
-    if (n_valid > 1) r.y = __bfloat162float(p[1]);
-    if (n_valid > 2) r.z = __bfloat162float(p[2]);
-    if (n_valid > 3) r.w = __bfloat162float(p[3]);
+__device__ __forceinline__ floatx4 ld4_bf16(const __hip_bfloat16 *p) {
+    floatx4 r;
+    const uintx2u w = *(const uintx2u *)p;
+    r.x = bf_lo(w.x);
+    r.y = bf_hi(w.x);
+    r.z = bf_lo(w.y);
+    r.w = bf_hi(w.y);
     return r;
 }
 
@@ -205,14 +199,14 @@ __device__ __forceinline__ floatx4 ld4_bf16(const __hip_bfloat16 *p, bool vec, u
 // between two loads makes the second wait for the first):
 //   EPI 0: act(z) goes to tmp_out (by slot or by vertex); nothing is read
 //   EPI 1: H is updated;  EPI 2: H is updated and the delta row written
-//   VEC: 16-byte accesses (row widths that are multiples of four); BF: bf16 embeddings
+//   VEC: every group is whole (row widths that are multiples of four); BF: bf16 embeddings
 template <int BN, int U, bool VEC, int EPI, bool BF>
 struct EpiRound {
     floatx4 old[U], add[U];
     uint32_t nv[U];                                        // valid columns of the group (0: nothing to do)
 
-    // request the old row and the addend of round it0 (no stores in here). With VEC, groups that will
-    // not be stored read a valid address all the same (the row of vertex 0 for slots past the end, the
+    // request the old row and the addend of round it0 (no stores in here, no branches between the loads). Groups that
+    // will not be stored read a valid address all the same (the row of vertex 0 for slots past the end, the
     // row's last four columns for padded columns), and a missing addend reads the bias instead.
     __device__ __forceinline__ void load(const TArgs &a, const uint32_t *s_vtx, const float *s_scale, uint32_t row0,
                                          uint32_t count, uint32_t n0, int tid, int it0) {
@@ -226,20 +220,12 @@ struct EpiRound {
             old[u] = (floatx4)(0.0f);
             add[u] = (floatx4)(0.0f);
             if (EPI == 0) continue;
-            if (VEC) {
-                const uint32_t lcol = min(col, a.N - 4u);
-                const size_t hidx = (size_t)s_vtx[r] * a.N + lcol;
-                old[u] = BF ? ld4_bf16((const __hip_bfloat16 *)a.Hout + hidx, true, 4) : ld4((const float *)a.Hout + hidx, true, 4);
-                const float *ap = a.addend ? a.addend + hidx : a.bias + lcol;
-                const floatx4 t = ld4(ap, true, 4);
-                const float sc = a.addend ? (a.addend_scaled ? s_scale[r] : 1.0f) : 0.0f;
-                add[u] = a.addend ? t * sc : (floatx4)(0.0f);
-            } else if (nv[u]) {
-                const size_t hidx = (size_t)s_vtx[r] * a.N + col;
-                old[u] = BF ? ld4_bf16((const __hip_bfloat16 *)a.Hout + hidx, false, nv[u])
-                            : ld4((const float *)a.Hout + hidx, false, nv[u]);
-                if (a.addend) add[u] = ld4(a.addend + hidx, false, nv[u]) * (a.addend_scaled ? s_scale[r] : 1.0f);
-            }
+            const uint32_t lcol = min(col, last_group(a.N));
+            const size_t hidx = (size_t)s_vtx[r] * a.N + lcol;
+            old[u] = BF ? ld4_bf16((const __hip_bfloat16 *)a.Hout + hidx) : ld4((const float *)a.Hout + hidx);
+            const floatx4 t = ld4(a.addend ? a.addend + hidx : a.bias + lcol);
+            const float sc = a.addend ? (a.addend_scaled ? s_scale[r] : 1.0f) : 0.0f;
+            add[u] = a.addend ? t * sc : (floatx4)(0.0f);
         }
     }
 
@@ -253,6 +239,7 @@ struct EpiRound {
             const int idx = tid + (it0 + u) * 256;
             const int r = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
             const uint32_t col = n0 + c4, slot = row0 + r;
+            const bool full = VEC || nv[u] == 4u;
             floatx4 v = *(const floatx4 *)&Cs[r * C_LD + c4] + *(const floatx4 *)(a.bias + col) + add[u];   // bias is padded
             if (a.act == RIPPLE_ACT_RELU) {
                 v.x = v.x > 0.0f ? v.x : 0.0f;
@@ -262,8 +249,8 @@ struct EpiRound {
             }
             if (EPI == 0) {
                 const size_t orow = (a.out_mode == 0) ? slot : s_vtx[r];
-                if (a.split_col && col >= a.split_col) st4(a.tmp_out2 + orow * a.tmp_out2_ld + (col - a.split_col), v, VEC, nv[u]);
-                else st4(a.tmp_out + orow * a.tmp_out_ld + col, v, VEC, nv[u]);
+                if (a.split_col && col >= a.split_col) st4(a.tmp_out2 + orow * a.tmp_out2_ld + (col - a.split_col), v, full, nv[u]);
+                else st4(a.tmp_out + orow * a.tmp_out_ld + col, v, full, nv[u]);
                 continue;
             }
             const size_t hidx = (size_t)s_vtx[r] * a.N + col;
@@ -272,8 +259,11 @@ struct EpiRound {
                 w.x = pack_bf16x2(v.x, v.y);
                 w.y = pack_bf16x2(v.z, v.w);
                 unsigned short *hp = (unsigned short *)a.Hout + hidx;
-                if (VEC) {
-                    *(uint2 *)hp = w;
+                if (full) {
+                    uintx2u wu;
+                    wu.x = w.x;
+                    wu.y = w.y;
+                    *(uintx2u *)hp = wu;
                 } else {
                     if (nv[u] > 0) hp[0] = (unsigned short)(w.x & 0xFFFFu);
                     if (nv[u] > 1) hp[1] = (unsigned short)(w.x >> 16);
@@ -285,9 +275,9 @@ struct EpiRound {
                 v.z = bf_lo(w.y);
                 v.w = bf_hi(w.y);
             } else {
-                st4((float *)a.Hout + hidx, v, VEC, nv[u]);
+                st4((float *)a.Hout + hidx, v, full, nv[u]);
             }
-            if (EPI == 2) st4(a.D + hidx, a.d_old ? old[u] : v - old[u], VEC, nv[u]);
+            if (EPI == 2) st4(a.D + hidx, a.d_old ? old[u] : v - old[u], full, nv[u]);
         }
     }
 };
@@ -635,20 +625,11 @@ __global__ __launch_bounds__(256, MINB) void k_transform_f32(TArgs a) {
     }
 }
 
-// Fallback for row widths that are not multiples of 4 (no 16-byte loads): same tiling, scalar
-// gathers, no prefetch.
-__device__ __forceinline__ float load_a1(const TArgs &a, uint32_t v, uint32_t slot, float scale, uint32_t k) {
+// [h_self | x] rows whose halves are not multiples of four columns wide (a group of four would straddle them; only layers
+// that concatenate and do not cache their self term get here): same tiling, scalar gathers, no prefetch.
+__device__ __forceinline__ float load_a1(const TArgs &a, uint32_t v, float scale, uint32_t k) {
     if (k >= a.K) return 0.0f;
-    switch (a.a_mode) {
-    case 0: return a.X[(size_t)v * a.d_in + k] * scale;
-    case 1:
-        return (k < a.d_in) ? rp_load_h(a.Hprev, a.store, (size_t)v * a.d_in + k)
-                            : a.X[(size_t)v * a.d_in + (k - a.d_in)] * scale;
-    case 2:
-        return a.one_plus_eps * rp_load_h(a.Hprev, a.store, (size_t)v * a.d_in + k) + a.X[(size_t)v * a.d_in + k] * scale;
-    case 4: return rp_load_h(a.Hprev, a.store, (size_t)v * a.d_in + k);
-    default: return a.tmp_in[(size_t)slot * a.tmp_ld + k];
-    }
+    return (k < a.d_in) ? rp_load_h(a.Hprev, a.store, (size_t)v * a.d_in + k) : a.X[(size_t)v * a.d_in + (k - a.d_in)] * scale;
 }
 
 template <int WAVES_M, int WAVES_N>
@@ -693,7 +674,7 @@ __global__ __launch_bounds__(256) void k_transform_generic(TArgs a) {
             for (int idx = tid; idx < BM * T_BK; idx += 256) {
                 const int r = idx / T_BK, k = idx % T_BK;
                 const uint32_t slot = row0 + r;
-                As[r][k] = (slot < count) ? load_a1(a, s_vtx[r], slot, s_scale[r], k0 + k) : 0.0f;
+                As[r][k] = (slot < count) ? load_a1(a, s_vtx[r], s_scale[r], k0 + k) : 0.0f;
             }
             for (int idx = tid; idx < T_BK * (BN / 4); idx += 256) {
                 const int kr = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
@@ -1121,11 +1102,11 @@ static void launch_fast(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t row
     }
 }
 
-static void launch_t(ripple_ctx *c, const TArgs &a, bool vec_ok, uint32_t rows_hint) {
+static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
     const bool narrow = rows_hint < 64u * c->n_cu;
     if (rp_launch_stream(c, a, rows_hint)) return;
     const uint32_t gx = c->n_cu * 2;
-    if (!vec_ok || a.K < 4) {
+    if (a.a_mode == 1 && (a.d_in & 3u)) {
         if (a.Npad >= 256) hipLaunchKernelGGL((k_transform_generic<1, 4>), dim3(gx, a.Npad / 256), dim3(256), 0, c->stream, a);
         else if (a.Npad == 128) hipLaunchKernelGGL((k_transform_generic<2, 2>), dim3(gx, 1), dim3(256), 0, c->stream, a);
         else hipLaunchKernelGGL((k_transform_generic<4, 1>), dim3(gx, 1), dim3(256), 0, c->stream, a);
@@ -1217,7 +1198,7 @@ void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
     a.Hout = nullptr;
     a.out_mode = 2;
     a.a_mode = 4;
-    launch_t(c, a, ly.d_in % 4 == 0, bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, a, bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
 }
 
 // Layers handled project-first that also cache their self term: both products of H^{l-1}[v], with W_self (into PS)
@@ -1255,7 +1236,7 @@ void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, con
         a.Npad = 96;
         a.split_col = 48;
     }
-    launch_t(c, a, true, hint);
+    launch_t(c, a, hint);
 }
 
 // Attention layer l: P[v] = H^{l-1}[v] W0 for the listed vertices (fp32, no bias, no activation).
@@ -1271,7 +1252,7 @@ void rp_launch_gat_project(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     a.tmp_out = ly.P;
     a.tmp_out_ld = ly.d_out;
     a.Hout = nullptr;
-    launch_t(c, a, ly.d_in % 4 == 0, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, a, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
 }
 
 // Cached self term of layer l: PS[v] = H^{l-1}[v] W_self for the listed vertices (fp32, no bias).
@@ -1290,7 +1271,7 @@ void rp_launch_self_project(ripple_ctx *c, uint32_t l, const uint32_t *list, con
     a.tmp_out = ly.PS;
     a.tmp_out_ld = ly.d_out;
     a.Hout = nullptr;
-    launch_t(c, a, ly.d_in % 4 == 0, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, a, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
 }
 
 // Re-apply layer l (1-based) to the vertices in `list` (count on the device).
@@ -1301,7 +1282,6 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     a.D = emit_delta ? c->D[l & 1] : nullptr;
     a.d_old = rp_layer_mono(c, l + 1) ? 1 : 0;
     a.a_mode = (ly.self_mode == RIPPLE_SELF_NONE) ? 0 : (ly.self_mode == RIPPLE_SELF_CONCAT ? 1 : 2);
-    const bool vec_in = (ly.d_in % 4 == 0);
     // expected row count: the previous batch's (bootstrap passes the list of all live vertices)
     const uint32_t hint = (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l);
     if (ly.agg == RIPPLE_AGG_ATTN) {             // h = act(numerator / denominator + b): no product left per row
@@ -1323,7 +1303,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
         a.a_mode = 4;                            // h_self * W_self: the first d_in rows of W0
         a.K = ly.d_in;
         a.Kpad = rp_round_up(ly.d_in, 32);
-        launch_t(c, a, vec_in, hint);
+        launch_t(c, a, hint);
         return;
     }
     if (ly.selfc) {                              // act((x * scale) W_neigh + PS[v] + b)
@@ -1338,12 +1318,12 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
         a.addend = ly.PS;
         a.addend_scaled = 0;
         a.act = (int)ly.act_out;
-        launch_t(c, a, vec_in, hint);
+        launch_t(c, a, hint);
         return;
     }
     if (ly.d_hidden == 0) {
         a.act = (int)ly.act_out;
-        launch_t(c, a, vec_in, hint);
+        launch_t(c, a, hint);
         return;
     }
     // two-stage update: hidden = act_inner(row W0 + b0) -> tmp, then h = act_out(hidden W1 + b1)
@@ -1355,7 +1335,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     s1.tmp_out_ld = ly.d_hidden;
     s1.Hout = nullptr;
     s1.D = nullptr;
-    launch_t(c, s1, vec_in, hint);
+    launch_t(c, s1, hint);
     TArgs s2 = a;
     s2.a_mode = 3;
     s2.tmp_in = c->tmp;
@@ -1373,5 +1353,5 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     s2.Npad = ly.N1pad;
     s2.act = (int)ly.act_out;
     s2.out_mode = 1;
-    launch_t(c, s2, ly.d_hidden % 4 == 0, hint);
+    launch_t(c, s2, hint);
 }

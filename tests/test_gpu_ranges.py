@@ -33,3 +33,21 @@ def test_bootstrap_sums_of_rows_that_span_runs(kind, weighted, edges):
         pair.check_embeddings()
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("kind,widths,store", [
+    ("gcn_sum", (1, 2, 3), "f32"), ("gcn_mean", (75, 190, 23), "f32"), ("sage_mean", (5, 129, 6), "f32"), ("gin_sum", (7, 9, 5), "f32"),
+    ("gat", (13, 31, 3), "f32"), ("sage_mean", (3, 33, 127, 2), "bf16"), ("gcn_sum", (9, 65, 31), "bf16"), ("gin_sum", (6, 11, 5), "bf16")])
+@pytest.mark.parametrize("self_cache", [True, False])
+def test_rows_of_any_width(kind, widths, store, self_cache):
+    """Widths that are not multiples of four: groups of four numbers are read past a row's end, written up to it."""
+    print("case widths", kind, widths, store, self_cache, flush=True)
+    pair, graph = make_pair(n=333, e=2000, d0=widths[0], kind=kind, widths=widths, store=store, seed=8, self_cache=self_cache)
+    try:
+        pair.check_embeddings()
+        stream = make_stream(pair, graph, MIX, 9)
+        for bs in (1, 60):
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload)
+    finally:
+        pair.close()
