@@ -573,7 +573,7 @@ extern "C" ripple_status ripple_full_infer(ripple_ctx *c) {
     // all live vertices as one list (the alive bitmap itself is the source)
     hipLaunchKernelGGL(k_or_words, dim3(rp_div_up(c->n_words, 256)), dim3(256), 0, c->stream, c->bm[0], c->alive,
                        c->n_words);
-    rp_launch_bitmap_to_list(c, c->bm[0], c->all_list, &c->ctr->a[0]);
+    rp_launch_bitmap_to_list(c, c->bm[0], c->all_list, 0xFFFFFFFFu, &c->ctr->a[0]);
     rp_launch_alive_list(c);                               // the same list once more, with its in-degree prefix
     for (uint32_t l = 1; l <= c->L; ++l) {
         if (rp_layer_attn(c, l)) {
@@ -1131,7 +1131,7 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
             }
         }
         if (multi && ops_done) {                   // the sets reported are those of the applied pieces
-            for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, &c->ctr->a[l]);
+            for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, 0xFFFFFFFFu, &c->ctr->a[l]);
             if (hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, s) == hipSuccess &&
                 hipStreamSynchronize(s) == hipSuccess)
                 for (uint32_t l = 0; l <= c->L; ++l) {
@@ -1144,7 +1144,7 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     }
     RP_HIP(c, hipGetLastError());
     if (multi) {                                   // sizes of the united sets
-        for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, &c->ctr->a[l]);
+        for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, 0xFFFFFFFFu, &c->ctr->a[l]);
         RP_HIP(c, hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, s));
         RP_HIP(c, hipStreamSynchronize(s));
         for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = c->ctr_host->a[l];
@@ -1273,7 +1273,7 @@ extern "C" ripple_status ripple_get_affected(ripple_ctx *c, uint32_t layer, uint
     hipStream_t s = c->stream;
     uint32_t *bitmap = c->last_from_rep ? c->rep[layer] : c->bm[layer];
     uint32_t *cnt_d = &c->ctr->n_all;              // free between batches
-    rp_launch_bitmap_to_list(c, bitmap, c->all_list, cnt_d);
+    rp_launch_bitmap_to_list(c, bitmap, c->all_list, 0xFFFFFFFFu, cnt_d);
     uint32_t n = 0;
     RP_HIP(c, hipMemcpyAsync(&n, cnt_d, 4, hipMemcpyDeviceToHost, s));
     RP_HIP(c, hipStreamSynchronize(s));

@@ -306,6 +306,16 @@ __device__ __forceinline__ uint32_t rp_seg_forward(const uint32_t *off, uint32_t
     }
     return rp_seg_search(off, lo, min(last, lo + step), e);
 }
+// inclusive prefix sum over the 64 lanes (data-parallel primitives: shifts inside rows of 16 lanes, then row broadcasts)
+__device__ __forceinline__ uint32_t rp_wave_scan(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
 // number of lanes whose value b (ascending over the lanes) is <= e, found with shuffles; to be
 // called by all 64 lanes together
 __device__ __forceinline__ uint32_t rp_count_le(uint32_t b, uint32_t e) {

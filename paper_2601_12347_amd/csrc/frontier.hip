@@ -9,6 +9,7 @@
 #include <cstring>
 
 #define MARK_CHUNK 256
+#define RP_STATIC_BLOCKS 16384u                  // entries of the static array (see below): blocks a compaction may have
 
 // mark the out-neighbours of every vertex of A_{l-1}. Every wavefront walks a contiguous run of
 // 256-edge chunks of the flattened out-edge space, so only its first chunk needs a search over the
@@ -242,103 +243,142 @@ struct CompactArgs {
     uint32_t list_cap;             // entries the list has room for (positions beyond are counted, not written)
 };
 
-// bitmap word of 32 mark bytes (each 0 or 1); the bytes are cleared again when any was set
-__device__ __forceinline__ uint32_t take_marks(uint8_t *mk, uint32_t idx) {
-    uint4 *p = (uint4 *)(mk + (size_t)idx * 32);
-    const uint4 lo = p[0], hi = p[1];
-    const uint32_t d[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    uint32_t w = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w |= (((d[k] * 0x00204081u) >> 21) & 0xFu) << (4 * k);   // bytes 0/1 -> four bits
-    if (w) {
-        p[0] = make_uint4(0, 0, 0, 0);
-        p[1] = make_uint4(0, 0, 0, 0);
-    }
-    return w;
-}
+// Compaction of a bitmap into its ascending list. A wavefront takes two bitmap words at a time, a lane being a vertex:
+// marks, degrees and list entries are then read and written with consecutive addresses (a lane per word read the degrees
+// of 32 consecutive vertices each, 64 cache lines per instruction: 15 + 48 us for both passes on 2.45 M vertices;
+// reading the degrees takes about 10). S steps of two words per wavefront, four wavefronts per
+// workgroup; the vertex's membership and degrees stay in registers between the sums and the list entries.
+template <int S>
+struct WordRange {
+    bool on[S];                    // this lane's vertex of step s is in the set
+    uint32_t o[S], i[S];           // its degrees (0 where not wanted or not in the set)
+    uint32_t cnt, tch, dout, din;  // the wavefront's totals
 
-__device__ __forceinline__ void word_degrees(const CompactArgs &a, uint32_t idx, uint32_t w, uint32_t &dout,
-                                             uint32_t &din) {
-    dout = din = 0;
-    if (!(a.want_out | a.want_in)) return;
-    while (w) {
-        uint32_t v = idx * 32 + (__ffs(w) - 1);
-        w &= w - 1;
-        if (a.want_out) dout += a.out_meta[v].y;
-        if (a.want_in) din += a.in_meta[v].y;
-    }
-}
+    static __device__ __forceinline__ uint32_t word(uint32_t w0, int s, int lane) { return w0 + 2u * s + ((uint32_t)lane >> 5); }
 
-// Degrees of the vertices of one bitmap word, all requested before any is used (the loads are
-// unconditional: a vertex that is not in the word reads entry 0 and counts as zero).
-struct WordDeg {
-    uint32_t o[32], i[32];
-    __device__ __forceinline__ void gather(const CompactArgs &a, uint32_t idx, uint32_t w, uint32_t &dout, uint32_t &din) {
-        dout = din = 0;
+    // the final set of words w0 .. w0 + 2 S - 1: marks, bitmap and roots merged and restricted to live vertices
+    __device__ __forceinline__ void merge(const CompactArgs &a, uint32_t w0, int lane) {
+        uint32_t w[S], live[S], root[S];
+        uint8_t m[S];
 #pragma unroll
-        for (int b = 0; b < 32; ++b) {
-            const bool on = (w >> b) & 1u;
-            const uint32_t v = on ? idx * 32 + b : 0u;
-            const uint32_t x = a.out_meta[v].y, y = a.in_meta[v].y;
-            o[b] = (on && a.want_out) ? x : 0u;
-            i[b] = (on && a.want_in) ? y : 0u;
-            dout += o[b];
-            din += i[b];
+        for (int s = 0; s < S; ++s) {
+            const uint32_t idx = word(w0, s, lane), ic = min(idx, a.n_words - 1u);
+            live[s] = idx < a.n_words ? a.alive[ic] : 0u;
+            w[s] = a.bm[ic];
+            m[s] = (a.mk && idx < a.n_words) ? a.mk[(size_t)ic * 32u + ((uint32_t)lane & 31u)] : (uint8_t)0;
+            root[s] = 0u;
+            if (a.bm_sink) root[s] |= a.bm_sink[ic] | a.bm_vadd[ic];
+            if (a.bm_prev) root[s] |= a.bm_prev[ic];
+        }
+        cnt = tch = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const uint32_t idx = word(w0, s, lane), b = (uint32_t)lane & 31u;
+            const bool lv = (live[s] >> b) & 1u;
+            const bool hit = lv && (m[s] != 0 || ((w[s] >> b) & 1u));
+            if (m[s]) a.mk[(size_t)idx * 32u + b] = 0;
+            on[s] = hit || (lv && ((root[s] >> b) & 1u));
+            const unsigned long long mask = __ballot(on[s]);
+            tch += (uint32_t)__popcll(__ballot(hit));              // vertices that received at least one message
+            cnt += (uint32_t)__popcll(mask);
+            if (b == 0 && idx < a.n_words) {
+                const uint32_t f = (lane == 0) ? (uint32_t)mask : (uint32_t)(mask >> 32);
+                if (f != w[s]) a.bm[idx] = f;
+                if (a.rep && f) a.rep[idx] |= f;
+            }
         }
     }
-    // list entries and prefixes of the word's vertices, starting at position oc with running sums oo, oi
-    __device__ __forceinline__ void emit(const CompactArgs &a, uint32_t idx, uint32_t w, uint32_t &oc, uint32_t &oo,
-                                         uint32_t &oi) const {
+    // the set as merge() left it in memory
+    __device__ __forceinline__ void read(const CompactArgs &a, uint32_t w0, int lane) {
+        uint32_t w[S];
 #pragma unroll
-        for (int b = 0; b < 32; ++b) {
-            if (!((w >> b) & 1u)) continue;
-            if (oc < a.list_cap) {
-                a.list[oc] = idx * 32 + b;
-                if (a.want_out) a.eoff[oc] = oo;
-                if (a.want_in) a.ioff[oc] = oi;
+        for (int s = 0; s < S; ++s) {
+            const uint32_t idx = word(w0, s, lane);
+            w[s] = idx < a.n_words ? a.bm[idx] & a.alive[idx] : 0u;
+        }
+        cnt = tch = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            on[s] = (w[s] >> ((uint32_t)lane & 31u)) & 1u;
+            cnt += (uint32_t)__popcll(__ballot(on[s]));
+        }
+    }
+    __device__ __forceinline__ void degrees(const CompactArgs &a, uint32_t w0, int lane) {
+        dout = din = 0;
+        if (!(a.want_out | a.want_in)) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) o[s] = i[s] = 0u;
+            return;
+        }
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const uint32_t v = (w0 + 2u * s) * 32u + (uint32_t)lane;
+            o[s] = (a.want_out && on[s]) ? a.out_meta[v].y : 0u;
+            i[s] = (a.want_in && on[s]) ? a.in_meta[v].y : 0u;
+        }
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            dout += o[s];
+            din += i[s];
+        }
+        dout = (uint32_t)__builtin_amdgcn_readlane((int)rp_wave_scan(dout), 63);
+        din = (uint32_t)__builtin_amdgcn_readlane((int)rp_wave_scan(din), 63);
+    }
+    // list entries and prefixes, from position oc and running sums oo, oi on
+    __device__ __forceinline__ void emit(const CompactArgs &a, uint32_t w0, int lane, uint32_t oc, uint32_t oo, uint32_t oi) const {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const unsigned long long mask = __ballot(on[s]);
+            if (!mask) continue;
+            const uint32_t pos = oc + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            const bool put = on[s] && pos < a.list_cap;
+            if (put) a.list[pos] = (w0 + 2u * s) * 32u + (uint32_t)lane;
+            oc += (uint32_t)__popcll(mask);
+            if (a.want_out) {
+                const uint32_t x = rp_wave_scan(o[s]);
+                if (put) a.eoff[pos] = oo + x - o[s];
+                oo += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
             }
-            oo += o[b];
-            oi += i[b];
-            ++oc;
+            if (a.want_in) {
+                const uint32_t x = rp_wave_scan(i[s]);
+                if (put) a.ioff[pos] = oi + x - i[s];
+                oi += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+            }
         }
     }
 };
 
+__device__ __forceinline__ void compact_totals(const CompactArgs &a, uint32_t oc, uint32_t oo, uint32_t oi) {
+    *a.count_out = oc;
+    if (a.want_out) {
+        a.eoff[oc] = oo;
+        if (a.msgs_out) *a.msgs_out = oo;
+    }
+    if (a.want_in) {
+        a.ioff[oc] = oi;
+        if (a.isum_out) *a.isum_out = oi;
+    }
+}
+
 // pass 1: merge the root sets (S, V_added, and the previous hop's set when the layer has a
 // self term) into the layer's bitmap, restrict to live vertices, count vertices and
-// (optionally) their degrees per block of 256 words
+// (optionally) their degrees per block of 8 S words
+template <int S>
 __global__ __launch_bounds__(256) void k_frontier_count(CompactArgs a) {
     __shared__ uint32_t sh[16];
-    const int tid = threadIdx.x;
-    uint32_t idx = blockIdx.x * 256 + tid;
-    uint32_t w = 0, tch = 0;
-    if (idx < a.n_words) {
-        const uint32_t live = a.alive[idx];
-        w = a.bm[idx];
-        if (a.mk) w |= take_marks(a.mk, idx);
-        w &= live;
-        tch = __popc(w);                         // vertices that received at least one message
-        if (a.bm_sink) w |= (a.bm_sink[idx] | a.bm_vadd[idx]) & live;
-        if (a.bm_prev) w |= a.bm_prev[idx] & live;
-        a.bm[idx] = w;
-        if (a.rep && w) a.rep[idx] |= w;
-    }
-    uint32_t cnt = __popc(w), dout, din;
-    word_degrees(a, idx, w, dout, din);
-    for (int o = 32; o > 0; o >>= 1) {
-        cnt += __shfl_down(cnt, o);
-        dout += __shfl_down(dout, o);
-        din += __shfl_down(din, o);
-        tch += __shfl_down(tch, o);
-    }
-    if ((tid & 63) == 0) {
-        sh[tid >> 6] = cnt;
-        sh[4 + (tid >> 6)] = dout;
-        sh[8 + (tid >> 6)] = din;
-        sh[12 + (tid >> 6)] = tch;
+    const int lane = rp_lane(), wave = threadIdx.x >> 6;
+    const uint32_t w0 = (blockIdx.x * 4u + wave) * 2u * S;
+    WordRange<S> r;
+    r.merge(a, w0, lane);
+    r.degrees(a, w0, lane);
+    if (lane == 0) {
+        sh[wave] = r.cnt;
+        sh[4 + wave] = r.dout;
+        sh[8 + wave] = r.din;
+        sh[12 + wave] = r.tch;
     }
     __syncthreads();
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         a.part_cnt[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
         a.part_out[blockIdx.x] = sh[4] + sh[5] + sh[6] + sh[7];
         a.part_in[blockIdx.x] = sh[8] + sh[9] + sh[10] + sh[11];
@@ -347,166 +387,123 @@ __global__ __launch_bounds__(256) void k_frontier_count(CompactArgs a) {
     }
 }
 
-// pass 2: write the ascending list, the degree prefixes and the per-word ranks
+// pass 2: write the ascending list and the degree prefixes
+template <int S>
 __global__ __launch_bounds__(256) void k_frontier_emit(CompactArgs a) {
-    __shared__ uint32_t sh[12];
-    __shared__ uint32_t wc[4], wo[4], wi[4];
+    __shared__ uint32_t sh[12], wt[12];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t w0 = (blockIdx.x * 4u + wave) * 2u * S;
+    WordRange<S> r;
+    r.read(a, w0, lane);                                   // on its way while the blocks before this one are summed
     uint32_t pc = 0, po = 0, pi = 0;
     for (uint32_t b = tid; b < blockIdx.x; b += 256) {
         pc += a.part_cnt[b];
         po += a.part_out[b];
         pi += a.part_in[b];
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        pc += __shfl_down(pc, o);
-        po += __shfl_down(po, o);
-        pi += __shfl_down(pi, o);
-    }
-    if (lane == 0) {
+    r.degrees(a, w0, lane);
+    pc = rp_wave_scan(pc);
+    po = rp_wave_scan(po);
+    pi = rp_wave_scan(pi);
+    if (lane == 63) {
         sh[wave] = pc;
         sh[4 + wave] = po;
         sh[8 + wave] = pi;
+        wt[wave] = r.cnt;
+        wt[4 + wave] = r.dout;
+        wt[8 + wave] = r.din;
     }
     __syncthreads();
-    pc = sh[0] + sh[1] + sh[2] + sh[3];
-    po = sh[4] + sh[5] + sh[6] + sh[7];
-    pi = sh[8] + sh[9] + sh[10] + sh[11];
-    uint32_t idx = blockIdx.x * 256 + tid;
-    uint32_t w = (idx < a.n_words) ? a.bm[idx] : 0u;
-    uint32_t cnt = __popc(w), dout = 0, din = 0;
-    WordDeg wd;
-    if (w) wd.gather(a, idx, w, dout, din);
-    uint32_t ic = cnt, io = dout, ii = din;
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t tc = __shfl_up(ic, o), to = __shfl_up(io, o), ti = __shfl_up(ii, o);
-        if (lane >= o) {
-            ic += tc;
-            io += to;
-            ii += ti;
-        }
-    }
-    if (lane == 63) {
-        wc[wave] = ic;
-        wo[wave] = io;
-        wi[wave] = ii;
-    }
-    __syncthreads();
-    uint32_t oc = pc + ic - cnt, oo = po + io - dout, oi = pi + ii - din;
+    uint32_t oc = sh[0] + sh[1] + sh[2] + sh[3], oo = sh[4] + sh[5] + sh[6] + sh[7], oi = sh[8] + sh[9] + sh[10] + sh[11];
     for (int k = 0; k < wave; ++k) {
-        oc += wc[k];
-        oo += wo[k];
-        oi += wi[k];
+        oc += wt[k];
+        oo += wt[4 + k];
+        oi += wt[8 + k];
     }
-    if (w) wd.emit(a, idx, w, oc, oo, oi);
-    if (blockIdx.x == gridDim.x - 1 && tid == 255) {     // the running values now hold the grand totals
-        *a.count_out = oc;
-        if (a.want_out) {
-            a.eoff[oc] = oo;
-            if (a.msgs_out) *a.msgs_out = oo;
-        }
-        if (a.want_in) {
-            a.ioff[oc] = oi;
-            if (a.isum_out) *a.isum_out = oi;
-        }
-    }
+    r.emit(a, w0, lane, oc, oo, oi);
+    if (blockIdx.x == gridDim.x - 1 && tid == 255) compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din);
 }
 
-// Both passes in one workgroup, for bitmaps of at most SMALL_WORDS words (small graphs: saves
-// two launches per hop, which is most of the hop's time when batches are small).
-#define SMALL_WPT 8
-#define SMALL_WORDS (1024 * SMALL_WPT)
-__global__ __launch_bounds__(1024) void k_frontier_compact_small(CompactArgs a) {
-    __shared__ uint32_t wc[16], wo[16], wi[16], wt[16];
+// Both passes in one workgroup, for bitmaps of at most ONE_WORDS words (8,192 vertices): one launch instead of two.
+#define ONE_STEPS 8
+#define ONE_WORDS (16u * 2u * ONE_STEPS)
+__global__ __launch_bounds__(1024) void k_frontier_compact_one(CompactArgs a) {
+    __shared__ uint32_t wt[16 * 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t wpt = (a.n_words + 1023u) / 1024u;      // consecutive words per thread (<= SMALL_WPT)
-    const uint32_t w0 = tid * wpt;
-    uint32_t words[SMALL_WPT];
-    uint32_t cnt = 0, dout = 0, din = 0, tch = 0;
-#pragma unroll
-    for (int k = 0; k < SMALL_WPT; ++k) {
-        words[k] = 0;
-        const uint32_t idx = w0 + k;
-        if ((uint32_t)k < wpt && idx < a.n_words) {
-            const uint32_t live = a.alive[idx];
-            uint32_t w = a.bm[idx];
-            if (a.mk) w |= take_marks(a.mk, idx);
-            w &= live;
-            tch += __popc(w);
-            if (a.bm_sink) w |= (a.bm_sink[idx] | a.bm_vadd[idx]) & live;
-            if (a.bm_prev) w |= a.bm_prev[idx] & live;
-            a.bm[idx] = w;
-            if (a.rep && w) a.rep[idx] |= w;
-            words[k] = w;
-            cnt += __popc(w);
-            uint32_t d_o, d_i;
-            word_degrees(a, idx, w, d_o, d_i);
-            dout += d_o;
-            din += d_i;
-        }
+    const uint32_t w0 = (uint32_t)wave * 2u * ONE_STEPS;
+    WordRange<ONE_STEPS> r;
+    r.merge(a, w0, lane);
+    r.degrees(a, w0, lane);
+    if (lane == 0) {
+        wt[wave] = r.cnt;
+        wt[16 + wave] = r.dout;
+        wt[32 + wave] = r.din;
+        wt[48 + wave] = r.tch;
     }
-    uint32_t ic = cnt, io = dout, ii = din, it = tch;
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t tc = __shfl_up(ic, o), to = __shfl_up(io, o), ti = __shfl_up(ii, o);
-        if (lane >= o) {
-            ic += tc;
-            io += to;
-            ii += ti;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) it += __shfl_down(it, o);
-    if (lane == 63) {
-        wc[wave] = ic;
-        wo[wave] = io;
-        wi[wave] = ii;
-    }
-    if (lane == 0) wt[wave] = it;
     __syncthreads();
-    uint32_t oc = ic - cnt, oo = io - dout, oi = ii - din;
+    uint32_t oc = 0, oo = 0, oi = 0;
     for (int k = 0; k < wave; ++k) {
-        oc += wc[k];
-        oo += wo[k];
-        oi += wi[k];
+        oc += wt[k];
+        oo += wt[16 + k];
+        oi += wt[32 + k];
     }
-#pragma unroll 1
-    for (uint32_t k = 0; k < wpt; ++k) {                   // one copy of the (long, unrolled) word code
-        const uint32_t idx = w0 + k;
-        if (idx >= a.n_words) break;
-        const uint32_t w = a.bm[idx];                      // this thread's own store of the first loop
-        if (!w) continue;
-        WordDeg wd;
-        uint32_t d_o, d_i;
-        wd.gather(a, idx, w, d_o, d_i);
-        wd.emit(a, idx, w, oc, oo, oi);
-    }
-    if (tid == 1023) {                                     // the last thread ends on the grand totals
-        *a.count_out = oc;
-        if (a.want_out) {
-            a.eoff[oc] = oo;
-            if (a.msgs_out) *a.msgs_out = oo;
-        }
-        if (a.want_in) {
-            a.ioff[oc] = oi;
-            if (a.isum_out) *a.isum_out = oi;
-        }
-    }
-    if (tid == 0 && a.touched_out) {
+    r.emit(a, w0, lane, oc, oo, oi);
+    if (tid == 1023) {
+        compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din);
         uint32_t t = 0;
-        for (int k = 0; k < 16; ++k) t += wt[k];
-        if (t) atomicAdd(a.touched_out, t);
+        for (int k = 0; k < 16; ++k) t += wt[48 + k];
+        if (a.touched_out && t) atomicAdd(a.touched_out, t);
     }
 }
 
-// expect: how many vertices the list will probably hold. One workgroup writes a long list slowly
-// (its scattered stores all leave through one CU), so the single-launch kernel is kept for short ones.
-static void launch_compact(ripple_ctx *c, const CompactArgs &a, uint32_t expect) {
-    if (a.n_words <= SMALL_WORDS && expect <= 4096) {
-        hipLaunchKernelGGL(k_frontier_compact_small, dim3(1), dim3(1024), 0, c->stream, a);
+// bitmap & alive -> ascending ids and their number, nothing else: every block adds up the words before its own by itself (at
+// most RANK_WORDS of them, from the L2), so one launch does it and no scratch is needed.
+#define RANK_WORDS 32768u
+__global__ __launch_bounds__(256) void k_bitmap_ids(CompactArgs a) {
+    constexpr int S = 4;
+    __shared__ uint32_t sh[4], wt[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t w0 = (blockIdx.x * 4u + wave) * 2u * S;
+    WordRange<S> r;
+    r.read(a, w0, lane);
+    uint32_t pc = 0;
+    typedef uint32_t uintx4u __attribute__((ext_vector_type(4), aligned(4)));
+    const uintx4u *bm4 = (const uintx4u *)a.bm, *al4 = (const uintx4u *)a.alive;   // 8 S words per block: whole groups of four
+    for (uint32_t k = tid; k < blockIdx.x * (2u * S); k += 256u) {
+        const uintx4u x = bm4[k], y = al4[k];
+        pc += __popc(x.x & y.x) + __popc(x.y & y.y) + __popc(x.z & y.z) + __popc(x.w & y.w);
+    }
+    pc = rp_wave_scan(pc);
+    if (lane == 63) {
+        sh[wave] = pc;
+        wt[wave] = r.cnt;
+    }
+    __syncthreads();
+    uint32_t oc = sh[0] + sh[1] + sh[2] + sh[3];
+    for (int k = 0; k < wave; ++k) oc += wt[k];
+#pragma unroll
+    for (int s = 0; s < S; ++s) r.o[s] = r.i[s] = 0u;
+    r.emit(a, w0, lane, oc, 0u, 0u);
+    if (blockIdx.x == gridDim.x - 1 && tid == 255) *a.count_out = oc + r.cnt;
+}
+
+// Words per block: 32 up to half a million vertices (several blocks per compute unit where the graph allows it), 64 above,
+// and 256 where 64 would need more blocks than the static array has entries.
+static void launch_compact(ripple_ctx *c, const CompactArgs &a) {
+    if (a.n_words <= ONE_WORDS) {
+        hipLaunchKernelGGL(k_frontier_compact_one, dim3(1), dim3(1024), 0, c->stream, a);
         return;
     }
-    const uint32_t nb = rp_div_up(a.n_words, 256);
-    hipLaunchKernelGGL(k_frontier_count, dim3(nb), dim3(256), 0, c->stream, a);
-    hipLaunchKernelGGL(k_frontier_emit, dim3(nb), dim3(256), 0, c->stream, a);
+#define RP_COMPACT(S)                                                                                            \
+    do {                                                                                                         \
+        const dim3 nb(rp_div_up(a.n_words, 8 * (S)));                                                            \
+        hipLaunchKernelGGL((k_frontier_count<S>), nb, dim3(256), 0, c->stream, a);                               \
+        hipLaunchKernelGGL((k_frontier_emit<S>), nb, dim3(256), 0, c->stream, a);                                \
+    } while (0)
+    if (a.n_words <= 16384u) RP_COMPACT(4);
+    else if (a.n_words <= 64u * RP_STATIC_BLOCKS) RP_COMPACT(8);
+    else RP_COMPACT(32);
+#undef RP_COMPACT
 }
 
 // degree prefixes over an arbitrary (unsorted) list, one workgroup: out-degrees into eoff (hop 0, and the
@@ -618,7 +615,7 @@ void rp_launch_alive_list(ripple_ctx *c) {
     a.list = c->all_list;
     a.ioff = c->ioff_all;
     a.count_out = &c->ctr->n_all;
-    launch_compact(c, a, c->n_cap);
+    launch_compact(c, a);
 }
 
 // bitmap of layer l, merged with S, V_added (and A_{l-1} when self_term) -> list[l], ctr->a[l];
@@ -651,7 +648,7 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
     a.msgs_out = (l < RIPPLE_MAX_LAYERS) ? &c->ctr->m[l + 1] : nullptr;
     a.isum_out = &c->ctr->isum[l];
     a.list_cap = 0xFFFFFFFFu;
-    launch_compact(c, a, rp_rows_hint(c, l));
+    launch_compact(c, a);
 }
 
 // Candidates of a max / min hop: the vertices marked by the out-edge walk from A_{l-1}, S and V_added,
@@ -675,14 +672,19 @@ void rp_launch_candidates(ripple_ctx *c, uint32_t l) {
     a.touched_out = &c->ctr->touched[l];
     a.list = c->all_list;
     a.count_out = &c->ctr->n_all;
-    launch_compact(c, a, c->hints_valid ? c->last_cand[l] : c->n_cap);
+    launch_compact(c, a);
 }
 
-// any bitmap & alive -> ascending list in `out_list`, count in *count_d (device)
-void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t *count_d) {
+static void bitmap_ids(ripple_ctx *c, CompactArgs &a) {
+    if (a.n_words <= RANK_WORDS) hipLaunchKernelGGL(k_bitmap_ids, dim3(rp_div_up(a.n_words, 32)), dim3(256), 0, c->stream, a);
+    else launch_compact(c, a);
+}
+
+// any bitmap & alive -> ascending list in `out_list` (room for cap), count in *count_d (both device memory, or pinned host memory)
+void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t cap, uint32_t *count_d) {
     CompactArgs a;
     memset(&a, 0, sizeof(a));
-    a.list_cap = 0xFFFFFFFFu;
+    a.list_cap = cap;
     a.bm = bitmap;
     a.alive = c->alive;
     a.n_words = c->n_words;
@@ -693,7 +695,7 @@ void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_lis
     a.part_in = c->part_ideg;
     a.list = out_list;
     a.count_out = count_d;
-    launch_compact(c, a, c->n_cap);
+    bitmap_ids(c, a);
 }
 
 // ---------------------------------------------------------------------------------
@@ -703,7 +705,6 @@ void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_lis
 // counts, and the out- and in-degree sums the first pass writes alongside). One copy per GPU, shared by
 // every context on that GPU and kept until the process ends; every launch writes the entries it reads,
 // so nothing has to be cleared between calls, and calls that overlap on one GPU race on it.
-#define RP_STATIC_BLOCKS 16384u                  // 256 bitmap words = 8192 vertices per block
 static __device__ __align__(256) uint32_t scratch[3 * RP_STATIC_BLOCKS];
 #define RP_MAX_DEVICES 64
 static uint32_t *g_scratch_ptr[RP_MAX_DEVICES] = {nullptr};    // the array's address on each GPU
@@ -728,8 +729,7 @@ ripple_status rp_launch_affected_static(ripple_ctx *c, uint32_t *bitmap, uint32_
         c->err = "the static scratch array was not set up for this GPU";
         return RIPPLE_ESTATE;
     }
-    const uint32_t nb = rp_div_up(c->n_words, 256);
-    if (nb > RP_STATIC_BLOCKS) {
+    if (rp_div_up(c->n_words, 256) > RP_STATIC_BLOCKS) {
         c->err = "vertex capacity " + std::to_string(c->n_cap) + " exceeds what the no-allocation call supports (" +
                  std::to_string(rp_static_max_vertices()) + ")";
         return RIPPLE_EINVAL;
@@ -747,8 +747,7 @@ ripple_status rp_launch_affected_static(ripple_ctx *c, uint32_t *bitmap, uint32_
     a.list = ids_out;
     a.list_cap = cap;
     a.count_out = n_out;
-    hipLaunchKernelGGL(k_frontier_count, dim3(nb), dim3(256), 0, c->stream, a);
-    hipLaunchKernelGGL(k_frontier_emit, dim3(nb), dim3(256), 0, c->stream, a);
+    bitmap_ids(c, a);
     RP_HIP(c, hipGetLastError());
     RP_HIP(c, hipStreamSynchronize(c->stream));
     return RIPPLE_OK;

@@ -30,7 +30,7 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
 void rp_launch_candidates(ripple_ctx *c, uint32_t l);
 void rp_launch_candidates_sparse(ripple_ctx *c, uint32_t l, bool self_term, uint32_t long_min);
 void rp_launch_list_offsets(ripple_ctx *c, uint32_t l, bool want_out);
-void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t *count_d);
+void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t cap, uint32_t *count_d);
 void rp_launch_list_eoff(ripple_ctx *c, uint32_t l);
 ripple_status rp_static_scratch_init(ripple_ctx *c);
 uint32_t rp_static_max_vertices();
