@@ -188,7 +188,8 @@ struct ripple_ctx {
     float *payload_pin = nullptr;
     uint32_t pin_ops_cap = 0, pin_feat_cap = 0;
 
-    // gather staging for get_* calls
+    // gather staging for get_* calls; pinned: 16 words (a count), then ids, then rows
+    uint32_t *io_pin = nullptr;
     float *gather_d = nullptr;
     uint32_t *gather_ids = nullptr;
     size_t gather_cap = 0, gather_ids_cap = 0;
