@@ -5,6 +5,7 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <chrono>
 #include <cstring>
 #include <new>
 
@@ -76,7 +77,7 @@ typedef float gfloatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t guintx2u __attribute__((ext_vector_type(2), aligned(2)));
 template <int STORE>
 __global__ __launch_bounds__(256) void k_gather_rows(const void *M, uint32_t d, const uint32_t *ids, uint32_t first,
-                                                     size_t n_rows, uint32_t n_cap, float *out) {
+                                                     size_t n_rows, uint32_t n_cap, float *out, HostFlag done) {
     const uint32_t groups = (d + 3u) / 4u;                   // of four numbers; a row's last one may be short
     const size_t total = n_rows * groups, stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
@@ -105,6 +106,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(const void *M, uint32_t d, 
             if (col + 2u < d) o[2] = v.z;
         }
     }
+    report_done(done, gridDim.x);
 }
 
 __global__ void k_or_words(uint32_t *dst, const uint32_t *src, uint32_t n) {
@@ -174,6 +176,29 @@ static ripple_status dev_alloc(ripple_ctx *c, T **p, size_t count, bool zero) {
         if (rc__ != RIPPLE_OK) return rc__;  \
     } while (0)
 
+static ripple_status fail(ripple_ctx *c, ripple_status rc, const char *msg);
+
+HostFlag rp_host_flag(ripple_ctx *c) { return HostFlag{c->pub_flag, ++c->pub_seq, c->ctr}; }
+
+// Waits until the launch that was given the last rp_host_flag has reported: it is the stream's last kernel, so the kernels before
+// it have finished, and what it and they wrote is visible. Looking at a word of pinned memory costs less than a wait for the
+// stream, which goes over every launch since the last one (a batch of twenty launches: 63 against 90 us). What takes longer than
+// the limit gets the stream wait, which also is what reports a device error.
+#define WAIT_SPIN_US 2000.0
+ripple_status rp_wait_flag(ripple_ctx *c) {
+    RP_HIP(c, hipGetLastError());
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t k = 0; __atomic_load_n(c->pub_flag, __ATOMIC_ACQUIRE) != c->pub_seq; ++k) {
+        __builtin_ia32_pause();
+        if ((k & 255u) == 255u && std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > WAIT_SPIN_US) {
+            RP_HIP(c, hipStreamSynchronize(c->stream));
+            break;
+        }
+    }
+    if (__atomic_load_n(c->pub_flag, __ATOMIC_ACQUIRE) != c->pub_seq) return fail(c, RIPPLE_EDEVICE, "a kernel did not report its end");
+    return RIPPLE_OK;
+}
+
 static size_t elem_size(const ripple_ctx *c) { return c->store ? 2 : 4; }
 
 static ripple_status fail(ripple_ctx *c, ripple_status rc, const char *msg) {
@@ -235,6 +260,8 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     RP_TRY(dev_alloc(c, &c->ctr, 1, true));
     RP_HIP(c, hipHostMalloc((void **)&c->ctr_host, sizeof(DevCtr), hipHostMallocDefault));
     memset(c->ctr_host, 0, sizeof(DevCtr));
+    RP_HIP(c, hipHostMalloc((void **)&c->pub_flag, 64, hipHostMallocDefault));
+    *c->pub_flag = 0;
     RP_HIP(c, hipHostMalloc((void **)&c->io_pin, (16 + IO_PIN_IDS + IO_PIN_FLOATS) * 4, hipHostMallocDefault));
     {   // features
         void *h0 = nullptr;
@@ -290,7 +317,7 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
     hipStreamSynchronize(c->stream);
     void *ptrs[] = {c->out_meta, c->in_meta, c->out_capv, c->in_capv, c->vstate, c->pend_out, c->pend_in, c->dead_out,
                     c->dead_in, c->hole_out, c->hole_in, c->out_pool, c->in_pool, c->in_w, c->alive, c->part_cnt, c->part_deg, c->part_ideg, c->ioff[0], c->ctr, c->D[0], c->D[1],
-                    c->tmp, c->PD, c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->seg_v, c->seg_done, c->seg_base, c->seg_r, c->seg_part, c->bm[0], c->rep[0], c->list[0], c->eoff[0], c->all_list, c->ioff_all, c->mk, c->ops_d, c->payload_d,
+                    c->tmp, c->PD, c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->seg_v, c->seg_done, c->seg_base, c->seg_r, c->seg_part, c->bm[0], c->rep[0], c->list[0], c->eoff[0], c->all_list, c->ioff_all, c->mk, c->ops_d,
                     c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_s, c->exp_a,
                     c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->tail_ids, c->tail_q, c->tail_w, c->sk_in, c->sk_out, c->sv_in, c->sv_out, c->sort_tmp, c->gather_d, c->gather_ids, c->pk_a, c->pk_b, c->pv_a, c->pv_b, c->pair_tmp};
     for (void *p : ptrs)
@@ -311,6 +338,7 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
     if (c->ops_pin) hipHostFree(c->ops_pin);
     if (c->payload_pin) hipHostFree(c->payload_pin);
     if (c->io_pin) hipHostFree(c->io_pin);
+    if (c->pub_flag) hipHostFree(c->pub_flag);
     if (c->timer) {
         for (hipEvent_t e : c->timer->ev) hipEventDestroy(e);
         delete c->timer;
@@ -607,28 +635,28 @@ extern "C" ripple_status ripple_full_infer(ripple_ctx *c) {
     // all live vertices as one list (the alive bitmap itself is the source)
     hipLaunchKernelGGL(k_or_words, dim3(rp_div_up(c->n_words, 256)), dim3(256), 0, c->stream, c->bm[0], c->alive,
                        c->n_words);
-    rp_launch_bitmap_to_list(c, c->bm[0], c->all_list, 0xFFFFFFFFu, &c->ctr->a[0]);
+    rp_launch_bitmap_to_list(c, c->bm[0], c->all_list, 0xFFFFFFFFu, &c->ctr->set[0].a);
     rp_launch_alive_list(c);                               // the same list once more, with its in-degree prefix
     for (uint32_t l = 1; l <= c->L; ++l) {
         if (rp_layer_attn(c, l)) {
-            rp_launch_gat_project(c, l, c->all_list, &c->ctr->a[0]);
-            rp_launch_gat_scores(c, l, c->all_list, &c->ctr->a[0]);
+            rp_launch_gat_project(c, l, c->all_list, &c->ctr->set[0].a);
+            rp_launch_gat_scores(c, l, c->all_list, &c->ctr->set[0].a);
             rp_launch_gat_scatter(c, l, true);
-            rp_launch_transform(c, l, c->all_list, &c->ctr->a[0], false);
+            rp_launch_transform(c, l, c->all_list, &c->ctr->set[0].a, false);
             continue;
         }
         if (rp_has_project_both(c, l)) {
-            rp_launch_project_both(c, l, c->all_list, &c->ctr->a[0], true);
+            rp_launch_project_both(c, l, c->all_list, &c->ctr->set[0].a, true);
         } else {
-            if (c->layers[l - 1].proj) rp_launch_project(c, l, c->all_list, &c->ctr->a[0], true);
-            if (c->layers[l - 1].selfc) rp_launch_self_project(c, l, c->all_list, &c->ctr->a[0]);
+            if (c->layers[l - 1].proj) rp_launch_project(c, l, c->all_list, &c->ctr->set[0].a, true);
+            if (c->layers[l - 1].selfc) rp_launch_self_project(c, l, c->all_list, &c->ctr->set[0].a);
         }
         if (c->opt_deterministic) rp_launch_scatter_pull_det(c, l, true);  // same summation order as the batches use
         else rp_launch_pull_all(c, l);
-        rp_launch_transform(c, l, c->all_list, &c->ctr->a[0], false);
+        rp_launch_transform(c, l, c->all_list, &c->ctr->set[0].a, false);
     }
     RP_HIP(c, hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, c->stream));
-    rp_launch_batch_reset(c);
+    rp_launch_batch_reset(c, nullptr, 0);
     RP_HIP(c, hipStreamSynchronize(c->stream));
     RP_HIP(c, hipGetLastError());
     const uint32_t range_rows = c->ctr_host->range_rows;
@@ -827,12 +855,9 @@ static ripple_status ensure_batch_buffers(ripple_ctx *c, uint32_t n_ops, uint32_
     if (n_feat > c->feat_cap) {
         RP_HIP(c, hipStreamSynchronize(c->stream));
         uint32_t cap = rp_round_up(std::max<uint32_t>(n_feat + n_feat / 2, 1024), 256);
-        if (c->payload_d) hipFree(c->payload_d);
         if (c->payload_pin) hipHostFree(c->payload_pin);
-        c->payload_d = nullptr;
         c->payload_pin = nullptr;
         c->feat_cap = 0;
-        RP_TRY(dev_alloc(c, &c->payload_d, (size_t)cap * c->d[0], false));
         RP_HIP(c, hipHostMalloc((void **)&c->payload_pin, (size_t)cap * c->d[0] * 4, hipHostMallocDefault));
         c->feat_cap = cap;
     }
@@ -859,13 +884,29 @@ static bool small_frontier(const ripple_ctx *c, uint32_t l, uint32_t n_ops, bool
            c->last_m[l] <= SPARSE_MAX_EDGES && c->last_n_ops && n_ops <= 2 * c->last_n_ops;
 }
 
+// Hop l of a sum or mean layer was so small that it pushes and is launched whole (rp_launch_hop_small): the same hint with
+// limits of its own. The push costs an atomic per number sent (3e11 a second), so the numbers are bounded to what takes
+// about as long as the launches saved; twice the vertices of small_frontier, because no single workgroup goes over the list here.
+#define TINY_MAX_ROWS 16384u
+#define TINY_MAX_NUMBERS (4u << 20)
+static bool tiny_hop(const ripple_ctx *c, uint32_t l, uint32_t n_ops, bool multi) {
+    const LayerDev &ly = c->layers[l - 1];
+    if (ly.proj && ly.self_mode == RIPPLE_SELF_CONCAT && !ly.selfc) return false;      // (a product per row is left in the row update)
+    return c->opt_sparse && !multi && c->opt_scatter <= 1 && c->opt_sorted < 2 && c->last_n_ops && n_ops <= 2 * c->last_n_ops &&
+           c->last_a[l] <= TINY_MAX_ROWS && c->last_a[l - 1] <= TINY_MAX_ROWS &&
+           (uint64_t)c->last_m[l] * c->xw[l] <= TINY_MAX_NUMBERS;
+}
+
 // Enqueue one conflict-free piece: Apply, then hop by hop frontier / scatter / transform.
 static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
     const uint32_t n = sb.end - sb.begin;
     int t = rp_timer_begin(c);
-    rp_launch_batch_reset(c);
-    rp_launch_mutate(c, n, sb.has_vadd, sb.has_vdel, sb.has_vertex_or_feat);
-    rp_launch_list_eoff(c, 0);
+    const ripple_update *ops = c->ops_pin + sb.begin;
+    if (!rp_launch_mutate_small(c, ops, n, sb.has_vdel, sb.has_vertex_or_feat)) {
+        rp_launch_batch_reset(c, ops, n);
+        rp_launch_mutate(c, n, sb.has_vadd, sb.has_vdel, sb.has_vertex_or_feat);
+        rp_launch_list_eoff(c, 0);
+    }
     rp_timer_end(c, t, RIPPLE_PH_INGEST, 0);
     if (multi)
         hipLaunchKernelGGL(k_or_words, dim3(rp_div_up(c->n_words, 256)), dim3(256), 0, c->stream, c->rep[0], c->bm[0],
@@ -882,10 +923,10 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             if (c->layers[l - 1].proj || c->layers[l - 1].selfc) {
                 t = rp_timer_begin(c);
                 if (rp_has_project_both(c, l)) {
-                    rp_launch_project_both(c, l, c->list[l - 1], &c->ctr->a[l - 1], false);
+                    rp_launch_project_both(c, l, c->list[l - 1], &c->ctr->set[l - 1].a, false);
                 } else {
-                    if (c->layers[l - 1].proj) rp_launch_project(c, l, c->list[l - 1], &c->ctr->a[l - 1], false);
-                    if (c->layers[l - 1].selfc) rp_launch_self_project(c, l, c->list[l - 1], &c->ctr->a[l - 1]);
+                    if (c->layers[l - 1].proj) rp_launch_project(c, l, c->list[l - 1], &c->ctr->set[l - 1].a, false);
+                    if (c->layers[l - 1].selfc) rp_launch_self_project(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
                 }
                 if (c->layers[l - 1].proj) rp_launch_messages(c, l);
                 rp_timer_end(c, t, RIPPLE_PH_OTHER, (int)l);
@@ -894,7 +935,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_launch_scatter_pull_det(c, l, false);
             rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);
             t = rp_timer_begin(c);
-            rp_launch_transform(c, l, c->list[l], &c->ctr->a[l], next_reads_delta(c, l));
+            rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));
             rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
         }
         return;
@@ -913,7 +954,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             }
             if (c->layers[l - 1].selfc) {
                 t = rp_timer_begin(c);
-                rp_launch_self_project(c, l, c->list[l - 1], &c->ctr->a[l - 1]);
+                rp_launch_self_project(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
                 rp_timer_end(c, t, RIPPLE_PH_OTHER, (int)l);
             }
             t = rp_timer_begin(c);
@@ -924,16 +965,16 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             else rp_launch_frontier_compact(c, l, layer_self(c, l), l < c->L, false, multi, true);
             rp_timer_end(c, t, RIPPLE_PH_COMPACT, (int)l);
             t = rp_timer_begin(c);
-            rp_launch_transform(c, l, c->list[l], &c->ctr->a[l], next_reads_delta(c, l));
+            rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));
             rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
             have_all = false;                          // the candidates went through the live-vertex list's buffer
             continue;
         }
         if (rp_layer_attn(c, l)) {                     // attention: recompute or numerator / denominator deltas (Sec. 3.4.1)
             t = rp_timer_begin(c);
-            rp_launch_gat_save(c, l, c->list[l - 1], &c->ctr->a[l - 1]);
-            rp_launch_gat_project(c, l, c->list[l - 1], &c->ctr->a[l - 1]);
-            rp_launch_gat_scores(c, l, c->list[l - 1], &c->ctr->a[l - 1]);
+            rp_launch_gat_save(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
+            rp_launch_gat_project(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
+            rp_launch_gat_scores(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
             rp_timer_end(c, t, RIPPLE_PH_OTHER, (int)l);
             const bool listed = small_frontier(c, l, n, multi);
             if (listed) {
@@ -952,7 +993,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_launch_gat_scatter(c, l, false, listed);
             rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);
             t = rp_timer_begin(c);
-            rp_launch_transform(c, l, c->list[l], &c->ctr->a[l], next_reads_delta(c, l));
+            rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));
             rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
             have_all = false;                          // the long-row queue went through the live-vertex list's buffer
             continue;
@@ -963,6 +1004,17 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         // mode: its kernels are enqueued only where the previous batch came near its threshold.
         // Weighted-sum layers gather along in-edges at every hop (the weights are stored with the in-rows only).
         const bool wsum = c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
+        if (!wsum && tiny_hop(c, l, n, multi)) {       // two or three launches for the whole hop
+            t = rp_timer_begin(c);
+            rp_launch_hop_small(c, l, layer_self(c, l));
+            rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
+            t = rp_timer_begin(c);
+            const LayerDev &ly = c->layers[l - 1];
+            if (ly.proj) rp_launch_small_addend(c, l, next_reads_delta(c, l));
+            else rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));
+            rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
+            continue;
+        }
         const bool may_pull = wsum || (l >= 2 && c->opt_scatter != 1 && !(c->opt_scatter == 0 && c->push_margin[l]));
         const bool may_disc = l >= 2 && may_pull && (c->opt_scatter == 3 || ((c->opt_scatter == 0 || wsum) && c->disc_near[l]));
         // a frontier that was small last time (and a batch of about the same size) is listed as it is marked
@@ -992,14 +1044,14 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         const bool both = rp_has_project_both(c, l);
         if (c->layers[l - 1].proj) {                   // what travels is already multiplied by W_neigh
             t = rp_timer_begin(c);
-            if (both) rp_launch_project_both(c, l, c->list[l - 1], &c->ctr->a[l - 1], false);   // and the self terms in the same pass
-            else rp_launch_project(c, l, c->list[l - 1], &c->ctr->a[l - 1], false);
+            if (both) rp_launch_project_both(c, l, c->list[l - 1], &c->ctr->set[l - 1].a, false);   // and the self terms in the same pass
+            else rp_launch_project(c, l, c->list[l - 1], &c->ctr->set[l - 1].a, false);
             rp_launch_messages(c, l);
             rp_timer_end(c, t, RIPPLE_PH_OTHER, (int)l);
         }
         if (c->layers[l - 1].selfc && !both) {         // H^{l-1} changed exactly on A_{l-1}
             t = rp_timer_begin(c);
-            rp_launch_self_project(c, l, c->list[l - 1], &c->ctr->a[l - 1]);
+            rp_launch_self_project(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
             rp_timer_end(c, t, RIPPLE_PH_OTHER, (int)l, !c->layers[l - 1].proj);
         }
         if (may_disc) {                                // scatters and marks A_l in one scan of all in-rows
@@ -1018,23 +1070,24 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         if (may_pull) rp_launch_scatter_pull(c, l, false, may_disc, pair_cap);
         rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);
         t = rp_timer_begin(c);
-        rp_launch_transform(c, l, c->list[l], &c->ctr->a[l], next_reads_delta(c, l));
+        rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));
         rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
     }
+}
+
+// The counters to the host, and the end of everything enqueued before.
+static ripple_status publish_and_wait(ripple_ctx *c) {
+    rp_launch_publish(c);
+    return rp_wait_flag(c);
 }
 
 // Stage, enqueue and wait for one piece; on a full adjacency pool or a full scratch buffer the piece (which
 // aborts on the device before it changes anything) is retried after compaction / growth. On return with
 // RIPPLE_OK the pinned mirror of the counters describes the piece.
 static ripple_status run_piece(ripple_ctx *c, const SubBatch &sb, bool multi, uint32_t *compactions) {
-    hipStream_t s = c->stream;
-    const uint32_t n = sb.end - sb.begin;
     for (int attempt = 0;; ++attempt) {
-        RP_HIP(c, hipMemcpyAsync(c->ops_d, c->ops_pin + sb.begin, (size_t)n * sizeof(ripple_update),
-                                 hipMemcpyHostToDevice, s));
         enqueue_piece(c, sb, multi);
-        RP_HIP(c, hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, s));
-        RP_HIP(c, hipStreamSynchronize(s));
+        RP_TRY(publish_and_wait(c));
         const DevCtr &h = *c->ctr_host;
         if (!h.abort_flag) return RIPPLE_OK;
         if (h.abort_flag & 8u) {
@@ -1045,7 +1098,6 @@ static ripple_status run_piece(ripple_ctx *c, const SubBatch &sb, bool multi, ui
         if (attempt >= 2) return fail(c, RIPPLE_ECAPACITY, "adjacency pool exhausted even after compaction");
         if (h.abort_flag & 4u) {
             uint32_t want = h.need_exp + h.need_exp / 2 + 1024;
-            // the caller's payload pointer may sit in payload_d: only the operation-side buffers grow here
             RP_TRY(ensure_batch_buffers(c, c->ops_cap, 0, want));
         }
         if (h.abort_flag & 1u) {
@@ -1067,7 +1119,7 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     hipStream_t s = c->stream;
     int t_total = rp_timer_begin(c);
 
-    RP_TRY(ensure_batch_buffers(c, n_ops, n_feat_rows, 0));
+    RP_TRY(ensure_batch_buffers(c, n_ops, (n_feat_rows && !is_device_ptr(feat_payload)) ? n_feat_rows : 0u, 0));
     // operations are needed on the host (validation, conflict analysis)
     const ripple_update *hops = ops;
     if (n_ops && is_device_ptr(ops)) {
@@ -1078,9 +1130,8 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     if (!ops_in_range(hops, n_ops, c->n_cap, n_feat_rows))
         return fail(c, RIPPLE_EINVAL, "operation with unknown kind, vertex id or payload row out of range");
     if (n_ops == 0) {                              // nothing to do: the affected sets become empty
-        rp_launch_batch_reset(c);
-        RP_HIP(c, hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, s));
-        RP_HIP(c, hipStreamSynchronize(s));
+        rp_launch_batch_reset(c, nullptr, 0);
+        RP_TRY(publish_and_wait(c));
         for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = 0;
         c->last_from_rep = false;
         if (res) {
@@ -1096,16 +1147,11 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
 
     if (multi)
         RP_HIP(c, hipMemsetAsync(c->rep[0], 0, (size_t)c->n_words * (c->L + 1) * 4, s));
-    // payload: used in place when it already lives on the device
-    float *payload_saved = c->payload_d;
-    if (n_feat_rows) {
-        size_t bytes = (size_t)n_feat_rows * c->d[0] * 4;
-        if (is_device_ptr(feat_payload)) {
-            c->payload_d = const_cast<float *>(feat_payload);
-        } else {
-            memcpy(c->payload_pin, feat_payload, bytes);
-            RP_HIP(c, hipMemcpyAsync(c->payload_d, c->payload_pin, bytes, hipMemcpyHostToDevice, s));
-        }
+    // feature rows: used in place when they already live on the device
+    c->payload = feat_payload;
+    if (n_feat_rows && !is_device_ptr(feat_payload)) {          // the kernel that applies them reads each row once, over the bus
+        memcpy(c->payload_pin, feat_payload, (size_t)n_feat_rows * c->d[0] * 4);
+        c->payload = c->payload_pin;
     }
 
     ripple_status rc = RIPPLE_OK;
@@ -1125,25 +1171,25 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
         n_struct += h.n_struct;
         range_rows += h.range_rows;
         for (uint32_t l = 1; l <= c->L; ++l) {
-            msgs[l] += h.m[l];
+            msgs[l] += h.set[l - 1].m;
             tchd[l] += h.touched[l];
-            c->last_m[l] = h.m[l];
+            c->last_m[l] = h.set[l - 1].m;
             c->last_isum[l] = h.isum[l];
             c->last_hop_mode[l] = h.hop_mode[l];
             hop_mode[l] = h.hop_mode[l];
             for (int k = 0; k < 3; ++k) mono[k][l] += h.mono[k][l];
             c->last_cand[l] = h.mono[0][l] + h.mono[1][l] + h.mono[2][l];
             // pull wins when m * row_bytes * ratio >= 8 * in-edges; remember if push won by a factor of 16
-            const unsigned long long lhs = (unsigned long long)h.m[l] * c->xw[l] * 4ull * (unsigned)c->opt_pull_ratio * 16ull;
+            const unsigned long long lhs = (unsigned long long)h.set[l - 1].m * c->xw[l] * 4ull * (unsigned)c->opt_pull_ratio * 16ull;
             c->push_margin[l] = lhs < 8ull * h.isum[l];
-            c->disc_near[l] = (unsigned long long)h.m[l] * 64ull >= h.n_edges;     // threshold: m * 8 >= edges
+            c->disc_near[l] = (unsigned long long)h.set[l - 1].m * 64ull >= h.n_edges;     // threshold: m * 8 >= edges
         }
         if (!multi)
-            for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = h.a[l];
+            for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = h.set[l].a;
         c->last_n_ops = multi ? 0u : n;
         c->hints_valid = !multi;
     }
-    c->payload_d = payload_saved;                  // never leave the caller's buffer in the context
+    c->payload = nullptr;                          // never leave the caller's buffer in the context
     if (rc != RIPPLE_OK) {
         // Pieces before the failing one stay applied and fully propagated (the state is that of the batch's
         // first ops_done operations); the failing piece changed nothing. Say how far the batch got.
@@ -1165,11 +1211,12 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
             }
         }
         if (multi && ops_done) {                   // the sets reported are those of the applied pieces
-            for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, 0xFFFFFFFFu, &c->ctr->a[l]);
+            for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, 0xFFFFFFFFu, &c->ctr->set[l].a);
+            c->ctr_dirty = true;
             if (hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, s) == hipSuccess &&
                 hipStreamSynchronize(s) == hipSuccess)
                 for (uint32_t l = 0; l <= c->L; ++l) {
-                    c->last_a[l] = c->ctr_host->a[l];
+                    c->last_a[l] = c->ctr_host->set[l].a;
                     if (res) res->affected[l] = c->last_a[l];
                 }
             c->last_from_rep = true;
@@ -1178,10 +1225,11 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     }
     RP_HIP(c, hipGetLastError());
     if (multi) {                                   // sizes of the united sets
-        for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, 0xFFFFFFFFu, &c->ctr->a[l]);
+        for (uint32_t l = 0; l <= c->L; ++l) rp_launch_bitmap_to_list(c, c->rep[l], c->all_list, 0xFFFFFFFFu, &c->ctr->set[l].a);
+        c->ctr_dirty = true;
         RP_HIP(c, hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, s));
         RP_HIP(c, hipStreamSynchronize(s));
-        for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = c->ctr_host->a[l];
+        for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = c->ctr_host->set[l].a;
     }
     c->last_from_rep = multi;
     rp_timer_end(c, t_total, RIPPLE_PH_TOTAL, 0);
@@ -1257,21 +1305,22 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
         RP_HIP(c, hipStreamSynchronize(s));
         return RIPPLE_OK;
     }
-    auto launch = [&](size_t r0, size_t rows, float *to) {
+    auto launch = [&](size_t r0, size_t rows, float *to, bool report) {
         const uint32_t gb = (uint32_t)std::min<size_t>((rows * ((d + 3) / 4) + 255) / 256, c->n_cu * 16);
         const uint32_t *from = ids_d ? ids_d + r0 : nullptr;
-        if (store) hipLaunchKernelGGL(k_gather_rows<1>, dim3(gb), dim3(256), 0, s, M, d, from, (uint32_t)r0, rows, c->n_cap, to);
-        else hipLaunchKernelGGL(k_gather_rows<0>, dim3(gb), dim3(256), 0, s, M, d, from, (uint32_t)r0, rows, c->n_cap, to);
+        const HostFlag done = (report && gb <= REPORT_WGS) ? rp_host_flag(c) : HostFlag{nullptr, 0u, nullptr};
+        if (store) hipLaunchKernelGGL(k_gather_rows<1>, dim3(gb), dim3(256), 0, s, M, d, from, (uint32_t)r0, rows, c->n_cap, to, done);
+        else hipLaunchKernelGGL(k_gather_rows<0>, dim3(gb), dim3(256), 0, s, M, d, from, (uint32_t)r0, rows, c->n_cap, to, done);
+        if (report && !done.flag) rp_launch_report(c);
     };
     if (to_device) {
-        launch(0, n_ids, out);
-        RP_HIP(c, hipStreamSynchronize(s));
-        return RIPPLE_OK;
+        launch(0, n_ids, out, true);
+        return rp_wait_flag(c);
     }
     if (total <= IO_PIN_FLOATS) {
         float *rows = (float *)(c->io_pin + 16 + IO_PIN_IDS);
-        launch(0, n_ids, rows);
-        RP_HIP(c, hipStreamSynchronize(s));
+        launch(0, n_ids, rows, true);
+        RP_TRY(rp_wait_flag(c));
         memcpy(out, rows, total * 4);
         return RIPPLE_OK;
     }
@@ -1286,7 +1335,7 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
     }
     for (size_t r0 = 0; r0 < n_ids; r0 += chunk_rows) {
         size_t rows = std::min<size_t>(chunk_rows, n_ids - r0);
-        launch(r0, rows, c->gather_d);
+        launch(r0, rows, c->gather_d, false);
         RP_HIP(c, hipMemcpyAsync(out + r0 * d, c->gather_d, rows * d * 4, hipMemcpyDeviceToHost, s));
         RP_HIP(c, hipStreamSynchronize(s));
     }
@@ -1326,11 +1375,10 @@ extern "C" ripple_status ripple_get_affected(ripple_ctx *c, uint32_t layer, uint
     if (!c) return RIPPLE_EINVAL;
     if (c->state != 3) return fail(c, RIPPLE_ESTATE, "no batch has been applied");
     if (layer > c->L || !n_out || (cap && !ids_out)) return fail(c, RIPPLE_EINVAL, "bad argument");
-    hipStream_t s = c->stream;
     uint32_t *bitmap = c->last_from_rep ? c->rep[layer] : c->bm[layer];
     const bool direct = cap <= IO_PIN_IDS;         // the ids go straight to pinned host memory
-    rp_launch_bitmap_to_list(c, bitmap, direct ? c->io_pin + 16 : c->all_list, cap, c->io_pin);
-    RP_HIP(c, hipStreamSynchronize(s));
+    rp_launch_bitmap_to_list(c, bitmap, direct ? c->io_pin + 16 : c->all_list, cap, c->io_pin, true);
+    RP_TRY(rp_wait_flag(c));
     const uint32_t n = c->io_pin[0];
     *n_out = n;
     uint32_t m = std::min(n, cap);

@@ -457,12 +457,12 @@ __global__ __launch_bounds__(TEAM * 64) void k_gat_scatter_seg(GatArgs a) {
     }
 }
 
-// bootstrap: every live vertex (c->all_list, count in ctr->a[0]) is recomputed
+// bootstrap: every live vertex (c->all_list, count in ctr->set[0].a) is recomputed
 void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool prequeued) {
     const LayerDev &ly = c->layers[l - 1];
     GatArgs a;
     a.list = bootstrap ? c->all_list : c->list[l];
-    a.count_ptr = bootstrap ? &c->ctr->a[0] : &c->ctr->a[l];
+    a.count_ptr = bootstrap ? &c->ctr->set[0].a : &c->ctr->set[l].a;
     a.queue = bootstrap ? c->list[0] : c->all_list;     // scratch that is free at that point
     a.queue_count = &c->ctr->n_long[l];
     a.in_meta = c->in_meta;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
+#include <stddef.h>
 #include <stdint.h>
 #include <string>
 #include <vector>
@@ -24,8 +25,18 @@
 #define EXP_IN 2u                    // (x -> w): erase w from x's out-row
 
 struct DevCtr {                      // device-resident counters, one instance per context
-    uint32_t a[RIPPLE_MAX_LAYERS + 1];        // |A_l|
-    uint32_t m[RIPPLE_MAX_LAYERS + 1];        // out-edges walked from A_{l-1}
+    // kept from batch to batch
+    unsigned long long n_edges;
+    uint32_t n_alive;
+    uint32_t out_top, in_top;                 // first free pool entry
+    uint32_t error;                           // sticky consistency error seen by a kernel
+    uint32_t blocks_done;                     // workgroups of a kernel with a last-workgroup part that have finished (0 between launches)
+    uint32_t n_all;                           // live vertices listed for a discovering hop
+    // from here on: zero when a batch begins (k_publish clears them once it has handed them to the host)
+    struct Set {
+        uint32_t a;                           // |A_l|
+        uint32_t m;                           // out-edges of A_l: messages into layer l + 1
+    } set[RIPPLE_MAX_LAYERS + 1];             // (eight bytes, so that small hops add to both at once)
     uint32_t touched[RIPPLE_MAX_LAYERS + 1];  // distinct live destinations of those edges
     uint32_t isum[RIPPLE_MAX_LAYERS + 1];     // sum of in-degrees over A_l
     uint32_t n_struct;
@@ -35,11 +46,8 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t n_applied, n_rejected;
     uint32_t n_add, n_del;                    // accepted edge adds / deletes (ops only)
     uint32_t need_out, need_in;               // pool entries relocation will take
-    uint32_t out_top, in_top;                 // first free pool entry
-    uint32_t n_alive;
     uint32_t n_vadd;
-    uint32_t abort_flag;                      // written by k_capacity's last workgroup: 0 ok, bit0 pool, bit1 edges, bit2 scratch
-    uint32_t n_all;                           // live vertices listed for a discovering hop
+    uint32_t abort_flag;                      // written by the capacity decision: 0 ok, bit0 pool, bit1 edges, bit2 scratch
     uint32_t n_long[RIPPLE_MAX_LAYERS + 1];   // max / min and attention hops: vertices with long in-rows queued for the workgroup kernel
     uint32_t cand[RIPPLE_MAX_LAYERS + 1];     // max / min hops: candidates listed while they were marked (small hops)
     uint32_t n_big[RIPPLE_MAX_LAYERS + 1];    // very long in-rows whose recomputation was split into segments
@@ -47,13 +55,12 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t mono[3][RIPPLE_MAX_LAYERS + 1];  // max / min hops: candidates left unchanged / raised from the messages / recomputed
     uint32_t hop_mode[RIPPLE_MAX_LAYERS + 1]; // 1 + RP_HOP_* of the scatter kernel that moved hop l's messages (0: none ran)
     uint32_t range_rows;                      // attention layers: rows updated from sums that were not finite
-    unsigned long long n_edges;
-    uint32_t blocks_done;                     // workgroups of k_capacity that have finished (0 between launches)
     uint32_t n_tail_q;                        // deterministic mode: in-rows whose appended entries a workgroup puts in order
-    uint32_t error;                           // sticky consistency error seen by a kernel
     uint32_t tail_top;                        // ... and the part of the copy buffer they have taken
     uint32_t pull_next[RIPPLE_MAX_LAYERS + 1];// pull scatter of hop l: runs of chunks handed out so far
 };
+#define RP_CTR_WORDS ((uint32_t)(sizeof(DevCtr) / 4))
+#define RP_CTR_BATCH ((uint32_t)(offsetof(DevCtr, set) / 4))   // first word that is zero when a batch begins
 
 #define RP_MONO_LISTED_LONG 64u        // small max / min and attention hops: in-rows longer than this are queued for a workgroup while the hop's vertices are listed
 #define ROW_SPLIT_MIN 512u
@@ -159,7 +166,7 @@ struct ripple_ctx {
     // batch staging
     uint32_t ops_cap = 0, feat_cap = 0;
     ripple_update *ops_d = nullptr;
-    float *payload_d = nullptr;
+    const float *payload = nullptr;                      // feature rows of the batch in progress: the caller's (device) or payload_pin
     uint32_t *op_status = nullptr, *op_pos_out = nullptr, *op_pos_in = nullptr;
     uint32_t *op_touch = nullptr;                        // per operation: accepted / add / first touch of its rows
     uint32_t *touch_out = nullptr, *touch_in = nullptr;  // touched row lists
@@ -183,10 +190,13 @@ struct ripple_ctx {
     void *sort_tmp = nullptr;
     size_t sort_tmp_bytes = 0;
     DevCtr *ctr = nullptr;
-    DevCtr *ctr_host = nullptr;                         // pinned mirror
+    DevCtr *ctr_host = nullptr;                         // pinned mirror, written by k_publish
+    uint32_t *pub_flag = nullptr;                       // pinned: number of the last k_publish that has finished
+    uint32_t pub_seq = 0;
+    bool ctr_dirty = false;                             // the per-batch counters are not zero (something ran after k_publish)
     ripple_update *ops_pin = nullptr;                   // pinned staging for ops
     float *payload_pin = nullptr;
-    uint32_t pin_ops_cap = 0, pin_feat_cap = 0;
+    uint32_t pin_ops_cap = 0;
 
     // gather staging for get_* calls; pinned: 16 words (a count), then ids, then rows
     uint32_t *io_pin = nullptr;
@@ -298,6 +308,10 @@ __device__ __forceinline__ uint32_t rp_seg_search_wave(const uint32_t *off, uint
     const uint32_t p = lo + lane;
     return lo + (uint32_t)__popcll(__ballot(p <= hi && p > lo && off[p] <= e));
 }
+// end of row i of the out-edge space of a listed set: eoff holds where each row begins, M is the total
+__device__ __forceinline__ uint32_t rp_row_end(const uint32_t *eoff, uint32_t count, uint32_t M, uint32_t i) {
+    return i + 1u < count ? eoff[i + 1u] : M;
+}
 // the same over [lo, last], for an answer expected close to lo: doubling steps, then bisection
 __device__ __forceinline__ uint32_t rp_seg_forward(const uint32_t *off, uint32_t lo, uint32_t last, uint32_t e) {
     uint32_t step = 1;
@@ -331,6 +345,36 @@ __device__ __forceinline__ uint32_t rp_count_le(uint32_t b, uint32_t e) {
     return lo;
 }
 
+// true in the last of n workgroups to get here (all of what the others wrote is then visible); called by whole workgroups
+__device__ __forceinline__ bool last_workgroup(DevCtr *ctr, uint32_t n) {
+    __shared__ uint32_t s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wavefront's stores and atomics have been performed: a barrier alone does not wait for them
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_last = atomicAdd(&ctr->blocks_done, 1u) == n - 1u ? 1u : 0u;
+        if (s_last) ctr->blocks_done = 0;
+    }
+    __syncthreads();
+    if (!s_last) return false;
+    __threadfence();
+    return true;
+}
+// The same for a launch whose results the host waits for by looking at *flag (pinned memory) instead of waiting for the stream: the
+// last workgroup stores `seq` there. flag null: nothing is reported. For launches of at most REPORT_WGS workgroups (each costs about
+// 60 ns, one after the other); after larger ones k_report does it.
+#define REPORT_WGS 24u
+struct HostFlag {
+    uint32_t *flag;
+    uint32_t seq;
+    DevCtr *ctr;
+};
+__device__ __forceinline__ void report_done(const HostFlag &h, uint32_t n) {
+    if (!h.flag) return;
+    __threadfence_system();                                 // results may lie in the host's memory
+    if (last_workgroup(h.ctr, n) && threadIdx.x == 0) __hip_atomic_store(h.flag, h.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---- packed messages ------------------------------------------------------------------
 // A message row of 33..48 numbers as one 128-byte line of sixteen 8-byte chunks. Chunk c holds columns
 // c, 16 + c and 32 + c as 19-bit two's-complement integers q (bits 0-18, 19-37, 38-56) that share a power of
@@ -342,16 +386,26 @@ __device__ __forceinline__ uint32_t rp_count_le(uint32_t b, uint32_t e) {
 #define RP_MSG_QBITS 19
 static inline uint32_t rp_msg_packed(uint32_t d) { return (d > 32u && d <= 48u) ? 1u : 0u; }   // up to 32 floats are one line as they are
 #ifdef __HIPCC__
-__device__ __forceinline__ uint2 rp_msg_encode(float m0, float m1, float m2, float &v0, float &v1, float &v2) {
-    const float big = fmaxf(fabsf(m0), fmaxf(fabsf(m1), fabsf(m2)));
+// binary exponent of the factor of a chunk whose largest magnitude is `big`; and a number as its integer
+__device__ __forceinline__ int rp_msg_exp(float big) {
     int e = 0;
     (void)frexpf(big, &e);                                  // big < 2^e
-    const int se = max(-81, min(45, e - (RP_MSG_QBITS - 1)));   // the factor is 2^se
-    const bool zero = !(big > 0.0f);
+    return max(-81, min(45, e - (RP_MSG_QBITS - 1)));       // the factor is 2^se
+}
+__device__ __forceinline__ int rp_msg_q(float m, int se) {
     const int lim = (1 << (RP_MSG_QBITS - 1)) - 1;
-    const int q0 = zero ? 0 : max(-lim - 1, min(lim, __float2int_rn(ldexpf(m0, -se))));
-    const int q1 = zero ? 0 : max(-lim - 1, min(lim, __float2int_rn(ldexpf(m1, -se))));
-    const int q2 = zero ? 0 : max(-lim - 1, min(lim, __float2int_rn(ldexpf(m2, -se))));
+    return max(-lim - 1, min(lim, __float2int_rn(ldexpf(m, -se))));
+}
+// what a number of such a chunk arrives as
+__device__ __forceinline__ float rp_msg_round(float m, float big) {
+    const int se = rp_msg_exp(big);
+    return big > 0.0f ? (float)rp_msg_q(m, se) * ldexpf(1.0f, se) : 0.0f;
+}
+__device__ __forceinline__ uint2 rp_msg_encode(float m0, float m1, float m2, float &v0, float &v1, float &v2) {
+    const float big = fmaxf(fabsf(m0), fmaxf(fabsf(m1), fabsf(m2)));
+    const int se = rp_msg_exp(big);
+    const bool zero = !(big > 0.0f);
+    const int q0 = zero ? 0 : rp_msg_q(m0, se), q1 = zero ? 0 : rp_msg_q(m1, se), q2 = zero ? 0 : rp_msg_q(m2, se);
     const float f = ldexpf(1.0f, se);
     v0 = (float)q0 * f;                                     // the values the integers stand for (exact products)
     v1 = (float)q1 * f;
@@ -400,7 +454,7 @@ __device__ __forceinline__ float rp_msg_decode_col(uint2 c, uint32_t col) {
 #define RP_HOP_DISCOVER 2
 #define RP_HOP_SORTED 3                 // a pull whose messages were listed by the out-edge walk and sorted by destination (reported only)
 __device__ __forceinline__ int rp_hop_mode(const DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio, int allow_disc) {
-    const unsigned long long m = ctr->m[l];
+    const unsigned long long m = ctr->set[l - 1].m;
     if (allow_disc && m > 0 && (mode == 3 || ((mode == 0 || mode == 4) && m * 8ull >= ctr->n_edges))) return RP_HOP_DISCOVER;
     if (mode == 1) return RP_HOP_PUSH;
     if (mode >= 2) return RP_HOP_PULL;

@@ -6,173 +6,10 @@
 // wavefronts regardless of degree skew.
 #include "common.h"
 #include "kernels.h"
+#include "walk.h"
 #include <cstring>
 
-#define MARK_CHUNK 256
 #define RP_STATIC_BLOCKS 16384u                  // entries of the static array (see below): blocks a compaction may have
-
-// mark the out-neighbours of every vertex of A_{l-1}. Every wavefront walks a contiguous run of
-// 256-edge chunks of the flattened out-edge space, so only its first chunk needs a search over the
-// whole list; the 64 rows after the chunk's first one are described in registers (one per lane:
-// where the row's edges start in the pool, and the first edge of the next row) and an edge finds its
-// row with shuffles. Nothing to do on a discovering hop (the in-row scan finds A_l).
-// Small frontiers (SparseArgs given): a marked vertex is entered into the hop's bitmap at once and the
-// first wavefront to do so appends it to the hop's list, so no scan of the whole bitmap is needed
-// afterwards; the list is then in no particular order.
-struct SparseArgs {
-    uint32_t *bm;                  // the hop's bitmap (zero on entry)
-    const uint32_t *alive;
-    uint32_t *list, *count;        // the hop's list and its length (zero on entry)
-    uint32_t *touched;             // += vertices first entered by an out-edge (statistics)
-    // roots merged in by the same kernel: sinks of changed edges, created vertices, the previous hop's set (self term)
-    const uint32_t *st_dst, *n_struct;
-    uint32_t struct_cap;
-    const uint32_t *list0, *count0, *bm_vadd;
-    int self_term;
-    // optional second list: vertices with more than long_min in-neighbours are appended there instead
-    const uint2 *in_meta;
-    uint32_t long_min;
-    uint32_t *long_list, *long_count;
-    int long_dup;                  // those vertices are appended to the hop's list as well
-};
-
-// T vertices per lane (0xFFFFFFFF: none): the T marks go out together and one reservation covers all of
-// them (two round trips instead of 2 T). To be called by all 64 lanes together.
-template <int T>
-__device__ __forceinline__ void sparse_enter_many(const SparseArgs &s, const uint32_t *v, bool from_edge) {
-    bool live[T], fresh[T], lng[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) live[t] = v[t] != 0xFFFFFFFFu && rp_bit(s.alive, v[t]);
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        fresh[t] = false;
-        if (live[t]) {
-            const uint32_t m = 1u << (v[t] & 31);
-            fresh[t] = !(atomicOr(&s.bm[v[t] >> 5], m) & m);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < T; ++t) lng[t] = fresh[t] && s.long_list && s.in_meta[v[t]].y > s.long_min;
-    unsigned long long mask[T], lmask[T];
-    uint32_t total = 0, ltotal = 0;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        mask[t] = __ballot(fresh[t] && (!lng[t] || s.long_dup));
-        lmask[t] = __ballot(lng[t]);
-        total += (uint32_t)__popcll(mask[t]);
-        ltotal += (uint32_t)__popcll(lmask[t]);
-    }
-    if (!(total + ltotal)) return;
-    const int lane = rp_lane();
-    uint32_t base = 0, lbase = 0;
-    if (lane == 0) {
-        if (total) base = atomicAdd(s.count, total);
-        if (ltotal) lbase = atomicAdd(s.long_count, ltotal);
-        if (from_edge && s.touched) atomicAdd(s.touched, total + ltotal);
-    }
-    base = __shfl(base, 0);
-    lbase = __shfl(lbase, 0);
-    const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        if (fresh[t] && (!lng[t] || s.long_dup)) s.list[base + (uint32_t)__popcll(mask[t] & below)] = v[t];
-        if (lng[t]) s.long_list[lbase + (uint32_t)__popcll(lmask[t] & below)] = v[t];
-        base += (uint32_t)__popcll(mask[t]);
-        lbase += (uint32_t)__popcll(lmask[t]);
-    }
-}
-
-// one vertex per valid lane; to be called by all 64 lanes together
-__device__ __forceinline__ void sparse_enter(const SparseArgs &s, uint32_t v, bool valid, bool from_edge) {
-    const uint32_t one[1] = {valid ? v : 0xFFFFFFFFu};
-    sparse_enter_many<1>(s, one, from_edge);
-}
-
-// EMIT: edge e of the flattened out-edge space is also written down as the pair (destination, source) in pk[e], pv[e]
-template <bool SPARSE, bool EMIT = false>
-__device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff,
-                                              const uint2 *out_meta, const uint32_t *out_pool, uint8_t *mk,
-                                              const SparseArgs &sp, uint32_t *pk = nullptr, uint32_t *pv = nullptr) {
-    const uint32_t count = *count_ptr;
-    if (count == 0) return;
-    constexpr int T = MARK_CHUNK / 64;
-    const int lane = rp_lane();
-    const uint32_t M = eoff[count];
-    // few out-edges: 64-edge chunks (only the first of a lane's T slots is used) so that more wavefronts share them
-    const uint32_t chunk = (SPARSE && M <= 16384u) ? 64u : (uint32_t)MARK_CHUNK;
-    const uint32_t n_chunks = (M + chunk - 1) / chunk;
-    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t per = (n_chunks + nw - 1) / nw;
-    const uint32_t c_begin = min(n_chunks, gw * per), c_end = min(n_chunks, c_begin + per);
-    if (c_begin >= c_end) return;
-    const uint32_t last = count - 1;
-    uint32_t i_lo = rp_seg_search_wave(eoff, 0, last, c_begin * chunk);
-    uint32_t rbase, bnd, rsrc = 0;                          // lane j: row i_lo + j
-    {
-        const uint32_t ri = min(last, i_lo + lane);
-        rsrc = list[ri];
-        rbase = out_meta[rsrc].x - eoff[ri];                // pool position of edge e: rbase + e (mod 2^32)
-        bnd = eoff[min(count, i_lo + 1 + lane)];
-    }
-    for (uint32_t c = c_begin; c < c_end; ++c) {
-        const uint32_t e0 = c * chunk, e1 = min(M, e0 + chunk);
-        const bool fits = __shfl(bnd, 63) > e1 - 1;         // every row of the chunk is among the 64 held
-        uint32_t v[T];
-        uint32_t i_nx;
-        if (fits) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const uint32_t e = e0 + lane + 64 * t;
-                const int r = (int)min(63u, rp_count_le(bnd, e));
-                const uint32_t base = __shfl(rbase, r);
-                v[t] = (e < e1) ? out_pool[base + e] : 0xFFFFFFFFu;
-                if (EMIT) {
-                    const uint32_t u = __shfl(rsrc, r);
-                    if (e < e1) {
-                        pk[e] = v[t];
-                        pv[e] = u;
-                    }
-                }
-            }
-            i_nx = min(last, i_lo + rp_count_le(bnd, e1));
-        } else {
-            const uint32_t i_hi = rp_seg_forward(eoff, i_lo, last, e1 - 1);
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const uint32_t e = e0 + lane + 64 * t;
-                v[t] = 0xFFFFFFFFu;
-                if (e < e1) {
-                    const uint32_t i = rp_seg_search(eoff, i_lo, i_hi, e);
-                    const uint32_t u = list[i];
-                    v[t] = out_pool[out_meta[u].x + (e - eoff[i])];
-                    if (EMIT) {
-                        pk[e] = v[t];
-                        pv[e] = u;
-                    }
-                }
-            }
-            i_nx = rp_seg_forward(eoff, i_hi, last, e1);
-        }
-        uint32_t rbase_n, bnd_n, rsrc_n;                    // next chunk's rows, requested before the marks
-        {
-            const uint32_t ri = min(last, i_nx + lane);
-            rsrc_n = list[ri];
-            rbase_n = out_meta[rsrc_n].x - eoff[ri];
-            bnd_n = eoff[min(count, i_nx + 1 + lane)];
-        }
-        if (SPARSE) {
-            sparse_enter_many<T>(sp, v, true);
-        } else {
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-                if (v[t] != 0xFFFFFFFFu) mk[v[t]] = 1;       // plain byte stores: idempotent, no atomics
-        }
-        i_lo = i_nx;
-        rbase = rbase_n;
-        bnd = bnd_n;
-        rsrc = rsrc_n;
-    }
-}
 
 // The walk that also lists the hop's messages as (destination, source) pairs for the sorted scatter: pair_cap entries
 // will be sorted, so the list is written only if the hop's out-edges fit, and the entries behind them get the key
@@ -184,12 +21,14 @@ __global__ __launch_bounds__(256) void k_frontier_mark_pairs(const uint32_t *lis
                                                              uint32_t *pk, uint32_t *pv, uint32_t pair_cap) {
     if (allow_disc && rp_hop_mode(ctr, l, d, mode, ratio, allow_disc) == RP_HOP_DISCOVER) return;
     const uint32_t count = *count_ptr;
-    const uint32_t M = count ? eoff[count] : 0u;
+    const uint32_t M = count ? count_ptr[1] : 0u;
     if (M == 0 || M > pair_cap) {
-        frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs());
+        frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
+                         (gridDim.x * blockDim.x) >> 6);
         return;
     }
-    frontier_walk<false, true>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), pk, pv);
+    frontier_walk<false, true>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
+                               (gridDim.x * blockDim.x) >> 6, pk, pv);
     for (uint32_t i = M + blockIdx.x * blockDim.x + threadIdx.x; i < pair_cap; i += gridDim.x * blockDim.x) pk[i] = 0xFFFFFFFFu;
 }
 
@@ -198,31 +37,17 @@ __global__ __launch_bounds__(256) void k_frontier_mark(const uint32_t *list, con
                                                        const uint32_t *out_pool, uint8_t *mk, const DevCtr *ctr,
                                                        uint32_t l, uint32_t d, int mode, int ratio, int allow_disc) {
     if (allow_disc && rp_hop_mode(ctr, l, d, mode, ratio, allow_disc) == RP_HOP_DISCOVER) return;
-    frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs());
+    frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
+                         (gridDim.x * blockDim.x) >> 6);
 }
 
 // the out-edge walk and the roots in one kernel, straight into the hop's bitmap and (unordered) list
 __global__ __launch_bounds__(256) void k_frontier_sparse(const uint32_t *list, const uint32_t *count_ptr,
                                                          const uint32_t *eoff, const uint2 *out_meta,
                                                          const uint32_t *out_pool, SparseArgs sp) {
-    frontier_walk<true>(list, count_ptr, eoff, out_meta, out_pool, nullptr, sp);
-    const int lane = rp_lane();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t n_s = min(*sp.n_struct, sp.struct_cap), n_0 = *sp.count0, n_p = sp.self_term ? *count_ptr : 0u;
-    const uint32_t total = n_s + n_0 + n_p;
-    for (uint32_t base = gw * 64; base < total; base += nw * 64) {
-        const uint32_t i = base + lane;
-        uint32_t v = 0;
-        bool valid = i < total;
-        if (valid) {
-            if (i < n_s) v = sp.st_dst[i];
-            else if (i < n_s + n_0) {
-                v = sp.list0[i - n_s];
-                valid = rp_bit(sp.bm_vadd, v);
-            } else v = list[i - n_s - n_0];
-        }
-        sparse_enter(sp, v, valid, false);
-    }
+    frontier_walk<true>(list, count_ptr, eoff, out_meta, out_pool, nullptr, sp, gw, nw);
+    enter_roots(list, count_ptr, sp, gw, nw);
 }
 
 struct CompactArgs {
@@ -241,6 +66,7 @@ struct CompactArgs {
     uint32_t *list, *eoff, *ioff;  // outputs
     uint32_t *count_out, *msgs_out, *isum_out;
     uint32_t list_cap;             // entries the list has room for (positions beyond are counted, not written)
+    HostFlag done;                 // k_bitmap_ids only
 };
 
 // Compaction of a bitmap into its ascending list. A wavefront takes two bitmap words at a time, a lane being a vertex:
@@ -485,6 +311,7 @@ __global__ __launch_bounds__(256) void k_bitmap_ids(CompactArgs a) {
     for (int s = 0; s < S; ++s) r.o[s] = r.i[s] = 0u;
     r.emit(a, w0, lane, oc, 0u, 0u);
     if (blockIdx.x == gridDim.x - 1 && tid == 255) *a.count_out = oc + r.cnt;
+    report_done(a.done, gridDim.x);
 }
 
 // Words per block: 32 up to half a million vertices (several blocks per compute unit where the graph allows it), 64 above,
@@ -588,11 +415,11 @@ __global__ __launch_bounds__(1024) void k_list_eoff(const uint32_t *list, const 
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     if (pair_cap) {
         hipLaunchKernelGGL(k_frontier_mark_pairs, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1],
-                           &c->ctr->a[l - 1], c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l],
+                           &c->ctr->set[l - 1].a, c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l],
                            rp_layer_mode(c, l), c->opt_pull_ratio, allow_disc ? 1 : 0, c->pk_a, c->pv_a, pair_cap);
         return;
     }
-    hipLaunchKernelGGL(k_frontier_mark, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->a[l - 1],
+    hipLaunchKernelGGL(k_frontier_mark, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,
                        c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], rp_layer_mode(c, l),
                        c->opt_pull_ratio, allow_disc ? 1 : 0);
 }
@@ -618,8 +445,8 @@ void rp_launch_alive_list(ripple_ctx *c) {
     launch_compact(c, a);
 }
 
-// bitmap of layer l, merged with S, V_added (and A_{l-1} when self_term) -> list[l], ctr->a[l];
-// want_out: eoff[l] and ctr->m[l+1] (the next hop's edge walk); want_in: ioff[l], ctr->isum[l]
+// bitmap of layer l, merged with S, V_added (and A_{l-1} when self_term) -> list[l], ctr->set[l].a;
+// want_out: eoff[l] and ctr->set[l].m (the next hop's edge walk); want_in: ioff[l], ctr->isum[l]
 // pruned: bm[l] already is the hop's final set (max / min layers: candidates whose aggregate did not
 // change have been taken out again), so neither marks nor S are merged into it
 void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool want_out, bool want_in,
@@ -639,13 +466,14 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
     a.part_cnt = c->part_cnt;
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
+    a.done.flag = nullptr;
     a.rep = accumulate_rep ? c->rep[l] : nullptr;
     a.touched_out = pruned ? nullptr : &c->ctr->touched[l];
     a.list = c->list[l];
     a.eoff = c->eoff[l];
     a.ioff = c->ioff[l];
-    a.count_out = &c->ctr->a[l];
-    a.msgs_out = (l < RIPPLE_MAX_LAYERS) ? &c->ctr->m[l + 1] : nullptr;
+    a.count_out = &c->ctr->set[l].a;
+    a.msgs_out = &c->ctr->set[l].m;
     a.isum_out = &c->ctr->isum[l];
     a.list_cap = 0xFFFFFFFFu;
     launch_compact(c, a);
@@ -675,13 +503,20 @@ void rp_launch_candidates(ripple_ctx *c, uint32_t l) {
     launch_compact(c, a);
 }
 
-static void bitmap_ids(ripple_ctx *c, CompactArgs &a) {
-    if (a.n_words <= RANK_WORDS) hipLaunchKernelGGL(k_bitmap_ids, dim3(rp_div_up(a.n_words, 32)), dim3(256), 0, c->stream, a);
-    else launch_compact(c, a);
+static void bitmap_ids(ripple_ctx *c, CompactArgs &a, bool report) {
+    a.done.flag = nullptr;
+    const uint32_t nb = rp_div_up(a.n_words, 32);
+    if (a.n_words <= RANK_WORDS) {
+        if (report && nb <= REPORT_WGS) a.done = rp_host_flag(c);
+        hipLaunchKernelGGL(k_bitmap_ids, dim3(nb), dim3(256), 0, c->stream, a);
+    } else {
+        launch_compact(c, a);
+    }
+    if (report && !a.done.flag) rp_launch_report(c);
 }
 
 // any bitmap & alive -> ascending list in `out_list` (room for cap), count in *count_d (both device memory, or pinned host memory)
-void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t cap, uint32_t *count_d) {
+void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t cap, uint32_t *count_d, bool report) {
     CompactArgs a;
     memset(&a, 0, sizeof(a));
     a.list_cap = cap;
@@ -695,7 +530,7 @@ void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_lis
     a.part_in = c->part_ideg;
     a.list = out_list;
     a.count_out = count_d;
-    bitmap_ids(c, a);
+    bitmap_ids(c, a, report);
 }
 
 // ---------------------------------------------------------------------------------
@@ -747,19 +582,17 @@ ripple_status rp_launch_affected_static(ripple_ctx *c, uint32_t *bitmap, uint32_
     a.list = ids_out;
     a.list_cap = cap;
     a.count_out = n_out;
-    bitmap_ids(c, a);
-    RP_HIP(c, hipGetLastError());
-    RP_HIP(c, hipStreamSynchronize(c->stream));
-    return RIPPLE_OK;
+    bitmap_ids(c, a, true);
+    return rp_wait_flag(c);
 }
 
 void rp_launch_list_eoff(ripple_ctx *c, uint32_t l) {
-    hipLaunchKernelGGL(k_list_eoff, dim3(1), dim3(1024), 0, c->stream, c->list[l], &c->ctr->a[l], c->out_meta,
-                       c->eoff[l], l < RIPPLE_MAX_LAYERS ? &c->ctr->m[l + 1] : (uint32_t *)nullptr,
+    hipLaunchKernelGGL(k_list_eoff, dim3(1), dim3(1024), 0, c->stream, c->list[l], &c->ctr->set[l].a, c->out_meta,
+                       c->eoff[l], &c->ctr->set[l].m,
                        (const uint2 *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
 }
 
-static SparseArgs sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_t *count, bool self_term) {
+SparseArgs rp_sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_t *count, bool self_term) {
     SparseArgs sp;
     sp.bm = c->bm[l];
     sp.alive = c->alive;
@@ -770,7 +603,7 @@ static SparseArgs sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_
     sp.n_struct = &c->ctr->n_struct;
     sp.struct_cap = c->struct_cap;
     sp.list0 = c->list[0];
-    sp.count0 = &c->ctr->a[0];
+    sp.count0 = &c->ctr->set[0].a;
     sp.bm_vadd = c->bm_vadd;
     sp.self_term = self_term ? 1 : 0;
     sp.in_meta = c->in_meta;
@@ -778,6 +611,9 @@ static SparseArgs sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_
     sp.long_list = nullptr;
     sp.long_count = nullptr;
     sp.long_dup = 0;
+    sp.eoff = nullptr;
+    sp.out_meta = c->out_meta;
+    sp.isum = &c->ctr->isum[l];
     return sp;
 }
 
@@ -785,11 +621,11 @@ static SparseArgs sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_
 // (with A_{l-1} when the layer has a self term) in bm[l] and, unordered, in c->all_list, count in
 // ctr->cand[l] (zero since the batch began).
 void rp_launch_candidates_sparse(ripple_ctx *c, uint32_t l, bool self_term, uint32_t long_min) {
-    SparseArgs sp = sparse_args(c, l, c->all_list, &c->ctr->cand[l], self_term);
+    SparseArgs sp = rp_sparse_args(c, l, c->all_list, &c->ctr->cand[l], self_term);
     sp.long_min = long_min;                              // candidates with longer in-rows: straight into the queue of the
     sp.long_list = c->eoff[l];                           // workgroup role (free until the hop's set is final), count in
     sp.long_count = &c->ctr->n_long[l];                  // ctr->n_long[l] (zero since the batch began)
-    hipLaunchKernelGGL(k_frontier_sparse, dim3(c->n_cu), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->a[l - 1],
+    hipLaunchKernelGGL(k_frontier_sparse, dim3(c->n_cu), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,
                        c->eoff[l - 1], c->out_meta, c->out_pool, sp);
 }
 
@@ -799,22 +635,22 @@ void rp_launch_candidates_sparse(ripple_ctx *c, uint32_t l, bool self_term, uint
 // long_min > 0 (attention hops): vertices with more in-neighbours than that are also queued in c->all_list
 // (count in ctr->n_long[l], zero since the batch began) for the workgroup role of the aggregation kernel.
 void rp_launch_frontier_sparse(ripple_ctx *c, uint32_t l, bool self_term, bool want_out, uint32_t long_min) {
-    SparseArgs sp = sparse_args(c, l, c->list[l], &c->ctr->a[l], self_term);
+    SparseArgs sp = rp_sparse_args(c, l, c->list[l], &c->ctr->set[l].a, self_term);
     if (long_min) {
         sp.long_min = long_min;
         sp.long_list = c->all_list;
         sp.long_count = &c->ctr->n_long[l];
         sp.long_dup = 1;
     }
-    hipLaunchKernelGGL(k_frontier_sparse, dim3(c->n_cu), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->a[l - 1],
+    hipLaunchKernelGGL(k_frontier_sparse, dim3(c->n_cu), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,
                        c->eoff[l - 1], c->out_meta, c->out_pool, sp);
     rp_launch_list_offsets(c, l, want_out);
 }
 
 // degree prefixes over the (unordered) list of hop l
 void rp_launch_list_offsets(ripple_ctx *c, uint32_t l, bool want_out) {
-    hipLaunchKernelGGL(k_list_eoff, dim3(1), dim3(1024), 0, c->stream, c->list[l], &c->ctr->a[l], c->out_meta,
+    hipLaunchKernelGGL(k_list_eoff, dim3(1), dim3(1024), 0, c->stream, c->list[l], &c->ctr->set[l].a, c->out_meta,
                        want_out ? c->eoff[l] : (uint32_t *)nullptr,
-                       (want_out && l < RIPPLE_MAX_LAYERS) ? &c->ctr->m[l + 1] : (uint32_t *)nullptr, c->in_meta, c->ioff[l],
+                       want_out ? &c->ctr->set[l].m : (uint32_t *)nullptr, c->in_meta, c->ioff[l],
                        &c->ctr->isum[l]);
 }

@@ -308,7 +308,6 @@ struct MutArgs {
     const float *payload;
     uint32_t *status, *pos_out, *pos_in;
     uint32_t *op_touch;                          // bit 0 accepted edge op, 1 it is an add, 2 / 3 first touch of out-row(u) / in-row(v)
-    int defer_touch;                             // large batches: touched-row lists and counts come from k_touch_lists
     uint2 *out_meta, *in_meta;
     uint32_t *out_capv, *in_capv;
     uint32_t *out_pool, *in_pool;
@@ -383,82 +382,74 @@ __global__ void k_vertex_validate(MutArgs a) {
     a.status[i] = st;
 }
 
+// Is the edge operation valid; where are its entries. To be called by the whole wavefront.
+__device__ __forceinline__ uint32_t check_edge(const MutArgs &a, const ripple_update &op, int &po, int &pi) {
+    const uint32_t u = op.u, v = op.v;
+    const uint2 mo = a.out_meta[u], mi = a.in_meta[v];
+    po = pi = -1;
+    if (op.kind == RIPPLE_EDGE_ADD) {
+        const int p = (mo.y <= mi.y) ? rp_wave_find(a.out_pool + mo.x, mo.y, v) : rp_wave_find(a.in_pool + mi.x, mi.y, u);
+        return p < 0 ? 1u : 0u;
+    }
+    po = rp_wave_find(a.out_pool + mo.x, mo.y, v);
+    if (po < 0) return 0u;
+    pi = rp_wave_find(a.in_pool + mi.x, mi.y, u);
+    if (pi >= 0) return 1u;
+    if (rp_lane() == 0) a.ctr->error = 3;                          // the two adjacencies disagree
+    return 0u;
+}
+// An accepted edge operation's per-row counts and first touches: bit 0 accepted, 1 add, 2 / 3 first touch of out-row(u) /
+// in-row(v). One lane.
+__device__ __forceinline__ uint32_t count_edge(const MutArgs &a, const ripple_update &op, uint32_t i, int po, int pi) {
+    const bool is_add = op.kind == RIPPLE_EDGE_ADD;
+    if (is_add) {
+        atomicAdd(&a.pend_out[op.u], 1u);
+        atomicAdd(&a.pend_in[op.v], 1u);
+    } else {
+        a.pos_out[i] = (uint32_t)po;
+        a.pos_in[i] = (uint32_t)pi;
+        atomicAdd(&a.dead_out[op.u], 1u);
+        atomicAdd(&a.dead_in[op.v], 1u);
+    }
+    uint32_t flags = 1u | (is_add ? 2u : 0u);
+    if (!(atomicOr(&a.vstate[op.u], VS_TOUCH_OUT) & VS_TOUCH_OUT)) flags |= 4u;
+    if (!(atomicOr(&a.vstate[op.v], VS_TOUCH_IN) & VS_TOUCH_IN)) flags |= 8u;
+    return flags;
+}
+// EDGE_REWEIGHT: the edge must exist; nothing about the rows' shape changes
+__device__ __forceinline__ int find_weight(const MutArgs &a, const ripple_update &op) {
+    if (!a.in_w || !rp_bit(a.alive, op.u) || !rp_bit(a.alive, op.v)) return -1;
+    const uint2 mi = a.in_meta[op.v];
+    return rp_wave_find(a.in_pool + mi.x, mi.y, op.u);
+}
+
 __global__ __launch_bounds__(256) void k_edge_validate(MutArgs a) {
     const int lane = rp_lane();
     uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t i = gw; i < a.n_ops; i += nw) {
         ripple_update op = a.ops[i];
+        uint32_t st = 0, flags = 0;
         if (op.kind == RIPPLE_FEAT_UPDATE) {               // needs the live flag only
-            if (lane == 0) {
-                a.status[i] = rp_bit(a.alive, op.u) ? 1u : 0u;
-                if (a.defer_touch) a.op_touch[i] = 0;
-            }
+            st = rp_bit(a.alive, op.u) ? 1u : 0u;
+        } else if (op.kind == RIPPLE_EDGE_REWEIGHT) {
+            const int p = find_weight(a, op);
+            st = p >= 0 ? 1u : 0u;
+            if (lane == 0 && st) a.pos_in[i] = (uint32_t)p;
+        } else if (op.kind == RIPPLE_EDGE_ADD || op.kind == RIPPLE_EDGE_DEL) {
+            const bool ok = (rp_bit(a.alive, op.u) || (a.vstate[op.u] & VS_ADDING)) &&
+                            (rp_bit(a.alive, op.v) || (a.vstate[op.v] & VS_ADDING));
+            int po = -1, pi = -1;
+            if (ok) st = check_edge(a, op, po, pi);
+            // thousands of wavefronts bumping the same few counters would queue up behind one
+            // another: only the per-row bits are set here, k_touch_lists builds lists and counts
+            if (lane == 0 && st) flags = count_edge(a, op, i, po, pi);
+        } else {                                           // vertex operations: k_vertex_validate
+            if (lane == 0) a.op_touch[i] = 0;
             continue;
-        }
-        if (op.kind == RIPPLE_EDGE_REWEIGHT) {             // the edge must exist; nothing about the rows' shape changes
-            int p = -1;
-            if (a.in_w && rp_bit(a.alive, op.u) && rp_bit(a.alive, op.v)) {
-                const uint2 mi = a.in_meta[op.v];
-                p = rp_wave_find(a.in_pool + mi.x, mi.y, op.u);
-            }
-            if (lane == 0) {
-                a.status[i] = p >= 0 ? 1u : 0u;
-                if (p >= 0) a.pos_in[i] = (uint32_t)p;
-                if (a.defer_touch) a.op_touch[i] = 0;
-            }
-            continue;
-        }
-        if (op.kind != RIPPLE_EDGE_ADD && op.kind != RIPPLE_EDGE_DEL) {
-            if (lane == 0 && a.defer_touch) a.op_touch[i] = 0;
-            continue;
-        }
-        uint32_t u = op.u, v = op.v;
-        bool ok = (rp_bit(a.alive, u) || (a.vstate[u] & VS_ADDING)) &&
-                  (rp_bit(a.alive, v) || (a.vstate[v] & VS_ADDING));
-        uint32_t st = 0;
-        int po = -1, pi = -1;
-        if (ok) {
-            uint2 mo = a.out_meta[u], mi = a.in_meta[v];
-            if (op.kind == RIPPLE_EDGE_ADD) {
-                int p = (mo.y <= mi.y) ? rp_wave_find(a.out_pool + mo.x, mo.y, v)
-                                       : rp_wave_find(a.in_pool + mi.x, mi.y, u);
-                st = (p < 0) ? 1u : 0u;
-            } else {
-                po = rp_wave_find(a.out_pool + mo.x, mo.y, v);
-                if (po >= 0) {
-                    pi = rp_wave_find(a.in_pool + mi.x, mi.y, u);
-                    if (pi >= 0) st = 1;
-                    else if (lane == 0) a.ctr->error = 3;     // the two adjacencies disagree
-                }
-            }
         }
         if (lane == 0) {
             a.status[i] = st;
-            uint32_t flags = 0;
-            if (st) {
-                const bool is_add = op.kind == RIPPLE_EDGE_ADD;
-                if (is_add) {
-                    atomicAdd(&a.pend_out[u], 1u);
-                    atomicAdd(&a.pend_in[v], 1u);
-                } else {
-                    a.pos_out[i] = (uint32_t)po;
-                    a.pos_in[i] = (uint32_t)pi;
-                    atomicAdd(&a.dead_out[u], 1u);
-                    atomicAdd(&a.dead_in[v], 1u);
-                }
-                if (a.defer_touch) {
-                    // thousands of wavefronts bumping the same few counters would queue up behind one
-                    // another: only the per-row bits are set here, k_touch_lists builds lists and counts
-                    flags = 1u | (is_add ? 2u : 0u);
-                    if (!(atomicOr(&a.vstate[u], VS_TOUCH_OUT) & VS_TOUCH_OUT)) flags |= 4u;
-                    if (!(atomicOr(&a.vstate[v], VS_TOUCH_IN) & VS_TOUCH_IN)) flags |= 8u;
-                } else {
-                    atomicAdd(is_add ? &a.ctr->n_add : &a.ctr->n_del, 1u);
-                    touch_row(a, u, VS_TOUCH_OUT);
-                    touch_row(a, v, VS_TOUCH_IN);
-                }
-            }
-            if (a.defer_touch) a.op_touch[i] = flags;
+            a.op_touch[i] = flags;
         }
     }
 }
@@ -523,31 +514,17 @@ __global__ __launch_bounds__(1024) void k_touch_lists(MutArgs a) {
     }
 }
 
-// How much pool space relocation will take, then (by the last workgroup to finish) the decision
-// whether the batch may be committed at all.
-__global__ void k_capacity(MutArgs a) {
-    uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t no = min(a.ctr->n_touch_out, a.touch_cap), ni = min(a.ctr->n_touch_in, a.touch_cap);
-    if (j < no) {
-        uint32_t x = a.touch_out[j], pend = a.pend_out[x];
-        uint32_t need = a.out_meta[x].y - a.dead_out[x] + pend;
-        if (pend && need > a.out_capv[x]) atomicAdd(&a.ctr->need_out, rp_row_cap(need));
-    } else if (j < no + ni) {
-        uint32_t x = a.touch_in[j - no], pend = a.pend_in[x];
-        uint32_t need = a.in_meta[x].y - a.dead_in[x] + pend;
-        if (pend && need > a.in_capv[x]) atomicAdd(&a.ctr->need_in, rp_row_cap(need));
-    }
-    __shared__ bool last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        last = atomicAdd(&a.ctr->blocks_done, 1u) == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (!last || threadIdx.x != 0) return;
-    __threadfence();
-    DevCtr *c = a.ctr;
-    const uint32_t need_out = atomicAdd(&c->need_out, 0u), need_in = atomicAdd(&c->need_in, 0u);
+// pool entries that relocating touched row j (out-rows first, `no` of them) takes
+__device__ __forceinline__ uint32_t row_need(const MutArgs &a, uint32_t j, uint32_t no) {
+    const bool out = j < no;
+    const uint32_t x = out ? a.touch_out[j] : a.touch_in[j - no];
+    const uint32_t pend = out ? a.pend_out[x] : a.pend_in[x];
+    const uint32_t need = out ? a.out_meta[x].y - a.dead_out[x] + pend : a.in_meta[x].y - a.dead_in[x] + pend;
+    return (pend && need > (out ? a.out_capv[x] : a.in_capv[x])) ? rp_row_cap(need) : 0u;
+}
+// whether the batch may be committed at all
+__device__ __forceinline__ uint32_t decide(const MutArgs &a, uint32_t need_out, uint32_t need_in) {
+    const DevCtr *c = a.ctr;
     uint32_t flag = 0;
     if ((unsigned long long)c->out_top + need_out > a.pool_cap || (unsigned long long)c->in_top + need_in > a.pool_cap)
         flag |= 1u;
@@ -556,8 +533,20 @@ __global__ void k_capacity(MutArgs a) {
         (unsigned long long)c->n_add + c->n_del + c->need_exp > a.touch_cap)
         flag |= 4u;
     if (c->error) flag |= 8u;
-    c->abort_flag = flag;
-    c->blocks_done = 0;
+    return flag;
+}
+
+// How much pool space relocation will take, then (by the last workgroup to finish) the decision
+// whether the batch may be committed at all.
+__global__ void k_capacity(MutArgs a) {
+    uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+    uint32_t no = min(a.ctr->n_touch_out, a.touch_cap), ni = min(a.ctr->n_touch_in, a.touch_cap);
+    if (j < no + ni) {
+        const uint32_t need = row_need(a, j, no);
+        if (need) atomicAdd(j < no ? &a.ctr->need_out : &a.ctr->need_in, need);
+    }
+    if (!last_workgroup(a.ctr, gridDim.x) || threadIdx.x != 0) return;
+    a.ctr->abort_flag = decide(a, atomicAdd(&a.ctr->need_out, 0u), atomicAdd(&a.ctr->need_in, 0u));
 }
 
 // slot in a global list for every lane with pred, one atomic per wavefront
@@ -665,8 +654,7 @@ __global__ __launch_bounds__(256) void k_expand_apply(MutArgs a) {
 }
 
 // tombstone deleted edges, list every changed edge as a structural term, count results
-__global__ __launch_bounds__(256) void k_apply_edges(MutArgs a) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void apply_edge(const MutArgs &a, uint32_t i) {
     bool in_range = i < a.n_ops;
     bool aborted = a.ctr->abort_flag != 0;
     ripple_update op = in_range ? a.ops[i] : ripple_update{99u, 0u, 0u, 0u};
@@ -711,12 +699,13 @@ __global__ __launch_bounds__(256) void k_apply_edges(MutArgs a) {
     }
     rp_set_bit(a.bm_sink, op.v);
 }
+__global__ __launch_bounds__(256) void k_apply_edges(MutArgs a) { apply_edge(a, blockIdx.x * blockDim.x + threadIdx.x); }
+
 
 // feature writes (with the hop-0 delta), vertex creation, vertex removal
-__global__ __launch_bounds__(256) void k_apply_vertices(MutArgs a) {
+__device__ __forceinline__ void apply_vertices(const MutArgs &a, uint32_t gw, uint32_t nw) {
     if (a.ctr->abort_flag) return;
     const int lane = rp_lane();
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t d0 = a.d[0];
     for (uint32_t i = gw; i < a.n_ops; i += nw) {
         ripple_update op = a.ops[i];
@@ -724,7 +713,7 @@ __global__ __launch_bounds__(256) void k_apply_vertices(MutArgs a) {
         uint32_t w = op.u;
         if (op.kind == RIPPLE_FEAT_UPDATE || op.kind == RIPPLE_VERTEX_ADD) {
             uint32_t slot = 0;
-            if (lane == 0) slot = atomicAdd(&a.ctr->a[0], 1u);
+            if (lane == 0) slot = atomicAdd(&a.ctr->set[0].a, 1u);
             slot = __shfl(slot, 0);
             const float *row = a.payload + (size_t)op.feat_row * d0;
             for (uint32_t c = lane; c < d0; c += 64) {
@@ -778,13 +767,16 @@ __global__ __launch_bounds__(256) void k_apply_vertices(MutArgs a) {
         }
     }
 }
+__global__ __launch_bounds__(256) void k_apply_vertices(MutArgs a) {
+    apply_vertices(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+}
+
 
 // one wavefront per touched row: squeeze tombstones out, move the row if the
 // pending appends do not fit, reset the row's scratch counters
-__global__ __launch_bounds__(256) void k_cleanup_rows(MutArgs a) {
+__device__ __forceinline__ void cleanup_rows(const MutArgs &a, uint32_t gw, uint32_t nw) {
     const int lane = rp_lane();
     const bool aborted = a.ctr->abort_flag != 0;
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     uint32_t no = min(a.ctr->n_touch_out, a.touch_cap), ni = min(a.ctr->n_touch_in, a.touch_cap);
     for (uint32_t j = gw; j < no + ni; j += nw) {
         const bool is_out = j < no;
@@ -891,6 +883,21 @@ __global__ __launch_bounds__(256) void k_cleanup_rows(MutArgs a) {
         }
     }
 }
+__global__ __launch_bounds__(256) void k_cleanup_rows(MutArgs a) {
+    cleanup_rows(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+}
+
+
+__device__ __forceinline__ void append_edge(const MutArgs &a, const ripple_update &op) {
+    uint32_t p = atomicAdd(&((uint32_t *)a.out_meta)[2 * (size_t)op.u + 1], 1u);
+    if (p < a.out_capv[op.u]) a.out_pool[a.out_meta[op.u].x + p] = op.v;
+    else a.ctr->error = 7;
+    p = atomicAdd(&((uint32_t *)a.in_meta)[2 * (size_t)op.v + 1], 1u);
+    if (p < a.in_capv[op.v]) {
+        a.in_pool[a.in_meta[op.v].x + p] = op.u;
+        if (a.in_w) a.in_w[a.in_meta[op.v].x + p] = __uint_as_float(op.feat_row);
+    } else a.ctr->error = 7;
+}
 
 __global__ void k_apply_adds(MutArgs a) {
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -906,14 +913,7 @@ __global__ void k_apply_adds(MutArgs a) {
         return;
     }
     if (aborted || op.kind != RIPPLE_EDGE_ADD || !a.status[i]) return;
-    uint32_t p = atomicAdd(&((uint32_t *)a.out_meta)[2 * (size_t)op.u + 1], 1u);
-    if (p < a.out_capv[op.u]) a.out_pool[a.out_meta[op.u].x + p] = op.v;
-    else a.ctr->error = 7;
-    p = atomicAdd(&((uint32_t *)a.in_meta)[2 * (size_t)op.v + 1], 1u);
-    if (p < a.in_capv[op.v]) {
-        a.in_pool[a.in_meta[op.v].x + p] = op.u;
-        if (a.in_w) a.in_w[a.in_meta[op.v].x + p] = __uint_as_float(op.feat_row);
-    } else a.ctr->error = 7;
+    append_edge(a, op);
 }
 
 // Deterministic mode. The entries appended above land in the order their atomics were served. A sum that
@@ -1000,6 +1000,14 @@ __global__ __launch_bounds__(1024) void k_sort_long_tails(MutArgs a) {
     }
 }
 
+__device__ __forceinline__ void struct_term(const MutArgs &a, uint32_t u, uint32_t v, uint32_t l, float sg, int lane) {
+    const uint32_t w = a.T[l] ? a.xw[l] : a.d[l - 1];
+    for (uint32_t c = lane; c < w; c += 64) {
+        const float val = a.T[l] ? a.T[l][(size_t)u * w + c] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + c);
+        if (val != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * w + c], sg * val);
+    }
+}
+
 // X^l[v] += sign * H^{l-1}[u] for every changed edge and every layer, taken
 // while all H still hold their pre-batch values (Sec. 3.3.3: an added edge
 // uses 0 as the source's old embedding, a deleted edge 0 as its new one).
@@ -1018,19 +1026,7 @@ __global__ __launch_bounds__(256) void k_struct_scatter(MutArgs a) {
         uint32_t u = a.st_src[e], v = a.st_dst[e];
         const float sg = ((a.wsum_mask >> l) & 1u) ? a.st_sign[e] : a.st_unit[e];
         if (sg == 0.0f) continue;                            // a new weight means nothing to a layer that ignores weights
-        if (a.T[l] == nullptr) {
-            const uint32_t dp = a.d[l - 1];
-            for (uint32_t c = lane; c < dp; c += 64) {
-                float val = rp_load_h(a.H[l - 1], a.store, (size_t)u * dp + c);
-                if (val != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * dp + c], sg * val);
-            }
-        } else {
-            const uint32_t dn = a.xw[l];
-            for (uint32_t c = lane; c < dn; c += 64) {
-                const float val = a.T[l][(size_t)u * dn + c];
-                if (val != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * dn + c], sg * val);
-            }
-        }
+        struct_term(a, u, v, l, sg, lane);
     }
 }
 
@@ -1093,34 +1089,226 @@ __global__ __launch_bounds__(256) void k_struct_ordered(MutArgs a) {
     }
 }
 
-__global__ void k_batch_reset(DevCtr *ctr, uint32_t *bitmaps, size_t n_bitmap_words) {
+// operations from pinned host memory
+__device__ __forceinline__ void stage_ops(const ripple_update *src, ripple_update *dst, uint32_t n) {
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) dst[i] = src[i];
+}
+
+__global__ void k_batch_reset(DevCtr *ctr, uint32_t *bitmaps, size_t n_bitmap_words, const ripple_update *src,
+                              ripple_update *dst, uint32_t n_ops) {
     size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_bitmap_words; i += stride) bitmaps[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        for (int l = 0; l <= RIPPLE_MAX_LAYERS; ++l) {
-            ctr->a[l] = 0;
-            ctr->m[l] = 0;
-            ctr->touched[l] = 0;
-            ctr->isum[l] = 0;
-            ctr->n_long[l] = 0;
-            ctr->cand[l] = 0;
-            ctr->n_big[l] = 0;
-            ctr->n_seg[l] = 0;
-            ctr->hop_mode[l] = 0;
-            ctr->pull_next[l] = 0;
+    if (blockIdx.x == 0)
+        for (uint32_t k = RP_CTR_BATCH + threadIdx.x; k < RP_CTR_WORDS; k += blockDim.x) ((uint32_t *)ctr)[k] = 0;
+    stage_ops(src, dst, n_ops);
+}
+
+// Hands the batch's counters to the host (pinned memory), clears those that a batch starts from zero and then says so: the
+// host sees the number of this call in `flag`. One launch in place of a copy and the wait for a stream.
+__global__ __launch_bounds__(256) void k_publish(DevCtr *ctr, DevCtr *host, HostFlag done) {
+    for (uint32_t k = threadIdx.x; k < RP_CTR_WORDS; k += blockDim.x) {
+        ((volatile uint32_t *)host)[k] = ((uint32_t *)ctr)[k];
+        if (k >= RP_CTR_BATCH) ((uint32_t *)ctr)[k] = 0;
+    }
+    report_done(done, 1u);
+}
+
+// reports the end of the launches before it: for launches of more workgroups than should report by themselves
+__global__ void k_report(HostFlag done) { report_done(done, 1u); }
+void rp_launch_report(ripple_ctx *c) { hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, c->stream, rp_host_flag(c)); }
+
+void rp_launch_publish(ripple_ctx *c) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, c->stream, c->ctr, c->ctr_host, rp_host_flag(c));
+    c->ctr_dirty = false;
+}
+
+// ---------------------------------------------------------------------------------
+// the Apply step of a small piece in three launches
+// ---------------------------------------------------------------------------------
+// A piece of up to SMALL_OPS operations without vertex deletions is paced by launches and chains of dependent reads, not by
+// bytes: its eleven launches (two copies, reset, validate, capacity, edges, structural terms, vertices, rows, adds, degree
+// prefix) are three here. Steps that only a finished predecessor separates are done by the last workgroup to finish
+// (capacity after validation; appends and the degree prefix after the rows are cleaned up), independent ones by different
+// workgroups of one launch (bitmaps cleared beside the validation; structural terms beside the tombstones; feature rows
+// beside the rows' cleanup). The operations are read from pinned host memory by the first kernel, feature rows by the third.
+#define SMALL_OPS 512u
+
+// Where `target` is in the row, searched by wavefronts `part` .. of `parts` that take blocks of 1,024 entries in turn; -1 if this
+// wavefront does not find it. A hub's row of ten thousand entries takes one wavefront ten rounds.
+__device__ __forceinline__ int find_part(const uint32_t *row, uint32_t len, uint32_t target, uint32_t part, uint32_t parts) {
+    for (uint32_t base = part * 1024u; base < len; base += parts * 1024u) {
+        const int p = rp_wave_find_blocks<16>(row, base, len, target);
+        if (p >= 0) return p;
+    }
+    return -1;
+}
+
+// The first nb workgroups validate an operation at a time (its rows searched by four wavefronts); the others clear the bitmaps.
+// The last of the former makes the lists of touched rows and decides. (nb is bounded: every workgroup that arrives there
+// costs about 60 ns, one after the other.)
+#define SMALL_WGS 128u
+__global__ __launch_bounds__(256) void k_small_validate(MutArgs a, const ripple_update *src, ripple_update *dst, uint32_t nb,
+                                                        uint32_t *bitmaps, uint32_t n_bitmap_words) {
+    __shared__ int s_po, s_pi;
+    __shared__ uint32_t s_need[2], s_o[4], s_i[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blockIdx.x >= nb) {
+        const uint32_t stride = (gridDim.x - nb) * 256u;
+        for (uint32_t k = (blockIdx.x - nb) * 256u + tid; k < n_bitmap_words; k += stride) bitmaps[k] = 0;
+        return;
+    }
+    for (uint32_t i = blockIdx.x; i < a.n_ops; i += nb) {
+    const ripple_update op = src[i];
+    const bool is_add = op.kind == RIPPLE_EDGE_ADD, is_edge = is_add || op.kind == RIPPLE_EDGE_DEL;
+    if (tid == 0) {
+        s_po = s_pi = -1;
+        dst[i] = op;
+    }
+    __syncthreads();
+    uint32_t st = 0;
+    if (op.kind == RIPPLE_FEAT_UPDATE) {
+        st = rp_bit(a.alive, op.u) ? 1u : 0u;
+    } else if (op.kind == RIPPLE_VERTEX_ADD) {
+        st = rp_bit(a.alive, op.u) ? 0u : 1u;
+    } else {
+        bool ok = true;
+        for (int side = 0; side < 2; ++side) {              // alive, or (edges) created by this piece
+            const uint32_t w = side ? op.v : op.u;
+            if (rp_bit(a.alive, w)) continue;
+            bool created = false;
+            if (is_edge)
+                for (uint32_t k = lane; k < a.n_ops; k += 64u) created |= src[k].kind == RIPPLE_VERTEX_ADD && src[k].u == w;
+            ok = ok && __ballot(created) != 0ull;
         }
-        ctr->n_struct = 0;
-        ctr->n_touch_out = ctr->n_touch_in = 0;
-        ctr->n_exp = ctr->need_exp = 0;
-        ctr->n_applied = ctr->n_rejected = 0;
-        ctr->n_add = ctr->n_del = 0;
-        ctr->need_out = ctr->need_in = 0;
-        ctr->n_vadd = 0;
-        ctr->abort_flag = 0;
-        ctr->range_rows = 0;
-        ctr->n_tail_q = ctr->tail_top = 0;
-        for (int k = 0; k < 3; ++k)
-            for (int l = 0; l <= RIPPLE_MAX_LAYERS; ++l) ctr->mono[k][l] = 0;
+        if (ok) {                                           // the same for all wavefronts
+            const uint2 mo = a.out_meta[op.u], mi = a.in_meta[op.v];
+            const uint32_t *ro = a.out_pool + mo.x, *ri = a.in_pool + mi.x;
+            int po = -1, pi = -1;
+            if (is_add) {                                   // absent from the shorter of the two rows
+                if (mo.y <= mi.y) po = find_part(ro, mo.y, op.v, wave, 4u);
+                else po = find_part(ri, mi.y, op.u, wave, 4u);
+            } else if (!is_edge) {                          // EDGE_REWEIGHT: the edge must exist
+                if (a.in_w) pi = find_part(ri, mi.y, op.u, wave, 4u);
+            } else if (wave < 2) {
+                po = find_part(ro, mo.y, op.v, wave, 2u);
+            } else {
+                pi = find_part(ri, mi.y, op.u, wave - 2, 2u);
+            }
+            if (lane == 0 && po >= 0) s_po = po;            // an entry occurs once: one wavefront finds it
+            if (lane == 0 && pi >= 0) s_pi = pi;
+        }
+        __syncthreads();
+        const int po = s_po, pi = s_pi;
+        if (ok && is_add) st = po < 0 ? 1u : 0u;
+        else if (ok && !is_edge) st = pi >= 0 ? 1u : 0u;
+        else if (ok) {
+            st = (po >= 0 && pi >= 0) ? 1u : 0u;
+            if (tid == 0 && (po >= 0) != (pi >= 0)) a.ctr->error = 3;     // the two adjacencies disagree
+        }
+        if (tid == 0 && !is_edge && st) a.pos_in[i] = (uint32_t)pi;
+    }
+    if (tid == 0) {
+        a.status[i] = st;
+        a.op_touch[i] = (is_edge && st) ? count_edge(a, op, i, s_po, s_pi) : 0u;
+    }
+    __syncthreads();                                        // (s_po and s_pi are set anew)
+    }
+    if (!last_workgroup(a.ctr, nb)) return;
+    if (tid < 2) s_need[tid] = 0;
+    uint32_t no = 0, ni = 0, adds = 0, dels = 0;
+    for (uint32_t start = 0; start < a.n_ops; start += 256u) {
+        const uint32_t j = start + tid;
+        const uint32_t f = j < a.n_ops ? a.op_touch[j] : 0u;
+        const unsigned long long mo = __ballot((f & 4u) != 0), mi = __ballot((f & 8u) != 0), below = (1ull << lane) - 1ull;
+        adds += (uint32_t)__popcll(__ballot((f & 3u) == 3u));
+        dels += (uint32_t)__popcll(__ballot((f & 3u) == 1u));
+        if (lane == 0) {
+            s_o[wave] = (uint32_t)__popcll(mo);
+            s_i[wave] = (uint32_t)__popcll(mi);
+        }
+        __syncthreads();
+        uint32_t po = no, pi = ni;
+        for (int k = 0; k < 4; ++k) {
+            if (k < wave) {
+                po += s_o[k];
+                pi += s_i[k];
+            }
+            no += s_o[k];
+            ni += s_i[k];
+        }
+        if (f & 4u) a.touch_out[po + (uint32_t)__popcll(mo & below)] = dst[j].u;     // at most n_ops entries: the lists have room
+        if (f & 8u) a.touch_in[pi + (uint32_t)__popcll(mi & below)] = dst[j].v;
+        __syncthreads();
+    }
+    if (lane == 0) {
+        s_o[wave] = adds;
+        s_i[wave] = dels;
+    }
+    __syncthreads();
+    for (uint32_t j = tid; j < no + ni; j += 256u) {
+        const uint32_t need = row_need(a, j, no);
+        if (need) atomicAdd(&s_need[j < no ? 0 : 1], need);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        a.ctr->n_touch_out = no;
+        a.ctr->n_touch_in = ni;
+        a.ctr->n_add = s_o[0] + s_o[1] + s_o[2] + s_o[3];
+        a.ctr->n_del = s_i[0] + s_i[1] + s_i[2] + s_i[3];
+        a.ctr->abort_flag = decide(a, s_need[0], s_need[1]);
+    }
+}
+
+// Tombstones and the list of changed edges (the first nb workgroups, a thread per operation) and the structural terms
+// (the others, a wavefront per operation and layer, straight from the operations: unweighted graphs only, where a term's sign
+// is the operation's kind). Nothing the one part reads is written by the other.
+__global__ __launch_bounds__(256) void k_small_edges(MutArgs a, uint32_t nb) {
+    if (blockIdx.x < nb) {
+        apply_edge(a, blockIdx.x * 256u + threadIdx.x);
+        return;
+    }
+    if (a.ctr->abort_flag) return;
+    const uint32_t t = ((blockIdx.x - nb) * 256u + threadIdx.x) >> 6, i = t / a.L, l = t - i * a.L + 1u;
+    if (i >= a.n_ops || ((a.mono_mask >> l) & 1u) || !a.status[i]) return;
+    const ripple_update op = a.ops[i];
+    if (op.kind == RIPPLE_EDGE_ADD) struct_term(a, op.u, op.v, l, 1.0f, rp_lane());
+    else if (op.kind == RIPPLE_EDGE_DEL) struct_term(a, op.u, op.v, l, -1.0f, rp_lane());
+}
+
+// Feature rows and created vertices (the first nb workgroups) and the touched rows (the others); then, in the last one to
+// finish, the appends and the out-degree prefix over A_0.
+__global__ __launch_bounds__(256) void k_small_rows(MutArgs a, uint32_t nb, uint32_t *eoff0) {
+    __shared__ uint32_t s_w[4], s_carry;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blockIdx.x < nb) apply_vertices(a, blockIdx.x * 4u + wave, nb * 4u);
+    else cleanup_rows(a, (blockIdx.x - nb) * 4u + wave, (gridDim.x - nb) * 4u);
+    if (!last_workgroup(a.ctr, gridDim.x)) return;
+    if (a.ctr->abort_flag) return;                          // (A_0 is empty)
+    if (tid == 0) a.ctr->n_edges += (unsigned long long)a.ctr->n_add - (unsigned long long)a.ctr->n_del;
+    for (uint32_t i = tid; i < a.n_ops; i += 256u) {
+        const ripple_update op = a.ops[i];
+        if (op.kind == RIPPLE_EDGE_ADD && a.status[i]) append_edge(a, op);
+    }
+    if (tid == 0) s_carry = 0;
+    __syncthreads();
+    __threadfence();                                        // degrees that this workgroup's atomics have just changed
+    const uint32_t count = a.ctr->set[0].a;
+    for (uint32_t base = 0; base < count; base += 256u) {
+        const uint32_t j = base + tid;
+        const uint32_t dg = j < count ? a.out_meta[a.list0[j]].y : 0u;
+        const uint32_t x = rp_wave_scan(dg);
+        if (lane == 63) s_w[wave] = x;
+        __syncthreads();
+        uint32_t off = s_carry;
+        for (int k = 0; k < wave; ++k) off += s_w[k];
+        if (j < count) eoff0[j] = off + x - dg;
+        __syncthreads();
+        if (tid == 255) s_carry = off + x;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        eoff0[count] = s_carry;
+        a.ctr->set[0].m = s_carry;
     }
 }
 
@@ -1128,12 +1316,11 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     MutArgs a;
     a.ops = c->ops_d;
     a.n_ops = n_ops;
-    a.payload = c->payload_d;
+    a.payload = c->payload;
     a.status = c->op_status;
     a.hole_out = c->hole_out;
     a.hole_in = c->hole_in;
     a.op_touch = c->op_touch;
-    a.defer_touch = n_ops > 512 ? 1 : 0;
     a.pos_out = c->op_pos_out;
     a.pos_in = c->op_pos_in;
     a.out_meta = c->out_meta;
@@ -1200,11 +1387,35 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     return a;
 }
 
-void rp_launch_batch_reset(ripple_ctx *c) {
+// counters and bitmaps cleared; n_ops operations from pinned host memory into ops_d
+void rp_launch_batch_reset(ripple_ctx *c, const ripple_update *src, uint32_t n_ops) {
     // the per-layer bitmaps, S and V_added are one allocation starting at bm[0]
     size_t words = (size_t)c->n_words * (c->L + 3);
-    uint32_t gb = std::min<uint32_t>(rp_div_up(words, 256), c->n_cu * 4);
-    hipLaunchKernelGGL(k_batch_reset, dim3(gb), dim3(256), 0, c->stream, c->ctr, c->bm[0], words);
+    uint32_t gb = std::min<uint32_t>(rp_div_up(std::max<size_t>(words, n_ops), 256), c->n_cu * 4);
+    hipLaunchKernelGGL(k_batch_reset, dim3(gb), dim3(256), 0, c->stream, c->ctr, c->bm[0], words, src, c->ops_d, n_ops);
+    c->ctr_dirty = false;
+}
+
+// The Apply step in three launches where the piece is small enough (see k_small_validate); the bitmaps are cleared and A_0's
+// prefix is made as well. false: nothing was enqueued.
+bool rp_launch_mutate_small(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, bool has_vertex_del, bool has_vertex_or_feat) {
+    if (n_ops == 0 || n_ops > SMALL_OPS || has_vertex_del || c->opt_deterministic || c->ctr_dirty) return false;
+    hipStream_t s = c->stream;
+    MutArgs a = make_args(c, n_ops);
+    const uint32_t words = c->n_words * (c->L + 3), nb = std::min(n_ops, SMALL_WGS);
+    hipLaunchKernelGGL(k_small_validate, dim3(nb + std::min<uint32_t>(rp_div_up(words, 1024), c->n_cu * 2)), dim3(256), 0, s, a, src,
+                       c->ops_d, nb, c->bm[0], words);
+    const uint32_t tb = rp_div_up(n_ops, 256);
+    if (c->in_w) {
+        hipLaunchKernelGGL(k_apply_edges, dim3(tb), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_struct_scatter, dim3(rp_div_up(n_ops * c->L, 4)), dim3(256), 0, s, a);
+    } else {
+        const bool terms = (a.mono_mask >> 1) != (1u << c->L) - 1u;        // some layer has structural terms
+        hipLaunchKernelGGL(k_small_edges, dim3(tb + (terms ? rp_div_up(n_ops * c->L, 4) : 0u)), dim3(256), 0, s, a, tb);
+    }
+    const uint32_t vb = has_vertex_or_feat ? std::min(rp_div_up(n_ops, 4), SMALL_WGS / 2) : 0u;
+    hipLaunchKernelGGL(k_small_rows, dim3(vb + std::min(rp_div_up(2 * n_ops, 4), SMALL_WGS)), dim3(256), 0, s, a, vb, c->eoff[0]);
+    return true;
 }
 
 // Enqueue the whole Apply step for the n_ops operations staged in ops_d / payload_d.
@@ -1217,7 +1428,7 @@ void rp_launch_mutate(ripple_ctx *c, uint32_t n_ops, bool has_vertex_add, bool h
     uint32_t big = c->n_cu * 8;
     if (has_vertex_add || has_vertex_del) hipLaunchKernelGGL(k_vertex_validate, dim3(tb), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_edge_validate, dim3(wb), dim3(256), 0, s, a);
-    if (a.defer_touch) hipLaunchKernelGGL(k_touch_lists, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(k_touch_lists, dim3(1), dim3(1024), 0, s, a);
     uint32_t touch_threads = 2 * n_ops;                               // validation touches <= n_ops rows per side
     hipLaunchKernelGGL(k_capacity, dim3(rp_div_up(touch_threads, 256)), dim3(256), 0, s, a);
     if (has_vertex_del) {

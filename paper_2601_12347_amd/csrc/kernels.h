@@ -9,7 +9,10 @@ void rp_exclusive_scan(hipStream_t s, const uint32_t *in, uint32_t *out, uint32_
 ripple_status rp_build_graph(ripple_ctx *c, uint32_t n_vertices, uint64_t n_edges, const uint32_t *src_h,
                              const uint32_t *dst_h, const float *w_h);
 ripple_status rp_compact(ripple_ctx *c);
-void rp_launch_batch_reset(ripple_ctx *c);
+void rp_launch_batch_reset(ripple_ctx *c, const ripple_update *src, uint32_t n_ops);
+void rp_launch_publish(ripple_ctx *c);
+void rp_launch_report(ripple_ctx *c);
+bool rp_launch_mutate_small(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, bool has_vertex_del, bool has_vertex_or_feat);
 void rp_launch_mutate(ripple_ctx *c, uint32_t n_ops, bool has_vertex_add, bool has_vertex_del, bool has_vertex_or_feat);
 
 // order.hip
@@ -30,12 +33,16 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
 void rp_launch_candidates(ripple_ctx *c, uint32_t l);
 void rp_launch_candidates_sparse(ripple_ctx *c, uint32_t l, bool self_term, uint32_t long_min);
 void rp_launch_list_offsets(ripple_ctx *c, uint32_t l, bool want_out);
-void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t cap, uint32_t *count_d);
+void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_list, uint32_t cap, uint32_t *count_d, bool report = false);
 void rp_launch_list_eoff(ripple_ctx *c, uint32_t l);
 ripple_status rp_static_scratch_init(ripple_ctx *c);
 uint32_t rp_static_max_vertices();
 ripple_status rp_launch_affected_static(ripple_ctx *c, uint32_t *bitmap, uint32_t *ids_out, uint32_t cap, uint32_t *n_out);
 void rp_launch_frontier_sparse(ripple_ctx *c, uint32_t l, bool self_term, bool want_out, uint32_t long_min = 0);
+
+// hop_small.hip
+void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term);
+void rp_launch_small_addend(ripple_ctx *c, uint32_t l, bool emit_delta);   // transform.hip
 
 // scatter.hip
 void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc);
@@ -58,6 +65,10 @@ void rp_launch_self_project(ripple_ctx *c, uint32_t l, const uint32_t *list, con
 void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap);
 bool rp_has_project_both(const ripple_ctx *c, uint32_t l);
 void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap);
+
+// api.hip: the flag the next launch reports to, and the wait for it
+HostFlag rp_host_flag(ripple_ctx *c);
+ripple_status rp_wait_flag(ripple_ctx *c);
 
 // api.hip: HIP-event timing of kernel classes (no-ops unless RIPPLE_OPT_TIMING is on)
 int rp_timer_begin(ripple_ctx *c);

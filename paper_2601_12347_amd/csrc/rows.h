@@ -1,0 +1,186 @@
+// How the row transforms read and write rows: shared by the tiled kernels and the one for few rows.
+#pragma once
+#include "transform_args.h"
+
+__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {     // round to nearest even
+    const __hip_bfloat16 a = __float2bfloat16(lo), b = __float2bfloat16(hi);
+    return (uint32_t)__builtin_bit_cast(unsigned short, a) | ((uint32_t)__builtin_bit_cast(unsigned short, b) << 16);
+}
+
+// Rows of any width: a row of 190 or 47 floats starts at a multiple of 4 bytes only, which a 16-byte global load takes all
+// the same. The last group of a row may read up to three numbers past its end (the next row's, or, behind the last row,
+// the padding dev_alloc puts behind every array); they are zeroed or dropped later.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uintx2u __attribute__((ext_vector_type(2), aligned(2)));    // four bf16 numbers
+__device__ __forceinline__ uint32_t last_group(uint32_t n) { return (n - 1u) & ~3u; }   // first column of a row's last group of four
+
+// Raw 16 (or 8) bytes for four consecutive k of one gathered row; no arithmetic on the data.
+// MODE 1 with bf16 embeddings and MODE 2 need two sources (p: own embedding, q: aggregate). MODE 1 takes rows whose width
+// is a multiple of four only (a group must not straddle the two halves).
+template <int MODE, int STORE>
+__device__ __forceinline__ void fetch_raw(const TArgs &a, uint32_t v, uint32_t slot, uint32_t k, floatx4 &p, floatx4 &q) {
+    const uint32_t kc = min(k, last_group(a.K));
+    const size_t row = (size_t)v * a.d_in;
+    auto bf4 = [](const void *h, size_t i) {
+        const uintx2u r = *(const uintx2u *)((const __hip_bfloat16 *)h + i);
+        floatx4 f = (floatx4)(0.0f);
+        f.x = __uint_as_float(r.x);
+        f.y = __uint_as_float(r.y);
+        return f;
+    };
+    if (MODE == 0) {
+        p = *(const floatx4u *)(a.X + row + kc);
+    } else if (MODE == 3) {
+        p = *(const floatx4u *)(a.tmp_in + (size_t)slot * a.tmp_ld + kc);
+    } else if (MODE == 4) {
+        if (STORE) p = bf4(a.Hprev, row + kc);
+        else p = *(const floatx4u *)((const float *)a.Hprev + row + kc);
+    } else if (MODE == 2) {
+        q = *(const floatx4u *)(a.X + row + kc);
+        if (STORE) p = bf4(a.Hprev, row + kc);
+        else p = *(const floatx4u *)((const float *)a.Hprev + row + kc);
+    } else {                                                  // MODE 1: k < d_in own embedding, else aggregate
+        if (STORE) {
+            const uint32_t kh = min(kc, a.d_in - 4u), kx = kc >= a.d_in ? kc - a.d_in : 0u;
+            p = bf4(a.Hprev, row + kh);
+            q = *(const floatx4u *)(a.X + row + kx);
+        } else {
+            const float *src = (kc < a.d_in) ? (const float *)a.Hprev + row + kc : a.X + row + (kc - a.d_in);
+            p = *(const floatx4u *)src;
+        }
+    }
+}
+
+template <int MODE, int STORE>
+__device__ __forceinline__ floatx4 finish_raw(const TArgs &a, floatx4 p, floatx4 q, uint32_t k, float scale) {
+    floatx4 h = p;
+    if (STORE && (MODE == 1 || MODE == 2 || MODE == 4)) {
+        const uint32_t w0 = __float_as_uint(p.x), w1 = __float_as_uint(p.y);
+        h.x = bf_lo(w0);
+        h.y = bf_hi(w0);
+        h.z = bf_lo(w1);
+        h.w = bf_hi(w1);
+    }
+    floatx4 r;
+    if (MODE == 0) {
+        r = p * scale;
+    } else if (MODE == 3) {
+        r = p;
+    } else if (MODE == 4) {
+        r = h;
+    } else if (MODE == 2) {
+        r = h * a.one_plus_eps + q * scale;
+    } else {
+        const floatx4 x = STORE ? q : p;
+        r = (k < a.d_in) ? h : x * scale;
+    }
+    if (k + 4u > a.K) {                                       // padding, and what was read past the row's end
+        r.x = k < a.K ? r.x : 0.0f;
+        r.y = k + 1u < a.K ? r.y : 0.0f;
+        r.z = k + 2u < a.K ? r.z : 0.0f;
+        r.w = k + 3u < a.K ? r.w : 0.0f;
+    }
+    return r;
+}
+
+// ---------------------------------------------------------------------------------
+// few rows
+// ---------------------------------------------------------------------------------
+// A hop of some hundred rows leaves most of the chip idle and is paced by the chain of dependent steps: list entry, row,
+// products, store. Here every wavefront has a 16 x 16 block of the output to itself (MFMA 16x16x4, fp32): a K of 256 is 64
+// products one after the other, a microsecond, where a 32 x 32 block takes four; there is no LDS and no barrier, so a
+// wavefront waits for its own loads only; rows and weights are requested three steps of 32 k ahead. A lane holds four
+// consecutive k of its row (one 16-byte load), which the four products of a group take one each, so the group's k are
+// numbered lane group first: k = 4 * (lane / 16) + i for product i; the weights are loaded to match.
+#define SMALL_GEMM_ROWS 2048u
+template <int MODE, int STORE>
+__device__ __forceinline__ void small_gemm(const TArgs &a, uint32_t gw, uint32_t nw) {
+    constexpr int STAGES = 4;
+    const uint32_t count = *a.count_ptr;
+    const int lane = (int)(threadIdx.x & 63u);
+    const uint32_t sub = (uint32_t)lane & 15u, grp = (uint32_t)lane >> 4;
+    const uint32_t n_ct = (a.N + 15u) / 16u, n_tiles = (count + 15u) / 16u * n_ct;
+    for (uint32_t tile = gw; tile < n_tiles; tile += nw) {
+        const uint32_t row0 = tile / n_ct * 16u, col = tile % n_ct * 16u + sub;
+        const uint32_t slot = min(row0 + sub, count - 1u);
+        const uint32_t v = a.list[slot];
+        const uint32_t deg = a.mean ? a.in_meta[v].y : 1u;
+        const float scale = 1.0f / (float)(deg > 1u ? deg : 1u);
+        floatx4 ra[STAGES][2], rq[STAGES][2];
+        float rb[STAGES][8];
+        auto request = [&](uint32_t k0, floatx4 (&pa)[2], floatx4 (&pq)[2], float (&pb)[8]) {
+            const uint32_t kc = min(k0, a.Kpad - 32u);       // past the end: the last step once more, not used
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const uint32_t k = kc + 16u * g + 4u * grp;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pb[4 * g + i] = a.W[(size_t)(k + i) * a.Npad + col];
+                pq[g] = (floatx4)(0.0f);
+                fetch_raw<MODE, STORE>(a, v, slot, k, pa[g], pq[g]);
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < STAGES; ++s) request(32u * s, ra[s], rq[s], rb[s]);
+        // the rows this lane stores (four per lane, one column): their old values and addends are on their way meanwhile
+        uint32_t ov[4];
+        float add[4], old[4], osc[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ov[r] = a.list[min(row0 + 4u * grp + r, count - 1u)];
+        const uint32_t ccol = min(col, a.N - 1u);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const size_t at = (size_t)ov[r] * a.N + ccol;
+            const uint32_t dg = (a.mean && a.addend && a.addend_scaled) ? a.in_meta[ov[r]].y : 1u;
+            osc[r] = 1.0f / (float)(dg > 1u ? dg : 1u);
+            add[r] = (a.out_mode == 1 && a.addend) ? a.addend[at] : 0.0f;
+            old[r] = (a.out_mode == 1 && a.D) ? rp_load_h(a.Hout, a.store, at) : 0.0f;
+        }
+        const float bias = a.bias[col];
+        floatx4 acc0 = (floatx4)(0.0f), acc1 = (floatx4)(0.0f);
+        for (uint32_t kb = 0; kb < a.Kpad; kb += 32u * STAGES) {
+#pragma unroll
+            for (int s = 0; s < STAGES; ++s) {
+                const uint32_t k0 = kb + 32u * s;
+                if (k0 >= a.Kpad) break;
+#pragma unroll
+                for (int g = 0; g < 2; ++g) {
+                    const floatx4 x = finish_raw<MODE, STORE>(a, ra[s][g], rq[s][g], k0 + 16u * g + 4u * grp, scale);
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, rb[s][4 * g + 0], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, rb[s][4 * g + 1], acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, rb[s][4 * g + 2], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, rb[s][4 * g + 3], acc1, 0, 0, 0);
+                }
+                request(k0 + 32u * STAGES, ra[s], rq[s], rb[s]);
+            }
+        }
+        const floatx4 acc = acc0 + acc1;
+        if (col >= a.N || (a.split_col && col >= a.N1 && col < a.split_col)) continue;   // padding columns
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t os = row0 + 4u * grp + r;
+            if (os >= count) continue;
+            float z = acc[r] + bias + add[r] * osc[r];
+            if (a.act == RIPPLE_ACT_RELU) z = z > 0.0f ? z : 0.0f;
+            if (a.out_mode != 1) {
+                const size_t orow = a.out_mode == 0 ? os : ov[r];
+                if (a.split_col && col >= a.split_col) a.tmp_out2[orow * a.tmp_out2_ld + (col - a.split_col)] = z;
+                else a.tmp_out[orow * a.tmp_out_ld + col] = z;
+                continue;
+            }
+            const size_t at = (size_t)ov[r] * a.N + col;
+            if (a.store) {
+                const __hip_bfloat16 zr = __float2bfloat16(z);
+                z = __bfloat162float(zr);
+                ((__hip_bfloat16 *)a.Hout)[at] = zr;
+            } else {
+                ((float *)a.Hout)[at] = z;
+            }
+            if (a.D) a.D[at] = a.d_old ? old[r] : z - old[r];
+        }
+    }
+}
+// wavefronts the blocks of about `rows` rows take
+static inline uint32_t small_gemm_waves(const TArgs &a, uint32_t rows) { return rp_div_up(rows ? rows : 1u, 16) * rp_div_up(a.N, 16); }

@@ -13,12 +13,11 @@
 // Bootstrap kernel: X^l[v] = sum over v's in-row of H^{l-1}, cut over edges like the pull.
 #include "common.h"
 #include "kernels.h"
+#include "push.h"
 
 
-#define PUSH_CHUNK 64
 #define PULL_CHUNK 256
 
-// PK = 1 (NJ = 1 only): the message rows are packed 128-byte lines (D points at them)
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 
 template <int NJ, int PK>
@@ -26,83 +25,11 @@ __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, cons
                                                       const uint32_t *eoff, const float *D, uint32_t ldd, uint32_t d,
                                                       const uint2 *out_meta, const uint32_t *out_pool, float *X,
                                                       DevCtr *ctr, uint32_t l, int may_pull, int mode, int ratio, int allow_disc) {
-    constexpr int G = (NJ <= 2) ? 8 : (NJ <= 4 ? 4 : (NJ <= 8 ? 2 : 1));   // edges per round
     const int hm = rp_hop_mode(ctr, l, d, mode, ratio, allow_disc);
     if (hm == RP_HOP_DISCOVER || (may_pull && hm == RP_HOP_PULL)) return;
-    const uint32_t count = *count_ptr;
-    if (count == 0) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctr->hop_mode[l] = 1u + RP_HOP_PUSH;
-    const int lane = rp_lane();
-    const uint32_t M = eoff[count];
-    const uint32_t chunk = (M <= 16384u) ? 16u : PUSH_CHUNK;   // few messages: spread them over more wavefronts
-    const uint32_t n_chunks = (M + chunk - 1) / chunk;
-    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t c = gw; c < n_chunks; c += nw) {
-        const uint32_t e0 = c * chunk, e1 = min(M, e0 + chunk);
-        // the chunk's first row by the wavefront together; the 64 rows from there on (vertex, pool position,
-        // end) one per lane, so an edge finds its row with shuffles instead of a chain of dependent reads
-        const uint32_t i_lo = rp_seg_search_wave(eoff, 0, count - 1, e0);
-        const uint32_t ri = min(count - 1, i_lo + (uint32_t)lane);
-        const uint32_t rv = list[ri];
-        const uint32_t rbase = out_meta[rv].x - eoff[ri];      // pool position of edge e: rbase + e (mod 2^32)
-        const uint32_t bnd = eoff[min(count, i_lo + 1u + (uint32_t)lane)];
-        const uint32_t e = min(e0 + (uint32_t)lane, e1 - 1);    // lanes past the chunk repeat its last edge (not used)
-        const uint32_t k = rp_count_le(bnd, e);
-        uint32_t my_i = i_lo + k, my_u = __shfl(rv, (int)min(k, 63u)), pos = __shfl(rbase, (int)min(k, 63u)) + e;
-        if (k >= 64u) {                                         // more than 64 rows in 64 edges (rows without out-edges)
-            my_i = rp_seg_search(eoff, i_lo + 64u, count - 1, e);
-            my_u = list[my_i];
-            pos = out_meta[my_u].x + (e - eoff[my_i]);
-        }
-        const uint32_t my_v = out_pool[pos];
-        const int n_here = (int)(e1 - e0);
-        // G edges per round: their sources' delta rows are requested together (consecutive edges mostly share
-        // the source: the repeats are cache hits), then the additions go out
-        for (int k0 = 0; k0 < n_here; k0 += G) {
-            float dreg[G][NJ];
-            uint32_t vk[G];
-            if constexpr (PK) {                              // lane = column: its chunk is lane mod 16
-                uint2 ch[G];
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const int k = min(k0 + g, n_here - 1);
-                    const uint32_t uk = __shfl(my_u, k);
-                    vk[g] = __shfl(my_v, k);
-                    ch[g] = *(const uint2 *)((const uint32_t *)D + (size_t)uk * RP_MSG_WORDS + 2u * ((uint32_t)lane & 15u));
-                }
-#pragma unroll
-                for (int g = 0; g < G; ++g) dreg[g][0] = ((uint32_t)lane < d) ? rp_msg_decode_col(ch[g], (uint32_t)lane) : 0.0f;
-            } else {
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const int k = min(k0 + g, n_here - 1);
-                    const uint32_t uk = __shfl(my_u, k);
-                    vk[g] = __shfl(my_v, k);
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const uint32_t col = lane + 64 * j;
-                        dreg[g][j] = (col < d) ? D[(size_t)uk * ldd + col] : 0.0f;
-                    }
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (k0 + g < n_here) {
-                    bool any = false;
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) any |= dreg[g][j] != 0.0f;
-                    if (__ballot(any) != 0ull) {                // an all-zero delta changes nothing
-                        float *xr = X + (size_t)vk[g] * d;
-#pragma unroll
-                        for (int j = 0; j < NJ; ++j) {
-                            const uint32_t col = lane + 64 * j;
-                            if (col < d) unsafeAtomicAdd(&xr[col], dreg[g][j]);
-                        }
-                    }
-                }
-            }
-        }
-    }
+    if (*count_ptr && blockIdx.x == 0 && threadIdx.x == 0) ctr->hop_mode[l] = 1u + RP_HOP_PUSH;
+    push_edges<NJ, PK>(list, count_ptr, eoff, D, nullptr, ldd, d, out_meta, out_pool, X, (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
+                       (gridDim.x * blockDim.x) >> 6);
 }
 
 void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc) {
@@ -113,7 +40,7 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
     const uint32_t ldd = proj ? c->pd_ld : d;
     dim3 grid(c->n_cu * 8), block(256);
 #define PUSH_CASE_PK(NJ, PK)                                                                                       \
-    hipLaunchKernelGGL((k_scatter_push<NJ, PK>), grid, block, 0, c->stream, c->list[l - 1], &c->ctr->a[l - 1],     \
+    hipLaunchKernelGGL((k_scatter_push<NJ, PK>), grid, block, 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,     \
                        c->eoff[l - 1], D, ldd, d, c->out_meta, c->out_pool, c->X[l], c->ctr, l, may_pull ? 1 : 0,  \
                        c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0)
 #define PUSH_CASE(NJ) PUSH_CASE_PK(NJ, 0)
@@ -163,7 +90,7 @@ struct PullArgs {
     uint32_t l;
     int mode, ratio, allow_disc;
     // the hop's messages may have been listed and sorted instead (rp_hop_sorted): then the pull leaves the hop alone
-    const uint32_t *m_eoff, *m_count;   // out-degree prefix over A_{l-1} and |A_{l-1}|: the number of messages
+    const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
     uint32_t sorted_cap;           // entries the host sorted (0: no list was made)
     int sorted_force;
     // deterministic variants only
@@ -289,7 +216,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     if (!DET && rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL)) return;
     if (!DET && !DISC && a.sorted_cap) {
         const uint32_t cp = *a.m_count;
-        if (rp_hop_sorted(a.ctr, a.l, cp ? a.m_eoff[cp] : 0u, a.sorted_cap, a.sorted_force)) return;
+        if (rp_hop_sorted(a.ctr, a.l, cp ? a.m_count[1] : 0u, a.sorted_cap, a.sorted_force)) return;
     }
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
@@ -474,7 +401,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
 // whether the list is used is decided here, like the hop's mode, from the hop's own counters.
 struct SortedArgs {
     const uint32_t *pk, *pv;       // sorted: destination, source
-    const uint32_t *m_eoff, *m_count;
+    const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
     uint32_t cap;
     int force;
     const float *D;
@@ -489,7 +416,7 @@ template <int NJ>
 __global__ __launch_bounds__(256) void k_scatter_sorted(SortedArgs a) {
     if (rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != RP_HOP_PULL) return;
     const uint32_t cp = *a.m_count;
-    const uint32_t M = cp ? a.m_eoff[cp] : 0u;
+    const uint32_t M = cp ? a.m_count[1] : 0u;
     if (!rp_hop_sorted(a.ctr, a.l, M, a.cap, a.force)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_SORTED;
     constexpr int G = (NJ >= 8) ? 2 : (NJ == 4 ? 4 : 8 / NJ);   // message rows per round trip (and up to as many destination rows)
@@ -853,13 +780,12 @@ __global__ __launch_bounds__(256) void k_pull_fixup(PullArgs a, uint32_t n_entri
 // c->ioff_all must have been produced by rp_launch_alive_list) and mark the receivers in bm[l].
 void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow_disc, uint32_t pair_cap) {
     PullArgs a;
-    a.m_eoff = c->eoff[l - 1];
-    a.m_count = &c->ctr->a[l - 1];
+    a.m_count = &c->ctr->set[l - 1].a;
     a.sorted_cap = discover ? 0u : pair_cap;
     a.sorted_force = c->opt_sorted == 2;
     a.side_runs = 0;
     a.list = discover ? c->all_list : c->list[l];
-    a.count_ptr = discover ? &c->ctr->n_all : &c->ctr->a[l];
+    a.count_ptr = discover ? &c->ctr->n_all : &c->ctr->set[l].a;
     a.ioff = discover ? c->ioff_all : c->ioff[l];
     a.in_meta = c->in_meta;
     a.in_pool = c->in_pool;
@@ -908,8 +834,7 @@ bool rp_launch_scatter_sorted(ripple_ctx *c, uint32_t l, bool allow_disc, uint32
     SortedArgs a;
     a.pk = c->pk_b;
     a.pv = c->pv_b;
-    a.m_eoff = c->eoff[l - 1];
-    a.m_count = &c->ctr->a[l - 1];
+    a.m_count = &c->ctr->set[l - 1].a;
     a.cap = pair_cap;
     a.force = c->opt_sorted == 2;
     a.D = ly.proj ? c->PD : c->D[(l - 1) & 1];
@@ -936,11 +861,11 @@ bool rp_launch_scatter_sorted(ripple_ctx *c, uint32_t l, bool allow_disc, uint32
 void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
     const LayerDev &ly = c->layers[l - 1];
     PullArgs a;
-    a.m_eoff = a.m_count = nullptr;
+    a.m_count = nullptr;
     a.sorted_cap = 0;
     a.sorted_force = 0;
     a.list = bootstrap ? c->all_list : c->list[l];
-    a.count_ptr = bootstrap ? &c->ctr->n_all : &c->ctr->a[l];
+    a.count_ptr = bootstrap ? &c->ctr->n_all : &c->ctr->set[l].a;
     a.ioff = bootstrap ? c->ioff_all : c->ioff[l];
     a.in_meta = c->in_meta;
     a.in_pool = c->in_pool;
@@ -1048,7 +973,7 @@ void rp_launch_messages(ripple_ctx *c, uint32_t l) {
     const LayerDev &ly = c->layers[l - 1];
     const uint32_t hint = rp_rows_hint(c, l - 1);
     const uint32_t grid = std::max<uint32_t>(1u, std::min<uint32_t>(c->n_cu * 8, rp_div_up(hint, 4 * 8) + 1));
-    hipLaunchKernelGGL(k_messages, dim3(grid), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->a[l - 1], c->PD, c->pd_ld,
+    hipLaunchKernelGGL(k_messages, dim3(grid), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->PD, c->pd_ld,
                        ly.T, c->xw[l], ly.packed, c->MSG);
 }
 
@@ -1628,7 +1553,7 @@ void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr
     // listed: the long rows are in c->eoff[l] already (rp_launch_candidates_sparse), nothing is queued here
     a.queue = listed ? nullptr : c->list[l];    // not written before the hop's set is final
     a.out_list = listed ? c->list[l] : nullptr;
-    a.out_count = &c->ctr->a[l];                // zero since the batch began
+    a.out_count = &c->ctr->set[l].a;                // zero since the batch began
     a.queue_count = &c->ctr->n_long[l];         // zero since the batch began
     a.in_meta = c->in_meta;
     a.in_pool = c->in_pool;

@@ -25,91 +25,8 @@
 #include "kernels.h"
 #include <algorithm>
 
-#include "transform_args.h"
-
-__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {     // round to nearest even
-    const __hip_bfloat16 a = __float2bfloat16(lo), b = __float2bfloat16(hi);
-    return (uint32_t)__builtin_bit_cast(unsigned short, a) | ((uint32_t)__builtin_bit_cast(unsigned short, b) << 16);
-}
-
-// Rows of any width: a row of 190 or 47 floats starts at a multiple of 4 bytes only, which a 16-byte global load takes all
-// the same. The last group of a row may read up to three numbers past its end (the next row's, or, behind the last row,
-// the padding dev_alloc puts behind every array); they are zeroed or dropped later.
-typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t uintx2u __attribute__((ext_vector_type(2), aligned(2)));    // four bf16 numbers
-__device__ __forceinline__ uint32_t last_group(uint32_t n) { return (n - 1u) & ~3u; }   // first column of a row's last group of four
-
-// Raw 16 (or 8) bytes for four consecutive k of one gathered row; no arithmetic on the data.
-// MODE 1 with bf16 embeddings and MODE 2 need two sources (p: own embedding, q: aggregate). MODE 1 takes rows whose width
-// is a multiple of four only (a group must not straddle the two halves).
-template <int MODE, int STORE>
-__device__ __forceinline__ void fetch_raw(const TArgs &a, uint32_t v, uint32_t slot, uint32_t k, floatx4 &p, floatx4 &q) {
-    const uint32_t kc = min(k, last_group(a.K));
-    const size_t row = (size_t)v * a.d_in;
-    auto bf4 = [](const void *h, size_t i) {
-        const uintx2u r = *(const uintx2u *)((const __hip_bfloat16 *)h + i);
-        floatx4 f = (floatx4)(0.0f);
-        f.x = __uint_as_float(r.x);
-        f.y = __uint_as_float(r.y);
-        return f;
-    };
-    if (MODE == 0) {
-        p = *(const floatx4u *)(a.X + row + kc);
-    } else if (MODE == 3) {
-        p = *(const floatx4u *)(a.tmp_in + (size_t)slot * a.tmp_ld + kc);
-    } else if (MODE == 4) {
-        if (STORE) p = bf4(a.Hprev, row + kc);
-        else p = *(const floatx4u *)((const float *)a.Hprev + row + kc);
-    } else if (MODE == 2) {
-        q = *(const floatx4u *)(a.X + row + kc);
-        if (STORE) p = bf4(a.Hprev, row + kc);
-        else p = *(const floatx4u *)((const float *)a.Hprev + row + kc);
-    } else {                                                  // MODE 1: k < d_in own embedding, else aggregate
-        if (STORE) {
-            const uint32_t kh = min(kc, a.d_in - 4u), kx = kc >= a.d_in ? kc - a.d_in : 0u;
-            p = bf4(a.Hprev, row + kh);
-            q = *(const floatx4u *)(a.X + row + kx);
-        } else {
-            const float *src = (kc < a.d_in) ? (const float *)a.Hprev + row + kc : a.X + row + (kc - a.d_in);
-            p = *(const floatx4u *)src;
-        }
-    }
-}
-
-template <int MODE, int STORE>
-__device__ __forceinline__ floatx4 finish_raw(const TArgs &a, floatx4 p, floatx4 q, uint32_t k, float scale) {
-    floatx4 h = p;
-    if (STORE && (MODE == 1 || MODE == 2 || MODE == 4)) {
-        const uint32_t w0 = __float_as_uint(p.x), w1 = __float_as_uint(p.y);
-        h.x = bf_lo(w0);
-        h.y = bf_hi(w0);
-        h.z = bf_lo(w1);
-        h.w = bf_hi(w1);
-    }
-    floatx4 r;
-    if (MODE == 0) {
-        r = p * scale;
-    } else if (MODE == 3) {
-        r = p;
-    } else if (MODE == 4) {
-        r = h;
-    } else if (MODE == 2) {
-        r = h * a.one_plus_eps + q * scale;
-    } else {
-        const floatx4 x = STORE ? q : p;
-        r = (k < a.d_in) ? h : x * scale;
-    }
-    if (k + 4u > a.K) {                                       // padding, and what was read past the row's end
-        r.x = k < a.K ? r.x : 0.0f;
-        r.y = k + 1u < a.K ? r.y : 0.0f;
-        r.z = k + 2u < a.K ? r.z : 0.0f;
-        r.w = k + 3u < a.K ? r.w : 0.0f;
-    }
-    return r;
-}
+#include "rows.h"
+#include "push.h"
 
 // Bias, (projected aggregate,) activation, delta against the stored row, store. Everything that
 // is read (old rows, aggregate rows) is read in batches of TN*16 loads before anything is written:
@@ -335,14 +252,57 @@ __device__ __forceinline__ void epilogue_staged(const TArgs &a, floatx16 (&acc)[
     else epilogue_pick<BN, ITER, U, false, BF>(a, Cs, s_vtx, s_scale, row0, count, n0, tid);
 }
 
+static TArgs base_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
+    const LayerDev &ly = c->layers[l - 1];
+    TArgs a;
+    a.list = list;
+    a.count_ptr = count_d;
+    a.Hprev = c->H[l - 1];
+    a.X = c->X[l];
+    a.in_meta = c->in_meta;
+    a.mean = (ly.agg == RIPPLE_AGG_MEAN) ? 1 : 0;
+    a.one_plus_eps = 1.0f + ly.eps;
+    a.d_in = ly.d_in;
+    a.tmp_in = nullptr;
+    a.tmp_ld = 0;
+    a.store = c->store;
+    a.Hout = c->H[l];
+    a.D = nullptr;
+    a.d_old = 0;
+    a.tmp_out = nullptr;
+    a.tmp_out_ld = 0;
+    a.split_col = 0;
+    a.N1 = ly.d_out;
+    a.tmp_out2 = nullptr;
+    a.tmp_out2_ld = 0;
+    a.addend = nullptr;
+    a.addend_scaled = 1;
+    a.addend2 = nullptr;
+    a.den = nullptr;
+    a.range_rows = &c->ctr->range_rows;
+    a.a_mode = 0;
+    a.out_mode = 1;
+    a.act = 0;
+    a.W = ly.W0;
+    a.Wt = (c->store && c->opt_bf16_mfma) ? ly.W0h : nullptr;   // bf16 storage: bf16 matrix cores
+    a.wt_ld = ly.K0pad;
+    a.Ws = ly.W0s;                                 // fp32 storage with split products, else null
+    a.ws_plane = (size_t)ly.N0pad * ly.K0pad;
+    a.bias = ly.b0;
+    a.K = ly.K;
+    a.Kpad = ly.K0pad;
+    a.N = ly.d_out;
+    a.Npad = ly.N0pad;
+    return a;
+}
+
 // Project-first layers have no matrix product left per row: h = act(Y[v] * scale + PS[v] + b), with
 // Y the projected aggregate and PS the cached self term (absent for GraphConv).
 template <bool BF>
-__device__ __forceinline__ void addend_only_rows(const TArgs &a) {
+__device__ __forceinline__ void addend_only_rows(const TArgs &a, uint32_t gw, uint32_t nw) {
     constexpr int R = 8;                                   // rows per wavefront and round: their loads overlap
     const uint32_t count = *a.count_ptr;
     const int lane = threadIdx.x & 63;
-    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t s0 = gw * R; s0 < count; s0 += nw * R) {
         uint32_t v[R];
         float sc[R];
@@ -452,6 +412,41 @@ __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
     }
 }
 
+// Small hops of a project-first layer: the row update, and (the workgroups from nb on) T brought up to date with the messages
+// that push_edges<.., 2> has sent: T += m, element by element as rp_message made it.
+__global__ __launch_bounds__(256) void k_small_addend(TArgs a, uint32_t nb, const uint32_t *src_list, const uint32_t *src_count,
+                                                      const float *PD, uint32_t ldd, float *T, int packed) {
+    if (blockIdx.x < nb) {
+        if (a.store) addend_only_rows<true>(a, blockIdx.x * 4u + (threadIdx.x >> 6), nb * 4u);
+        else addend_only_rows<false>(a, blockIdx.x * 4u + (threadIdx.x >> 6), nb * 4u);
+        return;
+    }
+    const uint32_t count = *src_count, lane = threadIdx.x & 63u, nw = (gridDim.x - nb) * 4u;
+    for (uint32_t i = (blockIdx.x - nb) * 4u + (threadIdx.x >> 6); i < count; i += nw) {
+        const uint32_t u = src_list[i];
+        for (uint32_t c0 = 0; c0 < a.N; c0 += 64u) {
+            const uint32_t col = c0 + lane;
+            const float p = col < a.N ? PD[(size_t)u * ldd + col] : 0.0f, t = col < a.N ? T[(size_t)u * a.N + col] : 0.0f;
+            const float m = rp_message(p - t, packed != 0);
+            if (col < a.N) T[(size_t)u * a.N + col] = packed ? t + m : p;
+        }
+    }
+}
+
+void rp_launch_small_addend(ripple_ctx *c, uint32_t l, bool emit_delta) {
+    const LayerDev &ly = c->layers[l - 1];
+    TArgs a = base_args(c, l, c->list[l], &c->ctr->set[l].a);
+    a.D = emit_delta ? c->D[l & 1] : nullptr;
+    a.d_old = rp_layer_mono(c, l + 1) ? 1 : 0;
+    a.addend = c->X[l];
+    a.act = (int)ly.act_out;
+    a.addend2 = ly.selfc ? ly.PS : nullptr;
+    const uint32_t nb = std::min(rp_div_up(c->last_a[l] + c->last_a[l] / 2u + 32u, 32), c->n_cu * 8);
+    const uint32_t nt = std::min(rp_div_up(c->last_a[l - 1] + c->last_a[l - 1] / 2u + 4u, 4), c->n_cu * 4);
+    hipLaunchKernelGGL(k_small_addend, dim3(nb + nt), dim3(256), 0, c->stream, a, nb, c->list[l - 1], &c->ctr->set[l - 1].a, c->PD, c->pd_ld,
+                       ly.T, (int)ly.packed);
+}
+
 static void launch_addend_flat(ripple_ctx *c, const TArgs &a) {
     const dim3 grid(c->n_cu * 16), block(256);
 #define RP_FLAT(BF, OLD, ADD2) hipLaunchKernelGGL((k_transform_addend_flat<BF, OLD, ADD2>), grid, block, 0, c->stream, a)
@@ -467,8 +462,9 @@ static void launch_addend_flat(ripple_ctx *c, const TArgs &a) {
 }
 
 __global__ __launch_bounds__(256) void k_transform_addend_only(TArgs a) {
-    if (a.store) addend_only_rows<true>(a);
-    else addend_only_rows<false>(a);
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    if (a.store) addend_only_rows<true>(a, gw, nw);
+    else addend_only_rows<false>(a, gw, nw);
 }
 
 template <int WAVES_M, int WAVES_N, int TM, int TN, int STAGES, int MODE, int STORE, int MINB = 2>
@@ -1073,18 +1069,16 @@ static void launch_split(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t ro
 }
 
 template <int MODE, int STORE>
+__global__ __launch_bounds__(256) void k_transform_small(TArgs a) {
+    small_gemm<MODE, STORE>(a, (blockIdx.x * 256u + threadIdx.x) >> 6, gridDim.x * 4u);
+}
+
+template <int MODE, int STORE>
 static void launch_fast(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t rows_hint) {
-    if (rows_hint <= 32 && a.Npad % 128 == 0) {
-        // a handful of rows: one 32-row tile, four wavefronts side by side on 32 columns each, so that the
-        // chain of dependent matrix-core operations per K step is a quarter of the 128 x 64 tile's
-        // (the grid does not follow the hint: workgroups without a tile leave at once, and a set that turns out
-        // large still finds the whole chip)
-        hipLaunchKernelGGL((k_transform_f32<1, 4, 1, 1, 3, MODE, STORE>), dim3(c->n_cu / 4, a.Npad / 128), dim3(256), 0, c->stream, a);
-        return;
-    }
-    if (rows_hint <= 2048) {                               // few rows: 64 x 64 tiles, one 32 x 32 block per wavefront
-        hipLaunchKernelGGL((k_transform_f32<2, 2, 1, 1, 3, MODE, STORE>), dim3(c->n_cu / 4, a.Npad / 64),
-                           dim3(256), 0, c->stream, a);
+    if (rows_hint <= SMALL_GEMM_ROWS) {
+        // at most two wavefronts per SIMD for the rows expected; a set that turns out larger finds the chip half full
+        const uint32_t waves = std::min(std::max(small_gemm_waves(a, rows_hint + rows_hint / 2u), c->n_cu), c->n_cu * 8);
+        hipLaunchKernelGGL((k_transform_small<MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
         return;
     }
     if (a.Npad == 96) {                                    // [W_self | W_neigh] of a narrow layer: three 32-column blocks per wavefront
@@ -1133,54 +1127,10 @@ static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
 #undef T_CASE
 }
 
-static TArgs base_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
-    const LayerDev &ly = c->layers[l - 1];
-    TArgs a;
-    a.list = list;
-    a.count_ptr = count_d;
-    a.Hprev = c->H[l - 1];
-    a.X = c->X[l];
-    a.in_meta = c->in_meta;
-    a.mean = (ly.agg == RIPPLE_AGG_MEAN) ? 1 : 0;
-    a.one_plus_eps = 1.0f + ly.eps;
-    a.d_in = ly.d_in;
-    a.tmp_in = nullptr;
-    a.tmp_ld = 0;
-    a.store = c->store;
-    a.Hout = c->H[l];
-    a.D = nullptr;
-    a.d_old = 0;
-    a.tmp_out = nullptr;
-    a.tmp_out_ld = 0;
-    a.split_col = 0;
-    a.N1 = ly.d_out;
-    a.tmp_out2 = nullptr;
-    a.tmp_out2_ld = 0;
-    a.addend = nullptr;
-    a.addend_scaled = 1;
-    a.addend2 = nullptr;
-    a.den = nullptr;
-    a.range_rows = &c->ctr->range_rows;
-    a.a_mode = 0;
-    a.out_mode = 1;
-    a.act = 0;
-    a.W = ly.W0;
-    a.Wt = (c->store && c->opt_bf16_mfma) ? ly.W0h : nullptr;   // bf16 storage: bf16 matrix cores
-    a.wt_ld = ly.K0pad;
-    a.Ws = ly.W0s;                                 // fp32 storage with split products, else null
-    a.ws_plane = (size_t)ly.N0pad * ly.K0pad;
-    a.bias = ly.b0;
-    a.K = ly.K;
-    a.Kpad = ly.K0pad;
-    a.N = ly.d_out;
-    a.Npad = ly.N0pad;
-    return a;
-}
-
 // Project-first layers: P[v] = H^{l-1}[v] W_neigh for the listed vertices, no bias, no activation.
 //   bootstrap: into the layer's T (what every vertex has sent: the aggregates are then summed from it)
 //   otherwise: into c->PD, from where rp_launch_messages turns the rows into this hop's messages
-void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
+TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
     const LayerDev &ly = c->layers[l - 1];
     TArgs a = base_args(c, l, list, count_d);
     a.mean = 0;
@@ -1198,7 +1148,11 @@ void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
     a.Hout = nullptr;
     a.out_mode = 2;
     a.a_mode = 4;
-    launch_t(c, a, bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
+    return a;
+}
+
+void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
+    launch_t(c, rp_project_args(c, l, list, count_d, bootstrap), bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
 }
 
 // Layers handled project-first that also cache their self term: both products of H^{l-1}[v], with W_self (into PS)
@@ -1206,7 +1160,7 @@ void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
 // layer's combined weight matrix [W_self | W_neigh] (second block from column 64 on).
 bool rp_has_project_both(const ripple_ctx *c, uint32_t l) { return c->layers[l - 1].Wc != nullptr; }
 
-void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
+TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
     const LayerDev &ly = c->layers[l - 1];
     TArgs a = base_args(c, l, list, count_d);
     a.mean = 0;
@@ -1228,6 +1182,12 @@ void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, con
     a.N1 = ly.d_out;
     a.tmp_out2 = bootstrap ? ly.T : c->PD;
     a.tmp_out2_ld = bootstrap ? ly.d_out : c->pd_ld;
+    return a;
+}
+
+void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
+    const LayerDev &ly = c->layers[l - 1];
+    TArgs a = rp_project_both_args(c, l, list, count_d, bootstrap);
     const uint32_t hint = bootstrap ? c->n_cap : rp_rows_hint(c, l - 1);
     if (rp_launch_project_both_stream(c, l, list, count_d, a.tmp_out2, a.tmp_out2_ld, hint)) return;
     if (ly.Wc96 && hint > 2048) {                  // many rows: the products are bound by the matrix cores, 96 columns instead of 128
@@ -1256,7 +1216,7 @@ void rp_launch_gat_project(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
 }
 
 // Cached self term of layer l: PS[v] = H^{l-1}[v] W_self for the listed vertices (fp32, no bias).
-void rp_launch_self_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
+TArgs rp_self_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
     const LayerDev &ly = c->layers[l - 1];
     TArgs a = base_args(c, l, list, count_d);
     a.mean = 0;
@@ -1271,7 +1231,11 @@ void rp_launch_self_project(ripple_ctx *c, uint32_t l, const uint32_t *list, con
     a.tmp_out = ly.PS;
     a.tmp_out_ld = ly.d_out;
     a.Hout = nullptr;
-    launch_t(c, a, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
+    return a;
+}
+
+void rp_launch_self_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
+    launch_t(c, rp_self_project_args(c, l, list, count_d), (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
 }
 
 // Re-apply layer l (1-based) to the vertices in `list` (count on the device).

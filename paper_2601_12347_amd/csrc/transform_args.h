@@ -52,3 +52,8 @@ bool rp_launch_stream(ripple_ctx *c, const TArgs &a, uint32_t rows_hint);
 // the same for both products of a narrow project-first layer with a cached self term (second product into out2)
 bool rp_launch_project_both_stream(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, float *out2,
                                    uint32_t ld2, uint32_t rows_hint);
+
+// transform.hip: the arguments of the products of a layer's previous embedding (see the launchers of the same names)
+TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap);
+TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap);
+TArgs rp_self_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d);

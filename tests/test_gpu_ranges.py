@@ -51,3 +51,44 @@ def test_rows_of_any_width(kind, widths, store, self_cache):
             pair.step(ops, payload)
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("kind,widths,store", [("gcn_sum", (12, 20, 8), "f32"), ("sage_mean", (16, 70, 130, 40), "f32"), ("gin_sum", (9, 24, 11), "f32"),
+                                               ("sage_mean", (33, 100, 47), "f32"), ("gcn_mean", (40, 512, 257), "bf16"), ("gcn_sum", (100, 47, 64), "f32")])
+@pytest.mark.parametrize("sizes", [(1, 1, 1, 2), (17, 16, 33, 60), (260, 511, 513, 512)])
+def test_small_pieces_and_hops(kind, widths, store, sizes):
+    """Batches small enough for the few-launch Apply step (up to 512 operations) and hops, on a graph with hubs; vertices are
+    created with their edges; every batch but the first finds hints of the one before, some too small for it."""
+    print("case small", kind, widths, store, sizes, flush=True)
+    pair, graph = make_pair(n=3000, e=16000, d0=widths[0], kind=kind, widths=widths, store=store, seed=31, slack=400, top_share=0.06)
+    mix = {"edge_add": 0.45, "edge_del": 0.3, "feat": 0.2, "vadd": 0.05, "vdel": 0.0}
+    stream = make_stream(pair, graph, mix, 32)
+    try:
+        for b, bs in enumerate(sizes):
+            print(" batch", b, bs, flush=True)
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload)
+        pair.check_graph()
+        pair.check_aggregates(tol=2e-2 if store == "bf16" else None)
+    finally:
+        pair.close()
+
+
+def test_small_piece_at_the_edge_capacity_changes_nothing():
+    print("case small capacity", flush=True)
+    n, k = 200, 400
+    src, dst = np.arange(k, dtype=np.uint32) % n, (np.arange(k, dtype=np.uint32) * 7 + 1 + np.arange(k, dtype=np.uint32) // n) % n
+    pair = Pair(n, n + 4, src, dst.astype(np.uint32), ri.features(n, 5, 1), ri.make_model("gcn_sum", (5, 6, 4), 2), edge_capacity=k + 3)
+    try:
+        have = set(zip(src.tolist(), dst.tolist()))
+        new = [(u, v) for u in range(20) for v in range(20) if u != v and (u, v) not in have]
+        ops = np.array([(ri.OP_EDGE_ADD, u, v, 0) for u, v in new[:4]], dtype=np.uint32)
+        before = pair.gpu_layer(2)
+        with pytest.raises(rp.RippleError) as ei:
+            rp.ripple_apply_updates(pair.ctx, ops, None)
+        assert ei.value.status == rp.binding.RIPPLE_ECAPACITY
+        assert np.array_equal(before, pair.gpu_layer(2))
+        pair.step(ops[:3], None)
+        pair.check_graph()
+    finally:
+        pair.close()
