@@ -330,7 +330,7 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
         LayerDev &ly = c->layers[l];
         void *w[] = {ly.W0, ly.b0, ly.W1, ly.b1, ly.W0h, ly.W1h, ly.bzero, (ly.Wn != ly.W0) ? ly.Wn : nullptr, ly.PS,
                      ly.W0s, ly.W1s, (ly.Wns != ly.W0s) ? ly.Wns : nullptr,
-                     ly.att, ly.P, ly.ssrc, ly.sdst, ly.den, ly.T, ly.Wc, ly.bzero_c, ly.Wc96, ly.Wc96p};
+                     ly.att, ly.P, ly.ssrc, ly.sdst, ly.den, ly.T, ly.Wc, ly.bzero_c, ly.Wc96, ly.Wc96p, ly.W0q, (ly.Wnq != ly.W0q) ? ly.Wnq : nullptr, ly.W1q, ly.Wcq};
         for (void *p : w)
             if (p) hipFree(p);
     }
@@ -353,10 +353,20 @@ extern "C" const char *ripple_last_error(const ripple_ctx *c) { return c ? c->er
 // ---------------------------------------------------------------------------------
 static uint32_t pad_n(uint32_t n) { return n <= 64 ? 64u : (n <= 128 ? 128u : rp_round_up(n, 256)); }
 
+// the padded matrix with k by fours (wave_gemm reads four consecutive k of a column at once)
+static ripple_status upload_quads(ripple_ctx *c, const float *w, uint32_t Kpad, uint32_t Npad, float **out) {
+    std::vector<float> q((size_t)Kpad * Npad);
+    for (uint32_t k = 0; k < Kpad; ++k)
+        for (uint32_t j = 0; j < Npad; ++j) q[((size_t)(k / 4) * Npad + j) * 4 + k % 4] = w[(size_t)k * Npad + j];
+    RP_TRY(dev_alloc(c, out, q.size(), false));
+    RP_HIP(c, hipMemcpy(*out, q.data(), q.size() * 4, hipMemcpyHostToDevice));
+    return RIPPLE_OK;
+}
+
 // planes (optional): the padded matrix as three transposed bf16 matrices [Npad x Kpad] whose sum is W exactly
 // (leading, middle and last 8 significant bits of every weight), for the split products on the bf16 matrix cores
 static ripple_status upload_padded(ripple_ctx *c, const float *w, const float *b, uint32_t K, uint32_t N,
-                                   uint32_t Kpad, uint32_t Npad, float **W_d, float **b_d,
+                                   uint32_t Kpad, uint32_t Npad, float **W_d, float **b_d, float **Wq_d,
                                    unsigned short **planes = nullptr) {
     std::vector<float> wp((size_t)Kpad * Npad, 0.0f), bp(Npad, 0.0f);
     for (uint32_t k = 0; k < K; ++k) memcpy(&wp[(size_t)k * Npad], &w[(size_t)k * N], (size_t)N * 4);
@@ -383,6 +393,7 @@ static ripple_status upload_padded(ripple_ctx *c, const float *w, const float *b
     RP_TRY(dev_alloc(c, W_d, wp.size(), false));
     RP_TRY(dev_alloc(c, b_d, bp.size(), false));
     RP_HIP(c, hipMemcpy(*W_d, wp.data(), wp.size() * 4, hipMemcpyHostToDevice));
+    RP_TRY(upload_quads(c, wp.data(), Kpad, Npad, Wq_d));
     RP_HIP(c, hipMemcpy(*b_d, bp.data(), bp.size() * 4, hipMemcpyHostToDevice));
     return RIPPLE_OK;
 }
@@ -426,7 +437,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         ly.K0pad = rp_round_up(ly.K, 32);
         ly.N0pad = pad_n(n0);
         const bool split = c->store == RIPPLE_STORE_F32 && c->opt_split;
-        RP_TRY(upload_padded(c, s.W0, s.b0, ly.K, n0, ly.K0pad, ly.N0pad, &ly.W0, &ly.b0, split ? &ly.W0s : nullptr));
+        RP_TRY(upload_padded(c, s.W0, s.b0, ly.K, n0, ly.K0pad, ly.N0pad, &ly.W0, &ly.b0, &ly.W0q, split ? &ly.W0s : nullptr));
         if (c->store == RIPPLE_STORE_BF16) {               // transposed bf16 copy for the bf16 matrix cores
             std::vector<uint16_t> wt((size_t)ly.N0pad * ly.K0pad, 0);
             for (uint32_t k = 0; k < ly.K; ++k)
@@ -455,10 +466,11 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
             std::vector<float> zeros(ly.N0pad, 0.0f);
             if (s.self_mode == RIPPLE_SELF_CONCAT) {           // rows d_in .. 2 d_in - 1 of W0
                 RP_TRY(upload_padded(c, s.W0 + (size_t)s.d_in * s.d_out, zeros.data(), s.d_in, s.d_out,
-                                     rp_round_up(s.d_in, 32), ly.N0pad, &ly.Wn, &ly.bzero, split ? &ly.Wns : nullptr));
+                                     rp_round_up(s.d_in, 32), ly.N0pad, &ly.Wn, &ly.bzero, &ly.Wnq, split ? &ly.Wns : nullptr));
                 ly.Wns_ld = rp_round_up(s.d_in, 32);
             } else {
                 ly.Wn = ly.W0;
+                ly.Wnq = ly.W0q;
                 ly.Wns = ly.W0s;
                 ly.Wns_ld = ly.K0pad;
                 RP_TRY(dev_alloc(c, &ly.bzero, (size_t)ly.N0pad, true));
@@ -474,6 +486,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
                 }
             RP_TRY(dev_alloc(c, &ly.Wc, wc.size(), false));
             RP_HIP(c, hipMemcpy(ly.Wc, wc.data(), wc.size() * 4, hipMemcpyHostToDevice));
+            RP_TRY(upload_quads(c, wc.data(), kp, 128, &ly.Wcq));
             RP_TRY(dev_alloc(c, &ly.bzero_c, (size_t)128, true));
             if (s.d_out <= 48) {
                 std::vector<float> w96((size_t)kp * 96, 0.0f);
@@ -501,7 +514,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         if (s.d_hidden) {
             ly.K1pad = rp_round_up(s.d_hidden, 32);
             ly.N1pad = pad_n(s.d_out);
-            RP_TRY(upload_padded(c, s.W1, s.b1, s.d_hidden, s.d_out, ly.K1pad, ly.N1pad, &ly.W1, &ly.b1, split ? &ly.W1s : nullptr));
+            RP_TRY(upload_padded(c, s.W1, s.b1, s.d_hidden, s.d_out, ly.K1pad, ly.N1pad, &ly.W1, &ly.b1, &ly.W1q, split ? &ly.W1s : nullptr));
         }
         c->d[l + 1] = s.d_out;
         c->dmax = std::max(c->dmax, s.d_out);

@@ -102,6 +102,8 @@ struct LayerDev {
     float *att, *P, *ssrc, *sdst, *den;
     // fp32 storage: W0, Wn, W1 as three transposed bf16 planes each (their sum is the matrix), or null
     unsigned short *W0s, *Wns, *W1s;
+    // the padded matrices once more with k by fours, [Kpad / 4][Npad][4] (wave_gemm); Wnq may alias W0q
+    float *W0q, *Wnq, *W1q, *Wcq;
     uint32_t Wns_ld;                          // row stride of the Wn planes (those of W0: K0pad, of W1: K1pad)
 };
 

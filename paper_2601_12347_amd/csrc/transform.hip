@@ -284,6 +284,7 @@ static TArgs base_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
     a.out_mode = 1;
     a.act = 0;
     a.W = ly.W0;
+    a.Wq = ly.W0q;
     a.Wt = (c->store && c->opt_bf16_mfma) ? ly.W0h : nullptr;   // bf16 storage: bf16 matrix cores
     a.wt_ld = ly.K0pad;
     a.Ws = ly.W0s;                                 // fp32 storage with split products, else null
@@ -1068,17 +1069,19 @@ static void launch_split(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t ro
     }
 }
 
-template <int MODE, int STORE>
-__global__ __launch_bounds__(256) void k_transform_small(TArgs a) {
-    small_gemm<MODE, STORE>(a, (blockIdx.x * 256u + threadIdx.x) >> 6, gridDim.x * 4u);
+template <int CT, int MODE, int STORE>
+__global__ __launch_bounds__(256) void k_transform_wave(TArgs a) {
+    wave_gemm<CT, MODE, STORE>(a, (blockIdx.x * 256u + threadIdx.x) >> 6, gridDim.x * 4u);
 }
 
 template <int MODE, int STORE>
 static void launch_fast(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t rows_hint) {
-    if (rows_hint <= SMALL_GEMM_ROWS) {
-        // at most two wavefronts per SIMD for the rows expected; a set that turns out larger finds the chip half full
-        const uint32_t waves = std::min(std::max(small_gemm_waves(a, rows_hint + rows_hint / 2u), c->n_cu), c->n_cu * 8);
-        hipLaunchKernelGGL((k_transform_small<MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
+    if (a.Wq && wave_gemm_waves(a, rows_hint, 2) <= WAVE_GEMM_2) {
+        // wavefronts for half as many rows again as expected; a set that turns out larger still finds every SIMD busy
+        const bool one = wave_gemm_waves(a, rows_hint, 1) <= WAVE_GEMM_1;
+        const uint32_t waves = std::max(wave_gemm_waves(a, rows_hint + rows_hint / 2u, one ? 1u : 2u), c->n_cu * 4);
+        if (one) hipLaunchKernelGGL((k_transform_wave<1, MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
+        else hipLaunchKernelGGL((k_transform_wave<2, MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
         return;
     }
     if (a.Npad == 96) {                                    // [W_self | W_neigh] of a narrow layer: three 32-column blocks per wavefront
@@ -1135,6 +1138,7 @@ TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uin
     TArgs a = base_args(c, l, list, count_d);
     a.mean = 0;
     a.W = ly.Wn;
+    a.Wq = ly.Wnq;
     a.Wt = nullptr;                                // messages are differences of such products: fp32 path also for bf16 rows
     a.Ws = ly.Wns;
     a.wt_ld = ly.Wns_ld;
@@ -1165,6 +1169,7 @@ TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     TArgs a = base_args(c, l, list, count_d);
     a.mean = 0;
     a.W = ly.Wc;
+    a.Wq = ly.Wcq;
     a.Wt = nullptr;
     a.Ws = nullptr;
     a.bias = ly.bzero_c;
@@ -1190,8 +1195,9 @@ void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, con
     TArgs a = rp_project_both_args(c, l, list, count_d, bootstrap);
     const uint32_t hint = bootstrap ? c->n_cap : rp_rows_hint(c, l - 1);
     if (rp_launch_project_both_stream(c, l, list, count_d, a.tmp_out2, a.tmp_out2_ld, hint)) return;
-    if (ly.Wc96 && hint > 2048) {                  // many rows: the products are bound by the matrix cores, 96 columns instead of 128
+    if (ly.Wc96 && wave_gemm_waves(a, hint, 2) > WAVE_GEMM_2) {                  // many rows: the products are bound by the matrix cores, 96 columns instead of 128
         a.W = ly.Wc96;
+        a.Wq = nullptr;
         a.N = 48 + ly.d_out;
         a.Npad = 96;
         a.split_col = 48;
@@ -1221,6 +1227,7 @@ TArgs rp_self_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     TArgs a = base_args(c, l, list, count_d);
     a.mean = 0;
     a.W = ly.W0;                                   // W_self: the first d_in rows (the kernel zeroes k >= K)
+    a.Wq = ly.W0q;
     a.Wt = nullptr;
     a.bias = ly.bzero;
     a.K = ly.d_in;
@@ -1273,6 +1280,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     if (ly.selfc) {                              // act((x * scale) W_neigh + PS[v] + b)
         a.a_mode = 0;
         a.W = ly.Wn;
+        a.Wq = ly.Wnq;
         a.Wt = nullptr;
         a.Ws = ly.Wns;
         a.wt_ld = ly.Wns_ld;
@@ -1306,6 +1314,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     s2.tmp_ld = ly.d_hidden;
     s2.mean = 0;
     s2.W = ly.W1;
+    s2.Wq = ly.W1q;
     s2.Wt = nullptr;
     s2.Ws = ly.W1s;
     s2.wt_ld = ly.K1pad;

@@ -18,6 +18,7 @@ struct TArgs {
     const float *tmp_in;
     uint32_t tmp_ld;
     const float *W;                // [Kpad x Npad], zero padded
+    const float *Wq;               // the same with k by fours, [Kpad / 4][Npad][4] (wave_gemm), or null
     const float *bias;             // [Npad]
     const __hip_bfloat16 *Wt;      // bf16 copy of W, transposed [Npad x Kpad] (k contiguous), or null
     const unsigned short *Ws;      // fp32 storage: W as three transposed bf16 planes (W = plane 0 + plane 1 + plane 2), or null
