@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void k_hop_small(HopArgs a) {
         push_edges<NJ, 0>(a.list, a.count_ptr, a.eoff, a.D, nullptr, a.ldd, a.d, a.out_meta, a.out_pool, a.X,
                           (blockIdx.x - a.nb_walk) * 4u + wave, a.nb_push * 4u);
     } else {
-        wave_gemm<1, 4, STORE>(a.g, (blockIdx.x - a.nb_walk - a.nb_push) * 4u + wave, (gridDim.x - a.nb_walk - a.nb_push) * 4u);
+        wave_gemm<4, STORE>(a.g, (blockIdx.x - a.nb_walk - a.nb_push) * 4u + wave, (gridDim.x - a.nb_walk - a.nb_push) * 4u);
     }
 }
 
@@ -77,7 +77,7 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
     if (ly.proj || ly.selfc) {
         a.g = both ? rp_project_both_args(c, l, a.list, a.count_ptr, false)
                    : (ly.proj ? rp_project_args(c, l, a.list, a.count_ptr, false) : rp_self_project_args(c, l, a.list, a.count_ptr));
-        if (ly.W0s || wave_gemm_waves(a.g, rows, 1) > WAVE_GEMM_1) {   // more rows than one block per wavefront is good for: launches of their own
+        if (ly.W0s || wave_gemm_waves(a.g, rows) > WAVE_GEMM_MAX) {   // many rows: launches of their own
             if (both) {
                 rp_launch_project_both(c, l, a.list, a.count_ptr, false);
             } else {
@@ -87,7 +87,7 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
             a.g.W = nullptr;
         } else {
             if (ly.proj && ly.selfc && !both) rp_launch_self_project(c, l, a.list, a.count_ptr);
-            nb_gemm = std::min(rp_div_up(wave_gemm_waves(a.g, rows + rows / 2u, 1), 4), c->n_cu * 2);
+            nb_gemm = std::min(rp_div_up(wave_gemm_waves(a.g, rows + rows / 2u), 4), c->n_cu * 2);
         }
     }
     const dim3 grid(a.nb_walk + a.nb_push + nb_gemm), block(256);

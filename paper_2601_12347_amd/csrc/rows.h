@@ -90,36 +90,31 @@ __device__ __forceinline__ floatx4 finish_raw(const TArgs &a, floatx4 p, floatx4
 // few rows
 // ---------------------------------------------------------------------------------
 // A hop of some hundred or thousand rows leaves most of the chip idle and is paced by the chain of dependent steps: list entry,
-// row, products, store. Here every wavefront has CT blocks of 16 x 16 outputs to itself, side by side (MFMA 16x16x4, fp32): a K
-// of 256 is 64 products one after the other for one block, a microsecond, where a 32 x 32 block takes four; there is no LDS
-// and no barrier, so a wavefront waits for its own loads only; rows and weights are requested STAGES - 1 steps of 16 k ahead. A
-// lane holds four consecutive k of its row (one 16-byte load), which the four products of a step take one each, so a step's
-// k are numbered lane group first: k = 4 * (lane / 16) + i for product i; the weights lie in that order in a.Wq (k by fours).
-// What bounds it is the L2: 32 KB per block at a K of 256. Measured (256 -> 256, launch included): 1,024 rows 8.0 us with one
-// block, 9.9 with two; 8,000 rows 33.6 / 22.4; the tiled kernels take 25.4 and 28.6, and less from 12,000 rows on. So: one block
-// while that gives each SIMD at most two wavefronts, two blocks while that gives it just under four, else the tiled kernels.
-#define WAVE_GEMM_1 2048u
-#define WAVE_GEMM_2 4000u
-template <int CT, int MODE, int STORE>
+// row, products, store. Here every wavefront has one 16 x 16 block of the output to itself (MFMA 16x16x4, fp32): a K of 256 is
+// 64 products one after the other, a microsecond, where a 32 x 32 block takes four; there is no LDS and no barrier, so a
+// wavefront waits for its own loads only; rows and weights are requested five steps of 16 k ahead. A lane holds four
+// consecutive k of its row (one 16-byte load), which the four products of a step take one each, so a step's k are
+// numbered lane group first: k = 4 * (lane / 16) + i for product i; the weights lie in that order in a.Wq (k by fours).
+// What bounds more rows is the L2, 32 KB per block at a K of 256. Measured (256 -> 256, launch included): 64 rows 7.0 us,
+// 1,024 rows 7.5, 2,048 rows 10.6, 3,000 rows 14.0; the 32 x 128 tiles take 11.0, 11.0, 11.4 and 11.7. So: up to two
+// wavefronts per SIMD.
+#define WAVE_GEMM_MAX 2048u
+template <int MODE, int STORE>
 __device__ __forceinline__ void wave_gemm(const TArgs &a, uint32_t gw, uint32_t nw) {
-    constexpr int STAGES = CT == 1 ? 6 : 3;                  // (more registers cost two-block wavefronts their company: 8,000 rows 28.4 us)
+    constexpr int STAGES = 6;
     constexpr bool TWO = (MODE == 2) || (MODE == 1 && STORE == 1);
     const uint32_t count = *a.count_ptr;
     const int lane = (int)(threadIdx.x & 63u);
     const uint32_t sub = (uint32_t)lane & 15u, grp = (uint32_t)lane >> 4;
-    const uint32_t n_ct = (a.N + 16u * CT - 1u) / (16u * CT), n_tiles = (count + 15u) / 16u * n_ct;
+    const uint32_t n_ct = (a.N + 15u) / 16u, n_tiles = (count + 15u) / 16u * n_ct;
     const floatx4 *Wq = (const floatx4 *)a.Wq;
     for (uint32_t tile = gw; tile < n_tiles; tile += nw) {
-        const uint32_t row0 = tile / n_ct * 16u, col0 = tile % n_ct * (16u * CT) + sub;
+        const uint32_t row0 = tile / n_ct * 16u, col = tile % n_ct * 16u + sub;
         const uint32_t slot = min(row0 + sub, count - 1u), v = a.list[slot];
-        uint32_t wcol[CT];                                   // (blocks past the matrix read its last one; not stored)
-#pragma unroll
-        for (int j = 0; j < CT; ++j) wcol[j] = min(col0 + 16u * j, a.Npad - 16u + sub);
-        floatx4 ra[STAGES], rq[TWO ? STAGES : 1], rb[STAGES][CT];
+        floatx4 ra[STAGES], rq[TWO ? STAGES : 1], rb[STAGES];
         auto request = [&](uint32_t k0, int s) {
             const uint32_t k = min(k0, a.Kpad - 16u) + 4u * grp;     // past the end: the last step once more, not used
-#pragma unroll
-            for (int j = 0; j < CT; ++j) rb[s][j] = Wq[(size_t)(k >> 2) * a.Npad + wcol[j]];
+            rb[s] = Wq[(size_t)(k >> 2) * a.Npad + col];
             floatx4 q = (floatx4)(0.0f);
             fetch_raw<MODE, STORE>(a, v, slot, k, ra[s], q);
             if constexpr (TWO) rq[s] = q;
@@ -128,29 +123,21 @@ __device__ __forceinline__ void wave_gemm(const TArgs &a, uint32_t gw, uint32_t 
         for (int s = 0; s < STAGES; ++s) request(16u * s, s);
         const uint32_t deg = a.mean ? a.in_meta[v].y : 1u;
         const float scale = 1.0f / (float)(deg > 1u ? deg : 1u);
-        // what this lane stores (four rows and one column per block) is combined with other rows: requested up front by
-        // one-block wavefronts, which are paced by latency, after the products by the others
+        // what this lane stores (four rows, one column) is combined with other rows: requested up front
         uint32_t ov[4];
-        float add[CT][4], old[CT][4], osc[4];
+        float add[4], old[4], osc[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) ov[r] = a.list[min(row0 + 4u * grp + r, count - 1u)];
-        auto others = [&]() {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const uint32_t dg = (a.mean && a.addend && a.addend_scaled) ? a.in_meta[ov[r]].y : 1u;
             osc[r] = 1.0f / (float)(dg > 1u ? dg : 1u);
-#pragma unroll
-            for (int j = 0; j < CT; ++j) {
-                const size_t at = (size_t)ov[r] * a.N + min(col0 + 16u * j, a.N - 1u);
-                add[j][r] = (a.out_mode == 1 && a.addend) ? a.addend[at] : 0.0f;
-                old[j][r] = (a.out_mode == 1 && a.D) ? rp_load_h(a.Hout, a.store, at) : 0.0f;
-            }
+            const size_t at = (size_t)ov[r] * a.N + min(col, a.N - 1u);
+            add[r] = (a.out_mode == 1 && a.addend) ? a.addend[at] : 0.0f;
+            old[r] = (a.out_mode == 1 && a.D) ? rp_load_h(a.Hout, a.store, at) : 0.0f;
         }
-        };
-        if (CT == 1) others();
-        floatx4 acc[CT], odd[CT];                            // one block: two sums, so that its products do not wait for one another
-#pragma unroll
-        for (int j = 0; j < CT; ++j) acc[j] = odd[j] = (floatx4)(0.0f);
+        const float bias = a.bias[col];
+        floatx4 even = (floatx4)(0.0f), odd = (floatx4)(0.0f);   // two sums, so that the products do not wait for one another
         for (uint32_t kb = 0; kb < a.Kpad; kb += 16u * STAGES) {
 #pragma unroll
             for (int s = 0; s < STAGES; ++s) {
@@ -159,46 +146,39 @@ __device__ __forceinline__ void wave_gemm(const TArgs &a, uint32_t gw, uint32_t 
                 floatx4 q = (floatx4)(0.0f);
                 if constexpr (TWO) q = rq[s];
                 const floatx4 x = finish_raw<MODE, STORE>(a, ra[s], q, k0 + 4u * grp, scale);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int j = 0; j < CT; ++j) {
-                        floatx4 &c = (CT == 1 && (e & 1)) ? odd[j] : acc[j];
-                        c = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], rb[s][j][e], c, 0, 0, 0);
-                    }
+                even = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, rb[s].x, even, 0, 0, 0);
+                odd = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, rb[s].y, odd, 0, 0, 0);
+                even = __builtin_amdgcn_mfma_f32_16x16x4f32(x.z, rb[s].z, even, 0, 0, 0);
+                odd = __builtin_amdgcn_mfma_f32_16x16x4f32(x.w, rb[s].w, odd, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);           // (the scheduler would sink the requests to their use)
                 request(k0 + 16u * STAGES, s);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (CT > 1) others();
+        if (col >= a.N || (a.split_col && col >= a.N1 && col < a.split_col)) continue;   // padding columns
 #pragma unroll
-        for (int j = 0; j < CT; ++j) {
-            const uint32_t col = col0 + 16u * j;
-            if (col >= a.N || (a.split_col && col >= a.N1 && col < a.split_col)) continue;   // padding columns
-            const float bias = a.bias[col];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t os = row0 + 4u * grp + r;
-                if (os >= count) continue;
-                float z = acc[j][r] + odd[j][r] + bias + add[j][r] * osc[r];
-                if (a.act == RIPPLE_ACT_RELU) z = z > 0.0f ? z : 0.0f;
-                if (a.out_mode != 1) {
-                    const size_t orow = a.out_mode == 0 ? os : ov[r];
-                    if (a.split_col && col >= a.split_col) a.tmp_out2[orow * a.tmp_out2_ld + (col - a.split_col)] = z;
-                    else a.tmp_out[orow * a.tmp_out_ld + col] = z;
-                    continue;
-                }
-                const size_t at = (size_t)ov[r] * a.N + col;
-                if (a.store) {
-                    const __hip_bfloat16 zr = __float2bfloat16(z);
-                    z = __bfloat162float(zr);
-                    ((__hip_bfloat16 *)a.Hout)[at] = zr;
-                } else {
-                    ((float *)a.Hout)[at] = z;
-                }
-                if (a.D) a.D[at] = a.d_old ? old[j][r] : z - old[j][r];
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t os = row0 + 4u * grp + r;
+            if (os >= count) continue;
+            float z = even[r] + odd[r] + bias + add[r] * osc[r];
+            if (a.act == RIPPLE_ACT_RELU) z = z > 0.0f ? z : 0.0f;
+            if (a.out_mode != 1) {
+                const size_t orow = a.out_mode == 0 ? os : ov[r];
+                if (a.split_col && col >= a.split_col) a.tmp_out2[orow * a.tmp_out2_ld + (col - a.split_col)] = z;
+                else a.tmp_out[orow * a.tmp_out_ld + col] = z;
+                continue;
             }
+            const size_t at = (size_t)ov[r] * a.N + col;
+            if (a.store) {
+                const __hip_bfloat16 zr = __float2bfloat16(z);
+                z = __bfloat162float(zr);
+                ((__hip_bfloat16 *)a.Hout)[at] = zr;
+            } else {
+                ((float *)a.Hout)[at] = z;
+            }
+            if (a.D) a.D[at] = a.d_old ? old[r] : z - old[r];
         }
     }
 }
-// wavefronts that `rows` rows take with ct blocks each
-static inline uint32_t wave_gemm_waves(const TArgs &a, uint32_t rows, uint32_t ct) { return rp_div_up(rows ? rows : 1u, 16u) * rp_div_up(a.N, 16u * ct); }
+// wavefronts (= 16 x 16 blocks) that `rows` rows take
+static inline uint32_t wave_gemm_waves(const TArgs &a, uint32_t rows) { return rp_div_up(rows ? rows : 1u, 16u) * rp_div_up(a.N, 16u); }

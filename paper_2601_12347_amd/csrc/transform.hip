@@ -848,8 +848,6 @@ __global__ __launch_bounds__(256, 2) void k_transform_bf16(TArgs a) {
     }
 }
 
-// narrow: few rows expected. One workgroup then covers 128 rows x 64 columns and the columns are
-// spread over blockIdx.y, which shortens the serial chain of matrix-core work per tile fourfold.
 // The grid holds about one workgroup per expected tile (a grid-stride loop covers any excess):
 // workgroups that start at different times do not all sit in their memory phase at once, which a
 // grid of resident, persistent workgroups does.
@@ -859,17 +857,22 @@ static uint32_t tile_grid(const ripple_ctx *c, uint32_t rows_hint, uint32_t bm, 
     return (uint32_t)std::max<uint64_t>(floor_wg, std::min(want, cap));
 }
 
+// tiles of 64 x 256 (128 x 128) where there are enough for every compute unit to have several, small ones below
 template <int MODE>
-static void launch_bf16(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t rows_hint) {
-    if (a.Npad >= 256 && !narrow) {
+static void launch_bf16(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
+    const bool many = rows_hint >= 64u * 4u * c->n_cu;
+    if (a.Npad >= 256 && many) {
         hipLaunchKernelGGL((k_transform_bf16<1, 4, 2, 2, 3, MODE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 256),
                            dim3(256), 0, c->stream, a);
-    } else if (a.Npad == 128 && !narrow) {
+    } else if (a.Npad == 128 && many) {
         hipLaunchKernelGGL((k_transform_bf16<2, 2, 2, 2, 3, MODE>), dim3(tile_grid(c, rows_hint, 128, c->n_cu * 2), 1), dim3(256), 0,
                            c->stream, a);
+    } else if (a.Npad % 128 == 0) {
+        hipLaunchKernelGGL((k_transform_bf16<1, 4, 1, 1, 3, MODE>), dim3(tile_grid(c, rows_hint, 32, c->n_cu * 2), a.Npad / 128), dim3(256), 0,
+                           c->stream, a);
     } else {
-        hipLaunchKernelGGL((k_transform_bf16<4, 1, 1, 2, 3, MODE>),
-                           dim3(tile_grid(c, rows_hint, 128, narrow ? c->n_cu : c->n_cu * 2), a.Npad / 64), dim3(256), 0, c->stream, a);
+        hipLaunchKernelGGL((k_transform_bf16<2, 2, 1, 1, 3, MODE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 64), dim3(256), 0,
+                           c->stream, a);
     }
 }
 
@@ -1069,33 +1072,27 @@ static void launch_split(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t ro
     }
 }
 
-template <int CT, int MODE, int STORE>
+template <int MODE, int STORE>
 __global__ __launch_bounds__(256) void k_transform_wave(TArgs a) {
-    wave_gemm<CT, MODE, STORE>(a, (blockIdx.x * 256u + threadIdx.x) >> 6, gridDim.x * 4u);
+    wave_gemm<MODE, STORE>(a, (blockIdx.x * 256u + threadIdx.x) >> 6, gridDim.x * 4u);
 }
 
+// Tiles of 32 x 128 (64 x 64 where the matrix is 64 columns wide): a wavefront's chain of products per K step is short and several
+// workgroups fit a compute unit, so one's memory phase is another's products, and the last round of workgroups wastes
+// little. Measured for 256 -> 256 against tiles of 64 x 256: 3,000 rows 11.7 / 28.7 us, 20,000 rows 35 / 50, 100,000 rows 159 /
+// 187, 600,000 rows 948 / 929; 256 -> 47 against 128 x 64: 8,000 rows 12.1 / 17.8, 150,000 rows 68 / 84.
 template <int MODE, int STORE>
-static void launch_fast(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t rows_hint) {
-    if (a.Wq && wave_gemm_waves(a, rows_hint, 2) <= WAVE_GEMM_2) {
+static void launch_fast(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
+    if (a.Wq && wave_gemm_waves(a, rows_hint) <= WAVE_GEMM_MAX) {
         // wavefronts for half as many rows again as expected; a set that turns out larger still finds every SIMD busy
-        const bool one = wave_gemm_waves(a, rows_hint, 1) <= WAVE_GEMM_1;
-        const uint32_t waves = std::max(wave_gemm_waves(a, rows_hint + rows_hint / 2u, one ? 1u : 2u), c->n_cu * 4);
-        if (one) hipLaunchKernelGGL((k_transform_wave<1, MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
-        else hipLaunchKernelGGL((k_transform_wave<2, MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
-        return;
-    }
-    if (a.Npad == 96) {                                    // [W_self | W_neigh] of a narrow layer: three 32-column blocks per wavefront
-        hipLaunchKernelGGL((k_transform_f32<4, 1, 1, 3, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 128, c->n_cu * 2), 1), dim3(256),
-                           0, c->stream, a);
-    } else if (a.Npad >= 256 && !narrow) {
-        hipLaunchKernelGGL((k_transform_f32<1, 4, 2, 2, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 256),
-                           dim3(256), 0, c->stream, a);
-    } else if (a.Npad == 128 && !narrow) {
-        hipLaunchKernelGGL((k_transform_f32<2, 2, 2, 2, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 128, c->n_cu * 2), 1), dim3(256),
+        const uint32_t waves = std::max(wave_gemm_waves(a, rows_hint + rows_hint / 2u), c->n_cu * 4);
+        hipLaunchKernelGGL((k_transform_wave<MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
+    } else if (a.Npad % 128 == 0) {
+        hipLaunchKernelGGL((k_transform_f32<1, 4, 1, 1, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 32, c->n_cu * 2), a.Npad / 128), dim3(256),
                            0, c->stream, a);
     } else {
-        hipLaunchKernelGGL((k_transform_f32<4, 1, 1, 2, 3, MODE, STORE>),
-                           dim3(tile_grid(c, rows_hint, 128, narrow ? c->n_cu : c->n_cu * 2), a.Npad / 64), dim3(256), 0, c->stream, a);
+        hipLaunchKernelGGL((k_transform_f32<2, 2, 1, 1, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 64), dim3(256),
+                           0, c->stream, a);
     }
 }
 
@@ -1111,10 +1108,10 @@ static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
     }
 #define T_CASE(M)                                            \
     case M:                                                  \
-        if (a.store && a.Wt) launch_bf16<M>(c, a, narrow, rows_hint);   \
-        else if (a.store) launch_fast<M, 1>(c, a, narrow, rows_hint);   \
+        if (a.store && a.Wt) launch_bf16<M>(c, a, rows_hint);           \
+        else if (a.store) launch_fast<M, 1>(c, a, rows_hint);   \
         else if (a.Ws) launch_split<M>(c, a, narrow, rows_hint);        \
-        else launch_fast<M, 0>(c, a, narrow, rows_hint);                \
+        else launch_fast<M, 0>(c, a, rows_hint);                \
         break;
     switch (a.a_mode) {
         T_CASE(0)
@@ -1122,9 +1119,9 @@ static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
         T_CASE(2)
         T_CASE(4)
     default:
-        if (a.store) launch_fast<3, 1>(c, a, narrow, rows_hint);   // compact fp32 rows; the storage type only shapes the epilogue
+        if (a.store) launch_fast<3, 1>(c, a, rows_hint);   // compact fp32 rows; the storage type only shapes the epilogue
         else if (a.Ws) launch_split<3>(c, a, narrow, rows_hint);
-        else launch_fast<3, 0>(c, a, narrow, rows_hint);
+        else launch_fast<3, 0>(c, a, rows_hint);
         break;
     }
 #undef T_CASE
@@ -1195,13 +1192,6 @@ void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, con
     TArgs a = rp_project_both_args(c, l, list, count_d, bootstrap);
     const uint32_t hint = bootstrap ? c->n_cap : rp_rows_hint(c, l - 1);
     if (rp_launch_project_both_stream(c, l, list, count_d, a.tmp_out2, a.tmp_out2_ld, hint)) return;
-    if (ly.Wc96 && wave_gemm_waves(a, hint, 2) > WAVE_GEMM_2) {                  // many rows: the products are bound by the matrix cores, 96 columns instead of 128
-        a.W = ly.Wc96;
-        a.Wq = nullptr;
-        a.N = 48 + ly.d_out;
-        a.Npad = 96;
-        a.split_col = 48;
-    }
     launch_t(c, a, hint);
 }
 
