@@ -317,7 +317,7 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
     hipStreamSynchronize(c->stream);
     void *ptrs[] = {c->out_meta, c->in_meta, c->out_capv, c->in_capv, c->vstate, c->pend_out, c->pend_in, c->dead_out,
                     c->dead_in, c->hole_out, c->hole_in, c->out_pool, c->in_pool, c->in_w, c->alive, c->part_cnt, c->part_deg, c->part_ideg, c->ioff[0], c->ctr, c->D[0], c->D[1],
-                    c->tmp, c->PD, c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->seg_v, c->seg_done, c->seg_base, c->seg_r, c->seg_part, c->bm[0], c->rep[0], c->list[0], c->eoff[0], c->all_list, c->ioff_all, c->mk, c->ops_d,
+                    c->tmp, c->PD, c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->gat_mag, c->gat_rec, c->seg_v, c->seg_done, c->seg_base, c->seg_r, c->seg_part, c->bm[0], c->rep[0], c->list[0], c->eoff[0], c->all_list, c->ioff_all, c->mk, c->ops_d,
                     c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_s, c->exp_a,
                     c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->tail_ids, c->tail_q, c->tail_w, c->sk_in, c->sk_out, c->sv_in, c->sv_out, c->sort_tmp, c->gather_d, c->gather_ids, c->pk_a, c->pk_b, c->pv_a, c->pv_b, c->pair_tmp};
     for (void *p : ptrs)
@@ -457,7 +457,8 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
             RP_TRY(dev_alloc(c, &ly.att, (size_t)2 * s.d_out, false));
             RP_HIP(c, hipMemcpy(ly.att, s.att, (size_t)2 * s.d_out * 4, hipMemcpyHostToDevice));
             RP_TRY(dev_alloc(c, &ly.bzero, (size_t)ly.N0pad, true));
-            RP_TRY(dev_alloc(c, &ly.P, (size_t)c->n_cap * s.d_out, true));
+            ly.ldp = s.d_out <= 63 ? rp_round_up(s.d_out + 1, 16) : s.d_out;
+            RP_TRY(dev_alloc(c, &ly.P, (size_t)c->n_cap * ly.ldp, true));
             RP_TRY(dev_alloc(c, &ly.ssrc, (size_t)c->n_cap, true));
             RP_TRY(dev_alloc(c, &ly.sdst, (size_t)c->n_cap, true));
             RP_TRY(dev_alloc(c, &ly.den, (size_t)c->n_cap, true));
@@ -529,10 +530,12 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
     {
         uint32_t aw = 0;                                 // widest attention layer
         for (uint32_t l = 1; l <= c->L; ++l)
-            if (rp_layer_attn(c, l)) aw = std::max(aw, c->d[l]);
+            if (rp_layer_attn(c, l)) aw = std::max(aw, c->layers[l - 1].ldp);
         if (aw) {
             RP_TRY(dev_alloc(c, &c->Pold, n * aw, true));
             RP_TRY(dev_alloc(c, &c->sold, n, true));
+            RP_TRY(dev_alloc(c, &c->gat_mag, n, true));
+            RP_TRY(dev_alloc(c, &c->gat_rec, n, true));
         }
     }
     {
@@ -989,7 +992,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
                 rp_launch_frontier_mark(c, l, false);
                 rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
                 t = rp_timer_begin(c);
-                rp_launch_frontier_compact(c, l, true, l < c->L, false, multi);
+                rp_launch_frontier_compact(c, l, true, l < c->L, true, multi);
                 rp_timer_end(c, t, RIPPLE_PH_COMPACT, (int)l);
             }
             t = rp_timer_begin(c);

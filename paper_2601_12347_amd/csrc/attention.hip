@@ -8,10 +8,12 @@
 // recomputes numerator and denominator from all its in-neighbours; any other vertex of A_l receives, per
 // changed in-neighbour u, the message of the paper: <w_new P_new[u] - w_old P_old[u], w_new - w_old>.
 // A vertex whose in-edges changed recomputes if its in-row is short; with a long in-row each changed edge
-// is a message too (its pre-batch weight and row, added or taken away). One owner per destination (a
-// wavefront; a workgroup for long in-rows; a workgroup per 512-entry segment when a very long row is
-// recomputed, the last of them adding the segments up in order), no atomics on rows.
+// is a message too (its pre-batch weight and row, added or taken away). Small hops have one owner per
+// destination (a wavefront; a workgroup for long in-rows; a workgroup per 512-entry segment when a very long
+// row is recomputed, the last of them adding the segments up in order), large ones are cut over edges.
 #include "kernels.h"
+#include "pull_scan.h"
+#include <algorithm>
 
 #define GAT_SLOPE 0.2f
 #define GAT_LONG 256u
@@ -19,20 +21,19 @@
 #define GAT_EDGE_SCAN 32768u      // longest list of changed edges a sink's workgroup searches; longer: recompute
 
 struct GatArgs {
-    const uint32_t *list;          // A_l, or every live vertex (bootstrap), or the queue of long rows
+    const uint32_t *list;          // A_l, or a queue of rows
     const uint32_t *count_ptr;
-    uint32_t *queue, *queue_count;
     const uint2 *in_meta;
     const uint32_t *in_pool;
     const uint32_t *bm_prev;       // A_{l-1}
     const uint32_t *bm_sink, *bm_vadd;
-    const float *P, *Pold;         // projected rows now / before the batch (the latter valid on A_{l-1})
+    const float *P, *Pold;         // projected rows now / before the batch (the latter valid on A_{l-1}), row stride ldp
+    uint32_t ldp;
     const float *ssrc, *sold, *sdst;
     uint32_t d;                    // d_out
     float *X, *den;
-    int all;                       // bootstrap: recompute every listed row
-    int few;                       // few rows this hop: latency of the longest row matters, not throughput
-    uint32_t long_min;             // in-rows longer than this (at most GAT_LONG) go to the workgroup kernel
+    int all;                       // recompute every listed row (the queue of cancelled rows)
+    uint32_t long_min;             // in-rows longer than this are the workgroup role's
     uint32_t split_min;            // in-rows of at least this many entries are recomputed in segments (k_gat_scatter_seg)
     uint32_t *n_big, *n_seg;       // split rows / queued segments of this hop
     uint32_t *seg_v, *seg_done, *seg_base, *seg_r;
@@ -85,8 +86,8 @@ __device__ __forceinline__ float gat_block(const GatArgs &a, uint32_t my_u, bool
             for (int j = 0; j < NJ; ++j) {
                 const uint32_t col = lane + 64 * j;
                 const bool in = g < n && col < d;
-                rn[g][j] = in ? a.P[(size_t)u * d + col] : 0.0f;
-                if (!recompute) ro[g][j] = in ? a.Pold[(size_t)u * d + col] : 0.0f;
+                rn[g][j] = in ? a.P[(size_t)u * a.ldp + col] : 0.0f;
+                if (!recompute) ro[g][j] = in ? a.Pold[(size_t)u * a.ldp + col] : 0.0f;
             }
         }
 #pragma unroll
@@ -124,7 +125,7 @@ __device__ __forceinline__ float gat_edge_block(const GatArgs &a, uint32_t my_u,
         mask &= mask - 1;
         const uint32_t u = __shfl(my_u, k);
         const float wk = __shfl(w, k) * __shfl(my_sgn, k);
-        const float *row = (__shfl((int)from_old, k) ? a.Pold : a.P) + (size_t)u * d;
+        const float *row = (__shfl((int)from_old, k) ? a.Pold : a.P) + (size_t)u * a.ldp;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             const uint32_t col = lane + 64 * j;
@@ -157,11 +158,8 @@ __device__ __forceinline__ void gat_wave_role(const GatArgs &a, uint32_t gw, uin
     for (uint32_t i = gw; i < count; i += nw) {
         const uint32_t v = a.list[i];
         const uint2 m = a.in_meta[v];
-        if (m.y > a.long_min) {                                // queued here, or already when the hop's vertices were listed
-            if (lane == 0 && a.queue) a.queue[atomicAdd(a.queue_count, 1u)] = v;
-            continue;
-        }
-        bool recompute = a.all || rp_bit(a.bm_prev, v) || rp_bit(a.bm_sink, v) || rp_bit(a.bm_vadd, v);
+        if (m.y > a.long_min) continue;                        // queued when the hop's vertices were listed
+        bool recompute = rp_bit(a.bm_prev, v) || rp_bit(a.bm_sink, v) || rp_bit(a.bm_vadd, v);
         const float t_v = a.sdst[v];
         float acc[NJ];
         float dsum;
@@ -192,11 +190,6 @@ __device__ __forceinline__ void gat_wave_role(const GatArgs &a, uint32_t gw, uin
         }
         if (lane == 0) a.den[v] = recompute ? dsum : a.den[v] + dsum;
     }
-}
-
-template <int NJ>
-__global__ __launch_bounds__(256) void k_gat_scatter(GatArgs a) {
-    gat_wave_role<NJ>(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
 }
 
 // one workgroup of TEAM wavefronts per long in-row; partial sums meet in LDS and are added in wavefront order.
@@ -278,13 +271,6 @@ __device__ __forceinline__ void gat_team_role(const GatArgs &a, uint32_t bid, ui
                     dsum += gat_block<NJ, GR, true>(a, my_u, valid, t_v, acc, mag);
                 }
             } else {
-                if (!a.few) {                                  // the chip is full: block after block
-                    for (uint32_t base = 64u * wave; base < m.y; base += 64u * TEAM) {
-                        const uint32_t e = base + lane;
-                        const uint32_t my_u = (e < m.y) ? a.in_pool[m.x + e] : 0u;
-                        dsum += gat_block<NJ, G, false>(a, my_u, e < m.y, t_v, acc, mag);
-                    }
-                } else
                 for (uint32_t base = 64u * wave; base < m.y; base += 64u * TEAM * IDS) {
                     uint32_t u[IDS];
                     bool any[IDS];
@@ -457,14 +443,304 @@ __global__ __launch_bounds__(TEAM * 64) void k_gat_scatter_seg(GatArgs a) {
     }
 }
 
-// bootstrap: every live vertex (c->all_list, count in ctr->set[0].a) is recomputed
-void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool prequeued) {
+// ---------------------------------------------------------------------------------
+// large hops and the bootstrap: cut over edges
+// ---------------------------------------------------------------------------------
+// One owner per row leaves the wavefronts with long rows running when the others are done, and a wavefront waits for half a
+// dozen dependent reads per row (81 K recomputed and 490 K patched rows of 47 over 31 M edges took 2.0 ms, a quarter of what
+// the line gathers alone cost). Here the in-edge space of the listed vertices is cut into runs of chunks, handed out from a
+// counter like a pull's. What an edge contributes is put into a list in LDS, in edge order, hence by destination: one entry
+// for an in-neighbour of a recomputed vertex, two (the new term and the old one, taken away) for a changed in-neighbour of any
+// other. The list is then summed like a pull's messages, one row per entry. A vertex whose in-edges lie in one run is
+// written by that run alone; what a run boundary cuts is combined with atomics (k_gat_prepare has zeroed the cut rows that
+// are recomputed). Changed edges of a vertex that keeps its long row are added before (k_gat_edge_terms). A patched
+// denominator that has cancelled (GAT_CANCEL) is found afterwards (k_gat_check) and its row recomputed by a workgroup.
+struct GatEdgeArgs {
+    PullArgs p;                    // list, count_ptr, ioff, in_meta, in_pool, bm_prev, d, X, ctr, l
+    const uint32_t *bm_sink, *bm_vadd;
+    const float *P, *Pold, *ssrc, *sold, *sdst;
+    uint32_t ldp;
+    float *den, *mag;              // mag: what a vertex's patches have added and taken away (valid for listed vertices)
+    uint8_t *rec;                  // per listed vertex: recomputed
+    int all;                       // bootstrap
+    uint32_t long_min;             // a sink with at most this many in-neighbours recomputes
+    uint32_t n_waves;              // wavefronts of the k_gat_edges launch
+    uint32_t *queue, *queue_count;
+    const uint32_t *st_src, *st_dst, *n_struct;
+    const float *st_sign;
+    uint32_t struct_cap;
+};
+
+__device__ __forceinline__ uint32_t gat_per(uint32_t n_chunks, uint32_t nw) { return max(1u, min((uint32_t)PULL_RUN, n_chunks / (2u * nw))); }
+__device__ __forceinline__ uint32_t gat_span(uint32_t total, uint32_t nw) {             // edges per run
+    return gat_per((total + PULL_CHUNK - 1) / PULL_CHUNK, nw) * PULL_CHUNK;
+}
+
+__global__ __launch_bounds__(256) void k_gat_prepare(GatEdgeArgs a) {
+    const int lane = rp_lane();
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t count = *a.p.count_ptr, d = a.p.d;
+    const uint32_t span = gat_span(count ? a.p.ioff[count] : 0u, a.n_waves);
+    for (uint32_t base = gw * 64u; base < count; base += nw * 64u) {
+        const uint32_t i = base + (uint32_t)lane;
+        bool zero = false;
+        uint32_t v = 0;
+        if (i < count) {
+            v = a.p.list[i];
+            const uint32_t e0 = a.p.ioff[i], e1 = a.p.ioff[i + 1u];
+            const bool rec = a.all || rp_bit(a.p.bm_prev, v) || rp_bit(a.bm_vadd, v) || (rp_bit(a.bm_sink, v) && e1 - e0 <= a.long_min);
+            a.rec[v] = rec ? 1 : 0;
+            a.mag[v] = 0.0f;
+            zero = rec && (e1 == e0 || e0 / span != (e1 - 1u) / span);
+            if (zero) a.den[v] = 0.0f;
+        }
+        unsigned long long m = __ballot(zero);
+        while (m) {
+            const uint32_t w = (uint32_t)__shfl((int)v, __ffsll((long long)m) - 1);
+            m &= m - 1ull;
+            for (uint32_t col = lane; col < d; col += 64u) a.p.X[(size_t)w * d + col] = 0.0f;
+        }
+    }
+}
+
+// changed edges of vertices that are not recomputed, as messages (see gat_edge_block); a wavefront each
+__global__ __launch_bounds__(256) void k_gat_edge_terms(GatEdgeArgs a) {
+    const int lane = rp_lane();
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t n = min(*a.n_struct, a.struct_cap), d = a.p.d;
+    for (uint32_t s = gw; s < n; s += nw) {
+        const uint32_t u = a.st_src[s], v = a.st_dst[s];
+        const float sgn = a.st_sign[s];
+        if (sgn == 0.0f || !rp_bit(a.bm_sink, v) || !rp_bit(a.p.bm_cur, v) || a.rec[v]) continue;   // (a deleted sink is in no set)
+        const bool from_old = rp_bit(a.p.bm_prev, u);
+        const float w = gat_weight(from_old ? a.sold[u] : a.ssrc[u], a.sdst[v]);
+        const float *row = (from_old ? a.Pold : a.P) + (size_t)u * a.ldp;
+        for (uint32_t col = lane; col < d; col += 64u) unsafeAtomicAdd(&a.p.X[(size_t)v * d + col], sgn * w * row[col]);
+        if (lane == 0) {
+            unsafeAtomicAdd(&a.den[v], sgn * w);
+            unsafeAtomicAdd(&a.mag[v], w);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_gat_check(GatEdgeArgs a) {
+    const uint32_t count = *a.p.count_ptr;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
+        const uint32_t v = a.p.list[i];
+        if (!a.rec[v] && a.mag[v] > 0.0f && !(a.den[v] > GAT_CANCEL * a.mag[v])) a.queue[atomicAdd(a.queue_count, 1u)] = v;
+    }
+}
+
+#define GAT_OLD 0x80000000u                 // entry: the source's row as it was before the batch, taken away
+// QUAD: rows of at most 63 columns that carry their score behind the last column (no read of its own): 16 lanes take a row, four
+// columns each, so a wavefront sums four entries at a time (the rate of instructions, not memory, bounds a row of two
+// cache lines otherwise). Else a wavefront per row, NJ columns per lane, weights made lane-parallel from the score array.
+template <int NJ, bool QUAD>
+__global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
+    constexpr int T = PULL_CHUNK / 64;
+    constexpr int G = QUAD ? 4 : (NJ >= 8) ? 2 : 16 / NJ;   // quads / rows in flight
+    constexpr uint32_t NONE = 0xFFFFFFFFu, PAD = 0x7FFFFFFEu, ITEMS = 2u * PULL_CHUNK + 16u;
+    __shared__ uint32_t s_u[4][ITEMS], s_v[4][ITEMS];
+    __shared__ float s_x[4][ITEMS];                         // QUAD: the destination's score; else the entry's weight
+    const uint32_t count = *a.p.count_ptr;
+    if (count == 0) return;
+    const int lane = rp_lane(), wave = threadIdx.x >> 6;
+    const uint32_t grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
+    const uint32_t d = a.p.d, ldp = a.ldp;
+    const uint32_t total = a.p.ioff[count];
+    const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t per = gat_per(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
+    uint32_t *su = s_u[wave], *sv = s_v[wave];
+    float *sx = s_x[wave];
+    for (uint32_t run = gw; run < n_runs;) {
+        const uint32_t c_begin = run * per, c_end = min(n_chunks, c_begin + per);
+        PullScan<T, 0, 1> scan;
+        scan.begin(a.p, count, c_begin, lane);
+        const uint32_t e_end = min(total, c_end * PULL_CHUNK);
+        const uint32_t v_first = (uint32_t)__shfl((int)scan.rv, 0), i_last = rp_seg_search_wave(a.p.ioff, 0, count - 1, e_end - 1u);
+        const uint32_t v_last = a.p.list[i_last];
+        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK, cut_last = a.p.ioff[i_last + 1u] > e_end;
+        uint32_t cur = NONE;
+        float acc[NJ], dsum = 0.0f, mag = 0.0f;
+        float4 acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[j] = 0.0f;
+        auto flush = [&]() {
+            const bool cut = (cur == v_first && cut_first) || (cur == v_last && cut_last);
+            const bool rec = a.rec[cur] != 0;
+            float *xr = a.p.X + (size_t)cur * d;
+            if (QUAD) {                                     // the four groups' sums together; lane (grp, sub) then has column 4 sub + grp
+#pragma unroll
+                for (int o = 16; o < 64; o <<= 1) {
+                    acq.x += __shfl_xor(acq.x, o);
+                    acq.y += __shfl_xor(acq.y, o);
+                    acq.z += __shfl_xor(acq.z, o);
+                    acq.w += __shfl_xor(acq.w, o);
+                    dsum += __shfl_xor(dsum, o);
+                    mag += __shfl_xor(mag, o);
+                }
+                acc[0] = grp == 0u ? acq.x : (grp == 1u ? acq.y : (grp == 2u ? acq.z : acq.w));
+                acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const uint32_t col = QUAD ? 4u * sub + grp : (uint32_t)lane + 64u * j;
+                if (col < d) {
+                    if (cut) unsafeAtomicAdd(&xr[col], acc[j]);
+                    else xr[col] = rec ? acc[j] : xr[col] + acc[j];
+                }
+                acc[j] = 0.0f;
+            }
+            if (lane == 0) {
+                if (cut) {
+                    unsafeAtomicAdd(&a.den[cur], dsum);
+                    if (!rec) unsafeAtomicAdd(&a.mag[cur], mag);
+                } else {
+                    a.den[cur] = rec ? dsum : a.den[cur] + dsum;
+                    if (!rec) a.mag[cur] += mag;
+                }
+            }
+            dsum = mag = 0.0f;
+        };
+        for (uint32_t c = c_begin; c < c_end; ++c) {
+            const uint32_t e0 = c * PULL_CHUNK, e1 = min(total, e0 + PULL_CHUNK);
+            uint32_t my_v[T], my_u[T];
+            float no_w[1];
+            bool valid[T], rec[T];
+            scan.chunk(a.p, count, e0, e1, lane, my_v, my_u, no_w, valid);
+            float t_v[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint32_t v = valid[t] ? my_v[t] : v_first;
+                rec[t] = a.rec[v] != 0;
+                t_v[t] = a.sdst[v];
+            }
+            uint32_t n = 0;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const bool one = valid[t] && (rec[t] || rp_bit(a.p.bm_prev, my_u[t]));
+                const bool two = one && !rec[t];
+                float wn = t_v[t], wo = t_v[t];
+                if (!QUAD) {
+                    wn = one ? gat_weight(a.ssrc[my_u[t]], t_v[t]) : 0.0f;
+                    wo = two ? -gat_weight(a.sold[my_u[t]], t_v[t]) : 0.0f;
+                }
+                const unsigned long long m1 = __ballot(one), m2 = __ballot(two), below = (1ull << lane) - 1ull;
+                const uint32_t at = n + (uint32_t)__popcll(m1 & below) + (uint32_t)__popcll(m2 & below);
+                if (one) {
+                    su[at] = my_u[t];
+                    sv[at] = my_v[t];
+                    sx[at] = wn;
+                }
+                if (two) {
+                    su[at + 1u] = my_u[t] | GAT_OLD;
+                    sv[at + 1u] = my_v[t];
+                    sx[at + 1u] = wo;
+                }
+                n += (uint32_t)__popcll(m1) + (uint32_t)__popcll(m2);
+            }
+            if (lane < 16) {                                // entries that the last round reads past the end: row 0, no destination
+                su[n + lane] = 0u;
+                sv[n + lane] = PAD;
+                sx[n + lane] = 0.0f;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (LDS accesses of one wavefront are executed in order)
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if constexpr (QUAD) {
+                for (uint32_t k0 = 0; k0 < n; k0 += 4u * G) {
+                    uint32_t u[G], v[G];
+                    float tv[G];
+                    float4 r[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint32_t idx = min(k0 + 4u * g, n) + grp;      // at most n + 3
+                        u[g] = su[idx];
+                        v[g] = sv[idx];
+                        tv[g] = sx[idx];
+                        const float *row = ((u[g] & GAT_OLD) ? a.Pold : a.P) + (size_t)(u[g] & ~GAT_OLD) * ldp;
+                        r[g] = 4u * sub < ldp ? *(const float4 *)(row + 4u * sub) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    }
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        if (k0 + 4u * g >= n) continue;
+                        const float mine = (d & 3u) == 0u ? r[g].x : ((d & 3u) == 1u ? r[g].y : ((d & 3u) == 2u ? r[g].z : r[g].w));
+                        const float w = gat_weight(__shfl(mine, (int)(16u * grp + d / 4u)), tv[g]);     // the row's score sits in lane d / 4
+                        const float sw = (u[g] & GAT_OLD) ? -w : w;
+                        if (!__any(v[g] != cur)) {
+                            acq.x = __builtin_fmaf(sw, r[g].x, acq.x);
+                            acq.y = __builtin_fmaf(sw, r[g].y, acq.y);
+                            acq.z = __builtin_fmaf(sw, r[g].z, acq.z);
+                            acq.w = __builtin_fmaf(sw, r[g].w, acq.w);
+                            dsum += sw;
+                            mag += w;
+                        } else {                            // entry by entry (they are sorted by destination)
+#pragma unroll
+                            for (uint32_t q = 0; q < 4u; ++q) {
+                                const uint32_t vq = (uint32_t)__builtin_amdgcn_readlane((int)v[g], 16 * (int)q);
+                                if (vq == PAD) continue;
+                                if (vq != cur) {
+                                    if (cur != NONE) flush();
+                                    cur = vq;
+                                }
+                                if (grp == q) {
+                                    acq.x = __builtin_fmaf(sw, r[g].x, acq.x);
+                                    acq.y = __builtin_fmaf(sw, r[g].y, acq.y);
+                                    acq.z = __builtin_fmaf(sw, r[g].z, acq.z);
+                                    acq.w = __builtin_fmaf(sw, r[g].w, acq.w);
+                                    dsum += sw;
+                                    mag += w;
+                                }
+                            }
+                        }
+                    }
+                }
+            } else {
+                for (uint32_t k0 = 0; k0 < n; k0 += G) {
+                    float r[G][NJ], w[G];
+                    uint32_t v[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint32_t idx = min(k0 + (uint32_t)g, n - 1u);
+                        const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)su[idx]);
+                        v[g] = (uint32_t)__builtin_amdgcn_readfirstlane((int)sv[idx]);
+                        w[g] = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(sx[idx])));
+                        const float *row = ((u & GAT_OLD) ? a.Pold : a.P) + (size_t)(u & ~GAT_OLD) * ldp;
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) r[g][j] = row[min((uint32_t)lane + 64u * j, d - 1u)];
+                    }
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        if (k0 + (uint32_t)g >= n) continue;
+                        if (v[g] != cur) {
+                            if (cur != NONE) flush();
+                            cur = v[g];
+                        }
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) acc[j] = __builtin_fmaf(w[g], r[g][j], acc[j]);
+                        dsum += w[g];
+                        mag += fabsf(w[g]);
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();                // the next chunk overwrites the list
+            scan.advance();
+        }
+        if (cur != NONE) flush();
+        if ((unsigned long long)nw * per >= n_chunks) break;
+        run = nw + rp_next_run(&a.p.ctr->pull_next[a.p.l], lane);
+    }
+}
+
+// bootstrap: every live vertex (c->all_list, its in-degree prefix in c->ioff_all, count in ctr->n_all) is recomputed.
+// listed: a small hop, whose vertices (and the long rows among them) were listed while they were marked: a wavefront or a
+// workgroup per row in one launch, which is paced by the longest chain of reads; all other hops are cut over edges.
+void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool listed) {
     const LayerDev &ly = c->layers[l - 1];
     GatArgs a;
-    a.list = bootstrap ? c->all_list : c->list[l];
-    a.count_ptr = bootstrap ? &c->ctr->set[0].a : &c->ctr->set[l].a;
-    a.queue = bootstrap ? c->list[0] : c->all_list;     // scratch that is free at that point
-    a.queue_count = &c->ctr->n_long[l];
+    a.list = c->list[l];
+    a.count_ptr = &c->ctr->set[l].a;
     a.in_meta = c->in_meta;
     a.in_pool = c->in_pool;
     a.bm_prev = c->bm[l - 1];
@@ -475,16 +751,13 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool prequ
     a.ssrc = ly.ssrc;
     a.sold = c->sold;
     a.sdst = ly.sdst;
+    a.ldp = ly.ldp;
     a.d = ly.d_out;
     a.X = c->X[l];
     a.den = ly.den;
-    a.all = bootstrap ? 1 : 0;
-    const bool few = !bootstrap && c->hints_valid && c->last_a[l] <= 8192u;
-    // few rows: one wavefront would read a row of 100+ in-neighbours, one workgroup a row of thousands, with the chip idle
-    a.few = (few || prequeued) ? 1 : 0;
-    a.long_min = (few || prequeued) ? RP_MONO_LISTED_LONG : GAT_LONG;   // (the limit the long rows were queued with)
-    const bool some = !bootstrap && c->hints_valid && c->last_a[l] <= 131072u;   // in between: split rows of a few thousand entries
-    a.split_min = few ? ROW_SPLIT_MIN : (some ? 4u : 64u) * ROW_SPLIT_MIN;
+    a.all = 0;
+    a.long_min = RP_MONO_LISTED_LONG;                    // (the limit the long rows were queued with)
+    a.split_min = ROW_SPLIT_MIN;
     a.n_big = &c->ctr->n_big[l];
     a.n_seg = &c->ctr->n_seg[l];
     a.seg_v = c->seg_v;
@@ -497,53 +770,98 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool prequ
     a.seg_ld = c->seg_ld;
     a.st_src = c->st_src;
     a.st_dst = c->st_dst;
-    a.st_sign = c->st_unit;                         // +1 added, -1 deleted, 0 re-weighted (attention ignores edge weights)
+    a.st_sign = c->st_unit;                              // +1 added, -1 deleted, 0 re-weighted (attention ignores edge weights)
     a.n_struct = &c->ctr->n_struct;
-    a.struct_cap = (c->in_w || bootstrap) ? 0u : c->struct_cap;   // weighted graphs: the sign carries the weight, sinks recompute
-    if (bootstrap) {                                     // a batch starts with them cleared
-        hipMemsetAsync(&c->ctr->n_long[l], 0, 4, c->stream);
-        hipMemsetAsync(&c->ctr->n_big[l], 0, 4, c->stream);
-        hipMemsetAsync(&c->ctr->n_seg[l], 0, 4, c->stream);
-    }
-    GatArgs b = a;
-    b.list = a.queue;
-    if (prequeued) a.queue = nullptr;                    // the wavefront role skips the long rows: they are in the queue already
+    a.struct_cap = (c->in_w || bootstrap) ? 0u : c->struct_cap;   // weighted graphs: sinks recompute
+    GatArgs b = a;                                       // the queue's side
+    b.list = c->all_list;
     b.count_ptr = &c->ctr->n_long[l];
-    dim3 grid(c->n_cu * (few ? 4 : 8)), block(256);
-#define GAT_CASE(NJ, TEAM)                                                                                   \
-    do {                                                                                                     \
-        if (prequeued) { /* every workgroup resident at once: half the compute units' worth for each role */ \
-            hipLaunchKernelGGL((k_gat_scatter_both<NJ, TEAM>), dim3(c->n_cu / 2 + (c->n_cu / 2) * (16 / TEAM)),  \
-                               dim3(TEAM * 64), 0, c->stream, a, b, c->n_cu / 2);                            \
-        } else {                                                                                             \
-            hipLaunchKernelGGL((k_gat_scatter<NJ>), grid, block, 0, c->stream, a);                           \
-            hipLaunchKernelGGL((k_gat_scatter_long<NJ, TEAM>), dim3(c->n_cu * 2), dim3(TEAM * 64), 0, c->stream, b); \
-        }                                                                                                    \
+    const dim3 block(256);
+    if (listed) {                                        // every workgroup resident at once: half the compute units' worth for each role
+#define GAT_CASE(NJ, TEAM)                                                                                            \
+    do {                                                                                                              \
+        hipLaunchKernelGGL((k_gat_scatter_both<NJ, TEAM>), dim3(c->n_cu / 2 + (c->n_cu / 2) * (16 / TEAM)),           \
+                           dim3(TEAM * 64), 0, c->stream, a, b, c->n_cu / 2);                                         \
         hipLaunchKernelGGL((k_gat_scatter_seg<NJ, ROW_SEG / 64>), dim3(c->n_cu * 4), dim3(ROW_SEG), 0, c->stream, b); \
     } while (0)
-    if (a.d <= 64) GAT_CASE(1, 16);
-    else if (a.d <= 128) GAT_CASE(2, 16);
-    else if (a.d <= 256) GAT_CASE(4, 16);
-    else if (a.d <= 512) GAT_CASE(8, 16);
-    else GAT_CASE(16, 8);
+        if (a.d <= 64) GAT_CASE(1, 16);
+        else if (a.d <= 128) GAT_CASE(2, 16);
+        else if (a.d <= 256) GAT_CASE(4, 16);
+        else if (a.d <= 512) GAT_CASE(8, 16);
+        else GAT_CASE(16, 8);
+#undef GAT_CASE
+        return;
+    }
+    const dim3 grid(c->n_cu * 8);
+    GatEdgeArgs e = {};
+    e.p.list = bootstrap ? c->all_list : c->list[l];
+    e.p.count_ptr = bootstrap ? &c->ctr->n_all : &c->ctr->set[l].a;
+    e.p.ioff = bootstrap ? c->ioff_all : c->ioff[l];
+    e.p.in_meta = c->in_meta;
+    e.p.in_pool = c->in_pool;
+    e.p.bm_prev = c->bm[l - 1];
+    e.p.bm_cur = c->bm[l];
+    e.p.d = ly.d_out;
+    e.p.X = c->X[l];
+    e.p.ctr = c->ctr;
+    e.p.l = l;
+    e.bm_sink = c->bm_sink;
+    e.bm_vadd = c->bm_vadd;
+    e.P = ly.P;
+    e.Pold = c->Pold;
+    e.ssrc = ly.ssrc;
+    e.sold = c->sold;
+    e.sdst = ly.sdst;
+    e.ldp = ly.ldp;
+    e.den = ly.den;
+    e.mag = c->gat_mag;
+    e.rec = c->gat_rec;
+    e.all = bootstrap ? 1 : 0;
+    e.long_min = c->in_w ? 0xFFFFFFFFu : GAT_LONG;
+    e.n_waves = c->n_cu * 8 * 4;
+    e.queue = c->all_list;
+    e.queue_count = &c->ctr->n_long[l];
+    e.st_src = c->st_src;
+    e.st_dst = c->st_dst;
+    e.st_sign = c->st_unit;
+    e.n_struct = &c->ctr->n_struct;
+    e.struct_cap = a.struct_cap;
+    hipLaunchKernelGGL(k_gat_prepare, grid, block, 0, c->stream, e);
+    if (e.struct_cap) hipLaunchKernelGGL(k_gat_edge_terms, dim3(c->n_cu * 2), block, 0, c->stream, e);
+    b.all = 1;                                           // rows whose patch has cancelled: read once more
+    b.split_min = 0xFFFFFFFFu;
+#define GAT_CASE(NJ, QUAD, TEAM)                                                                                              \
+    do {                                                                                                                      \
+        hipLaunchKernelGGL((k_gat_edges<NJ, QUAD>), grid, block, 0, c->stream, e);                                            \
+        if (bootstrap) break;                                                                                                 \
+        hipLaunchKernelGGL(k_gat_check, dim3(c->n_cu * 2), block, 0, c->stream, e);                                           \
+        hipLaunchKernelGGL((k_gat_scatter_long<NJ, TEAM>), dim3(c->n_cu), dim3(TEAM * 64), 0, c->stream, b);                  \
+    } while (0)
+    if (e.ldp > e.p.d) GAT_CASE(1, true, 16);
+    else if (e.p.d <= 64) GAT_CASE(1, false, 16);
+    else if (e.p.d <= 128) GAT_CASE(2, false, 16);
+    else if (e.p.d <= 256) GAT_CASE(4, false, 16);
+    else if (e.p.d <= 512) GAT_CASE(8, false, 16);
+    else GAT_CASE(16, false, 8);
 #undef GAT_CASE
 }
 
 // before the projection of A_{l-1} is refreshed: keep the old rows and source scores for the messages
 __global__ __launch_bounds__(256) void k_gat_save(const uint32_t *list, const uint32_t *count_ptr, const float *P,
-                                                  const float *ssrc, uint32_t d, float *Pold, float *sold) {
+                                                  const float *ssrc, uint32_t ldp, float *Pold, float *sold) {
     const uint32_t count = *count_ptr;
     const int lane = rp_lane();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t i = gw; i < count; i += nw) {
         const uint32_t v = list[i];
-        for (uint32_t col = lane; col < d; col += 64) Pold[(size_t)v * d + col] = P[(size_t)v * d + col];
+        for (uint32_t col = lane; col < ldp; col += 64) Pold[(size_t)v * ldp + col] = P[(size_t)v * ldp + col];
         if (lane == 0) sold[v] = ssrc[v];
     }
 }
 
-// s_src[v] = a_src . P[v], s_dst[v] = a_dst . P[v] for the listed vertices (att: a_src then a_dst)
-__global__ __launch_bounds__(256) void k_gat_scores(const uint32_t *list, const uint32_t *count_ptr, const float *P,
+// s_src[v] = a_src . P[v], s_dst[v] = a_dst . P[v] for the listed vertices (att: a_src then a_dst); rows with room keep s_src
+// behind their last column as well
+__global__ __launch_bounds__(256) void k_gat_scores(const uint32_t *list, const uint32_t *count_ptr, float *P, uint32_t ldp,
                                                     const float *att, uint32_t d, float *ssrc, float *sdst) {
     const uint32_t count = *count_ptr;
     const int lane = rp_lane();
@@ -552,7 +870,7 @@ __global__ __launch_bounds__(256) void k_gat_scores(const uint32_t *list, const 
         const uint32_t v = list[i];
         float s = 0.0f, t = 0.0f;
         for (uint32_t col = lane; col < d; col += 64) {
-            const float p = P[(size_t)v * d + col];
+            const float p = P[(size_t)v * ldp + col];
             s += p * att[col];
             t += p * att[d + col];
         }
@@ -561,18 +879,19 @@ __global__ __launch_bounds__(256) void k_gat_scores(const uint32_t *list, const 
         if (lane == 0) {
             ssrc[v] = s;
             sdst[v] = t;
+            if (ldp > d) P[(size_t)v * ldp + d] = s;
         }
     }
 }
 
 void rp_launch_gat_save(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
     const LayerDev &ly = c->layers[l - 1];
-    hipLaunchKernelGGL(k_gat_save, dim3(c->n_cu * 4), dim3(256), 0, c->stream, list, count_d, ly.P, ly.ssrc, ly.d_out,
+    hipLaunchKernelGGL(k_gat_save, dim3(c->n_cu * 4), dim3(256), 0, c->stream, list, count_d, ly.P, ly.ssrc, ly.ldp,
                        c->Pold, c->sold);
 }
 
 void rp_launch_gat_scores(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
     const LayerDev &ly = c->layers[l - 1];
-    hipLaunchKernelGGL(k_gat_scores, dim3(c->n_cu * 4), dim3(256), 0, c->stream, list, count_d, ly.P, ly.att, ly.d_out,
-                       ly.ssrc, ly.sdst);
+    hipLaunchKernelGGL(k_gat_scores, dim3(c->n_cu * 4), dim3(256), 0, c->stream, list, count_d, ly.P, ly.ldp, ly.att,
+                       ly.d_out, ly.ssrc, ly.sdst);
 }

@@ -98,6 +98,7 @@ struct LayerDev {
     // attention layers: projected rows P[v] = H^{l-1}[v] W0 [n x d_out], scores a_src . P[v] and a_dst . P[v],
     // denominators of the softmax (the numerators are the layer's X rows); att = a_src then a_dst on the device
     float *att, *P, *ssrc, *sdst, *den;
+    uint32_t ldp;                             // row stride of P: rows of up to 63 columns carry s_src behind them
     // fp32 storage: W0, Wn, W1 as three transposed bf16 planes each (their sum is the matrix), or null
     unsigned short *W0s, *Wns, *W1s;
     // the padded matrices once more with k by fours, [Kpad / 4][Npad][4] (wave_gemm); Wnq may alias W0q
@@ -146,6 +147,8 @@ struct ripple_ctx {
     float *seg_part = nullptr;
     uint32_t big_cap = 0, seg_cap = 0, seg_ld = 0;
     uint32_t seg_limit = 0xffffffffu;                   // RIPPLE_OPT_ROW_SEGMENTS: segments a hop may queue (<= seg_cap is used)
+    float *gat_mag = nullptr;                           // attention hops: what a vertex's patches have added and taken away
+    uint8_t *gat_rec = nullptr;                         // ... and whether it is recomputed (both valid for the hop's vertices)
     float *Pold = nullptr, *sold = nullptr;             // attention hops: projected rows / source scores of A_{l-1} before the batch
     uint32_t xw[RIPPLE_MAX_LAYERS + 1] = {0};           // width of X^l (d_{l-1}, or d_l when projected)
     uint32_t pd_ld = 0;                                 // row stride of PD (64-byte multiple)

@@ -1,0 +1,134 @@
+// The walk along a list's in-edges that the pull kernels share: scatter.hip (hops and bootstrap), attention.hip.
+#pragma once
+#include "common.h"
+
+#define PULL_CHUNK 256
+#define PULL_RUN 8                      // chunks a wavefront takes at a time on a large hop
+// the next run's number, fetched by lane 0 for the wavefront
+__device__ __forceinline__ uint32_t rp_next_run(uint32_t *counter, int lane) {
+    uint32_t r = 0;
+    if (lane == 0) r = atomicAdd(counter, 1u);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)r);
+}
+
+struct PullArgs {
+    const uint32_t *list;          // destinations, ascending
+    const uint32_t *count_ptr;
+    const uint32_t *ioff;          // in-degree prefix over the list
+    const uint2 *in_meta;
+    const uint32_t *in_pool;
+    const float *in_w;             // edge weights parallel to in_pool (weighted-sum layers), or null
+    const uint32_t *bm_prev;       // A_{l-1} as bitmap
+    uint32_t *bm_cur;              // bitmap of A_l: receivers are marked here when discovering
+    const float *D;                // delta rows, indexed by vertex
+    uint32_t ldd;                  // their row stride
+    uint32_t msg_bytes;            // packed message rows (k_scatter_pull4): size of the table in bytes, below 4 GB
+    uint32_t d;
+    float *X;
+    DevCtr *ctr;
+    uint32_t l;
+    int mode, ratio, allow_disc;
+    // the hop's messages may have been listed and sorted instead (rp_hop_sorted): then the pull leaves the hop alone
+    const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
+    uint32_t sorted_cap;           // entries the host sorted (0: no list was made)
+    int sorted_force;
+    // deterministic variants only
+    const uint32_t *bm_rec;        // destinations that are recomputed from all their in-neighbours (bootstrap inference), or null
+    const void *Hprev;             // what a recomputed row sums: rows of H^{l-1} (storage format `store`) ...
+    const float *R;                // ... or, for a project-first layer, of T (what every vertex has sent so far); stride d
+    int store;
+    uint32_t side_runs;            // runs the side entries have room for (two entries per run)
+    uint32_t *side_v;              // per run: the destinations of its first and last in-edge, if it has sums for them
+    float *side_acc;               // ... and those sums, d floats per entry
+};
+
+// The part both pull kernels share: which in-edges a chunk holds. Lane j describes row i_lo + j of the
+// list: destination rv, pool position of edge e is rbase + e (mod 2^32), and bnd = first edge of row
+// i_lo + j + 1 (the total beyond the list's end). ALL: every in-edge counts, no source is tested.
+template <int T, int WT, int ALL = 0>
+struct PullScan {
+    uint32_t i_lo, rv, rbase, bnd;
+    uint32_t i_nx, rv_n, rbase_n, bnd_n;
+
+    __device__ __forceinline__ void begin(const PullArgs &a, uint32_t count, uint32_t c_begin, int lane) {
+        const uint32_t last = count - 1;
+        i_lo = rp_seg_search_wave(a.ioff, 0, last, c_begin * PULL_CHUNK);
+        const uint32_t ri = min(last, i_lo + lane);
+        rv = a.list[ri];
+        rbase = a.in_meta[rv].x - a.ioff[ri];
+        bnd = a.ioff[min(count, i_lo + 1 + lane)];
+    }
+    // edge e0 + 64 t + lane of the chunk [e0, e1): its destination, source, weight and whether the source is in
+    // A_{l-1}; then requests the rows of the next chunk, which are in flight while this chunk's messages are gathered
+    __device__ __forceinline__ void chunk(const PullArgs &a, uint32_t count, uint32_t e0, uint32_t e1, int lane,
+                                          uint32_t (&my_v)[T], uint32_t (&my_u)[T], float (&my_w)[WT ? T : 1], bool (&dirty)[T]) {
+        const uint32_t last = count - 1;
+        const bool fits = __shfl(bnd, 63) > e1 - 1;         // every row of the chunk is among the 64 held
+        if (fits) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const uint32_t e = e0 + 64 * t + lane;
+                const int r = (int)min(63u, rp_count_le(bnd, e));
+                my_v[t] = __shfl(rv, r);
+                const uint32_t base = __shfl(rbase, r);
+                my_u[t] = 0;
+                dirty[t] = false;
+                if (WT) my_w[t] = 0.0f;
+                if (e < e1) {
+                    my_u[t] = a.in_pool[base + e];
+                    if (WT) my_w[t] = a.in_w[base + e];
+                    dirty[t] = ALL || ((a.bm_prev[my_u[t] >> 5] >> (my_u[t] & 31)) & 1u);
+                }
+            }
+            i_nx = min(last, i_lo + rp_count_le(bnd, e1));
+        } else {
+            // Short rows (a stretch of vertices with fewer than four in-neighbours on average, e.g. vertices created
+            // by earlier batches, which sit together at the end of the id range): the chunk is taken in pieces of
+            // 64 rows, each like a chunk that fits. (A search per edge instead made such chunks several times as
+            // slow as the others, and since a wavefront's chunks are neighbours, the wavefronts at the end of the
+            // id range then held up the whole hop: 2.1 -> 3.8 ms after 400 batches that each create 100 vertices.)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                my_v[t] = 0;
+                my_u[t] = 0;
+                if (WT) my_w[t] = 0.0f;
+                dirty[t] = false;
+            }
+            uint32_t il = i_lo, rv_p = rv, rb_p = rbase, bn_p = bnd, es = e0;
+            for (;;) {
+                const uint32_t top = min(e1, (uint32_t)__shfl(bn_p, 63));   // edges [es, top) lie in the 64 rows held
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    const uint32_t e = e0 + 64 * t + lane;
+                    const int r = (int)min(63u, rp_count_le(bn_p, e));
+                    const uint32_t v = __shfl(rv_p, r);
+                    const uint32_t base = __shfl(rb_p, r);
+                    if (e >= es && e < top) {
+                        my_v[t] = v;
+                        my_u[t] = a.in_pool[base + e];
+                        if (WT) my_w[t] = a.in_w[base + e];
+                        dirty[t] = ALL || ((a.bm_prev[my_u[t] >> 5] >> (my_u[t] & 31)) & 1u);
+                    }
+                }
+                if (top >= e1) break;
+                es = top;
+                il = min(last, il + 64u);
+                const uint32_t rp = min(last, il + lane);
+                rv_p = a.list[rp];
+                rb_p = a.in_meta[rv_p].x - a.ioff[rp];
+                bn_p = a.ioff[min(count, il + 1 + lane)];
+            }
+            i_nx = min(last, il + rp_count_le(bn_p, e1));
+        }
+        const uint32_t ri = min(last, i_nx + lane);
+        rv_n = a.list[ri];
+        rbase_n = a.in_meta[rv_n].x - a.ioff[ri];
+        bnd_n = a.ioff[min(count, i_nx + 1 + lane)];
+    }
+    __device__ __forceinline__ void advance() {
+        i_lo = i_nx;
+        rv = rv_n;
+        rbase = rbase_n;
+        bnd = bnd_n;
+    }
+};

@@ -1206,7 +1206,7 @@ void rp_launch_gat_project(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     a.a_mode = 4;
     a.out_mode = 2;
     a.tmp_out = ly.P;
-    a.tmp_out_ld = ly.d_out;
+    a.tmp_out_ld = ly.ldp;
     a.Hout = nullptr;
     launch_t(c, a, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
 }
