@@ -498,7 +498,10 @@ void rp_launch_candidates(ripple_ctx *c, uint32_t l) {
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
     a.touched_out = &c->ctr->touched[l];
+    a.want_in = 1;                                 // for the hops that recompute every candidate, and for the choice of the next batch
     a.list = c->all_list;
+    a.ioff = c->ioff_all;
+    a.isum_out = &c->ctr->isum[l];
     a.count_out = &c->ctr->n_all;
     launch_compact(c, a);
 }

@@ -1408,6 +1408,16 @@ __global__ __launch_bounds__(TEAM * 64) void k_scatter_mono_seg(MonoArgs a) {
     }
 }
 
+static void launch_mono_direct(ripple_ctx *c, uint32_t l, const MonoArgs &h);
+
+// A candidate escapes recomputation only if none of its columns' extremes was set by a changed in-neighbour and got worse. With
+// m messages over the candidates' in-entries, a share m / entries of a row's in-neighbours has changed, so m * width / entries
+// columns of it, on average, are in danger: from two on nearly every candidate would be recomputed after its messages have
+// been read in vain. Judged by the previous batch; both ways are exact.
+static bool mono_direct(const ripple_ctx *c, uint32_t l) {
+    return c->hints_valid && c->last_m[l] && (uint64_t)c->last_m[l] * c->xw[l] >= 2ull * c->last_isum[l];
+}
+
 // candidates in c->all_list, *count_ptr of them (rp_launch_candidates[_sparse]); D[(l-1)&1] holds the pre-batch rows of A_{l-1}
 void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr, bool listed) {
     MonoArgs a;
@@ -1451,6 +1461,10 @@ void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr
     a.big_cap = c->big_cap;
     a.seg_cap = std::min(c->seg_cap, c->seg_limit);
     a.seg_ld = c->seg_ld;
+    if (!listed && mono_direct(c, l)) {
+        launch_mono_direct(c, l, a);
+        return;
+    }
     MonoArgs b = a;
     b.list = listed ? c->eoff[l] : a.queue;
     b.count_ptr = &c->ctr->n_long[l];
@@ -1495,11 +1509,16 @@ void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr
 // k_pull_all_init puts there (together with the zeros of vertices without in-edges). One wavefront per row, one row in
 // flight, is what this replaces: 34.0 / 15.6 / 8.3 ms for rows of 256 / 100 / 47 floats over 31 M edges, most of it
 // spent waiting for the few wavefronts with the longest rows.
+// The same cut serves the hops of max / min layers whose candidates are all recomputed (mono_direct): a candidate's new
+// aggregate is compared with the old one when it is complete, stored if it differs and taken out of the hop's set if not;
+// what a run boundary cuts is put together in XN and finished by k_mono_close.
 struct PullAllArgs {
-    PullArgs p;                    // list (live vertices), count_ptr, ioff, in_meta, in_pool, in_w, d, X
+    PullArgs p;                    // list (live vertices or candidates), count_ptr, ioff, in_meta, in_pool, in_w, d, X
     const void *Hprev;
     int op;
     uint32_t n_cap;
+    float *XN;                     // candidates: rows that a run boundary cuts [vertex x d]
+    uint32_t n_waves;              // wavefronts of the k_pull_all launch
 };
 
 __device__ __forceinline__ uint32_t pull_all_per(uint32_t n_chunks, uint32_t nw) {
@@ -1507,14 +1526,15 @@ __device__ __forceinline__ uint32_t pull_all_per(uint32_t n_chunks, uint32_t nw)
 }
 __device__ __forceinline__ float pull_all_start(int op) { return op == 0 ? 0.0f : (op == 1 ? -INFINITY : INFINITY); }
 
-// nw: wavefronts of the k_pull_all launch
-__global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a, uint32_t nw_pull) {
+// HOP: candidates of a max / min hop
+template <int HOP>
+__global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a) {
     const int lane = rp_lane();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     const uint32_t total = count ? a.p.ioff[count] : 0u;
-    const uint32_t span = pull_all_per((total + PULL_CHUNK - 1) / PULL_CHUNK, nw_pull) * PULL_CHUNK;    // edges per run
-    for (uint32_t base = gw * 64u; base < a.n_cap; base += nw * 64u) {      // no in-edges (or not alive): zero
+    const uint32_t span = pull_all_per((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;  // edges per run
+    for (uint32_t base = gw * 64u; !HOP && base < a.n_cap; base += nw * 64u) {   // no in-edges (or not alive): zero
         const uint32_t v = base + (uint32_t)lane;
         unsigned long long m = __ballot(v < a.n_cap && a.p.in_meta[v].y == 0u);
         while (m) {
@@ -1536,7 +1556,8 @@ __global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a, uint32_t n
         while (m) {
             const uint32_t w = (uint32_t)__shfl((int)v, __ffsll((long long)m) - 1);
             m &= m - 1ull;
-            for (uint32_t col = lane; col < d; col += 64u) a.p.X[(size_t)w * d + col] = pull_all_start(a.op);
+            float *x = HOP ? a.XN : a.p.X;
+            for (uint32_t col = lane; col < d; col += 64u) x[(size_t)w * d + col] = pull_all_start(a.op);
         }
     }
 }
@@ -1550,8 +1571,8 @@ __device__ __forceinline__ void rp_atomic_extreme(float *p, float x, bool is_max
     else (void)(is_max ? atomicMin((unsigned int *)p, (unsigned int)i) : atomicMax((unsigned int *)p, (unsigned int)i));
 }
 
-template <int NJ, int STORE, int WT>
-__global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a) {
+template <int NJ, int STORE, int WT, int HOP>
+__global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
     constexpr int G = (NJ >= 8) ? 2 : 16 / NJ;              // rows per round trip
     constexpr int T = PULL_CHUNK / 64;
     constexpr uint32_t NONE = 0xFFFFFFFFu;
@@ -1576,12 +1597,20 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a) {
         const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK;
         const bool cut_last = a.p.ioff[i_last + 1u] > e_end;
         uint32_t cur = NONE;
-        float acc[NJ];
+        float acc[NJ], xo[HOP ? NJ : 1];                     // HOP: the destination's old aggregate, requested with its first edge
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[j] = start;
         auto flush = [&]() {
-            float *xr = a.p.X + (size_t)cur * d;
             const bool cut = (cur == v_first && cut_first) || (cur == v_last && cut_last);
+            float *xr = ((HOP && cut) ? a.XN : a.p.X) + (size_t)cur * d;
+            if constexpr (HOP) {
+                if (!cut) {
+                    mono_finish<NJ>(h, cur, rp_bit(h.bm_vadd, cur), xo, acc);
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) acc[j] = start;
+                    return;
+                }
+            }
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const uint32_t col = lane + 64 * j;
@@ -1620,6 +1649,10 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a) {
                             if (vk != cur) {
                                 if (cur != NONE) flush();
                                 cur = vk;
+                                if constexpr (HOP) {
+#pragma unroll
+                                    for (int j = 0; j < NJ; ++j) xo[j] = a.p.X[(size_t)vk * d + min((uint32_t)lane + 64u * j, d - 1u)];
+                                }
                             }
                             const float wk = WT ? __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(my_w[WT ? t : 0]), k0 + g)) : 1.0f;
 #pragma unroll
@@ -1637,11 +1670,45 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a) {
     }
 }
 
-// X^l[v] = sum over v's in-row of the previous layer's rows (of their projections, kept in the layer's T,
-// for project-first layers). The live vertices and their in-degree prefix are in c->all_list and c->ioff_all.
-void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
+// Candidates without in-edges or cut by a run boundary: finished here, a wavefront each.
+template <int NJ>
+__global__ __launch_bounds__(256) void k_mono_close(PullAllArgs a, MonoArgs h) {
+    const int lane = rp_lane();
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t count = *a.p.count_ptr, d = a.p.d;
+    const uint32_t total = count ? a.p.ioff[count] : 0u;
+    const uint32_t span = pull_all_per((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;
+    if (gw == 0 && lane == 0) h.ctr->mono[2][h.l] = count;               // all of them are recomputed
+    for (uint32_t base = gw * 64u; base < count; base += nw * 64u) {
+        const uint32_t i = base + (uint32_t)lane;
+        uint32_t v = 0, e0 = 0, e1 = 1;
+        bool todo = false;
+        if (i < count) {
+            e0 = a.p.ioff[i];
+            e1 = a.p.ioff[i + 1u];
+            v = a.p.list[i];
+            todo = e1 == e0 || e0 / span != (e1 - 1u) / span;
+        }
+        unsigned long long m = __ballot(todo);
+        while (m) {
+            const int k = __ffsll((long long)m) - 1;
+            m &= m - 1ull;
+            const uint32_t w = (uint32_t)__shfl((int)v, k);
+            const bool none = __shfl((int)(e1 - e0), k) == 0;
+            float xo[NJ], xn[NJ];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const uint32_t col = min((uint32_t)lane + 64u * j, d - 1u);
+                xo[j] = a.p.X[(size_t)w * d + col];
+                xn[j] = none ? 0.0f : a.XN[(size_t)w * d + col];
+            }
+            mono_finish<NJ>(h, w, rp_bit(h.bm_vadd, w), xo, xn);
+        }
+    }
+}
+
+static PullAllArgs pull_all_args(ripple_ctx *c, uint32_t l) {
     const bool proj = c->layers[l - 1].proj != 0;
-    const int store = proj ? 0 : c->store;
     PullAllArgs a = {};
     a.p.list = c->all_list;
     a.p.count_ptr = &c->ctr->n_all;
@@ -1654,9 +1721,19 @@ void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
     a.Hprev = proj ? (const void *)c->layers[l - 1].T : c->H[l - 1];
     a.op = c->layers[l - 1].agg == RIPPLE_AGG_MAX ? 1 : (c->layers[l - 1].agg == RIPPLE_AGG_MIN ? 2 : 0);
     a.n_cap = c->n_cap;
+    a.n_waves = c->n_cu * 8 * 4;
+    return a;
+}
+
+// X^l[v] = sum over v's in-row of the previous layer's rows (of their projections, kept in the layer's T,
+// for project-first layers). The live vertices and their in-degree prefix are in c->all_list and c->ioff_all.
+void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
+    const int store = c->layers[l - 1].proj ? 0 : c->store;
+    const PullAllArgs a = pull_all_args(c, l);
+    const MonoArgs none = {};
     const dim3 grid(c->n_cu * 8), block(256);
-    hipLaunchKernelGGL(k_pull_all_init, grid, block, 0, c->stream, a, c->n_cu * 8 * 4);
-#define PULL_CASE_W(NJ, STORE, WT) hipLaunchKernelGGL((k_pull_all<NJ, STORE, WT>), grid, block, 0, c->stream, a)
+    hipLaunchKernelGGL(k_pull_all_init<0>, grid, block, 0, c->stream, a);
+#define PULL_CASE_W(NJ, STORE, WT) hipLaunchKernelGGL((k_pull_all<NJ, STORE, WT, 0>), grid, block, 0, c->stream, a, none)
 #define PULL_CASE(NJ)                                  \
     do {                                               \
         if (store && a.p.in_w) PULL_CASE_W(NJ, 1, 1);  \
@@ -1671,4 +1748,25 @@ void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
     else PULL_CASE(16);
 #undef PULL_CASE
 #undef PULL_CASE_W
+}
+
+// All candidates of a max / min hop (in c->all_list with their in-degree prefix in c->ioff_all) recomputed; h: what mono_finish
+// needs. The rows a run boundary cuts are put together in the buffer that the row update will fill afterwards.
+static void launch_mono_direct(ripple_ctx *c, uint32_t l, const MonoArgs &h) {
+    PullAllArgs a = pull_all_args(c, l);
+    a.XN = c->D[l & 1];
+    const dim3 grid(c->n_cu * 8), block(256);
+    hipLaunchKernelGGL(k_pull_all_init<1>, dim3(c->n_cu * 2), block, 0, c->stream, a);
+#define PULL_CASE(NJ)                                                                                                    \
+    do {                                                                                                                 \
+        if (c->store) hipLaunchKernelGGL((k_pull_all<NJ, 1, 0, 1>), grid, block, 0, c->stream, a, h);                    \
+        else hipLaunchKernelGGL((k_pull_all<NJ, 0, 0, 1>), grid, block, 0, c->stream, a, h);                             \
+        hipLaunchKernelGGL(k_mono_close<NJ>, dim3(c->n_cu * 4), block, 0, c->stream, a, h);                              \
+    } while (0)
+    if (a.p.d <= 64) PULL_CASE(1);
+    else if (a.p.d <= 128) PULL_CASE(2);
+    else if (a.p.d <= 256) PULL_CASE(4);
+    else if (a.p.d <= 512) PULL_CASE(8);
+    else PULL_CASE(16);
+#undef PULL_CASE
 }
