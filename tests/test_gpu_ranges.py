@@ -92,3 +92,24 @@ def test_small_piece_at_the_edge_capacity_changes_nothing():
         pair.check_graph()
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("kind,widths,store", [
+    ("gcn_max", (8, 1, 5, 3), "f32"), ("gcn_min", (9, 64, 65, 7), "f32"), ("gcn_max", (16, 130, 270, 6), "bf16"), ("gat", (8, 1, 5, 3), "f32"),
+    ("gat", (9, 16, 47, 63), "f32"), ("gat", (16, 64, 65, 7), "f32"), ("gat", (7, 130, 260, 4), "f32")])
+def test_hops_cut_over_edges(kind, widths, store):
+    """Max / min hops that recompute every candidate and attention hops, none of them listed: hubs of up to 1,000 in-edges
+    that several runs share, vertices created with their edges, rows left without in-edges."""
+    print("case cut hops", kind, widths, store, flush=True)
+    pair, graph = make_pair(n=3000, e=16000, d0=widths[0], kind=kind, widths=widths, store=store, seed=51, slack=400, top_share=0.06)
+    mix = {"edge_add": 0.4, "edge_del": 0.35, "feat": 0.2, "vadd": 0.05, "vdel": 0.0}
+    stream = make_stream(pair, graph, mix, 52)
+    try:
+        rp.ripple_set_option(pair.ctx, rp.OPT_SPARSE_FRONTIER, 0)
+        for b, bs in enumerate((300, 600, 300)):           # from the second one on there are hints
+            print(" batch", b, flush=True)
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload)
+        pair.check_embeddings()
+    finally:
+        pair.close()
