@@ -582,9 +582,11 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
 
 // Deterministic mode, after a DET pull: the side entries (two per run of chunks, in run order; entries of one
 // destination are neighbours, apart from empty ones between them) are added up per destination in that order
-// and the sum is added to the row, or replaces it if the row is recomputed. One wavefront per entry; the one
-// that holds a destination's first entry does the work. Recomputed rows without any in-edge are zeroed here too:
-// no in-edge, so the pull never met them.
+// and the sum is added to the row, or replaces it if the row is recomputed. One wavefront per entry and block of 64
+// columns; the one that holds a destination's first entry does the work. The order of the additions is fixed, the reads
+// are not: sixteen entries are on their way at a time (one read per addition and all columns by one wavefront made the
+// destination with the longest in-row, 40 entries of 256 columns, hold up the hop: 24 us). Recomputed rows without any
+// in-edge are zeroed here too: no in-edge, so the pull never met them.
 __global__ __launch_bounds__(256) void k_pull_fixup(PullArgs a, uint32_t n_entries, uint32_t pull_nw) {
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     const uint32_t count = *a.count_ptr;
@@ -602,7 +604,9 @@ __global__ __launch_bounds__(256) void k_pull_fixup(PullArgs a, uint32_t n_entri
         if (a.in_meta[v].y == 0 && rp_bit(a.bm_rec, v))
             for (uint32_t c = 0; c < d; ++c) a.X[(size_t)v * d + c] = 0.0f;
     }
-    for (uint32_t k = gw; k < n_entries; k += nw) {
+    const uint32_t blocks = (d + 63u) / 64u;
+    for (uint32_t t0 = gw; t0 < n_entries * blocks; t0 += nw) {
+        const uint32_t k = t0 / blocks, col = (t0 - k * blocks) * 64u + (uint32_t)lane;
         const uint32_t v = a.side_v[k];
         if (v == NONE) continue;
         // the nearest entry before k that is not empty: the same destination means k is not the first
@@ -619,30 +623,36 @@ __global__ __launch_bounds__(256) void k_pull_fixup(PullArgs a, uint32_t n_entri
         }
         if (!first) continue;
         const bool rec = a.bm_rec && rp_bit(a.bm_rec, v);
-        for (uint32_t c0 = 0; c0 < d; c0 += 64) {
-            const uint32_t col = c0 + lane;
-            float t = (col < d) ? a.side_acc[(size_t)k * d + col] : 0.0f;
-            bool more = true;
-            for (uint32_t f0 = k + 1; f0 < n_entries && more; f0 += 64) {
-                const uint32_t f = f0 + (uint32_t)lane;
-                const uint32_t val = (f < n_entries) ? a.side_v[f] : NONE;
-                unsigned long long same = __ballot(val == v);
-                const unsigned long long other = __ballot(val != NONE && val != v);
-                if (other) {                                             // entries past the first other destination are not ours
-                    same &= (1ull << (__ffsll((long long)other) - 1)) - 1ull;
-                    more = false;
-                }
-                while (same) {
-                    const uint32_t e = f0 + (uint32_t)(__ffsll((long long)same) - 1);
-                    same &= same - 1;
-                    if (col < d) t += a.side_acc[(size_t)e * d + col];
-                }
+        float *x = &a.X[(size_t)v * d + col];
+        const float old = (col < d && !rec) ? *x : 0.0f;
+        float t = (col < d) ? a.side_acc[(size_t)k * d + col] : 0.0f;
+        bool more = true;
+        for (uint32_t f0 = k + 1; f0 < n_entries && more; f0 += 64) {
+            const uint32_t f = f0 + (uint32_t)lane;
+            const uint32_t val = (f < n_entries) ? a.side_v[f] : NONE;
+            unsigned long long same = __ballot(val == v);
+            const unsigned long long other = __ballot(val != NONE && val != v);
+            if (other) {                                             // entries past the first other destination are not ours
+                same &= (1ull << (__ffsll((long long)other) - 1)) - 1ull;
+                more = false;
             }
-            if (col < d) {
-                float *x = &a.X[(size_t)v * d + col];
-                *x = rec ? t : *x + t;
+            while (same) {
+                constexpr int G = 16;
+                float part[G];
+                bool has[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    has[g] = same != 0;
+                    const uint32_t e = f0 + (uint32_t)(has[g] ? __ffsll((long long)same) - 1 : 0);
+                    same &= same - 1;                                // (0 stays 0)
+                    part[g] = (has[g] && col < d) ? a.side_acc[(size_t)e * d + col] : 0.0f;
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    if (has[g]) t += part[g];
             }
         }
+        if (col < d) *x = rec ? t : old + t;
     }
 }
 
@@ -766,8 +776,8 @@ void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
     else if (a.d <= 256) hipLaunchKernelGGL((k_scatter_pull<4, 0, 0, 1>), grid, block, 0, c->stream, a);
     else if (a.d <= 512) hipLaunchKernelGGL((k_scatter_pull<8, 0, 0, 1>), grid, block, 0, c->stream, a);
     else hipLaunchKernelGGL((k_scatter_pull<16, 0, 0, 1>), grid, block, 0, c->stream, a);
-    hipLaunchKernelGGL(k_pull_fixup, dim3(std::min<uint32_t>(rp_div_up(n_entries, 4), c->n_cu * 32)), block, 0, c->stream, a, n_entries,
-                       grid.x * 4u);
+    hipLaunchKernelGGL(k_pull_fixup, dim3(std::min<uint32_t>(rp_div_up(n_entries * rp_div_up(a.d, 64), 4), c->n_cu * 32)), block, 0,
+                       c->stream, a, n_entries, grid.x * 4u);
 }
 
 // ---------------------------------------------------------------------------------
