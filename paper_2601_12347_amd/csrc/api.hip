@@ -318,8 +318,8 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
     void *ptrs[] = {c->out_meta, c->in_meta, c->out_capv, c->in_capv, c->vstate, c->pend_out, c->pend_in, c->dead_out,
                     c->dead_in, c->hole_out, c->hole_in, c->out_pool, c->in_pool, c->in_w, c->alive, c->part_cnt, c->part_deg, c->part_ideg, c->ioff[0], c->ctr, c->D[0], c->D[1],
                     c->tmp, c->PD, c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->gat_mag, c->gat_rec, c->seg_v, c->seg_done, c->seg_base, c->seg_r, c->seg_part, c->bm[0], c->rep[0], c->list[0], c->eoff[0], c->all_list, c->ioff_all, c->mk, c->ops_d,
-                    c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_s, c->exp_a,
-                    c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->tail_ids, c->tail_q, c->tail_w, c->sk_in, c->sk_out, c->sv_in, c->sv_out, c->sort_tmp, c->gather_d, c->gather_ids, c->pk_a, c->pk_b, c->pv_a, c->pv_b, c->pair_tmp};
+                    c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_pos, c->exp_rank, c->exp_a,
+                    c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->op_rank_out, c->op_rank_in, c->seg_id, c->seg_x, c->srt_id, c->srt_x, c->gather_d, c->gather_ids, c->pk_a, c->pk_b, c->pv_a, c->pv_b, c->pair_tmp};
     for (void *p : ptrs)
         if (p) hipFree(p);
     for (uint32_t l = 0; l <= RIPPLE_MAX_LAYERS; ++l) {
@@ -662,7 +662,7 @@ extern "C" ripple_status ripple_full_infer(ripple_ctx *c) {
         rp_launch_transform(c, l, c->all_list, &c->ctr->set[0].a, false);
     }
     RP_HIP(c, hipMemcpyAsync(c->ctr_host, c->ctr, sizeof(DevCtr), hipMemcpyDeviceToHost, c->stream));
-    rp_launch_batch_reset(c, nullptr, 0);
+    rp_launch_batch_reset(c);
     RP_HIP(c, hipStreamSynchronize(c->stream));
     RP_HIP(c, hipGetLastError());
     const uint32_t range_rows = c->ctr_host->range_rows;
@@ -726,7 +726,7 @@ struct TouchTable {
 
 struct SubBatch {
     uint32_t begin, end;
-    bool has_vadd, has_vdel, has_vertex_or_feat;
+    bool has_vdel, has_vertex_or_feat;
 };
 
 // Cut the batch where an operation depends on an earlier one of the same piece, so that every
@@ -735,7 +735,7 @@ static void split_batch(const ripple_update *ops, uint32_t n, TouchTable &tt, st
     out.clear();
     tt.reserve((size_t)n * 3 + 16);
     tt.next_generation();
-    SubBatch cur{0, 0, false, false, false};
+    SubBatch cur{0, 0, false, false};
     const uint64_t VKEY = 0x8000000000000000ull;
     for (uint32_t i = 0; i < n; ++i) {
         const ripple_update &op = ops[i];
@@ -764,11 +764,10 @@ static void split_batch(const ripple_update *ops, uint32_t n, TouchTable &tt, st
             if (!conflict) break;
             cur.end = i;                       // close the piece before this operation and start afresh
             out.push_back(cur);
-            cur = SubBatch{i, i, false, false, false};
+            cur = SubBatch{i, i, false, false};
             tt.next_generation();
         }
         if (op.kind == RIPPLE_VERTEX_DEL) cur.has_vdel = true;
-        if (op.kind == RIPPLE_VERTEX_ADD) cur.has_vadd = true;
         if (op.kind >= RIPPLE_VERTEX_ADD && op.kind <= RIPPLE_FEAT_UPDATE) cur.has_vertex_or_feat = true;
     }
     cur.end = n;
@@ -807,15 +806,12 @@ static ripple_status ensure_batch_buffers(ripple_ctx *c, uint32_t n_ops, uint32_
         uint32_t cap = std::max<uint32_t>(std::max<uint32_t>(n_ops, c->ops_cap), 4096);
         cap = rp_round_up(cap + cap / 2, 1024);
         uint32_t exp = std::max<uint32_t>(std::max<uint32_t>(want_exp, c->exp_cap), 1u << 20);
-        void *old[] = {c->ops_d, c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_s,
-                       c->exp_a, c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->tail_ids, c->tail_q, c->tail_w, c->sk_in, c->sk_out, c->sv_in, c->sv_out, c->sort_tmp};
+        void *old[] = {c->ops_d, c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_pos,
+                       c->exp_rank, c->exp_a, c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->op_rank_out, c->op_rank_in, c->seg_id,
+                       c->seg_x, c->srt_id, c->srt_x};
         for (void *p : old)
             if (p) hipFree(p);
-        c->tail_ids = c->tail_q = nullptr;
-        c->tail_w = nullptr;
-        c->sk_in = c->sk_out = nullptr;
-        c->sv_in = c->sv_out = nullptr;
-        c->sort_tmp = nullptr;
+        c->srt_id = c->srt_x = nullptr;
         c->ops_cap = c->exp_cap = c->touch_cap = c->struct_cap = 0;
         RP_TRY(dev_alloc(c, &c->ops_d, cap, false));
         RP_TRY(dev_alloc(c, &c->op_status, cap, true));
@@ -825,26 +821,22 @@ static ripple_status ensure_batch_buffers(ripple_ctx *c, uint32_t n_ops, uint32_
         RP_TRY(dev_alloc(c, &c->touch_out, (size_t)cap + exp, false));
         RP_TRY(dev_alloc(c, &c->touch_in, (size_t)cap + exp, false));
         RP_TRY(dev_alloc(c, &c->exp_kind, exp, false));
-        RP_TRY(dev_alloc(c, &c->exp_s, exp, false));
+        RP_TRY(dev_alloc(c, &c->exp_pos, exp, false));
+        RP_TRY(dev_alloc(c, &c->exp_rank, exp, false));
         RP_TRY(dev_alloc(c, &c->exp_a, exp, false));
         RP_TRY(dev_alloc(c, &c->exp_b, exp, false));
         RP_TRY(dev_alloc(c, &c->st_src, (size_t)cap + exp, false));
         RP_TRY(dev_alloc(c, &c->st_dst, (size_t)cap + exp, false));
         RP_TRY(dev_alloc(c, &c->st_sign, (size_t)cap + exp, false));
         RP_TRY(dev_alloc(c, &c->st_unit, (size_t)cap + exp, false));
+        const size_t entries = 2 * (size_t)cap + exp;
+        RP_TRY(dev_alloc(c, &c->op_rank_out, cap, false));
+        RP_TRY(dev_alloc(c, &c->op_rank_in, cap, false));
+        RP_TRY(dev_alloc(c, &c->seg_id, entries, false));
+        RP_TRY(dev_alloc(c, &c->seg_x, entries, false));
         if (c->opt_deterministic) {
-            RP_TRY(dev_alloc(c, &c->tail_ids, cap, false));
-            RP_TRY(dev_alloc(c, &c->tail_w, cap, false));
-            RP_TRY(dev_alloc(c, &c->tail_q, (size_t)cap + exp, false));
-            RP_TRY(dev_alloc(c, &c->sk_in, (size_t)cap + exp, false));
-            RP_TRY(dev_alloc(c, &c->sk_out, (size_t)cap + exp, false));
-            RP_TRY(dev_alloc(c, &c->sv_in, (size_t)cap + exp, false));
-            RP_TRY(dev_alloc(c, &c->sv_out, (size_t)cap + exp, false));
-            c->sort_tmp_bytes = rp_sort_u64_tmp_bytes((size_t)cap + exp);
-            if (!c->sort_tmp_bytes) return fail(c, RIPPLE_EDEVICE, "the sort's temporary storage could not be sized");
-            unsigned char *tmp = nullptr;
-            RP_TRY(dev_alloc(c, &tmp, c->sort_tmp_bytes, false));
-            c->sort_tmp = tmp;
+            RP_TRY(dev_alloc(c, &c->srt_id, entries, false));
+            RP_TRY(dev_alloc(c, &c->srt_x, entries, false));
         }
         c->ops_cap = cap;
         c->exp_cap = exp;
@@ -908,11 +900,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
     const uint32_t n = sb.end - sb.begin;
     int t = rp_timer_begin(c);
     const ripple_update *ops = c->ops_pin + sb.begin;
-    if (!rp_launch_mutate_small(c, ops, n, sb.has_vdel, sb.has_vertex_or_feat)) {
-        rp_launch_batch_reset(c, ops, n);
-        rp_launch_mutate(c, n, sb.has_vadd, sb.has_vdel, sb.has_vertex_or_feat);
-        rp_launch_list_eoff(c, 0);
-    }
+    rp_launch_mutate(c, ops, n, sb.has_vdel, sb.has_vertex_or_feat);
     rp_timer_end(c, t, RIPPLE_PH_INGEST, 0);
     if (multi)
         hipLaunchKernelGGL(k_or_words, dim3(rp_div_up(c->n_words, 256)), dim3(256), 0, c->stream, c->rep[0], c->bm[0],
@@ -1136,7 +1124,7 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     if (!ops_in_range(hops, n_ops, c->n_cap, n_feat_rows))
         return fail(c, RIPPLE_EINVAL, "operation with unknown kind, vertex id or payload row out of range");
     if (n_ops == 0) {                              // nothing to do: the affected sets become empty
-        rp_launch_batch_reset(c, nullptr, 0);
+        rp_launch_batch_reset(c);
         RP_TRY(publish_and_wait(c));
         for (uint32_t l = 0; l <= c->L; ++l) c->last_a[l] = 0;
         c->last_from_rep = false;

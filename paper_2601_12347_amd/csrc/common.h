@@ -45,6 +45,9 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t need_exp;                        // upper bound of n_exp computed while validating
     uint32_t n_applied, n_rejected;
     uint32_t n_add, n_del;                    // accepted edge adds / deletes (ops only)
+    uint32_t n_gone;                          // edges that go with deleted vertices
+    unsigned long long n_listed;              // touched out-rows (low half) and in-rows that edge operations have listed so far
+    uint32_t n_entries;                       // entries of the touched rows' segments handed out so far
     uint32_t need_out, need_in;               // pool entries relocation will take
     uint32_t n_vadd;
     uint32_t abort_flag;                      // written by the capacity decision: 0 ok, bit0 pool, bit1 edges, bit2 scratch
@@ -55,8 +58,6 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t mono[3][RIPPLE_MAX_LAYERS + 1];  // max / min hops: candidates left unchanged / raised from the messages / recomputed
     uint32_t hop_mode[RIPPLE_MAX_LAYERS + 1]; // 1 + RP_HOP_* of the scatter kernel that moved hop l's messages (0: none ran)
     uint32_t range_rows;                      // attention layers: rows updated from sums that were not finite
-    uint32_t n_tail_q;                        // deterministic mode: in-rows whose appended entries a workgroup puts in order
-    uint32_t tail_top;                        // ... and the part of the copy buffer they have taken
     uint32_t pull_next[RIPPLE_MAX_LAYERS + 1];// pull scatter of hop l: runs of chunks handed out so far
 };
 #define RP_CTR_WORDS ((uint32_t)(sizeof(DevCtr) / 4))
@@ -131,7 +132,7 @@ struct ripple_ctx {
     uint32_t *vstate = nullptr;                         // VS_* bits, zero between batches
     uint32_t *pend_out = nullptr, *pend_in = nullptr;   // appended this batch
     uint32_t *dead_out = nullptr, *dead_in = nullptr;   // tombstones this batch
-    uint32_t *hole_out = nullptr, *hole_in = nullptr;   // where a row's latest tombstone sits
+    uint32_t *hole_out = nullptr, *hole_in = nullptr;   // where a touched row's segment of seg_id / seg_x begins
 
     // embeddings and cached sums
     void *H[RIPPLE_MAX_LAYERS + 1] = {nullptr};
@@ -175,23 +176,19 @@ struct ripple_ctx {
     uint32_t *touch_out = nullptr, *touch_in = nullptr;  // touched row lists
     uint32_t touch_cap = 0;
     uint32_t exp_cap = 0;
-    uint32_t *exp_kind = nullptr, *exp_a = nullptr, *exp_b = nullptr, *exp_s = nullptr;
+    uint32_t *exp_kind = nullptr, *exp_a = nullptr, *exp_b = nullptr, *exp_pos = nullptr, *exp_rank = nullptr;
     uint32_t struct_cap = 0;
     uint32_t *st_src = nullptr, *st_dst = nullptr;
     float *st_sign = nullptr;                           // per changed edge: what its sink's weighted sums gain, +alpha / -alpha / alpha_new - alpha_old
     float *st_unit = nullptr;                           // the same for aggregates that ignore weights: +1 added, -1 deleted, 0 re-weighted
-    // deterministic mode: appended in-row entries are put in id order through these (ops_cap entries each; queue: touch_cap)
-    uint32_t *tail_ids = nullptr, *tail_q = nullptr;
-    float *tail_w = nullptr;
-    // ... and the pull kernels leave the sums of rows whose in-edges lie in more than one run of chunks here (two entries per run)
+    uint32_t *op_rank_out = nullptr, *op_rank_in = nullptr;
+    // a touched row's deletions and additions, the rows one after the other (2 ops_cap + exp_cap entries), and for the deterministic
+    // mode the same in order
+    uint32_t *seg_id = nullptr, *seg_x = nullptr, *srt_id = nullptr, *srt_x = nullptr;
+    // deterministic mode: the pull kernels leave the sums of rows whose in-edges lie in more than one run of chunks here (two entries per run)
     uint32_t *side_v = nullptr;
     float *side_acc = nullptr;
     uint32_t side_runs = 0;                             // runs there is room for
-    // ... and the changed edges are sorted by (sink, source) before their structural terms are added (struct_cap entries each)
-    unsigned long long *sk_in = nullptr, *sk_out = nullptr;
-    float *sv_in = nullptr, *sv_out = nullptr;
-    void *sort_tmp = nullptr;
-    size_t sort_tmp_bytes = 0;
     DevCtr *ctr = nullptr;
     DevCtr *ctr_host = nullptr;                         // pinned mirror, written by k_publish
     uint32_t *pub_flag = nullptr;                       // pinned: number of the last k_publish that has finished
@@ -477,35 +474,37 @@ __device__ __forceinline__ bool rp_hop_sorted(const DevCtr *ctr, uint32_t l, uin
     return cap && M > 0 && M <= cap && (force || RP_SORTED_FACTOR * M + RP_SORTED_FIXED <= ctr->isum[l]);
 }
 
-// position of `target` in row[0..len), searched by one wavefront; -1 when absent. Long (hub) rows
-// are read sixteen 64-entry blocks per round, short ones four, so that a row is not paced by one
-// memory round trip per 64 entries.
+// position of `target` in row[0..len), searched by one wavefront; -1 when absent. Rows begin at multiples of four entries and
+// have room for a multiple of four, so every lane reads four at a time, and long (hub) rows are read eight such blocks per round:
+// a row of 24,000 entries takes 12 round trips (four bytes per lane and sixteen blocks took 24: 10,000 operations 80 us instead of 35).
 template <int T>
 __device__ __forceinline__ int rp_wave_find_blocks(const uint32_t *row, uint32_t base, uint32_t len, uint32_t target) {
     const int lane = rp_lane();
-    uint32_t v[T];
+    uint4 v[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        const uint32_t i = base + 64 * t + lane;
-        v[t] = (i < len) ? row[i] : RP_TOMB;                // a tombstone never equals a vertex id
+        const uint32_t i = base + 256 * t + 4 * lane;
+        v[t] = (i < len) ? *(const uint4 *)(row + i) : make_uint4(RP_TOMB, RP_TOMB, RP_TOMB, RP_TOMB);   // never a vertex id
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-        const unsigned long long m = __ballot(v[t] == target);
-        if (m) return (int)(base + 64 * t + __ffsll((long long)m) - 1);
+        const uint32_t i = base + 256 * t + 4 * lane;
+        const int k = v[t].x == target ? 0 : (v[t].y == target && i + 1 < len) ? 1 : (v[t].z == target && i + 2 < len) ? 2
+                      : (v[t].w == target && i + 3 < len) ? 3 : 4;
+        const unsigned long long m = __ballot(k < 4);
+        if (m) {
+            const int at = __ffsll((long long)m) - 1;
+            return (int)(base + 256 * t + 4 * at + __shfl(k, at));
+        }
     }
     return -1;
 }
 __device__ __forceinline__ int rp_wave_find(const uint32_t *row, uint32_t len, uint32_t target) {
     uint32_t base = 0;
-    for (; base + 1024 <= len; base += 1024) {
-        const int p = rp_wave_find_blocks<16>(row, base, len, target);
+    for (; base + 256 < len; base += 2048) {
+        const int p = rp_wave_find_blocks<8>(row, base, len, target);
         if (p >= 0) return p;
     }
-    for (; base < len; base += 256) {
-        const int p = rp_wave_find_blocks<4>(row, base, len, target);
-        if (p >= 0) return p;
-    }
-    return -1;
+    return base < len ? rp_wave_find_blocks<1>(row, base, len, target) : -1;
 }
 #endif

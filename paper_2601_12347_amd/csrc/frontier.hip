@@ -589,12 +589,6 @@ ripple_status rp_launch_affected_static(ripple_ctx *c, uint32_t *bitmap, uint32_
     return rp_wait_flag(c);
 }
 
-void rp_launch_list_eoff(ripple_ctx *c, uint32_t l) {
-    hipLaunchKernelGGL(k_list_eoff, dim3(1), dim3(1024), 0, c->stream, c->list[l], &c->ctr->set[l].a, c->out_meta,
-                       c->eoff[l], &c->ctr->set[l].m,
-                       (const uint2 *)nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
-}
-
 SparseArgs rp_sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_t *count, bool self_term) {
     SparseArgs sp;
     sp.bm = c->bm[l];

@@ -307,6 +307,7 @@ struct MutArgs {
     uint32_t n_ops;
     const float *payload;
     uint32_t *status, *pos_out, *pos_in;
+    uint32_t *rank_out, *rank_in;                // an edge operation's number among the row's additions or deletions
     uint32_t *op_touch;                          // bit 0 accepted edge op, 1 it is an add, 2 / 3 first touch of out-row(u) / in-row(v)
     uint2 *out_meta, *in_meta;
     uint32_t *out_capv, *in_capv;
@@ -314,17 +315,20 @@ struct MutArgs {
     float *in_w;                                 // edge weights parallel to in_pool, or null
     uint32_t *alive, *vstate;
     uint32_t *pend_out, *pend_in, *dead_out, *dead_in;
-    uint32_t *hole_out, *hole_in;                // position of a row's latest tombstone (exact when the row has one)
+    uint32_t *hole_out, *hole_in;                // where a touched row's segment of seg_id / seg_x begins
+    uint32_t *seg_id, *seg_x;                    // per row: deletions (seg_x: position; in-rows, seg_id: source), then additions (seg_id:
+                                                 // the other end; in-rows, seg_x: the weight's bits)
+    uint32_t *srt_id, *srt_x;                    // deterministic mode: long segments in order
     uint32_t *touch_out, *touch_in;
     uint32_t touch_cap;
     uint32_t *exp_kind, *exp_a, *exp_b;
-    uint32_t *exp_s;                             // structural-list slot of an expanded out-edge (weighted graphs)
+    uint32_t *exp_pos, *exp_rank;                // where such an edge is in the row that stays, and its number among the row's deletions
     uint32_t exp_cap;
     uint32_t *st_src, *st_dst;
     float *st_sign, *st_unit;
     uint32_t struct_cap;
     uint32_t *bm0, *bm_sink, *bm_vadd;
-    uint32_t *list0;
+    uint32_t *list0, *eoff0;
     float *D0;
     DevCtr *ctr;
     uint32_t n_cap;
@@ -339,15 +343,7 @@ struct MutArgs {
     uint32_t mono_mask;                          // bit l: layer l takes max / min or attention (no structural terms)
     uint32_t wsum_mask;                          // bit l: layer l aggregates with the edge weights
     int d0_old;                                  // layer 1 does: D0 receives the old feature row instead of the difference
-    int det;                                     // deterministic mode: appended in-row entries are put in id order
-    uint32_t *tail_ids, *tail_q;                 // ... through a copy (tail_cap entries) and a queue of rows with many of them
-    float *tail_w;
-    uint32_t tail_cap;
-    unsigned long long *sk_in;                   // ... and the changed edges sorted by (sink, source): keys before / after,
-    const unsigned long long *sk_out;
-    float *sv_in;                                // ... with what each adds to its sink's aggregates (+1 / -1 / 0)
-    const float *sv_out;
-    uint32_t n_sort;                             // entries the sort takes (those past n_struct hold the largest key)
+    int det;                                     // deterministic mode
 };
 
 __device__ __forceinline__ void touch_row(const MutArgs &a, uint32_t x, uint32_t bit) {
@@ -358,195 +354,6 @@ __device__ __forceinline__ void touch_row(const MutArgs &a, uint32_t x, uint32_t
     uint32_t p = atomicAdd(cnt, 1u);
     if (p < a.touch_cap) lst[p] = x;
     else a.ctr->error = 2;
-}
-
-__global__ void k_vertex_validate(MutArgs a) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n_ops) return;
-    ripple_update op = a.ops[i];
-    uint32_t st = 0;
-    if (op.kind == RIPPLE_VERTEX_ADD) {
-        if (!rp_bit(a.alive, op.u)) {
-            st = 1;
-            atomicOr(&a.vstate[op.u], VS_ADDING);
-        }
-    } else if (op.kind == RIPPLE_VERTEX_DEL) {
-        if (rp_bit(a.alive, op.u)) {
-            st = 1;
-            atomicOr(&a.vstate[op.u], VS_DYING);
-            atomicAdd(&a.ctr->need_exp, a.out_meta[op.u].y + a.in_meta[op.u].y);
-        }
-    } else {
-        return;                                   // edge operations and feature updates: k_edge_validate
-    }
-    a.status[i] = st;
-}
-
-// Is the edge operation valid; where are its entries. To be called by the whole wavefront.
-__device__ __forceinline__ uint32_t check_edge(const MutArgs &a, const ripple_update &op, int &po, int &pi) {
-    const uint32_t u = op.u, v = op.v;
-    const uint2 mo = a.out_meta[u], mi = a.in_meta[v];
-    po = pi = -1;
-    if (op.kind == RIPPLE_EDGE_ADD) {
-        const int p = (mo.y <= mi.y) ? rp_wave_find(a.out_pool + mo.x, mo.y, v) : rp_wave_find(a.in_pool + mi.x, mi.y, u);
-        return p < 0 ? 1u : 0u;
-    }
-    po = rp_wave_find(a.out_pool + mo.x, mo.y, v);
-    if (po < 0) return 0u;
-    pi = rp_wave_find(a.in_pool + mi.x, mi.y, u);
-    if (pi >= 0) return 1u;
-    if (rp_lane() == 0) a.ctr->error = 3;                          // the two adjacencies disagree
-    return 0u;
-}
-// An accepted edge operation's per-row counts and first touches: bit 0 accepted, 1 add, 2 / 3 first touch of out-row(u) /
-// in-row(v). One lane.
-__device__ __forceinline__ uint32_t count_edge(const MutArgs &a, const ripple_update &op, uint32_t i, int po, int pi) {
-    const bool is_add = op.kind == RIPPLE_EDGE_ADD;
-    if (is_add) {
-        atomicAdd(&a.pend_out[op.u], 1u);
-        atomicAdd(&a.pend_in[op.v], 1u);
-    } else {
-        a.pos_out[i] = (uint32_t)po;
-        a.pos_in[i] = (uint32_t)pi;
-        atomicAdd(&a.dead_out[op.u], 1u);
-        atomicAdd(&a.dead_in[op.v], 1u);
-    }
-    uint32_t flags = 1u | (is_add ? 2u : 0u);
-    if (!(atomicOr(&a.vstate[op.u], VS_TOUCH_OUT) & VS_TOUCH_OUT)) flags |= 4u;
-    if (!(atomicOr(&a.vstate[op.v], VS_TOUCH_IN) & VS_TOUCH_IN)) flags |= 8u;
-    return flags;
-}
-// EDGE_REWEIGHT: the edge must exist; nothing about the rows' shape changes
-__device__ __forceinline__ int find_weight(const MutArgs &a, const ripple_update &op) {
-    if (!a.in_w || !rp_bit(a.alive, op.u) || !rp_bit(a.alive, op.v)) return -1;
-    const uint2 mi = a.in_meta[op.v];
-    return rp_wave_find(a.in_pool + mi.x, mi.y, op.u);
-}
-
-__global__ __launch_bounds__(256) void k_edge_validate(MutArgs a) {
-    const int lane = rp_lane();
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t i = gw; i < a.n_ops; i += nw) {
-        ripple_update op = a.ops[i];
-        uint32_t st = 0, flags = 0;
-        if (op.kind == RIPPLE_FEAT_UPDATE) {               // needs the live flag only
-            st = rp_bit(a.alive, op.u) ? 1u : 0u;
-        } else if (op.kind == RIPPLE_EDGE_REWEIGHT) {
-            const int p = find_weight(a, op);
-            st = p >= 0 ? 1u : 0u;
-            if (lane == 0 && st) a.pos_in[i] = (uint32_t)p;
-        } else if (op.kind == RIPPLE_EDGE_ADD || op.kind == RIPPLE_EDGE_DEL) {
-            const bool ok = (rp_bit(a.alive, op.u) || (a.vstate[op.u] & VS_ADDING)) &&
-                            (rp_bit(a.alive, op.v) || (a.vstate[op.v] & VS_ADDING));
-            int po = -1, pi = -1;
-            if (ok) st = check_edge(a, op, po, pi);
-            // thousands of wavefronts bumping the same few counters would queue up behind one
-            // another: only the per-row bits are set here, k_touch_lists builds lists and counts
-            if (lane == 0 && st) flags = count_edge(a, op, i, po, pi);
-        } else {                                           // vertex operations: k_vertex_validate
-            if (lane == 0) a.op_touch[i] = 0;
-            continue;
-        }
-        if (lane == 0) {
-            a.status[i] = st;
-            a.op_touch[i] = flags;
-        }
-    }
-}
-
-// Touched-row lists and accepted add / delete counts of the edge operations, from the flags that
-// k_edge_validate left per operation: one workgroup, block-wide ranks instead of one atomic per row.
-__global__ __launch_bounds__(1024) void k_touch_lists(MutArgs a) {
-    __shared__ uint32_t s_o[16], s_i[16], s_a[16], s_d[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t base_o = a.ctr->n_touch_out, base_i = a.ctr->n_touch_in;     // nothing else runs meanwhile
-    uint32_t adds = 0, dels = 0;                                            // per wavefront (lane 0 keeps them)
-    for (uint32_t start = 0; start < a.n_ops; start += 1024) {
-        const uint32_t i = start + tid;
-        const uint32_t f = (i < a.n_ops) ? a.op_touch[i] : 0u;
-        const unsigned long long mo = __ballot((f & 4u) != 0), mi = __ballot((f & 8u) != 0);
-        adds += (uint32_t)__popcll(__ballot((f & 3u) == 3u));
-        dels += (uint32_t)__popcll(__ballot((f & 3u) == 1u));
-        if (lane == 0) {
-            s_o[wave] = (uint32_t)__popcll(mo);
-            s_i[wave] = (uint32_t)__popcll(mi);
-        }
-        __syncthreads();
-        uint32_t off_o = 0, off_i = 0, tot_o = 0, tot_i = 0;
-        for (int k = 0; k < 16; ++k) {
-            if (k < wave) {
-                off_o += s_o[k];
-                off_i += s_i[k];
-            }
-            tot_o += s_o[k];
-            tot_i += s_i[k];
-        }
-        const unsigned long long below = (1ull << lane) - 1ull;
-        if (f & 4u) {
-            const uint32_t p = base_o + off_o + (uint32_t)__popcll(mo & below);
-            if (p < a.touch_cap) a.touch_out[p] = a.ops[i].u;
-            else a.ctr->error = 2;
-        }
-        if (f & 8u) {
-            const uint32_t p = base_i + off_i + (uint32_t)__popcll(mi & below);
-            if (p < a.touch_cap) a.touch_in[p] = a.ops[i].v;
-            else a.ctr->error = 2;
-        }
-        base_o += tot_o;
-        base_i += tot_i;
-        __syncthreads();                                    // s_o / s_i are rewritten by the next round
-    }
-    if (lane == 0) {
-        s_a[wave] = adds;
-        s_d[wave] = dels;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t ta = 0, td = 0;
-        for (int k = 0; k < 16; ++k) {
-            ta += s_a[k];
-            td += s_d[k];
-        }
-        a.ctr->n_add += ta;
-        a.ctr->n_del += td;
-        a.ctr->n_touch_out = base_o;
-        a.ctr->n_touch_in = base_i;
-    }
-}
-
-// pool entries that relocating touched row j (out-rows first, `no` of them) takes
-__device__ __forceinline__ uint32_t row_need(const MutArgs &a, uint32_t j, uint32_t no) {
-    const bool out = j < no;
-    const uint32_t x = out ? a.touch_out[j] : a.touch_in[j - no];
-    const uint32_t pend = out ? a.pend_out[x] : a.pend_in[x];
-    const uint32_t need = out ? a.out_meta[x].y - a.dead_out[x] + pend : a.in_meta[x].y - a.dead_in[x] + pend;
-    return (pend && need > (out ? a.out_capv[x] : a.in_capv[x])) ? rp_row_cap(need) : 0u;
-}
-// whether the batch may be committed at all
-__device__ __forceinline__ uint32_t decide(const MutArgs &a, uint32_t need_out, uint32_t need_in) {
-    const DevCtr *c = a.ctr;
-    uint32_t flag = 0;
-    if ((unsigned long long)c->out_top + need_out > a.pool_cap || (unsigned long long)c->in_top + need_in > a.pool_cap)
-        flag |= 1u;
-    if (c->n_edges + c->n_add > a.e_cap + c->n_del) flag |= 2u;
-    if (c->need_exp > a.exp_cap || (unsigned long long)c->n_add + c->n_del + c->need_exp > a.struct_cap ||
-        (unsigned long long)c->n_add + c->n_del + c->need_exp > a.touch_cap)
-        flag |= 4u;
-    if (c->error) flag |= 8u;
-    return flag;
-}
-
-// How much pool space relocation will take, then (by the last workgroup to finish) the decision
-// whether the batch may be committed at all.
-__global__ void k_capacity(MutArgs a) {
-    uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t no = min(a.ctr->n_touch_out, a.touch_cap), ni = min(a.ctr->n_touch_in, a.touch_cap);
-    if (j < no + ni) {
-        const uint32_t need = row_need(a, j, no);
-        if (need) atomicAdd(j < no ? &a.ctr->need_out : &a.ctr->need_in, need);
-    }
-    if (!last_workgroup(a.ctr, gridDim.x) || threadIdx.x != 0) return;
-    a.ctr->abort_flag = decide(a, atomicAdd(&a.ctr->need_out, 0u), atomicAdd(&a.ctr->need_in, 0u));
 }
 
 // slot in a global list for every lane with pred, one atomic per wavefront
@@ -561,146 +368,584 @@ __device__ __forceinline__ uint32_t wave_reserve(uint32_t *counter, bool pred) {
     return base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
 }
 
-__global__ __launch_bounds__(256) void k_expand_vdel(MutArgs a) {
-    if (a.ctr->abort_flag) return;
+// The Apply step is paced by launches and by chains of dependent reads, not by bytes. Its launches are as few as its global
+// dependencies allow: operations staged and vertex operations judged (k_stage), edge operations judged (k_validate, beside
+// which the edges of deleted vertices are listed, then found by k_find_expanded), rows listed and measured and the decision
+// taken (k_measure), edges (k_edges: tombstones, changed edges and structural terms, A_0) and rows
+// (k_rows: feature rows, and every touched row finished by one wavefront). Small pieces do all that precedes k_edges in one
+// launch (k_small_validate). 1,000 operations on the sparse graph took eleven to thirteen launches and 120 us of kernels.
+//
+// What an operation adds to or takes out of a row reaches the row's wavefront through a segment of two arrays: validation
+// counts a row's additions and deletions (the counts' old values number them), the rows' segments are laid out one after
+// the other (base in hole_out / hole_in: first the deletions, then the additions), and k_edges puts every operation's entry
+// where its number says. So neither tombstones nor room for additions have to be searched for: squeezing two tombstones
+// out of a row of ten thousand entries reads two entries and not all.
+
+// operations from pinned host memory; vertex operations are judged on the way; bitmaps cleared
+__global__ __launch_bounds__(256) void k_stage(MutArgs a, const ripple_update *src, ripple_update *dst, uint32_t *bitmaps, uint32_t n_bitmap_words) {
+    const uint32_t stride = gridDim.x * 256u, t = blockIdx.x * 256u + threadIdx.x;
+    for (uint32_t k = t; k < n_bitmap_words; k += stride) bitmaps[k] = 0;
+    for (uint32_t i = t; i < a.n_ops; i += stride) {
+        const ripple_update op = src[i];
+        dst[i] = op;
+        if (op.kind == RIPPLE_VERTEX_ADD) {
+            const bool ok = !rp_bit(a.alive, op.u);
+            if (ok) atomicOr(&a.vstate[op.u], VS_ADDING);
+            a.status[i] = ok ? 1u : 0u;
+        } else if (op.kind == RIPPLE_VERTEX_DEL) {
+            const bool ok = rp_bit(a.alive, op.u);
+            if (ok) {
+                atomicOr(&a.vstate[op.u], VS_DYING);
+                atomicAdd(&a.ctr->need_exp, a.out_meta[op.u].y + a.in_meta[op.u].y);
+            }
+            a.status[i] = ok ? 1u : 0u;
+        }
+    }
+}
+
+// Where `target` is in the row, searched by PARTS wavefronts that take blocks of 2,048 entries in turn; -1 if this wavefront does
+// not find it
+template <uint32_t PARTS>
+__device__ __forceinline__ int find_part(const uint32_t *row, uint32_t len, uint32_t target, uint32_t part) {
+    if (PARTS == 1) return rp_wave_find(row, len, target);
+    if (len <= 256u) return part == 0 && len ? rp_wave_find_blocks<1>(row, 0, len, target) : -1;
+    for (uint32_t base = part * 2048u; base < len; base += PARTS * 2048u) {
+        const int p = rp_wave_find_blocks<8>(row, base, len, target);
+        if (p >= 0) return p;
+    }
+    return -1;
+}
+
+// An accepted edge operation's number in its rows, and its flags: bit 0 accepted, 1 add, 2 / 3 first touch of out-row(u) /
+// in-row(v). One lane.
+__device__ __forceinline__ uint32_t count_edge(const MutArgs &a, const ripple_update &op, uint32_t i, int po, int pi) {
+    const bool is_add = op.kind == RIPPLE_EDGE_ADD;
+    // the four atomics are under way together: nothing waits for one before the next is sent
+    const uint32_t to = atomicOr(&a.vstate[op.u], VS_TOUCH_OUT), ti = atomicOr(&a.vstate[op.v], VS_TOUCH_IN);
+    const uint32_t ro = atomicAdd(is_add ? &a.pend_out[op.u] : &a.dead_out[op.u], 1u);
+    const uint32_t ri = atomicAdd(is_add ? &a.pend_in[op.v] : &a.dead_in[op.v], 1u);
+    if (!is_add) {
+        a.pos_out[i] = (uint32_t)po;
+        a.pos_in[i] = (uint32_t)pi;
+    }
+    a.rank_out[i] = ro;
+    a.rank_in[i] = ri;
+    const uint32_t flags = 1u | (is_add ? 2u : 0u) | ((to & VS_TOUCH_OUT) ? 0u : 4u) | ((ti & VS_TOUCH_IN) ? 0u : 8u);
+    return flags;
+}
+
+// One operation, by W wavefronts that search its rows together (W = 1: one wavefront that shares nothing with the others of its
+// workgroup). Thousands of wavefronts bumping the same few counters would queue up behind one another: only the rows' own bits
+// and counts are set here, measure() makes the lists.
+// SMALL: vertex operations are judged here too, and a vertex that is not alive may have been created by this piece (ops)
+template <int W, int SMALL>
+__device__ __forceinline__ void validate_op(const MutArgs &a, const ripple_update *ops, uint32_t i, const ripple_update &op, int *s_pos) {
     const int lane = rp_lane();
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t wave = W == 1 ? 0u : threadIdx.x >> 6;
+    const bool first = W == 1 ? lane == 0 : threadIdx.x == 0;
+    const bool is_add = op.kind == RIPPLE_EDGE_ADD, is_edge = is_add || op.kind == RIPPLE_EDGE_DEL;
+    if (W > 1) {
+        if (threadIdx.x < 2) s_pos[threadIdx.x] = -1;
+        __syncthreads();
+    }
+    uint32_t st = 0;
+    bool judged = true;
+    int po = -1, pi = -1;
+    if (op.kind == RIPPLE_FEAT_UPDATE) {                   // needs the live flag only
+        st = rp_bit(a.alive, op.u) ? 1u : 0u;
+    } else if (op.kind == RIPPLE_VERTEX_ADD || op.kind == RIPPLE_VERTEX_DEL) {
+        judged = SMALL;                                    // (otherwise by k_stage)
+        if (SMALL) st = rp_bit(a.alive, op.u) ? 0u : 1u;   // (small pieces delete no vertices)
+    } else {
+        bool ok = true;
+        for (int side = 0; side < 2; ++side) {              // alive, or (edges) created by this piece
+            const uint32_t w = side ? op.v : op.u;
+            if (rp_bit(a.alive, w)) continue;
+            bool created = false;
+            if (!SMALL) {
+                created = is_edge && (a.vstate[w] & VS_ADDING);
+            } else if (is_edge) {
+                for (uint32_t k = lane; k < a.n_ops; k += 64u) created |= ops[k].kind == RIPPLE_VERTEX_ADD && ops[k].u == w;
+                created = __ballot(created) != 0ull;
+            }
+            ok = ok && created;
+        }
+        if (ok) {                                           // the same for all wavefronts
+            const uint2 mo = a.out_meta[op.u], mi = a.in_meta[op.v];
+            const uint32_t *ro = a.out_pool + mo.x, *ri = a.in_pool + mi.x;
+            const uint32_t half = W / 2;
+            if (is_add) {                                   // absent from the shorter of the two rows
+                if (mo.y <= mi.y) po = find_part<W>(ro, mo.y, op.v, wave);
+                else po = find_part<W>(ri, mi.y, op.u, wave);
+            } else if (!is_edge) {                          // EDGE_REWEIGHT: the edge must exist; the rows' shape stays
+                if (a.in_w) pi = find_part<W>(ri, mi.y, op.u, wave);
+            } else if (W == 1) {
+                po = find_part<1>(ro, mo.y, op.v, 0);
+                if (po >= 0) pi = find_part<1>(ri, mi.y, op.u, 0);
+            } else if (wave < half) {
+                po = find_part<(W > 1 ? W / 2 : 1)>(ro, mo.y, op.v, wave);
+            } else {
+                pi = find_part<(W > 1 ? W / 2 : 1)>(ri, mi.y, op.u, wave - half);
+            }
+            if (W > 1 && lane == 0 && po >= 0) s_pos[0] = po;    // an entry occurs once: one wavefront finds it
+            if (W > 1 && lane == 0 && pi >= 0) s_pos[1] = pi;
+        }
+        if (W > 1) {
+            __syncthreads();
+            po = s_pos[0];
+            pi = s_pos[1];
+        }
+        if (ok && is_add) st = po < 0 ? 1u : 0u;
+        else if (ok && !is_edge) st = pi >= 0 ? 1u : 0u;
+        else if (ok) {
+            st = (po >= 0 && pi >= 0) ? 1u : 0u;
+            if (first && (po >= 0) != (pi >= 0)) a.ctr->error = 3;     // the two adjacencies disagree
+        }
+        if (first && !is_edge && st) a.pos_in[i] = (uint32_t)pi;
+    }
+    if (first) {
+        if (judged) a.status[i] = st;
+        a.op_touch[i] = (is_edge && st) ? count_edge(a, op, i, po, pi) : 0u;
+    }
+    if (W > 1) __syncthreads();                             // (s_pos is set anew)
+}
+
+// the edges of the vertices that the piece deletes, a wavefront per vertex
+__device__ __forceinline__ void list_expanded(const MutArgs &a, uint32_t gw, uint32_t nw) {
+    if (a.ctr->need_exp > a.exp_cap) return;                // no room: the piece will not be committed
+    const int lane = rp_lane();
     for (uint32_t i = gw; i < a.n_ops; i += nw) {
-        ripple_update op = a.ops[i];
+        const ripple_update op = a.ops[i];
         if (op.kind != RIPPLE_VERTEX_DEL || !a.status[i]) continue;
-        uint32_t w = op.u;
-        uint2 mo = a.out_meta[w], mi = a.in_meta[w];
+        const uint32_t w = op.u;
+        const uint2 mo = a.out_meta[w], mi = a.in_meta[w];
         uint32_t base = 0;
         if (lane == 0) base = atomicAdd(&a.ctr->n_exp, mo.y + mi.y);
         base = __shfl(base, 0);
         uint32_t gone = mo.y;                               // every out-edge disappears
-        for (uint32_t j0 = 0; j0 < mo.y; j0 += 64) {
-            uint32_t j = j0 + lane;
-            bool valid = j < mo.y;
-            uint32_t y = valid ? a.out_pool[mo.x + j] : 0u;
-            bool keep = valid && !(a.vstate[y] & VS_DYING);
-            if (valid) {
-                a.exp_kind[base + j] = keep ? EXP_OUT : EXP_NONE;
-                a.exp_a[base + j] = w;
-                a.exp_b[base + j] = y;
-            }
-            uint32_t s = wave_reserve(&a.ctr->n_struct, keep);
-            if (keep) {
-                if (s < a.struct_cap) {
-                    a.st_src[s] = w;
-                    a.st_dst[s] = y;
-                    a.st_sign[s] = -1.0f;                   // times the edge weight: k_expand_apply, which finds the edge in y's in-row
-                    a.st_unit[s] = -1.0f;
-                }
-                if (a.in_w) a.exp_s[base + j] = s;
-                rp_set_bit(a.bm_sink, y);
-            }
+        for (uint32_t j = lane; j < mo.y; j += 64) {
+            const uint32_t y = a.out_pool[mo.x + j];
+            a.exp_kind[base + j] = (a.vstate[y] & VS_DYING) ? EXP_NONE : EXP_OUT;
+            a.exp_a[base + j] = w;
+            a.exp_b[base + j] = y;
         }
-        uint32_t cnt_in = 0;
         for (uint32_t j0 = 0; j0 < mi.y; j0 += 64) {
-            uint32_t j = j0 + lane;
-            bool valid = j < mi.y;
-            uint32_t x = valid ? a.in_pool[mi.x + j] : 0u;
-            bool keep = valid && !(a.vstate[x] & VS_DYING);   // edges between two dying vertices count once
+            const uint32_t j = j0 + lane;
+            const bool valid = j < mi.y;
+            const uint32_t x = valid ? a.in_pool[mi.x + j] : 0u;
+            const bool keep = valid && !(a.vstate[x] & VS_DYING);   // edges between two dying vertices count once
             if (valid) {
                 a.exp_kind[base + mo.y + j] = keep ? EXP_IN : EXP_NONE;
                 a.exp_a[base + mo.y + j] = x;
                 a.exp_b[base + mo.y + j] = w;
             }
-            cnt_in += (uint32_t)__popcll(__ballot(keep));
+            gone += (uint32_t)__popcll(__ballot(keep));
         }
-        gone += cnt_in;
-        if (lane == 0) atomicAdd(&a.ctr->n_edges, (unsigned long long)(-(long long)gone));
+        if (lane == 0) atomicAdd(&a.ctr->n_gone, gone);
     }
 }
 
-__global__ __launch_bounds__(256) void k_expand_apply(MutArgs a) {
+// The first nb workgroups judge operations, the others list the edges of deleted vertices. A workgroup per operation (W = 4) while
+// all of them are resident at once, a wavefront per operation above that: 10,000 operations take 86 and 52 us, 1,000 take 14 and 15.
+#define WORKGROUP_OPS 2048u
+template <int W>
+__global__ __launch_bounds__(256) void k_validate(MutArgs a, uint32_t nb) {
+    __shared__ int s_pos[2];
+    const uint32_t wave = threadIdx.x >> 6;
+    if (blockIdx.x >= nb) {
+        list_expanded(a, (blockIdx.x - nb) * 4u + wave, (gridDim.x - nb) * 4u);
+        return;
+    }
+    for (uint32_t i = W == 1 ? blockIdx.x * 4u + wave : blockIdx.x; i < a.n_ops; i += W == 1 ? nb * 4u : nb)
+        validate_op<W, 0>(a, a.ops, i, a.ops[i], s_pos);
+}
+
+// where a deleted vertex's edges are in the rows of the vertices that stay
+__global__ __launch_bounds__(256) void k_find_expanded(MutArgs a) {
+    const int lane = rp_lane();
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t n = min(a.ctr->n_exp, a.exp_cap);
+    for (uint32_t e = gw; e < n; e += nw) {
+        const uint32_t kind = a.exp_kind[e];
+        if (kind == EXP_NONE) continue;
+        const bool from_in = kind == EXP_OUT;               // x -> y with x dying: x leaves y's in-row; else y leaves x's out-row
+        const uint32_t x = a.exp_a[e], y = a.exp_b[e], row = from_in ? y : x;
+        const uint2 m = from_in ? a.in_meta[row] : a.out_meta[row];
+        const int p = rp_wave_find((from_in ? a.in_pool : a.out_pool) + m.x, m.y, from_in ? x : y);
+        if (lane) continue;
+        if (p < 0) {
+            a.ctr->error = from_in ? 4 : 5;                 // the two adjacencies disagree
+            a.exp_kind[e] = EXP_NONE;
+            continue;
+        }
+        a.exp_pos[e] = (uint32_t)p;
+        a.exp_rank[e] = atomicAdd(from_in ? &a.dead_in[row] : &a.dead_out[row], 1u);
+        touch_row(a, row, from_in ? VS_TOUCH_IN : VS_TOUCH_OUT);
+    }
+}
+
+// whether the batch may be committed at all
+__device__ __forceinline__ uint32_t decide(const MutArgs &a) {
+    const volatile DevCtr *c = a.ctr;
+    const uint32_t need_out = c->need_out, need_in = c->need_in;
+    uint32_t flag = 0;
+    if ((unsigned long long)c->out_top + need_out > a.pool_cap || (unsigned long long)c->in_top + need_in > a.pool_cap)
+        flag |= 1u;
+    if (c->n_edges + c->n_add > a.e_cap + c->n_del) flag |= 2u;
+    if (c->need_exp > a.exp_cap || (unsigned long long)c->n_add + c->n_del + c->need_exp > a.struct_cap ||
+        (unsigned long long)c->n_add + c->n_del + c->need_exp > a.touch_cap)
+        flag |= 4u;
+    if (c->error) flag |= 8u;
+    return flag;
+}
+
+// Touched rows are listed and measured: the entries a row's segment takes, and the pool space that moving it takes. `j` is an
+// operation whose flags say which rows it was the first to touch, or (EXPANDED) a row that k_find_expanded has listed. A few
+// atomics per wavefront; the ones that hand out places and segments are under way together.
+template <int EXPANDED>
+__device__ __forceinline__ void measure(const MutArgs &a, const ripple_update *ops, uint32_t j, uint32_t listed_out, uint32_t listed_in) {
+    const int lane = rp_lane();
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t f = 0, u = 0, v = 0;
+    if (EXPANDED) {
+        if (j < listed_out) {
+            f = 4u;
+            u = a.touch_out[j];
+        } else if (j < listed_out + listed_in) {
+            f = 8u;
+            v = a.touch_in[j - listed_out];
+        }
+    } else if (j < a.n_ops) {
+        f = a.op_touch[j];
+        if (f) {
+            u = ops[j].u;
+            v = ops[j].v;
+        }
+    }
+    const unsigned long long mo = __ballot((f & 4u) != 0), mi = __ballot((f & 8u) != 0);
+    uint32_t eo = 0, ei = 0, no = 0, ni = 0;
+    if (f & 4u) {
+        const uint32_t pend = a.pend_out[u], dead = a.dead_out[u], need = a.out_meta[u].y - dead + pend;
+        eo = dead + pend;
+        if (pend && need > a.out_capv[u]) no = rp_row_cap(need);
+    }
+    if (f & 8u) {
+        const uint32_t pend = a.pend_in[v], dead = a.dead_in[v], need = a.in_meta[v].y - dead + pend;
+        ei = dead + pend;
+        if (pend && need > a.in_capv[v]) ni = rp_row_cap(need);
+    }
+    const uint32_t incl = rp_wave_scan(eo + ei), sum_no = rp_wave_scan(no), sum_ni = rp_wave_scan(ni);
+    const uint32_t adds = (uint32_t)__popcll(__ballot((f & 3u) == 3u)), dels = (uint32_t)__popcll(__ballot((f & 3u) == 1u));
+    unsigned long long place = 0;
+    uint32_t first = 0;
+    if (lane == 63) {
+        if (!EXPANDED) {
+            if (mo | mi)
+                place = atomicAdd(&a.ctr->n_listed, ((unsigned long long)__popcll(mi) << 32) | (uint32_t)__popcll(mo));
+            if (adds) atomicAdd(&a.ctr->n_add, adds);
+            if (dels) atomicAdd(&a.ctr->n_del, dels);
+        }
+        if (incl) first = atomicAdd(&a.ctr->n_entries, incl);
+        if (sum_no) atomicAdd(&a.ctr->need_out, sum_no);
+        if (sum_ni) atomicAdd(&a.ctr->need_in, sum_ni);
+    }
+    first = (uint32_t)__shfl((int)first, 63) + incl - eo - ei;
+    if (f & 4u) a.hole_out[u] = first;
+    if (f & 8u) a.hole_in[v] = first + eo;
+    if (EXPANDED) return;
+    const uint32_t po = listed_out + (uint32_t)__shfl((int)(uint32_t)place, 63) + (uint32_t)__popcll(mo & below);
+    const uint32_t pi = listed_in + (uint32_t)__shfl((int)(uint32_t)(place >> 32), 63) + (uint32_t)__popcll(mi & below);
+    if (f & 4u) {
+        if (po < a.touch_cap) a.touch_out[po] = u;
+        else a.ctr->error = 2;
+    }
+    if (f & 8u) {
+        if (pi < a.touch_cap) a.touch_in[pi] = v;
+        else a.ctr->error = 2;
+    }
+}
+// by one thread, when all rows have been measured
+__device__ __forceinline__ void close_lists(const MutArgs &a, uint32_t listed_out, uint32_t listed_in) {
+    const unsigned long long n = *(const volatile unsigned long long *)&a.ctr->n_listed;
+    a.ctr->n_touch_out = listed_out + (uint32_t)n;
+    a.ctr->n_touch_in = listed_in + (uint32_t)(n >> 32);
+    a.ctr->abort_flag = decide(a);
+}
+// (one workgroup over 2,000 rows takes 17 us, four take 6: a compute unit has only so many reads under way)
+__global__ __launch_bounds__(256) void k_measure(MutArgs a) {
+    const uint32_t listed_out = a.ctr->n_touch_out, listed_in = a.ctr->n_touch_in;       // by k_find_expanded
+    for (uint32_t start = blockIdx.x * 256u; start < a.n_ops; start += gridDim.x * 256u)
+        measure<0>(a, a.ops, start + threadIdx.x, listed_out, listed_in);
+    for (uint32_t start = blockIdx.x * 256u; start < listed_out + listed_in; start += gridDim.x * 256u)
+        measure<1>(a, a.ops, start + threadIdx.x, listed_out, listed_in);
+    if (last_workgroup(a.ctr, gridDim.x) && threadIdx.x == 0) close_lists(a, listed_out, listed_in);
+}
+
+// All that precedes k_edges in one launch, for pieces of up to SMALL_OPS operations without vertex deletions. The first nb
+// workgroups judge the operations, which they read from pinned host memory; the others clear the bitmaps. The last of the former
+// makes the lists of touched rows, measures them and decides. Every workgroup that arrives there costs about 60 ns, one after the
+// other, so they are at most SMALL_WGS: a workgroup per operation (W = 4) up to that number, a wavefront per operation (W = 1) above.
+#define SMALL_WGS 128u
+#define SMALL_OPS (4u * SMALL_WGS)
+template <int W>
+__global__ __launch_bounds__(256) void k_small_validate(MutArgs a, const ripple_update *src, ripple_update *dst, uint32_t nb,
+                                                        uint32_t *bitmaps, uint32_t n_bitmap_words) {
+    __shared__ int s_pos[2];
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x >= nb) {
+        const uint32_t stride = (gridDim.x - nb) * 256u;
+        for (uint32_t k = (blockIdx.x - nb) * 256u + tid; k < n_bitmap_words; k += stride) bitmaps[k] = 0;
+        return;
+    }
+    for (uint32_t i = W == 1 ? blockIdx.x * 4u + (tid >> 6) : blockIdx.x; i < a.n_ops; i += W == 1 ? nb * 4u : nb) {
+        const ripple_update op = src[i];
+        if (W == 1 ? (tid & 63u) == 0 : tid == 0) dst[i] = op;
+        validate_op<W, 1>(a, src, i, op, s_pos);
+    }
+    if (!last_workgroup(a.ctr, nb)) return;
+    for (uint32_t start = 0; start < a.n_ops; start += 256u) measure<0>(a, dst, start + tid, 0u, 0u);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the counts have been added
+    __syncthreads();
+    if (tid == 0) close_lists(a, 0u, 0u);
+}
+// X^l[v] += sign * H^{l-1}[u] for one changed edge, while all H still hold their pre-batch values (Sec. 3.3.3: an added edge
+// uses 0 as the source's old embedding, a deleted edge 0 as its new one). A project-first layer's aggregate is the sum of
+// what its in-neighbours have sent (T), so a changed edge adds or removes T[u] itself.
+__device__ __forceinline__ void struct_term(const MutArgs &a, uint32_t u, uint32_t v, uint32_t l, float sg, int lane) {
+    const uint32_t w = a.T[l] ? a.xw[l] : a.d[l - 1];
+    for (uint32_t c = lane; c < w; c += 64) {
+        const float val = a.T[l] ? a.T[l][(size_t)u * w + c] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + c);
+        if (val != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * w + c], sg * val);
+    }
+}
+// layers whose rows with a changed in-edge are recomputed have no such terms, and the deterministic mode orders them (k_det_terms)
+__device__ __forceinline__ bool has_terms(const MutArgs &a, uint32_t l) { return !a.det && !((a.mono_mask >> l) & 1u); }
+
+__device__ __forceinline__ void list_changed(const MutArgs &a, uint32_t s, uint32_t u, uint32_t v, float weighted, float unit) {
+    if (s < a.struct_cap) {
+        a.st_src[s] = u;
+        a.st_dst[s] = v;
+        a.st_sign[s] = weighted;
+        a.st_unit[s] = unit;
+    }
+    rp_set_bit(a.bm_sink, v);
+}
+
+// One operation per thread: tombstones, the rows' segments, the list of changed edges, A_0 with its out-degree prefix
+__device__ __forceinline__ void apply_op(const MutArgs &a, uint32_t i) {
+    const bool in_range = i < a.n_ops;
+    const ripple_update op = in_range ? a.ops[i] : ripple_update{99u, 0u, 0u, 0u};
+    if (op.kind == RIPPLE_VERTEX_ADD || op.kind == RIPPLE_VERTEX_DEL) atomicAnd(&a.vstate[op.u], ~(VS_ADDING | VS_DYING));
     if (a.ctr->abort_flag) return;
     const int lane = rp_lane();
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    uint32_t n = min(a.ctr->n_exp, a.exp_cap);
-    for (uint32_t e = gw; e < n; e += nw) {
-        uint32_t kind = a.exp_kind[e];
-        if (kind == EXP_NONE) continue;
-        uint32_t x = a.exp_a[e], y = a.exp_b[e];
-        if (kind == EXP_OUT) {                               // x -> y with x dying: erase x from y's in-row
-            uint2 mi = a.in_meta[y];
-            int p = rp_wave_find(a.in_pool + mi.x, mi.y, x);
-            if (lane == 0) {
-                if (p >= 0) {
-                    if (a.in_w) {
-                        const uint32_t slot = a.exp_s[e];
-                        if (slot < a.struct_cap) a.st_sign[slot] = -a.in_w[mi.x + p];
-                    }
-                    a.in_pool[mi.x + p] = RP_TOMB;
-                    a.hole_in[y] = (uint32_t)p;
-                    atomicAdd(&a.dead_in[y], 1u);
-                    touch_row(a, y, VS_TOUCH_IN);
-                } else a.ctr->error = 4;
-            }
-        } else {                                             // x -> y with y dying: erase y from x's out-row
-            uint2 mo = a.out_meta[x];
-            int p = rp_wave_find(a.out_pool + mo.x, mo.y, y);
-            if (lane == 0) {
-                if (p >= 0) {
-                    a.out_pool[mo.x + p] = RP_TOMB;
-                    a.hole_out[x] = (uint32_t)p;
-                    atomicAdd(&a.dead_out[x], 1u);
-                    touch_row(a, x, VS_TOUCH_OUT);
-                } else a.ctr->error = 5;
-            }
-        }
-    }
-}
-
-// tombstone deleted edges, list every changed edge as a structural term, count results
-__device__ __forceinline__ void apply_edge(const MutArgs &a, uint32_t i) {
-    bool in_range = i < a.n_ops;
-    bool aborted = a.ctr->abort_flag != 0;
-    ripple_update op = in_range ? a.ops[i] : ripple_update{99u, 0u, 0u, 0u};
-    bool acc = in_range && a.status[i] != 0;
-    unsigned long long ma = __ballot(acc), mr = __ballot(in_range && !acc);
-    if (rp_lane() == 0 && !aborted) {
+    const bool acc = in_range && a.status[i] != 0;
+    const unsigned long long ma = __ballot(acc), mr = __ballot(in_range && !acc);
+    if (lane == 0) {
         if (ma) atomicAdd(&a.ctr->n_applied, (uint32_t)__popcll(ma));
         if (mr) atomicAdd(&a.ctr->n_rejected, (uint32_t)__popcll(mr));
     }
-    if (aborted) return;
-    bool edge = acc && (op.kind == RIPPLE_EDGE_ADD || op.kind == RIPPLE_EDGE_DEL || op.kind == RIPPLE_EDGE_REWEIGHT);
-    uint32_t s = wave_reserve(&a.ctr->n_struct, edge);
-    if (!edge) return;
-    if (op.kind == RIPPLE_EDGE_REWEIGHT) {           // the weighted sums of the sink gain (alpha_new - alpha_old) h_u
-        float *w = a.in_w + a.in_meta[op.v].x + a.pos_in[i];
-        const float alpha_new = __uint_as_float(op.feat_row);
-        if (s < a.struct_cap) {
-            a.st_src[s] = op.u;
-            a.st_dst[s] = op.v;
-            a.st_sign[s] = alpha_new - *w;
-            a.st_unit[s] = 0.0f;
+    const bool row = acc && (op.kind == RIPPLE_FEAT_UPDATE || op.kind == RIPPLE_VERTEX_ADD);
+    const unsigned long long mrow = __ballot(row);
+    if (mrow) {                                             // place and prefix come from the same addition
+        const uint32_t dg = row ? a.out_meta[op.u].y - a.dead_out[op.u] + a.pend_out[op.u] : 0u;
+        const uint32_t incl = rp_wave_scan(dg);
+        unsigned long long old = 0;
+        if (lane == 63)
+            old = atomicAdd((unsigned long long *)&a.ctr->set[0], ((unsigned long long)incl << 32) | (uint32_t)__popcll(mrow));
+        const uint32_t slot = (uint32_t)__shfl((int)(uint32_t)old, 63) + (uint32_t)__popcll(mrow & ((1ull << lane) - 1ull));
+        const uint32_t first = (uint32_t)__shfl((int)(uint32_t)(old >> 32), 63);
+        if (row) {
+            a.list0[slot] = op.u;
+            a.eoff0[slot] = first + incl - dg;
         }
-        *w = alpha_new;
-        rp_set_bit(a.bm_sink, op.v);
+    }
+    const bool edge = acc && (op.kind == RIPPLE_EDGE_ADD || op.kind == RIPPLE_EDGE_DEL);
+    const uint32_t s = wave_reserve(&a.ctr->n_struct, edge);
+    if (!edge) return;
+    float alpha = 1.0f;                                     // the edge's weight (1 on unweighted graphs)
+    if (op.kind == RIPPLE_EDGE_DEL) {
+        const uint32_t po = a.pos_out[i], pi = a.pos_in[i], si = a.hole_in[op.v] + a.rank_in[i];
+        const size_t ri = (size_t)a.in_meta[op.v].x + pi;
+        if (a.in_w) alpha = a.in_w[ri];
+        a.seg_x[a.hole_out[op.u] + a.rank_out[i]] = po;
+        a.seg_x[si] = pi;
+        a.seg_id[si] = op.u;
+        a.out_pool[a.out_meta[op.u].x + po] = RP_TOMB;
+        a.in_pool[ri] = RP_TOMB;
+        list_changed(a, s, op.u, op.v, -alpha, -1.0f);
+    } else {
+        const uint32_t si = a.hole_in[op.v] + a.dead_in[op.v] + a.rank_in[i];
+        if (a.in_w) alpha = __uint_as_float(op.feat_row);   // weighted graphs: EDGE_ADD carries the weight's bits there
+        a.seg_id[a.hole_out[op.u] + a.dead_out[op.u] + a.rank_out[i]] = op.v;
+        a.seg_id[si] = op.u;
+        a.seg_x[si] = __float_as_uint(alpha);
+        list_changed(a, s, op.u, op.v, alpha, 1.0f);
+    }
+}
+
+// the edges of deleted vertices: the same, a thread per edge, then the terms, a wavefront per edge
+__device__ __forceinline__ void apply_expanded(const MutArgs &a, uint32_t gw, uint32_t nw) {
+    if (a.ctr->abort_flag) return;
+    const int lane = rp_lane();
+    const uint32_t n = min(a.ctr->n_exp, a.exp_cap);
+    for (uint32_t e0 = gw * 64u; e0 < n; e0 += nw * 64u) {
+        const uint32_t e = e0 + lane, kind = e < n ? a.exp_kind[e] : EXP_NONE;
+        const uint32_t s = wave_reserve(&a.ctr->n_struct, kind == EXP_OUT);
+        if (kind == EXP_NONE) continue;
+        const uint32_t x = a.exp_a[e], y = a.exp_b[e], p = a.exp_pos[e];
+        if (kind == EXP_OUT) {
+            const uint32_t si = a.hole_in[y] + a.exp_rank[e];
+            const size_t ri = (size_t)a.in_meta[y].x + p;
+            a.seg_id[si] = x;
+            a.seg_x[si] = p;
+            a.in_pool[ri] = RP_TOMB;
+            list_changed(a, s, x, y, a.in_w ? -a.in_w[ri] : -1.0f, -1.0f);
+        } else {
+            a.seg_x[a.hole_out[x] + a.exp_rank[e]] = p;
+            a.out_pool[a.out_meta[x].x + p] = RP_TOMB;
+        }
+    }
+    if (a.det) return;
+    for (uint32_t e = gw; e < n; e += nw) {
+        if (a.exp_kind[e] != EXP_OUT) continue;
+        const uint32_t x = a.exp_a[e], y = a.exp_b[e];
+        const float alpha = a.in_w ? a.in_w[a.in_meta[y].x + a.exp_pos[e]] : 1.0f;
+        for (uint32_t l = 1; l <= a.L; ++l)
+            if (has_terms(a, l)) struct_term(a, x, y, l, ((a.wsum_mask >> l) & 1u) ? -alpha : -1.0f, lane);
+    }
+}
+
+// Three parts of one launch, none of which reads what another writes: a thread per operation (tb workgroups); the structural
+// terms of the operations' edges, a wavefront per operation and layer, or on weighted graphs per operation (sb workgroups): that
+// wavefront also gives a re-weighted edge its weight; the edges of deleted vertices (the rest).
+__global__ __launch_bounds__(256) void k_edges(MutArgs a, uint32_t tb, uint32_t sb) {
+    if (blockIdx.x < tb) {
+        apply_op(a, blockIdx.x * 256u + threadIdx.x);
         return;
     }
-    float alpha = 1.0f;                              // the edge's weight (1 on unweighted graphs)
-    if (op.kind == RIPPLE_EDGE_DEL) {
-        if (a.in_w) alpha = a.in_w[a.in_meta[op.v].x + a.pos_in[i]];
-        a.out_pool[a.out_meta[op.u].x + a.pos_out[i]] = RP_TOMB;
-        a.in_pool[a.in_meta[op.v].x + a.pos_in[i]] = RP_TOMB;
-        a.hole_out[op.u] = a.pos_out[i];
-        a.hole_in[op.v] = a.pos_in[i];
-    } else if (a.in_w) {
-        alpha = __uint_as_float(op.feat_row);       // weighted graphs: EDGE_ADD carries the weight's bits there
+    const uint32_t wave = threadIdx.x >> 6;
+    if (blockIdx.x >= tb + sb) {
+        apply_expanded(a, (blockIdx.x - tb - sb) * 4u + wave, (gridDim.x - tb - sb) * 4u);
+        return;
     }
-    if (s < a.struct_cap) {
-        a.st_src[s] = op.u;
-        a.st_dst[s] = op.v;
-        a.st_sign[s] = (op.kind == RIPPLE_EDGE_ADD) ? alpha : -alpha;
-        a.st_unit[s] = (op.kind == RIPPLE_EDGE_ADD) ? 1.0f : -1.0f;
+    if (a.ctr->abort_flag) return;
+    const int lane = rp_lane();
+    const uint32_t per = a.in_w ? 1u : a.L;
+    for (unsigned long long t = (blockIdx.x - tb) * 4u + wave; t < (unsigned long long)a.n_ops * per; t += sb * 4u) {
+        const uint32_t i = (uint32_t)(t / per), l = (uint32_t)(t - (unsigned long long)i * per) + 1u;
+        if (!a.status[i]) continue;
+        const ripple_update op = a.ops[i];
+        if (op.kind != RIPPLE_EDGE_ADD && op.kind != RIPPLE_EDGE_DEL && op.kind != RIPPLE_EDGE_REWEIGHT) continue;
+        const float unit = op.kind == RIPPLE_EDGE_ADD ? 1.0f : (op.kind == RIPPLE_EDGE_DEL ? -1.0f : 0.0f);
+        if (!a.in_w) {                                      // nothing is re-weighted, all layers see +1 / -1
+            if (has_terms(a, l)) struct_term(a, op.u, op.v, l, unit, lane);
+            continue;
+        }
+        const float given = __uint_as_float(op.feat_row);
+        float *wp = op.kind == RIPPLE_EDGE_ADD ? nullptr : a.in_w + a.in_meta[op.v].x + a.pos_in[i];
+        const float had = wp ? *wp : 0.0f;
+        const float weighted = op.kind == RIPPLE_EDGE_ADD ? given : (op.kind == RIPPLE_EDGE_DEL ? -had : given - had);
+        for (uint32_t k = 1; k <= a.L; ++k) {
+            const float sg = ((a.wsum_mask >> k) & 1u) ? weighted : unit;
+            if (sg != 0.0f && has_terms(a, k)) struct_term(a, op.u, op.v, k, sg, lane);   // (a new weight means nothing to layers that ignore weights)
+        }
+        if (op.kind == RIPPLE_EDGE_REWEIGHT && lane == 0) {  // the weighted sums of the sink gain (alpha_new - alpha_old) h_u
+            *wp = given;
+            list_changed(a, atomicAdd(&a.ctr->n_struct, 1u), op.u, op.v, weighted, 0.0f);
+        }
     }
-    rp_set_bit(a.bm_sink, op.v);
 }
-__global__ __launch_bounds__(256) void k_apply_edges(MutArgs a) { apply_edge(a, blockIdx.x * blockDim.x + threadIdx.x); }
 
+// Deterministic mode: the structural terms without atomics, and the order of appended in-row entries. A sum that walks a row in
+// storage order is only a function of the graph if that order is one: the sinks' segments, filled in the order in which
+// atomics were served, are put in ascending id order (a piece holds at most one operation per edge, so ids are distinct
+// within a segment), the terms are added in it, with plain loads and stores by one owner per 64 columns, and k_rows appends
+// the additions in it. With the rows built in the order the edges were given, and the fills of k_rows being functions of the row
+// and the deleted positions alone, an in-row's order then depends on the batches that were applied and on nothing else.
+// A workgroup per touched in-row; its wavefronts share the layers and columns, eight source rows are on their way at a time
+// (one wavefront per sink, after a radix sort of all changed edges, took 77 us per 1,000 operations where this takes 15).
+// Segments of up to DET_IDS entries are ranked in LDS, longer ones (hubs in large batches) tile by tile through `srt`.
+#define DET_IDS 1024u
+__global__ __launch_bounds__(256) void k_det_terms(MutArgs a) {
+    constexpr uint32_t ADD = 0x80000000u;                   // ids are below 2^31
+    constexpr int G = 8;
+    __shared__ uint32_t s_in[DET_IDS], s_id[DET_IDS], s_x[DET_IDS], s_w[4];
+    if (a.ctr->abort_flag) return;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t ni = min(a.ctr->n_touch_in, a.touch_cap);
+    for (uint32_t j = blockIdx.x; j < ni; j += gridDim.x) {
+        const uint32_t v = a.touch_in[j], base = a.hole_in[v], dead = a.dead_in[v], n = dead + a.pend_in[v];
+        const bool in_lds = n <= DET_IDS;
+        uint32_t *ids = in_lds ? s_id : a.srt_id + base, *xs = in_lds ? s_x : a.srt_x + base;
+        for (uint32_t i0 = 0; i0 < n; i0 += 256u) {         // every entry's rank, DET_IDS others at a time
+            const uint32_t i = i0 + tid;
+            const uint32_t my = i < n ? a.seg_id[base + i] : 0u, x = i < n ? a.seg_x[base + i] : 0u;
+            uint32_t rank = 0;
+            for (uint32_t t0 = 0; t0 < n; t0 += DET_IDS) {
+                const uint32_t cnt = min(DET_IDS, n - t0);
+                if (i0 == 0 || !in_lds) {
+                    __syncthreads();
+                    for (uint32_t k = tid; k < cnt; k += 256u) s_in[k] = a.seg_id[base + t0 + k];
+                    __syncthreads();
+                }
+                if (i < n)
+                    for (uint32_t k = 0; k < cnt; ++k) rank += s_in[k] < my ? 1u : 0u;
+            }
+            if (i < n) {
+                ids[rank] = my | (i >= dead ? ADD : 0u);
+                xs[rank] = x;
+            }
+        }
+        __threadfence_block();
+        __syncthreads();
+        uint32_t at = base + dead;                          // the additions, in order, back to their part of the segment
+        for (uint32_t i0 = 0; i0 < n; i0 += 256u) {
+            const uint32_t i = i0 + tid;
+            const uint32_t id = i < n ? ids[i] : 0u;
+            const unsigned long long m = __ballot((id & ADD) != 0);
+            if (lane == 0) s_w[wave] = (uint32_t)__popcll(m);
+            __syncthreads();
+            uint32_t off = at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            for (uint32_t k = 0; k < 4; ++k) {
+                if (k < wave) off += s_w[k];
+                at += s_w[k];
+            }
+            if (id & ADD) {
+                a.seg_id[off] = id & ~ADD;
+                a.seg_x[off] = xs[i];
+            }
+            __syncthreads();
+        }
+        uint32_t task = 0;
+        for (uint32_t l = 1; l <= a.L; ++l) {
+            if ((a.mono_mask >> l) & 1u) continue;
+            const float *Tl = a.T[l];
+            const uint32_t w = Tl ? a.xw[l] : a.d[l - 1];
+            for (uint32_t c0 = 0; c0 < w; c0 += 64, ++task) {
+                if ((task & 3u) != wave) continue;
+                const uint32_t col = c0 + lane;
+                float *xp = a.X[l] + (size_t)v * w + col;
+                float x = (col < w) ? *xp : 0.0f;
+                for (uint32_t j0 = 0; j0 < n; j0 += G) {
+                    float val[G], sg[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const uint32_t id = ids[min(j0 + (uint32_t)g, n - 1u)], u = id & ~ADD;
+                        sg[g] = (id & ADD) ? 1.0f : -1.0f;
+                        val[g] = 0.0f;
+                        if (col < w && j0 + (uint32_t)g < n)
+                            val[g] = Tl ? Tl[(size_t)u * w + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
+                    }
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+                        if (j0 + (uint32_t)g < n) x += sg[g] * val[g];
+                }
+                if (col < w) *xp = x;
+            }
+        }
+        __syncthreads();                                    // the next row's entries go to the same arrays
+    }
+}
 
 // feature writes (with the hop-0 delta), vertex creation, vertex removal
 __device__ __forceinline__ void apply_vertices(const MutArgs &a, uint32_t gw, uint32_t nw) {
@@ -712,9 +957,6 @@ __device__ __forceinline__ void apply_vertices(const MutArgs &a, uint32_t gw, ui
         if (!a.status[i]) continue;
         uint32_t w = op.u;
         if (op.kind == RIPPLE_FEAT_UPDATE || op.kind == RIPPLE_VERTEX_ADD) {
-            uint32_t slot = 0;
-            if (lane == 0) slot = atomicAdd(&a.ctr->set[0].a, 1u);
-            slot = __shfl(slot, 0);
             const float *row = a.payload + (size_t)op.feat_row * d0;
             for (uint32_t c = lane; c < d0; c += 64) {
                 float nv = row[c];
@@ -734,7 +976,6 @@ __device__ __forceinline__ void apply_vertices(const MutArgs &a, uint32_t gw, ui
                 a.D0[idx] = a.d0_old ? old : nv - old;
             }
             if (lane == 0) {
-                a.list0[slot] = w;
                 rp_set_bit(a.bm0, w);
                 if (op.kind == RIPPLE_VERTEX_ADD) {
                     atomicOr(&a.alive[w >> 5], 1u << (w & 31));
@@ -767,14 +1008,69 @@ __device__ __forceinline__ void apply_vertices(const MutArgs &a, uint32_t gw, ui
         }
     }
 }
-__global__ __launch_bounds__(256) void k_apply_vertices(MutArgs a) {
-    apply_vertices(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
+
+// Tombstones squeezed out of a row, by one wavefront: rows are unordered, so holes in the part that stays (the first
+// keep = len - dead entries) take live entries of the part that goes: its k-th hole the tail's k-th live entry.
+__device__ __forceinline__ void fill_holes(uint32_t *row, float *wrow, uint32_t keep, uint32_t len, const uint32_t *holes, uint32_t *s_live) {
+    const int lane = rp_lane();
+    const uint32_t dead = len - keep;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (dead <= 64u) {                                      // the positions are known: nothing of the head is read
+        const uint32_t hole = (uint32_t)lane < dead ? holes[lane] : 0xFFFFFFFFu;
+        const uint32_t val = (uint32_t)lane < dead ? row[keep + lane] : RP_TOMB;
+        const unsigned long long live = __ballot(val != RP_TOMB);
+        if (val != RP_TOMB) s_live[__popcll(live & below)] = (uint32_t)lane;
+        uint32_t rank = 0;
+        for (uint32_t k = 0; k < dead; ++k) rank += (uint32_t)__shfl((int)hole, (int)k) < hole ? 1u : 0u;
+        __builtin_amdgcn_wave_barrier();
+        if (hole < keep) {                                  // as many as the tail has live entries
+            const uint32_t from = keep + s_live[rank];
+            row[hole] = row[from];
+            if (wrow) wrow[hole] = wrow[from];
+        }
+        return;
+    }
+    // First the live entries of the tail are packed to its front, then the head is read sixteen blocks per round.
+    uint32_t n_tail = 0;                                    // live entries packed at keep ..
+    for (uint32_t base = keep; base < len; base += 64) {
+        const uint32_t i = base + lane;
+        const uint32_t val = (i < len) ? row[i] : RP_TOMB;
+        const float wv = (wrow && i < len) ? wrow[i] : 0.0f;
+        const bool live = val != RP_TOMB;
+        const unsigned long long mask = __ballot(live);
+        const uint32_t off = (uint32_t)__popcll(mask & below);
+        if (live) {
+            row[keep + n_tail + off] = val;
+            if (wrow) wrow[keep + n_tail + off] = wv;
+        }
+        n_tail += (uint32_t)__popcll(mask);
+    }
+    uint32_t filled = 0;                                    // holes of the head filled so far
+    for (uint32_t base = 0; base < keep && filled < n_tail; base += 1024) {
+        uint32_t v[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const uint32_t i = base + 64 * t + lane;
+            v[t] = (i < keep) ? row[i] : 0u;
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const uint32_t i = base + 64 * t + lane;
+            const bool hole = i < keep && v[t] == RP_TOMB;
+            const unsigned long long mask = __ballot(hole);
+            const uint32_t k = filled + (uint32_t)__popcll(mask & below);
+            if (hole && k < n_tail) {
+                row[i] = row[keep + k];
+                if (wrow) wrow[i] = wrow[keep + k];
+            }
+            filled += (uint32_t)__popcll(mask);
+        }
+    }
 }
 
-
-// one wavefront per touched row: squeeze tombstones out, move the row if the
-// pending appends do not fit, reset the row's scratch counters
-__device__ __forceinline__ void cleanup_rows(const MutArgs &a, uint32_t gw, uint32_t nw) {
+// one wavefront per touched row: tombstones squeezed out, the row moved if the additions do not fit, the additions appended,
+// the row's scratch counters reset
+__device__ __forceinline__ void finish_rows(const MutArgs &a, uint32_t gw, uint32_t nw, uint32_t *s_live) {
     const int lane = rp_lane();
     const bool aborted = a.ctr->abort_flag != 0;
     uint32_t no = min(a.ctr->n_touch_out, a.touch_cap), ni = min(a.ctr->n_touch_in, a.touch_cap);
@@ -787,78 +1083,36 @@ __device__ __forceinline__ void cleanup_rows(const MutArgs &a, uint32_t gw, uint
         float *wp = is_out ? nullptr : a.in_w;             // weights travel with the in-row's entries
         uint32_t *deadv = is_out ? a.dead_out : a.dead_in;
         uint32_t *pendv = is_out ? a.pend_out : a.pend_in;
-        uint32_t *top = is_out ? &a.ctr->out_top : &a.ctr->in_top;
         if (!aborted) {
             uint2 m = meta[x];
-            uint32_t dead = deadv[x], pend = pendv[x];
-            uint32_t len = m.y;
-            const uint32_t hole = is_out ? a.hole_out[x] : a.hole_in[x];
-            if (dead == 1 && len && hole < len && pool[m.x + hole] == RP_TOMB) {
-                // the usual case, one deletion in the row: its position is known, the last entry fills it
-                if (hole != len - 1 && lane == 0) {
-                    pool[m.x + hole] = pool[m.x + len - 1];
-                    if (wp) wp[m.x + hole] = wp[m.x + len - 1];
+            const uint32_t dead = deadv[x], pend = pendv[x], cap = capv[x], seg = is_out ? a.hole_out[x] : a.hole_in[x];
+            uint32_t len = m.y - min(dead, m.y);
+            if (dead == 1 && m.y) {                         // the usual case: the last entry fills the hole
+                const uint32_t hole = a.seg_x[seg];
+                if (hole < len && lane == 0) {
+                    pool[m.x + hole] = pool[m.x + len];
+                    if (wp) wp[m.x + hole] = wp[m.x + len];
                 }
-                len -= 1;
-            } else if (dead && len) {
-                // Rows are unordered, so holes in the part that stays (the first len - dead entries) are
-                // filled from the part that goes. First the live entries of that tail are packed to its
-                // front (it is at most `dead` long), then the head is read sixteen blocks per round and
-                // its k-th hole takes the tail's k-th live entry.
-                const uint32_t keep_len = len - min(dead, len);
-                uint32_t n_tail = 0;                               // live entries packed at keep_len ..
-                for (uint32_t base = keep_len; base < len; base += 64) {
-                    const uint32_t i = base + lane;
-                    const uint32_t val = (i < len) ? pool[m.x + i] : RP_TOMB;
-                    const float wv = (wp && i < len) ? wp[m.x + i] : 0.0f;
-                    const bool keep = val != RP_TOMB;
-                    const unsigned long long mask = __ballot(keep);
-                    const uint32_t off = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                    if (keep) {
-                        pool[m.x + keep_len + n_tail + off] = val;
-                        if (wp) wp[m.x + keep_len + n_tail + off] = wv;
-                    }
-                    n_tail += (uint32_t)__popcll(mask);
-                }
-                uint32_t filled = 0;                               // holes of the head filled so far
-                for (uint32_t base = 0; base < keep_len && filled < n_tail; base += 1024) {
-                    uint32_t v[16];
-#pragma unroll
-                    for (int t = 0; t < 16; ++t) {
-                        const uint32_t i = base + 64 * t + lane;
-                        v[t] = (i < keep_len) ? pool[m.x + i] : 0u;
-                    }
-#pragma unroll
-                    for (int t = 0; t < 16; ++t) {
-                        const uint32_t i = base + 64 * t + lane;
-                        const bool hole = i < keep_len && v[t] == RP_TOMB;
-                        const unsigned long long mask = __ballot(hole);
-                        const uint32_t k = filled + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                        if (hole && k < n_tail) {
-                            pool[m.x + i] = pool[m.x + keep_len + k];
-                            if (wp) wp[m.x + i] = wp[m.x + keep_len + k];
-                        }
-                        filled += (uint32_t)__popcll(mask);
-                    }
-                }
-                len = keep_len;
+            } else if (dead) {
+                fill_holes(pool + m.x, wp ? wp + m.x : nullptr, len, m.y, a.seg_x + seg, s_live);
             }
-            uint32_t need = len + pend;
-            if (pend && need > capv[x]) {
+            const uint32_t need = len + pend;
+            bool room = true;
+            if (pend && need > cap) {
                 uint32_t ncap = rp_row_cap(need);
                 uint32_t ns = 0;
-                if (lane == 0) ns = atomicAdd(top, ncap);
+                if (lane == 0) ns = atomicAdd(is_out ? &a.ctr->out_top : &a.ctr->in_top, ncap);
                 ns = __shfl(ns, 0);
                 if ((unsigned long long)ns + ncap <= a.pool_cap) {
-                    for (uint32_t base = 0; base < len; base += 512) {      // eight blocks in flight per round
-                        uint32_t v[8];
+                    for (uint32_t base = 0; base < len; base += 1024) {     // sixteen blocks in flight per round
+                        uint32_t v[16];
 #pragma unroll
-                        for (int t = 0; t < 8; ++t) {
+                        for (int t = 0; t < 16; ++t) {
                             const uint32_t i = base + 64 * t + lane;
                             v[t] = (i < len) ? pool[m.x + i] : 0u;
                         }
 #pragma unroll
-                        for (int t = 0; t < 8; ++t) {
+                        for (int t = 0; t < 16; ++t) {
                             const uint32_t i = base + 64 * t + lane;
                             if (i < len) pool[ns + i] = v[t];
                         }
@@ -867,14 +1121,17 @@ __device__ __forceinline__ void cleanup_rows(const MutArgs &a, uint32_t gw, uint
                         for (uint32_t i = lane; i < len; i += 64) wp[ns + i] = wp[m.x + i];
                     m.x = ns;
                     if (lane == 0) capv[x] = ncap;
-                } else if (lane == 0) {
-                    a.ctr->error = 6;                        // cannot happen: space was checked before commit
+                } else {
+                    room = false;
+                    if (lane == 0) a.ctr->error = 6;         // cannot happen: space was checked before commit
                 }
             }
-            if (lane == 0) {
-                meta[x] = make_uint2(m.x, len);
-                if (a.det && !is_out) a.hole_in[x] = len;    // where this batch's appends start (the hole is filled)
+            for (uint32_t k = lane; room && k < pend; k += 64) {
+                const uint32_t at = seg + dead + k;
+                pool[m.x + len + k] = a.seg_id[at];
+                if (wp) wp[m.x + len + k] = __uint_as_float(a.seg_x[at]);
             }
+            if (lane == 0) meta[x] = make_uint2(m.x, room ? need : len);
         }
         if (lane == 0) {
             deadv[x] = 0;
@@ -883,224 +1140,26 @@ __device__ __forceinline__ void cleanup_rows(const MutArgs &a, uint32_t gw, uint
         }
     }
 }
-__global__ __launch_bounds__(256) void k_cleanup_rows(MutArgs a) {
-    cleanup_rows(a, (blockIdx.x * blockDim.x + threadIdx.x) >> 6, (gridDim.x * blockDim.x) >> 6);
-}
 
-
-__device__ __forceinline__ void append_edge(const MutArgs &a, const ripple_update &op) {
-    uint32_t p = atomicAdd(&((uint32_t *)a.out_meta)[2 * (size_t)op.u + 1], 1u);
-    if (p < a.out_capv[op.u]) a.out_pool[a.out_meta[op.u].x + p] = op.v;
-    else a.ctr->error = 7;
-    p = atomicAdd(&((uint32_t *)a.in_meta)[2 * (size_t)op.v + 1], 1u);
-    if (p < a.in_capv[op.v]) {
-        a.in_pool[a.in_meta[op.v].x + p] = op.u;
-        if (a.in_w) a.in_w[a.in_meta[op.v].x + p] = __uint_as_float(op.feat_row);
-    } else a.ctr->error = 7;
-}
-
-__global__ void k_apply_adds(MutArgs a) {
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool aborted = a.ctr->abort_flag != 0;
-    if (i == 0 && !aborted) {
-        atomicAdd(&a.ctr->n_edges, (unsigned long long)a.ctr->n_add);
-        atomicAdd(&a.ctr->n_edges, (unsigned long long)(-(long long)a.ctr->n_del));
+// Feature rows, created and deleted vertices (the first nb workgroups) and the touched rows (the others). The two parts meet
+// nowhere: a deleted vertex's own rows are not touched ones.
+__global__ __launch_bounds__(256) void k_rows(MutArgs a, uint32_t nb) {
+    __shared__ uint32_t s_live[4][64];
+    const uint32_t wave = threadIdx.x >> 6;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.eoff0[a.ctr->set[0].a] = a.ctr->set[0].m;
+        if (!a.ctr->abort_flag)
+            a.ctr->n_edges += (unsigned long long)a.ctr->n_add - (unsigned long long)a.ctr->n_del - (unsigned long long)a.ctr->n_gone;
     }
-    if (i >= a.n_ops) return;
-    ripple_update op = a.ops[i];
-    if (op.kind == RIPPLE_VERTEX_ADD || op.kind == RIPPLE_VERTEX_DEL) {
-        atomicAnd(&a.vstate[op.u], ~(VS_ADDING | VS_DYING));
-        return;
-    }
-    if (aborted || op.kind != RIPPLE_EDGE_ADD || !a.status[i]) return;
-    append_edge(a, op);
+    if (blockIdx.x < nb) apply_vertices(a, blockIdx.x * 4u + wave, nb * 4u);
+    else finish_rows(a, (blockIdx.x - nb) * 4u + wave, (gridDim.x - nb) * 4u, s_live[wave]);
 }
 
-// Deterministic mode. The entries appended above land in the order their atomics were served. A sum that
-// walks a row in storage order is only a function of the graph if that order is one, so the appended part
-// of every touched in-row (it starts where k_cleanup_rows left the row's end) is put in ascending id order;
-// ids are distinct within a row. With the rows built in the order the edges were given, and the fills of
-// k_cleanup_rows being functions of the row and the deleted positions alone, an in-row's order then depends
-// on the batches that were applied and on nothing else. Up to 64 appended entries are ranked in registers by
-// the row's wavefront; longer runs are queued for k_sort_long_tails.
-__global__ __launch_bounds__(256) void k_sort_tails(MutArgs a) {
-    if (a.ctr->abort_flag) return;
-    const int lane = rp_lane();
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t ni = min(a.ctr->n_touch_in, a.touch_cap);
-    for (uint32_t j = gw; j < ni; j += nw) {
-        const uint32_t x = a.touch_in[j];
-        const uint2 m = a.in_meta[x];
-        const uint32_t start = a.hole_in[x];
-        if (start >= m.y || m.y - start < 2u) continue;
-        const uint32_t t = m.y - start;
-        if (t > 64u) {
-            if (lane == 0) a.tail_q[atomicAdd(&a.ctr->n_tail_q, 1u)] = x;
-            continue;
-        }
-        uint32_t *row = a.in_pool + m.x + start;
-        float *wr = a.in_w ? a.in_w + m.x + start : nullptr;
-        const bool mine = (uint32_t)lane < t;
-        const uint32_t id = mine ? row[lane] : 0xFFFFFFFFu;
-        const float wv = (mine && wr) ? wr[lane] : 0.0f;
-        uint32_t rank = 0;
-        for (uint32_t k = 0; k < t; ++k) rank += (__shfl(id, (int)k) < id) ? 1u : 0u;
-        if (mine) {
-            row[rank] = id;
-            if (wr) wr[rank] = wv;
-        }
-    }
-}
-
-// one workgroup per queued row: the appended entries are copied aside, every one counts the smaller ids
-// (the copy is read through LDS, 4096 at a time) and goes to that position
-__global__ __launch_bounds__(1024) void k_sort_long_tails(MutArgs a) {
-    __shared__ uint32_t s_ids[4096];
-    __shared__ uint32_t s_base;
-    if (a.ctr->abort_flag) return;
-    const uint32_t tid = threadIdx.x;
-    const uint32_t n = min(a.ctr->n_tail_q, a.touch_cap);
-    for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
-        const uint32_t x = a.tail_q[q];
-        const uint2 m = a.in_meta[x];
-        const uint32_t start = a.hole_in[x];
-        const uint32_t t = m.y - start;
-        __syncthreads();
-        if (tid == 0) s_base = atomicAdd(&a.ctr->tail_top, t);
-        __syncthreads();
-        const uint32_t base = s_base;
-        if ((unsigned long long)base + t > a.tail_cap) {     // cannot happen: a batch appends at most n_ops entries
-            if (tid == 0) a.ctr->error = 10;
-            continue;
-        }
-        uint32_t *row = a.in_pool + m.x + start;
-        float *wr = a.in_w ? a.in_w + m.x + start : nullptr;
-        for (uint32_t i = tid; i < t; i += 1024) {
-            a.tail_ids[base + i] = row[i];
-            if (wr) a.tail_w[base + i] = wr[i];
-        }
-        __syncthreads();
-        for (uint32_t eb = 0; eb < t; eb += 1024) {
-            const uint32_t i = eb + tid;
-            const uint32_t my = (i < t) ? a.tail_ids[base + i] : 0u;
-            uint32_t rank = 0;
-            for (uint32_t tb = 0; tb < t; tb += 4096) {
-                const uint32_t cnt = min(4096u, t - tb);
-                __syncthreads();
-                for (uint32_t k = tid; k < cnt; k += 1024) s_ids[k] = a.tail_ids[base + tb + k];
-                __syncthreads();
-                if (i < t)
-                    for (uint32_t k = 0; k < cnt; ++k) rank += (s_ids[k] < my) ? 1u : 0u;
-            }
-            if (i < t) {
-                row[rank] = my;
-                if (wr) wr[rank] = a.tail_w[base + i];
-            }
-        }
-    }
-}
-
-__device__ __forceinline__ void struct_term(const MutArgs &a, uint32_t u, uint32_t v, uint32_t l, float sg, int lane) {
-    const uint32_t w = a.T[l] ? a.xw[l] : a.d[l - 1];
-    for (uint32_t c = lane; c < w; c += 64) {
-        const float val = a.T[l] ? a.T[l][(size_t)u * w + c] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + c);
-        if (val != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * w + c], sg * val);
-    }
-}
-
-// X^l[v] += sign * H^{l-1}[u] for every changed edge and every layer, taken
-// while all H still hold their pre-batch values (Sec. 3.3.3: an added edge
-// uses 0 as the source's old embedding, a deleted edge 0 as its new one).
-__global__ __launch_bounds__(256) void k_struct_scatter(MutArgs a) {
-    if (a.ctr->abort_flag) return;
-    const int lane = rp_lane();
-    uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    uint32_t n = min(a.ctr->n_struct, a.struct_cap);
-    // one task per changed edge and layer. A project-first layer's aggregate is the sum of what its in-neighbours
-    // have sent (T), so a changed edge adds or removes T[u] itself
-    const uint32_t per = a.L;
-    unsigned long long total = (unsigned long long)n * per;
-    for (unsigned long long t = gw; t < total; t += nw) {
-        const uint32_t e = (uint32_t)(t / per), l = (uint32_t)(t % per) + 1;
-        if ((a.mono_mask >> l) & 1u) continue;               // rows with a changed in-edge are recomputed instead
-        uint32_t u = a.st_src[e], v = a.st_dst[e];
-        const float sg = ((a.wsum_mask >> l) & 1u) ? a.st_sign[e] : a.st_unit[e];
-        if (sg == 0.0f) continue;                            // a new weight means nothing to a layer that ignores weights
-        struct_term(a, u, v, l, sg, lane);
-    }
-}
-
-// Deterministic mode: the same terms without atomics. The changed edges are sorted by (sink, source) - a piece of a
-// batch holds at most one operation per edge, so the keys are distinct and the order is a function of the piece -
-// and the wavefront that finds the first entry of a sink adds that sink's terms one after the other, for every
-// layer, with plain loads and stores; eight source rows are in flight at a time.
-__global__ void k_struct_keys(MutArgs a) {
-    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= a.n_sort) return;
-    const uint32_t n = a.ctr->abort_flag ? 0u : min(a.ctr->n_struct, a.struct_cap);
-    a.sk_in[e] = (e < n) ? (((unsigned long long)a.st_dst[e] << 32) | a.st_src[e]) : ~0ull;
-    a.sv_in[e] = (e < n) ? a.st_unit[e] : 0.0f;
-}
-
-__global__ __launch_bounds__(256) void k_struct_ordered(MutArgs a) {
-    if (a.ctr->abort_flag) return;
-    constexpr int G = 8;
-    const int lane = rp_lane();
-    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t n = min(min(a.ctr->n_struct, a.struct_cap), a.n_sort);
-    for (uint32_t e0 = gw; e0 < n; e0 += nw) {
-        const uint32_t v = (uint32_t)(a.sk_out[e0] >> 32);
-        if (e0 > 0 && (uint32_t)(a.sk_out[e0 - 1] >> 32) == v) continue;   // not the sink's first entry
-        uint32_t len = 1;                                                  // entries of this sink
-        for (bool more = true; more;) {
-            const uint32_t f = e0 + len + (uint32_t)lane;
-            const unsigned long long other = __ballot(f >= n || (uint32_t)(a.sk_out[f] >> 32) != v);
-            if (other) {
-                len += (uint32_t)__ffsll((long long)other) - 1u;
-                more = false;
-            } else len += 64u;
-        }
-        for (uint32_t l = 1; l <= a.L; ++l) {
-            if ((a.mono_mask >> l) & 1u) continue;
-            const float *Tl = a.T[l];
-            const uint32_t w = Tl ? a.xw[l] : a.d[l - 1];
-            for (uint32_t c0 = 0; c0 < w; c0 += 64) {
-                const uint32_t col = c0 + (uint32_t)lane;
-                float *xp = a.X[l] + (size_t)v * w + col;
-                float x = (col < w) ? *xp : 0.0f;
-                for (uint32_t j0 = 0; j0 < len; j0 += G) {
-                    float val[G], sg[G];
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const uint32_t e = e0 + min(j0 + (uint32_t)g, len - 1u);
-                        const uint32_t u = (uint32_t)a.sk_out[e];
-                        sg[g] = (j0 + (uint32_t)g < len) ? a.sv_out[e] : 0.0f;
-                        val[g] = 0.0f;
-                        if (col < w && sg[g] != 0.0f)
-                            val[g] = Tl ? Tl[(size_t)u * w + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
-                    }
-#pragma unroll
-                    for (int g = 0; g < G; ++g)
-                        if (sg[g] != 0.0f) x += sg[g] * val[g];
-                }
-                if (col < w) *xp = x;
-            }
-        }
-    }
-}
-
-// operations from pinned host memory
-__device__ __forceinline__ void stage_ops(const ripple_update *src, ripple_update *dst, uint32_t n) {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) dst[i] = src[i];
-}
-
-__global__ void k_batch_reset(DevCtr *ctr, uint32_t *bitmaps, size_t n_bitmap_words, const ripple_update *src,
-                              ripple_update *dst, uint32_t n_ops) {
+__global__ void k_batch_reset(DevCtr *ctr, uint32_t *bitmaps, size_t n_bitmap_words) {
     size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_bitmap_words; i += stride) bitmaps[i] = 0;
     if (blockIdx.x == 0)
         for (uint32_t k = RP_CTR_BATCH + threadIdx.x; k < RP_CTR_WORDS; k += blockDim.x) ((uint32_t *)ctr)[k] = 0;
-    stage_ops(src, dst, n_ops);
 }
 
 // Hands the batch's counters to the host (pinned memory), clears those that a batch starts from zero and then says so: the
@@ -1122,196 +1181,6 @@ void rp_launch_publish(ripple_ctx *c) {
     c->ctr_dirty = false;
 }
 
-// ---------------------------------------------------------------------------------
-// the Apply step of a small piece in three launches
-// ---------------------------------------------------------------------------------
-// A piece of up to SMALL_OPS operations without vertex deletions is paced by launches and chains of dependent reads, not by
-// bytes: its eleven launches (two copies, reset, validate, capacity, edges, structural terms, vertices, rows, adds, degree
-// prefix) are three here. Steps that only a finished predecessor separates are done by the last workgroup to finish
-// (capacity after validation; appends and the degree prefix after the rows are cleaned up), independent ones by different
-// workgroups of one launch (bitmaps cleared beside the validation; structural terms beside the tombstones; feature rows
-// beside the rows' cleanup). The operations are read from pinned host memory by the first kernel, feature rows by the third.
-#define SMALL_OPS 512u
-
-// Where `target` is in the row, searched by wavefronts `part` .. of `parts` that take blocks of 1,024 entries in turn; -1 if this
-// wavefront does not find it. A hub's row of ten thousand entries takes one wavefront ten rounds.
-__device__ __forceinline__ int find_part(const uint32_t *row, uint32_t len, uint32_t target, uint32_t part, uint32_t parts) {
-    for (uint32_t base = part * 1024u; base < len; base += parts * 1024u) {
-        const int p = rp_wave_find_blocks<16>(row, base, len, target);
-        if (p >= 0) return p;
-    }
-    return -1;
-}
-
-// The first nb workgroups validate an operation at a time (its rows searched by four wavefronts); the others clear the bitmaps.
-// The last of the former makes the lists of touched rows and decides. (nb is bounded: every workgroup that arrives there
-// costs about 60 ns, one after the other.)
-#define SMALL_WGS 128u
-__global__ __launch_bounds__(256) void k_small_validate(MutArgs a, const ripple_update *src, ripple_update *dst, uint32_t nb,
-                                                        uint32_t *bitmaps, uint32_t n_bitmap_words) {
-    __shared__ int s_po, s_pi;
-    __shared__ uint32_t s_need[2], s_o[4], s_i[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (blockIdx.x >= nb) {
-        const uint32_t stride = (gridDim.x - nb) * 256u;
-        for (uint32_t k = (blockIdx.x - nb) * 256u + tid; k < n_bitmap_words; k += stride) bitmaps[k] = 0;
-        return;
-    }
-    for (uint32_t i = blockIdx.x; i < a.n_ops; i += nb) {
-    const ripple_update op = src[i];
-    const bool is_add = op.kind == RIPPLE_EDGE_ADD, is_edge = is_add || op.kind == RIPPLE_EDGE_DEL;
-    if (tid == 0) {
-        s_po = s_pi = -1;
-        dst[i] = op;
-    }
-    __syncthreads();
-    uint32_t st = 0;
-    if (op.kind == RIPPLE_FEAT_UPDATE) {
-        st = rp_bit(a.alive, op.u) ? 1u : 0u;
-    } else if (op.kind == RIPPLE_VERTEX_ADD) {
-        st = rp_bit(a.alive, op.u) ? 0u : 1u;
-    } else {
-        bool ok = true;
-        for (int side = 0; side < 2; ++side) {              // alive, or (edges) created by this piece
-            const uint32_t w = side ? op.v : op.u;
-            if (rp_bit(a.alive, w)) continue;
-            bool created = false;
-            if (is_edge)
-                for (uint32_t k = lane; k < a.n_ops; k += 64u) created |= src[k].kind == RIPPLE_VERTEX_ADD && src[k].u == w;
-            ok = ok && __ballot(created) != 0ull;
-        }
-        if (ok) {                                           // the same for all wavefronts
-            const uint2 mo = a.out_meta[op.u], mi = a.in_meta[op.v];
-            const uint32_t *ro = a.out_pool + mo.x, *ri = a.in_pool + mi.x;
-            int po = -1, pi = -1;
-            if (is_add) {                                   // absent from the shorter of the two rows
-                if (mo.y <= mi.y) po = find_part(ro, mo.y, op.v, wave, 4u);
-                else po = find_part(ri, mi.y, op.u, wave, 4u);
-            } else if (!is_edge) {                          // EDGE_REWEIGHT: the edge must exist
-                if (a.in_w) pi = find_part(ri, mi.y, op.u, wave, 4u);
-            } else if (wave < 2) {
-                po = find_part(ro, mo.y, op.v, wave, 2u);
-            } else {
-                pi = find_part(ri, mi.y, op.u, wave - 2, 2u);
-            }
-            if (lane == 0 && po >= 0) s_po = po;            // an entry occurs once: one wavefront finds it
-            if (lane == 0 && pi >= 0) s_pi = pi;
-        }
-        __syncthreads();
-        const int po = s_po, pi = s_pi;
-        if (ok && is_add) st = po < 0 ? 1u : 0u;
-        else if (ok && !is_edge) st = pi >= 0 ? 1u : 0u;
-        else if (ok) {
-            st = (po >= 0 && pi >= 0) ? 1u : 0u;
-            if (tid == 0 && (po >= 0) != (pi >= 0)) a.ctr->error = 3;     // the two adjacencies disagree
-        }
-        if (tid == 0 && !is_edge && st) a.pos_in[i] = (uint32_t)pi;
-    }
-    if (tid == 0) {
-        a.status[i] = st;
-        a.op_touch[i] = (is_edge && st) ? count_edge(a, op, i, s_po, s_pi) : 0u;
-    }
-    __syncthreads();                                        // (s_po and s_pi are set anew)
-    }
-    if (!last_workgroup(a.ctr, nb)) return;
-    if (tid < 2) s_need[tid] = 0;
-    uint32_t no = 0, ni = 0, adds = 0, dels = 0;
-    for (uint32_t start = 0; start < a.n_ops; start += 256u) {
-        const uint32_t j = start + tid;
-        const uint32_t f = j < a.n_ops ? a.op_touch[j] : 0u;
-        const unsigned long long mo = __ballot((f & 4u) != 0), mi = __ballot((f & 8u) != 0), below = (1ull << lane) - 1ull;
-        adds += (uint32_t)__popcll(__ballot((f & 3u) == 3u));
-        dels += (uint32_t)__popcll(__ballot((f & 3u) == 1u));
-        if (lane == 0) {
-            s_o[wave] = (uint32_t)__popcll(mo);
-            s_i[wave] = (uint32_t)__popcll(mi);
-        }
-        __syncthreads();
-        uint32_t po = no, pi = ni;
-        for (int k = 0; k < 4; ++k) {
-            if (k < wave) {
-                po += s_o[k];
-                pi += s_i[k];
-            }
-            no += s_o[k];
-            ni += s_i[k];
-        }
-        if (f & 4u) a.touch_out[po + (uint32_t)__popcll(mo & below)] = dst[j].u;     // at most n_ops entries: the lists have room
-        if (f & 8u) a.touch_in[pi + (uint32_t)__popcll(mi & below)] = dst[j].v;
-        __syncthreads();
-    }
-    if (lane == 0) {
-        s_o[wave] = adds;
-        s_i[wave] = dels;
-    }
-    __syncthreads();
-    for (uint32_t j = tid; j < no + ni; j += 256u) {
-        const uint32_t need = row_need(a, j, no);
-        if (need) atomicAdd(&s_need[j < no ? 0 : 1], need);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        a.ctr->n_touch_out = no;
-        a.ctr->n_touch_in = ni;
-        a.ctr->n_add = s_o[0] + s_o[1] + s_o[2] + s_o[3];
-        a.ctr->n_del = s_i[0] + s_i[1] + s_i[2] + s_i[3];
-        a.ctr->abort_flag = decide(a, s_need[0], s_need[1]);
-    }
-}
-
-// Tombstones and the list of changed edges (the first nb workgroups, a thread per operation) and the structural terms
-// (the others, a wavefront per operation and layer, straight from the operations: unweighted graphs only, where a term's sign
-// is the operation's kind). Nothing the one part reads is written by the other.
-__global__ __launch_bounds__(256) void k_small_edges(MutArgs a, uint32_t nb) {
-    if (blockIdx.x < nb) {
-        apply_edge(a, blockIdx.x * 256u + threadIdx.x);
-        return;
-    }
-    if (a.ctr->abort_flag) return;
-    const uint32_t t = ((blockIdx.x - nb) * 256u + threadIdx.x) >> 6, i = t / a.L, l = t - i * a.L + 1u;
-    if (i >= a.n_ops || ((a.mono_mask >> l) & 1u) || !a.status[i]) return;
-    const ripple_update op = a.ops[i];
-    if (op.kind == RIPPLE_EDGE_ADD) struct_term(a, op.u, op.v, l, 1.0f, rp_lane());
-    else if (op.kind == RIPPLE_EDGE_DEL) struct_term(a, op.u, op.v, l, -1.0f, rp_lane());
-}
-
-// Feature rows and created vertices (the first nb workgroups) and the touched rows (the others); then, in the last one to
-// finish, the appends and the out-degree prefix over A_0.
-__global__ __launch_bounds__(256) void k_small_rows(MutArgs a, uint32_t nb, uint32_t *eoff0) {
-    __shared__ uint32_t s_w[4], s_carry;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (blockIdx.x < nb) apply_vertices(a, blockIdx.x * 4u + wave, nb * 4u);
-    else cleanup_rows(a, (blockIdx.x - nb) * 4u + wave, (gridDim.x - nb) * 4u);
-    if (!last_workgroup(a.ctr, gridDim.x)) return;
-    if (a.ctr->abort_flag) return;                          // (A_0 is empty)
-    if (tid == 0) a.ctr->n_edges += (unsigned long long)a.ctr->n_add - (unsigned long long)a.ctr->n_del;
-    for (uint32_t i = tid; i < a.n_ops; i += 256u) {
-        const ripple_update op = a.ops[i];
-        if (op.kind == RIPPLE_EDGE_ADD && a.status[i]) append_edge(a, op);
-    }
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    __threadfence();                                        // degrees that this workgroup's atomics have just changed
-    const uint32_t count = a.ctr->set[0].a;
-    for (uint32_t base = 0; base < count; base += 256u) {
-        const uint32_t j = base + tid;
-        const uint32_t dg = j < count ? a.out_meta[a.list0[j]].y : 0u;
-        const uint32_t x = rp_wave_scan(dg);
-        if (lane == 63) s_w[wave] = x;
-        __syncthreads();
-        uint32_t off = s_carry;
-        for (int k = 0; k < wave; ++k) off += s_w[k];
-        if (j < count) eoff0[j] = off + x - dg;
-        __syncthreads();
-        if (tid == 255) s_carry = off + x;
-        __syncthreads();
-    }
-    if (tid == 0) {
-        eoff0[count] = s_carry;
-        a.ctr->set[0].m = s_carry;
-    }
-}
-
 static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     MutArgs a;
     a.ops = c->ops_d;
@@ -1320,6 +1189,13 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     a.status = c->op_status;
     a.hole_out = c->hole_out;
     a.hole_in = c->hole_in;
+    a.rank_out = c->op_rank_out;
+    a.rank_in = c->op_rank_in;
+    a.seg_id = c->seg_id;
+    a.seg_x = c->seg_x;
+    a.srt_id = c->srt_id;
+    a.srt_x = c->srt_x;
+    a.eoff0 = c->eoff[0];
     a.op_touch = c->op_touch;
     a.pos_out = c->op_pos_out;
     a.pos_in = c->op_pos_in;
@@ -1340,7 +1216,8 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     a.touch_in = c->touch_in;
     a.touch_cap = c->touch_cap;
     a.exp_kind = c->exp_kind;
-    a.exp_s = c->exp_s;
+    a.exp_pos = c->exp_pos;
+    a.exp_rank = c->exp_rank;
     a.exp_a = c->exp_a;
     a.exp_b = c->exp_b;
     a.exp_cap = c->exp_cap;
@@ -1375,86 +1252,50 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     }
     a.d0_old = rp_layer_mono(c, 1) ? 1 : 0;
     a.det = c->opt_deterministic;
-    a.tail_ids = c->tail_ids;
-    a.tail_q = c->tail_q;
-    a.tail_w = c->tail_w;
-    a.tail_cap = c->ops_cap;
-    a.sk_in = c->sk_in;
-    a.sk_out = c->sk_out;
-    a.sv_in = c->sv_in;
-    a.sv_out = c->sv_out;
-    a.n_sort = 0;
     return a;
 }
 
-// counters and bitmaps cleared; n_ops operations from pinned host memory into ops_d
-void rp_launch_batch_reset(ripple_ctx *c, const ripple_update *src, uint32_t n_ops) {
+// counters and bitmaps cleared
+void rp_launch_batch_reset(ripple_ctx *c) {
     // the per-layer bitmaps, S and V_added are one allocation starting at bm[0]
-    size_t words = (size_t)c->n_words * (c->L + 3);
-    uint32_t gb = std::min<uint32_t>(rp_div_up(std::max<size_t>(words, n_ops), 256), c->n_cu * 4);
-    hipLaunchKernelGGL(k_batch_reset, dim3(gb), dim3(256), 0, c->stream, c->ctr, c->bm[0], words, src, c->ops_d, n_ops);
+    const size_t words = (size_t)c->n_words * (c->L + 3);
+    const uint32_t gb = std::min<uint32_t>(rp_div_up(words, 256), c->n_cu * 4);
+    hipLaunchKernelGGL(k_batch_reset, dim3(gb), dim3(256), 0, c->stream, c->ctr, c->bm[0], words);
     c->ctr_dirty = false;
 }
 
-// The Apply step in three launches where the piece is small enough (see k_small_validate); the bitmaps are cleared and A_0's
-// prefix is made as well. false: nothing was enqueued.
-bool rp_launch_mutate_small(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, bool has_vertex_del, bool has_vertex_or_feat) {
-    if (n_ops == 0 || n_ops > SMALL_OPS || has_vertex_del || c->opt_deterministic || c->ctr_dirty) return false;
-    hipStream_t s = c->stream;
-    MutArgs a = make_args(c, n_ops);
-    const uint32_t words = c->n_words * (c->L + 3), nb = std::min(n_ops, SMALL_WGS);
-    hipLaunchKernelGGL(k_small_validate, dim3(nb + std::min<uint32_t>(rp_div_up(words, 1024), c->n_cu * 2)), dim3(256), 0, s, a, src,
-                       c->ops_d, nb, c->bm[0], words);
-    const uint32_t tb = rp_div_up(n_ops, 256);
-    if (c->in_w) {
-        hipLaunchKernelGGL(k_apply_edges, dim3(tb), dim3(256), 0, s, a);
-        hipLaunchKernelGGL(k_struct_scatter, dim3(rp_div_up(n_ops * c->L, 4)), dim3(256), 0, s, a);
-    } else {
-        const bool terms = (a.mono_mask >> 1) != (1u << c->L) - 1u;        // some layer has structural terms
-        hipLaunchKernelGGL(k_small_edges, dim3(tb + (terms ? rp_div_up(n_ops * c->L, 4) : 0u)), dim3(256), 0, s, a, tb);
-    }
-    const uint32_t vb = has_vertex_or_feat ? std::min(rp_div_up(n_ops, 4), SMALL_WGS / 2) : 0u;
-    hipLaunchKernelGGL(k_small_rows, dim3(vb + std::min(rp_div_up(2 * n_ops, 4), SMALL_WGS)), dim3(256), 0, s, a, vb, c->eoff[0]);
-    return true;
-}
-
-// Enqueue the whole Apply step for the n_ops operations staged in ops_d / payload_d.
-void rp_launch_mutate(ripple_ctx *c, uint32_t n_ops, bool has_vertex_add, bool has_vertex_del, bool has_vertex_or_feat) {
+// Enqueues the whole Apply step for the n_ops operations at src (pinned host memory): bitmaps cleared, A_0 listed with its prefix.
+void rp_launch_mutate(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, bool has_vertex_del, bool has_vertex_or_feat) {
+    if (c->ctr_dirty || n_ops == 0) rp_launch_batch_reset(c);
     if (n_ops == 0) return;
     hipStream_t s = c->stream;
     MutArgs a = make_args(c, n_ops);
-    uint32_t tb = rp_div_up(n_ops, 256);                              // thread per op
-    uint32_t wb = std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu * 8);  // wavefront per op
-    uint32_t big = c->n_cu * 8;
-    if (has_vertex_add || has_vertex_del) hipLaunchKernelGGL(k_vertex_validate, dim3(tb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_edge_validate, dim3(wb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_touch_lists, dim3(1), dim3(1024), 0, s, a);
-    uint32_t touch_threads = 2 * n_ops;                               // validation touches <= n_ops rows per side
-    hipLaunchKernelGGL(k_capacity, dim3(rp_div_up(touch_threads, 256)), dim3(256), 0, s, a);
-    if (has_vertex_del) {
-        hipLaunchKernelGGL(k_expand_vdel, dim3(wb), dim3(256), 0, s, a);
-        hipLaunchKernelGGL(k_expand_apply, dim3(big), dim3(256), 0, s, a);
-    }
-    hipLaunchKernelGGL(k_apply_edges, dim3(tb), dim3(256), 0, s, a);
-    int t = rp_timer_begin(c);
-    if (c->opt_deterministic) {
-        // without vertex deletions a piece changes at most one edge per operation; with them, any number up to the lists' size
-        a.n_sort = has_vertex_del ? c->struct_cap : std::min<uint32_t>(n_ops, c->struct_cap);
-        hipLaunchKernelGGL(k_struct_keys, dim3(rp_div_up(a.n_sort, 256)), dim3(256), 0, s, a);
-        rp_sort_pairs_u64(c, c->sk_in, c->sk_out, c->sv_in, c->sv_out, a.n_sort, c->sort_tmp, c->sort_tmp_bytes);
-        hipLaunchKernelGGL(k_struct_ordered, dim3(std::min<uint32_t>(big, rp_div_up(a.n_sort, 4))), dim3(256), 0, s, a);
+    const uint32_t words = c->n_words * (c->L + 3), big = c->n_cu * 8, tb = rp_div_up(n_ops, 256);
+    const bool small = n_ops <= SMALL_OPS && !has_vertex_del;
+    if (small) {
+        const bool wide = n_ops <= SMALL_WGS;
+        const uint32_t nb = wide ? n_ops : rp_div_up(n_ops, 4);
+        const dim3 grid(nb + std::min<uint32_t>(rp_div_up(words, 1024), c->n_cu * 2));
+        if (wide) hipLaunchKernelGGL(k_small_validate<4>, grid, dim3(256), 0, s, a, src, c->ops_d, nb, c->bm[0], words);
+        else hipLaunchKernelGGL(k_small_validate<1>, grid, dim3(256), 0, s, a, src, c->ops_d, nb, c->bm[0], words);
     } else {
-        hipLaunchKernelGGL(k_struct_scatter, dim3(has_vertex_del ? big : std::min<uint32_t>(big, rp_div_up((uint64_t)n_ops * c->L, 4))),
-                           dim3(256), 0, s, a);
+        const bool wide = n_ops <= WORKGROUP_OPS;
+        const uint32_t nb = wide ? n_ops : std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu * 32), nd = has_vertex_del ? std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu) : 0u;
+        hipLaunchKernelGGL(k_stage, dim3(std::min<uint32_t>(rp_div_up(std::max(words, n_ops), 256), c->n_cu * 4)), dim3(256), 0, s, a, src,
+                           c->ops_d, c->bm[0], words);
+        if (wide) hipLaunchKernelGGL(k_validate<4>, dim3(nb + nd), dim3(256), 0, s, a, nb);
+        else hipLaunchKernelGGL(k_validate<1>, dim3(nb + nd), dim3(256), 0, s, a, nb);
+        if (has_vertex_del) hipLaunchKernelGGL(k_find_expanded, dim3(big), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_measure, dim3(has_vertex_del ? SMALL_WGS : std::min<uint32_t>(tb, SMALL_WGS)), dim3(256), 0, s, a);
     }
-    rp_timer_end(c, t, RIPPLE_PH_STRUCT, 0);
-    if (has_vertex_or_feat) hipLaunchKernelGGL(k_apply_vertices, dim3(wb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_cleanup_rows, dim3(has_vertex_del ? big : std::min<uint32_t>(big, rp_div_up(2 * (uint64_t)n_ops, 4))),
-                       dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_apply_adds, dim3(tb), dim3(256), 0, s, a);
-    if (c->opt_deterministic) {
-        hipLaunchKernelGGL(k_sort_tails, dim3(has_vertex_del ? big : std::min<uint32_t>(big, rp_div_up((uint64_t)n_ops, 4))),
-                           dim3(256), 0, s, a);
-        hipLaunchKernelGGL(k_sort_long_tails, dim3(c->n_cu), dim3(1024), 0, s, a);
+    const bool terms = !a.det && (a.mono_mask >> 1) != (1u << c->L) - 1u;      // some layer has terms to be added here
+    const uint32_t sb = (terms || c->in_w) ? std::min<uint32_t>(rp_div_up((uint64_t)n_ops * (c->in_w ? 1u : c->L), 4), big) : 0u;
+    hipLaunchKernelGGL(k_edges, dim3(tb + sb + (has_vertex_del ? big : 0u)), dim3(256), 0, s, a, tb, sb);
+    if (a.det) {
+        int t = rp_timer_begin(c);
+        hipLaunchKernelGGL(k_det_terms, dim3(has_vertex_del ? big : std::min<uint32_t>(n_ops, big)), dim3(256), 0, s, a);
+        rp_timer_end(c, t, RIPPLE_PH_STRUCT, 0);
     }
+    const uint32_t vb = has_vertex_or_feat ? std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu * 2) : 0u;
+    hipLaunchKernelGGL(k_rows, dim3(vb + (has_vertex_del ? big : std::min<uint32_t>(rp_div_up(2 * (uint64_t)n_ops, 4), big))), dim3(256), 0, s, a, vb);
 }

@@ -113,3 +113,31 @@ def test_hops_cut_over_edges(kind, widths, store):
         pair.check_embeddings()
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("deterministic,weighted", [(False, False), (True, False), (False, True)])
+@pytest.mark.parametrize("dels,adds", [(1, 0), (2, 1), (64, 0), (65, 64), (511, 2), (700, 324), (600, 425), (1500, 1300), (2999, 1990), (3000, 1500)])
+def test_many_changes_of_one_row(deterministic, weighted, dels, adds):
+    """Deletions and additions that all meet in vertex 0's in-row and vertex 1's out-row (3,000 entries each): few ones, a
+    wavefront's worth and one more, what is put in order in LDS and one more, all entries."""
+    print("case one row", deterministic, weighted, dels, adds, flush=True)
+    n, k = 6000, 3000
+    rng = np.random.default_rng(dels * 7 + adds)
+    ids = np.arange(2, 2 + k, dtype=np.uint32)
+    chain = np.arange(3999, 5999, dtype=np.uint32)         # (so that the new neighbours have something to send at every layer)
+    src, dst = np.concatenate([ids, np.full(k, 1, np.uint32), chain]), np.concatenate([np.zeros(k, np.uint32), ids, chain + 1])
+    weights = ri.edge_weights(len(src), 5) if weighted else None
+    model = ri.make_model("gcn_wsum" if weighted else "sage_mean", (5, 9, 70, 4), 3)
+    pair = Pair(n, n + 5, src, dst, ri.features(n, 5, 1), model, weights=weights, deterministic=deterministic, edge_capacity=20000)
+    try:
+        gone, new = rng.permutation(ids)[:dels], np.arange(4000, 4000 + adds, dtype=np.uint32)
+        bits = (np.full(adds, 0.75, np.float32) if weighted else np.zeros(adds, np.float32)).view(np.uint32)
+        for flip in (False, True):                         # in-row of 0, then out-row of 1
+            a = [(ri.OP_EDGE_DEL, 1, x, 0) if flip else (ri.OP_EDGE_DEL, x, 0, 0) for x in gone]
+            b = [(ri.OP_EDGE_ADD, 1, x, w) if flip else (ri.OP_EDGE_ADD, x, 0, w) for x, w in zip(new, bits)]
+            ops = np.array(a + b, dtype=np.uint32)
+            pair.step(ops[rng.permutation(len(ops))], None)
+        pair.check_graph()
+        pair.check_aggregates()
+    finally:
+        pair.close()
