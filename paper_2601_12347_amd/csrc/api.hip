@@ -803,8 +803,8 @@ extern "C" ripple_status ripple_plan_batch(const ripple_update *ops, uint32_t n_
 static ripple_status ensure_batch_buffers(ripple_ctx *c, uint32_t n_ops, uint32_t n_feat, uint32_t want_exp) {
     if (n_ops > c->ops_cap || want_exp > c->exp_cap) {
         RP_HIP(c, hipStreamSynchronize(c->stream));
-        uint32_t cap = std::max<uint32_t>(std::max<uint32_t>(n_ops, c->ops_cap), 4096);
-        cap = rp_round_up(cap + cap / 2, 1024);
+        uint32_t cap = c->ops_cap;
+        if (n_ops > cap) cap = rp_round_up(std::max<uint32_t>(n_ops, 4096) / 2 * 3, 1024);
         uint32_t exp = std::max<uint32_t>(std::max<uint32_t>(want_exp, c->exp_cap), 1u << 20);
         void *old[] = {c->ops_d, c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_pos,
                        c->exp_rank, c->exp_a, c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->op_rank_out, c->op_rank_in, c->seg_id,
@@ -1092,7 +1092,7 @@ static ripple_status run_piece(ripple_ctx *c, const SubBatch &sb, bool multi, ui
         if (attempt >= 2) return fail(c, RIPPLE_ECAPACITY, "adjacency pool exhausted even after compaction");
         if (h.abort_flag & 4u) {
             uint32_t want = h.need_exp + h.need_exp / 2 + 1024;
-            RP_TRY(ensure_batch_buffers(c, c->ops_cap, 0, want));
+            RP_TRY(ensure_batch_buffers(c, 0, 0, want));  // (the operations in ops_pin are read again by the retry: they stay where they are)
         }
         if (h.abort_flag & 1u) {
             ++*compactions;

@@ -8,7 +8,7 @@ import pytest
 import oracle
 import paper_2601_12347_amd as rp
 import ripple_inputs as ri
-from harness import make_pair, make_stream, config_pair
+from harness import Pair, make_pair, make_stream, config_pair
 
 pytestmark = pytest.mark.gpu
 
@@ -381,6 +381,35 @@ def test_pool_growth_relocation_and_compaction():
         assert ei.value.status == rp.binding.RIPPLE_ECAPACITY
         pair.check_graph()
         pair.check_embeddings()
+    finally:
+        pair.close()
+
+
+def test_deletions_that_outgrow_the_scratch_twice():
+    """The scratch for the edges of deleted vertices grows in the middle of a batch and the piece is tried again with the operations
+    that are already staged. Two batches of one context outgrow it: first 2^20 edges, then what the first growth made of it."""
+    print("case scratch growth", flush=True)
+    n, e, rng = 3000, 2_500_000, np.random.default_rng(77)
+    keys = rng.choice(n * n, e + 2 * n, replace=False)
+    keys = keys[keys // n != keys % n][:e]
+    src, dst = (keys // n).astype(np.uint32), (keys % n).astype(np.uint32)
+    pair = Pair(n, n + 4, src, dst, ri.features(n, 4, 1), ri.make_model("gcn_sum", (4, 3), 2), edge_capacity=e + 1000)
+    try:
+        deg = np.bincount(src, minlength=n) + np.bincount(dst, minlength=n)
+        first, second = np.arange(700), np.arange(700, 2300)
+        assert deg[first].sum() > 1 << 20                    # outgrows the scratch a context starts with ...
+        left = (src >= 700) & (dst >= 700)
+        more = np.bincount(src[left], minlength=n) + np.bincount(dst[left], minlength=n)
+        assert more[second].sum() > deg[first].sum() // 2 * 3 + 1024   # ... and what that growth made of it
+        for who in (first, second):
+            print(" deleting", len(who), flush=True)
+            ops = np.array([(ri.OP_VERTEX_DEL, int(w), 0, 0) for w in who] + [(ri.OP_FEAT_UPDATE, 2900 + i, 0, i) for i in range(8)], dtype=np.uint32)
+            rows = rng.standard_normal((8, 4)).astype(np.float32)
+            rec = pair.ora.apply_batch(ops, rows)
+            res = rp.ripple_apply_updates(pair.ctx, ops, rows)
+            assert rec.accepted.all() and res.n_applied == len(ops) and res.n_edges == pair.ora.n_edges()
+            pair.check_embeddings()
+        pair.check_graph()
     finally:
         pair.close()
 
