@@ -585,8 +585,10 @@ ripple_status rp_launch_affected_static(ripple_ctx *c, uint32_t *bitmap, uint32_
     a.list = ids_out;
     a.list_cap = cap;
     a.count_out = n_out;
-    bitmap_ids(c, a, true);
-    return rp_wait_flag(c);
+    bitmap_ids(c, a, false);
+    RP_HIP(c, hipGetLastError());
+    RP_HIP(c, hipStreamSynchronize(c->stream));            // (the call's contract; a word in pinned memory would be there about 10 us earlier)
+    return RIPPLE_OK;
 }
 
 SparseArgs rp_sparse_args(ripple_ctx *c, uint32_t l, uint32_t *list, uint32_t *count, bool self_term) {

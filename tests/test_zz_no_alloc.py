@@ -68,3 +68,24 @@ def test_no_allocation_entry_point_matches_get_affected():
     finally:
         big.close()
         small.close()
+
+
+def test_the_stream_is_idle_when_the_static_call_returns():
+    """The call's contract: it returns after the context's stream has been synchronised."""
+    torch = pytest.importorskip("torch")
+    print("case static call, stream idle", flush=True)
+    stream = torch.cuda.Stream()
+    src, dst, _, _ = ri.chung_lu_graph(2000, 9000, 2.1, 0.03, 5)
+    ctx = rp.ripple_init_graph(2000, 2010, src, dst, ri.features(2000, 8, 1), hip_stream=stream.cuda_stream)
+    try:
+        rp.ripple_load_model(ctx, ri.make_model("sage_mean", (8, 16, 6), 2))
+        rp.ripple_full_infer(ctx)
+        ids_t, n_t = torch.zeros(2010, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        for b in range(40):
+            rows = np.full((1, 8), float(b), np.float32)
+            rp.ripple_apply_updates(ctx, np.array([(ri.OP_FEAT_UPDATE, b, 0, 0)], np.uint32), rows)
+            rp.ripple_get_affected_static(ctx, 2, ids_t.data_ptr(), 2010, n_t.data_ptr())
+            assert stream.query(), f"batch {b}: the stream still has work"
+    finally:
+        rp.ripple_destroy(ctx)
