@@ -138,15 +138,19 @@ __global__ __launch_bounds__(256) void k_export_rows(const uint2 *meta, const ui
 // ---------------------------------------------------------------------------------
 // helpers
 // ---------------------------------------------------------------------------------
-static bool is_device_ptr(const void *p) {
+// where a caller's memory is; a kernel of this context writes to FAR_GPU memory only with peer access
+enum Place { ON_HOST, OWN_GPU, FAR_GPU };
+static Place place_of(const ripple_ctx *c, const void *p) {
     hipPointerAttribute_t at;
     hipError_t e = hipPointerGetAttributes(&at, p);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return ON_HOST;
     }
-    return at.type == hipMemoryTypeDevice || at.type == hipMemoryTypeManaged;
+    if (at.type == hipMemoryTypeManaged) return OWN_GPU;
+    return at.type != hipMemoryTypeDevice ? ON_HOST : (at.device == c->device ? OWN_GPU : FAR_GPU);
 }
+static bool is_device_ptr(const ripple_ctx *c, const void *p) { return place_of(c, p) != ON_HOST; }
 
 // every array has 16 bytes behind its end: the row transforms read rows in groups of four numbers
 #define ARRAY_PAD 16
@@ -1113,10 +1117,10 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     hipStream_t s = c->stream;
     int t_total = rp_timer_begin(c);
 
-    RP_TRY(ensure_batch_buffers(c, n_ops, (n_feat_rows && !is_device_ptr(feat_payload)) ? n_feat_rows : 0u, 0));
+    RP_TRY(ensure_batch_buffers(c, n_ops, (n_feat_rows && !is_device_ptr(c, feat_payload)) ? n_feat_rows : 0u, 0));
     // operations are needed on the host (validation, conflict analysis)
     const ripple_update *hops = ops;
-    if (n_ops && is_device_ptr(ops)) {
+    if (n_ops && is_device_ptr(c, ops)) {
         RP_HIP(c, hipMemcpyAsync(c->ops_pin, ops, (size_t)n_ops * sizeof(ripple_update), hipMemcpyDeviceToHost, s));
         RP_HIP(c, hipStreamSynchronize(s));
         hops = c->ops_pin;
@@ -1143,7 +1147,7 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
         RP_HIP(c, hipMemsetAsync(c->rep[0], 0, (size_t)c->n_words * (c->L + 1) * 4, s));
     // feature rows: used in place when they already live on the device
     c->payload = feat_payload;
-    if (n_feat_rows && !is_device_ptr(feat_payload)) {          // the kernel that applies them reads each row once, over the bus
+    if (n_feat_rows && !is_device_ptr(c, feat_payload)) {          // the kernel that applies them reads each row once, over the bus
         memcpy(c->payload_pin, feat_payload, (size_t)n_feat_rows * c->d[0] * 4);
         c->payload = c->payload_pin;
     }
@@ -1271,7 +1275,7 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
     if (!ids && n_ids > c->n_cap) return fail(c, RIPPLE_EINVAL, "more rows requested than vertex_capacity");
     const uint32_t *ids_d = nullptr;
     if (ids) {
-        if (is_device_ptr(ids)) {
+        if (is_device_ptr(c, ids)) {
             ids_d = ids;
         } else {
             for (uint32_t i = 0; i < n_ids; ++i)
@@ -1292,9 +1296,9 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
             }
         }
     }
-    const bool to_device = is_device_ptr(out);
+    const Place place = place_of(c, out);
     const size_t total = (size_t)n_ids * d;
-    if (!ids && !store && (to_device || total > IO_PIN_FLOATS)) {   // contiguous float32 rows: plain copy
+    if (!ids && !store && (place != ON_HOST || total > IO_PIN_FLOATS)) {   // contiguous float32 rows: plain copy
         RP_HIP(c, hipMemcpyAsync(out, M, total * 4, hipMemcpyDefault, s));
         RP_HIP(c, hipStreamSynchronize(s));
         return RIPPLE_OK;
@@ -1307,11 +1311,11 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
         else hipLaunchKernelGGL(k_gather_rows<0>, dim3(gb), dim3(256), 0, s, M, d, from, (uint32_t)r0, rows, c->n_cap, to, done);
         if (report && !done.flag) rp_launch_report(c);
     };
-    if (to_device) {
+    if (place == OWN_GPU) {
         launch(0, n_ids, out, true);
         return rp_wait_flag(c);
     }
-    if (total <= IO_PIN_FLOATS) {
+    if (place == ON_HOST && total <= IO_PIN_FLOATS) {
         float *rows = (float *)(c->io_pin + 16 + IO_PIN_IDS);
         launch(0, n_ids, rows, true);
         RP_TRY(rp_wait_flag(c));
@@ -1330,7 +1334,7 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
     for (size_t r0 = 0; r0 < n_ids; r0 += chunk_rows) {
         size_t rows = std::min<size_t>(chunk_rows, n_ids - r0);
         launch(r0, rows, c->gather_d, false);
-        RP_HIP(c, hipMemcpyAsync(out + r0 * d, c->gather_d, rows * d * 4, hipMemcpyDeviceToHost, s));
+        RP_HIP(c, hipMemcpyAsync(out + r0 * d, c->gather_d, rows * d * 4, hipMemcpyDefault, s));   // the host's or another GPU's
         RP_HIP(c, hipStreamSynchronize(s));
     }
     return RIPPLE_OK;
@@ -1386,7 +1390,7 @@ extern "C" ripple_status ripple_get_affected_static(ripple_ctx *c, uint32_t laye
     if (!c) return RIPPLE_EINVAL;
     if (c->state != 3) return fail(c, RIPPLE_ESTATE, "no batch has been applied");
     if (layer > c->L || !n_out || (cap && !ids_out)) return fail(c, RIPPLE_EINVAL, "bad argument");
-    if (!is_device_ptr(n_out) || (cap && !is_device_ptr(ids_out)))
+    if (!is_device_ptr(c, n_out) || (cap && !is_device_ptr(c, ids_out)))
         return fail(c, RIPPLE_EINVAL, "ids_out and n_out must be device memory");
     return rp_launch_affected_static(c, c->last_from_rep ? c->rep[layer] : c->bm[layer], ids_out, cap, n_out);
 }
