@@ -258,7 +258,10 @@ ripple_status ripple_apply_updates(ripple_ctx *ctx, const ripple_update *ops, ui
  * [n_ids x d_layer] (host or device). ids: host or device, or NULL for rows
  * 0..n_ids-1. Rows of dead vertices are zero. This is the read side of trigger-based
  * inference (Sec. 2.2): every embedding is kept current by ripple_apply_updates, so a
- * query is a row copy, with no computation at request time; layer L holds the predictions. */
+ * query is a row copy, with no computation at request time; layer L holds the predictions.
+ * This call, ripple_get_aggregates, ripple_get_affected and ripple_apply_updates return when their results are in place, visible
+ * to the host and to whatever is enqueued on any stream afterwards. They do not always wait for the stream itself:
+ * hipStreamQuery may say for a few microseconds more that its last kernel is being retired. */
 ripple_status ripple_get_embeddings(ripple_ctx *ctx, uint32_t layer, const uint32_t *ids,
                                     uint32_t n_ids, float *out);
 
