@@ -152,6 +152,12 @@ static Place place_of(const ripple_ctx *c, const void *p) {
 }
 static bool is_device_ptr(const ripple_ctx *c, const void *p) { return place_of(c, p) != ON_HOST; }
 
+#define RP_TRY(expr)                         \
+    do {                                     \
+        ripple_status rc__ = (expr);         \
+        if (rc__ != RIPPLE_OK) return rc__;  \
+    } while (0)
+
 // every array has 16 bytes behind its end: the row transforms read rows in groups of four numbers
 #define ARRAY_PAD 16
 template <typename T>
@@ -168,17 +174,35 @@ static ripple_status dev_alloc(ripple_ctx *c, T **p, size_t count, bool zero) {
     return RIPPLE_OK;
 }
 
+// Arrays that live and die together, in one allocation: hipMalloc of a few megabytes takes 50 to 300 us and every clearing memset
+// is a launch, so a context of a small graph spent most of its preparation and half of its first batch on them.
+struct Block {
+    struct Part {
+        void **p;
+        size_t at;
+    } part[32];
+    uint32_t n = 0;
+    size_t bytes = 0;
+    template <typename T>
+    void add(T **p, size_t count) {
+        part[n++] = {(void **)p, bytes};
+        bytes += (std::max<size_t>(count, 1) * sizeof(T) + ARRAY_PAD + 255) & ~(size_t)255;
+    }
+};
+static ripple_status block_alloc(ripple_ctx *c, const Block &b, uint8_t **base, bool zero) {
+    RP_TRY(dev_alloc(c, base, b.bytes, zero));
+    for (uint32_t i = 0; i < b.n; ++i) *b.part[i].p = *base + b.part[i].at;
+    return RIPPLE_OK;
+}
+
 // Small transfers to the host go through pinned memory that the kernel itself writes (and reads ids from): a kernel and one
 // wait, where a copy to pageable memory costs a second launch and a second wait. Larger ones are left to the copy
 // engine, which is faster once the transfer itself counts (0.13 against 0.03 ms at half a megabyte).
 #define IO_PIN_IDS 32768u
 #define IO_PIN_FLOATS 65536u
-
-#define RP_TRY(expr)                         \
-    do {                                     \
-        ripple_status rc__ = (expr);         \
-        if (rc__ != RIPPLE_OK) return rc__;  \
-    } while (0)
+// operations and feature rows of a batch that the pinned block has room for; larger batches get staging of their own
+#define PIN_OPS 6144u
+#define PIN_ROWS 1024u
 
 static ripple_status fail(ripple_ctx *c, ripple_status rc, const char *msg);
 
@@ -242,31 +266,44 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     c->store = store;
     c->d[0] = d0;
     const size_t n = c->n_cap;
-    RP_TRY(dev_alloc(c, &c->out_meta, n, true));
-    RP_TRY(dev_alloc(c, &c->in_meta, n, true));
-    RP_TRY(dev_alloc(c, &c->out_capv, n, true));
-    RP_TRY(dev_alloc(c, &c->in_capv, n, true));
-    RP_TRY(dev_alloc(c, &c->vstate, n, true));
-    RP_TRY(dev_alloc(c, &c->pend_out, n, true));
-    RP_TRY(dev_alloc(c, &c->pend_in, n, true));
-    RP_TRY(dev_alloc(c, &c->dead_out, n, true));
-    RP_TRY(dev_alloc(c, &c->dead_in, n, true));
-    RP_TRY(dev_alloc(c, &c->hole_out, n, true));
-    RP_TRY(dev_alloc(c, &c->hole_in, n, true));
+    Block g;
+    g.add(&c->out_meta, n);
+    g.add(&c->in_meta, n);
+    g.add(&c->out_capv, n);
+    g.add(&c->in_capv, n);
+    g.add(&c->vstate, n);
+    g.add(&c->pend_out, n);
+    g.add(&c->pend_in, n);
+    g.add(&c->dead_out, n);
+    g.add(&c->dead_in, n);
+    g.add(&c->hole_out, n);
+    g.add(&c->hole_in, n);
+    g.add(&c->alive, (size_t)c->n_words);
+    c->n_part = std::max(rp_div_up(n, 1024), rp_div_up(c->n_words, 256)) + 1;
+    g.add(&c->part_cnt, (size_t)c->n_part);
+    g.add(&c->part_deg, (size_t)c->n_part);
+    g.add(&c->part_ideg, (size_t)c->n_part);
+    g.add(&c->ctr, 1);
+    RP_TRY(block_alloc(c, g, &c->graph_block, true));
     RP_TRY(dev_alloc(c, &c->out_pool, (size_t)pool_cap, false));
     RP_TRY(dev_alloc(c, &c->in_pool, (size_t)pool_cap, false));
     if (weights) RP_TRY(dev_alloc(c, &c->in_w, (size_t)pool_cap, false));
-    RP_TRY(dev_alloc(c, &c->alive, (size_t)c->n_words, true));
-    c->n_part = std::max(rp_div_up(n, 1024), rp_div_up(c->n_words, 256)) + 1;
-    RP_TRY(dev_alloc(c, &c->part_cnt, (size_t)c->n_part, true));
-    RP_TRY(dev_alloc(c, &c->part_deg, (size_t)c->n_part, true));
-    RP_TRY(dev_alloc(c, &c->part_ideg, (size_t)c->n_part, true));
-    RP_TRY(dev_alloc(c, &c->ctr, 1, true));
-    RP_HIP(c, hipHostMalloc((void **)&c->ctr_host, sizeof(DevCtr), hipHostMallocDefault));
-    memset(c->ctr_host, 0, sizeof(DevCtr));
-    RP_HIP(c, hipHostMalloc((void **)&c->pub_flag, 64, hipHostMallocDefault));
-    *c->pub_flag = 0;
-    RP_HIP(c, hipHostMalloc((void **)&c->io_pin, (16 + IO_PIN_IDS + IO_PIN_FLOATS) * 4, hipHostMallocDefault));
+    {   // pinned memory, in one allocation (200 to 300 us each, whatever the size): counters, the flag, read-back, and the staging of
+        // ordinary batches
+        const size_t ctr_at = 0, flag_at = (sizeof(DevCtr) + 63) & ~(size_t)63, io_at = flag_at + 64;
+        const size_t ops_at = io_at + (16 + IO_PIN_IDS + IO_PIN_FLOATS) * 4, rows_at = ops_at + PIN_OPS * sizeof(ripple_update);
+        c->pin_bytes = rows_at + (size_t)PIN_ROWS * d0 * 4;
+        RP_HIP(c, hipHostMalloc((void **)&c->pin_block, c->pin_bytes, hipHostMallocDefault));
+        c->ctr_host = (DevCtr *)(c->pin_block + ctr_at);
+        c->pub_flag = (uint32_t *)(c->pin_block + flag_at);
+        c->io_pin = (uint32_t *)(c->pin_block + io_at);
+        c->ops_pin = (ripple_update *)(c->pin_block + ops_at);
+        c->payload_pin = (float *)(c->pin_block + rows_at);
+        c->pin_ops_cap = PIN_OPS;
+        c->feat_cap = PIN_ROWS;
+        memset(c->ctr_host, 0, sizeof(DevCtr));
+        *c->pub_flag = 0;
+    }
     {   // features
         void *h0 = nullptr;
         size_t bytes = n * d0 * elem_size(c);
@@ -316,14 +353,17 @@ extern "C" ripple_status ripple_init_graph_weighted(ripple_ctx **out, uint32_t n
                       store, hip_stream);
 }
 
+// staging that has not been replaced by a larger one of its own
+static bool in_pin_block(const ripple_ctx *c, const void *p) {
+    const uint8_t *q = (const uint8_t *)p, *end = c->pin_block + c->pin_bytes;
+    return c->pin_block && q >= c->pin_block && q < end;
+}
+
 extern "C" void ripple_destroy(ripple_ctx *c) {
     if (!c) return;
     hipStreamSynchronize(c->stream);
-    void *ptrs[] = {c->out_meta, c->in_meta, c->out_capv, c->in_capv, c->vstate, c->pend_out, c->pend_in, c->dead_out,
-                    c->dead_in, c->hole_out, c->hole_in, c->out_pool, c->in_pool, c->in_w, c->alive, c->part_cnt, c->part_deg, c->part_ideg, c->ioff[0], c->ctr, c->D[0], c->D[1],
-                    c->tmp, c->PD, c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->gat_mag, c->gat_rec, c->seg_v, c->seg_done, c->seg_base, c->seg_r, c->seg_part, c->bm[0], c->rep[0], c->list[0], c->eoff[0], c->all_list, c->ioff_all, c->mk, c->ops_d,
-                    c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_pos, c->exp_rank, c->exp_a,
-                    c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->op_rank_out, c->op_rank_in, c->seg_id, c->seg_x, c->srt_id, c->srt_x, c->gather_d, c->gather_ids, c->pk_a, c->pk_b, c->pv_a, c->pv_b, c->pair_tmp};
+    void *ptrs[] = {c->graph_block, c->list_block, c->batch_block, c->pair_block, c->out_pool, c->in_pool, c->in_w, c->D[0], c->D[1], c->tmp, c->PD,
+                    c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->gat_mag, c->gat_rec, c->seg_block, c->gather_d, c->gather_ids};
     for (void *p : ptrs)
         if (p) hipFree(p);
     for (uint32_t l = 0; l <= RIPPLE_MAX_LAYERS; ++l) {
@@ -338,11 +378,9 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
         for (void *p : w)
             if (p) hipFree(p);
     }
-    if (c->ctr_host) hipHostFree(c->ctr_host);
-    if (c->ops_pin) hipHostFree(c->ops_pin);
-    if (c->payload_pin) hipHostFree(c->payload_pin);
-    if (c->io_pin) hipHostFree(c->io_pin);
-    if (c->pub_flag) hipHostFree(c->pub_flag);
+    if (c->ops_pin && !in_pin_block(c, c->ops_pin)) hipHostFree(c->ops_pin);
+    if (c->payload_pin && !in_pin_block(c, c->payload_pin)) hipHostFree(c->payload_pin);
+    if (c->pin_block) hipHostFree(c->pin_block);
     if (c->timer) {
         for (hipEvent_t e : c->timer->ev) hipEventDestroy(e);
         delete c->timer;
@@ -357,13 +395,18 @@ extern "C" const char *ripple_last_error(const ripple_ctx *c) { return c ? c->er
 // ---------------------------------------------------------------------------------
 static uint32_t pad_n(uint32_t n) { return n <= 64 ? 64u : (n <= 128 ? 128u : rp_round_up(n, 256)); }
 
-// the padded matrix with k by fours (wave_gemm reads four consecutive k of a column at once)
-static ripple_status upload_quads(ripple_ctx *c, const float *w, uint32_t Kpad, uint32_t Npad, float **out) {
-    std::vector<float> q((size_t)Kpad * Npad);
-    for (uint32_t k = 0; k < Kpad; ++k)
-        for (uint32_t j = 0; j < Npad; ++j) q[((size_t)(k / 4) * Npad + j) * 4 + k % 4] = w[(size_t)k * Npad + j];
-    RP_TRY(dev_alloc(c, out, q.size(), false));
-    RP_HIP(c, hipMemcpy(*out, q.data(), q.size() * 4, hipMemcpyHostToDevice));
+// The padded matrix [Kpad x Npad] with k by fours (wave_gemm reads four consecutive k of a column at once), made on the device from
+// the one that was uploaded: rearranged and copied by the host, the second layout took a quarter of ripple_load_model.
+__global__ void k_quads(const float *w, float *q, uint32_t n, uint32_t Npad) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t t = i & 3u, j = (i >> 2) % Npad, k4 = (i >> 2) / Npad;
+    q[i] = w[(size_t)(4u * k4 + t) * Npad + j];
+}
+static ripple_status make_quads(ripple_ctx *c, const float *w, uint32_t Kpad, uint32_t Npad, float **out) {
+    const uint32_t n = Kpad * Npad;                          // (at most 2048 x 1024; Kpad is a multiple of 32)
+    RP_TRY(dev_alloc(c, out, n, false));
+    hipLaunchKernelGGL(k_quads, dim3(rp_div_up(n, 256)), dim3(256), 0, c->stream, w, *out, n, Npad);
     return RIPPLE_OK;
 }
 
@@ -397,8 +440,73 @@ static ripple_status upload_padded(ripple_ctx *c, const float *w, const float *b
     RP_TRY(dev_alloc(c, W_d, wp.size(), false));
     RP_TRY(dev_alloc(c, b_d, bp.size(), false));
     RP_HIP(c, hipMemcpy(*W_d, wp.data(), wp.size() * 4, hipMemcpyHostToDevice));
-    RP_TRY(upload_quads(c, wp.data(), Kpad, Npad, Wq_d));
+    RP_TRY(make_quads(c, *W_d, Kpad, Npad, Wq_d));
     RP_HIP(c, hipMemcpy(*b_d, bp.data(), bp.size() * 4, hipMemcpyHostToDevice));
+    return RIPPLE_OK;
+}
+
+// Device scratch for batches of n_ops operations and want_exp edges of deleted vertices; what is there already is not made smaller
+static ripple_status grow_scratch(ripple_ctx *c, uint32_t n_ops, uint32_t want_exp) {
+    if (n_ops <= c->ops_cap && want_exp <= c->exp_cap) return RIPPLE_OK;
+    RP_HIP(c, hipStreamSynchronize(c->stream));
+    const uint32_t cap = n_ops <= c->ops_cap ? c->ops_cap : rp_round_up(n_ops <= PIN_OPS ? PIN_OPS : n_ops + n_ops / 2, 1024);
+    const uint32_t exp = std::max(want_exp, c->exp_cap);
+    if (c->batch_block) hipFree(c->batch_block);
+    c->batch_block = nullptr;
+    c->ops_cap = c->exp_cap = c->touch_cap = c->struct_cap = 0;
+    const size_t both = (size_t)cap + exp, entries = 2 * (size_t)cap + exp;
+    Block b;
+    b.add(&c->ops_d, cap);
+    b.add(&c->op_status, cap);
+    b.add(&c->op_pos_out, cap);
+    b.add(&c->op_pos_in, cap);
+    b.add(&c->op_touch, cap);
+    b.add(&c->op_rank_out, cap);
+    b.add(&c->op_rank_in, cap);
+    b.add(&c->touch_out, both);
+    b.add(&c->touch_in, both);
+    b.add(&c->exp_kind, exp);
+    b.add(&c->exp_pos, exp);
+    b.add(&c->exp_rank, exp);
+    b.add(&c->exp_a, exp);
+    b.add(&c->exp_b, exp);
+    b.add(&c->st_src, both);
+    b.add(&c->st_dst, both);
+    b.add(&c->st_sign, both);
+    b.add(&c->st_unit, both);
+    b.add(&c->seg_id, entries);
+    b.add(&c->seg_x, entries);
+    if (c->opt_deterministic) {
+        b.add(&c->srt_id, entries);
+        b.add(&c->srt_x, entries);
+    }
+    RP_TRY(block_alloc(c, b, &c->batch_block, false));
+    c->ops_cap = cap;
+    c->exp_cap = exp;
+    c->touch_cap = c->struct_cap = (uint32_t)both;
+    return RIPPLE_OK;
+}
+
+// Pinned staging for n_ops operations and n_feat feature rows. Not to be called while a piece is under way: it reads them.
+static ripple_status grow_staging(ripple_ctx *c, uint32_t n_ops, uint32_t n_feat) {
+    if (n_ops <= c->pin_ops_cap && n_feat <= c->feat_cap) return RIPPLE_OK;
+    RP_HIP(c, hipStreamSynchronize(c->stream));
+    if (n_ops > c->pin_ops_cap) {
+        if (c->ops_pin && !in_pin_block(c, c->ops_pin)) hipHostFree(c->ops_pin);
+        c->ops_pin = nullptr;
+        c->pin_ops_cap = 0;
+        const uint32_t cap = rp_round_up(n_ops + n_ops / 2, 1024);
+        RP_HIP(c, hipHostMalloc((void **)&c->ops_pin, (size_t)cap * sizeof(ripple_update), hipHostMallocDefault));
+        c->pin_ops_cap = cap;
+    }
+    if (n_feat > c->feat_cap) {
+        if (c->payload_pin && !in_pin_block(c, c->payload_pin)) hipHostFree(c->payload_pin);
+        c->payload_pin = nullptr;
+        c->feat_cap = 0;
+        const uint32_t cap = rp_round_up(n_feat + n_feat / 2, 256);
+        RP_HIP(c, hipHostMalloc((void **)&c->payload_pin, (size_t)cap * c->d[0] * 4, hipHostMallocDefault));
+        c->feat_cap = cap;
+    }
     return RIPPLE_OK;
 }
 
@@ -491,7 +599,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
                 }
             RP_TRY(dev_alloc(c, &ly.Wc, wc.size(), false));
             RP_HIP(c, hipMemcpy(ly.Wc, wc.data(), wc.size() * 4, hipMemcpyHostToDevice));
-            RP_TRY(upload_quads(c, wc.data(), kp, 128, &ly.Wcq));
+            RP_TRY(make_quads(c, ly.Wc, kp, 128, &ly.Wcq));
             RP_TRY(dev_alloc(c, &ly.bzero_c, (size_t)128, true));
             if (s.d_in == 256 && s.d_out > 16 && s.d_out <= 48) {           // [k][n][j]: n < 16 column 16 j + n of W_self, else 16 j + n - 16 of W_neigh
                 std::vector<float> wp((size_t)256 * 96, 0.0f);
@@ -552,11 +660,13 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
             c->big_cap = (uint32_t)std::min<uint64_t>(c->pool_cap / ROW_SPLIT_MIN + 1, ROW_SEG_MAX);
             c->seg_cap = (uint32_t)std::min<uint64_t>(c->pool_cap / ROW_SEG + c->big_cap, ROW_SEG_MAX);
             c->seg_ld = rp_round_up(mw, 32);             // partial rows share no 128-byte line
-            RP_TRY(dev_alloc(c, &c->seg_v, c->big_cap, false));
-            RP_TRY(dev_alloc(c, &c->seg_done, c->big_cap, false));
-            RP_TRY(dev_alloc(c, &c->seg_base, c->big_cap, false));
-            RP_TRY(dev_alloc(c, &c->seg_r, c->seg_cap, false));
-            RP_TRY(dev_alloc(c, &c->seg_part, (size_t)c->seg_cap * c->seg_ld, false));
+            Block b;
+            b.add(&c->seg_v, c->big_cap);
+            b.add(&c->seg_done, c->big_cap);
+            b.add(&c->seg_base, c->big_cap);
+            b.add(&c->seg_r, c->seg_cap);
+            b.add(&c->seg_part, (size_t)c->seg_cap * c->seg_ld);
+            RP_TRY(block_alloc(c, b, &c->seg_block, false));
         }
     }
     RP_TRY(dev_alloc(c, &c->D[0], n * c->dmax, false));
@@ -591,24 +701,29 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         while (c->pair_bits < 32 && (1ull << c->pair_bits) <= n) ++c->pair_bits;   // 2^bits > every vertex id; the filler key has all of them set
         c->pair_tmp_bytes = rp_sort_u32_tmp_bytes(c->pair_cap);
         if (c->pair_tmp_bytes) {
-            uint8_t *tmp = nullptr;
-            RP_TRY(dev_alloc(c, &c->pk_a, c->pair_cap, false));
-            RP_TRY(dev_alloc(c, &c->pk_b, c->pair_cap, false));
-            RP_TRY(dev_alloc(c, &c->pv_a, c->pair_cap, false));
-            RP_TRY(dev_alloc(c, &c->pv_b, c->pair_cap, false));
-            RP_TRY(dev_alloc(c, &tmp, c->pair_tmp_bytes, false));
-            c->pair_tmp = tmp;
+            Block b;
+            b.add(&c->pk_a, c->pair_cap);
+            b.add(&c->pk_b, c->pair_cap);
+            b.add(&c->pv_a, c->pair_cap);
+            b.add(&c->pv_b, c->pair_cap);
+            b.add((uint8_t **)&c->pair_tmp, c->pair_tmp_bytes);
+            RP_TRY(block_alloc(c, b, &c->pair_block, false));
         } else {
             c->pair_cap = 0;
         }
     }
     // bitmaps: layers 0..L, then S, then V_added, contiguous; reporting copies separately
     uint32_t *bmall = nullptr, *repall = nullptr, *lists = nullptr, *eoffs = nullptr, *ioffs = nullptr;
-    RP_TRY(dev_alloc(c, &bmall, (size_t)c->n_words * (c->L + 3), true));
-    RP_TRY(dev_alloc(c, &repall, (size_t)c->n_words * (c->L + 1), true));
-    RP_TRY(dev_alloc(c, &lists, (n + 1) * (c->L + 1), true));
-    RP_TRY(dev_alloc(c, &eoffs, (n + 1) * (c->L + 1), true));
-    RP_TRY(dev_alloc(c, &ioffs, (n + 1) * (c->L + 1), true));
+    Block b;
+    b.add(&bmall, (size_t)c->n_words * (c->L + 3));
+    b.add(&repall, (size_t)c->n_words * (c->L + 1));
+    b.add(&lists, (n + 1) * (c->L + 1));
+    b.add(&eoffs, (n + 1) * (c->L + 1));
+    b.add(&ioffs, (n + 1) * (c->L + 1));
+    b.add(&c->all_list, n + 1);
+    b.add(&c->mk, (size_t)c->n_words * 32);
+    b.add(&c->ioff_all, n + 1);
+    RP_TRY(block_alloc(c, b, &c->list_block, true));
     for (uint32_t l = 0; l <= c->L; ++l) {
         c->bm[l] = bmall + (size_t)l * c->n_words;
         c->rep[l] = repall + (size_t)l * c->n_words;
@@ -618,13 +733,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
     }
     c->bm_sink = bmall + (size_t)(c->L + 1) * c->n_words;
     c->bm_vadd = bmall + (size_t)(c->L + 2) * c->n_words;
-    RP_TRY(dev_alloc(c, &c->all_list, n + 1, true));
-    {
-        uint32_t *mkw = nullptr;                         // n_words * 32 bytes
-        RP_TRY(dev_alloc(c, &mkw, (size_t)c->n_words * 8, true));
-        c->mk = (uint8_t *)mkw;
-    }
-    RP_TRY(dev_alloc(c, &c->ioff_all, n + 1, true));
+    RP_TRY(grow_scratch(c, PIN_OPS, 0));
     RP_HIP(c, hipStreamSynchronize(c->stream));
     c->state = 2;
     return RIPPLE_OK;
@@ -801,68 +910,6 @@ extern "C" ripple_status ripple_plan_batch(const ripple_update *ops, uint32_t n_
     for (size_t p = 0; p < pieces.size(); ++p)
         if (p < cap) piece_end[p] = pieces[p].end;
     *n_pieces = (uint32_t)pieces.size();
-    return RIPPLE_OK;
-}
-
-static ripple_status ensure_batch_buffers(ripple_ctx *c, uint32_t n_ops, uint32_t n_feat, uint32_t want_exp) {
-    if (n_ops > c->ops_cap || want_exp > c->exp_cap) {
-        RP_HIP(c, hipStreamSynchronize(c->stream));
-        uint32_t cap = c->ops_cap;
-        if (n_ops > cap) cap = rp_round_up(std::max<uint32_t>(n_ops, 4096) / 2 * 3, 1024);
-        uint32_t exp = std::max<uint32_t>(std::max<uint32_t>(want_exp, c->exp_cap), 1u << 20);
-        void *old[] = {c->ops_d, c->op_status, c->op_pos_out, c->op_pos_in, c->op_touch, c->touch_out, c->touch_in, c->exp_kind, c->exp_pos,
-                       c->exp_rank, c->exp_a, c->exp_b, c->st_src, c->st_dst, c->st_sign, c->st_unit, c->op_rank_out, c->op_rank_in, c->seg_id,
-                       c->seg_x, c->srt_id, c->srt_x};
-        for (void *p : old)
-            if (p) hipFree(p);
-        c->srt_id = c->srt_x = nullptr;
-        c->ops_cap = c->exp_cap = c->touch_cap = c->struct_cap = 0;
-        RP_TRY(dev_alloc(c, &c->ops_d, cap, false));
-        RP_TRY(dev_alloc(c, &c->op_status, cap, true));
-        RP_TRY(dev_alloc(c, &c->op_pos_out, cap, true));
-        RP_TRY(dev_alloc(c, &c->op_pos_in, cap, true));
-        RP_TRY(dev_alloc(c, &c->op_touch, cap, true));
-        RP_TRY(dev_alloc(c, &c->touch_out, (size_t)cap + exp, false));
-        RP_TRY(dev_alloc(c, &c->touch_in, (size_t)cap + exp, false));
-        RP_TRY(dev_alloc(c, &c->exp_kind, exp, false));
-        RP_TRY(dev_alloc(c, &c->exp_pos, exp, false));
-        RP_TRY(dev_alloc(c, &c->exp_rank, exp, false));
-        RP_TRY(dev_alloc(c, &c->exp_a, exp, false));
-        RP_TRY(dev_alloc(c, &c->exp_b, exp, false));
-        RP_TRY(dev_alloc(c, &c->st_src, (size_t)cap + exp, false));
-        RP_TRY(dev_alloc(c, &c->st_dst, (size_t)cap + exp, false));
-        RP_TRY(dev_alloc(c, &c->st_sign, (size_t)cap + exp, false));
-        RP_TRY(dev_alloc(c, &c->st_unit, (size_t)cap + exp, false));
-        const size_t entries = 2 * (size_t)cap + exp;
-        RP_TRY(dev_alloc(c, &c->op_rank_out, cap, false));
-        RP_TRY(dev_alloc(c, &c->op_rank_in, cap, false));
-        RP_TRY(dev_alloc(c, &c->seg_id, entries, false));
-        RP_TRY(dev_alloc(c, &c->seg_x, entries, false));
-        if (c->opt_deterministic) {
-            RP_TRY(dev_alloc(c, &c->srt_id, entries, false));
-            RP_TRY(dev_alloc(c, &c->srt_x, entries, false));
-        }
-        c->ops_cap = cap;
-        c->exp_cap = exp;
-        c->touch_cap = cap + exp;
-        c->struct_cap = cap + exp;
-    }
-    if (n_ops > c->pin_ops_cap) {
-        if (c->ops_pin) hipHostFree(c->ops_pin);
-        c->ops_pin = nullptr;
-        c->pin_ops_cap = 0;
-        RP_HIP(c, hipHostMalloc((void **)&c->ops_pin, (size_t)c->ops_cap * sizeof(ripple_update), hipHostMallocDefault));
-        c->pin_ops_cap = c->ops_cap;
-    }
-    if (n_feat > c->feat_cap) {
-        RP_HIP(c, hipStreamSynchronize(c->stream));
-        uint32_t cap = rp_round_up(std::max<uint32_t>(n_feat + n_feat / 2, 1024), 256);
-        if (c->payload_pin) hipHostFree(c->payload_pin);
-        c->payload_pin = nullptr;
-        c->feat_cap = 0;
-        RP_HIP(c, hipHostMalloc((void **)&c->payload_pin, (size_t)cap * c->d[0] * 4, hipHostMallocDefault));
-        c->feat_cap = cap;
-    }
     return RIPPLE_OK;
 }
 
@@ -1096,7 +1143,7 @@ static ripple_status run_piece(ripple_ctx *c, const SubBatch &sb, bool multi, ui
         if (attempt >= 2) return fail(c, RIPPLE_ECAPACITY, "adjacency pool exhausted even after compaction");
         if (h.abort_flag & 4u) {
             uint32_t want = h.need_exp + h.need_exp / 2 + 1024;
-            RP_TRY(ensure_batch_buffers(c, 0, 0, want));  // (the operations in ops_pin are read again by the retry: they stay where they are)
+            RP_TRY(grow_scratch(c, 0, want));
         }
         if (h.abort_flag & 1u) {
             ++*compactions;
@@ -1117,7 +1164,8 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     hipStream_t s = c->stream;
     int t_total = rp_timer_begin(c);
 
-    RP_TRY(ensure_batch_buffers(c, n_ops, (n_feat_rows && !is_device_ptr(c, feat_payload)) ? n_feat_rows : 0u, 0));
+    const bool rows_on_host = n_feat_rows && !is_device_ptr(c, feat_payload);
+    RP_TRY(grow_staging(c, n_ops, rows_on_host ? n_feat_rows : 0u));
     // operations are needed on the host (validation, conflict analysis)
     const ripple_update *hops = ops;
     if (n_ops && is_device_ptr(c, ops)) {
@@ -1141,13 +1189,17 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     }
     split_batch(hops, n_ops, tt, pieces);
     const bool multi = pieces.size() > 1;
+    // room for the edges of deleted vertices only where there are any; what turns out too small grows (run_piece)
+    bool deletes = false;
+    for (const SubBatch &sb : pieces) deletes |= sb.has_vdel;
+    RP_TRY(grow_scratch(c, n_ops, deletes ? std::max<uint32_t>(c->exp_cap, (uint32_t)std::min<uint64_t>(1u << 20, 2 * c->e_cap + 1)) : 0u));
     if (hops != c->ops_pin) memcpy(c->ops_pin, hops, (size_t)n_ops * sizeof(ripple_update));
 
     if (multi)
         RP_HIP(c, hipMemsetAsync(c->rep[0], 0, (size_t)c->n_words * (c->L + 1) * 4, s));
     // feature rows: used in place when they already live on the device
     c->payload = feat_payload;
-    if (n_feat_rows && !is_device_ptr(c, feat_payload)) {          // the kernel that applies them reads each row once, over the bus
+    if (rows_on_host) {                                    // the kernel that applies them reads each row once, over the bus
         memcpy(c->payload_pin, feat_payload, (size_t)n_feat_rows * c->d[0] * 4);
         c->payload = c->payload_pin;
     }

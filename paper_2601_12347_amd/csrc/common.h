@@ -197,6 +197,10 @@ struct ripple_ctx {
     ripple_update *ops_pin = nullptr;                   // pinned staging for ops
     float *payload_pin = nullptr;
     uint32_t pin_ops_cap = 0;
+    uint8_t *pin_block = nullptr;                       // pinned: ctr_host, pub_flag, io_pin and the first ops_pin / payload_pin
+    size_t pin_bytes = 0;
+    // device arrays that share an allocation: the graph store's (but the pools), bitmaps and lists, batch scratch, messages as pairs, row segments
+    uint8_t *graph_block = nullptr, *list_block = nullptr, *batch_block = nullptr, *pair_block = nullptr, *seg_block = nullptr;
 
     // gather staging for get_* calls; pinned: 16 words (a count), then ids, then rows
     uint32_t *io_pin = nullptr;

@@ -141,3 +141,24 @@ def test_many_changes_of_one_row(deterministic, weighted, dels, adds):
         pair.check_aggregates()
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("deterministic", [False, True])
+def test_batches_around_the_room_a_context_starts_with(deterministic):
+    """Operations and feature rows are staged in memory that a context has from its start, up to 6,144 and 1,024 of them; larger
+    batches bring room of their own, deleted vertices room for their edges. All sizes in turn on one context."""
+    print("case staging", deterministic, flush=True)
+    pair, _ = make_pair(n=7000, e=12000, d0=3, kind="sage_mean", widths=(3, 5, 2), seed=61, slack=8, deterministic=deterministic)
+    rng = np.random.default_rng(62)
+    try:
+        for feats, dels in ((1, 0), (1024, 0), (1025, 0), (2, 3), (6143, 0), (6144, 1), (6145, 0), (3, 0)):
+            print(" feature rows", feats, "deleted", dels, flush=True)
+            alive = rng.permutation(np.flatnonzero(pair.ora.alive[:7000]))
+            feats = min(feats, len(alive) - dels)
+            ops = np.array([(ri.OP_FEAT_UPDATE, w, 0, i) for i, w in enumerate(alive[:feats])] + [(ri.OP_VERTEX_DEL, w, 0, 0) for w in alive[feats:feats + dels]],
+                           dtype=np.uint32)
+            pair.step(ops, rng.standard_normal((feats, 3)).astype(np.float32))
+        pair.check_graph()
+        pair.check_aggregates()
+    finally:
+        pair.close()
