@@ -862,13 +862,83 @@ __global__ __launch_bounds__(256) void k_edges(MutArgs a, uint32_t tb, uint32_t 
 // within a segment), the terms are added in it, with plain loads and stores by one owner per 64 columns, and k_rows appends
 // the additions in it. With the rows built in the order the edges were given, and the fills of k_rows being functions of the row
 // and the deleted positions alone, an in-row's order then depends on the batches that were applied and on nothing else.
-// A workgroup per touched in-row; its wavefronts share the layers and columns, eight source rows are on their way at a time
+// A workgroup per touched in-row; its wavefronts share the layers and columns, sixteen source rows are on their way at a time
 // (one wavefront per sink, after a radix sort of all changed edges, took 77 us per 1,000 operations where this takes 15).
-// Segments of up to DET_IDS entries are ranked in LDS, longer ones (hubs in large batches) tile by tile through `srt`.
+// Segments of up to DET_IDS entries are ranked in LDS. Longer ones (hubs in large batches) are ranked tile by tile and the tiles
+// merged by the workgroup, `srt` and the segment itself taking turns; every entry finds its place in the other run by bisection.
+// (All entries ranked against all others: batches of 2,000, 20,000 and 60,000 changes of one row took 1.5, 92 and 766 ms; now
+// 0.69, 7.5 and 24.)
 #define DET_IDS 1024u
+#define DET_ADD 0x80000000u                 // an addition; ids are below 2^31
+
+// Entries [0, cnt) of a tile, four per thread at most: ranked by id and written to the tile's places in `to_id` / `to_x` (which may be
+// where they came from) with their kind; entries at or behind `dead` are additions. By the whole workgroup; cnt <= DET_IDS.
+__device__ __forceinline__ void det_rank_tile(const uint32_t *id, const uint32_t *x, uint32_t cnt, uint32_t dead, uint32_t *s_in, uint32_t *to_id, uint32_t *to_x) {
+    const uint32_t tid = threadIdx.x;
+    uint32_t my[4], xv[4], rank[4];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t i = tid + 256u * q;
+        my[q] = i < cnt ? id[i] : 0u;
+        xv[q] = i < cnt ? x[i] : 0u;
+        rank[q] = 0;
+        if (i < cnt) s_in[i] = my[q];
+    }
+    __syncthreads();
+    for (uint32_t k = 0; k < cnt; ++k) {
+        const uint32_t o = s_in[k];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) rank[q] += o < my[q] ? 1u : 0u;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+        const uint32_t i = tid + 256u * q;
+        if (i < cnt) {
+            to_id[rank[q]] = my[q] | (i >= dead ? DET_ADD : 0u);
+            to_x[rank[q]] = xv[q];
+        }
+    }
+    __threadfence_block();
+    __syncthreads();
+}
+
+// Runs of `run` entries (the last one shorter) merged in pairs from one pair of arrays to another. By the whole workgroup.
+__device__ __forceinline__ void det_merge(const uint32_t *id, const uint32_t *x, uint32_t *to_id, uint32_t *to_x, uint32_t n, uint32_t run) {
+    for (uint32_t i0 = 0; i0 < n; i0 += 1024u) {
+        uint32_t e[4], lo[4], hi[4], at[4];                 // four bisections at a time: each step is a read that the next one waits for
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t i = min(i0 + 256u * q + threadIdx.x, n - 1u);
+            const uint32_t pair = i / (2u * run) * (2u * run), mid = min(n, pair + run), end = min(n, pair + 2u * run);
+            e[q] = id[i];
+            lo[q] = i < mid ? mid : pair;                   // the other run
+            hi[q] = i < mid ? end : mid;
+            at[q] = (i < mid ? i : pair + (i - mid)) - lo[q];   // + the place found there: where the entry goes (mod 2^32)
+        }
+        for (uint32_t left = run; left; left >>= 1)         // (`run` is a power of two; run entries take log2(run) + 1 steps)
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t m = (lo[q] + hi[q]) >> 1;
+                const bool open = lo[q] < hi[q], below = (id[min(m, n - 1u)] & ~DET_ADD) < (e[q] & ~DET_ADD);
+                if (open && below) lo[q] = m + 1u;
+                else if (open) hi[q] = m;
+            }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t i = i0 + 256u * q + threadIdx.x;
+            if (i < n) {
+                to_id[at[q] + lo[q]] = e[q];
+                to_x[at[q] + lo[q]] = x[i];
+            }
+        }
+    }
+    __threadfence_block();
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(256) void k_det_terms(MutArgs a) {
-    constexpr uint32_t ADD = 0x80000000u;                   // ids are below 2^31
-    constexpr int G = 8;
+    constexpr int G = 16;
     __shared__ uint32_t s_in[DET_IDS], s_id[DET_IDS], s_x[DET_IDS], s_w[4];
     if (a.ctr->abort_flag) return;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -877,42 +947,43 @@ __global__ __launch_bounds__(256) void k_det_terms(MutArgs a) {
         const uint32_t v = a.touch_in[j], base = a.hole_in[v], dead = a.dead_in[v], n = dead + a.pend_in[v];
         const bool in_lds = n <= DET_IDS;
         uint32_t *ids = in_lds ? s_id : a.srt_id + base, *xs = in_lds ? s_x : a.srt_x + base;
-        for (uint32_t i0 = 0; i0 < n; i0 += 256u) {         // every entry's rank, DET_IDS others at a time
-            const uint32_t i = i0 + tid;
-            const uint32_t my = i < n ? a.seg_id[base + i] : 0u, x = i < n ? a.seg_x[base + i] : 0u;
-            uint32_t rank = 0;
-            for (uint32_t t0 = 0; t0 < n; t0 += DET_IDS) {
-                const uint32_t cnt = min(DET_IDS, n - t0);
-                if (i0 == 0 || !in_lds) {
-                    __syncthreads();
-                    for (uint32_t k = tid; k < cnt; k += 256u) s_in[k] = a.seg_id[base + t0 + k];
-                    __syncthreads();
-                }
-                if (i < n)
-                    for (uint32_t k = 0; k < cnt; ++k) rank += s_in[k] < my ? 1u : 0u;
-            }
-            if (i < n) {
-                ids[rank] = my | (i >= dead ? ADD : 0u);
-                xs[rank] = x;
+        if (in_lds) {
+            det_rank_tile(a.seg_id + base, a.seg_x + base, n, dead, s_in, s_id, s_x);
+        } else {
+            uint32_t passes = 0;
+            while ((DET_IDS << passes) < n) ++passes;       // (n is below 2^31)
+            uint32_t *fi = (passes & 1u) ? a.seg_id + base : ids, *fx = (passes & 1u) ? a.seg_x + base : xs;   // the last pass ends in srt
+            uint32_t *ti = (passes & 1u) ? ids : a.seg_id + base, *tx = (passes & 1u) ? xs : a.seg_x + base;
+            for (uint32_t t0 = 0; t0 < n; t0 += DET_IDS)
+                det_rank_tile(a.seg_id + base + t0, a.seg_x + base + t0, min(DET_IDS, n - t0), dead - min(dead, t0), s_in, fi + t0, fx + t0);
+            for (uint32_t p = 0; p < passes; ++p) {
+                det_merge(fi, fx, ti, tx, n, DET_IDS << p);
+                uint32_t *s = fi;
+                fi = ti;
+                ti = s;
+                s = fx;
+                fx = tx;
+                tx = s;
             }
         }
-        __threadfence_block();
-        __syncthreads();
-        uint32_t at = base + dead;                          // the additions, in order, back to their part of the segment
+        uint32_t adds = 0;                                  // the additions, in order, back to their part of the segment
         for (uint32_t i0 = 0; i0 < n; i0 += 256u) {
             const uint32_t i = i0 + tid;
             const uint32_t id = i < n ? ids[i] : 0u;
-            const unsigned long long m = __ballot((id & ADD) != 0);
+            const unsigned long long m = __ballot((id & DET_ADD) != 0);
             if (lane == 0) s_w[wave] = (uint32_t)__popcll(m);
             __syncthreads();
-            uint32_t off = at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+            uint32_t before = adds + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
             for (uint32_t k = 0; k < 4; ++k) {
-                if (k < wave) off += s_w[k];
-                at += s_w[k];
+                if (k < wave) before += s_w[k];
+                adds += s_w[k];
             }
-            if (id & ADD) {
-                a.seg_id[off] = id & ~ADD;
-                a.seg_x[off] = xs[i];
+            if (id & DET_ADD) {
+                a.seg_id[base + dead + before] = id & ~DET_ADD;
+                a.seg_x[base + dead + before] = xs[i];
+            } else if (!in_lds && i < n) {                  // (the merge went through the segment: the deletions' part is written again as well)
+                a.seg_id[base + i - before] = id;
+                a.seg_x[base + i - before] = xs[i];
             }
             __syncthreads();
         }
@@ -926,19 +997,24 @@ __global__ __launch_bounds__(256) void k_det_terms(MutArgs a) {
                 const uint32_t col = c0 + lane;
                 float *xp = a.X[l] + (size_t)v * w + col;
                 float x = (col < w) ? *xp : 0.0f;
-                for (uint32_t j0 = 0; j0 < n; j0 += G) {
-                    float val[G], sg[G];
+                uint32_t next = lane < n ? ids[lane] : 0u;  // 64 entries, one per lane; the next 64 are under way meanwhile
+                for (uint32_t j0 = 0; j0 < n; j0 += 64u) {
+                    const uint32_t mine = next, cnt = min(64u, n - j0);
+                    if (j0 + 64u + lane < n) next = ids[j0 + 64u + lane];
+                    for (uint32_t k0 = 0; k0 < cnt; k0 += G) {
+                        float val[G], sg[G];
 #pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const uint32_t id = ids[min(j0 + (uint32_t)g, n - 1u)], u = id & ~ADD;
-                        sg[g] = (id & ADD) ? 1.0f : -1.0f;
-                        val[g] = 0.0f;
-                        if (col < w && j0 + (uint32_t)g < n)
-                            val[g] = Tl ? Tl[(size_t)u * w + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
+                        for (int g = 0; g < G; ++g) {
+                            val[g] = 0.0f;
+                            if (k0 + (uint32_t)g >= cnt) continue;
+                            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(k0 + (uint32_t)g)), u = id & ~DET_ADD;
+                            sg[g] = (id & DET_ADD) ? 1.0f : -1.0f;
+                            if (col < w) val[g] = Tl ? Tl[(size_t)u * w + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
+                        }
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+                            if (k0 + (uint32_t)g < cnt) x += sg[g] * val[g];
                     }
-#pragma unroll
-                    for (int g = 0; g < G; ++g)
-                        if (j0 + (uint32_t)g < n) x += sg[g] * val[g];
                 }
                 if (col < w) *xp = x;
             }

@@ -162,3 +162,25 @@ def test_batches_around_the_room_a_context_starts_with(deterministic):
         pair.check_aggregates()
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("dels,adds", [(1024, 1024), (1, 2048), (3000, 1096), (4096, 1), (9000, 11001)])
+def test_long_rows_of_changes_are_put_in_order(dels, adds):
+    """Deterministic mode: the changes of one row in two, three, four, five and twenty tiles that are merged. What is appended has to
+    be in ascending order, and the terms are sums of it."""
+    print("case merged changes", dels, adds, flush=True)
+    n, k = 24000, 9500
+    rng = np.random.default_rng(dels + adds)
+    src = np.arange(1, 1 + k, dtype=np.uint32)
+    pair = Pair(n, n + 3, src, np.zeros(k, np.uint32), ri.features(n, 5, 1), ri.make_model("sage_mean", (5, 9, 70, 4), 3), deterministic=True, edge_capacity=40000)
+    try:
+        gone, new = rng.permutation(src)[:dels], rng.permutation(np.arange(10000, 10000 + adds, dtype=np.uint32))
+        ops = np.array([(ri.OP_EDGE_DEL, x, 0, 0) for x in gone] + [(ri.OP_EDGE_ADD, x, 0, 0) for x in new], dtype=np.uint32)
+        pair.step(ops[rng.permutation(len(ops))], None)
+        pair.check_graph()
+        pair.check_aggregates()
+        s, d, m = rp.ripple_export_edges(pair.ctx, 1, 40000)
+        row = s[:m][d[:m] == 0]
+        assert len(row) == k - dels + adds and np.array_equal(row[k - dels:], np.sort(new))
+    finally:
+        pair.close()
