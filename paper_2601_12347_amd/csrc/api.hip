@@ -4,6 +4,7 @@
 // read-back calls the tests use.
 #include "common.h"
 #include "kernels.h"
+#include "pull_scan.h"
 
 #include <chrono>
 #include <cstring>
@@ -669,8 +670,15 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
             RP_TRY(block_alloc(c, b, &c->seg_block, false));
         }
     }
-    RP_TRY(dev_alloc(c, &c->D[0], n * c->dmax, false));
-    RP_TRY(dev_alloc(c, &c->D[1], n * c->dmax, false));
+    {   // rows of changes; the bootstrap and attention hops leave the parts of cut rows there before (two per run of chunks)
+        size_t part = 0;
+        for (uint32_t l = 1; l <= c->L && !c->opt_deterministic; ++l)
+            if (!rp_layer_mono(c, l)) part = std::max<size_t>(part, c->xw[l] + (rp_layer_attn(c, l) ? 2u : 0u));
+        c->max_runs = rp_max_runs(c->pool_cap, c->n_cu * 8 * 4);
+        part = part ? 2 * c->max_runs * (1 + part) : 0;
+        RP_TRY(dev_alloc(c, &c->D[0], std::max(n * c->dmax, part), false));
+        RP_TRY(dev_alloc(c, &c->D[1], std::max(n * c->dmax, part), false));
+    }
     if (c->hmax) RP_TRY(dev_alloc(c, &c->tmp, n * c->hmax, false));
     {
         uint32_t pw = 0;

@@ -452,14 +452,15 @@ __global__ __launch_bounds__(TEAM * 64) void k_gat_scatter_seg(GatArgs a) {
 // counter like a pull's. What an edge contributes is put into a list in LDS, in edge order, hence by destination: one entry
 // for an in-neighbour of a recomputed vertex, two (the new term and the old one, taken away) for a changed in-neighbour of any
 // other. The list is then summed like a pull's messages, one row per entry. A vertex whose in-edges lie in one run is
-// written by that run alone; what a run boundary cuts is combined with atomics (k_gat_prepare has zeroed the cut rows that
-// are recomputed). Changed edges of a vertex that keeps its long row are added before (k_gat_edge_terms). A patched
+// written by that run alone; what a run boundary cuts is left in parts, which k_gat_close adds up in run order (see
+// rp_sum_parts). Changed edges of a vertex that keeps its long row are added before (k_gat_edge_terms). A patched
 // denominator that has cancelled (GAT_CANCEL) is found afterwards (k_gat_check) and its row recomputed by a workgroup.
 struct GatEdgeArgs {
     PullArgs p;                    // list, count_ptr, ioff, in_meta, in_pool, bm_prev, d, X, ctr, l
     const uint32_t *bm_sink, *bm_vadd;
     const float *P, *Pold, *ssrc, *sold, *sdst;
     uint32_t ldp;
+    CutRows c;                     // vertices that a run boundary cuts; a row: numerator (d), denominator, mag
     float *den, *mag;              // mag: what a vertex's patches have added and taken away (valid for listed vertices)
     uint8_t *rec;                  // per listed vertex: recomputed
     int all;                       // bootstrap
@@ -471,16 +472,10 @@ struct GatEdgeArgs {
     uint32_t struct_cap;
 };
 
-__device__ __forceinline__ uint32_t gat_per(uint32_t n_chunks, uint32_t nw) { return max(1u, min((uint32_t)PULL_RUN, n_chunks / (2u * nw))); }
-__device__ __forceinline__ uint32_t gat_span(uint32_t total, uint32_t nw) {             // edges per run
-    return gat_per((total + PULL_CHUNK - 1) / PULL_CHUNK, nw) * PULL_CHUNK;
-}
-
 __global__ __launch_bounds__(256) void k_gat_prepare(GatEdgeArgs a) {
     const int lane = rp_lane();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
-    const uint32_t span = gat_span(count ? a.p.ioff[count] : 0u, a.n_waves);
     for (uint32_t base = gw * 64u; base < count; base += nw * 64u) {
         const uint32_t i = base + (uint32_t)lane;
         bool zero = false;
@@ -491,7 +486,7 @@ __global__ __launch_bounds__(256) void k_gat_prepare(GatEdgeArgs a) {
             const bool rec = a.all || rp_bit(a.p.bm_prev, v) || rp_bit(a.bm_vadd, v) || (rp_bit(a.bm_sink, v) && e1 - e0 <= a.long_min);
             a.rec[v] = rec ? 1 : 0;
             a.mag[v] = 0.0f;
-            zero = rec && (e1 == e0 || e0 / span != (e1 - 1u) / span);
+            zero = rec && e1 == e0;                         // no run meets it
             if (zero) a.den[v] = 0.0f;
         }
         unsigned long long m = __ballot(zero);
@@ -550,7 +545,7 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
     const uint32_t total = a.p.ioff[count];
     const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t per = gat_per(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
+    const uint32_t per = rp_chunks_per_run(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
     uint32_t *su = s_u[wave], *sv = s_v[wave];
     float *sx = s_x[wave];
     for (uint32_t run = gw; run < n_runs;) {
@@ -560,16 +555,22 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
         const uint32_t e_end = min(total, c_end * PULL_CHUNK);
         const uint32_t v_first = (uint32_t)__shfl((int)scan.rv, 0), i_last = rp_seg_search_wave(a.p.ioff, 0, count - 1, e_end - 1u);
         const uint32_t v_last = a.p.list[i_last];
-        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK, cut_last = a.p.ioff[i_last + 1u] > e_end;
+        const uint32_t e_last = a.p.ioff[i_last + 1u];
+        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK, cut_last = e_last > e_end;
+        const bool goes_on = cut_last && !(v_last == v_first && cut_first);   // a vertex that begins here and ends in a later run
+        if (lane == 0) a.c.cut[run] = make_uint2(goes_on ? v_last : NONE, (e_last - 1u) / (per * PULL_CHUNK));
+        bool wrote_first = false, wrote_last = false;
         uint32_t cur = NONE;
         float acc[NJ], dsum = 0.0f, mag = 0.0f;
         float4 acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[j] = 0.0f;
         auto flush = [&]() {
-            const bool cut = (cur == v_first && cut_first) || (cur == v_last && cut_last);
-            const bool rec = a.rec[cur] != 0;
-            float *xr = a.p.X + (size_t)cur * d;
+            const bool began_before = cur == v_first && cut_first, cut = began_before || (cur == v_last && cut_last);
+            const bool rec = cut || a.rec[cur] != 0;         // a part is stored plainly, like a recomputed row
+            float *xr = cut ? a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * (d + 2u) : a.p.X + (size_t)cur * d;
+            wrote_first |= began_before;
+            wrote_last |= cut && !began_before;
             if (QUAD) {                                     // the four groups' sums together; lane (grp, sub) then has column 4 sub + grp
 #pragma unroll
                 for (int o = 16; o < 64; o <<= 1) {
@@ -586,16 +587,13 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const uint32_t col = QUAD ? 4u * sub + grp : (uint32_t)lane + 64u * j;
-                if (col < d) {
-                    if (cut) unsafeAtomicAdd(&xr[col], acc[j]);
-                    else xr[col] = rec ? acc[j] : xr[col] + acc[j];
-                }
+                if (col < d) xr[col] = rec ? acc[j] : xr[col] + acc[j];
                 acc[j] = 0.0f;
             }
             if (lane == 0) {
                 if (cut) {
-                    unsafeAtomicAdd(&a.den[cur], dsum);
-                    if (!rec) unsafeAtomicAdd(&a.mag[cur], mag);
+                    xr[d] = dsum;
+                    xr[d + 1u] = mag;
                 } else {
                     a.den[cur] = rec ? dsum : a.den[cur] + dsum;
                     if (!rec) a.mag[cur] += mag;
@@ -728,8 +726,43 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
             scan.advance();
         }
         if (cur != NONE) flush();
+        // nothing in this run changed for a vertex that it shares with others: its part is zero
+        for (uint32_t col = lane; cut_first && !wrote_first && col < d + 2u; col += 64u) a.c.part[(size_t)(2u * run) * (d + 2u) + col] = 0.0f;
+        for (uint32_t col = lane; goes_on && !wrote_last && col < d + 2u; col += 64u) a.c.part[(size_t)(2u * run + 1u) * (d + 2u) + col] = 0.0f;
         if ((unsigned long long)nw * per >= n_chunks) break;
         run = nw + rp_next_run(&a.p.ctr->pull_next[a.p.l], lane);
+    }
+}
+
+// Vertices that a run boundary cuts, a wavefront per run (22 us for 256 columns and 12 K runs, 13 for 47 and 17 K)
+__global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
+    const int lane = rp_lane();
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t count = *a.p.count_ptr, d = a.p.d;
+    if (count == 0) return;
+    const uint32_t total = a.p.ioff[count], n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
+    const uint32_t per = rp_chunks_per_run(n_chunks, a.n_waves), n_runs = (n_chunks + per - 1) / per;
+    for (uint32_t r = gw; r < n_runs; r += nw) {
+        const uint2 c = a.c.cut[r];
+        if (c.x == 0xFFFFFFFFu) continue;
+        const uint32_t v = c.x;
+        const bool rec = a.rec[v] != 0;
+        for (uint32_t c0 = lane; c0 < d + 2u; c0 += 64u * PARTS_B) {
+            float old[PARTS_B], t[PARTS_B];
+            float *to[PARTS_B];
+#pragma unroll
+            for (int b = 0; b < PARTS_B; ++b) {
+                const uint32_t col = c0 + 64u * b;
+                to[b] = col < d ? &a.p.X[(size_t)v * d + col] : (col == d ? &a.den[v] : &a.mag[v]);
+                old[b] = (!rec && col < d + 2u) ? *to[b] : 0.0f;
+            }
+            rp_sum_parts(a.c.part, d + 2u, r, c.y, c0, t);
+#pragma unroll
+            for (int b = 0; b < PARTS_B; ++b) {
+                const uint32_t col = c0 + 64u * b;
+                if (col <= d || (!rec && col == d + 1u)) *to[b] = old[b] + t[b];
+            }
+        }
     }
 }
 
@@ -813,6 +846,7 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool liste
     e.sold = c->sold;
     e.sdst = ly.sdst;
     e.ldp = ly.ldp;
+    e.c = rp_cut_rows(c->D[l & 1], c->max_runs);                                // (free until the row update fills it; load_model has made it large enough)
     e.den = ly.den;
     e.mag = c->gat_mag;
     e.rec = c->gat_rec;
@@ -833,6 +867,7 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool liste
 #define GAT_CASE(NJ, QUAD, TEAM)                                                                                              \
     do {                                                                                                                      \
         hipLaunchKernelGGL((k_gat_edges<NJ, QUAD>), grid, block, 0, c->stream, e);                                            \
+        hipLaunchKernelGGL(k_gat_close, dim3(c->n_cu * 16), block, 0, c->stream, e);                                                     \
         if (bootstrap) break;                                                                                                 \
         hipLaunchKernelGGL(k_gat_check, dim3(c->n_cu * 2), block, 0, c->stream, e);                                           \
         hipLaunchKernelGGL((k_gat_scatter_long<NJ, TEAM>), dim3(c->n_cu), dim3(TEAM * 64), 0, c->stream, b);                  \

@@ -138,6 +138,7 @@ struct ripple_ctx {
     void *H[RIPPLE_MAX_LAYERS + 1] = {nullptr};
     float *X[RIPPLE_MAX_LAYERS + 1] = {nullptr};
     float *D[2] = {nullptr, nullptr};                   // delta rows D^l[v] (valid for v in A_l), ping-pong
+    size_t max_runs = 0;                                // runs of chunks that the bootstrap and attention hops leave parts of cut rows for, in D
     float *tmp = nullptr;                               // hidden activations of two-stage updates
     float *PD = nullptr;                                // project-first layers: projected rows, then fp32 messages (by vertex)
     uint32_t *MSG = nullptr;                            // project-first layers with packed messages: 32 words per vertex

@@ -1,6 +1,7 @@
 // The walk along a list's in-edges that the pull kernels share: scatter.hip (hops and bootstrap), attention.hip.
 #pragma once
 #include "common.h"
+#include <algorithm>
 
 #define PULL_CHUNK 256
 #define PULL_RUN 8                      // chunks a wavefront takes at a time on a large hop
@@ -132,3 +133,46 @@ struct PullScan {
         bnd = bnd_n;
     }
 };
+
+// Runs of chunks as the kernels cut them that have one sum per destination to make (k_pull_all, k_gat_edges): chunks per run
+__host__ __device__ __forceinline__ uint32_t rp_chunks_per_run(uint32_t n_chunks, uint32_t nw) {
+    const uint32_t p = n_chunks / (2u * nw);
+    return p < 1u ? 1u : (p > PULL_RUN ? PULL_RUN : p);
+}
+// ... and the most runs that in-rows of up to `entries` entries can give: 4 nw + 1 while runs are shorter than PULL_RUN chunks
+static inline size_t rp_max_runs(uint64_t entries, uint32_t nw) {
+    return (size_t)std::min<uint64_t>(entries / PULL_CHUNK + 2, std::max<uint64_t>(4ull * nw + 1, entries / (PULL_CHUNK * PULL_RUN) + 2));
+}
+#ifdef __HIPCC__
+// A destination whose in-edges lie in several runs is summed in run order: every run leaves its share in one of its two rows of
+// `part` (the first for a destination that began in an earlier run, the second for one that begins here and goes on), and says in
+// `cut` which destination goes on and up to which run; a wavefront per run then adds the parts up. Atomics in their place would make
+// the sum depend on which run came first, from one bootstrap to the next.
+struct CutRows {
+    uint2 *cut;                    // per run: the destination (or 0xFFFFFFFF), the run of its last in-edge
+    float *part;                   // per run: two rows
+};
+// in an array of 2 runs (1 + row) numbers
+static inline CutRows rp_cut_rows(float *p, size_t runs) { return {(uint2 *)p, p + 2 * runs}; }
+// Row 2 r + 1 of `part` plus rows 2 (r + 1), ... 2 r_last, for PARTS_B blocks of 64 columns from `col` on (the caller's lane): eight
+// rows of all blocks are on their way at a time.
+#define PARTS_B 4
+__device__ __forceinline__ void rp_sum_parts(const float *part, uint32_t ld, uint32_t r, uint32_t r_last, uint32_t col, float (&t)[PARTS_B]) {
+    constexpr int G = 8;
+#pragma unroll
+    for (int b = 0; b < PARTS_B; ++b) t[b] = part[(size_t)(2u * r + 1u) * ld + min(col + 64u * b, ld - 1u)];
+    for (uint32_t f = r + 1u; f <= r_last; f += G) {
+        float p[G][PARTS_B];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (f + (uint32_t)g <= r_last)
+#pragma unroll
+                for (int b = 0; b < PARTS_B; ++b) p[g][b] = part[(size_t)(2u * (f + (uint32_t)g)) * ld + min(col + 64u * b, ld - 1u)];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            if (f + (uint32_t)g <= r_last)
+#pragma unroll
+                for (int b = 0; b < PARTS_B; ++b) t[b] += p[g][b];
+    }
+}
+#endif

@@ -1515,10 +1515,12 @@ void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr
 // Bound by the gather of one row per in-edge. In-degrees are skewed (24 K entries in the longest in-row of a graph of
 // 31 M edges), so the cut is over edges and not over rows: the flattened in-edge space of all live vertices is cut into
 // runs of PULL_CHUNK-edge chunks, G rows are in flight per wavefront, and a destination whose in-edges all lie in one run is
-// stored plainly. Only the destinations that a run boundary cuts are combined with atomics, onto the start value that
-// k_pull_all_init puts there (together with the zeros of vertices without in-edges). One wavefront per row, one row in
-// flight, is what this replaces: 34.0 / 15.6 / 8.3 ms for rows of 256 / 100 / 47 floats over 31 M edges, most of it
-// spent waiting for the few wavefronts with the longest rows.
+// stored plainly. Sums of destinations that a run boundary cuts are left in parts and added up in run order by
+// k_pull_all_close: a bootstrap of the same graph gives the same bits every time. Extremes do not depend on an order and are
+// combined with atomics, onto the start value that k_pull_all_init puts there (together with the zeros of vertices without
+// in-edges). One wavefront per row, one row in flight, is what this replaces: 34.0 / 15.6 / 8.3 ms for rows of 256 / 100 / 47
+// floats over 31 M edges, most of it spent waiting for the few wavefronts with the longest rows; now 4.3 / 2.0 / 1.25 ms (7.4, 6.2
+// and 4.7 TB/s of rows), 4.7 / 2.2 / 1.3 while sums and extremes were told apart in the inner loop.
 // The same cut serves the hops of max / min layers whose candidates are all recomputed (mono_direct): a candidate's new
 // aggregate is compared with the old one when it is complete, stored if it differs and taken out of the hop's set if not;
 // what a run boundary cuts is put together in XN and finished by k_mono_close.
@@ -1528,12 +1530,10 @@ struct PullAllArgs {
     int op;
     uint32_t n_cap;
     float *XN;                     // candidates: rows that a run boundary cuts [vertex x d]
+    CutRows c;                     // sums: rows that a run boundary cuts
     uint32_t n_waves;              // wavefronts of the k_pull_all launch
 };
 
-__device__ __forceinline__ uint32_t pull_all_per(uint32_t n_chunks, uint32_t nw) {
-    return max(1u, min((uint32_t)PULL_RUN, n_chunks / (2u * nw)));
-}
 __device__ __forceinline__ float pull_all_start(int op) { return op == 0 ? 0.0f : (op == 1 ? -INFINITY : INFINITY); }
 
 // HOP: candidates of a max / min hop
@@ -1543,7 +1543,7 @@ __global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     const uint32_t total = count ? a.p.ioff[count] : 0u;
-    const uint32_t span = pull_all_per((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;  // edges per run
+    const uint32_t span = rp_chunks_per_run((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;  // edges per run
     for (uint32_t base = gw * 64u; !HOP && base < a.n_cap; base += nw * 64u) {   // no in-edges (or not alive): zero
         const uint32_t v = base + (uint32_t)lane;
         unsigned long long m = __ballot(v < a.n_cap && a.p.in_meta[v].y == 0u);
@@ -1553,7 +1553,7 @@ __global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a) {
             for (uint32_t col = lane; col < d; col += 64u) a.p.X[(size_t)w * d + col] = 0.0f;
         }
     }
-    for (uint32_t base = gw * 64u; base < count; base += nw * 64u) {        // cut by a run boundary: the start value
+    for (uint32_t base = gw * 64u; a.op != 0 && base < count; base += nw * 64u) {   // extremes cut by a run boundary: the start value
         const uint32_t i = base + (uint32_t)lane;
         bool cut = false;
         uint32_t v = 0;
@@ -1581,8 +1581,10 @@ __device__ __forceinline__ void rp_atomic_extreme(float *p, float x, bool is_max
     else (void)(is_max ? atomicMin((unsigned int *)p, (unsigned int)i) : atomicMax((unsigned int *)p, (unsigned int)i));
 }
 
-template <int NJ, int STORE, int WT, int HOP>
+// MODE 0: sums; 1: extremes (max / min) of the bootstrap; 2: extremes of a hop's candidates
+template <int NJ, int STORE, int WT, int MODE>
 __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
+    constexpr bool SUM = MODE == 0, HOP = MODE == 2;
     constexpr int G = (NJ >= 8) ? 2 : 16 / NJ;              // rows per round trip
     constexpr int T = PULL_CHUNK / 64;
     constexpr uint32_t NONE = 0xFFFFFFFFu;
@@ -1593,8 +1595,8 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
     const uint32_t total = a.p.ioff[count];
     const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t per = pull_all_per(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
-    const float start = pull_all_start(a.op);
+    const uint32_t per = rp_chunks_per_run(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
+    const float start = SUM ? 0.0f : pull_all_start(a.op);
     for (uint32_t run = gw; run < n_runs; run += nw) {
         const uint32_t c_begin = run * per, c_end = min(n_chunks, c_begin + per);
         PullScan<T, WT, 1> scan;
@@ -1605,14 +1607,18 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
         const uint32_t i_last = rp_seg_search_wave(a.p.ioff, 0, count - 1, e_end - 1u);
         const uint32_t v_last = a.p.list[i_last];
         const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK;
-        const bool cut_last = a.p.ioff[i_last + 1u] > e_end;
+        const uint32_t e_last = a.p.ioff[i_last + 1u];
+        const bool cut_last = e_last > e_end;
+        if (SUM && lane == 0)
+            a.c.cut[run] = make_uint2(cut_last && !(v_last == v_first && cut_first) ? v_last : NONE, (e_last - 1u) / (per * PULL_CHUNK));
         uint32_t cur = NONE;
         float acc[NJ], xo[HOP ? NJ : 1];                     // HOP: the destination's old aggregate, requested with its first edge
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[j] = start;
         auto flush = [&]() {
-            const bool cut = (cur == v_first && cut_first) || (cur == v_last && cut_last);
+            const bool began_before = cur == v_first && cut_first, cut = began_before || (cur == v_last && cut_last);
             float *xr = ((HOP && cut) ? a.XN : a.p.X) + (size_t)cur * d;
+            if (SUM && cut) xr = a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * d;
             if constexpr (HOP) {
                 if (!cut) {
                     mono_finish<NJ>(h, cur, rp_bit(h.bm_vadd, cur), xo, acc);
@@ -1625,8 +1631,7 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
             for (int j = 0; j < NJ; ++j) {
                 const uint32_t col = lane + 64 * j;
                 if (col < d) {
-                    if (!cut) xr[col] = acc[j];
-                    else if (a.op == 0) unsafeAtomicAdd(&xr[col], acc[j]);
+                    if (SUM || !cut) xr[col] = acc[j];
                     else rp_atomic_extreme(&xr[col], acc[j], a.op == 1);
                 }
                 acc[j] = start;
@@ -1667,7 +1672,7 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
                             const float wk = WT ? __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(my_w[WT ? t : 0]), k0 + g)) : 1.0f;
 #pragma unroll
                             for (int j = 0; j < NJ; ++j) {
-                                if (a.op == 0) acc[j] = WT ? __builtin_fmaf(wk, r[g][j], acc[j]) : acc[j] + r[g][j];
+                                if (SUM) acc[j] = WT ? __builtin_fmaf(wk, r[g][j], acc[j]) : acc[j] + r[g][j];
                                 else acc[j] = a.op == 1 ? fmaxf(acc[j], r[g][j]) : fminf(acc[j], r[g][j]);
                             }
                         }
@@ -1680,6 +1685,27 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
     }
 }
 
+// Sums of destinations that a run boundary cuts, a wavefront per run: paced by three dependent reads and by the longest row's parts
+// (31 M edges, 17 K runs: 11 / 13 / 10 us for rows of 100 / 256 / 47; 26 for 256 with one block of 64 columns after the other).
+__global__ __launch_bounds__(256) void k_pull_all_close(PullAllArgs a) {
+    const int lane = rp_lane();
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t count = *a.p.count_ptr, d = a.p.d;
+    if (count == 0) return;
+    const uint32_t total = a.p.ioff[count], n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
+    const uint32_t per = rp_chunks_per_run(n_chunks, a.n_waves), n_runs = (n_chunks + per - 1) / per;
+    for (uint32_t r = gw; r < n_runs; r += nw) {
+        const uint2 c = a.c.cut[r];
+        for (uint32_t c0 = lane; c.x != 0xFFFFFFFFu && c0 < d; c0 += 64u * PARTS_B) {
+            float t[PARTS_B];
+            rp_sum_parts(a.c.part, d, r, c.y, c0, t);
+#pragma unroll
+            for (int b = 0; b < PARTS_B; ++b)
+                if (c0 + 64u * b < d) a.p.X[(size_t)c.x * d + c0 + 64u * b] = t[b];
+        }
+    }
+}
+
 // Candidates without in-edges or cut by a run boundary: finished here, a wavefront each.
 template <int NJ>
 __global__ __launch_bounds__(256) void k_mono_close(PullAllArgs a, MonoArgs h) {
@@ -1687,7 +1713,7 @@ __global__ __launch_bounds__(256) void k_mono_close(PullAllArgs a, MonoArgs h) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     const uint32_t total = count ? a.p.ioff[count] : 0u;
-    const uint32_t span = pull_all_per((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;
+    const uint32_t span = rp_chunks_per_run((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;
     if (gw == 0 && lane == 0) h.ctr->mono[2][h.l] = count;               // all of them are recomputed
     for (uint32_t base = gw * 64u; base < count; base += nw * 64u) {
         const uint32_t i = base + (uint32_t)lane;
@@ -1739,14 +1765,17 @@ static PullAllArgs pull_all_args(ripple_ctx *c, uint32_t l) {
 // for project-first layers). The live vertices and their in-degree prefix are in c->all_list and c->ioff_all.
 void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
     const int store = c->layers[l - 1].proj ? 0 : c->store;
-    const PullAllArgs a = pull_all_args(c, l);
+    PullAllArgs a = pull_all_args(c, l);
+    a.c = rp_cut_rows(c->D[l & 1], c->max_runs);         // (no rows of changes during the bootstrap; load_model has made it large enough)
     const MonoArgs none = {};
     const dim3 grid(c->n_cu * 8), block(256);
     hipLaunchKernelGGL(k_pull_all_init<0>, grid, block, 0, c->stream, a);
 #define PULL_CASE_W(NJ, STORE, WT) hipLaunchKernelGGL((k_pull_all<NJ, STORE, WT, 0>), grid, block, 0, c->stream, a, none)
 #define PULL_CASE(NJ)                                  \
     do {                                               \
-        if (store && a.p.in_w) PULL_CASE_W(NJ, 1, 1);  \
+        if (a.op != 0 && store) hipLaunchKernelGGL((k_pull_all<NJ, 1, 0, 1>), grid, block, 0, c->stream, a, none); \
+        else if (a.op != 0) hipLaunchKernelGGL((k_pull_all<NJ, 0, 0, 1>), grid, block, 0, c->stream, a, none);     \
+        else if (store && a.p.in_w) PULL_CASE_W(NJ, 1, 1);  \
         else if (store) PULL_CASE_W(NJ, 1, 0);         \
         else if (a.p.in_w) PULL_CASE_W(NJ, 0, 1);      \
         else PULL_CASE_W(NJ, 0, 0);                    \
@@ -1758,6 +1787,7 @@ void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
     else PULL_CASE(16);
 #undef PULL_CASE
 #undef PULL_CASE_W
+    if (a.op == 0) hipLaunchKernelGGL(k_pull_all_close, dim3(c->n_cu * 16), block, 0, c->stream, a);
 }
 
 // All candidates of a max / min hop (in c->all_list with their in-degree prefix in c->ioff_all) recomputed; h: what mono_finish
@@ -1769,8 +1799,8 @@ static void launch_mono_direct(ripple_ctx *c, uint32_t l, const MonoArgs &h) {
     hipLaunchKernelGGL(k_pull_all_init<1>, dim3(c->n_cu * 2), block, 0, c->stream, a);
 #define PULL_CASE(NJ)                                                                                                    \
     do {                                                                                                                 \
-        if (c->store) hipLaunchKernelGGL((k_pull_all<NJ, 1, 0, 1>), grid, block, 0, c->stream, a, h);                    \
-        else hipLaunchKernelGGL((k_pull_all<NJ, 0, 0, 1>), grid, block, 0, c->stream, a, h);                             \
+        if (c->store) hipLaunchKernelGGL((k_pull_all<NJ, 1, 0, 2>), grid, block, 0, c->stream, a, h);                    \
+        else hipLaunchKernelGGL((k_pull_all<NJ, 0, 0, 2>), grid, block, 0, c->stream, a, h);                             \
         hipLaunchKernelGGL(k_mono_close<NJ>, dim3(c->n_cu * 4), block, 0, c->stream, a, h);                              \
     } while (0)
     if (a.p.d <= 64) PULL_CASE(1);

@@ -184,3 +184,22 @@ def test_long_rows_of_changes_are_put_in_order(dels, adds):
         assert len(row) == k - dels + adds and np.array_equal(row[k - dels:], np.sort(new))
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("kind,widths", [("gcn_sum", (70, 9)), ("sage_mean", (12, 300, 24)), ("gcn_wsum", (20, 6)), ("gat", (12, 20, 130)), ("gat", (9, 47))])
+def test_a_bootstrap_gives_the_same_bits_again(kind, widths):
+    """Destinations whose in-edges lie in several runs of chunks (hubs of up to 9,000) are summed in run order."""
+    print("case same bits", kind, widths, flush=True)
+    pair, _ = make_pair(n=12000, e=150000, d0=widths[0], kind=kind, widths=widths, seed=81, top_share=0.06, weighted=kind == "gcn_wsum")
+    try:
+        pair.check_embeddings()
+        pair.check_aggregates()
+        rows = lambda: [pair.gpu_layer(l) for l in range(1, pair.L + 1)] + [  # noqa: E731
+            rp.ripple_get_aggregates(pair.ctx, l, rp.ripple_get_layer_info(pair.ctx, l)[0], n_rows=pair.cap) for l in range(1, pair.L + 1)]
+        first = rows()
+        for again in range(6):
+            rp.ripple_full_infer(pair.ctx)
+            for a, b in zip(first, rows()):
+                assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+    finally:
+        pair.close()
