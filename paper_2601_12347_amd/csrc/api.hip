@@ -292,12 +292,13 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     {   // pinned memory, in one allocation (200 to 300 us each, whatever the size): counters, the flag, read-back, and the staging of
         // ordinary batches
         const size_t ctr_at = 0, flag_at = (sizeof(DevCtr) + 63) & ~(size_t)63, io_at = flag_at + 64;
-        const size_t ops_at = io_at + (16 + IO_PIN_IDS + IO_PIN_FLOATS) * 4, rows_at = ops_at + PIN_OPS * sizeof(ripple_update);
+        const size_t made_at = io_at + (16 + IO_PIN_IDS + IO_PIN_FLOATS) * 4, ops_at = made_at + SMALL_OPS * 4, rows_at = ops_at + PIN_OPS * sizeof(ripple_update);
         c->pin_bytes = rows_at + (size_t)PIN_ROWS * d0 * 4;
         RP_HIP(c, hipHostMalloc((void **)&c->pin_block, c->pin_bytes, hipHostMallocDefault));
         c->ctr_host = (DevCtr *)(c->pin_block + ctr_at);
         c->pub_flag = (uint32_t *)(c->pin_block + flag_at);
         c->io_pin = (uint32_t *)(c->pin_block + io_at);
+        c->made_pin = (uint32_t *)(c->pin_block + made_at);
         c->ops_pin = (ripple_update *)(c->pin_block + ops_at);
         c->payload_pin = (float *)(c->pin_block + rows_at);
         c->pin_ops_cap = PIN_OPS;

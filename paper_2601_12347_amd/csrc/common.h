@@ -107,6 +107,10 @@ struct LayerDev {
     uint32_t Wns_ld;                          // row stride of the Wn planes (those of W0: K0pad, of W1: K1pad)
 };
 
+// pieces of up to SMALL_OPS operations without vertex deletions: the Apply step in three launches (k_small_validate)
+#define SMALL_WGS 128u
+#define SMALL_OPS (4u * SMALL_WGS)
+
 struct PhaseTimer;
 
 struct ripple_ctx {
@@ -198,7 +202,8 @@ struct ripple_ctx {
     ripple_update *ops_pin = nullptr;                   // pinned staging for ops
     float *payload_pin = nullptr;
     uint32_t pin_ops_cap = 0;
-    uint8_t *pin_block = nullptr;                       // pinned: ctr_host, pub_flag, io_pin and the first ops_pin / payload_pin
+    uint32_t *made_pin = nullptr;                       // pinned: the vertices a small piece creates (SMALL_OPS entries)
+    uint8_t *pin_block = nullptr;                       // pinned: ctr_host, pub_flag, io_pin, made_pin and the first ops_pin / payload_pin
     size_t pin_bytes = 0;
     // device arrays that share an allocation: the graph store's (but the pools), bitmaps and lists, batch scratch, messages as pairs, row segments
     uint8_t *graph_block = nullptr, *list_block = nullptr, *batch_block = nullptr, *pair_block = nullptr, *seg_block = nullptr;

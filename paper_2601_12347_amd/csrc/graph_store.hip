@@ -305,6 +305,8 @@ ripple_status rp_compact(ripple_ctx *c) {
 struct MutArgs {
     const ripple_update *ops;
     uint32_t n_ops;
+    const uint32_t *made;                        // small pieces: the vertices that the piece creates (pinned host memory)
+    uint32_t n_made;
     const float *payload;
     uint32_t *status, *pos_out, *pos_in;
     uint32_t *rank_out, *rank_in;                // an edge operation's number among the row's additions or deletions
@@ -437,9 +439,9 @@ __device__ __forceinline__ uint32_t count_edge(const MutArgs &a, const ripple_up
 // One operation, by W wavefronts that search its rows together (W = 1: one wavefront that shares nothing with the others of its
 // workgroup). Thousands of wavefronts bumping the same few counters would queue up behind one another: only the rows' own bits
 // and counts are set here, measure() makes the lists.
-// SMALL: vertex operations are judged here too, and a vertex that is not alive may have been created by this piece (ops)
+// SMALL: vertex operations are judged here too, and a vertex that is not alive may be one that this piece creates (a.made)
 template <int W, int SMALL>
-__device__ __forceinline__ void validate_op(const MutArgs &a, const ripple_update *ops, uint32_t i, const ripple_update &op, int *s_pos) {
+__device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const ripple_update &op, int *s_pos) {
     const int lane = rp_lane();
     const uint32_t wave = W == 1 ? 0u : threadIdx.x >> 6;
     const bool first = W == 1 ? lane == 0 : threadIdx.x == 0;
@@ -465,7 +467,7 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, const ripple_updat
             if (!SMALL) {
                 created = is_edge && (a.vstate[w] & VS_ADDING);
             } else if (is_edge) {
-                for (uint32_t k = lane; k < a.n_ops; k += 64u) created |= ops[k].kind == RIPPLE_VERTEX_ADD && ops[k].u == w;
+                for (uint32_t k = lane; k < a.n_made; k += 64u) created |= a.made[k] == w;
                 created = __ballot(created) != 0ull;
             }
             ok = ok && created;
@@ -557,7 +559,7 @@ __global__ __launch_bounds__(256) void k_validate(MutArgs a, uint32_t nb) {
         return;
     }
     for (uint32_t i = W == 1 ? blockIdx.x * 4u + wave : blockIdx.x; i < a.n_ops; i += W == 1 ? nb * 4u : nb)
-        validate_op<W, 0>(a, a.ops, i, a.ops[i], s_pos);
+        validate_op<W, 0>(a, i, a.ops[i], s_pos);
 }
 
 // where a deleted vertex's edges are in the rows of the vertices that stay
@@ -685,8 +687,6 @@ __global__ __launch_bounds__(256) void k_measure(MutArgs a) {
 // workgroups judge the operations, which they read from pinned host memory; the others clear the bitmaps. The last of the former
 // makes the lists of touched rows, measures them and decides. Every workgroup that arrives there costs about 60 ns, one after the
 // other, so they are at most SMALL_WGS: a workgroup per operation (W = 4) up to that number, a wavefront per operation (W = 1) above.
-#define SMALL_WGS 128u
-#define SMALL_OPS (4u * SMALL_WGS)
 template <int W>
 __global__ __launch_bounds__(256) void k_small_validate(MutArgs a, const ripple_update *src, ripple_update *dst, uint32_t nb,
                                                         uint32_t *bitmaps, uint32_t n_bitmap_words) {
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(256) void k_small_validate(MutArgs a, const ripple_
     for (uint32_t i = W == 1 ? blockIdx.x * 4u + (tid >> 6) : blockIdx.x; i < a.n_ops; i += W == 1 ? nb * 4u : nb) {
         const ripple_update op = src[i];
         if (W == 1 ? (tid & 63u) == 0 : tid == 0) dst[i] = op;
-        validate_op<W, 1>(a, src, i, op, s_pos);
+        validate_op<W, 1>(a, i, op, s_pos);
     }
     if (!last_workgroup(a.ctr, nb)) return;
     for (uint32_t start = 0; start < a.n_ops; start += 256u) measure<0>(a, dst, start + tid, 0u, 0u);
@@ -1261,6 +1261,8 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     MutArgs a;
     a.ops = c->ops_d;
     a.n_ops = n_ops;
+    a.made = c->made_pin;
+    a.n_made = 0;
     a.payload = c->payload;
     a.status = c->op_status;
     a.hole_out = c->hole_out;
@@ -1349,6 +1351,10 @@ void rp_launch_mutate(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, b
     const uint32_t words = c->n_words * (c->L + 3), big = c->n_cu * 8, tb = rp_div_up(n_ops, 256);
     const bool small = n_ops <= SMALL_OPS && !has_vertex_del;
     if (small) {
+        // Every wavefront with an endpoint that is not alive reads the created vertices over the bus: a list of their own, not all
+        // operations (50 vertices with 8 edges each: a batch of 173 us -> 164)
+        for (uint32_t i = 0; has_vertex_or_feat && i < n_ops; ++i)
+            if (src[i].kind == RIPPLE_VERTEX_ADD) c->made_pin[a.n_made++] = src[i].u;
         const bool wide = n_ops <= SMALL_WGS;
         const uint32_t nb = wide ? n_ops : rp_div_up(n_ops, 4);
         const dim3 grid(nb + std::min<uint32_t>(rp_div_up(words, 1024), c->n_cu * 2));

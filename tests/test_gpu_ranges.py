@@ -203,3 +203,29 @@ def test_a_bootstrap_gives_the_same_bits_again(kind, widths):
                 assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("made", [1, 3, 40, 70])
+def test_edges_of_vertices_that_a_small_piece_creates(made):
+    """Pieces of 9 to 492 operations: edges between a created vertex and a live one, between two created ones, and to a vertex that is
+    not alive and stays so (rejected); one creation of a live vertex (rejected)."""
+    print("case created endpoints", made, flush=True)
+    pair, _ = make_pair(n=900, e=4000, d0=6, kind="sage_mean", widths=(6, 10, 5), seed=91, slack=200)
+    rng = np.random.default_rng(92 + made)
+    try:
+        for turn in range(2):
+            first = 900 + 75 * turn
+            ops = [(ri.OP_VERTEX_ADD, first + i, 0, i) for i in range(made)] + [(ri.OP_VERTEX_ADD, 7, 0, 0)]
+            for i in range(made):
+                w = first + i
+                ops += [(ri.OP_EDGE_ADD, w, int(x), 0) for x in rng.choice(900, 2, replace=False)] + [(ri.OP_EDGE_ADD, int(x), w, 0) for x in rng.choice(900, 2, replace=False)]
+                ops += [(ri.OP_EDGE_ADD, w, first + (i + 1) % made, 0)] if made > 1 else []
+                ops += [(ri.OP_EDGE_ADD, w, 1095, 0)]
+            ops = np.array(ops, dtype=np.uint32)
+            assert len(ops) <= 512
+            res, rec, _ = pair.step(ops, rng.standard_normal((made, 6)).astype(np.float32))
+            assert res.n_sub_batches == 1 and res.n_rejected == made + 1
+        pair.check_graph()
+        pair.check_aggregates()
+    finally:
+        pair.close()
