@@ -74,7 +74,7 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
 //     destination once. Only the destinations of a run's first and last in-edge can have in-edges in another run;
 //     their sums go to two side entries per run instead of memory, and k_pull_fixup adds the entries of one
 //     destination in run order. All other rows are written with plain loads and stores by their only writer.
-// The changed edges' structural terms have been added before the first hop, in (sink, source) order (k_struct_ordered).
+// The changed edges' structural terms have been added before the first hop, in that order too (k_det_terms).
 // Bootstrap inference runs the same kernels with every destination marked as recomputed: every in-edge of such a
 // row contributes, with the source's current row (of H^{l-1}, or of T for a project-first layer) in place of a
 // message, and the sum replaces the row. The hop is always pulled.

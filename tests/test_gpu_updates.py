@@ -654,8 +654,8 @@ def _in_rows(ctx, cap, n_edges):
 def test_deterministic_mode_keeps_in_rows_in_a_reproducible_order():
     """The deterministic mode adds a row's sources in the order the in-row stores them, so that order has to
     be a function of the input and the batches: rows are built in the order the edges were given, and
-    what a batch appends to a row ends up in ascending id order, whether it is a handful of entries (ranked by
-    a wavefront), more than 64 (copied aside by a workgroup) or more than 4,096 (several LDS tiles). Deletions
+    what a batch appends to a row ends up in ascending id order, whether it is a handful of entries, some hundred (both
+    ranked in LDS) or more than 1,024 (tiles that are merged). Deletions
     in the same rows and a second context fed the same batches are checked as well."""
     print("case deterministic row order", flush=True)
     kw = dict(n=9000, e=60000, d0=16, kind="sage_mean", widths=(16, 40, 10), seed=91, slack=64, deterministic=True)
