@@ -548,7 +548,9 @@ __device__ __forceinline__ void list_expanded(const MutArgs &a, uint32_t gw, uin
 }
 
 // The first nb workgroups judge operations, the others list the edges of deleted vertices. A workgroup per operation (W = 4) while
-// all of them are resident at once, a wavefront per operation above that: 10,000 operations take 86 and 52 us, 1,000 take 14 and 15.
+// all of them are resident at once, a wavefront per operation above that. Averages of 40 to 60 launches, W = 4 and 1: 1,000
+// operations on 1.2 M edges 10.0 and 11.1 us (single launches differ by 2.5), 1,777 on 31 M edges 16.2 and 21.4 (0.7), 10,000 on
+// 124 M edges 53.6 and 34.7 (0.4).
 #define WORKGROUP_OPS 2048u
 template <int W>
 __global__ __launch_bounds__(256) void k_validate(MutArgs a, uint32_t nb) {
