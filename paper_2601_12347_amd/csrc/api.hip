@@ -257,6 +257,7 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     c->stream = (hipStream_t)hip_stream;
     RP_HIP(c, hipGetDevice(&c->device));
     RP_TRY(rp_static_scratch_init(c));
+    RP_HIP(c, hipEventCreateWithFlags(&c->idle, hipEventDisableTiming));
     int cu = 0;
     RP_HIP(c, hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, c->device));
     c->n_cu = cu > 0 ? (uint32_t)cu : 256u;
@@ -383,6 +384,7 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
     if (c->ops_pin && !in_pin_block(c, c->ops_pin)) hipHostFree(c->ops_pin);
     if (c->payload_pin && !in_pin_block(c, c->payload_pin)) hipHostFree(c->payload_pin);
     if (c->pin_block) hipHostFree(c->pin_block);
+    if (c->idle) hipEventDestroy(c->idle);
     if (c->timer) {
         for (hipEvent_t e : c->timer->ev) hipEventDestroy(e);
         delete c->timer;

@@ -198,6 +198,7 @@ struct ripple_ctx {
     DevCtr *ctr_host = nullptr;                         // pinned mirror, written by k_publish
     uint32_t *pub_flag = nullptr;                       // pinned: number of the last k_publish that has finished
     uint32_t pub_seq = 0;
+    hipEvent_t idle = nullptr;                          // recorded behind the launches of a call that promises a synchronised stream
     bool ctr_dirty = false;                             // the per-batch counters are not zero (something ran after k_publish)
     ripple_update *ops_pin = nullptr;                   // pinned staging for ops
     float *payload_pin = nullptr;
@@ -486,7 +487,8 @@ __device__ __forceinline__ bool rp_hop_sorted(const DevCtr *ctr, uint32_t l, uin
 
 // position of `target` in row[0..len), searched by one wavefront; -1 when absent. Rows begin at multiples of four entries and
 // have room for a multiple of four, so every lane reads four at a time, and long (hub) rows are read eight such blocks per round:
-// a row of 24,000 entries takes 12 round trips (four bytes per lane and sixteen blocks took 24: 10,000 operations 80 us instead of 35).
+// a row of 24,000 entries takes 12 round trips (four bytes per lane and sixteen blocks took 24: 10,000 operations, a wavefront each, 80 us
+// instead of 35).
 template <int T>
 __device__ __forceinline__ int rp_wave_find_blocks(const uint32_t *row, uint32_t base, uint32_t len, uint32_t target) {
     const int lane = rp_lane();
