@@ -454,7 +454,7 @@ __global__ __launch_bounds__(TEAM * 64) void k_gat_scatter_seg(GatArgs a) {
 // other. The list is then summed like a pull's messages, one row per entry. A vertex whose in-edges lie in one run is
 // written by that run alone; what a run boundary cuts is left in parts, which k_gat_close adds up in run order (see
 // rp_sum_parts). Changed edges of a vertex that keeps its long row are added before (k_gat_edge_terms). A patched
-// denominator that has cancelled (GAT_CANCEL) is found afterwards (k_gat_check) and its row recomputed by a workgroup.
+// denominator that has cancelled (GAT_CANCEL) is found there too and its row recomputed by a workgroup.
 struct GatEdgeArgs {
     PullArgs p;                    // list, count_ptr, ioff, in_meta, in_pool, bm_prev, d, X, ctr, l
     const uint32_t *bm_sink, *bm_vadd;
@@ -515,14 +515,6 @@ __global__ __launch_bounds__(256) void k_gat_edge_terms(GatEdgeArgs a) {
             unsafeAtomicAdd(&a.den[v], sgn * w);
             unsafeAtomicAdd(&a.mag[v], w);
         }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_gat_check(GatEdgeArgs a) {
-    const uint32_t count = *a.p.count_ptr;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
-        const uint32_t v = a.p.list[i];
-        if (!a.rec[v] && a.mag[v] > 0.0f && !(a.den[v] > GAT_CANCEL * a.mag[v])) a.queue[atomicAdd(a.queue_count, 1u)] = v;
     }
 }
 
@@ -734,19 +726,23 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
     }
 }
 
-// Vertices that a run boundary cuts, a wavefront per run (22 us for 256 columns and 12 K runs, 13 for 47 and 17 K)
+// Vertices that a run boundary cuts: their parts added up, a wavefront per run (22 us for 256 columns and 12 K runs, 13 for 47 and
+// 17 K). Then (hops) every patched denominator that has cancelled is queued: of the cut vertices by the wavefront that has just
+// finished it, of the others, which this launch does not write, by a thread each.
 __global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
     const int lane = rp_lane();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     if (count == 0) return;
     const uint32_t total = a.p.ioff[count], n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
-    const uint32_t per = rp_chunks_per_run(n_chunks, a.n_waves), n_runs = (n_chunks + per - 1) / per;
+    const uint32_t per = rp_chunks_per_run(n_chunks, a.n_waves), n_runs = (n_chunks + per - 1) / per, span = per * PULL_CHUNK;
+    auto cancelled = [](float den, float mag) { return mag > 0.0f && !(den > GAT_CANCEL * mag); };
     for (uint32_t r = gw; r < n_runs; r += nw) {
         const uint2 c = a.c.cut[r];
         if (c.x == 0xFFFFFFFFu) continue;
         const uint32_t v = c.x;
         const bool rec = a.rec[v] != 0;
+        float den = 0.0f, mag = 0.0f;                       // in the lanes of columns d and d + 1
         for (uint32_t c0 = lane; c0 < d + 2u; c0 += 64u * PARTS_B) {
             float old[PARTS_B], t[PARTS_B];
             float *to[PARTS_B];
@@ -760,9 +756,20 @@ __global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
 #pragma unroll
             for (int b = 0; b < PARTS_B; ++b) {
                 const uint32_t col = c0 + 64u * b;
-                if (col <= d || (!rec && col == d + 1u)) *to[b] = old[b] + t[b];
+                const float x = old[b] + t[b];
+                if (col <= d) *to[b] = x;                   // (mag is looked at here only)
+                if (col == d) den = x;
+                if (col == d + 1u) mag = x;
             }
         }
+        den = __shfl(den, (int)(d & 63u));
+        mag = __shfl(mag, (int)((d + 1u) & 63u));
+        if (lane == 0 && !a.all && !rec && cancelled(den, mag)) a.queue[atomicAdd(a.queue_count, 1u)] = v;
+    }
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; !a.all && i < count; i += gridDim.x * blockDim.x) {
+        const uint32_t v = a.p.list[i], e0 = a.p.ioff[i], e1 = a.p.ioff[i + 1u];
+        if (a.rec[v] || (e1 > e0 && e0 / span != (e1 - 1u) / span)) continue;
+        if (cancelled(a.den[v], a.mag[v])) a.queue[atomicAdd(a.queue_count, 1u)] = v;
     }
 }
 
@@ -869,7 +876,6 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool liste
         hipLaunchKernelGGL((k_gat_edges<NJ, QUAD>), grid, block, 0, c->stream, e);                                            \
         hipLaunchKernelGGL(k_gat_close, dim3(c->n_cu * 16), block, 0, c->stream, e);                                                     \
         if (bootstrap) break;                                                                                                 \
-        hipLaunchKernelGGL(k_gat_check, dim3(c->n_cu * 2), block, 0, c->stream, e);                                           \
         hipLaunchKernelGGL((k_gat_scatter_long<NJ, TEAM>), dim3(c->n_cu), dim3(TEAM * 64), 0, c->stream, b);                  \
     } while (0)
     if (e.ldp > e.p.d) GAT_CASE(1, true, 16);
