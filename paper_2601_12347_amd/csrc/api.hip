@@ -179,20 +179,23 @@ static ripple_status dev_alloc(ripple_ctx *c, T **p, size_t count, bool zero) {
 // is a launch, so a context of a small graph spent most of its preparation and half of its first batch on them.
 struct Block {
     struct Part {
-        void **p;
+        void *p;                                             // where the array's address goes
         size_t at;
     } part[32];
     uint32_t n = 0;
     size_t bytes = 0;
     template <typename T>
     void add(T **p, size_t count) {
-        part[n++] = {(void **)p, bytes};
+        part[n++] = {p, bytes};
         bytes += (std::max<size_t>(count, 1) * sizeof(T) + ARRAY_PAD + 255) & ~(size_t)255;
     }
 };
 static ripple_status block_alloc(ripple_ctx *c, const Block &b, uint8_t **base, bool zero) {
     RP_TRY(dev_alloc(c, base, b.bytes, zero));
-    for (uint32_t i = 0; i < b.n; ++i) *b.part[i].p = *base + b.part[i].at;
+    for (uint32_t i = 0; i < b.n; ++i) {
+        void *at = *base + b.part[i].at;
+        memcpy(b.part[i].p, &at, sizeof(at));
+    }
     return RIPPLE_OK;
 }
 
