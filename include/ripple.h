@@ -198,7 +198,9 @@ typedef enum {
                                      the graph and the batches alone (no float atomics: in-rows keep a reproducible order,
                                      hops are gathered along them, rows that several wavefronts read are finished in
                                      wavefront order, changed edges are sorted), so that two runs over the same
-                                     operations on the same device model give the same bits. About 1.3x the time.
+                                     operations on the same device model give the same bits. About 1.5x the time
+                                     on a large graph. (Without it, two bootstraps of one stored graph do too, and max / min
+                                     rows; sums of messages agree up to rounding order.)
                                      Sum and mean layers only. */
 } ripple_option;
 
