@@ -185,10 +185,11 @@ typedef enum {
                                      8 bytes, so that a number is off by at most 2^-19 of the largest of its three. What the
                                      rounding takes from a message is carried into the sender's next one: the cached
                                      aggregates stay the exact sum of what was sent and nothing accumulates. */
-    RIPPLE_OPT_STREAM_TRANSFORM = 11, /* 0/1/2 (default 1): large row updates of 256 -> 256 layers (fp32 rows) run in persistent
-                                     workgroups that write a finished tile while the next one is being multiplied; 0 keeps
-                                     the one-tile-per-workgroup kernel; 2 takes the streaming kernel whatever the number of
-                                     rows (for tests). Same arithmetic up to rounding order. */
+    RIPPLE_OPT_STREAM_TRANSFORM = 11, /* 0/1/2 (default 1): products of many rows (from 32,768 on; widths of up to 256) run in persistent
+                                     workgroups that write a finished tile while the next one is being multiplied, every
+                                     fp32 number as three bf16 parts on the bf16 matrix cores (closer to 64-bit sums than a
+                                     chain of fp32 products); 0 keeps the one-tile-per-workgroup kernels on the fp32 matrix
+                                     cores; 2 takes the streaming kernel whatever the number of rows (for tests). */
     RIPPLE_OPT_SORTED_MESSAGES = 12, /* 0/1/2 (default 1): a hop that would be pulled while few of the scanned in-row entries
                                       carry a message is scattered from the list of its messages instead, which the out-edge
                                       walk writes down and a radix sort orders by destination; 1 where the previous batch's

@@ -5,6 +5,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "pull_scan.h"
+#include "transform_args.h"
 
 #include <chrono>
 #include <cstring>
@@ -368,7 +369,7 @@ static bool in_pin_block(const ripple_ctx *c, const void *p) {
 extern "C" void ripple_destroy(ripple_ctx *c) {
     if (!c) return;
     hipStreamSynchronize(c->stream);
-    void *ptrs[] = {c->graph_block, c->list_block, c->batch_block, c->pair_block, c->out_pool, c->in_pool, c->in_w, c->D[0], c->D[1], c->tmp, c->PD,
+    void *ptrs[] = {c->graph_block, c->list_block, c->batch_block, c->pair_block, c->part_block, c->out_pool, c->in_pool, c->in_w, c->D[0], c->D[1], c->tmp, c->PD,
                     c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->gat_mag, c->gat_rec, c->seg_block, c->gather_d, c->gather_ids};
     for (void *p : ptrs)
         if (p) hipFree(p);
@@ -380,7 +381,7 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
         LayerDev &ly = c->layers[l];
         void *w[] = {ly.W0, ly.b0, ly.W1, ly.b1, ly.W0h, ly.W1h, ly.bzero, (ly.Wn != ly.W0) ? ly.Wn : nullptr, ly.PS,
                      ly.W0s, ly.W1s, (ly.Wns != ly.W0s) ? ly.Wns : nullptr,
-                     ly.att, ly.P, ly.ssrc, ly.sdst, ly.den, ly.T, ly.Wc, ly.bzero_c, ly.Wc96p, ly.W0q, (ly.Wnq != ly.W0q) ? ly.Wnq : nullptr, ly.W1q, ly.Wcq};
+                     ly.att, ly.P, ly.ssrc, ly.sdst, ly.den, ly.T, ly.Wc, ly.bzero_c, ly.W0q, (ly.Wnq != ly.W0q) ? ly.Wnq : nullptr, ly.W1q, ly.Wcq};
         for (void *p : w)
             if (p) hipFree(p);
     }
@@ -608,18 +609,6 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
             RP_HIP(c, hipMemcpy(ly.Wc, wc.data(), wc.size() * 4, hipMemcpyHostToDevice));
             RP_TRY(make_quads(c, ly.Wc, kp, 128, &ly.Wcq));
             RP_TRY(dev_alloc(c, &ly.bzero_c, (size_t)128, true));
-            if (s.d_in == 256 && s.d_out > 16 && s.d_out <= 48) {           // [k][n][j]: n < 16 column 16 j + n of W_self, else 16 j + n - 16 of W_neigh
-                std::vector<float> wp((size_t)256 * 96, 0.0f);
-                for (uint32_t k = 0; k < 256; ++k)
-                    for (uint32_t n = 0; n < 32; ++n)
-                        for (uint32_t j = 0; j < 3; ++j) {
-                            const uint32_t col = 16 * j + (n & 15u);
-                            if (col >= s.d_out) continue;
-                            wp[((size_t)k * 32 + n) * 3 + j] = s.W0[(size_t)((n < 16 ? 0 : s.d_in) + k) * s.d_out + col];
-                        }
-                RP_TRY(dev_alloc(c, &ly.Wc96p, wp.size(), false));
-                RP_HIP(c, hipMemcpy(ly.Wc96p, wp.data(), wp.size() * 4, hipMemcpyHostToDevice));
-            }
         }
         if (s.d_hidden) {
             ly.K1pad = rp_round_up(s.d_hidden, 32);
@@ -629,6 +618,31 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         c->d[l + 1] = s.d_out;
         c->dmax = std::max(c->dmax, s.d_out);
         c->hmax = std::max(c->hmax, s.d_hidden);
+    }
+    {   // the weights in parts (fp32 rows; bf16 rows: where the products stay on fp32 numbers)
+        Block b;
+        struct Part {
+            const float *w;
+            uint32_t K, Npad;
+            unsigned short **out;
+        };
+        std::vector<Part> parts;
+        auto add = [&](const float *w, uint32_t K, uint32_t Npad, unsigned short **out) {
+            if (!w || Npad > 256u || K > 256u) return;
+            b.add(out, rp_weight_parts_size(K, Npad));
+            parts.push_back({w, K, Npad, out});
+        };
+        for (uint32_t l = 0; l < n_layers; ++l) {
+            LayerDev &ly = c->layers[l];
+            add(ly.W0, ly.self_mode == RIPPLE_SELF_CONCAT ? ly.d_in : ly.K, ly.N0pad, &ly.W0p);
+            if (ly.Wn != ly.W0) add(ly.Wn, ly.d_in, ly.N0pad, &ly.Wnp);
+            add(ly.W1, ly.d_hidden, ly.N1pad, &ly.W1p);
+            add(ly.Wc, ly.d_in, 128u, &ly.Wcp);
+        }
+        if (b.n) RP_TRY(block_alloc(c, b, &c->part_block, false));
+        for (const Part &p : parts) rp_launch_weight_parts(c, p.w, p.K, p.Npad, *p.out);
+        for (uint32_t l = 0; l < n_layers; ++l)
+            if (c->layers[l].Wn == c->layers[l].W0) c->layers[l].Wnp = c->layers[l].W0p;
     }
     const size_t n = c->n_cap;
     for (uint32_t l = 1; l <= c->L; ++l) {

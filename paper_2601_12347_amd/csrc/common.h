@@ -94,8 +94,7 @@ struct LayerDev {
     float *PS;
     // project-first layers with a cached self term: [W_self | W_neigh] as one matrix [roundup(d_in,32) x 128] (W_neigh
     // from column 64 on) and 128 zeros, so that one pass over the rows of A_{l-1} yields both products; else null.
-    // Wc96p: the same for d_in = 256 and d_out <= 48 in 96 columns, permuted for k_project_both_stream, [256][32][3], else null
-    float *Wc, *bzero_c, *Wc96p;
+    float *Wc, *bzero_c;
     // attention layers: projected rows P[v] = H^{l-1}[v] W0 [n x d_out], scores a_src . P[v] and a_dst . P[v],
     // denominators of the softmax (the numerators are the layer's X rows); att = a_src then a_dst on the device
     float *att, *P, *ssrc, *sdst, *den;
@@ -104,6 +103,8 @@ struct LayerDev {
     unsigned short *W0s, *Wns, *W1s;
     // the padded matrices once more with k by fours, [Kpad / 4][Npad][4] (wave_gemm); Wnq may alias W0q
     float *W0q, *Wnq, *W1q, *Wcq;
+    // ... and as three bf16 parts each, in the order k_split_stream takes them (of W0 of a layer that concatenates: W_self); Wnp may alias W0p
+    unsigned short *W0p, *Wnp, *W1p, *Wcp;
     uint32_t Wns_ld;                          // row stride of the Wn planes (those of W0: K0pad, of W1: K1pad)
 };
 
@@ -206,8 +207,8 @@ struct ripple_ctx {
     uint32_t *made_pin = nullptr;                       // pinned: the vertices a small piece creates (SMALL_OPS entries)
     uint8_t *pin_block = nullptr;                       // pinned: ctr_host, pub_flag, io_pin, made_pin and the first ops_pin / payload_pin
     size_t pin_bytes = 0;
-    // device arrays that share an allocation: the graph store's (but the pools), bitmaps and lists, batch scratch, messages as pairs, row segments
-    uint8_t *graph_block = nullptr, *list_block = nullptr, *batch_block = nullptr, *pair_block = nullptr, *seg_block = nullptr;
+    // device arrays that share an allocation: the graph store's (but the pools), bitmaps and lists, batch scratch, messages as pairs, row segments, weights in parts
+    uint8_t *graph_block = nullptr, *list_block = nullptr, *batch_block = nullptr, *pair_block = nullptr, *seg_block = nullptr, *part_block = nullptr;
 
     // gather staging for get_* calls; pinned: 16 words (a count), then ids, then rows
     uint32_t *io_pin = nullptr;
@@ -241,7 +242,7 @@ struct ripple_ctx {
     int opt_project = 1;                        // allow project-first layers (read by load_model)
     int opt_selfcache = 1;                      // allow cached self projections (read by load_model)
     int opt_sparse = 1;                         // small frontiers are listed as they are marked (no bitmap scan)
-    int opt_stream = 1;                         // large 256 -> 256 row updates: persistent workgroups, tiles written while the next is multiplied (2: any size)
+    int opt_stream = 1;                         // products of many rows: persistent workgroups, tiles written while the next is multiplied (2: any size)
     int opt_split = 0;                          // fp32 storage: products on the bf16 matrix cores, operands split in three (read by load_model)
     int opt_deterministic = 0;                  // bit-reproducible aggregation (owner kernels, no float atomics)
     int opt_pull_ratio = 1;                     // pull when messages * width * ratio >= scanned in-edges

@@ -289,6 +289,8 @@ static TArgs base_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
     a.wt_ld = ly.K0pad;
     a.Ws = ly.W0s;                                 // fp32 storage with split products, else null
     a.ws_plane = (size_t)ly.N0pad * ly.K0pad;
+    a.Wp = ly.W0p;
+    a.wp_k = rp_round_up(ly.self_mode == RIPPLE_SELF_CONCAT ? ly.d_in : ly.K, 128);
     a.bias = ly.b0;
     a.K = ly.K;
     a.Kpad = ly.K0pad;
@@ -1140,6 +1142,8 @@ TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uin
     a.Ws = ly.Wns;
     a.wt_ld = ly.Wns_ld;
     a.ws_plane = (size_t)ly.N0pad * ly.Wns_ld;
+    a.Wp = ly.Wnp;
+    a.wp_k = rp_round_up(ly.d_in, 128);
     a.bias = ly.bzero;
     a.K = ly.d_in;
     a.Kpad = rp_round_up(ly.d_in, 32);
@@ -1169,6 +1173,8 @@ TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     a.Wq = ly.Wcq;
     a.Wt = nullptr;
     a.Ws = nullptr;
+    a.Wp = ly.Wcp;
+    a.wp_k = rp_round_up(ly.d_in, 128);
     a.bias = ly.bzero_c;
     a.K = ly.d_in;
     a.Kpad = rp_round_up(ly.d_in, 32);
@@ -1188,11 +1194,8 @@ TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
 }
 
 void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
-    const LayerDev &ly = c->layers[l - 1];
     TArgs a = rp_project_both_args(c, l, list, count_d, bootstrap);
-    const uint32_t hint = bootstrap ? c->n_cap : rp_rows_hint(c, l - 1);
-    if (rp_launch_project_both_stream(c, l, list, count_d, a.tmp_out2, a.tmp_out2_ld, hint)) return;
-    launch_t(c, a, hint);
+    launch_t(c, a, bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
 }
 
 // Attention layer l: P[v] = H^{l-1}[v] W0 for the listed vertices (fp32, no bias, no activation).
@@ -1275,6 +1278,8 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
         a.Ws = ly.Wns;
         a.wt_ld = ly.Wns_ld;
         a.ws_plane = (size_t)ly.N0pad * ly.Wns_ld;
+        a.Wp = ly.Wnp;
+        a.wp_k = rp_round_up(ly.d_in, 128);
         a.K = ly.d_in;
         a.Kpad = rp_round_up(ly.d_in, 32);
         a.addend = ly.PS;
@@ -1309,6 +1314,8 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     s2.Ws = ly.W1s;
     s2.wt_ld = ly.K1pad;
     s2.ws_plane = (size_t)ly.N1pad * ly.K1pad;
+    s2.Wp = ly.W1p;
+    s2.wp_k = rp_round_up(ly.d_hidden, 128);
     s2.bias = ly.b1;
     s2.K = ly.d_hidden;
     s2.Kpad = ly.K1pad;

@@ -24,6 +24,8 @@ struct TArgs {
     const unsigned short *Ws;      // fp32 storage: W as three transposed bf16 planes (W = plane 0 + plane 1 + plane 2), or null
     size_t ws_plane;               // elements per plane
     uint32_t wt_ld;                // its row stride
+    const unsigned short *Wp;      // W as three bf16 parts in the order the matrix cores take them (k_split_stream), or null
+    uint32_t wp_k;                 // its rows (a multiple of 128)
     uint32_t K, Kpad, N, Npad;
     int act;
     int out_mode;                  // 0 write act(z) to tmp_out[slot] | 1 update H, emit delta | 2 write to tmp_out[vertex]
@@ -50,9 +52,9 @@ struct TArgs {
 
 // transform_stream.hip: launches the streaming kernel if the arguments have its shape and enough rows are expected
 bool rp_launch_stream(ripple_ctx *c, const TArgs &a, uint32_t rows_hint);
-// the same for both products of a narrow project-first layer with a cached self term (second product into out2)
-bool rp_launch_project_both_stream(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, float *out2,
-                                   uint32_t ld2, uint32_t rows_hint);
+// a weight matrix [K x Npad] in that order: numbers it takes, and the launch that makes it
+size_t rp_weight_parts_size(uint32_t K, uint32_t Npad);
+void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t Npad, unsigned short *out);
 
 // transform.hip: the arguments of the products of a layer's previous embedding (see the launchers of the same names)
 TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap);

@@ -1,441 +1,447 @@
-#include "transform_args.h"
 #include "kernels.h"
+#include "transform_args.h"
 
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// Streaming variant of the row transform (the Compute step of Sec. 3.3 in re-apply form) for the shape that dominates
-// large batches: x W with K = N = 256 (x = X^l[v], divided by the in-degree for mean), fp32 rows, H updated in place
-// (ADD: plus an unscaled cached row; DELTA: the delta row is written too).
+// Row transform of many rows (the Compute step of Sec. 3.3 in re-apply form, and the products of the previous embedding that a
+// layer caches), fp32 numbers on the bf16 matrix cores.
 //
-// A workgroup of four wavefronts owns 64-row tiles; wavefront w owns 64 output columns, as two 32-column blocks of
-// interleaved columns (block j holds columns 64 w + 2 n + j), so that everything a lane reads or writes per row is
-// eight adjacent bytes. Workgroups are persistent and no part of a tile waits for memory on its own:
-//  * the weights never pass through LDS: a wavefront only needs its own 64 columns, so each lane loads the two
-//    numbers it feeds into the matrix cores for a pair of k straight from the (L2-resident) matrix, eight pairs
-//    (half a step) ahead, into the register an earlier pair has just freed;
-//  * the gathered rows pass through a double-buffered LDS slice (one barrier per step): slice s + 1 is written while
-//    slice s is multiplied, from registers requested two steps earlier, also across the tile boundary;
-//  * the finished tile's accumulators are parked in a second set of registers and leave for memory in eight chunks
-//    during the K steps of the next tile; the cached / old values a chunk is combined with are requested two steps
-//    before the chunk is finished (the first two chunks of a tile during its own last steps);
-//  * all of this is issued between the matrix-core operations of a step, where the wavefront has issue slots to spare;
-//  * the mean's 1/deg is applied to the finished row instead of the gathered one, so staging is a plain copy.
-// Every array is addressed through a buffer descriptor with 32-bit offsets (row id * 1 KB + constants): as flat
-// addresses the compiler keeps dozens of 64-bit pointers alive across the unrolled steps, which no register file holds.
-// The launch therefore requires vertex_capacity * 1 KB < 4 GB - 4 KB.
-template <bool ADD, bool DELTA>
-__global__ __launch_bounds__(256, 2) void k_transform_stream(TArgs a, uint32_t n_cap) {
-    constexpr int BM = 64, KS = 8, NA = 2, LEAD = 2, KP = T_BK / 2, WLEAD = 8;
-    __shared__ __attribute__((aligned(16))) float As[2][BM][T_BK + 1];
-    __shared__ uint32_t s_vtx[2][BM];
-    __shared__ float s_scale[2][BM];
+// A product of fp32 numbers: x = x0 + x1 + x2 and w = w0 + w1 + w2 with bf16 numbers, each the rounding of what the ones before it
+// leave (exact to 2^-26 of x), and x w is the six largest of the nine products; the three left out are below 2^-24 x w together.
+// x0 w0 and the five others go to two accumulators, so the small terms are not rounded to the large sum's last bit on the way.
+// Against 64-bit sums the rows are closer than a chain of fp32 products: 2-norm of the error over that of the result, K = 256,
+// normal / rectified rows: 8.5e-8 / 6.6e-8 (fp32 matrix cores 2.9e-7 / 2.0e-7; K = 32: 3.9e-8 against 1.0e-7; K = 96 and 128 in between).
+// What bounds it: six products of a bf16 rate of 1.7 to 2.1 PFLOP/s (dense matrix products of numbers that are not zero lower the clock;
+// 2.4 with zeros) and memory, about as much each; fp32 products reach 138 TFLOP/s, 3/8 of that in the end. Measured, fp32 products
+// (persistent workgroups for 256 -> 256, 32 x 128 tiles otherwise) -> now: 1.5 M rows 256 -> 256 with a cached row 1.66 -> 1.35 ms
+// (4.6 GB moved), 612 K rows 0.68 -> 0.53, without it 0.84 -> 0.46, 100 -> 256 0.49 -> 0.32 and 0.55 -> 0.38, both products of 256 -> 47
+// 1.5 M rows 0.73 -> 0.71 and 612 K 0.28 -> 0.27; 1.5 M bf16 rows 256 -> 47 0.53 -> 0.29. fp32 rows to at most 64 columns stay with the
+// tiles of fp32 products: 0.107 ms there, 0.139 here for 427 K rows 190 -> 23 (the tile of 256 rows leaves no registers).
+// Other shapes of the same kernel: two workgroups of four wavefronts without a parked tile 1.50 ms for the first of these, four
+// wavefronts that only fetch and eight that only multiply 1.6, products of 16 x 16 x 32 no difference.
+// Rows stored in bf16 are exact as they are: three products.
+// What a sum of finite products cannot show: infinities and NaNs of the rows or the weights, and numbers that bf16 rounds to
+// infinity, leave a sum that is not finite (x1 = x - x0 is a NaN then). Such an element is computed again from fp32 products, one
+// after the other.
+//
+// A workgroup of eight wavefronts per compute unit is persistent and owns tiles of BM rows by all N columns; a wavefront has 64 rows
+// by 32 columns of one. No part of a tile waits for memory on its own:
+//  * the weights never pass through LDS: they come from the L2 in the order in which the matrix cores take them (k by eights), 16
+//    bytes per lane and part, two steps of 16 k ahead;
+//  * the gathered rows pass through a double-buffered LDS slice of 32 or 64 k (one barrier per slice), split as they are written there from
+//    registers requested two slices earlier, also across the tile boundary;
+//  * the finished tile's sums are parked in registers and leave for memory in eight chunks during the slices of the next tile; the
+//    cached / old values that a chunk is combined with are requested two slices before the chunk is finished;
+//  * the mean's 1/deg is applied to the finished row.
+// Every array is addressed through a buffer descriptor with 32-bit offsets (as flat addresses the unrolled slices kept dozens of
+// 64-bit pointers alive): arrays of less than 4 GB.
+struct StreamArgs {
+    TArgs t;
+    uint32_t x_row, x_bytes;       // gathered rows: stride and extent in bytes
+    uint32_t o_row, o_bytes;       // rows written (H, D, addend / tmp_out): stride and extent in bytes
+    uint32_t o2_row, o2_bytes;     // tmp_out2
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wn = tid >> 6;
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
+    floatx2 f;
+    f.x = a;
+    f.y = b;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));     // to nearest even
+}
+// four numbers as PL bf16 numbers each, four to eight bytes per part
+template <int PL>
+__device__ __forceinline__ void split_parts(floatx4 x, uintx2 (&part)[PL]) {
+#pragma unroll
+    for (int p = 0; p < PL; ++p) {
+        part[p].x = to_bf16x2(x.x, x.y);
+        part[p].y = to_bf16x2(x.z, x.w);
+        if (p + 1 < PL) {                                  // what is left: exact
+            x.x -= __uint_as_float(part[p].x << 16);
+            x.y -= __uint_as_float(part[p].x & 0xFFFF0000u);
+            x.z -= __uint_as_float(part[p].y << 16);
+            x.w -= __uint_as_float(part[p].y & 0xFFFF0000u);
+        }
+    }
+}
+
+// element k of the row in slot `slot` as the product takes it
+template <int MODE, int STORE>
+__device__ __forceinline__ float row_number(const TArgs &a, uint32_t slot, uint32_t v, uint32_t k, float scale) {
+    if (MODE == 0) return a.X[(size_t)v * a.d_in + k] * scale;
+    if (MODE == 3) return a.tmp_in[(size_t)slot * a.tmp_ld + k];
+    const float h = rp_load_h(a.Hprev, STORE, (size_t)v * a.d_in + k);
+    if (MODE == 2) return h * a.one_plus_eps + a.X[(size_t)v * a.d_in + k] * scale;
+    return h;
+}
+
+// SW: k per slice, KS slices (K <= SW KS); WN: wavefronts side by side (32 WN columns); MODE, STORE: see fetch_raw (MODE 0, 2, 3, 4).
+// OUT 0: the product goes to tmp_out (and tmp_out2). 1: H is updated; ADD: plus an unscaled cached row, DELTA: the delta row is written too.
+template <int SW, int KS, int WN, int MODE, int STORE, int OUT, bool ADD, bool DELTA>
+__global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
+    static_assert(OUT == 1 || (!ADD && !DELTA), "products are stored as they are");
+    constexpr int WM = 8 / WN, TM = 2, BM = 32 * TM * WM;                     // a wavefront: TM blocks of 32 x 32
+    constexpr int TPR = SW / 4, RPP = 512 / TPR, NA = BM / RPP;               // staging: threads per row, rows at a time, groups of four per thread and slice
+    constexpr int NC = 4 * TM, SPS = SW / 16, STEPS = SPS * KS, EVERY = STEPS / NC;           // chunks of a tile; steps of 16 k of a slice and a tile, steps per chunk
+    constexpr int LEAD = 2;                                // chunks requested ahead
+    constexpr int PL = STORE ? 1 : 3;                      // parts of a row number
+    constexpr int BQ = 2;                                  // steps whose weights are held or on their way
+    constexpr int LD = SW + 8;                             // LDS row stride in bf16 (eight rows cover all banks)
+    constexpr bool TWO = MODE == 2;
+    static_assert(EVERY >= 1 && STEPS % BQ == 0 && NC % LEAD == 0, "schedule");
+    __shared__ __attribute__((aligned(16))) unsigned short As[2][PL][BM][LD];
+    __shared__ uint32_t s_row[2][BM];                      // output row of every slot of the tile
+    __shared__ float s_scale[MODE == 0 ? 2 : 1][MODE == 0 ? BM : 1];
+
+    const TArgs &a = sa.t;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wn = wave % WN, wm = wave / WN;
     const uint32_t count = *a.count_ptr;
     const uint32_t n_tiles = (count + BM - 1) / BM;
     uint32_t tile = blockIdx.x;
     if (tile >= n_tiles) return;
 
-    constexpr uint32_t RSRC3 = 0x00020000u;                // raw buffer, 32-bit elements
-    const uint32_t row_bytes_total = n_cap * 1024u;        // < 4 GB - 4 KB (checked by the launch)
-    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)a.W, 0, 256 * 256 * 4, RSRC3);
-    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)a.X, 0, row_bytes_total, RSRC3);
-    const __amdgpu_buffer_rsrc_t hres = __builtin_amdgcn_make_buffer_rsrc(a.Hout, 0, row_bytes_total, RSRC3);
-    const __amdgpu_buffer_rsrc_t pres = __builtin_amdgcn_make_buffer_rsrc((void *)(ADD ? a.addend : a.X), 0, row_bytes_total, RSRC3);
-    const __amdgpu_buffer_rsrc_t dres = __builtin_amdgcn_make_buffer_rsrc((void *)(DELTA ? a.D : (float *)a.Hout), 0, row_bytes_total, RSRC3);
+    constexpr uint32_t RSRC3 = 0x00020000u, NOWHERE = 0xFFFFF000u;        // beyond every array: nothing is stored there
+    const uint32_t plane = a.wp_k * a.Npad * 2u;           // bytes of one part of the weights
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)a.Wp, 0, 3u * plane, RSRC3);
+    const void *xsrc = MODE == 0 ? (const void *)a.X : (MODE == 3 ? (const void *)a.tmp_in : a.Hprev);
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc((void *)xsrc, 0, sa.x_bytes, RSRC3);
+    const __amdgpu_buffer_rsrc_t qres = __builtin_amdgcn_make_buffer_rsrc((void *)(TWO ? (const void *)a.X : xsrc), 0, sa.x_bytes, RSRC3);
+    const bool second = OUT == 0 && a.split_col && wn * 32u >= a.split_col;   // this wavefront's columns are the second product's
+    const uint32_t out_row = second ? sa.o2_row : sa.o_row;
+    const __amdgpu_buffer_rsrc_t ores = __builtin_amdgcn_make_buffer_rsrc(
+        OUT == 1 ? a.Hout : (void *)(second ? a.tmp_out2 : a.tmp_out), 0, second ? sa.o2_bytes : sa.o_bytes, RSRC3);
+    const __amdgpu_buffer_rsrc_t pres = __builtin_amdgcn_make_buffer_rsrc((void *)(ADD ? a.addend : a.X), 0, ADD ? sa.o_bytes : 0u, RSRC3);
+    const __amdgpu_buffer_rsrc_t dres = __builtin_amdgcn_make_buffer_rsrc((void *)(DELTA ? a.D : (float *)a.X), 0, DELTA ? sa.o_bytes : 0u, RSRC3);
 
-    const uint32_t c4a = (tid % (T_BK / 4)) * 4;
-    const int r_own = tid / (T_BK / 4);                    // this thread stages rows r_own and r_own + 32 of every slice
-    const uint32_t colb = (wn * 64 + 2 * (lane & 31)) * 4u;    // byte offset of its two adjacent output columns in a row
-    const uint32_t wvo = (lane >> 5) * 1024u + colb;       // weights: row (lane >> 5) of a pair of k, those two columns
-    const floatx2 bias = *(const floatx2 *)(a.bias + wn * 64 + 2 * (lane & 31));
+    const uint32_t c4a = tid % TPR * 4u;
+    const uint32_t r_own = tid / TPR;                      // this thread stages rows r_own + RPP i of every slice
+    const uint32_t col = wn * 32u + (lane & 31u);
+    const uint32_t ocol = second ? col - a.split_col : col;                   // column of the array it is stored in
+    const uint32_t lim = OUT == 0 && a.split_col ? (second ? a.N - a.split_col : a.N1) : a.N;
+    const bool stored = ocol < lim;                        // (padding columns are not)
+    const uint32_t colb = ocol * 4u;
+    const uint32_t wvo = ((lane >> 5) * a.Npad + col) * 16u;                  // weights: eight k of one column
+    const float bias = a.bias[col];                        // (padded)
+    constexpr uint32_t XB = STORE && MODE != 3 ? 2u : 4u;  // bytes of a gathered number
+    const uint32_t k_last = (a.K - 1u) & ~3u;              // first k of a row's last group of four
+    const uint32_t kstep = 2u * a.Npad * 16u;              // bytes of the weights of 16 k
 
-    // byte offsets of the two rows this thread stages, for the current and the next tile; rows past the end repeat
-    // the last one and are never stored
-    uint32_t xo_cur[NA], xo_nxt[NA];
-    float sc_cur[NA], sc_nxt[NA];
+    auto row_scale = [&](uint32_t v) {
+        const uint32_t deg = a.in_meta[v].y;
+        return a.mean ? 1.0f / (float)(deg > 1u ? deg : 1u) : 1.0f;
+    };
+    // the rows this thread stages, of the current tile and the next two; slots past the end repeat the last one and are never stored
+    constexpr bool SCALE = MODE == 0 || TWO;
+    uint32_t v_cur[NA], v_nxt[NA], v_far[NA];
+    float sc_cur[SCALE ? NA : 1], sc_nxt[SCALE ? NA : 1];
+    auto slot_of = [&](uint32_t t, int i) { return min(t * BM + r_own + (uint32_t)RPP * i, count - 1u); };
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const uint32_t v = a.list[min(tile * BM + r_own + i * 32, count - 1u)];
-        xo_cur[i] = v * 1024u + c4a * 4u;
-        xo_nxt[i] = xo_cur[i];
-        const uint32_t deg = a.in_meta[v].y;
-        sc_cur[i] = a.mean ? 1.0f / (float)(deg > 1u ? deg : 1u) : 1.0f;
-        sc_nxt[i] = sc_cur[i];
-        if (c4a == 0) {                                    // nothing is parked yet: its row ids only have to be valid
-            s_vtx[1][r_own + i * 32] = v;
-            s_scale[1][r_own + i * 32] = 1.0f;
+        v_cur[i] = a.list[slot_of(tile, i)];
+        v_nxt[i] = a.list[slot_of(tile + gridDim.x, i)];
+        if constexpr (SCALE) sc_cur[i] = row_scale(v_cur[i]);
+        if (c4a == 0) {                                    // nothing is parked yet: its rows only have to be valid
+            s_row[1][r_own + RPP * i] = (OUT == 0 && a.out_mode == 0) ? 0u : v_cur[i];
+            if (MODE == 0) s_scale[1][r_own + RPP * i] = 1.0f;
         }
     }
-
-    auto load_x = [&](uint32_t xo, int slice) {
-        return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(xres, xo + slice * T_BK * 4, 0, 0));
-    };
-    auto load_w = [&](int slice, int q) {                  // pair q of k of a slice: the lane's operand for both column blocks
-        return __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(wres, wvo, slice * T_BK * 1024 + q * 2048, 0));
-    };
-    auto stage_x = [&](int buf, const floatx4 (&r)[NA]) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            float *dst = &As[buf][r_own + i * 32][c4a];
-            dst[0] = r[i].x;
-            dst[1] = r[i].y;
-            dst[2] = r[i].z;
-            dst[3] = r[i].w;
+    floatx4 ra[2][NA], rq[TWO ? 2 : 1][TWO ? NA : 1];
+    auto load_x = [&](int buf, int i, uint32_t t, uint32_t v, int slice) {
+        const uint32_t off = (MODE == 3 ? slot_of(t, i) : v) * sa.x_row + min((uint32_t)slice * SW + c4a, k_last) * XB;
+        if (XB == 2u) {
+            const uintx2 w = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(xres, off, 0, 0));
+            ra[buf][i].x = __uint_as_float(w.x);
+            ra[buf][i].y = __uint_as_float(w.y);
+        } else {
+            ra[buf][i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(xres, off, 0, 0));
         }
+        if constexpr (TWO) rq[buf][i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(qres, off, 0, 0));
     };
+    auto stage_x = [&](int buf, int slice, int i, float sc) {                 // slice `slice` from ra[buf] into As[buf]
+        floatx4 x = ra[buf][i];
+        const uint32_t k = (uint32_t)slice * SW + c4a;
+        uintx2 part[PL];
+        if (XB == 2u) {                                    // bf16 rows: as they are
+            uint32_t w0 = __float_as_uint(x.x), w1 = __float_as_uint(x.y);
+            w0 = k + 1u < a.K ? w0 : (k < a.K ? w0 & 0xFFFFu : 0u);
+            w1 = k + 3u < a.K ? w1 : (k + 2u < a.K ? w1 & 0xFFFFu : 0u);
+            part[0].x = w0;
+            part[0].y = w1;
+        } else {
+            if constexpr (TWO) x = x * a.one_plus_eps + rq[buf][i] * sc;
+            x.x = k < a.K ? x.x : 0.0f;                    // padding, and what was read past the row's end
+            x.y = k + 1u < a.K ? x.y : 0.0f;
+            x.z = k + 2u < a.K ? x.z : 0.0f;
+            x.w = k + 3u < a.K ? x.w : 0.0f;
+            split_parts<PL>(x, part);
+        }
+#pragma unroll
+        for (int p = 0; p < PL; ++p) *(uintx2 *)&As[buf][p][r_own + RPP * i][c4a] = part[p];
+    };
+    uintx4 bq[BQ][3];                                      // weights of step g in bq[g % BQ]
+    auto load_w = [&](int g) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            bq[g % BQ][p] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(wres, wvo, (uint32_t)(g % STEPS) * kstep + p * plane, 0));
+    };
+    bf16x8 av[2][TM][PL];                                  // row operands of step g in av[g & 1]
+    auto read_a = [&](int g) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+                av[g & 1][i][p] = __builtin_bit_cast(bf16x8, *(const uintx4 *)&As[(g / SPS) & 1][p][(wm * TM + i) * 32 + (lane & 31)][g % SPS * 16 + (lane >> 5) * 8]);
+    };
+#pragma unroll
+    for (int i = 0; i < NA; ++i) load_x(0, i, tile, v_cur[i], 0);
+#pragma unroll
+    for (int g = 0; g < BQ; ++g) load_w(g);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) load_x(1, i, tile, v_cur[i], 1);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) stage_x(0, 0, i, TWO ? sc_cur[TWO ? i : 0] : 1.0f);
+    if (KS > 2)                                            // (KS = 2: the next tile's first slice, requested in this tile's)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) load_x(0, i, tile, v_cur[i], 2);
 
-    floatx4 ra[2][NA];                                     // ra[p]: the slice that goes to As[p] next
-    floatx2 bq[WLEAD];                                     // bq[q % WLEAD]: pair q of k, requested WLEAD pairs before its use
+    floatx16 acc[TM], cor[TM], done[TM];                   // large terms, small terms, the parked tile's sums
 #pragma unroll
-    for (int i = 0; i < NA; ++i) ra[0][i] = load_x(xo_cur[i], 0);
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int i = 0; i < NA; ++i) ra[1][i] = load_x(xo_cur[i], 1);
-#pragma unroll
-    for (int q = 0; q < WLEAD; ++q) bq[q] = load_w(0, q);
-    stage_x(0, ra[0]);
-#pragma unroll
-    for (int i = 0; i < NA; ++i) ra[0][i] = load_x(xo_cur[i], 2);
-
-    floatx16 acc[2][2], accp[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                acc[i][j][r] = 0.0f;
-                accp[i][j][r] = 0.0f;
-            }
-    uint32_t prev_rows = 0;                                // valid rows of the parked tile (0: nothing parked)
-    int par = 0;                                           // s_vtx / s_scale [par]: the current tile, [par ^ 1]: the parked one
-    floatx2 pa[LEAD][4], po[LEAD][4];                      // cached-row and old values of the chunks in flight
+        for (int r = 0; r < 16; ++r) acc[i][r] = cor[i][r] = done[i][r] = 0.0f;
+    uint32_t prev_tile = 0, prev_rows = 0;                 // the parked tile and its valid rows (0: nothing parked)
+    int par = 0;                                           // s_row / s_scale [par]: the current tile, [par ^ 1]: the parked one
+    float pa[LEAD][4], po[LEAD][4];                        // cached-row and old values of the chunks in flight
 #pragma unroll
     for (int q = 0; q < LEAD; ++q)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            pa[q][j] = (floatx2)(0.0f);
-            po[q][j] = (floatx2)(0.0f);
-        }
+        for (int j = 0; j < 4; ++j) pa[q][j] = po[q][j] = 0.0f;
 
-    // Chunk c of a tile: accumulator elements 4 (c & 3) .. + 3 of blocks [c >> 2][0] and [c >> 2][1], i.e. for this lane
-    // four rows (j) with its two columns each. `buf` names the tile's entry in s_vtx / s_scale.
-    uint32_t rowoff[4];                                    // byte offsets of the chunk being finished (rows past the end of the
-    float rsc[4];                                          // list: beyond the buffer, so that the hardware drops their stores)
-    auto finish_rows = [&](int c, int buf, uint32_t rows) {
-        const int lr0 = (c >> 2) * 32 + (c & 3) * 8 + (lane >> 5) * 4;
+    // Chunk c of a tile: sums 4 (c & 3) .. + 3 of block c >> 2, four rows (j) of this lane's column. `buf`: the tile's entry in s_row.
+    auto chunk_row = [&](int c, int j) { return (uint32_t)((wm * TM + (c >> 2)) * 32 + (c & 3) * 8 + (lane >> 5) * 4 + j); };
+    auto request_chunk = [&](int c, int buf) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            rowoff[j] = s_vtx[buf][lr0 + j] * 1024u;
-            rsc[j] = s_scale[buf][lr0 + j];
+            const uint32_t off = stored ? s_row[buf][chunk_row(c, j)] * sa.o_row + colb : NOWHERE;
+            if (ADD) pa[c % LEAD][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pres, off, 0, 0));
+            if (DELTA) po[c % LEAD][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ores, off, 0, 0));
+        }
+    };
+    auto finish_chunk = [&](int c, int buf) {
+        float z[4];
+        bool bad = false;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            z[j] = done[c >> 2][(c & 3) * 4 + j];
+            if (MODE == 0) z[j] *= s_scale[buf][chunk_row(c, j)];
+            bad |= !__builtin_isfinite(z[j]);
+        }
+        if (__builtin_expect(__any(bad && stored), 0)) {                      // see above
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t slot = prev_tile * BM + chunk_row(c, j);
+                if (__builtin_isfinite(z[j]) || !stored || chunk_row(c, j) >= prev_rows) continue;
+                const uint32_t v = a.list[slot];
+                const float sc = (MODE == 0 || MODE == 2) ? row_scale(v) : 1.0f;
+                float t = 0.0f;
+#pragma unroll 1
+                for (uint32_t k = 0; k < a.K; ++k) t = __builtin_fmaf(row_number<MODE, STORE>(a, slot, v, k, sc), a.W[(size_t)k * a.Npad + col], t);
+                z[j] = t;
+            }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) rowoff[j] = (((uint32_t)(lr0 + j) < rows) ? rowoff[j] : 0xFFFFF000u) + colb;
-    };
-    auto finish_row = [&](int c, int j) {
-        floatx2 z;
-        z.x = accp[c >> 2][0][(c & 3) * 4 + j] * rsc[j] + bias.x + (ADD ? pa[c % LEAD][j].x : 0.0f);
-        z.y = accp[c >> 2][1][(c & 3) * 4 + j] * rsc[j] + bias.y + (ADD ? pa[c % LEAD][j].y : 0.0f);
-        if (a.act == RIPPLE_ACT_RELU) {
-            z.x = z.x > 0.0f ? z.x : 0.0f;
-            z.y = z.y > 0.0f ? z.y : 0.0f;
+        for (int j = 0; j < 4; ++j) {
+            z[j] += bias + (ADD ? pa[c % LEAD][j] : 0.0f);
+            if (a.act == RIPPLE_ACT_RELU) z[j] = z[j] > 0.0f ? z[j] : 0.0f;
+            const uint32_t lr = chunk_row(c, j), off = stored && lr < prev_rows ? s_row[buf][lr] * out_row + colb : NOWHERE;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(z[j]), ores, off, 0, 0);
+            if (DELTA) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a.d_old ? po[c % LEAD][j] : z[j] - po[c % LEAD][j]), dres, off, 0, 0);
         }
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, z), hres, rowoff[j], 0, 0);
-        if (DELTA) {
-            const floatx2 d = a.d_old ? po[c % LEAD][j] : z - po[c % LEAD][j];
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, d), dres, rowoff[j], 0, 0);
-        }
-    };
-    auto request_row = [&](int c, int buf, int j) {
-        const uint32_t off = s_vtx[buf][(c >> 2) * 32 + (c & 3) * 8 + (lane >> 5) * 4 + j] * 1024u + colb;
-        if (ADD) pa[c % LEAD][j] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(pres, off, 0, 0));
-        if (DELTA) po[c % LEAD][j] = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(hres, off, 0, 0));
     };
 
     for (;;) {
         const uint32_t tile_n = tile + gridDim.x;
-        uint32_t v_nxt[NA];
 #pragma unroll
-        for (int i = 0; i < NA; ++i) v_nxt[i] = a.list[min(tile_n * BM + r_own + i * 32, count - 1u)];
+        for (int i = 0; i < NA; ++i) v_far[i] = a.list[slot_of(tile_n + gridDim.x, i)];
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             // every wavefront is done with slice s - 1 (As[(s + 1) & 1] may be overwritten) and has written its part of slice s
             __syncthreads();
-            if (s == 0 && c4a == 0) {                      // this tile's row ids and scale factors, for when it is written out
+            read_a(SPS * s);
+            if (s == 0) {
+                if (c4a == 0)                              // this tile's rows, for when it is written out
 #pragma unroll
-                for (int i = 0; i < NA; ++i) {
-                    s_vtx[par][r_own + i * 32] = xo_cur[i] >> 10;
-                    s_scale[par][r_own + i * 32] = sc_cur[i];
-                }
+                    for (int i = 0; i < NA; ++i) {
+                        s_row[par][r_own + RPP * i] = (OUT == 0 && a.out_mode == 0) ? slot_of(tile, i) : v_cur[i];
+                        if constexpr (MODE == 0) s_scale[par][r_own + RPP * i] = sc_cur[i];
+                    }
+                if constexpr (SCALE)
+#pragma unroll
+                    for (int i = 0; i < NA; ++i) sc_nxt[i] = row_scale(v_nxt[i]);
+                if (KS == 2)
+#pragma unroll
+                    for (int i = 0; i < NA; ++i) load_x(0, i, tile_n, v_nxt[i], 0);
             }
-            if (s == 1) {                                  // the next tile's rows: offsets and scale factors
 #pragma unroll
-                for (int i = 0; i < NA; ++i) {
-                    xo_nxt[i] = v_nxt[i] * 1024u + c4a * 4u;
-                    const uint32_t deg = a.in_meta[v_nxt[i]].y;
-                    sc_nxt[i] = a.mean ? 1.0f / (float)(deg > 1u ? deg : 1u) : 1.0f;
-                }
-            }
-            float av[2][2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) av[0][i] = As[s & 1][i * 32 + (lane & 31)][lane >> 5];
-#pragma unroll
-            for (int q = 0; q < KP; ++q) {
-                const int cur = q & 1, nxt = cur ^ 1;
-                if (q + 1 < KP) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) av[nxt][i] = As[s & 1][i * 32 + (lane & 31)][2 * (q + 1) + (lane >> 5)];
-                }
+            for (int kk = 0; kk < SPS; ++kk) {
+                const int g = SPS * s + kk, now = g & 1;
+                if (kk + 1 < SPS) read_a(g + 1);                // (the next slice's are read behind the barrier)
                 __builtin_amdgcn_sched_barrier(0);
+                bf16x8 bv[3];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur][i], bq[q % WLEAD].x, acc[i][0], 0, 0, 0);
-                    acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur][i], bq[q % WLEAD].y, acc[i][1], 0, 0, 0);
+                for (int p = 0; p < 3; ++p) bv[p] = __builtin_bit_cast(bf16x8, bq[g % BQ][p]);
+#define TERM(dst, x, w)                                                                                        \
+    _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                             \
+        dst[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[now][i][x], bv[w], dst[i], 0, 0, 0)
+                TERM(cor, 0, 2);
+                if constexpr (PL == 3) {
+                    TERM(cor, 2, 0);
+                    TERM(cor, 1, 1);
+                    TERM(cor, 1, 0);
                 }
-                // between the products: the pair WLEAD on (past the slice's end: of the next slice; after the last
-                // slice: slice 0, for the next tile) ...
-                bq[q % WLEAD] = (q + WLEAD < KP) ? load_w(s, q + WLEAD) : load_w((s + 1) % KS, q + WLEAD - KP);
-                // ... and one piece of the parked tile's traffic or of the row staging. Chunk s of the parked tile,
-                // requested LEAD steps ago, is finished; the chunk LEAD on is requested (the first LEAD chunks of the
-                // tile being multiplied, once the parked one has none left).
-                if (q == 0) {
-                    finish_rows(s, par ^ 1, prev_rows);
-                } else if (q <= 4) {
-                    finish_row(s, q - 1);
-                } else if (q >= 8 && q < 12) {
-                    if (s + LEAD < KS) request_row(s + LEAD, par ^ 1, q - 8);
-                    else request_row(s + LEAD - KS, par, q - 8);
-                } else if (q == 12) {                      // slice s + 1 into the other LDS buffer
-                    stage_x((s + 1) & 1, ra[(s + 1) & 1]);
-                } else if (q == 13) {                      // and slice s + 3 into the registers it came from
+                TERM(cor, 0, 1);
+                TERM(acc, 0, 0);
+#undef TERM
+                __builtin_amdgcn_sched_barrier(0);         // (the scheduler would sink the requests to their use)
+                load_w(g + BQ);                            // past the tile's end: the next tile's first steps
+                // a chunk of the parked tile, requested LEAD chunks ago, is finished; the one LEAD on is requested (of the tile being
+                // multiplied, once the parked one has none left)
+                if (g % EVERY == 0) {
+                    const int c = g / EVERY;
+                    finish_chunk(c, par ^ 1);
+                    if (ADD || DELTA) request_chunk((c + LEAD) % NC, c + LEAD < NC ? par ^ 1 : par);
+                }
+                // slice s + 1 into the other LDS buffer, slice s + 3 into the registers it came from
 #pragma unroll
-                    for (int i = 0; i < NA; ++i)
-                        ra[(s + 1) & 1][i] = load_x((s + 3 < KS) ? xo_cur[i] : xo_nxt[i], (s + 3) % KS);
-                }
+                for (int i = 0; i < NA; ++i)
+                    if (i * SPS / NA == kk) {
+                        stage_x((s + 1) & 1, (s + 1) % KS, i, TWO ? (s + 1 < KS ? sc_cur[TWO ? i : 0] : sc_nxt[TWO ? i : 0]) : 1.0f);
+                        if (KS > 2 || s == 0) load_x((s + 1) & 1, i, s + 3 < KS ? tile : tile_n, s + 3 < KS ? v_cur[i] : v_nxt[i], (s + 3) % KS);
+                    }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // park the tile, move on
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                accp[i][j] = acc[i][j];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+            for (int r = 0; r < 16; ++r) {
+                done[i][r] = acc[i][r] + cor[i][r];
+                acc[i][r] = cor[i][r] = 0.0f;
             }
+        prev_tile = tile;
         prev_rows = min((uint32_t)BM, count - tile * BM);
+        par ^= 1;
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            xo_cur[i] = xo_nxt[i];
-            sc_cur[i] = sc_nxt[i];
+            v_cur[i] = v_nxt[i];
+            v_nxt[i] = v_far[i];
+            if constexpr (SCALE) sc_cur[i] = sc_nxt[i];
         }
-        par ^= 1;
         tile = tile_n;
         if (tile >= n_tiles) break;
     }
     // the last tile: its first LEAD chunks are on their way already
 #pragma unroll
-    for (int c = 0; c < KS; ++c) {
-        finish_rows(c, par ^ 1, prev_rows);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) finish_row(c, j);
-        if (c + LEAD < KS) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) request_row(c + LEAD, par ^ 1, j);
-        }
+    for (int c = 0; c < NC; ++c) {
+        finish_chunk(c, par ^ 1);
+        if ((ADD || DELTA) && c + LEAD < NC) request_chunk(c + LEAD, par ^ 1);
     }
 }
 
-// x W with K = N = 256 on fp32 rows, H updated in place, and enough rows for every persistent workgroup to see several
-// tiles (RIPPLE_OPT_STREAM_TRANSFORM = 2: whatever the number of rows)
+// The weights as the kernel takes them: three parts, each [Kp / 8][Npad][8] bf16, zero rows from K on
+__global__ void k_weight_parts(const float *w, uint32_t K, uint32_t Kp, uint32_t Npad, unsigned short *out) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= Kp / 8u * Npad) return;
+    const uint32_t n = i % Npad, k8 = i / Npad * 8u;
+    floatx4 x[2];
+#pragma unroll
+    for (uint32_t t = 0; t < 8u; ++t) {
+        const uint32_t k = k8 + t;
+        const float f = k < K ? w[(size_t)k * Npad + n] : 0.0f;
+        x[t >> 2][t & 3u] = f;
+    }
+    uintx2 lo[3], hi[3];
+    split_parts<3>(x[0], lo);
+    split_parts<3>(x[1], hi);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        uintx4 q;
+        q.x = lo[p].x;
+        q.y = lo[p].y;
+        q.z = hi[p].x;
+        q.w = hi[p].y;
+        *(uintx4 *)(out + ((size_t)p * (Kp / 8u) * Npad + i) * 8u) = q;
+    }
+}
+
+size_t rp_weight_parts_size(uint32_t K, uint32_t Npad) { return (size_t)3 * rp_round_up(K, 128) * Npad; }
+void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t Npad, unsigned short *out) {
+    const uint32_t kp = rp_round_up(K, 128);
+    hipLaunchKernelGGL(k_weight_parts, dim3(rp_div_up(kp / 8u * Npad, 256)), dim3(256), 0, c->stream, w, K, kp, Npad, out);
+}
+
+// K: 128 or 256, the rows of the weights' parts. Slices of 64 k where the tile has 64 rows; tiles of 128 and 256 rows have no room for
+// them in registers and LDS.
+template <int K>
+static bool launch_k(ripple_ctx *c, const StreamArgs &s) {
+    const TArgs &a = s.t;
+    const dim3 grid(c->n_cu), block(512);
+#define GO(WN, ...) hipLaunchKernelGGL((k_split_stream<(WN == 8 ? 64 : 32), K / (WN == 8 ? 64 : 32), WN, __VA_ARGS__>), grid, block, 0, c->stream, s)
+    if (a.a_mode == 4) {
+        if (a.Npad == 256 && !a.store) GO(8, 4, 0, 0, false, false);
+        else if (a.Npad == 128 && !a.store) GO(4, 4, 0, 0, false, false);
+        else if (a.Npad == 128) GO(4, 4, 1, 0, false, false);
+        else if (a.Npad == 64) GO(2, 4, 1, 0, false, false);
+        else return false;
+    } else if (a.a_mode == 0) {
+#define ROWS(WN)                                                       \
+    do {                                                               \
+        if (a.addend && a.D) GO(WN, 0, 0, 1, true, true);              \
+        else if (a.addend) GO(WN, 0, 0, 1, true, false);               \
+        else if (a.D) GO(WN, 0, 0, 1, false, true);                    \
+        else GO(WN, 0, 0, 1, false, false);                            \
+    } while (0)
+        if (a.Npad == 256) ROWS(8);
+        else ROWS(4);
+#undef ROWS
+    } else if (a.a_mode == 2) {
+        GO(8, 2, 0, 0, false, false);
+    } else {
+        if (a.D) GO(8, 3, 0, 1, false, true);
+        else GO(8, 3, 0, 1, false, false);
+    }
+#undef GO
+    return true;
+}
+
+// Enough rows for every persistent workgroup to see two tiles: about 20 us go by before the first tile is out, in which the tiles of
+// fp32 products finish 12 K rows (1.6 us per thousand of 256 -> 256; here 0.8). RIPPLE_OPT_STREAM_TRANSFORM = 2: any number.
+#define STREAM_MIN_TILES 2u
 bool rp_launch_stream(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
-    if (!c->opt_stream || a.a_mode != 0 || a.store || a.Ws || a.out_mode != 1) return false;
-    if (a.K != 256 || a.Kpad != 256 || a.N != 256 || a.Npad != 256 || a.d_in != 256) return false;
-    if (a.addend && a.addend_scaled) return false;
-    if ((uint64_t)c->n_cap * 1024u > 0xFFFFF000ull) return false;   // 32-bit byte offsets into the row arrays, the top 4 KB kept free
-    if (rows_hint < 64u * 4u * 2u * c->n_cu) return false;          // at least four tiles per persistent workgroup
-    const dim3 grid(2 * c->n_cu), block(256);
-    if (a.addend && a.D) hipLaunchKernelGGL((k_transform_stream<true, true>), grid, block, 0, c->stream, a, c->n_cap);
-    else if (a.addend) hipLaunchKernelGGL((k_transform_stream<true, false>), grid, block, 0, c->stream, a, c->n_cap);
-    else if (a.D) hipLaunchKernelGGL((k_transform_stream<false, true>), grid, block, 0, c->stream, a, c->n_cap);
-    else hipLaunchKernelGGL((k_transform_stream<false, false>), grid, block, 0, c->stream, a, c->n_cap);
-    return true;
-}
-
-// ---------------------------------------------------------------------------------
-// Both products of a narrow project-first layer, H^{l-1}[v] W_self (into PS) and H^{l-1}[v] W_neigh (into PD, or T at
-// the bootstrap), for d_in = 256 and d_out <= 48 on fp32 rows. Every wavefront is on its own: it owns 32-row tiles and
-// all 96 columns (three matrix-core blocks), stages its rows through a private, double-buffered LDS slice and reads the
-// weights straight from L2 into the operand registers half a step ahead, so there is no barrier anywhere and three
-// wavefronts per SIMD cover one another's waits. The weight matrix comes permuted, [k][n][j] with three adjacent
-// floats per lane: position n < 16 of block j is column 16 j + n of W_self, n >= 16 column 16 j + n - 16 of W_neigh,
-// so a lane ends up with columns (c, 16 + c, 32 + c) of one of the two products.
-// ---------------------------------------------------------------------------------
-struct PArgs {
-    const uint32_t *list;
-    const uint32_t *count_ptr;
-    const float *H;                // [n_cap x 256]
-    const float *Wp;               // [256][32][3]
-    float *out1, *out2;            // PS [n_cap x ld1], PD or T [n_cap x ld2]
-    uint32_t ld1, ld2, d_out, n_cap;
-};
-
-typedef uint32_t uintx3 __attribute__((ext_vector_type(3)));
-typedef float floatx3 __attribute__((ext_vector_type(3)));
-
-__global__ __launch_bounds__(256, 3) void k_project_both_stream(PArgs a) {
-    constexpr int BM = 32, KS = 8, NA = 4, KP = T_BK / 2, WLEAD = 8;
-    __shared__ __attribute__((aligned(16))) float As_all[4][2][BM][T_BK + 1];
-    __shared__ uint32_t s_vtx_all[4][BM];
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float (*As)[BM][T_BK + 1] = As_all[wave];
-    uint32_t *s_vtx = s_vtx_all[wave];
-    const uint32_t count = *a.count_ptr;
-    const uint32_t n_tiles = (count + BM - 1) / BM;
-    const uint32_t n_waves = gridDim.x * 4u;
-    uint32_t tile = blockIdx.x * 4u + wave;
-    if (tile >= n_tiles) return;
-
-    constexpr uint32_t RSRC3 = 0x00020000u;
-    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)a.Wp, 0, 256 * 96 * 4, RSRC3);
-    const __amdgpu_buffer_rsrc_t hres = __builtin_amdgcn_make_buffer_rsrc((void *)a.H, 0, a.n_cap * 1024u, RSRC3);
-
-    const uint32_t c4a = (lane & 7) * 4;                   // the lane stages rows (lane >> 3) + 8 i, i = 0..3, of every slice
-    const int r_own = lane >> 3;
-    const uint32_t wvo = (lane >> 5) * 384u + (lane & 31) * 12u;   // weights: row (lane >> 5) of a pair of k, its three numbers
-
-    auto load_h = [&](uint32_t ho, int slice) {
-        return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(hres, ho + slice * T_BK * 4, 0, 0));
+    if (!c->opt_stream || !a.Wp || a.K > 256u || a.Npad > 256u || a.Npad < 64u) return false;
+    const bool shape = a.a_mode == 4   ? a.out_mode == 2 && (a.Npad == 128u || (a.Npad == 64u) == (a.store != 0))
+                       : a.a_mode == 0 ? a.out_mode == 1 && !a.store && !(a.addend && a.addend_scaled) && a.Npad >= 128u
+                       : a.a_mode == 2 ? a.out_mode == 0 && !a.store && a.Npad == 256u
+                       : a.a_mode == 3 ? a.out_mode == 1 && !a.store && !a.addend && a.Npad == 256u
+                                       : false;
+    if (!shape) return false;
+    if (c->opt_stream != 2 && rows_hint < STREAM_MIN_TILES * c->n_cu * (64u * 256u / a.Npad)) return false;
+    StreamArgs s;
+    s.t = a;
+    uint64_t most = 0;                                     // rows are addressed with 32-bit byte offsets, the top 4 KB kept free
+    auto extent = [&](uint64_t row, uint32_t &row_out, uint32_t &bytes) {
+        const uint64_t b = (uint64_t)c->n_cap * row + 16u; // (every array has 16 bytes behind its end)
+        most = std::max(most, b);
+        row_out = (uint32_t)row;
+        bytes = (uint32_t)b;
     };
-    auto load_w = [&](int slice, int q) {
-        return __builtin_bit_cast(floatx3, __builtin_amdgcn_raw_buffer_load_b96(wres, wvo, slice * T_BK * 384 + q * 768, 0));
-    };
-    auto stage = [&](int buf, const floatx4 (&r)[NA]) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            float *dst = &As[buf][r_own + 8 * i][c4a];
-            dst[0] = r[i].x;
-            dst[1] = r[i].y;
-            dst[2] = r[i].z;
-            dst[3] = r[i].w;
-        }
-    };
-
-    uint32_t ho_cur[NA], ho_nxt[NA];
-#pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        ho_cur[i] = a.list[min(tile * BM + r_own + 8 * i, count - 1u)] * 1024u + c4a * 4u;   // rows past the end repeat the last one
-        ho_nxt[i] = ho_cur[i];
-    }
-    floatx4 ra[2][NA];
-    floatx3 bq[WLEAD];                                     // bq[q % WLEAD]: pair q of k, requested WLEAD pairs before its use
-#pragma unroll
-    for (int i = 0; i < NA; ++i) ra[0][i] = load_h(ho_cur[i], 0);
-#pragma unroll
-    for (int i = 0; i < NA; ++i) ra[1][i] = load_h(ho_cur[i], 1);
-#pragma unroll
-    for (int q = 0; q < WLEAD; ++q) bq[q] = load_w(0, q);
-    stage(0, ra[0]);
-#pragma unroll
-    for (int i = 0; i < NA; ++i) ra[0][i] = load_h(ho_cur[i], 2);
-
-    floatx16 acc[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
-
-    // where this lane's three columns go
-    const uint32_t sub = lane & 15u;
-    const bool second = (lane & 16) != 0;
-    float *const obase = (second ? a.out2 : a.out1) + sub;
-    const uint32_t old = second ? a.ld2 : a.ld1;
-
-    for (;;) {
-        const uint32_t tile_n = tile + n_waves;
-        uint32_t v_nxt[NA];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) v_nxt[i] = a.list[min(tile_n * BM + r_own + 8 * i, count - 1u)];
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            // the wavefront's LDS accesses are served in order: slice s (written during step s - 1) is complete
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (s == 0 && c4a == 0) {
-#pragma unroll
-                for (int i = 0; i < NA; ++i) s_vtx[r_own + 8 * i] = ho_cur[i] >> 10;
-            }
-            if (s == 1) {
-#pragma unroll
-                for (int i = 0; i < NA; ++i) ho_nxt[i] = v_nxt[i] * 1024u + c4a * 4u;
-            }
-            float av[2];
-            av[0] = As[s & 1][lane & 31][lane >> 5];
-#pragma unroll
-            for (int q = 0; q < KP; ++q) {
-                const int cur = q & 1, nxt = cur ^ 1;
-                if (q + 1 < KP) av[nxt] = As[s & 1][lane & 31][2 * (q + 1) + (lane >> 5)];
-                __builtin_amdgcn_sched_barrier(0);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur], bq[q % WLEAD].x, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur], bq[q % WLEAD].y, acc[1], 0, 0, 0);
-                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur], bq[q % WLEAD].z, acc[2], 0, 0, 0);
-                // the pair WLEAD on (past the slice's end: of the next slice; after the last slice: slice 0, for the next tile)
-                bq[q % WLEAD] = (q + WLEAD < KP) ? load_w(s, q + WLEAD) : load_w((s + 1) % KS, q + WLEAD - KP);
-                if (q == 10) {                             // slice s + 1 into the other LDS buffer
-                    stage((s + 1) & 1, ra[(s + 1) & 1]);
-                } else if (q == 11) {                      // and slice s + 3 into the registers it came from
-#pragma unroll
-                    for (int i = 0; i < NA; ++i)
-                        ra[(s + 1) & 1][i] = load_h((s + 3 < KS) ? ho_cur[i] : ho_nxt[i], (s + 3) % KS);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // the tile's 32 x 96 results leave straight from the accumulators: element r of block j is row
-        // 8 (r >> 2) + 4 (lane >> 5) + (r & 3), column 16 j + sub of this lane's product
-        const uint32_t rows = min((uint32_t)BM, count - tile * BM);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const uint32_t lr = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-            if (lr < rows) {
-                float *o = obase + (size_t)s_vtx[lr] * old;
-                o[0] = acc[0][r];
-                if (16u + sub < a.d_out) o[16] = acc[1][r];
-                if (32u + sub < a.d_out) o[32] = acc[2][r];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) ho_cur[i] = ho_nxt[i];
-        tile = tile_n;
-        if (tile >= n_tiles) break;
-    }
-}
-
-bool rp_launch_project_both_stream(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, float *out2,
-                                   uint32_t ld2, uint32_t rows_hint) {
-    const LayerDev &ly = c->layers[l - 1];
-    if (!c->opt_stream || !ly.Wc96p || c->store || ly.d_in != 256 || ly.d_out > 48 || ly.d_out < 17) return false;
-    if ((uint64_t)c->n_cap * 1024u > 0xFFFFF000ull) return false;
-    if (rows_hint < 131072u && c->opt_stream != 2) return false;   // enough 32-row tiles for every wavefront of the chip (2: any number, for tests)
-    PArgs a;
-    a.list = list;
-    a.count_ptr = count_d;
-    a.H = (const float *)c->H[l - 1];
-    a.Wp = ly.Wc96p;
-    a.out1 = ly.PS;
-    a.ld1 = ly.d_out;
-    a.out2 = out2;
-    a.ld2 = ld2;
-    a.d_out = ly.d_out;
-    a.n_cap = c->n_cap;
-    hipLaunchKernelGGL(k_project_both_stream, dim3(3 * c->n_cu), dim3(256), 0, c->stream, a);
-    return true;
+    extent(a.a_mode == 3 ? (uint64_t)a.tmp_ld * 4u : (uint64_t)a.d_in * (a.a_mode == 4 && a.store ? 2u : 4u), s.x_row, s.x_bytes);
+    extent(a.out_mode == 1 ? (uint64_t)a.N * 4u : (uint64_t)a.tmp_out_ld * 4u, s.o_row, s.o_bytes);
+    s.o2_row = s.o2_bytes = 0;
+    if (a.split_col) extent((uint64_t)a.tmp_out2_ld * 4u, s.o2_row, s.o2_bytes);
+    if (most > 0xFFFFF000ull) return false;
+    return a.K <= 128u ? launch_k<128>(c, s) : launch_k<256>(c, s);
 }

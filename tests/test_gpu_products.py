@@ -1,0 +1,93 @@
+"""Products of many rows (k_split_stream: fp32 numbers as three bf16 parts on the bf16 matrix cores) at small sizes, forced with
+RIPPLE_OPT_STREAM_TRANSFORM = 2, against the oracle and against the fp32 matrix cores (option 0)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2601_12347_amd as rp
+import ripple_inputs as ri
+from harness import Pair, make_pair, make_stream
+
+pytestmark = pytest.mark.gpu
+
+MIX = {"edge_add": 0.4, "edge_del": 0.25, "feat": 0.2, "vadd": 0.08, "vdel": 0.07}
+
+# widths on both sides of every multiple the kernel works in (4 numbers, 16 and 32 k, 32 and 64 columns), one and two slices of k,
+# 64, 128 and 256 padded columns, odd row strides; every kind of row (aggregate, own row, GIN sum, hidden row) and both stores
+SHAPES = [("sage_mean", (75, 190, 190, 23), "f32", False), ("gcn_wsum", (75, 190, 190, 23), "f32", True), ("gin_sum", (33, 256, 200, 129), "f32", False),
+          ("sage_mean", (129, 65, 128, 40), "f32", False), ("gcn_sum", (17, 100, 70), "f32", False), ("gat", (100, 256, 129, 47), "f32", False),
+          ("gcn_max", (31, 255, 97), "f32", False), ("sage_mean", (100, 256, 256, 47), "bf16", False), ("gcn_sum", (66, 250, 33), "bf16", False),
+          ("gcn_sum", (100, 256, 100), "bf16", False)]
+
+
+@pytest.mark.parametrize("kind,widths,store,weighted", SHAPES)
+def test_products_of_every_shape(kind, widths, store, weighted):
+    print("case products", kind, widths, store, flush=True)
+    pair, graph = make_pair(n=700, e=7000, d0=widths[0], kind=kind, widths=widths, seed=271, slack=64, weighted=weighted, store=store)
+    rp.ripple_set_option(pair.ctx, rp.OPT_STREAM_TRANSFORM, 2)
+    rp.ripple_full_infer(pair.ctx)
+    stream = make_stream(pair, graph, MIX, 273, weighted=weighted)
+    try:
+        pair.check_embeddings()
+        for b, bs in enumerate([1, 40, 200]):
+            print(" batch", b, bs, flush=True)
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload)
+            pair.check_aggregates()
+    finally:
+        pair.close()
+
+
+def _rows(kind, widths, feats, option):
+    n, e = 400, 3000
+    src, dst, _, _ = ri.chung_lu_graph(n, e, 2.1, 0.03, 281)
+    model = ri.make_model(kind, widths, 283)
+    ctx = rp.ripple_init_graph(n, n, src, dst, feats)
+    rp.ripple_load_model(ctx, model)
+    try:
+        rp.ripple_set_option(ctx, rp.OPT_STREAM_TRANSFORM, option)
+        rp.ripple_full_infer(ctx)
+        return [rp.ripple_get_embeddings(ctx, l, widths[l], n_rows=n) for l in range(1, len(widths))]
+    finally:
+        rp.ripple_destroy(ctx)
+
+
+@pytest.mark.parametrize("kind", ["sage_mean", "gcn_sum", "gin_sum"])
+def test_numbers_that_have_no_parts(kind):
+    """Infinities, NaNs and numbers that bf16 rounds to infinity: the same elements are infinite (with the same sign), NaN and finite as
+    with fp32 products, and the finite ones agree. One layer without activation: 256 sums of at most 50 rows keep 1e-5 of the largest."""
+    widths = (100, 200)
+    feats = ri.features(400, 100, 282)
+    feats[3, 5], feats[40, 99], feats[77, 0], feats[200, 31], feats[310, 64] = np.inf, -np.inf, np.nan, 3.4e38, -3.395e38
+    on, off = _rows(kind, widths, feats, 2)[0], _rows(kind, widths, feats, 0)[0]
+    assert np.array_equal(np.isnan(on), np.isnan(off)) and np.array_equal(np.isposinf(on), np.isposinf(off)) and np.array_equal(np.isneginf(on), np.isneginf(off))
+    assert np.isnan(on).any() and (np.abs(on[np.isfinite(on)]) > 1e36).any()
+    assert np.isinf(on).any() or kind == "gin_sum"          # (a second product makes NaNs of them)
+    fin = np.isfinite(on)
+    scale = np.maximum(np.where(fin, np.abs(off), 0).max(axis=1, keepdims=True), 1e-30)
+    assert (np.abs(np.where(fin, on, 0) - np.where(fin, off, 0)) / scale).max() <= 1e-5
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-10, 1.0, 1e10, 1e30])
+def test_rows_of_any_magnitude(scale):
+    """The parts of a number are relative to it: rows of 1e-30 and of 1e30 are as exact as rows of 1 (weights of about 0.1, biases 0)."""
+    widths = (100, 200)
+    feats = (ri.features(400, 100, 284) * np.float32(scale)).astype(np.float32)
+    n = 400
+    src, dst, _, _ = ri.chung_lu_graph(n, 3000, 2.1, 0.03, 281)
+    model = ri.make_model("sage_mean", widths, 285)
+    for layer in model:
+        layer["b0"] = np.zeros_like(layer["b0"])
+    errs = {}
+    for option in (2, 0):
+        pair = Pair(n, n, src, dst, feats, model)
+        try:
+            rp.ripple_set_option(pair.ctx, rp.OPT_STREAM_TRANSFORM, option)
+            rp.ripple_full_infer(pair.ctx)
+            want = oracle.full_recompute(pair.ora, model)[1]
+            got = rp.ripple_get_embeddings(pair.ctx, 1, widths[1], n_rows=n).astype(np.float64)
+            errs[option] = np.linalg.norm((got - want) / scale) / np.linalg.norm(want / scale)
+        finally:
+            pair.close()
+    print("scale %g: error against 64 bits %.2e, fp32 products %.2e" % (scale, errs[2], errs[0]), flush=True)
+    assert errs[2] <= max(1.1 * errs[0], 1.5e-7)
