@@ -191,10 +191,11 @@ typedef enum {
                                      chain of fp32 products); 0 keeps the one-tile-per-workgroup kernels on the fp32 matrix
                                      cores; 2 takes the streaming kernel whatever the number of rows (for tests). */
     RIPPLE_OPT_SORTED_MESSAGES = 12, /* 0/1/2 (default 1): a hop that would be pulled while few of the scanned in-row entries
-                                      carry a message is scattered from the list of its messages instead, which the out-edge
-                                      walk writes down and a radix sort orders by destination; 1 where the previous batch's
-                                      counts say so, 2 wherever a hop is pulled (tests), 0 never. Same results up to the order
-                                      of the sums. Not used in the deterministic mode, by weighted-sum layers or packed rows. */
+                                      carry a message, or pushed with many numbers to add, is scattered from the list of its
+                                      messages instead, which the out-edge walk writes down by destination; 1 where the previous
+                                      batch's counts say so, 2 at every hop from the second on that does not discover (tests), 0
+                                      never. Same results up to the order of the sums. Not used in the deterministic mode, by
+                                      weighted-sum layers and on graphs of more than 2^25 vertices. */
     RIPPLE_OPT_DETERMINISTIC = 6  /* 0/1 (default 0), before load_model: every sum is taken in an order that is a function of
                                      the graph and the batches alone (no float atomics: in-rows keep a reproducible order,
                                      hops are gathered along them, rows that several wavefronts read are finished in

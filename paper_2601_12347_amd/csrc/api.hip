@@ -722,23 +722,13 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         RP_TRY(dev_alloc(c, &c->side_acc, entries * xmax, false));
     }
     if (!c->opt_deterministic) {
-        // (destination, source) pairs of a hop's messages, before and after the sort by destination: room for a quarter
-        // of the edge capacity (a hop with more messages than that is pulled or discovers), at most 2^25
+        // (destination, source) pairs of a hop's messages: room for twice a quarter of the edge capacity, at most 2^26 (a hop with
+        // more messages than that quarter is pulled, pushed or discovers)
         c->pair_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(c->pool_cap / 4, 1u << 14), 1u << 25);
-        c->pair_bits = 1;
-        while (c->pair_bits < 32 && (1ull << c->pair_bits) <= n) ++c->pair_bits;   // 2^bits > every vertex id; the filler key has all of them set
-        c->pair_tmp_bytes = rp_sort_u32_tmp_bytes(c->pair_cap);
-        if (c->pair_tmp_bytes) {
-            Block b;
-            b.add(&c->pk_a, c->pair_cap);
-            b.add(&c->pk_b, c->pair_cap);
-            b.add(&c->pv_a, c->pair_cap);
-            b.add(&c->pv_b, c->pair_cap);
-            b.add((uint8_t **)&c->pair_tmp, c->pair_tmp_bytes);
-            RP_TRY(block_alloc(c, b, &c->pair_block, false));
-        } else {
-            c->pair_cap = 0;
-        }
+        Block b;
+        b.add(&c->pairs, 2 * (size_t)c->pair_cap);
+        b.add(&c->pair_sorted, c->pair_cap);
+        RP_TRY(block_alloc(c, b, &c->pair_block, false));
     }
     // bitmaps: layers 0..L, then S, then V_added, contiguous; reporting copies separately
     uint32_t *bmall = nullptr, *repall = nullptr, *lists = nullptr, *eoffs = nullptr, *ioffs = nullptr;
@@ -751,6 +741,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
     b.add(&c->all_list, n + 1);
     b.add(&c->mk, (size_t)c->n_words * 32);
     b.add(&c->ioff_all, n + 1);
+    b.add(&c->pair_cnt, RP_LIST_BUCKETS);
     RP_TRY(block_alloc(c, b, &c->list_block, true));
     for (uint32_t l = 0; l <= c->L; ++l) {
         c->bm[l] = bmall + (size_t)l * c->n_words;
@@ -1097,18 +1088,20 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_launch_alive_list(c);
             have_all = true;
         }
-        // A hop that the last batch pulled (or took from the list already) through in-rows holding enough entries for the
-        // sort to pay (rp_sorted_pays) is taken from the sorted list of its messages (k_scatter_sorted): the out-edge
-        // walk writes the list, and as many entries are sorted as the last batch had messages, and a quarter more. The
-        // kernels make sure on the device that the list is only used if this batch's messages fit and the sort
-        // still pays; else the hop is pulled.
+        // A hop that the last batch moved a good many messages at without discovering its set is taken from the list of them
+        // (k_scatter_list) where that pays: in place of a pull through in-rows that hold enough entries, or of a push of enough numbers.
+        // The out-edge walk writes the list; a quarter more messages than the last batch had are expected, four times as many where
+        // the hop would be pushed (small sets differ more, depending on the hubs they meet). The kernels make sure on the device that
+        // the list is only used if this batch's messages fit and it still pays; else the hop is pulled or pushed.
         uint32_t pair_cap = 0;
-        if (may_pull && !wsum && !sparse && c->pair_cap && c->opt_sorted && !(c->layers[l - 1].proj && c->layers[l - 1].packed)) {
+        if (l >= 2 && !wsum && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3 && c->n_cap <= RP_LIST_BUCKETS * RP_LIST_IDS) {
+            const uint64_t m = c->last_m[l];
+            const bool pulls = c->opt_scatter == 2 || m * c->xw[l] * 4ull * (unsigned)c->opt_pull_ratio >= 8ull * c->last_isum[l];
             if (c->opt_sorted == 2) pair_cap = c->pair_cap;
-            else if (c->hints_valid && c->last_m[l] && rp_sorted_pays(c->last_m[l], c->last_isum[l]) &&
-                     (c->last_hop_mode[l] == 1u + RP_HOP_PULL || c->last_hop_mode[l] == 1u + RP_HOP_SORTED)) {
-                const uint64_t want = ((uint64_t)c->last_m[l] + c->last_m[l] / 4 + 4096) & ~4095ull;
-                if (want <= c->pair_cap) pair_cap = (uint32_t)want;
+            else if (c->hints_valid && m && c->last_hop_mode[l] != 1u + RP_HOP_DISCOVER &&
+                     (pulls ? rp_list_pays_pull(m, c->last_isum[l]) : m * c->xw[l] >= RP_LIST_NUMBERS)) {
+                const uint64_t want = ((pulls ? m + m / 4 : 4 * m) + 4096) & ~4095ull;
+                if (pulls ? want <= c->pair_cap : m <= c->pair_cap) pair_cap = (uint32_t)std::min<uint64_t>(want, c->pair_cap);
             }
         }
         if (sparse) rp_launch_frontier_sparse(c, l, layer_self(c, l), l < c->L);
@@ -1138,8 +1131,8 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_timer_end(c, t, RIPPLE_PH_COMPACT, (int)l);
         }
         t = rp_timer_begin(c);
-        if (!wsum && (c->opt_scatter < 2 || !may_pull)) rp_launch_scatter_push(c, l, may_pull, may_disc);
-        if (pair_cap && !rp_launch_scatter_sorted(c, l, may_disc, pair_cap)) pair_cap = 0;
+        if (!wsum && (c->opt_scatter < 2 || !may_pull)) rp_launch_scatter_push(c, l, may_pull, may_disc, pair_cap);
+        if (pair_cap) rp_launch_scatter_list(c, l, may_disc, pair_cap);
         if (may_pull) rp_launch_scatter_pull(c, l, false, may_disc, pair_cap);
         rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);
         t = rp_timer_begin(c);

@@ -59,7 +59,11 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t hop_mode[RIPPLE_MAX_LAYERS + 1]; // 1 + RP_HOP_* of the scatter kernel that moved hop l's messages (0: none ran)
     uint32_t range_rows;                      // attention layers: rows updated from sums that were not finite
     uint32_t pull_next[RIPPLE_MAX_LAYERS + 1];// pull scatter of hop l: runs of chunks handed out so far
+    uint32_t pair_over[RIPPLE_MAX_LAYERS + 1];// a bucket of hop l's messages had no room for all of its own
 };
+// buckets of a hop's messages: at most this many, each of at most this many consecutive vertices
+#define RP_LIST_BUCKETS 8192u
+#define RP_LIST_IDS 4096u
 #define RP_CTR_WORDS ((uint32_t)(sizeof(DevCtr) / 4))
 #define RP_CTR_BATCH ((uint32_t)(offsetof(DevCtr, set) / 4))   // first word that is zero when a batch begins
 
@@ -223,13 +227,11 @@ struct ripple_ctx {
     uint32_t last_m[RIPPLE_MAX_LAYERS + 1] = {0};       // messages per hop of the last batch (a size hint)
     uint32_t last_isum[RIPPLE_MAX_LAYERS + 1] = {0};    // in-row entries a pull of that hop would have scanned
     uint32_t last_hop_mode[RIPPLE_MAX_LAYERS + 1] = {0};// 1 + RP_HOP_* of the kernel that moved that hop's messages
-    // messages of a hop as (destination, source) pairs, as the out-edge walk lists them and sorted by destination
-    uint32_t *pk_a = nullptr, *pk_b = nullptr, *pv_a = nullptr, *pv_b = nullptr;
-    uint32_t pair_cap = 0;
-    void *pair_tmp = nullptr;
-    size_t pair_tmp_bytes = 0;
-    unsigned pair_bits = 32;                            // key bits that tell vertex ids and the filler key apart
-    int opt_sorted = 1;                                 // 0 never, 1 where the last batch says it pays, 2 wherever a hop is pulled
+    // messages of a hop as (destination, source) pairs in buckets by destination (k_frontier_list), and how many each holds
+    uint2 *pairs = nullptr, *pair_sorted = nullptr;     // ... and in order of destination
+    uint32_t *pair_cnt = nullptr;                       // (zero between hops)
+    uint32_t pair_cap = 0;                              // messages a listed hop may have; there is room for twice as many
+    int opt_sorted = 1;                                 // 0 never, 1 where the last batch says it pays, 2 wherever it can be
     uint32_t last_n_ops = 0;                            // operations of the last single-piece batch    // candidates of the last batch's max / min hops (a size hint)
     bool last_from_rep = false;
     bool push_margin[RIPPLE_MAX_LAYERS + 1] = {false};  // last batch pushed at this hop by a wide margin
@@ -464,7 +466,7 @@ __device__ __forceinline__ float rp_msg_decode_col(uint2 c, uint32_t col) {
 #define RP_HOP_PUSH 0
 #define RP_HOP_PULL 1
 #define RP_HOP_DISCOVER 2
-#define RP_HOP_SORTED 3                 // a pull whose messages were listed by the out-edge walk and sorted by destination (reported only)
+#define RP_HOP_SORTED 3                 // from the list of the hop's messages, sorted by destination (reported only)
 __device__ __forceinline__ int rp_hop_mode(const DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio, int allow_disc) {
     const unsigned long long m = ctr->set[l - 1].m;
     if (allow_disc && m > 0 && (mode == 3 || ((mode == 0 || mode == 4) && m * 8ull >= ctr->n_edges))) return RP_HOP_DISCOVER;
@@ -473,17 +475,18 @@ __device__ __forceinline__ int rp_hop_mode(const DevCtr *ctr, uint32_t l, uint32
     return (m > 0 && m * d * 4ull * (unsigned long long)ratio >= 8ull * ctr->isum[l]) ? RP_HOP_PULL : RP_HOP_PUSH;
 }
 
-// A hop that would be pulled is taken from the sorted list of its messages instead when the list was made (M fits
-// the `cap` entries the host sorted) and it pays (force: whenever the list was made): sorting a pair costs about as
-// much as eight tests of an in-neighbour, and the sort's launches as much as six million of them, so the in-rows
-// that a pull would scan have to hold more than 8 M + 6 * 2^20 entries. M: out-edges of A_{l-1}.
-#define RP_SORTED_FACTOR 8ull
-#define RP_SORTED_FIXED (6ull << 20)
-static inline bool rp_sorted_pays(unsigned long long m, unsigned long long in_entries) {
-    return RP_SORTED_FACTOR * m + RP_SORTED_FIXED <= in_entries;
-}
-__device__ __forceinline__ bool rp_hop_sorted(const DevCtr *ctr, uint32_t l, uint32_t M, uint32_t cap, int force) {
-    return cap && M > 0 && M <= cap && (force || RP_SORTED_FACTOR * M + RP_SORTED_FIXED <= ctr->isum[l]);
+// A hop is taken from the list of its messages instead when the list was made (M fits the `cap` entries the host expected, no bucket
+// has run over) and it pays (force: whenever the list was made). M: out-edges of A_{l-1}. In place of a pull: writing a message down and
+// putting it in its place costs about what RP_LIST_FACTOR tests of an in-neighbour cost, and the launches what RP_LIST_FIXED of them cost. In
+// place of a push: the M * d float atomics take longer from RP_LIST_NUMBERS on.
+#define RP_LIST_FACTOR 4ull
+#define RP_LIST_FIXED (2ull << 20)
+#define RP_LIST_NUMBERS (16ull << 20)
+static inline bool rp_list_pays_pull(unsigned long long m, unsigned long long in_entries) { return RP_LIST_FACTOR * m + RP_LIST_FIXED <= in_entries; }
+__device__ __forceinline__ bool rp_hop_listed(const DevCtr *ctr, uint32_t l, uint32_t d, uint32_t M, uint32_t cap, int force, int hop_mode) {
+    if (!cap || M == 0 || M > cap || ctr->pair_over[l] || hop_mode == RP_HOP_DISCOVER) return false;
+    if (force) return true;
+    return hop_mode == RP_HOP_PULL ? RP_LIST_FACTOR * M + RP_LIST_FIXED <= ctr->isum[l] : (unsigned long long)M * d >= RP_LIST_NUMBERS;
 }
 
 // position of `target` in row[0..len), searched by one wavefront; -1 when absent. Rows begin at multiples of four entries and

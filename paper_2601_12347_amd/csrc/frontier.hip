@@ -11,25 +11,61 @@
 
 #define RP_STATIC_BLOCKS 16384u                  // entries of the static array (see below): blocks a compaction may have
 
-// The walk that also lists the hop's messages as (destination, source) pairs for the sorted scatter: pair_cap entries
-// will be sorted, so the list is written only if the hop's out-edges fit, and the entries behind them get the key
-// that sorts last.
-__global__ __launch_bounds__(256) void k_frontier_mark_pairs(const uint32_t *list, const uint32_t *count_ptr,
-                                                             const uint32_t *eoff, const uint2 *out_meta,
-                                                             const uint32_t *out_pool, uint8_t *mk, const DevCtr *ctr,
-                                                             uint32_t l, uint32_t d, int mode, int ratio, int allow_disc,
-                                                             uint32_t *pk, uint32_t *pv, uint32_t pair_cap) {
+// The walk that also lists the hop's messages: (destination, source) pairs in buckets by destination, each with room of its own, for
+// k_scatter_list. A workgroup holds 16 K edges in registers, counts its share of every bucket in LDS, takes that much room at once and writes.
+// `cap`: the messages the host expects at most; a hop with more is marked only.
+// In place of a list in edge order and a radix sort of it (4.6 M pairs: 0.09 ms for the walk, 0.24 for the sort and its launches; here 0.117
+// for the walk and 0.036 for k_list_order).
+#define LIST_C 4
+struct ListWalk {
+    uint2 *pairs;
+    uint32_t *cnt;
+    ListCut cut;
+    uint32_t cap;
+};
+__global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff, const uint2 *out_meta,
+                                                        const uint32_t *out_pool, uint8_t *mk, DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio,
+                                                        int allow_disc, ListWalk w) {
     if (allow_disc && rp_hop_mode(ctr, l, d, mode, ratio, allow_disc) == RP_HOP_DISCOVER) return;
-    const uint32_t count = *count_ptr;
+    constexpr uint32_t NONE = 0xFFFFFFFFu, FULL = 0xFF000000u;
+    __shared__ uint32_t s_at[RP_LIST_BUCKETS];              // per bucket: this tile's pairs, then where the next one goes
+    const uint32_t count = *count_ptr, wave = threadIdx.x >> 6;
     const uint32_t M = count ? count_ptr[1] : 0u;
-    if (M == 0 || M > pair_cap) {
-        frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
-                         (gridDim.x * blockDim.x) >> 6);
+    if (M == 0 || M > w.cap) {
+        frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), blockIdx.x * 16u + wave, gridDim.x * 16u);
         return;
     }
-    frontier_walk<false, true>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
-                               (gridDim.x * blockDim.x) >> 6, pk, pv);
-    for (uint32_t i = M + blockIdx.x * blockDim.x + threadIdx.x; i < pair_cap; i += gridDim.x * blockDim.x) pk[i] = 0xFFFFFFFFu;
+    constexpr uint32_t TILE = 16u * LIST_C;                 // chunks of a workgroup
+    const uint32_t n_tiles = (M + TILE * MARK_CHUNK - 1) / (TILE * MARK_CHUNK);
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        for (uint32_t b = threadIdx.x; b < w.cut.n; b += 1024u) s_at[b] = 0;
+        uint32_t v[4 * LIST_C], u[4 * LIST_C];
+        walk_collect<LIST_C>(list, count, M, eoff, out_meta, out_pool, tile * TILE + wave * LIST_C, v, u);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 4 * LIST_C; ++t)
+            if (v[t] != NONE) {
+                mk[v[t]] = 1;
+                atomicAdd(&s_at[v[t] >> w.cut.shift], 1u);
+            }
+        __syncthreads();
+        for (uint32_t b = threadIdx.x; b < w.cut.n; b += 1024u) {
+            const uint32_t n = s_at[b];
+            if (!n) continue;
+            const uint32_t at = atomicAdd(&w.cnt[b], n);
+            const bool fits = at + n <= w.cut.room;
+            if (!fits) ctr->pair_over[l] = 1;               // the hop is pushed or pulled
+            s_at[b] = fits ? b * w.cut.room + at : FULL;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 4 * LIST_C; ++t)
+            if (v[t] != NONE) {
+                const uint32_t at = atomicAdd(&s_at[v[t] >> w.cut.shift], 1u);
+                if (at < FULL) w.pairs[at] = make_uint2(v[t], u[t]);
+            }
+        __syncthreads();
+    }
 }
 
 __global__ __launch_bounds__(256) void k_frontier_mark(const uint32_t *list, const uint32_t *count_ptr,
@@ -414,9 +450,9 @@ __global__ __launch_bounds__(1024) void k_list_eoff(const uint32_t *list, const 
 
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     if (pair_cap) {
-        hipLaunchKernelGGL(k_frontier_mark_pairs, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1],
-                           &c->ctr->set[l - 1].a, c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l],
-                           rp_layer_mode(c, l), c->opt_pull_ratio, allow_disc ? 1 : 0, c->pk_a, c->pv_a, pair_cap);
+        const ListWalk w = {c->pairs, c->pair_cnt, rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap), pair_cap};
+        hipLaunchKernelGGL(k_frontier_list, dim3(c->n_cu * 2), dim3(1024), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->eoff[l - 1],
+                           c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], rp_layer_mode(c, l), c->opt_pull_ratio, allow_disc ? 1 : 0, w);
         return;
     }
     hipLaunchKernelGGL(k_frontier_mark, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,

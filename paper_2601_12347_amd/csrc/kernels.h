@@ -17,9 +17,6 @@ void rp_launch_mutate(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, b
 // order.hip
 ripple_status rp_stable_sort_pairs(ripple_ctx *c, const uint32_t *keys_in, uint32_t *keys_out, const uint32_t *vals_in,
                                    uint32_t *vals_out, size_t n, unsigned key_bits);
-size_t rp_sort_u32_tmp_bytes(size_t n_max);
-bool rp_sort_pairs_u32(ripple_ctx *c, const uint32_t *keys_in, uint32_t *keys_out, const uint32_t *vals_in, uint32_t *vals_out,
-                       size_t n, unsigned key_bits, void *tmp, size_t tmp_bytes);
 
 // frontier.hip
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap = 0);
@@ -40,10 +37,15 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term);
 void rp_launch_small_addend(ripple_ctx *c, uint32_t l, bool emit_delta);   // transform.hip
 
 // scatter.hip
-void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc);
+void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc, uint32_t pair_cap = 0);
 void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap);
 void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow_disc, uint32_t pair_cap = 0);
-bool rp_launch_scatter_sorted(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap);
+// buckets of the lists of a hop of about `messages` messages: a bucket is the vertices that agree in id >> shift
+struct ListCut {
+    uint32_t n, shift, room;                             // buckets, their width, entries each has room for
+};
+ListCut rp_list_cut(const ripple_ctx *c, uint32_t messages);
+void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap);
 void rp_launch_pull_all(ripple_ctx *c, uint32_t l);
 void rp_launch_messages(ripple_ctx *c, uint32_t l);
 void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr, bool listed);

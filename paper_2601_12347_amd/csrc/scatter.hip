@@ -24,15 +24,20 @@ template <int NJ, int PK>
 __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, const uint32_t *count_ptr,
                                                       const uint32_t *eoff, const float *D, uint32_t ldd, uint32_t d,
                                                       const uint2 *out_meta, const uint32_t *out_pool, float *X,
-                                                      DevCtr *ctr, uint32_t l, int may_pull, int mode, int ratio, int allow_disc) {
+                                                      DevCtr *ctr, uint32_t l, int may_pull, int mode, int ratio, int allow_disc,
+                                                      uint32_t list_cap, int list_force) {
     const int hm = rp_hop_mode(ctr, l, d, mode, ratio, allow_disc);
     if (hm == RP_HOP_DISCOVER || (may_pull && hm == RP_HOP_PULL)) return;
+    if (list_cap) {
+        const uint32_t cp = *count_ptr;
+        if (rp_hop_listed(ctr, l, d, cp ? count_ptr[1] : 0u, list_cap, list_force, hm)) return;
+    }
     if (*count_ptr && blockIdx.x == 0 && threadIdx.x == 0) ctr->hop_mode[l] = 1u + RP_HOP_PUSH;
     push_edges<NJ, PK>(list, count_ptr, eoff, D, nullptr, ldd, d, out_meta, out_pool, X, (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
                        (gridDim.x * blockDim.x) >> 6);
 }
 
-void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc) {
+void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc, uint32_t pair_cap) {
     const bool proj = c->layers[l - 1].proj != 0;           // project-first: messages are already d_out wide
     const uint32_t d = c->xw[l];
     const bool packed = proj && c->layers[l - 1].packed;
@@ -42,7 +47,7 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
 #define PUSH_CASE_PK(NJ, PK)                                                                                       \
     hipLaunchKernelGGL((k_scatter_push<NJ, PK>), grid, block, 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,     \
                        c->eoff[l - 1], D, ldd, d, c->out_meta, c->out_pool, c->X[l], c->ctr, l, may_pull ? 1 : 0,  \
-                       c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0)
+                       c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0, pair_cap, c->opt_sorted == 2 ? 1 : 0)
 #define PUSH_CASE(NJ) PUSH_CASE_PK(NJ, 0)
     if (packed) PUSH_CASE_PK(1, 1);
     else if (d <= 64) PUSH_CASE(1);
@@ -80,14 +85,17 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
 // message, and the sum replaces the row. The hop is always pulled.
 //
 // WT = 1: every message is multiplied by its edge's weight (weighted sum, m = alpha (h - h_old), Sec. 3.3.3)
+__device__ __forceinline__ bool pull_is_listed(const PullArgs &a) {
+    if (!a.sorted_cap) return false;
+    const uint32_t cp = *a.m_count;
+    return rp_hop_listed(a.ctr, a.l, a.d, cp ? a.m_count[1] : 0u, a.sorted_cap, a.sorted_force, RP_HOP_PULL);
+}
+
 template <int NJ, int DISC, int WT, int DET>
 __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     static_assert(!DET || (!DISC && !WT), "the deterministic form pulls into A_l, unweighted");
     if (!DET && rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL)) return;
-    if (!DET && !DISC && a.sorted_cap) {
-        const uint32_t cp = *a.m_count;
-        if (rp_hop_sorted(a.ctr, a.l, cp ? a.m_count[1] : 0u, a.sorted_cap, a.sorted_force)) return;
-    }
+    if (!DET && !DISC && pull_is_listed(a)) return;
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
@@ -263,31 +271,106 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
 // The same hop from the list of its messages. A pull finds the messages by testing every in-neighbour of every vertex
 // of A_l against the bitmap of A_{l-1}; when few of them carry a message (hop 2 of a large batch on the dense
 // graph: 4.6 M of 110 M), those tests, each a request to the L2 that a compute unit can only have so many of in
-// flight, are most of the hop. The out-edge walk that marks A_l has every message in its hands, so it writes them
-// down as (destination, source) pairs (k_frontier_mark_pairs), a radix sort (rocPRIM) puts them in destination
-// order, and this kernel is the pull's inner part over that list: every wavefront takes a contiguous run of pairs,
-// gathers the sources' delta rows G at a time, sums while the destination stays and sends one row of atomic
-// additions per destination and wavefront. The host sorts `cap` entries, a number it takes from the previous batch;
-// whether the list is used is decided here, like the hop's mode, from the hop's own counters.
-struct SortedArgs {
-    const uint32_t *pk, *pv;       // sorted: destination, source
+// flight, are most of the hop; a push adds every number with an atomic of its own. The out-edge walk that marks A_l has every message
+// in its hands and writes it down as a (destination, source) pair in the bucket of its destination (k_frontier_list); k_list_order puts
+// every bucket's pairs in order, one bucket's behind the other's; and this kernel is the pull's inner part over that list: every
+// wavefront takes a contiguous run of pairs, gathers the sources' rows G at a time and sums while the destination stays.
+// Measured: hop 2 of 10,000 updates on the dense graph (4.6 M messages of 1 KB to 1.5 M rows) 0.33 ms for walk and list (pairs in edge
+// order, then a radix sort) + 1.02 -> 0.15 + 1.02; hop 3 of 100 updates (3 M packed messages to 1 M rows) 0.48 (pushed) -> 0.07 + 0.18.
+// A workgroup per bucket that orders it in LDS and sums it at once took 1.23 ms and 0.28 ms for the second part: while it
+// orders, nothing is on its way.
+struct ListArgs {
+    const uint2 *pairs;
+    uint2 *sorted;
+    uint32_t *cnt;
+    ListCut cut;
     const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
     uint32_t cap;
     int force;
     const float *D;
     uint32_t ldd, d;
+    uint32_t msg_bytes;            // packed messages: size of the table in bytes, below 4 GB
     float *X;
     DevCtr *ctr;
     uint32_t l;
     int mode, ratio, allow_disc;
 };
 
-template <int NJ>
-__global__ __launch_bounds__(256) void k_scatter_sorted(SortedArgs a) {
-    if (rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != RP_HOP_PULL) return;
+// Whether the hop was listed at all (M: its messages), and whether the list is what moves them
+__device__ __forceinline__ bool list_is_used(const ListArgs &a, uint32_t &M, bool &made) {
     const uint32_t cp = *a.m_count;
-    const uint32_t M = cp ? a.m_count[1] : 0u;
-    if (!rp_hop_sorted(a.ctr, a.l, M, a.cap, a.force)) return;
+    M = cp ? a.m_count[1] : 0u;
+    const int hm = rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc);
+    made = M > 0 && M <= a.cap && hm != RP_HOP_DISCOVER;
+    return rp_hop_listed(a.ctr, a.l, a.d, M, a.cap, a.force, hm);
+}
+
+// A workgroup per bucket: its pairs counted per destination in LDS, then put in place behind the pairs of the buckets before it. The order
+// within a destination is that in which the pairs come up.
+__global__ __launch_bounds__(256) void k_list_order(ListArgs a) {
+    uint32_t M;
+    bool made;
+    if (!list_is_used(a, M, made)) return;
+    __shared__ uint32_t s_at[RP_LIST_IDS];
+    __shared__ uint32_t s_sum[4], s_before[4];
+    constexpr int PER = 8;
+    const uint32_t tid = threadIdx.x, bucket = blockIdx.x, ids = 1u << a.cut.shift, mask = ids - 1u;
+    const uint32_t n = a.cnt[bucket];
+    uint32_t before = 0;
+    for (uint32_t b = tid; b < bucket; b += 256u) before += a.cnt[b];
+    const uint2 *from = a.pairs + (size_t)bucket * a.cut.room;
+    for (uint32_t i = tid; i < ids; i += 256u) s_at[i] = 0;
+    __syncthreads();
+    for (uint32_t c0 = tid; c0 < n; c0 += 256u * PER) {
+        uint32_t v[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) v[k] = from[min(c0 + 256u * k, n - 1u)].x;
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (c0 + 256u * k < n) atomicAdd(&s_at[v[k] & mask], 1u);
+    }
+    __syncthreads();
+    const uint32_t per = (ids + 255u) / 256u, i0 = min(ids, tid * per), i1 = min(ids, i0 + per);
+    uint32_t mine = 0;
+    for (uint32_t i = i0; i < i1; ++i) mine += s_at[i];
+    const uint32_t incl = rp_wave_scan(mine);
+    before = rp_wave_scan(before);
+    if ((tid & 63u) == 63u) {
+        s_sum[tid >> 6] = incl;
+        s_before[tid >> 6] = before;
+    }
+    __syncthreads();
+    uint32_t at = s_before[0] + s_before[1] + s_before[2] + s_before[3] + incl - mine;
+    for (uint32_t w = 0; w < (tid >> 6); ++w) at += s_sum[w];
+    for (uint32_t i = i0; i < i1; ++i) {
+        const uint32_t n_i = s_at[i];
+        s_at[i] = at;
+        at += n_i;
+    }
+    __syncthreads();
+    for (uint32_t c0 = tid; c0 < n; c0 += 256u * PER) {
+        uint2 p[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) p[k] = from[min(c0 + 256u * k, n - 1u)];
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (c0 + 256u * k < n) a.sorted[atomicAdd(&s_at[p[k].x & mask], 1u)] = p[k];
+    }
+}
+
+// the buckets' counts cleared for the next hop that is listed
+__device__ __forceinline__ void list_clear(const ListArgs &a) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < a.cut.n) a.cnt[i] = 0;
+}
+
+template <int NJ>
+__global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
+    uint32_t M;
+    bool made;
+    const bool used = list_is_used(a, M, made);
+    if (made) list_clear(a);
+    if (!used) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_SORTED;
     constexpr int G = (NJ >= 8) ? 2 : (NJ == 4 ? 4 : 8 / NJ);   // message rows per round trip (and up to as many destination rows)
     constexpr uint32_t NONE = 0xFFFFFFFFu;
@@ -303,7 +386,7 @@ __global__ __launch_bounds__(256) void k_scatter_sorted(SortedArgs a) {
     // float atomics costs the L2 one operation per number: 1.5 M rows of 256 took 0.9 ms that way, more than the
     // gathers). Only the destinations of the run's first and last pair can have pairs in a neighbour's run; their sums
     // go to memory as atomic additions.
-    const uint32_t v_first = a.pk[c_begin * 64u], v_last = a.pk[min(M, c_end * 64u) - 1u];
+    const uint32_t v_first = a.sorted[c_begin * 64u].x, v_last = a.sorted[min(M, c_end * 64u) - 1u].x;
     uint32_t cur = NONE;
     float acc[NJ];
 #pragma unroll
@@ -321,13 +404,12 @@ __global__ __launch_bounds__(256) void k_scatter_sorted(SortedArgs a) {
         }
     };
     uint32_t e = c_begin * 64u + lane;
-    uint32_t nv = (e < M) ? a.pk[e] : NONE, nu = (e < M) ? a.pv[e] : 0u;
+    uint2 nx = (e < M) ? a.sorted[e] : make_uint2(NONE, 0u);
     for (uint32_t c = c_begin; c < c_end; ++c) {
-        const uint32_t my_v = nv, my_u = nu;
+        const uint2 my = nx;
         const uint32_t n = min(64u, M - c * 64u);
         e += 64u;                                            // the next chunk's pairs are on their way during the gathers
-        nv = (c + 1 < c_end && e < M) ? a.pk[e] : NONE;
-        nu = (c + 1 < c_end && e < M) ? a.pv[e] : 0u;
+        nx = (c + 1 < c_end && e < M) ? a.sorted[e] : make_uint2(NONE, 0u);
         for (uint32_t k0 = 0; k0 < n; k0 += G) {
             float r[G][NJ], rx[G][NJ];
             uint32_t vk[G];
@@ -335,8 +417,8 @@ __global__ __launch_bounds__(256) void k_scatter_sorted(SortedArgs a) {
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const int k = (int)min(k0 + g, 63u);
-                const uint32_t uk = (uint32_t)__builtin_amdgcn_readlane((int)my_u, k);
-                vk[g] = (uint32_t)__builtin_amdgcn_readlane((int)my_v, k);
+                const uint32_t uk = (uint32_t)__builtin_amdgcn_readlane((int)my.y, k);
+                vk[g] = (uint32_t)__builtin_amdgcn_readlane((int)my.x, k);
                 const bool live = k0 + g < n;
                 const bool own = live && vk[g] != prev && vk[g] != v_first && vk[g] != v_last;   // first pair of an unshared destination
                 prev = vk[g];
@@ -382,6 +464,7 @@ template <int DISC, int WT, int DET>
 __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     static_assert(!DET || (!DISC && !WT), "the deterministic form pulls into A_l, unweighted");
     if (!DET && rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL)) return;
+    if (!DET && !DISC && pull_is_listed(a)) return;
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
@@ -580,6 +663,106 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
         for (; run < a.side_runs; run += nw) a.side_v[2 * run] = a.side_v[2 * run + 1] = NONE;
 }
 
+// The list of a hop's messages (see k_scatter_list) where they are packed rows: four at a time, 16 lanes each, like k_scatter_pull4. The
+// destination's row, if no other run has pairs of it, is read with its first message and stored with the sum.
+__global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
+    uint32_t M;
+    bool made;
+    const bool used = list_is_used(a, M, made);
+    if (made) list_clear(a);
+    if (!used) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_SORTED;
+    constexpr uint32_t NONE = 0xFFFFFFFFu;
+    const int lane = rp_lane();
+    const uint32_t d = a.d, grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
+    const uint32_t n_chunks = (M + 63u) / 64u;
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t per = (n_chunks + nw - 1) / nw;
+    const uint32_t c_begin = min(n_chunks, gw * per), c_end = min(n_chunks, c_begin + per);
+    if (c_begin >= c_end) return;
+    const __amdgpu_buffer_rsrc_t mres = __builtin_amdgcn_make_buffer_rsrc((void *)a.D, 0, a.msg_bytes, 0x00020000u);
+    const uint32_t my_col = 16u * grp + sub;                // the column this lane sends to memory
+    const bool sends = grp < 3u && my_col < d, has2 = 32u + sub < d;
+    const uint32_t v_first = a.sorted[c_begin * 64u].x, v_last = a.sorted[min(M, c_end * 64u) - 1u].x;
+    uint32_t cur = NONE;
+    float acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;            // this group's partial sums of columns sub, 16 + sub, 32 + sub
+    auto flush = [&]() {
+        acc0 += __shfl_xor(acc0, 16);
+        acc1 += __shfl_xor(acc1, 16);
+        acc2 += __shfl_xor(acc2, 16);
+        acc0 += __shfl_xor(acc0, 32);
+        acc1 += __shfl_xor(acc1, 32);
+        acc2 += __shfl_xor(acc2, 32);
+        const float mine = grp == 0u ? acc0 : (grp == 1u ? acc1 : acc2);
+        if (sends) {
+            float *x = &a.X[(size_t)cur * d + my_col];
+            if (cur != v_first && cur != v_last) *x = mine;
+            else if (mine != 0.0f) unsafeAtomicAdd(x, mine);
+        }
+        acc0 = acc1 = acc2 = 0.0f;
+    };
+    uint32_t e = c_begin * 64u + lane;
+    uint2 nx = (e < M) ? a.sorted[e] : make_uint2(PULL4_PAD, 0u);
+    uint32_t before = NONE;                                 // the destination of the pair before the chunk
+    for (uint32_t c = c_begin; c < c_end; ++c) {
+        const uint2 my = nx;
+        const uint32_t n = min(64u, M - c * 64u);
+        e += 64u;
+        nx = (c + 1 < c_end && e < M) ? a.sorted[e] : make_uint2(PULL4_PAD, 0u);
+        // which pairs are the first of a destination that nobody else writes
+        uint32_t left = (uint32_t)__shfl_up((int)my.x, 1);
+        left = lane == 0 ? before : left;
+        const uint32_t first = my.x != left && my.x != v_first && my.x != v_last && my.x != PULL4_PAD ? 1u : 0u;
+        before = (uint32_t)__shfl((int)my.x, 63);
+        for (uint32_t k0 = 0; k0 < n; k0 += 4u * PULL4_QUADS) {
+            uint32_t v[PULL4_QUADS];
+            uint2 ch[PULL4_QUADS];
+            float x[PULL4_QUADS][3];
+#pragma unroll
+            for (int r = 0; r < PULL4_QUADS; ++r) {
+                const int idx = (int)(k0 + 4u * r + grp);    // below 64; past the list's end: row 0, no destination
+                const uint32_t u = (uint32_t)__shfl((int)my.y, idx);
+                v[r] = (uint32_t)__shfl((int)my.x, idx);
+                const bool own = __shfl((int)first, idx) != 0;
+                const uintx2 w2 = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(mres, (u << 7) + 8u * sub, 0, 0));
+                ch[r] = make_uint2(w2.x, w2.y);
+                const float *xr = a.X + (size_t)v[r] * d + sub;
+                x[r][0] = own ? xr[0] : 0.0f;
+                x[r][1] = own ? xr[16] : 0.0f;
+                x[r][2] = own && has2 ? xr[32] : 0.0f;
+            }
+#pragma unroll
+            for (int r = 0; r < PULL4_QUADS; ++r) {
+                if (k0 + 4u * r >= n) continue;
+                float q0, q1, q2, f;
+                rp_msg_decode_parts(ch[r], q0, q1, q2, f);
+                if (!__any(v[r] != cur)) {                   // the whole quad goes on
+                    acc0 = __builtin_fmaf(q0, f, acc0);
+                    acc1 = __builtin_fmaf(q1, f, acc1);
+                    acc2 = __builtin_fmaf(q2, f, acc2);
+                } else {                                     // pair by pair
+#pragma unroll
+                    for (uint32_t g = 0; g < 4u; ++g) {
+                        const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)v[r], 16 * (int)g);
+                        if (vg != PULL4_PAD) {
+                            if (vg != cur) {
+                                if (cur != NONE) flush();
+                                cur = vg;
+                            }
+                            if (grp == g) {                  // (x is zero but for an unshared destination's first message)
+                                acc0 += __builtin_fmaf(q0, f, x[r][0]);
+                                acc1 += __builtin_fmaf(q1, f, x[r][1]);
+                                acc2 += __builtin_fmaf(q2, f, x[r][2]);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+    }
+    if (cur != NONE) flush();
+}
+
 // Deterministic mode, after a DET pull: the side entries (two per run of chunks, in run order; entries of one
 // destination are neighbours, apart from empty ones between them) are added up per destination in that order
 // and the sum is added to the row, or replaces it if the row is recomputed. One wavefront per entry and block of 64
@@ -705,34 +888,49 @@ void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow
 #undef PULL_CASE
 }
 
-// Sorts the pairs the out-edge walk wrote (pair_cap entries; the filler key sorts last) and enqueues the kernel that
-// scatters from the sorted list. False, and nothing enqueued, if the sort could not be set up: the caller then has
-// to launch the pull without a list (pair_cap 0).
-bool rp_launch_scatter_sorted(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
-    if (!rp_sort_pairs_u32(c, c->pk_a, c->pk_b, c->pv_a, c->pv_b, pair_cap, c->pair_bits, c->pair_tmp, c->pair_tmp_bytes)) return false;
+// About a thousand messages per bucket, so that a workgroup takes most of them in one round, and at most RP_LIST_IDS vertices (graphs of more
+// than RP_LIST_BUCKETS times that have no lists)
+ListCut rp_list_cut(const ripple_ctx *c, uint32_t messages) {
+    uint32_t bits = 0, want = 8;
+    while ((1ull << bits) < c->n_cap) ++bits;
+    while ((1u << want) < RP_LIST_BUCKETS && ((messages >> want) > 1024u || (RP_LIST_IDS << want) < c->n_cap)) ++want;
+    ListCut cut;
+    cut.shift = bits > want ? bits - want : 0u;
+    cut.n = ((c->n_cap - 1u) >> cut.shift) + 1u;
+    cut.room = 2u * c->pair_cap / cut.n;
+    return cut;
+}
+
+// From the list that k_frontier_list has made (the same pair_cap): nothing happens if it was not made or does not pay.
+void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     const LayerDev &ly = c->layers[l - 1];
-    SortedArgs a;
-    a.pk = c->pk_b;
-    a.pv = c->pv_b;
+    const bool packed = ly.proj && ly.packed;
+    ListArgs a;
+    a.pairs = c->pairs;
+    a.sorted = c->pair_sorted;
+    a.cnt = c->pair_cnt;
+    a.cut = rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap);
     a.m_count = &c->ctr->set[l - 1].a;
     a.cap = pair_cap;
     a.force = c->opt_sorted == 2;
-    a.D = ly.proj ? c->PD : c->D[(l - 1) & 1];
+    a.D = packed ? (const float *)c->MSG : (ly.proj ? c->PD : c->D[(l - 1) & 1]);
     a.d = c->xw[l];
     a.ldd = ly.proj ? c->pd_ld : a.d;
+    a.msg_bytes = (uint32_t)(c->n_cap * (RP_MSG_WORDS * 4u));
     a.X = c->X[l];
     a.ctr = c->ctr;
     a.l = l;
     a.mode = rp_layer_mode(c, l);
     a.ratio = c->opt_pull_ratio;
     a.allow_disc = allow_disc ? 1 : 0;
-    dim3 grid(c->n_cu * 8), block(256);
-    if (a.d <= 64) hipLaunchKernelGGL((k_scatter_sorted<1>), grid, block, 0, c->stream, a);
-    else if (a.d <= 128) hipLaunchKernelGGL((k_scatter_sorted<2>), grid, block, 0, c->stream, a);
-    else if (a.d <= 256) hipLaunchKernelGGL((k_scatter_sorted<4>), grid, block, 0, c->stream, a);
-    else if (a.d <= 512) hipLaunchKernelGGL((k_scatter_sorted<8>), grid, block, 0, c->stream, a);
-    else hipLaunchKernelGGL((k_scatter_sorted<16>), grid, block, 0, c->stream, a);
-    return true;
+    hipLaunchKernelGGL(k_list_order, dim3(a.cut.n), dim3(256), 0, c->stream, a);
+    const dim3 grid(c->n_cu * 8), block(256);
+    if (packed) hipLaunchKernelGGL(k_scatter_list4, grid, block, 0, c->stream, a);
+    else if (a.d <= 64) hipLaunchKernelGGL((k_scatter_list<1>), grid, block, 0, c->stream, a);
+    else if (a.d <= 128) hipLaunchKernelGGL((k_scatter_list<2>), grid, block, 0, c->stream, a);
+    else if (a.d <= 256) hipLaunchKernelGGL((k_scatter_list<4>), grid, block, 0, c->stream, a);
+    else if (a.d <= 512) hipLaunchKernelGGL((k_scatter_list<8>), grid, block, 0, c->stream, a);
+    else hipLaunchKernelGGL((k_scatter_list<16>), grid, block, 0, c->stream, a);
 }
 
 // Deterministic mode: the hop is pulled into A_l (bootstrap: into every live vertex, all of them recomputed;

@@ -120,12 +120,10 @@ __device__ __forceinline__ void sparse_enter(const SparseArgs &s, uint32_t v, bo
     sparse_enter_many<1>(s, one, from_edge);
 }
 
-// EMIT: edge e of the flattened out-edge space is also written down as the pair (destination, source) in pk[e], pv[e]
-template <bool SPARSE, bool EMIT = false>
+template <bool SPARSE>
 __device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff,
                                               const uint2 *out_meta, const uint32_t *out_pool, uint8_t *mk,
-                                              const SparseArgs &sp, uint32_t gw, uint32_t nw, uint32_t *pk = nullptr,
-                                              uint32_t *pv = nullptr) {
+                                              const SparseArgs &sp, uint32_t gw, uint32_t nw) {
     const uint32_t count = *count_ptr;
     if (count == 0) return;
     constexpr int T = MARK_CHUNK / 64;
@@ -139,11 +137,10 @@ __device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32
     if (c_begin >= c_end) return;
     const uint32_t last = count - 1;
     uint32_t i_lo = rp_seg_search_wave(eoff, 0, last, c_begin * chunk);
-    uint32_t rbase, bnd, rsrc = 0;                          // lane j: row i_lo + j
+    uint32_t rbase, bnd;                                    // lane j: row i_lo + j
     {
         const uint32_t ri = min(last, i_lo + lane);
-        rsrc = list[ri];
-        rbase = out_meta[rsrc].x - eoff[ri];                // pool position of edge e: rbase + e (mod 2^32)
+        rbase = out_meta[list[ri]].x - eoff[ri];                // pool position of edge e: rbase + e (mod 2^32)
         bnd = rp_row_end(eoff, count, M, i_lo + lane);
     }
     for (uint32_t c = c_begin; c < c_end; ++c) {
@@ -158,13 +155,6 @@ __device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32
                 const int r = (int)min(63u, rp_count_le(bnd, e));
                 const uint32_t base = __shfl(rbase, r);
                 v[t] = (e < e1) ? out_pool[base + e] : 0xFFFFFFFFu;
-                if (EMIT) {
-                    const uint32_t u = __shfl(rsrc, r);
-                    if (e < e1) {
-                        pk[e] = v[t];
-                        pv[e] = u;
-                    }
-                }
             }
             i_nx = min(last, i_lo + rp_count_le(bnd, e1));
         } else {
@@ -177,19 +167,14 @@ __device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32
                     const uint32_t i = rp_seg_search(eoff, i_lo, i_hi, e);
                     const uint32_t u = list[i];
                     v[t] = out_pool[out_meta[u].x + (e - eoff[i])];
-                    if (EMIT) {
-                        pk[e] = v[t];
-                        pv[e] = u;
-                    }
                 }
             }
             i_nx = rp_seg_forward(eoff, i_hi, last, e1);
         }
-        uint32_t rbase_n, bnd_n, rsrc_n;                    // next chunk's rows, requested before the marks
+        uint32_t rbase_n, bnd_n;                            // next chunk's rows, requested before the marks
         {
             const uint32_t ri = min(last, i_nx + lane);
-            rsrc_n = list[ri];
-            rbase_n = out_meta[rsrc_n].x - eoff[ri];
+            rbase_n = out_meta[list[ri]].x - eoff[ri];
             bnd_n = rp_row_end(eoff, count, M, i_nx + lane);
         }
         if (SPARSE) {
@@ -202,7 +187,41 @@ __device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32
         i_lo = i_nx;
         rbase = rbase_n;
         bnd = bnd_n;
-        rsrc = rsrc_n;
+    }
+}
+
+// Edges c0 * MARK_CHUNK .. (c0 + C) * MARK_CHUNK - 1 of the flattened out-edge space, four per lane and chunk: destination v (0xFFFFFFFF past
+// the end) and source u. By all 64 lanes; rows are found as in frontier_walk.
+template <int C>
+__device__ __forceinline__ void walk_collect(const uint32_t *list, uint32_t count, uint32_t M, const uint32_t *eoff, const uint2 *out_meta,
+                                             const uint32_t *out_pool, uint32_t c0, uint32_t (&v)[4 * C], uint32_t (&u)[4 * C]) {
+    const int lane = rp_lane();
+    const uint32_t last = count - 1;
+    uint32_t i_lo = c0 * MARK_CHUNK < M ? rp_seg_search_wave(eoff, 0, last, c0 * MARK_CHUNK) : 0u;
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const uint32_t e0 = (c0 + k) * MARK_CHUNK, e1 = min(M, e0 + MARK_CHUNK);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[4 * k + t] = 0xFFFFFFFFu;
+        if (e0 >= M) continue;                              // (the same for all lanes)
+        const uint32_t ri = min(last, i_lo + lane), rsrc = list[ri], rbase = out_meta[rsrc].x - eoff[ri], bnd = rp_row_end(eoff, count, M, i_lo + lane);
+        uint32_t i_hi = i_lo;
+        const bool fits = __shfl(bnd, 63) > e1 - 1;
+        if (!fits) i_hi = rp_seg_forward(eoff, i_lo, last, e1 - 1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t e = e0 + lane + 64 * t;
+            const int r = (int)min(63u, rp_count_le(bnd, e));
+            uint32_t src = __shfl(rsrc, r), at = __shfl(rbase, r) + e;
+            if (!fits && e < e1) {
+                const uint32_t i = rp_seg_search(eoff, i_lo, i_hi, e);
+                src = list[i];
+                at = out_meta[src].x + (e - eoff[i]);
+            }
+            u[4 * k + t] = src;
+            if (e < e1) v[4 * k + t] = out_pool[at];
+        }
+        i_lo = fits ? min(last, i_lo + rp_count_le(bnd, e1)) : rp_seg_forward(eoff, i_hi, last, e1);
     }
 }
 

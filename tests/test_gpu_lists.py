@@ -1,0 +1,68 @@
+"""Hops from the list of their messages (k_frontier_list, k_scatter_list, k_scatter_list4): packed rows, buckets that take more than one
+round, buckets that run over. (Rows of other widths: test_gpu_updates.py, sorted messages.)"""
+import numpy as np
+import pytest
+
+import paper_2601_12347_amd as rp
+import ripple_inputs as ri
+from harness import Pair, make_pair, make_stream
+from ripple_inputs.graphs import OP_FEAT_UPDATE
+
+pytestmark = pytest.mark.gpu
+
+MIX = {"edge_add": 0.4, "edge_del": 0.25, "feat": 0.2, "vadd": 0.08, "vdel": 0.07}
+
+
+@pytest.mark.parametrize("mode", [0, 2])
+@pytest.mark.parametrize("kind,widths,store", [("sage_mean", (12, 96, 47), "f32"), ("gcn_sum", (24, 88, 33), "f32"), ("gcn_sum", (24, 100, 48), "bf16"),
+                                               ("sage_mean", (12, 96, 96, 40), "f32")])
+def test_packed_rows_from_the_list(mode, kind, widths, store):
+    print("case packed list", mode, kind, widths, store, flush=True)
+    pair, graph = make_pair(n=900, e=9000, d0=widths[0], kind=kind, widths=widths, seed=361, slack=128, store=store)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SCATTER_MODE, mode)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SORTED_MESSAGES, 2)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SPARSE_FRONTIER, 0)
+    stream = make_stream(pair, graph, MIX, 363)
+    listed = 0
+    try:
+        for b, bs in enumerate([1, 30, 200, 30, 300]):
+            ops, payload, _ = stream.next_batch(bs)
+            res, _, _ = pair.step(ops, payload)
+            modes = list(res.hop_mode[1:len(widths)])
+            print(" batch", b, bs, "hop modes", modes, flush=True)
+            listed += modes[-1] == 4
+        pair.check_aggregates()
+    finally:
+        pair.close()
+    assert listed >= 2                                     # (automatic mode discovers the hops that send along most edges)
+
+
+@pytest.mark.parametrize("room", ["rounds", "over"])
+@pytest.mark.parametrize("widths", [(8, 24, 40, 6), (8, 96, 47)])
+def test_one_destination_with_thousands_of_messages(room, widths):
+    """3,000 vertices with one in-neighbour and the same two out-neighbours: when the in-neighbour's features change, hop 2 sends 3,000
+    messages each to two sinks, in one bucket. With a large edge capacity the bucket has room for all of them and takes two rounds;
+    with a small one it runs over and the hop is pulled or pushed."""
+    n, k = 3400, 3000
+    rng = np.random.default_rng(7)
+    mid = np.arange(10, 10 + k)
+    src = np.concatenate([np.zeros(k, np.int64), mid, mid, rng.integers(3100, n, 600)])
+    dst = np.concatenate([mid, np.full(k, 3), np.full(k, 2), rng.integers(10, n, 600)])
+    keep = np.unique(src * n + dst)
+    src, dst = (keep // n).astype(np.uint32), (keep % n).astype(np.uint32)
+    model = ri.make_model("gcn_sum", widths, 371)
+    pair = Pair(n, n + 8, src, dst, ri.features(n, widths[0], 372), model, edge_capacity=4_000_000 if room == "rounds" else None, project_first=len(widths) == 3)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SORTED_MESSAGES, 2)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SPARSE_FRONTIER, 0)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SCATTER_MODE, 2)
+    try:
+        for b in range(3):
+            ops = np.zeros((1, 4), np.uint32)
+            ops[0] = (OP_FEAT_UPDATE, 0, 0, 0)
+            res, _, _ = pair.step(ops, rng.standard_normal((1, widths[0])).astype(np.float32))
+            print(" batch", b, "hop modes", list(res.hop_mode[1:len(widths)]), "messages", list(res.messages[1:len(widths)]), flush=True)
+            assert res.messages[2] >= 2 * k
+            assert b == 0 or res.hop_mode[2] == (4 if room == "rounds" else 2)   # (the first batch cuts its buckets without a hint)
+        pair.check_aggregates()
+    finally:
+        pair.close()
