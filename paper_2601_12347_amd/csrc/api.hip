@@ -380,7 +380,6 @@ extern "C" void ripple_destroy(ripple_ctx *c) {
     for (uint32_t l = 0; l < c->L; ++l) {
         LayerDev &ly = c->layers[l];
         void *w[] = {ly.W0, ly.b0, ly.W1, ly.b1, ly.W0h, ly.W1h, ly.bzero, (ly.Wn != ly.W0) ? ly.Wn : nullptr, ly.PS,
-                     ly.W0s, ly.W1s, (ly.Wns != ly.W0s) ? ly.Wns : nullptr,
                      ly.att, ly.P, ly.ssrc, ly.sdst, ly.den, ly.T, ly.Wc, ly.bzero_c, ly.W0q, (ly.Wnq != ly.W0q) ? ly.Wnq : nullptr, ly.W1q, ly.Wcq};
         for (void *p : w)
             if (p) hipFree(p);
@@ -418,33 +417,11 @@ static ripple_status make_quads(ripple_ctx *c, const float *w, uint32_t Kpad, ui
     return RIPPLE_OK;
 }
 
-// planes (optional): the padded matrix as three transposed bf16 matrices [Npad x Kpad] whose sum is W exactly
-// (leading, middle and last 8 significant bits of every weight), for the split products on the bf16 matrix cores
 static ripple_status upload_padded(ripple_ctx *c, const float *w, const float *b, uint32_t K, uint32_t N,
-                                   uint32_t Kpad, uint32_t Npad, float **W_d, float **b_d, float **Wq_d,
-                                   unsigned short **planes = nullptr) {
+                                   uint32_t Kpad, uint32_t Npad, float **W_d, float **b_d, float **Wq_d) {
     std::vector<float> wp((size_t)Kpad * Npad, 0.0f), bp(Npad, 0.0f);
     for (uint32_t k = 0; k < K; ++k) memcpy(&wp[(size_t)k * Npad], &w[(size_t)k * N], (size_t)N * 4);
     memcpy(bp.data(), b, (size_t)N * 4);
-    if (planes) {
-        const size_t plane = (size_t)Npad * Kpad;
-        std::vector<uint16_t> pl(3 * plane, 0);
-        for (uint32_t k = 0; k < K; ++k)
-            for (uint32_t j = 0; j < N; ++j) {
-                float x = wp[(size_t)k * Npad + j];
-                for (int p = 0; p < 3; ++p) {
-                    uint32_t bits;
-                    memcpy(&bits, &x, 4);
-                    bits &= 0xFFFF0000u;
-                    float head;
-                    memcpy(&head, &bits, 4);
-                    pl[p * plane + (size_t)j * Kpad + k] = (uint16_t)(bits >> 16);
-                    x -= head;                         // exact
-                }
-            }
-        RP_TRY(dev_alloc(c, planes, pl.size(), false));
-        RP_HIP(c, hipMemcpy(*planes, pl.data(), pl.size() * 2, hipMemcpyHostToDevice));
-    }
     RP_TRY(dev_alloc(c, W_d, wp.size(), false));
     RP_TRY(dev_alloc(c, b_d, bp.size(), false));
     RP_HIP(c, hipMemcpy(*W_d, wp.data(), wp.size() * 4, hipMemcpyHostToDevice));
@@ -556,8 +533,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         uint32_t n0 = s.d_hidden ? s.d_hidden : s.d_out;
         ly.K0pad = rp_round_up(ly.K, 32);
         ly.N0pad = pad_n(n0);
-        const bool split = c->store == RIPPLE_STORE_F32 && c->opt_split;
-        RP_TRY(upload_padded(c, s.W0, s.b0, ly.K, n0, ly.K0pad, ly.N0pad, &ly.W0, &ly.b0, &ly.W0q, split ? &ly.W0s : nullptr));
+        RP_TRY(upload_padded(c, s.W0, s.b0, ly.K, n0, ly.K0pad, ly.N0pad, &ly.W0, &ly.b0, &ly.W0q));
         if (c->store == RIPPLE_STORE_BF16) {               // transposed bf16 copy for the bf16 matrix cores
             std::vector<uint16_t> wt((size_t)ly.N0pad * ly.K0pad, 0);
             for (uint32_t k = 0; k < ly.K; ++k)
@@ -587,17 +563,14 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
             std::vector<float> zeros(ly.N0pad, 0.0f);
             if (s.self_mode == RIPPLE_SELF_CONCAT) {           // rows d_in .. 2 d_in - 1 of W0
                 RP_TRY(upload_padded(c, s.W0 + (size_t)s.d_in * s.d_out, zeros.data(), s.d_in, s.d_out,
-                                     rp_round_up(s.d_in, 32), ly.N0pad, &ly.Wn, &ly.bzero, &ly.Wnq, split ? &ly.Wns : nullptr));
-                ly.Wns_ld = rp_round_up(s.d_in, 32);
+                                     rp_round_up(s.d_in, 32), ly.N0pad, &ly.Wn, &ly.bzero, &ly.Wnq));
             } else {
                 ly.Wn = ly.W0;
                 ly.Wnq = ly.W0q;
-                ly.Wns = ly.W0s;
-                ly.Wns_ld = ly.K0pad;
                 RP_TRY(dev_alloc(c, &ly.bzero, (size_t)ly.N0pad, true));
             }
         }
-        if (ly.proj && ly.selfc && s.d_out <= 64 && s.d_in % 4 == 0 && !split) {
+        if (ly.proj && ly.selfc && s.d_out <= 64 && s.d_in % 4 == 0) {
             const uint32_t kp = rp_round_up(s.d_in, 32);
             std::vector<float> wc((size_t)kp * 128, 0.0f);
             for (uint32_t k = 0; k < s.d_in; ++k)
@@ -613,7 +586,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         if (s.d_hidden) {
             ly.K1pad = rp_round_up(s.d_hidden, 32);
             ly.N1pad = pad_n(s.d_out);
-            RP_TRY(upload_padded(c, s.W1, s.b1, s.d_hidden, s.d_out, ly.K1pad, ly.N1pad, &ly.W1, &ly.b1, &ly.W1q, split ? &ly.W1s : nullptr));
+            RP_TRY(upload_padded(c, s.W1, s.b1, s.d_hidden, s.d_out, ly.K1pad, ly.N1pad, &ly.W1, &ly.b1, &ly.W1q));
         }
         c->d[l + 1] = s.d_out;
         c->dmax = std::max(c->dmax, s.d_out);
@@ -628,13 +601,13 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         };
         std::vector<Part> parts;
         auto add = [&](const float *w, uint32_t K, uint32_t Npad, unsigned short **out) {
-            if (!w || Npad > 256u || K > 256u) return;
+            if (!w) return;
             b.add(out, rp_weight_parts_size(K, Npad));
             parts.push_back({w, K, Npad, out});
         };
         for (uint32_t l = 0; l < n_layers; ++l) {
             LayerDev &ly = c->layers[l];
-            add(ly.W0, ly.self_mode == RIPPLE_SELF_CONCAT ? ly.d_in : ly.K, ly.N0pad, &ly.W0p);
+            add(ly.W0, ly.K, ly.N0pad, &ly.W0p);   // all rows: a product with W_self alone zeroes its rows from d_in on
             if (ly.Wn != ly.W0) add(ly.Wn, ly.d_in, ly.N0pad, &ly.Wnp);
             add(ly.W1, ly.d_hidden, ly.N1pad, &ly.W1p);
             add(ly.Wc, ly.d_in, 128u, &ly.Wcp);

@@ -103,13 +103,10 @@ struct LayerDev {
     // denominators of the softmax (the numerators are the layer's X rows); att = a_src then a_dst on the device
     float *att, *P, *ssrc, *sdst, *den;
     uint32_t ldp;                             // row stride of P: rows of up to 63 columns carry s_src behind them
-    // fp32 storage: W0, Wn, W1 as three transposed bf16 planes each (their sum is the matrix), or null
-    unsigned short *W0s, *Wns, *W1s;
     // the padded matrices once more with k by fours, [Kpad / 4][Npad][4] (wave_gemm); Wnq may alias W0q
     float *W0q, *Wnq, *W1q, *Wcq;
-    // ... and as three bf16 parts each, in the order k_split_stream takes them (of W0 of a layer that concatenates: W_self); Wnp may alias W0p
+    // ... and as three bf16 parts each, in the order k_split_stream takes them (W0p: all K rows); Wnp may alias W0p
     unsigned short *W0p, *Wnp, *W1p, *Wcp;
-    uint32_t Wns_ld;                          // row stride of the Wn planes (those of W0: K0pad, of W1: K1pad)
 };
 
 // pieces of up to SMALL_OPS operations without vertex deletions: the Apply step in three launches (k_small_validate)
@@ -245,7 +242,7 @@ struct ripple_ctx {
     int opt_selfcache = 1;                      // allow cached self projections (read by load_model)
     int opt_sparse = 1;                         // small frontiers are listed as they are marked (no bitmap scan)
     int opt_stream = 1;                         // products of many rows: persistent workgroups, tiles written while the next is multiplied (2: any size)
-    int opt_split = 0;                          // fp32 storage: products on the bf16 matrix cores, operands split in three (read by load_model)
+    int opt_split = 0;                          // products of few rows on the bf16 matrix cores as well, operands in three parts
     int opt_deterministic = 0;                  // bit-reproducible aggregation (owner kernels, no float atomics)
     int opt_pull_ratio = 1;                     // pull when messages * width * ratio >= scanned in-edges
     int opt_pack = 1;                           // project-first layers of 33..48 columns send one-line packed messages (read by load_model)

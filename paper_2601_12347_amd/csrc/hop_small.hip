@@ -77,7 +77,7 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
     if (ly.proj || ly.selfc) {
         a.g = both ? rp_project_both_args(c, l, a.list, a.count_ptr, false)
                    : (ly.proj ? rp_project_args(c, l, a.list, a.count_ptr, false) : rp_self_project_args(c, l, a.list, a.count_ptr));
-        if (ly.W0s || wave_gemm_waves(a.g, rows) > WAVE_GEMM_MAX) {   // many rows: launches of their own
+        if (c->opt_split || wave_gemm_waves(a.g, rows) > WAVE_GEMM_MAX) {   // many rows: launches of their own
             if (both) {
                 rp_launch_project_both(c, l, a.list, a.count_ptr, false);
             } else {

@@ -2,6 +2,12 @@
 #pragma once
 #include "transform_args.h"
 
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
@@ -84,6 +90,42 @@ __device__ __forceinline__ floatx4 finish_raw(const TArgs &a, floatx4 p, floatx4
         r.w = k + 3u < a.K ? r.w : 0.0f;
     }
     return r;
+}
+
+// ---------------------------------------------------------------------------------
+// fp32 numbers as bf16 parts
+// ---------------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
+    floatx2 f;
+    f.x = a;
+    f.y = b;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));     // to nearest even
+}
+// four numbers as PL bf16 numbers each, four to eight bytes per part
+template <int PL>
+__device__ __forceinline__ void split_parts(floatx4 x, uintx2 (&part)[PL]) {
+#pragma unroll
+    for (int p = 0; p < PL; ++p) {
+        part[p].x = to_bf16x2(x.x, x.y);
+        part[p].y = to_bf16x2(x.z, x.w);
+        if (p + 1 < PL) {                                  // what is left: exact
+            x.x -= __uint_as_float(part[p].x << 16);
+            x.y -= __uint_as_float(part[p].x & 0xFFFF0000u);
+            x.z -= __uint_as_float(part[p].y << 16);
+            x.w -= __uint_as_float(part[p].y & 0xFFFF0000u);
+        }
+    }
+}
+
+// element k of the row in slot `slot` as the product takes it
+template <int MODE, int STORE>
+__device__ __forceinline__ float row_number(const TArgs &a, uint32_t slot, uint32_t v, uint32_t k, float scale) {
+    if (MODE == 0) return a.X[(size_t)v * a.d_in + k] * scale;
+    if (MODE == 3) return a.tmp_in[(size_t)slot * a.tmp_ld + k];
+    if (MODE == 1 && k >= a.d_in) return a.X[(size_t)v * a.d_in + (k - a.d_in)] * scale;
+    const float h = rp_load_h(a.Hprev, STORE, (size_t)v * a.d_in + k);
+    if (MODE == 2) return h * a.one_plus_eps + a.X[(size_t)v * a.d_in + k] * scale;
+    return h;
 }
 
 // ---------------------------------------------------------------------------------

@@ -6,12 +6,12 @@
 //     D^l[v] = h_new - H^l[v],   H^l[v] = h_new
 // so that the next hop can forward the delta (Sec. 3.3.3).
 //
-// Tiling: a workgroup of four wavefronts computes a (WAVES_M*TM*32) x (WAVES_N*TN*32)
-// output tile; each wavefront owns TM x TN MFMA 32x32x2 (fp32) accumulators. K is
-// consumed in slices of 32 staged through LDS. Later slices are already on their
-// way from memory into registers while the matrix cores work on the current one:
-// the weight slice (an L2 hit) one step ahead, the gathered rows (HBM latency)
-// STAGES steps ahead. The fetch is branch-free (addresses are clamped, the row
+// Tiling: a workgroup of four wavefronts computes a tile of rows x columns, each
+// wavefront accumulators of 32 x 32 (k_transform_split, k_transform_bf16; few rows:
+// wave_gemm). K is consumed in slices of 32 staged through LDS. Later slices are
+// already on their way from memory into registers while the matrix cores work on
+// the current one: the weights (an L2 hit) one step ahead, the gathered rows (HBM
+// latency) STAGES steps ahead. The fetch is branch-free (addresses are clamped, the row
 // mode is a template parameter) and touches no loaded value, so nothing waits on
 // memory until the registers are written to LDS; scaling, the SAGE/GIN combination
 // and zero padding are applied at that point.
@@ -287,10 +287,8 @@ static TArgs base_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
     a.Wq = ly.W0q;
     a.Wt = (c->store && c->opt_bf16_mfma) ? ly.W0h : nullptr;   // bf16 storage: bf16 matrix cores
     a.wt_ld = ly.K0pad;
-    a.Ws = ly.W0s;                                 // fp32 storage with split products, else null
-    a.ws_plane = (size_t)ly.N0pad * ly.K0pad;
     a.Wp = ly.W0p;
-    a.wp_k = rp_round_up(ly.self_mode == RIPPLE_SELF_CONCAT ? ly.d_in : ly.K, 128);
+    a.wp_k = rp_round_up(ly.K, 128);
     a.bias = ly.b0;
     a.K = ly.K;
     a.Kpad = ly.K0pad;
@@ -470,160 +468,6 @@ __global__ __launch_bounds__(256) void k_transform_addend_only(TArgs a) {
     else addend_only_rows<false>(a, gw, nw);
 }
 
-template <int WAVES_M, int WAVES_N, int TM, int TN, int STAGES, int MODE, int STORE, int MINB = 2>
-__global__ __launch_bounds__(256, MINB) void k_transform_f32(TArgs a) {
-    constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32;
-    constexpr int NA = BM / 32, NB = BN / 32;              // float4 per thread per slice (A, B)
-    constexpr bool TWO = (MODE == 2) || (MODE == 1 && STORE == 1);
-    constexpr int A_BYTES = BM * (T_BK + 1) * 4, B_BYTES = T_BK * BN * 4, C_BYTES = BM * (BN + 4) * 4;
-    constexpr int S_BYTES = (A_BYTES + B_BYTES > C_BYTES) ? A_BYTES + B_BYTES : C_BYTES;
-    static_assert(A_BYTES % 16 == 0, "alignment of the weight slice");
-    __shared__ __attribute__((aligned(16))) char smem[S_BYTES];   // A and B slices; reused by the staged epilogue
-    float (*As)[T_BK + 1] = (float (*)[T_BK + 1]) smem;
-    float (*Bs)[BN] = (float (*)[BN])(smem + A_BYTES);
-    __shared__ uint32_t s_vtx[BM];
-    __shared__ float s_scale[BM];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const uint32_t count = *a.count_ptr;
-    const uint32_t n_tiles = (count + BM - 1) / BM;
-    const uint32_t n0 = blockIdx.y * BN;
-
-    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const uint32_t row0 = tile * BM;
-        __syncthreads();                                   // previous tile's epilogue has read s_vtx
-        for (int r = tid; r < BM; r += 256) {
-            uint32_t slot = row0 + r;
-            uint32_t v = 0;                                // rows past the end read vertex 0; never stored
-            float sc = 1.0f;
-            if (slot < count) {
-                v = a.list[slot];
-                if (a.mean) {
-                    uint32_t deg = a.in_meta[v].y;
-                    sc = 1.0f / (float)(deg > 1u ? deg : 1u);
-                }
-            }
-            s_vtx[r] = v;
-            s_scale[r] = sc;
-        }
-        __syncthreads();
-
-        floatx16 acc[TM][TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-        // per-thread row coordinates of its NA float4 of every slice
-        uint32_t my_v[NA], my_slot[NA];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int r = (tid + i * 256) / (T_BK / 4);
-            my_v[i] = s_vtx[r];
-            my_slot[i] = min(row0 + r, count - 1u);
-        }
-        const uint32_t c4a = (tid % (T_BK / 4)) * 4;       // (tid + i*256) % 8 is the same for every i
-
-        floatx4 ra[STAGES][NA], rq[TWO ? STAGES : 1][TWO ? NA : 1], rb[NB];
-        // weights first, as in every step of the loop, so that one wait count fits both ways into it
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int idx = tid + i * 256;
-            const int kr = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
-            rb[i] = *(const floatx4 *)(a.W + (size_t)kr * a.Npad + n0 + c4);
-        }
-#pragma unroll
-        for (int st = 0; st < STAGES; ++st)
-#pragma unroll
-            for (int i = 0; i < NA; ++i) {
-                floatx4 q = (floatx4)(0.0f);
-                fetch_raw<MODE, STORE>(a, my_v[i], my_slot[i], (uint32_t)st * T_BK + c4a, ra[st][i], q);
-                if constexpr (TWO) rq[st][i] = q;
-            }
-        __builtin_amdgcn_sched_barrier(0);
-
-        // The staging registers rotate by unrolling (slot s of step s mod STAGES), not by moves: a move
-        // would have to wait for the load it copies.
-        for (uint32_t kbase = 0; kbase < a.Kpad; kbase += STAGES * T_BK) {
-#pragma unroll
-          for (int s = 0; s < STAGES; ++s) {
-            const uint32_t k0 = kbase + s * T_BK;
-            if (k0 >= a.Kpad) break;
-            __syncthreads();                               // the matrix cores are done with the previous slice
-#pragma unroll
-            for (int i = 0; i < NA; ++i) {
-                const int r = (tid + i * 256) / (T_BK / 4);
-                floatx4 q = (floatx4)(0.0f);
-                if constexpr (TWO) q = rq[s][i];
-                const floatx4 val = finish_raw<MODE, STORE>(a, ra[s][i], q, k0 + c4a, s_scale[r]);
-                As[r][c4a + 0] = val.x;
-                As[r][c4a + 1] = val.y;
-                As[r][c4a + 2] = val.z;
-                As[r][c4a + 3] = val.w;
-            }
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                const int idx = tid + i * 256;
-                const int kr = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
-                *(floatx4 *)&Bs[kr][c4] = rb[i];
-            }
-            __syncthreads();
-            // memory returns loads in order: the weights (needed one step from now) are requested
-            // before the rows (needed STAGES steps from now), so waiting for them leaves the rows in flight
-            {                                              // weights of the next slice (last step re-reads its own: in bounds)
-                const uint32_t kb = min(k0 + T_BK, a.Kpad - T_BK);
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int idx = tid + i * 256;
-                    const int kr = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
-                    rb[i] = *(const floatx4 *)(a.W + (size_t)(kb + kr) * a.Npad + n0 + c4);
-                }
-            }
-            {                                              // rows of the slice STAGES steps ahead (clamped: harmless past the end)
-                const uint32_t kn = k0 + STAGES * T_BK + c4a;
-#pragma unroll
-                for (int i = 0; i < NA; ++i) {
-                    floatx4 q = (floatx4)(0.0f);
-                    fetch_raw<MODE, STORE>(a, my_v[i], my_slot[i], kn, ra[s][i], q);
-                    if constexpr (TWO) rq[s][i] = q;
-                }
-            }
-            // keep the requests above the matrix-core work: the scheduler would otherwise sink them to
-            // the end of the step, where nothing is left to hide their latency behind
-            __builtin_amdgcn_sched_barrier(0);
-            // operands of the next pair of k are read from LDS before the matrix cores take the
-            // current pair, so that no LDS round trip separates two groups of products
-            float av[2][TM], bv[2][TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) av[0][i] = As[(wm * TM + i) * 32 + (lane & 31)][lane >> 5];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bv[0][j] = Bs[lane >> 5][(wn * TN + j) * 32 + (lane & 31)];
-#pragma unroll
-            for (int kk = 0; kk < T_BK; kk += 2) {
-                const int cur = (kk >> 1) & 1, nxt = cur ^ 1;
-                if (kk + 2 < T_BK) {
-                    const int kq = kk + 2 + (lane >> 5);
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) av[nxt][i] = As[(wm * TM + i) * 32 + (lane & 31)][kq];
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) bv[nxt][j] = Bs[kq][(wn * TN + j) * 32 + (lane & 31)];
-                }
-                __builtin_amdgcn_sched_barrier(0);         // the scheduler would move the reads back next to their use
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[cur][i], bv[cur][j], acc[i][j], 0, 0, 0);
-            }
-          }
-        }
-        epilogue_staged<TM, TN, BM, BN, STORE != 0>(a, acc, (float *)smem, s_vtx, s_scale, row0, count, n0, wm, wn, tid);
-    }
-}
-
 // [h_self | x] rows whose halves are not multiples of four columns wide (a group of four would straddle them; only layers
 // that concatenate and do not cache their self term get here): same tiling, scalar gathers, no prefetch.
 __device__ __forceinline__ float load_a1(const TArgs &a, uint32_t v, float scale, uint32_t k) {
@@ -706,8 +550,6 @@ __global__ __launch_bounds__(256) void k_transform_generic(TArgs a) {
 // they are written to LDS, the weights come from a transposed bf16 copy so that the eight
 // consecutive k a lane feeds into one MFMA are one 16-byte LDS read for both operands.
 // ---------------------------------------------------------------------------------
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 #define TB_LD 40                                            // LDS row stride in bf16 (80 bytes)
 
 template <int WAVES_M, int WAVES_N, int TM, int TN, int STAGES, int MODE>
@@ -878,40 +720,23 @@ static void launch_bf16(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
     }
 }
 
-// fp32 embeddings on the bf16 matrix cores: every fp32 number is the exact sum of three bf16 numbers
-// (its leading 8 significant bits, the next 8, the last 8), so a product a b is the sum of nine bf16
-// products; the six largest (a1 b1, a1 b2, a2 b1, a2 b2, a1 b3, a3 b1) are kept, each exact in the
-// fp32 accumulator, and what is dropped is below 2^-24 |a b|. Six bf16 products cost 3/8 of one fp32
-// product on this chip (the bf16 rate is sixteen times the fp32 rate), which leaves the kernel bound by
-// the gathered rows rather than by the matrix cores. Rows are split as they enter LDS, the weights
-// come from three transposed bf16 planes made when the model is loaded.
-__device__ __forceinline__ void split3(float a, float &a1, float &a2, float &a3) {
-    a1 = __uint_as_float(__float_as_uint(a) & 0xFFFF0000u);
-    const float r = a - a1;                                   // exact: the low 16 bits of the significand
-    a2 = __uint_as_float(__float_as_uint(r) & 0xFFFF0000u);
-    a3 = r - a2;                                              // exact, at most 8 significant bits
-}
-__device__ __forceinline__ uint32_t pack_hi16(float lo, float hi) {       // the two values are bf16-representable
-    return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xFFFF0000u);
-}
-
-template <int WAVES_M, int WAVES_N, int TM, int TN, int STAGES, int MODE>
-__global__ __launch_bounds__(256, 2) void k_transform_split(TArgs a) {
-    constexpr int STORE = 0;
-    constexpr int BM = WAVES_M * TM * 32, BN = WAVES_N * TN * 32;
-    constexpr int NA = BM / 32, NB = BN / 64;              // per thread per slice: float4 of A, 16-byte chunks of B per plane
-    constexpr bool TWO = (MODE == 2);
-    constexpr int A_BYTES = BM * TB_LD * 2, B_BYTES = BN * TB_LD * 2, C_BYTES = BM * (BN + 4) * 4;
-    constexpr int PB = 3;                                  // weight planes
-    constexpr int S_BYTES = (3 * A_BYTES + PB * B_BYTES > C_BYTES) ? 3 * A_BYTES + PB * B_BYTES : C_BYTES;
-    static_assert(A_BYTES % 16 == 0 && B_BYTES % 16 == 0, "alignment of the planes");
-    __shared__ __attribute__((aligned(16))) char smem[S_BYTES];   // three A and three B planes; reused by the staged epilogue
-    typedef unsigned short (*plane_t)[TB_LD];
-    plane_t As[3], Bs[PB];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) As[p] = (plane_t)(smem + p * A_BYTES);
-#pragma unroll
-    for (int p = 0; p < PB; ++p) Bs[p] = (plane_t)(smem + 3 * A_BYTES + p * B_BYTES);
+// Some thousand rows: fp32 numbers as three bf16 parts on the bf16 matrix cores (see k_split_stream: six products, the small terms summed
+// apart, closer to 64-bit sums than fp32 products; sums that are not finite are made again from fp32 products). Tiles of 32 x 128, or
+// 64 x 64 where the matrix is 64 columns wide, a wavefront 32 x 32 of them; the rows pass through LDS, split as they are written there, the
+// weights come from the L2 in the order in which the matrix cores take them. What bounds it is the chain of slices (LDS, barrier,
+// products) and the workgroups that share a compute unit's matrix cores: six bf16 products take 3/8 of the fp32 products' time.
+// 256 -> 256 against the same tiles of fp32 products (launch included): 10 K rows with a cached row 20.6 -> 15.8 us, 35 K rows 40 -> 31 (23 for
+// the bytes alone), without it 18.4 -> 12.7 and 22 -> 16.8; both products of an MLP on 10 K rows 37 -> 31 and 26 -> 18.
+template <int WAVES_M, int WAVES_N, int STAGES, int MODE, int STORE>
+__global__ __launch_bounds__(256, (WAVES_N == 4 ? 3 : 2)) void k_transform_split(TArgs a) {
+    constexpr int BM = WAVES_M * 32, BN = WAVES_N * 32;
+    constexpr int NA = BM / 32;                            // groups of four numbers per thread and slice
+    constexpr bool TWO = (MODE == 2) || (MODE == 1 && STORE == 1);
+    constexpr int PL = STORE && MODE == 4 ? 1 : 3;         // parts of a row number (bf16 rows are exact as they are)
+    constexpr int A_BYTES = 2 * PL * BM * TB_LD * 2, C_BYTES = BM * (BN + 4) * 4;
+    __shared__ __attribute__((aligned(16))) char smem[A_BYTES > C_BYTES ? A_BYTES : C_BYTES];   // two slices of rows; reused by the staged epilogue
+    typedef unsigned short (*slice_t)[BM][TB_LD];
+    slice_t As[2] = {(slice_t)smem, (slice_t)(smem + A_BYTES / 2)};
     __shared__ uint32_t s_vtx[BM];
     __shared__ float s_scale[BM];
 
@@ -919,35 +744,24 @@ __global__ __launch_bounds__(256, 2) void k_transform_split(TArgs a) {
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const uint32_t count = *a.count_ptr;
     const uint32_t n_tiles = (count + BM - 1) / BM;
-    const uint32_t n0 = blockIdx.y * BN;
+    const uint32_t n0 = blockIdx.y * BN, col = n0 + wn * 32 + (lane & 31);
+    const uintx4 *Wp = (const uintx4 *)a.Wp + (size_t)(lane >> 5) * a.Npad + col;    // eight k of the lane's column
+    const size_t part = (size_t)(a.wp_k / 8u) * a.Npad, step = 2u * a.Npad;
 
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const uint32_t row0 = tile * BM;
-        __syncthreads();
+        __syncthreads();                                   // previous tile's epilogue has read s_vtx
         for (int r = tid; r < BM; r += 256) {
-            uint32_t slot = row0 + r;
-            uint32_t v = 0;
+            const uint32_t v = a.list[min(row0 + r, count - 1u)];   // rows past the end repeat the last one and are never stored
             float sc = 1.0f;
-            if (slot < count) {
-                v = a.list[slot];
-                if (a.mean) {
-                    uint32_t deg = a.in_meta[v].y;
-                    sc = 1.0f / (float)(deg > 1u ? deg : 1u);
-                }
+            if (a.mean) {
+                const uint32_t deg = a.in_meta[v].y;
+                sc = 1.0f / (float)(deg > 1u ? deg : 1u);
             }
             s_vtx[r] = v;
             s_scale[r] = sc;
         }
         __syncthreads();
-
-        floatx16 acc[TM][TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
         uint32_t my_v[NA], my_slot[NA];
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
@@ -956,17 +770,15 @@ __global__ __launch_bounds__(256, 2) void k_transform_split(TArgs a) {
             my_slot[i] = min(row0 + r, count - 1u);
         }
         const uint32_t c4a = (tid % (T_BK / 4)) * 4;
-
         floatx4 ra[STAGES][NA], rq[TWO ? STAGES : 1][TWO ? NA : 1];
-        uintx4 rb[PB][NB];
+        uintx4 bq[2][3];                                   // weights of step g (16 k) in bq[g & 1]
+        auto load_w = [&](uint32_t g) {
+            const uint32_t at = min(g, a.Kpad / 16u - 1u); // past the end: the last step once more, not used
 #pragma unroll
-        for (int p = 0; p < PB; ++p)
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {                 // weights first, as in every step of the loop
-                const int idx = tid + i * 256;
-                const int n = idx / 4, kc = (idx % 4) * 8;
-                rb[p][i] = *(const uintx4 *)(a.Ws + p * a.ws_plane + (size_t)(n0 + n) * a.wt_ld + kc);
-            }
+            for (int p = 0; p < 3; ++p) bq[g & 1][p] = Wp[p * part + at * step];
+        };
+        load_w(0);
+        load_w(1);
 #pragma unroll
         for (int st = 0; st < STAGES; ++st)
 #pragma unroll
@@ -976,101 +788,72 @@ __global__ __launch_bounds__(256, 2) void k_transform_split(TArgs a) {
                 if constexpr (TWO) rq[st][i] = q;
             }
         __builtin_amdgcn_sched_barrier(0);
-
+        floatx16 acc[1][1], cor;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][0][r] = cor[r] = 0.0f;
         for (uint32_t kbase = 0; kbase < a.Kpad; kbase += STAGES * T_BK) {    // staging registers rotate by unrolling
 #pragma unroll
           for (int s = 0; s < STAGES; ++s) {
             const uint32_t k0 = kbase + s * T_BK;
             if (k0 >= a.Kpad) break;
-            __syncthreads();
+            static_assert(STAGES % 2 == 0, "the LDS buffers alternate");
 #pragma unroll
             for (int i = 0; i < NA; ++i) {
                 const int r = (tid + i * 256) / (T_BK / 4);
                 floatx4 q = (floatx4)(0.0f);
                 if constexpr (TWO) q = rq[s][i];
-                const floatx4 val = finish_raw<MODE, STORE>(a, ra[s][i], q, k0 + c4a, s_scale[r]);
-                float x1[4], x2[4], x3[4];
-                split3(val.x, x1[0], x2[0], x3[0]);
-                split3(val.y, x1[1], x2[1], x3[1]);
-                split3(val.z, x1[2], x2[2], x3[2]);
-                split3(val.w, x1[3], x2[3], x3[3]);
-                *(uint2 *)&As[0][r][c4a] = make_uint2(pack_hi16(x1[0], x1[1]), pack_hi16(x1[2], x1[3]));
-                *(uint2 *)&As[1][r][c4a] = make_uint2(pack_hi16(x2[0], x2[1]), pack_hi16(x2[2], x2[3]));
-                *(uint2 *)&As[2][r][c4a] = make_uint2(pack_hi16(x3[0], x3[1]), pack_hi16(x3[2], x3[3]));
+                uintx2 parts[PL];
+                split_parts<PL>(finish_raw<MODE, STORE>(a, ra[s][i], q, k0 + c4a, s_scale[r]), parts);
+#pragma unroll
+                for (int p = 0; p < PL; ++p) *(uintx2 *)&As[s & 1][p][r][c4a] = parts[p];
             }
+            __syncthreads();                               // (one per slice: the other buffer was read before the last one)
 #pragma unroll
-            for (int p = 0; p < PB; ++p)
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int idx = tid + i * 256;
-                    const int n = idx / 4, kc = (idx % 4) * 8;
-                    *(uintx4 *)&Bs[p][n][kc] = rb[p][i];
-                }
-            __syncthreads();
-            {
-                const uint32_t kb = min(k0 + T_BK, a.Kpad - T_BK);
-#pragma unroll
-                for (int p = 0; p < PB; ++p)
-#pragma unroll
-                    for (int i = 0; i < NB; ++i) {
-                        const int idx = tid + i * 256;
-                        const int n = idx / 4, kc = (idx % 4) * 8;
-                        rb[p][i] = *(const uintx4 *)(a.Ws + p * a.ws_plane + (size_t)(n0 + n) * a.wt_ld + kb + kc);
-                    }
-            }
-            {
-                const uint32_t kn = k0 + STAGES * T_BK + c4a;
-#pragma unroll
-                for (int i = 0; i < NA; ++i) {
-                    floatx4 q = (floatx4)(0.0f);
-                    fetch_raw<MODE, STORE>(a, my_v[i], my_slot[i], kn, ra[s][i], q);
-                    if constexpr (TWO) rq[s][i] = q;
-                }
+            for (int i = 0; i < NA; ++i) {                 // rows of the slice STAGES steps ahead (clamped: harmless past the end)
+                floatx4 q = (floatx4)(0.0f);
+                fetch_raw<MODE, STORE>(a, my_v[i], my_slot[i], k0 + STAGES * T_BK + c4a, ra[s][i], q);
+                if constexpr (TWO) rq[s][i] = q;
             }
             __builtin_amdgcn_sched_barrier(0);             // requests stay above the matrix-core work
+            bf16x8 av[2][PL];
 #pragma unroll
-            for (int kh = 0; kh < 2; ++kh) {
-                const int ko = kh * 16 + (lane >> 5) * 8;
-                bf16x8 av[3][TM];
+            for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-                for (int p = 0; p < 3; ++p)
+                for (int p = 0; p < PL; ++p) av[kk][p] = __builtin_bit_cast(bf16x8, *(const uintx4 *)&As[s & 1][p][wm * 32 + (lane & 31)][kk * 16 + (lane >> 5) * 8]);
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        av[p][i] = __builtin_bit_cast(bf16x8, *(const uintx4 *)&As[p][(wm * TM + i) * 32 + (lane & 31)][ko]);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {               // one column block's three planes at a time (registers)
-                    bf16x8 bv[PB];
-#pragma unroll
-                    for (int p = 0; p < PB; ++p)
-                        bv[p] = __builtin_bit_cast(bf16x8, *(const uintx4 *)&Bs[p][(wn * TN + j) * 32 + (lane & 31)][ko]);
-#pragma unroll
-                    for (int i = 0; i < TM; ++i) {           // smallest terms first
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[2][i], bv[0], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0][i], bv[2], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[1][i], bv[1], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[1][i], bv[0], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0][i], bv[1], acc[i][j], 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[0][i], bv[0], acc[i][j], 0, 0, 0);
-                    }
+            for (int kk = 0; kk < 2; ++kk) {
+#define TERM(dst, x, w) dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[kk][x], __builtin_bit_cast(bf16x8, bq[kk][w]), dst, 0, 0, 0)
+                TERM(cor, 0, 2);
+                TERM(acc[0][0], 0, 0);
+                if constexpr (PL == 3) {
+                    TERM(cor, 2, 0);
+                    TERM(cor, 1, 1);
+                    TERM(cor, 1, 0);
                 }
+                TERM(cor, 0, 1);
+#undef TERM
+                load_w(k0 / 16u + kk + 2u);
             }
           }
         }
-        epilogue_staged<TM, TN, BM, BN, false>(a, acc, (float *)smem, s_vtx, s_scale, row0, count, n0, wm, wn, tid);
-    }
-}
-
-template <int MODE>
-static void launch_split(ripple_ctx *c, const TArgs &a, bool narrow, uint32_t rows_hint) {
-    if (a.Npad >= 256 && !narrow) {
-        hipLaunchKernelGGL((k_transform_split<1, 4, 2, 2, 3, MODE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 256),
-                           dim3(256), 0, c->stream, a);
-    } else if (a.Npad == 128 && !narrow) {
-        hipLaunchKernelGGL((k_transform_split<2, 2, 2, 2, 3, MODE>), dim3(tile_grid(c, rows_hint, 128, c->n_cu * 2), 1), dim3(256), 0,
-                           c->stream, a);
-    } else {
-        hipLaunchKernelGGL((k_transform_split<4, 1, 1, 2, 3, MODE>),
-                           dim3(tile_grid(c, rows_hint, 128, narrow ? c->n_cu : c->n_cu * 2), a.Npad / 64), dim3(256), 0, c->stream, a);
+        bool bad = false;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            acc[0][0][r] += cor[r];
+            bad |= !__builtin_isfinite(acc[0][0][r]);
+        }
+        if (__builtin_expect(__any(bad && col < a.N), 0)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t lr = wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), slot = row0 + lr;
+                if (__builtin_isfinite(acc[0][0][r]) || col >= a.N || slot >= count) continue;
+                float t = 0.0f;
+#pragma unroll 1
+                for (uint32_t k = 0; k < a.K; ++k) t = __builtin_fmaf(row_number<MODE, STORE>(a, slot, s_vtx[lr], k, s_scale[lr]), a.W[(size_t)k * a.Npad + col], t);
+                acc[0][0][r] = t;
+            }
+        }
+        epilogue_staged<1, 1, BM, BN, STORE != 0>(a, acc, (float *)smem, s_vtx, s_scale, row0, count, n0, wm, wn, tid);
     }
 }
 
@@ -1079,27 +862,21 @@ __global__ __launch_bounds__(256) void k_transform_wave(TArgs a) {
     wave_gemm<MODE, STORE>(a, (blockIdx.x * 256u + threadIdx.x) >> 6, gridDim.x * 4u);
 }
 
-// Tiles of 32 x 128 (64 x 64 where the matrix is 64 columns wide): a wavefront's chain of products per K step is short and several
-// workgroups fit a compute unit, so one's memory phase is another's products, and the last round of workgroups wastes
-// little. Measured for 256 -> 256 against tiles of 64 x 256: 3,000 rows 11.7 / 28.7 us, 20,000 rows 35 / 50, 100,000 rows 159 /
-// 187, 600,000 rows 948 / 929; 256 -> 47 against 128 x 64: 8,000 rows 12.1 / 17.8, 150,000 rows 68 / 84.
+// Few rows: a product per wavefront (wave_gemm); more: tiles. Every matrix has its parts (wp_k >= Kpad: no read leaves them).
 template <int MODE, int STORE>
 static void launch_fast(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
-    if (a.Wq && wave_gemm_waves(a, rows_hint) <= WAVE_GEMM_MAX) {
+    if (a.Wq && !c->opt_split && wave_gemm_waves(a, rows_hint) <= WAVE_GEMM_MAX) {
         // wavefronts for half as many rows again as expected; a set that turns out larger still finds every SIMD busy
         const uint32_t waves = std::max(wave_gemm_waves(a, rows_hint + rows_hint / 2u), c->n_cu * 4);
         hipLaunchKernelGGL((k_transform_wave<MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
     } else if (a.Npad % 128 == 0) {
-        hipLaunchKernelGGL((k_transform_f32<1, 4, 1, 1, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 32, c->n_cu * 2), a.Npad / 128), dim3(256),
-                           0, c->stream, a);
+        hipLaunchKernelGGL((k_transform_split<1, 4, 4, MODE, STORE>), dim3(tile_grid(c, rows_hint, 32, c->n_cu * 2), a.Npad / 128), dim3(256), 0, c->stream, a);
     } else {
-        hipLaunchKernelGGL((k_transform_f32<2, 2, 1, 1, 3, MODE, STORE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 64), dim3(256),
-                           0, c->stream, a);
+        hipLaunchKernelGGL((k_transform_split<2, 2, 4, MODE, STORE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 64), dim3(256), 0, c->stream, a);
     }
 }
 
 static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
-    const bool narrow = rows_hint < 64u * c->n_cu;
     if (rp_launch_stream(c, a, rows_hint)) return;
     const uint32_t gx = c->n_cu * 2;
     if (a.a_mode == 1 && (a.d_in & 3u)) {
@@ -1112,7 +889,6 @@ static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
     case M:                                                  \
         if (a.store && a.Wt) launch_bf16<M>(c, a, rows_hint);           \
         else if (a.store) launch_fast<M, 1>(c, a, rows_hint);   \
-        else if (a.Ws) launch_split<M>(c, a, narrow, rows_hint);        \
         else launch_fast<M, 0>(c, a, rows_hint);                \
         break;
     switch (a.a_mode) {
@@ -1122,7 +898,6 @@ static void launch_t(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
         T_CASE(4)
     default:
         if (a.store) launch_fast<3, 1>(c, a, rows_hint);   // compact fp32 rows; the storage type only shapes the epilogue
-        else if (a.Ws) launch_split<3>(c, a, narrow, rows_hint);
         else launch_fast<3, 0>(c, a, rows_hint);
         break;
     }
@@ -1139,9 +914,6 @@ TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uin
     a.W = ly.Wn;
     a.Wq = ly.Wnq;
     a.Wt = nullptr;                                // messages are differences of such products: fp32 path also for bf16 rows
-    a.Ws = ly.Wns;
-    a.wt_ld = ly.Wns_ld;
-    a.ws_plane = (size_t)ly.N0pad * ly.Wns_ld;
     a.Wp = ly.Wnp;
     a.wp_k = rp_round_up(ly.d_in, 128);
     a.bias = ly.bzero;
@@ -1172,7 +944,6 @@ TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     a.W = ly.Wc;
     a.Wq = ly.Wcq;
     a.Wt = nullptr;
-    a.Ws = nullptr;
     a.Wp = ly.Wcp;
     a.wp_k = rp_round_up(ly.d_in, 128);
     a.bias = ly.bzero_c;
@@ -1275,9 +1046,6 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
         a.W = ly.Wn;
         a.Wq = ly.Wnq;
         a.Wt = nullptr;
-        a.Ws = ly.Wns;
-        a.wt_ld = ly.Wns_ld;
-        a.ws_plane = (size_t)ly.N0pad * ly.Wns_ld;
         a.Wp = ly.Wnp;
         a.wp_k = rp_round_up(ly.d_in, 128);
         a.K = ly.d_in;
@@ -1311,9 +1079,6 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     s2.W = ly.W1;
     s2.Wq = ly.W1q;
     s2.Wt = nullptr;
-    s2.Ws = ly.W1s;
-    s2.wt_ld = ly.K1pad;
-    s2.ws_plane = (size_t)ly.N1pad * ly.K1pad;
     s2.Wp = ly.W1p;
     s2.wp_k = rp_round_up(ly.d_hidden, 128);
     s2.bias = ly.b1;

@@ -21,11 +21,9 @@ struct TArgs {
     const float *Wq;               // the same with k by fours, [Kpad / 4][Npad][4] (wave_gemm), or null
     const float *bias;             // [Npad]
     const __hip_bfloat16 *Wt;      // bf16 copy of W, transposed [Npad x Kpad] (k contiguous), or null
-    const unsigned short *Ws;      // fp32 storage: W as three transposed bf16 planes (W = plane 0 + plane 1 + plane 2), or null
-    size_t ws_plane;               // elements per plane
     uint32_t wt_ld;                // its row stride
     const unsigned short *Wp;      // W as three bf16 parts in the order the matrix cores take them (k_split_stream), or null
-    uint32_t wp_k;                 // its rows (a multiple of 128)
+    uint32_t wp_k;                 // its rows (a multiple of 128, never below Kpad)
     uint32_t K, Kpad, N, Npad;
     int act;
     int out_mode;                  // 0 write act(z) to tmp_out[slot] | 1 update H, emit delta | 2 write to tmp_out[vertex]

@@ -1,11 +1,5 @@
 #include "kernels.h"
-#include "transform_args.h"
-
-typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#include "rows.h"
 
 // Row transform of many rows (the Compute step of Sec. 3.3 in re-apply form, and the products of the previous embedding that a
 // layer caches), fp32 numbers on the bf16 matrix cores.
@@ -45,38 +39,6 @@ struct StreamArgs {
     uint32_t o_row, o_bytes;       // rows written (H, D, addend / tmp_out): stride and extent in bytes
     uint32_t o2_row, o2_bytes;     // tmp_out2
 };
-
-__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
-    floatx2 f;
-    f.x = a;
-    f.y = b;
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));     // to nearest even
-}
-// four numbers as PL bf16 numbers each, four to eight bytes per part
-template <int PL>
-__device__ __forceinline__ void split_parts(floatx4 x, uintx2 (&part)[PL]) {
-#pragma unroll
-    for (int p = 0; p < PL; ++p) {
-        part[p].x = to_bf16x2(x.x, x.y);
-        part[p].y = to_bf16x2(x.z, x.w);
-        if (p + 1 < PL) {                                  // what is left: exact
-            x.x -= __uint_as_float(part[p].x << 16);
-            x.y -= __uint_as_float(part[p].x & 0xFFFF0000u);
-            x.z -= __uint_as_float(part[p].y << 16);
-            x.w -= __uint_as_float(part[p].y & 0xFFFF0000u);
-        }
-    }
-}
-
-// element k of the row in slot `slot` as the product takes it
-template <int MODE, int STORE>
-__device__ __forceinline__ float row_number(const TArgs &a, uint32_t slot, uint32_t v, uint32_t k, float scale) {
-    if (MODE == 0) return a.X[(size_t)v * a.d_in + k] * scale;
-    if (MODE == 3) return a.tmp_in[(size_t)slot * a.tmp_ld + k];
-    const float h = rp_load_h(a.Hprev, STORE, (size_t)v * a.d_in + k);
-    if (MODE == 2) return h * a.one_plus_eps + a.X[(size_t)v * a.d_in + k] * scale;
-    return h;
-}
 
 // SW: k per slice, KS slices (K <= SW KS); WN: wavefronts side by side (32 WN columns); MODE, STORE: see fetch_raw (MODE 0, 2, 3, 4).
 // OUT 0: the product goes to tmp_out (and tmp_out2). 1: H is updated; ADD: plus an unscaled cached row, DELTA: the delta row is written too.

@@ -1,5 +1,6 @@
 """Products of many rows (k_split_stream: fp32 numbers as three bf16 parts on the bf16 matrix cores) at small sizes, forced with
-RIPPLE_OPT_STREAM_TRANSFORM = 2, against the oracle and against the fp32 matrix cores (option 0)."""
+RIPPLE_OPT_STREAM_TRANSFORM = 2, against the oracle and against the other kernels' products (option 0); and the tiles of
+k_transform_split, forced with RIPPLE_OPT_SPLIT_MFMA."""
 import numpy as np
 import pytest
 
@@ -91,3 +92,24 @@ def test_rows_of_any_magnitude(scale):
             pair.close()
     print("scale %g: error against 64 bits %.2e, fp32 products %.2e" % (scale, errs[2], errs[0]), flush=True)
     assert errs[2] <= max(1.1 * errs[0], 1.5e-7)
+
+
+# rows of [own | aggregate] (2 d_in of k, from a layer that concatenates and keeps no self term), of more than 256 k, and matrices of
+# 64, 128, 256 and 512 padded columns; project-first layers take the same matrix with its first d_in rows alone
+@pytest.mark.parametrize("kind,widths,self_cache,project_first", [
+    ("sage_mean", (100, 132, 260, 47), False, True), ("sage_mean", (100, 132, 260, 47), False, False), ("sage_mean", (200, 260, 64, 130), False, False),
+    ("sage_mean", (75, 129, 31), False, False), ("gcn_sum", (300, 270, 40), True, False), ("gin_sum", (260, 300, 129), True, True)])
+def test_split_products_of_wide_rows(kind, widths, self_cache, project_first):
+    print("case wide rows", kind, widths, self_cache, project_first, flush=True)
+    pair, graph = make_pair(n=500, e=4000, d0=widths[0], kind=kind, widths=widths, seed=291, slack=64, self_cache=self_cache,
+                            project_first=project_first, split=True)
+    stream = make_stream(pair, graph, MIX, 293)
+    try:
+        pair.check_embeddings()
+        for b, bs in enumerate([1, 40, 200]):
+            print(" batch", b, bs, flush=True)
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload)
+            pair.check_aggregates()
+    finally:
+        pair.close()
