@@ -188,14 +188,14 @@ typedef enum {
     RIPPLE_OPT_STREAM_TRANSFORM = 11, /* 0/1/2 (default 1): products of many rows (from 32,768 on; widths of up to 256) run in persistent
                                      workgroups that write a finished tile while the next one is being multiplied, every
                                      fp32 number as three bf16 parts on the bf16 matrix cores (closer to 64-bit sums than a
-                                     chain of fp32 products); 0 keeps the one-tile-per-workgroup kernels on the fp32 matrix
-                                     cores; 2 takes the streaming kernel whatever the number of rows (for tests). */
+                                     chain of fp32 products); 0 keeps the kernels of one tile per workgroup
+                                     (the same parts) and of one product per wavefront (fp32 products); 2 takes the streaming kernel whatever the number of rows (for tests). */
     RIPPLE_OPT_SORTED_MESSAGES = 12, /* 0/1/2 (default 1): a hop that would be pulled while few of the scanned in-row entries
                                       carry a message, or pushed with many numbers to add, is scattered from the list of its
                                       messages instead, which the out-edge walk writes down by destination; 1 where the previous
                                       batch's counts say so, 2 at every hop from the second on that does not discover (tests), 0
-                                      never. Same results up to the order of the sums. Not used in the deterministic mode, by
-                                      weighted-sum layers and on graphs of more than 2^25 vertices. */
+                                      never. Same results up to the order of the sums. Not used in the deterministic mode and on
+                                      graphs of more than 2^25 vertices. */
     RIPPLE_OPT_DETERMINISTIC = 6  /* 0/1 (default 0), before load_model: every sum is taken in an order that is a function of
                                      the graph and the batches alone (no float atomics: in-rows keep a reproducible order,
                                      hops are gathered along them, rows that several wavefronts read are finished in
@@ -223,8 +223,7 @@ ripple_status ripple_init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
  * weighted sum, Sec. 3.3.3 "Other linear aggregators"): layers with RIPPLE_AGG_WSUM aggregate
  * sum_u alpha_uv h_u, other layers ignore the weights. A weight is fixed when its edge is created: an
  * EDGE_ADD operation on such a graph carries the float32 bits of alpha_uv in its feat_row word, and
- * RIPPLE_EDGE_REWEIGHT replaces it later. Weighted graphs always gather along in-edges (no push kernel) and do
- * not combine with RIPPLE_OPT_DETERMINISTIC. */
+ * RIPPLE_EDGE_REWEIGHT replaces it later. Weighted-sum layers do not combine with RIPPLE_OPT_DETERMINISTIC. */
 ripple_status ripple_init_graph_weighted(ripple_ctx **out, uint32_t n_vertices, uint32_t vertex_capacity,
                                          uint64_t n_edges, uint64_t edge_capacity,
                                          const uint32_t *src, const uint32_t *dst, const float *edge_weights,

@@ -293,7 +293,10 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     RP_TRY(block_alloc(c, g, &c->graph_block, true));
     RP_TRY(dev_alloc(c, &c->out_pool, (size_t)pool_cap, false));
     RP_TRY(dev_alloc(c, &c->in_pool, (size_t)pool_cap, false));
-    if (weights) RP_TRY(dev_alloc(c, &c->in_w, (size_t)pool_cap, false));
+    if (weights) {
+        RP_TRY(dev_alloc(c, &c->in_w, (size_t)pool_cap, false));
+        RP_TRY(dev_alloc(c, &c->out_w, (size_t)pool_cap, false));
+    }
     {   // pinned memory, in one allocation (200 to 300 us each, whatever the size): counters, the flag, read-back, and the staging of
         // ordinary batches
         const size_t ctr_at = 0, flag_at = (sizeof(DevCtr) + 63) & ~(size_t)63, io_at = flag_at + 64;
@@ -369,7 +372,7 @@ static bool in_pin_block(const ripple_ctx *c, const void *p) {
 extern "C" void ripple_destroy(ripple_ctx *c) {
     if (!c) return;
     hipStreamSynchronize(c->stream);
-    void *ptrs[] = {c->graph_block, c->list_block, c->batch_block, c->pair_block, c->part_block, c->out_pool, c->in_pool, c->in_w, c->D[0], c->D[1], c->tmp, c->PD,
+    void *ptrs[] = {c->graph_block, c->list_block, c->batch_block, c->pair_block, c->part_block, c->out_pool, c->in_pool, c->in_w, c->out_w, c->D[0], c->D[1], c->tmp, c->PD,
                     c->MSG, c->side_v, c->side_acc, c->Pold, c->sold, c->gat_mag, c->gat_rec, c->seg_block, c->gather_d, c->gather_ids};
     for (void *p : ptrs)
         if (p) hipFree(p);
@@ -701,6 +704,10 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         Block b;
         b.add(&c->pairs, 2 * (size_t)c->pair_cap);
         b.add(&c->pair_sorted, c->pair_cap);
+        if (c->out_w) {                                  // ... and the edges' weights
+            b.add(&c->pair_w, 2 * (size_t)c->pair_cap);
+            b.add(&c->pair_w_sorted, c->pair_cap);
+        }
         RP_TRY(block_alloc(c, b, &c->pair_block, false));
     }
     // bitmaps: layers 0..L, then S, then V_added, contiguous; reporting copies separately
@@ -1039,9 +1046,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         // previous batch pushed with a wide margin the pull kernel is not even enqueued (pushing is
         // always correct; the prediction only saves a launch). The same goes for the discovering
         // mode: its kernels are enqueued only where the previous batch came near its threshold.
-        // Weighted-sum layers gather along in-edges at every hop (the weights are stored with the in-rows only).
-        const bool wsum = c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
-        if (!wsum && tiny_hop(c, l, n, multi)) {       // two or three launches for the whole hop
+        if (tiny_hop(c, l, n, multi)) {       // two or three launches for the whole hop
             t = rp_timer_begin(c);
             rp_launch_hop_small(c, l, layer_self(c, l));
             rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
@@ -1052,8 +1057,8 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
             continue;
         }
-        const bool may_pull = wsum || (l >= 2 && c->opt_scatter != 1 && !(c->opt_scatter == 0 && c->push_margin[l]));
-        const bool may_disc = l >= 2 && may_pull && (c->opt_scatter == 3 || ((c->opt_scatter == 0 || wsum) && c->disc_near[l]));
+        const bool may_pull = l >= 2 && c->opt_scatter != 1 && !(c->opt_scatter == 0 && c->push_margin[l]);
+        const bool may_disc = l >= 2 && may_pull && (c->opt_scatter == 3 || (c->opt_scatter == 0 && c->disc_near[l]));
         // a frontier that was small last time (and a batch of about the same size) is listed as it is marked
         const bool sparse = !may_disc && small_frontier(c, l, n, multi);
         t = rp_timer_begin(c);
@@ -1067,7 +1072,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         // the hop would be pushed (small sets differ more, depending on the hubs they meet). The kernels make sure on the device that
         // the list is only used if this batch's messages fit and it still pays; else the hop is pulled or pushed.
         uint32_t pair_cap = 0;
-        if (l >= 2 && !wsum && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3 && c->n_cap <= RP_LIST_BUCKETS * RP_LIST_IDS) {
+        if (l >= 2 && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3 && c->n_cap <= RP_LIST_BUCKETS * RP_LIST_IDS) {
             const uint64_t m = c->last_m[l];
             const bool pulls = c->opt_scatter == 2 || m * c->xw[l] * 4ull * (unsigned)c->opt_pull_ratio >= 8ull * c->last_isum[l];
             if (c->opt_sorted == 2) pair_cap = c->pair_cap;
@@ -1104,7 +1109,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_timer_end(c, t, RIPPLE_PH_COMPACT, (int)l);
         }
         t = rp_timer_begin(c);
-        if (!wsum && (c->opt_scatter < 2 || !may_pull)) rp_launch_scatter_push(c, l, may_pull, may_disc, pair_cap);
+        if (c->opt_scatter < 2 || !may_pull) rp_launch_scatter_push(c, l, may_pull, may_disc, pair_cap);
         if (pair_cap) rp_launch_scatter_list(c, l, may_disc, pair_cap);
         if (may_pull) rp_launch_scatter_pull(c, l, false, may_disc, pair_cap);
         rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);

@@ -133,7 +133,7 @@ struct ripple_ctx {
     uint2 *out_meta = nullptr, *in_meta = nullptr;      // {start, len} per vertex
     uint32_t *out_capv = nullptr, *in_capv = nullptr;   // row capacity
     uint32_t *out_pool = nullptr, *in_pool = nullptr;
-    float *in_w = nullptr;                              // edge weights, parallel to in_pool (weighted graphs only)
+    float *in_w = nullptr, *out_w = nullptr;            // edge weights, parallel to in_pool and to out_pool (weighted graphs only)
     uint32_t *alive = nullptr;                          // bitmap
     uint32_t *vstate = nullptr;                         // VS_* bits, zero between batches
     uint32_t *pend_out = nullptr, *pend_in = nullptr;   // appended this batch
@@ -226,6 +226,7 @@ struct ripple_ctx {
     uint32_t last_hop_mode[RIPPLE_MAX_LAYERS + 1] = {0};// 1 + RP_HOP_* of the kernel that moved that hop's messages
     // messages of a hop as (destination, source) pairs in buckets by destination (k_frontier_list), and how many each holds
     uint2 *pairs = nullptr, *pair_sorted = nullptr;     // ... and in order of destination
+    float *pair_w = nullptr, *pair_w_sorted = nullptr;  // weighted graphs: the edges' weights, beside them
     uint32_t *pair_cnt = nullptr;                       // (zero between hops)
     uint32_t pair_cap = 0;                              // messages a listed hop may have; there is room for twice as many
     int opt_sorted = 1;                                 // 0 never, 1 where the last batch says it pays, 2 wherever it can be
@@ -261,7 +262,6 @@ struct ripple_ctx {
         }                                                                              \
     } while (0)
 
-// scatter policy of hop l as the kernels see it (see rp_hop_mode)
 // |A_l| of the previous batch as a hint for launch shapes (tile sizes, grids, which compaction kernel); before
 // the first batch nothing is known and the shapes for large sets are taken, which are never far off
 static inline uint32_t rp_rows_hint(const ripple_ctx *c, uint32_t l) { return c->hints_valid ? c->last_a[l] : c->n_cap; }
@@ -270,9 +270,6 @@ static inline bool rp_layer_mono(const ripple_ctx *c, uint32_t l) {      // laye
 }
 static inline bool rp_layer_attn(const ripple_ctx *c, uint32_t l) {
     return l >= 1 && l <= c->L && c->layers[l - 1].agg == RIPPLE_AGG_ATTN;
-}
-static inline int rp_layer_mode(const ripple_ctx *c, uint32_t l) {
-    return c->layers[l - 1].agg == RIPPLE_AGG_WSUM ? 4 : c->opt_scatter;
 }
 static inline uint32_t rp_div_up(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 static inline uint32_t rp_round_up(uint32_t a, uint32_t b) { return (a + b - 1) / b * b; }
@@ -458,15 +455,14 @@ __device__ __forceinline__ float rp_msg_decode_col(uint2 c, uint32_t col) {
 // message once. 2 discover: when A_{l-1} sends along a large share of all edges nearly every vertex
 // is hit, so the in-rows of all live vertices are scanned once, which both gathers the messages and
 // finds A_l, and the out-edge walk that would have marked A_l is skipped.
-// mode: 0 automatic, 1 push, 2 pull, 3 discover wherever it is allowed, 4 automatic without push (layers whose
-// messages carry an edge weight, which is stored with the in-rows only).
+// mode: 0 automatic, 1 push, 2 pull, 3 discover wherever it is allowed.
 #define RP_HOP_PUSH 0
 #define RP_HOP_PULL 1
 #define RP_HOP_DISCOVER 2
 #define RP_HOP_SORTED 3                 // from the list of the hop's messages, sorted by destination (reported only)
 __device__ __forceinline__ int rp_hop_mode(const DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio, int allow_disc) {
     const unsigned long long m = ctr->set[l - 1].m;
-    if (allow_disc && m > 0 && (mode == 3 || ((mode == 0 || mode == 4) && m * 8ull >= ctr->n_edges))) return RP_HOP_DISCOVER;
+    if (allow_disc && m > 0 && (mode == 3 || (mode == 0 && m * 8ull >= ctr->n_edges))) return RP_HOP_DISCOVER;
     if (mode == 1) return RP_HOP_PUSH;
     if (mode >= 2) return RP_HOP_PULL;
     return (m > 0 && m * d * 4ull * (unsigned long long)ratio >= 8ull * ctr->isum[l]) ? RP_HOP_PULL : RP_HOP_PUSH;

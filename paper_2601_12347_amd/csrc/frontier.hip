@@ -19,10 +19,13 @@
 #define LIST_C 4
 struct ListWalk {
     uint2 *pairs;
+    const float *out_w;            // weighted sums: weights beside the out-rows, and where they go beside the pairs
+    float *pair_w;
     uint32_t *cnt;
     ListCut cut;
     uint32_t cap;
 };
+template <int WT>
 __global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff, const uint2 *out_meta,
                                                         const uint32_t *out_pool, uint8_t *mk, DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio,
                                                         int allow_disc, ListWalk w) {
@@ -40,7 +43,8 @@ __global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, co
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         for (uint32_t b = threadIdx.x; b < w.cut.n; b += 1024u) s_at[b] = 0;
         uint32_t v[4 * LIST_C], u[4 * LIST_C];
-        walk_collect<LIST_C>(list, count, M, eoff, out_meta, out_pool, tile * TILE + wave * LIST_C, v, u);
+        float wt[WT ? 4 * LIST_C : 1];
+        walk_collect<LIST_C, WT>(list, count, M, eoff, out_meta, out_pool, w.out_w, tile * TILE + wave * LIST_C, v, u, wt);
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < 4 * LIST_C; ++t)
@@ -62,7 +66,10 @@ __global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, co
         for (int t = 0; t < 4 * LIST_C; ++t)
             if (v[t] != NONE) {
                 const uint32_t at = atomicAdd(&s_at[v[t] >> w.cut.shift], 1u);
-                if (at < FULL) w.pairs[at] = make_uint2(v[t], u[t]);
+                if (at < FULL) {
+                    w.pairs[at] = make_uint2(v[t], u[t]);
+                    if (WT) w.pair_w[at] = wt[WT ? t : 0];
+                }
             }
         __syncthreads();
     }
@@ -450,13 +457,14 @@ __global__ __launch_bounds__(1024) void k_list_eoff(const uint32_t *list, const 
 
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     if (pair_cap) {
-        const ListWalk w = {c->pairs, c->pair_cnt, rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap), pair_cap};
-        hipLaunchKernelGGL(k_frontier_list, dim3(c->n_cu * 2), dim3(1024), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->eoff[l - 1],
-                           c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], rp_layer_mode(c, l), c->opt_pull_ratio, allow_disc ? 1 : 0, w);
+        const ListWalk w = {c->pairs, c->out_w, c->pair_w, c->pair_cnt, rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap), pair_cap};
+        const auto kernel = c->layers[l - 1].agg == RIPPLE_AGG_WSUM ? k_frontier_list<1> : k_frontier_list<0>;
+        hipLaunchKernelGGL(kernel, dim3(c->n_cu * 2), dim3(1024), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->eoff[l - 1],
+                           c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0, w);
         return;
     }
     hipLaunchKernelGGL(k_frontier_mark, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,
-                       c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], rp_layer_mode(c, l),
+                       c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], c->opt_scatter,
                        c->opt_pull_ratio, allow_disc ? 1 : 0);
 }
 

@@ -206,8 +206,8 @@ ripple_status rp_build_graph(ripple_ctx *c, uint32_t n_vertices, uint64_t n_edge
         c->err = "edge_capacity too small for the initial graph";
         rc = RIPPLE_ECAPACITY;
     } else if (n_edges) {
-        hipLaunchKernelGGL(k_fill_rows, dim3(gb), dim3(256), 0, s, src_d, dst_d, (const float *)nullptr, n_edges,
-                           c->out_meta, c->out_pool, (float *)nullptr);
+        hipLaunchKernelGGL(k_fill_rows, dim3(gb), dim3(256), 0, s, src_d, dst_d, (const float *)w_d, n_edges,
+                           c->out_meta, c->out_pool, w_d ? c->out_w : (float *)nullptr);
         // in-rows: stable sort of the edge numbers by sink, then every edge knows its place
         uint32_t *ord = nullptr;
         unsigned key_bits = 1;
@@ -285,7 +285,7 @@ static ripple_status compact_one(ripple_ctx *c, uint2 *meta, uint32_t *capv, uin
 
 ripple_status rp_compact(ripple_ctx *c) {
     // pend_* / dead_* are zero between batches and serve as scratch here
-    ripple_status rc = compact_one(c, c->out_meta, c->out_capv, &c->out_pool, nullptr, &c->ctr->out_top, c->pend_out,
+    ripple_status rc = compact_one(c, c->out_meta, c->out_capv, &c->out_pool, &c->out_w, &c->ctr->out_top, c->pend_out,
                                    c->dead_out);
     if (rc != RIPPLE_OK) return rc;
     rc = compact_one(c, c->in_meta, c->in_capv, &c->in_pool, &c->in_w, &c->ctr->in_top, c->pend_in, c->dead_in);
@@ -314,12 +314,12 @@ struct MutArgs {
     uint2 *out_meta, *in_meta;
     uint32_t *out_capv, *in_capv;
     uint32_t *out_pool, *in_pool;
-    float *in_w;                                 // edge weights parallel to in_pool, or null
+    float *in_w, *out_w;                         // edge weights parallel to in_pool and out_pool, or null
     uint32_t *alive, *vstate;
     uint32_t *pend_out, *pend_in, *dead_out, *dead_in;
     uint32_t *hole_out, *hole_in;                // where a touched row's segment of seg_id / seg_x begins
     uint32_t *seg_id, *seg_x;                    // per row: deletions (seg_x: position; in-rows, seg_id: source), then additions (seg_id:
-                                                 // the other end; in-rows, seg_x: the weight's bits)
+                                                 // the other end; seg_x: the weight's bits)
     uint32_t *srt_id, *srt_x;                    // deterministic mode: long segments in order
     uint32_t *touch_out, *touch_in;
     uint32_t touch_cap;
@@ -479,8 +479,7 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
             if (is_add) {                                   // absent from the shorter of the two rows
                 if (mo.y <= mi.y) po = find_part<W>(ro, mo.y, op.v, wave);
                 else po = find_part<W>(ri, mi.y, op.u, wave);
-            } else if (!is_edge) {                          // EDGE_REWEIGHT: the edge must exist; the rows' shape stays
-                if (a.in_w) pi = find_part<W>(ri, mi.y, op.u, wave);
+            } else if (!is_edge && !a.in_w) {               // EDGE_REWEIGHT (else like a deletion: the edge must exist in both rows)
             } else if (W == 1) {
                 po = find_part<1>(ro, mo.y, op.v, 0);
                 if (po >= 0) pi = find_part<1>(ri, mi.y, op.u, 0);
@@ -498,12 +497,14 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
             pi = s_pos[1];
         }
         if (ok && is_add) st = po < 0 ? 1u : 0u;
-        else if (ok && !is_edge) st = pi >= 0 ? 1u : 0u;
         else if (ok) {
             st = (po >= 0 && pi >= 0) ? 1u : 0u;
             if (first && (po >= 0) != (pi >= 0)) a.ctr->error = 3;     // the two adjacencies disagree
         }
-        if (first && !is_edge && st) a.pos_in[i] = (uint32_t)pi;
+        if (first && !is_edge && st) {
+            a.pos_out[i] = (uint32_t)po;
+            a.pos_in[i] = (uint32_t)pi;
+        }
     }
     if (first) {
         if (judged) a.status[i] = st;
@@ -776,9 +777,10 @@ __device__ __forceinline__ void apply_op(const MutArgs &a, uint32_t i) {
         a.in_pool[ri] = RP_TOMB;
         list_changed(a, s, op.u, op.v, -alpha, -1.0f);
     } else {
-        const uint32_t si = a.hole_in[op.v] + a.dead_in[op.v] + a.rank_in[i];
+        const uint32_t si = a.hole_in[op.v] + a.dead_in[op.v] + a.rank_in[i], so = a.hole_out[op.u] + a.dead_out[op.u] + a.rank_out[i];
         if (a.in_w) alpha = __uint_as_float(op.feat_row);   // weighted graphs: EDGE_ADD carries the weight's bits there
-        a.seg_id[a.hole_out[op.u] + a.dead_out[op.u] + a.rank_out[i]] = op.v;
+        a.seg_id[so] = op.v;
+        a.seg_x[so] = __float_as_uint(alpha);
         a.seg_id[si] = op.u;
         a.seg_x[si] = __float_as_uint(alpha);
         list_changed(a, s, op.u, op.v, alpha, 1.0f);
@@ -853,6 +855,7 @@ __global__ __launch_bounds__(256) void k_edges(MutArgs a, uint32_t tb, uint32_t 
         }
         if (op.kind == RIPPLE_EDGE_REWEIGHT && lane == 0) {  // the weighted sums of the sink gain (alpha_new - alpha_old) h_u
             *wp = given;
+            a.out_w[a.out_meta[op.u].x + a.pos_out[i]] = given;
             list_changed(a, atomicAdd(&a.ctr->n_struct, 1u), op.u, op.v, weighted, 0.0f);
         }
     }
@@ -1158,7 +1161,7 @@ __device__ __forceinline__ void finish_rows(const MutArgs &a, uint32_t gw, uint3
         uint2 *meta = is_out ? a.out_meta : a.in_meta;
         uint32_t *capv = is_out ? a.out_capv : a.in_capv;
         uint32_t *pool = is_out ? a.out_pool : a.in_pool;
-        float *wp = is_out ? nullptr : a.in_w;             // weights travel with the in-row's entries
+        float *wp = is_out ? a.out_w : a.in_w;             // weights travel with the rows' entries
         uint32_t *deadv = is_out ? a.dead_out : a.dead_in;
         uint32_t *pendv = is_out ? a.pend_out : a.pend_in;
         if (!aborted) {
@@ -1286,6 +1289,7 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
     a.out_pool = c->out_pool;
     a.in_pool = c->in_pool;
     a.in_w = c->in_w;
+    a.out_w = c->out_w;
     a.alive = c->alive;
     a.vstate = c->vstate;
     a.pend_out = c->pend_out;

@@ -20,10 +20,10 @@
 
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
 
-template <int NJ, int PK>
+template <int NJ, int PK, int WT>
 __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, const uint32_t *count_ptr,
                                                       const uint32_t *eoff, const float *D, uint32_t ldd, uint32_t d,
-                                                      const uint2 *out_meta, const uint32_t *out_pool, float *X,
+                                                      const uint2 *out_meta, const uint32_t *out_pool, const float *out_w, float *X,
                                                       DevCtr *ctr, uint32_t l, int may_pull, int mode, int ratio, int allow_disc,
                                                       uint32_t list_cap, int list_force) {
     const int hm = rp_hop_mode(ctr, l, d, mode, ratio, allow_disc);
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, cons
         if (rp_hop_listed(ctr, l, d, cp ? count_ptr[1] : 0u, list_cap, list_force, hm)) return;
     }
     if (*count_ptr && blockIdx.x == 0 && threadIdx.x == 0) ctr->hop_mode[l] = 1u + RP_HOP_PUSH;
-    push_edges<NJ, PK>(list, count_ptr, eoff, D, nullptr, ldd, d, out_meta, out_pool, X, (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
+    push_edges<NJ, PK, WT>(list, count_ptr, eoff, D, nullptr, ldd, d, out_meta, out_pool, out_w, X, (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
                        (gridDim.x * blockDim.x) >> 6);
 }
 
@@ -44,10 +44,16 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
     const float *D = packed ? (const float *)c->MSG : (proj ? c->PD : c->D[(l - 1) & 1]);
     const uint32_t ldd = proj ? c->pd_ld : d;
     dim3 grid(c->n_cu * 8), block(256);
-#define PUSH_CASE_PK(NJ, PK)                                                                                       \
-    hipLaunchKernelGGL((k_scatter_push<NJ, PK>), grid, block, 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,     \
-                       c->eoff[l - 1], D, ldd, d, c->out_meta, c->out_pool, c->X[l], c->ctr, l, may_pull ? 1 : 0,  \
+    const bool wt = c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
+#define PUSH_CASE_WT(NJ, PK, WT)                                                                                   \
+    hipLaunchKernelGGL((k_scatter_push<NJ, PK, WT>), grid, block, 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,     \
+                       c->eoff[l - 1], D, ldd, d, c->out_meta, c->out_pool, c->out_w, c->X[l], c->ctr, l, may_pull ? 1 : 0,  \
                        c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0, pair_cap, c->opt_sorted == 2 ? 1 : 0)
+#define PUSH_CASE_PK(NJ, PK)                     \
+    do {                                         \
+        if (wt) PUSH_CASE_WT(NJ, PK, 1);         \
+        else PUSH_CASE_WT(NJ, PK, 0);            \
+    } while (0)
 #define PUSH_CASE(NJ) PUSH_CASE_PK(NJ, 0)
     if (packed) PUSH_CASE_PK(1, 1);
     else if (d <= 64) PUSH_CASE(1);
@@ -57,6 +63,7 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
     else PUSH_CASE(16);
 #undef PUSH_CASE
 #undef PUSH_CASE_PK
+#undef PUSH_CASE_WT
 }
 
 // ---------------------------------------------------------------------------------
@@ -282,6 +289,8 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
 struct ListArgs {
     const uint2 *pairs;
     uint2 *sorted;
+    const float *pair_w;           // weighted sums: the edges' weights, beside the pairs
+    float *sorted_w;
     uint32_t *cnt;
     ListCut cut;
     const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
@@ -307,6 +316,7 @@ __device__ __forceinline__ bool list_is_used(const ListArgs &a, uint32_t &M, boo
 
 // A workgroup per bucket: its pairs counted per destination in LDS, then put in place behind the pairs of the buckets before it. The order
 // within a destination is that in which the pairs come up.
+template <int WT>
 __global__ __launch_bounds__(256) void k_list_order(ListArgs a) {
     uint32_t M;
     bool made;
@@ -350,11 +360,20 @@ __global__ __launch_bounds__(256) void k_list_order(ListArgs a) {
     __syncthreads();
     for (uint32_t c0 = tid; c0 < n; c0 += 256u * PER) {
         uint2 p[PER];
+        float w[PER];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) p[k] = from[min(c0 + 256u * k, n - 1u)];
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t i = min(c0 + 256u * k, n - 1u);
+            p[k] = from[i];
+            w[k] = WT ? a.pair_w[(size_t)bucket * a.cut.room + i] : 1.0f;
+        }
 #pragma unroll
         for (int k = 0; k < PER; ++k)
-            if (c0 + 256u * k < n) a.sorted[atomicAdd(&s_at[p[k].x & mask], 1u)] = p[k];
+            if (c0 + 256u * k < n) {
+                const uint32_t to = atomicAdd(&s_at[p[k].x & mask], 1u);
+                a.sorted[to] = p[k];
+                if (WT) a.sorted_w[to] = w[k];
+            }
     }
 }
 
@@ -364,7 +383,7 @@ __device__ __forceinline__ void list_clear(const ListArgs &a) {
     if (i < a.cut.n) a.cnt[i] = 0;
 }
 
-template <int NJ>
+template <int NJ, int WT>
 __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
     uint32_t M;
     bool made;
@@ -405,13 +424,16 @@ __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
     };
     uint32_t e = c_begin * 64u + lane;
     uint2 nx = (e < M) ? a.sorted[e] : make_uint2(NONE, 0u);
+    float nx_w = (WT && e < M) ? a.sorted_w[e] : 1.0f;
     for (uint32_t c = c_begin; c < c_end; ++c) {
         const uint2 my = nx;
+        const float my_w = nx_w;
         const uint32_t n = min(64u, M - c * 64u);
         e += 64u;                                            // the next chunk's pairs are on their way during the gathers
         nx = (c + 1 < c_end && e < M) ? a.sorted[e] : make_uint2(NONE, 0u);
+        if (WT) nx_w = (c + 1 < c_end && e < M) ? a.sorted_w[e] : 1.0f;
         for (uint32_t k0 = 0; k0 < n; k0 += G) {
-            float r[G][NJ], rx[G][NJ];
+            float r[G][NJ], rx[G][NJ], w[G];
             uint32_t vk[G];
             uint32_t prev = cur;                             // every pair before k0 has been summed: cur is pair k0 - 1's destination
 #pragma unroll
@@ -419,6 +441,7 @@ __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
                 const int k = (int)min(k0 + g, 63u);
                 const uint32_t uk = (uint32_t)__builtin_amdgcn_readlane((int)my.y, k);
                 vk[g] = (uint32_t)__builtin_amdgcn_readlane((int)my.x, k);
+                w[g] = WT ? __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(my_w), k)) : 1.0f;
                 const bool live = k0 + g < n;
                 const bool own = live && vk[g] != prev && vk[g] != v_first && vk[g] != v_last;   // first pair of an unshared destination
                 prev = vk[g];
@@ -439,7 +462,7 @@ __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
                         for (int j = 0; j < NJ; ++j) acc[j] = rx[g][j];
                     }
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j) acc[j] += r[g][j];
+                    for (int j = 0; j < NJ; ++j) acc[j] = WT ? __builtin_fmaf(w[g], r[g][j], acc[j]) : acc[j] + r[g][j];
                 }
             }
         }
@@ -665,6 +688,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
 
 // The list of a hop's messages (see k_scatter_list) where they are packed rows: four at a time, 16 lanes each, like k_scatter_pull4. The
 // destination's row, if no other run has pairs of it, is read with its first message and stored with the sum.
+template <int WT>
 __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
     uint32_t M;
     bool made;
@@ -703,12 +727,15 @@ __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
     };
     uint32_t e = c_begin * 64u + lane;
     uint2 nx = (e < M) ? a.sorted[e] : make_uint2(PULL4_PAD, 0u);
+    float nx_w = (WT && e < M) ? a.sorted_w[e] : 0.0f;
     uint32_t before = NONE;                                 // the destination of the pair before the chunk
     for (uint32_t c = c_begin; c < c_end; ++c) {
         const uint2 my = nx;
+        const float my_w = nx_w;
         const uint32_t n = min(64u, M - c * 64u);
         e += 64u;
         nx = (c + 1 < c_end && e < M) ? a.sorted[e] : make_uint2(PULL4_PAD, 0u);
+        if (WT) nx_w = (c + 1 < c_end && e < M) ? a.sorted_w[e] : 0.0f;
         // which pairs are the first of a destination that nobody else writes
         uint32_t left = (uint32_t)__shfl_up((int)my.x, 1);
         left = lane == 0 ? before : left;
@@ -717,12 +744,13 @@ __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
         for (uint32_t k0 = 0; k0 < n; k0 += 4u * PULL4_QUADS) {
             uint32_t v[PULL4_QUADS];
             uint2 ch[PULL4_QUADS];
-            float x[PULL4_QUADS][3];
+            float x[PULL4_QUADS][3], wk[PULL4_QUADS];
 #pragma unroll
             for (int r = 0; r < PULL4_QUADS; ++r) {
                 const int idx = (int)(k0 + 4u * r + grp);    // below 64; past the list's end: row 0, no destination
                 const uint32_t u = (uint32_t)__shfl((int)my.y, idx);
                 v[r] = (uint32_t)__shfl((int)my.x, idx);
+                wk[r] = WT ? __shfl(my_w, idx) : 1.0f;
                 const bool own = __shfl((int)first, idx) != 0;
                 const uintx2 w2 = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(mres, (u << 7) + 8u * sub, 0, 0));
                 ch[r] = make_uint2(w2.x, w2.y);
@@ -736,6 +764,7 @@ __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
                 if (k0 + 4u * r >= n) continue;
                 float q0, q1, q2, f;
                 rp_msg_decode_parts(ch[r], q0, q1, q2, f);
+                if (WT) f *= wk[r];                          // a power of two times the weight: exact
                 if (!__any(v[r] != cur)) {                   // the whole quad goes on
                     acc0 = __builtin_fmaf(q0, f, acc0);
                     acc1 = __builtin_fmaf(q1, f, acc1);
@@ -862,7 +891,7 @@ void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow
     a.X = c->X[l];
     a.ctr = c->ctr;
     a.l = l;
-    a.mode = rp_layer_mode(c, l);
+    a.mode = c->opt_scatter;
     a.ratio = c->opt_pull_ratio;
     a.allow_disc = allow_disc ? 1 : 0;
     dim3 grid(c->n_cu * 8), block(256);
@@ -920,17 +949,28 @@ void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t
     a.X = c->X[l];
     a.ctr = c->ctr;
     a.l = l;
-    a.mode = rp_layer_mode(c, l);
+    a.mode = c->opt_scatter;
     a.ratio = c->opt_pull_ratio;
     a.allow_disc = allow_disc ? 1 : 0;
-    hipLaunchKernelGGL(k_list_order, dim3(a.cut.n), dim3(256), 0, c->stream, a);
+    a.pair_w = c->pair_w;
+    a.sorted_w = c->pair_w_sorted;
+    const bool wt = ly.agg == RIPPLE_AGG_WSUM;
+    if (wt) hipLaunchKernelGGL(k_list_order<1>, dim3(a.cut.n), dim3(256), 0, c->stream, a);
+    else hipLaunchKernelGGL(k_list_order<0>, dim3(a.cut.n), dim3(256), 0, c->stream, a);
     const dim3 grid(c->n_cu * 8), block(256);
-    if (packed) hipLaunchKernelGGL(k_scatter_list4, grid, block, 0, c->stream, a);
-    else if (a.d <= 64) hipLaunchKernelGGL((k_scatter_list<1>), grid, block, 0, c->stream, a);
-    else if (a.d <= 128) hipLaunchKernelGGL((k_scatter_list<2>), grid, block, 0, c->stream, a);
-    else if (a.d <= 256) hipLaunchKernelGGL((k_scatter_list<4>), grid, block, 0, c->stream, a);
-    else if (a.d <= 512) hipLaunchKernelGGL((k_scatter_list<8>), grid, block, 0, c->stream, a);
-    else hipLaunchKernelGGL((k_scatter_list<16>), grid, block, 0, c->stream, a);
+#define LIST_CASE(NJ)                                                                             \
+    do {                                                                                          \
+        if (wt) hipLaunchKernelGGL((k_scatter_list<NJ, 1>), grid, block, 0, c->stream, a);        \
+        else hipLaunchKernelGGL((k_scatter_list<NJ, 0>), grid, block, 0, c->stream, a);           \
+    } while (0)
+    if (packed && wt) hipLaunchKernelGGL(k_scatter_list4<1>, grid, block, 0, c->stream, a);
+    else if (packed) hipLaunchKernelGGL(k_scatter_list4<0>, grid, block, 0, c->stream, a);
+    else if (a.d <= 64) LIST_CASE(1);
+    else if (a.d <= 128) LIST_CASE(2);
+    else if (a.d <= 256) LIST_CASE(4);
+    else if (a.d <= 512) LIST_CASE(8);
+    else LIST_CASE(16);
+#undef LIST_CASE
 }
 
 // Deterministic mode: the hop is pulled into A_l (bootstrap: into every live vertex, all of them recomputed;

@@ -191,10 +191,11 @@ __device__ __forceinline__ void frontier_walk(const uint32_t *list, const uint32
 }
 
 // Edges c0 * MARK_CHUNK .. (c0 + C) * MARK_CHUNK - 1 of the flattened out-edge space, four per lane and chunk: destination v (0xFFFFFFFF past
-// the end) and source u. By all 64 lanes; rows are found as in frontier_walk.
-template <int C>
+// the end) and source u, and (WT) the edge's weight w. By all 64 lanes; rows are found as in frontier_walk.
+template <int C, int WT>
 __device__ __forceinline__ void walk_collect(const uint32_t *list, uint32_t count, uint32_t M, const uint32_t *eoff, const uint2 *out_meta,
-                                             const uint32_t *out_pool, uint32_t c0, uint32_t (&v)[4 * C], uint32_t (&u)[4 * C]) {
+                                             const uint32_t *out_pool, const float *out_w, uint32_t c0, uint32_t (&v)[4 * C], uint32_t (&u)[4 * C],
+                                             float (&w)[WT ? 4 * C : 1]) {
     const int lane = rp_lane();
     const uint32_t last = count - 1;
     uint32_t i_lo = c0 * MARK_CHUNK < M ? rp_seg_search_wave(eoff, 0, last, c0 * MARK_CHUNK) : 0u;
@@ -220,6 +221,7 @@ __device__ __forceinline__ void walk_collect(const uint32_t *list, uint32_t coun
             }
             u[4 * k + t] = src;
             if (e < e1) v[4 * k + t] = out_pool[at];
+            if (WT) w[WT ? 4 * k + t : 0] = e < e1 ? out_w[at] : 0.0f;
         }
         i_lo = fits ? min(last, i_lo + rp_count_le(bnd, e1)) : rp_seg_forward(eoff, i_hi, last, e1);
     }

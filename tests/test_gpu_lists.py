@@ -1,12 +1,12 @@
 """Hops from the list of their messages (k_frontier_list, k_scatter_list, k_scatter_list4): packed rows, buckets that take more than one
-round, buckets that run over. (Rows of other widths: test_gpu_updates.py, sorted messages.)"""
+round, buckets that run over; and the weights beside the out-rows that pushed and listed messages are multiplied by. (Rows of other widths: test_gpu_updates.py, sorted messages.)"""
 import numpy as np
 import pytest
 
 import paper_2601_12347_amd as rp
 import ripple_inputs as ri
 from harness import Pair, make_pair, make_stream
-from ripple_inputs.graphs import OP_FEAT_UPDATE
+from ripple_inputs.graphs import OP_EDGE_ADD, OP_EDGE_DEL, OP_EDGE_REWEIGHT, OP_FEAT_UPDATE
 
 pytestmark = pytest.mark.gpu
 
@@ -64,5 +64,65 @@ def test_one_destination_with_thousands_of_messages(room, widths):
             assert res.messages[2] >= 2 * k
             assert b == 0 or res.hop_mode[2] == (4 if room == "rounds" else 2)   # (the first batch cuts its buckets without a hint)
         pair.check_aggregates()
+    finally:
+        pair.close()
+
+
+MIXW = {"edge_add": 0.25, "edge_del": 0.2, "feat": 0.25, "vadd": 0.05, "vdel": 0.05, "reweight": 0.2}
+
+
+@pytest.mark.parametrize("way", ["push", "list", "small"])
+@pytest.mark.parametrize("kind,widths,store", [("gcn_wsum", (12, 96, 47), "f32"), ("sage_wsum", (75, 190, 190, 23), "f32"), ("gcn_wsum", (24, 300, 130), "f32"),
+                                               ("gcn_wsum", (24, 100, 48), "bf16"), ("gcn_wsum", (17, 600, 40), "f32")])
+def test_weights_along_out_rows(way, kind, widths, store):
+    print("case out-row weights", way, kind, widths, store, flush=True)
+    pair, graph = make_pair(n=700, e=6000, d0=widths[0], kind=kind, widths=widths, seed=381, slack=128, store=store, weighted=True, edge_capacity=7000)
+    if way == "push":
+        rp.ripple_set_option(pair.ctx, rp.OPT_SCATTER_MODE, 1)
+    if way == "list":
+        rp.ripple_set_option(pair.ctx, rp.OPT_SORTED_MESSAGES, 2)
+        rp.ripple_set_option(pair.ctx, rp.OPT_SCATTER_MODE, 2)
+    if way != "small":
+        rp.ripple_set_option(pair.ctx, rp.OPT_SPARSE_FRONTIER, 0)
+    stream = make_stream(pair, graph, MIXW, 383, weighted=True)
+    seen = set()
+    try:
+        for b, bs in enumerate([1, 30, 200, 30, 300, 3, 3]):
+            ops, payload, _ = stream.next_batch(bs)
+            res, _, _ = pair.step(ops, payload)
+            modes = list(res.hop_mode[1:len(widths)])
+            print(" batch", b, bs, "hop modes", modes, flush=True)
+            seen |= set(modes)
+        pair.check_aggregates()
+    finally:
+        pair.close()
+    assert (4 if way == "list" else 1) in seen
+
+
+@pytest.mark.parametrize("gone", [1, 2, 64, 65, 200])
+def test_weights_of_a_long_out_row(gone):
+    """A vertex with 300 out-edges: `gone` of them deleted (every way in which a row closes its holes), some of the others given new weights,
+    more added than the row has room for. Each time its features change and the messages along every edge of the row are compared."""
+    n, k = 700, 300
+    src = np.concatenate([np.zeros(k, np.uint32), np.arange(1, 600, dtype=np.uint32)])
+    dst = np.concatenate([np.arange(10, 10 + k, dtype=np.uint32), np.arange(2, 601, dtype=np.uint32)])
+    weights = ri.edge_weights(len(src), 391)
+    pair = Pair(n, n + 8, src, dst, ri.features(n, 12, 392), ri.make_model("gcn_wsum", (12, 20, 6), 393), weights=weights)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SCATTER_MODE, 1)
+    rng = np.random.default_rng(394)
+    bits = lambda x: int(np.float32(x).view(np.uint32))
+    feat = lambda: pair.step(np.array([(OP_FEAT_UPDATE, 0, 0, 0)], np.uint32), rng.standard_normal((1, 12)).astype(np.float32))
+    out = rng.permutation(np.arange(10, 10 + k))
+    try:
+        print("case long out-row", gone, flush=True)
+        feat()
+        pair.step(np.array([(OP_EDGE_DEL, 0, v, 0) for v in out[:gone]] + [(OP_EDGE_REWEIGHT, 0, v, bits(rng.uniform(0.2, 2))) for v in out[gone:gone + 40]], np.uint32), None)
+        feat()
+        pair.step(np.array([(OP_EDGE_ADD, 0, v, bits(rng.uniform(0.2, 2))) for v in range(320, 640)], np.uint32), None)
+        feat()
+        pair.step(np.array([(OP_EDGE_REWEIGHT, 0, v, bits(rng.uniform(0.2, 2))) for v in range(400, 500)] + [(OP_EDGE_DEL, 0, v, 0) for v in range(320, 330)], np.uint32), None)
+        feat()
+        pair.check_aggregates()
+        pair.check_graph()
     finally:
         pair.close()
