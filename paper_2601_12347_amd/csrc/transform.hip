@@ -363,52 +363,98 @@ __device__ __forceinline__ void addend_only_rows(const TArgs &a, uint32_t gw, ui
     }
 }
 
-// The same for sum / mean layers (no denominators), element by element over the flattened (slot, column) space: rows
-// of a narrow layer (47 columns) leave a quarter of a wavefront idle when a lane is a column, and consecutive slots are
-// mostly consecutive vertices, so consecutive lanes read consecutive addresses across row ends. OLD: the stored row is
-// read (a delta row is written); ADD2: there is a cached self term.
+// The same for sum / mean layers (no denominators), four columns per thread over the flattened (slot, group) space: rows of a narrow layer
+// (47 columns) leave a quarter of a wavefront idle when a lane is a column, and consecutive slots are mostly consecutive vertices, so
+// consecutive lanes read consecutive addresses across row ends. OLD: the stored row is read (a delta row is written); ADD2: there is a
+// cached self term. Bound by memory; with a number per thread it was bound by the two divisions and the three index reads of
+// each: 2.4 M rows of 47 with a self term 411 -> 298 us (1.4 GB: 4.6 TB/s), 1 M of them scattered over the graph 203 -> 186, 2.4 M bf16
+// rows 196 -> 178. (Four groups per round: 305, 186 and 186.)
 template <bool BF, bool OLD, bool ADD2>
 __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
-    constexpr int U = 4;                                   // elements per thread and round: their loads overlap
-    const uint32_t count = *a.count_ptr;
-    const uint32_t total = count * a.N;                    // < 2^32 (checked by the launch)
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint64_t e0 = blockIdx.x * blockDim.x + threadIdx.x; e0 < total; e0 += (uint64_t)stride * U) {
-        uint32_t col[U];
+    constexpr int U = 2;                                   // groups per thread and round: their loads overlap
+    const uint32_t count = *a.count_ptr, groups = (a.N + 3u) / 4u;
+    const uint32_t total = count * groups;                 // < 2^32 (checked by the launch)
+    const uint32_t stride = gridDim.x * blockDim.x, t0 = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t0 >= total) return;
+    const uint32_t d_slot = stride / groups, d_g = stride - d_slot * groups;   // one division per thread: what a stride adds to slot and group
+    uint32_t slot = t0 / groups, g = t0 - slot * groups;
+    for (uint64_t e0 = t0; e0 < total; e0 += (uint64_t)stride * U) {
+        uint32_t col[U], sl[U];
         size_t hidx[U];
-        float sc[U], y[U], p[U], old[U];
+        float sc[U];
+        floatx4 y[U], p[U], old[U];
         bool ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint64_t e = e0 + (uint64_t)u * stride;
-            ok[u] = e < total;
-            const uint32_t ec = ok[u] ? (uint32_t)e : total - 1u;   // past the end: the last element again, not stored
-            const uint32_t slot = ec / a.N;
-            col[u] = ec - slot * a.N;
-            const uint32_t v = a.list[slot];
-            hidx[u] = (size_t)v * a.N + col[u];
-            const uint32_t deg = a.in_meta[v].y;
-            sc[u] = a.mean ? 1.0f / (float)(deg > 1u ? deg : 1u) : 1.0f;
+            ok[u] = e0 + (uint64_t)u * stride < total;
+            sl[u] = ok[u] ? slot : count - 1u;             // past the end: the last row again, not stored
+            col[u] = 4u * g;
+            slot += d_slot;
+            g += d_g;
+            if (g >= groups) {
+                g -= groups;
+                ++slot;
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            y[u] = a.addend[hidx[u]];
-            p[u] = ADD2 ? a.addend2[hidx[u]] : 0.0f;
-            old[u] = !OLD ? 0.0f : BF ? __bfloat162float(((const __hip_bfloat16 *)a.Hout)[hidx[u]]) : ((const float *)a.Hout)[hidx[u]];
+            const uint32_t v = a.list[sl[u]];
+            hidx[u] = (size_t)v * a.N + col[u];
+            const uint32_t deg = a.mean ? a.in_meta[v].y : 1u;
+            sc[u] = 1.0f / (float)(deg > 1u ? deg : 1u);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                      // (up to three numbers past a row: the arrays have room behind them)
+            y[u] = *(const floatx4u *)(a.addend + hidx[u]);
+            p[u] = old[u] = (floatx4)(0.0f);
+            if (ADD2) p[u] = *(const floatx4u *)(a.addend2 + hidx[u]);
+            if (OLD && BF) {
+                const uintx2u w = *(const uintx2u *)((const __hip_bfloat16 *)a.Hout + hidx[u]);
+                old[u].x = __uint_as_float(w.x << 16);
+                old[u].y = __uint_as_float(w.x & 0xFFFF0000u);
+                old[u].z = __uint_as_float(w.y << 16);
+                old[u].w = __uint_as_float(w.y & 0xFFFF0000u);
+            } else if (OLD) {
+                old[u] = *(const floatx4u *)((const float *)a.Hout + hidx[u]);
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (!ok[u]) continue;
-            float z = y[u] * sc[u] + a.bias[col[u]] + p[u];
-            if (a.act == RIPPLE_ACT_RELU) z = z > 0.0f ? z : 0.0f;
-            if (BF) {
-                const __hip_bfloat16 zr = __float2bfloat16(z);
-                z = __bfloat162float(zr);
-                ((__hip_bfloat16 *)a.Hout)[hidx[u]] = zr;
-            } else {
-                ((float *)a.Hout)[hidx[u]] = z;
+            const uint32_t n = min(4u, a.N - col[u]);
+            floatx4 z, dl;
+            __hip_bfloat16 zr[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float b = a.bias[min(col[u] + (uint32_t)k, a.N - 1u)];
+                float t = y[u][k] * sc[u] + b + p[u][k];
+                if (a.act == RIPPLE_ACT_RELU) t = t > 0.0f ? t : 0.0f;
+                if (BF) {
+                    zr[k] = __float2bfloat16(t);
+                    t = __bfloat162float(zr[k]);
+                }
+                z[k] = t;
+                dl[k] = a.d_old ? old[u][k] : t - old[u][k];
             }
-            if (OLD) a.D[hidx[u]] = a.d_old ? old[u] : z - old[u];
+            if (n == 4u) {
+                if (BF) {
+                    uintx2u w;
+                    w.x = __float_as_uint(z.x) >> 16 | (__float_as_uint(z.y) & 0xFFFF0000u);
+                    w.y = __float_as_uint(z.z) >> 16 | (__float_as_uint(z.w) & 0xFFFF0000u);
+                    *(uintx2u *)((__hip_bfloat16 *)a.Hout + hidx[u]) = w;
+                } else {
+                    *(floatx4u *)((float *)a.Hout + hidx[u]) = z;
+                }
+                if (OLD) *(floatx4u *)(a.D + hidx[u]) = dl;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    if ((uint32_t)k >= n) continue;
+                    if (BF) ((__hip_bfloat16 *)a.Hout)[hidx[u] + k] = zr[k];
+                    else ((float *)a.Hout)[hidx[u] + k] = z[k];
+                    if (OLD) a.D[hidx[u] + k] = dl[k];
+                }
+            }
         }
     }
 }

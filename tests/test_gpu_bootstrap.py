@@ -4,7 +4,7 @@ import pytest
 
 import paper_2601_12347_amd as rp
 import ripple_inputs as ri
-from harness import make_pair, config_pair, Pair
+from harness import make_pair, make_stream, config_pair, Pair
 
 pytestmark = pytest.mark.gpu
 
@@ -149,3 +149,29 @@ def test_measured_peaks_are_plausible():
     assert 60.0 < p["mfma_f32_tflops"] < 157.3 * 1.02
     assert 800.0 < p["mfma_bf16_tflops"] < 2500.0 * 1.02
     assert p["compute_units"] >= 64
+
+
+# Rows of project-first layers and rows that are read back, four columns per thread over (row, group): rows of one number, of one group, of
+# every remainder, of 64. Enough vertices (65,536 rows on) for the kernel that takes them so, in the bootstrap and in a batch; a layer
+# before the last one also writes its rows' differences.
+@pytest.mark.parametrize("kind,widths,store", [("sage_mean", (12, 1), "f32"), ("sage_mean", (40, 18, 2), "f32"), ("gcn_sum", (40, 20, 3), "f32"), ("gcn_sum", (44, 21, 5), "bf16"),
+                                               ("sage_mean", (46, 23, 7), "bf16"), ("gcn_sum", (94, 47, 4), "bf16"), ("sage_mean", (130, 64, 9), "f32")])
+def test_narrow_rows_of_many_vertices(kind, widths, store):
+    print("case narrow rows", kind, widths, store, flush=True)
+    pair, graph = make_pair(n=66_000, e=90_000, d0=widths[0], kind=kind, widths=widths, seed=401, slack=1024, store=store)
+    stream = make_stream(pair, graph, {"edge_add": 0.3, "edge_del": 0.2, "feat": 0.4, "vadd": 0.05, "vdel": 0.05}, 403)
+    # bf16 rows: every number is off by up to 2^-9, in two layers' rows that the output depends on (2^-8). A sum of 47 products of random
+    # sign is 1 / (0.64 sqrt(47)) = 1 / 4.4 of the sum of their magnitudes, and the largest of a row's few columns can be half of that in
+    # 66,000 rows: 8.8 * 2^-8 and the row's own 2^-9 = 3.7e-2 (2.97e-2 is met, by the kernel of one number per thread as well).
+    tol = 4e-2 if store == "bf16" else None
+    try:
+        pair.check_embeddings(tol)
+        for bs in (5000, 3, 5000):
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload, tol=tol)
+        ids = np.random.default_rng(405).integers(0, pair.cap, 1003).astype(np.uint32)
+        table = pair.gpu_layer(pair.L)
+        for k in (1, 5, 1003):
+            assert np.array_equal(rp.ripple_get_embeddings(pair.ctx, pair.L, widths[-1], ids=ids[:k]), table[ids[:k]])
+    finally:
+        pair.close()
