@@ -945,6 +945,20 @@ static bool tiny_hop(const ripple_ctx *c, uint32_t l, uint32_t n_ops, bool multi
            (uint64_t)c->last_m[l] * c->xw[l] <= TINY_MAX_NUMBERS;
 }
 
+// |A_l| where no previous batch says it: a replaced row reaches its out-neighbours, any other operation one or two vertices, every hop
+// after it multiplies by the mean degree. Below some thousand rows the kernels do not differ enough to trust a guess with.
+#define GUESS_MIN_ROWS 4096u
+static void guess_rows(ripple_ctx *c, const ripple_update *ops, uint32_t n) {
+    uint64_t feat = 0;
+    for (uint32_t i = 0; i < n; ++i) feat += ops[i].kind == RIPPLE_FEAT_UPDATE || ops[i].kind == RIPPLE_VERTEX_ADD;
+    const uint64_t reach = c->e_cap / c->n_cap + 2;
+    uint64_t rows = feat;
+    for (uint32_t l = 0; l <= c->L; ++l) {
+        c->guess_a[l] = (uint32_t)std::min<uint64_t>(c->n_cap, std::max<uint64_t>(rows, GUESS_MIN_ROWS));
+        rows = std::min<uint64_t>(c->n_cap, rows * reach + (l == 0 ? 2ull * (n - feat) : 0ull));
+    }
+}
+
 // Enqueue one conflict-free piece: Apply, then hop by hop frontier / scatter / transform.
 static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
     const uint32_t n = sb.end - sb.begin;
@@ -952,6 +966,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
     const ripple_update *ops = c->ops_pin + sb.begin;
     rp_launch_mutate(c, ops, n, sb.has_vdel, sb.has_vertex_or_feat);
     rp_timer_end(c, t, RIPPLE_PH_INGEST, 0);
+    if (!c->hints_valid) guess_rows(c, ops, n);
     if (multi)
         hipLaunchKernelGGL(k_or_words, dim3(rp_div_up(c->n_words, 256)), dim3(256), 0, c->stream, c->rep[0], c->bm[0],
                            c->n_words);

@@ -220,6 +220,7 @@ struct ripple_ctx {
     // last batch's sets (reporting)
     uint32_t last_a[RIPPLE_MAX_LAYERS + 1] = {0};
     bool hints_valid = false;                           // last_a / last_cand describe a batch (not the state after the bootstrap)
+    uint32_t guess_a[RIPPLE_MAX_LAYERS + 1] = {0};      // |A_l| as the operations let expect it, where last_a says nothing
     uint32_t last_cand[RIPPLE_MAX_LAYERS + 1] = {0};
     uint32_t last_m[RIPPLE_MAX_LAYERS + 1] = {0};       // messages per hop of the last batch (a size hint)
     uint32_t last_isum[RIPPLE_MAX_LAYERS + 1] = {0};    // in-row entries a pull of that hop would have scanned
@@ -265,6 +266,10 @@ struct ripple_ctx {
 // |A_l| of the previous batch as a hint for launch shapes (tile sizes, grids, which compaction kernel); before
 // the first batch nothing is known and the shapes for large sets are taken, which are never far off
 static inline uint32_t rp_rows_hint(const ripple_ctx *c, uint32_t l) { return c->hints_valid ? c->last_a[l] : c->n_cap; }
+// the same where a choice between kernels hangs on it that are each right for any size: without a previous batch, what the piece's operations reach
+// on a graph of this mean degree. (First batch of a context: three hops of a few vertices each that were given persistent workgroups
+// for every vertex took 20 us a product, tiles take 11.)
+static inline uint32_t rp_rows_guess(const ripple_ctx *c, uint32_t l) { return c->hints_valid ? c->last_a[l] : c->guess_a[l]; }
 static inline bool rp_layer_mono(const ripple_ctx *c, uint32_t l) {      // layer l (1-based) aggregates with max or min
     return l >= 1 && l <= c->L && (c->layers[l - 1].agg == RIPPLE_AGG_MAX || c->layers[l - 1].agg == RIPPLE_AGG_MIN);
 }

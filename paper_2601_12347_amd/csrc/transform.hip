@@ -975,7 +975,7 @@ TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uin
 }
 
 void rp_launch_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
-    launch_t(c, rp_project_args(c, l, list, count_d, bootstrap), bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, rp_project_args(c, l, list, count_d, bootstrap), bootstrap ? c->n_cap : rp_rows_guess(c, l - 1));
 }
 
 // Layers handled project-first that also cache their self term: both products of H^{l-1}[v], with W_self (into PS)
@@ -1012,7 +1012,7 @@ TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
 
 void rp_launch_project_both(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap) {
     TArgs a = rp_project_both_args(c, l, list, count_d, bootstrap);
-    launch_t(c, a, bootstrap ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, a, bootstrap ? c->n_cap : rp_rows_guess(c, l - 1));
 }
 
 // Attention layer l: P[v] = H^{l-1}[v] W0 for the listed vertices (fp32, no bias, no activation).
@@ -1028,7 +1028,7 @@ void rp_launch_gat_project(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     a.tmp_out = ly.P;
     a.tmp_out_ld = ly.ldp;
     a.Hout = nullptr;
-    launch_t(c, a, (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, a, (list == c->all_list) ? c->n_cap : rp_rows_guess(c, l - 1));
 }
 
 // Cached self term of layer l: PS[v] = H^{l-1}[v] W_self for the listed vertices (fp32, no bias).
@@ -1052,7 +1052,7 @@ TArgs rp_self_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
 }
 
 void rp_launch_self_project(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d) {
-    launch_t(c, rp_self_project_args(c, l, list, count_d), (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l - 1));
+    launch_t(c, rp_self_project_args(c, l, list, count_d), (list == c->all_list) ? c->n_cap : rp_rows_guess(c, l - 1));
 }
 
 // Re-apply layer l (1-based) to the vertices in `list` (count on the device).
@@ -1064,7 +1064,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     a.d_old = rp_layer_mono(c, l + 1) ? 1 : 0;
     a.a_mode = (ly.self_mode == RIPPLE_SELF_NONE) ? 0 : (ly.self_mode == RIPPLE_SELF_CONCAT ? 1 : 2);
     // expected row count: the previous batch's (bootstrap passes the list of all live vertices)
-    const uint32_t hint = (list == c->all_list) ? c->n_cap : rp_rows_hint(c, l);
+    const uint32_t hint = (list == c->all_list) ? c->n_cap : rp_rows_guess(c, l);
     if (ly.agg == RIPPLE_AGG_ATTN) {             // h = act(numerator / denominator + b): no product left per row
         a.addend = c->X[l];
         a.den = ly.den;
