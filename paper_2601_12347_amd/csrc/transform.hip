@@ -363,13 +363,15 @@ __device__ __forceinline__ void addend_only_rows(const TArgs &a, uint32_t gw, ui
     }
 }
 
-// The same for sum / mean layers (no denominators), four columns per thread over the flattened (slot, group) space: rows of a narrow layer
+// The same for many rows, four columns per thread over the flattened (slot, group) space: rows of a narrow layer
 // (47 columns) leave a quarter of a wavefront idle when a lane is a column, and consecutive slots are mostly consecutive vertices, so
-// consecutive lanes read consecutive addresses across row ends. OLD: the stored row is read (a delta row is written); ADD2: there is a
-// cached self term. Bound by memory; with a number per thread it was bound by the two divisions and the three index reads of
+// consecutive lanes read consecutive addresses across row ends. OLD: the stored row is read (a delta row is written); KIND 1: there is a
+// cached self term, 2: attention (denominators; a row that is not finite is counted by the thread with its first such column).
+// Bound by memory; with a number per thread it was bound by the two divisions and the three index reads of
 // each: 2.4 M rows of 47 with a self term 411 -> 298 us (1.4 GB: 4.6 TB/s), 1 M of them scattered over the graph 203 -> 186, 2.4 M bf16
-// rows 196 -> 178. (Four groups per round: 305, 186 and 186.)
-template <bool BF, bool OLD, bool ADD2>
+// rows 196 -> 178. (Four groups per round: 305, 186 and 186.) Attention, 300 updates on 31 M edges: rows of 47 columns 119 -> 64 us, of 256
+// with rows of changes 119 -> 105; below three million numbers the row-by-row kernel takes 11 us and this one no less.
+template <bool BF, bool OLD, int KIND>
 __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
     constexpr int U = 2;                                   // groups per thread and round: their loads overlap
     const uint32_t count = *a.count_ptr, groups = (a.N + 3u) / 4u;
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
     for (uint64_t e0 = t0; e0 < total; e0 += (uint64_t)stride * U) {
         uint32_t col[U], sl[U];
         size_t hidx[U];
-        float sc[U];
+        float sc[U], dn[U];
         floatx4 y[U], p[U], old[U];
         bool ok[U];
 #pragma unroll
@@ -400,14 +402,19 @@ __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
         for (int u = 0; u < U; ++u) {
             const uint32_t v = a.list[sl[u]];
             hidx[u] = (size_t)v * a.N + col[u];
-            const uint32_t deg = a.mean ? a.in_meta[v].y : 1u;
-            sc[u] = 1.0f / (float)(deg > 1u ? deg : 1u);
+            if (KIND == 2) {                               // numerator / denominator, 0 without in-neighbours
+                dn[u] = a.den[v];
+                sc[u] = (a.in_meta[v].y > 0u && dn[u] > 0.0f) ? 1.0f / dn[u] : 0.0f;
+            } else {
+                const uint32_t deg = a.mean ? a.in_meta[v].y : 1u;
+                sc[u] = 1.0f / (float)(deg > 1u ? deg : 1u);
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {                      // (up to three numbers past a row: the arrays have room behind them)
             y[u] = *(const floatx4u *)(a.addend + hidx[u]);
             p[u] = old[u] = (floatx4)(0.0f);
-            if (ADD2) p[u] = *(const floatx4u *)(a.addend2 + hidx[u]);
+            if (KIND == 1) p[u] = *(const floatx4u *)(a.addend2 + hidx[u]);
             if (OLD && BF) {
                 const uintx2u w = *(const uintx2u *)((const __hip_bfloat16 *)a.Hout + hidx[u]);
                 old[u].x = __uint_as_float(w.x << 16);
@@ -424,10 +431,12 @@ __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
             const uint32_t n = min(4u, a.N - col[u]);
             floatx4 z, dl;
             __hip_bfloat16 zr[4];
+            bool bad = KIND == 2 && !isfinite(dn[u]);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float b = a.bias[min(col[u] + (uint32_t)k, a.N - 1u)];
                 float t = y[u][k] * sc[u] + b + p[u][k];
+                if (KIND == 2) bad |= (uint32_t)k < n && !isfinite(t);
                 if (a.act == RIPPLE_ACT_RELU) t = t > 0.0f ? t : 0.0f;
                 if (BF) {
                     zr[k] = __float2bfloat16(t);
@@ -435,6 +444,12 @@ __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
                 }
                 z[k] = t;
                 dl[k] = a.d_old ? old[u][k] : t - old[u][k];
+            }
+            if (KIND == 2 && __builtin_expect(bad, 0)) {
+                bool first = col[u] == 0u || isfinite(dn[u]);
+                const float *row = a.addend + (hidx[u] - col[u]);
+                for (uint32_t k = 0; k < col[u] && first; ++k) first = isfinite(row[k] * sc[u] + a.bias[k]);
+                if (first) atomicAdd(a.range_rows, 1u);
             }
             if (n == 4u) {
                 if (BF) {
@@ -494,18 +509,22 @@ void rp_launch_small_addend(ripple_ctx *c, uint32_t l, bool emit_delta) {
                        ly.T, (int)ly.packed);
 }
 
-static void launch_addend_flat(ripple_ctx *c, const TArgs &a) {
+// Many rows: every lane busy, whatever the row width. (Fewer: the launch is what counts.)
+static bool launch_addend_flat(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
+    if ((uint64_t)c->n_cap * a.N >= (1ull << 32) || (rows_hint < 65536u && (uint64_t)rows_hint * a.N < (3u << 20))) return false;
     const dim3 grid(c->n_cu * 16), block(256);
-#define RP_FLAT(BF, OLD, ADD2) hipLaunchKernelGGL((k_transform_addend_flat<BF, OLD, ADD2>), grid, block, 0, c->stream, a)
-    const bool old = a.D != nullptr, add2 = a.addend2 != nullptr;
-    if (a.store) {
-        if (old) { if (add2) RP_FLAT(true, true, true); else RP_FLAT(true, true, false); }
-        else { if (add2) RP_FLAT(true, false, true); else RP_FLAT(true, false, false); }
-    } else {
-        if (old) { if (add2) RP_FLAT(false, true, true); else RP_FLAT(false, true, false); }
-        else { if (add2) RP_FLAT(false, false, true); else RP_FLAT(false, false, false); }
-    }
+#define RP_FLAT(BF, OLD)                                                                                            \
+    do {                                                                                                            \
+        if (a.den) hipLaunchKernelGGL((k_transform_addend_flat<BF, OLD, 2>), grid, block, 0, c->stream, a);         \
+        else if (a.addend2) hipLaunchKernelGGL((k_transform_addend_flat<BF, OLD, 1>), grid, block, 0, c->stream, a);\
+        else hipLaunchKernelGGL((k_transform_addend_flat<BF, OLD, 0>), grid, block, 0, c->stream, a);               \
+    } while (0)
+    if (a.store && a.D) RP_FLAT(true, true);
+    else if (a.store) RP_FLAT(true, false);
+    else if (a.D) RP_FLAT(false, true);
+    else RP_FLAT(false, false);
 #undef RP_FLAT
+    return true;
 }
 
 __global__ __launch_bounds__(256) void k_transform_addend_only(TArgs a) {
@@ -1069,7 +1088,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
         a.addend = c->X[l];
         a.den = ly.den;
         a.act = (int)ly.act_out;
-        hipLaunchKernelGGL(k_transform_addend_only, dim3(c->n_cu * 8), dim3(256), 0, c->stream, a);
+        if (!launch_addend_flat(c, a, hint)) hipLaunchKernelGGL(k_transform_addend_only, dim3(c->n_cu * 8), dim3(256), 0, c->stream, a);
         return;
     }
     if (ly.proj) {                               // aggregate already multiplied by W_neigh: add it in the epilogue
@@ -1077,8 +1096,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
         a.act = (int)ly.act_out;
         if (ly.self_mode == RIPPLE_SELF_NONE || ly.selfc) {
             a.addend2 = ly.selfc ? ly.PS : nullptr;
-            if (hint >= 65536u && (uint64_t)c->n_cap * a.N < (1ull << 32)) launch_addend_flat(c, a);  // many rows: every lane busy, whatever the row width
-            else hipLaunchKernelGGL(k_transform_addend_only, dim3(c->n_cu * 8), dim3(256), 0, c->stream, a);
+            if (!launch_addend_flat(c, a, hint)) hipLaunchKernelGGL(k_transform_addend_only, dim3(c->n_cu * 8), dim3(256), 0, c->stream, a);
             return;
         }
         a.a_mode = 4;                            // h_self * W_self: the first d_in rows of W0
