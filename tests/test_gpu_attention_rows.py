@@ -18,7 +18,7 @@ def _graph(seed):
     return ri.chung_lu_graph(N, 3 * N, 2.2, 0.004, seed)[:2]
 
 
-@pytest.mark.parametrize("widths,store", [((8, 47, 6), "f32"), ((8, 64, 5), "f32"), ((12, 13, 4, 1), "f32"), ((8, 46, 7), "bf16")])
+@pytest.mark.parametrize("widths,store", [((8, 47, 6), "f32"), ((8, 67, 5), "f32"), ((8, 64, 5), "f32"), ((12, 13, 4, 1), "f32"), ((8, 46, 7), "bf16")])
 def test_rows_of_many_vertices(widths, store):
     print("case attention rows", widths, store, flush=True)
     src, dst = _graph(401)
