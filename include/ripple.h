@@ -189,7 +189,8 @@ typedef enum {
                                      workgroups that write a finished tile while the next one is being multiplied, every
                                      fp32 number as three bf16 parts on the bf16 matrix cores (closer to 64-bit sums than a
                                      chain of fp32 products); 0 keeps the kernels of one tile per workgroup
-                                     (the same parts) and of one product per wavefront (fp32 products); 2 takes the streaming kernel whatever the number of rows (for tests). */
+                                     (the same parts) and of one product per wavefront (fp32 products); 2 takes the streaming kernel whatever the number
+                                     of rows, in two workgroups (for tests). */
     RIPPLE_OPT_SORTED_MESSAGES = 12, /* 0/1/2 (default 1): a hop that would be pulled while few of the scanned in-row entries
                                       carry a message, or pushed with many numbers to add, is scattered from the list of its
                                       messages instead, which the out-edge walk writes down by destination; 1 where the previous

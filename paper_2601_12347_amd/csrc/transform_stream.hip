@@ -111,6 +111,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
         }
     }
     floatx4 ra[2][NA], rq[TWO ? 2 : 1][TWO ? NA : 1];
+    // (bf16 rows of odd width begin at multiples of two bytes only: a buffer load takes those, like a global one)
     auto load_x = [&](int buf, int i, uint32_t t, uint32_t v, int slice) {
         const uint32_t off = (MODE == 3 ? slot_of(t, i) : v) * sa.x_row + min((uint32_t)slice * SW + c4a, k_last) * XB;
         if (XB == 2u) {
@@ -350,7 +351,7 @@ void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t 
 template <int K>
 static bool launch_k(ripple_ctx *c, const StreamArgs &s) {
     const TArgs &a = s.t;
-    const dim3 grid(c->n_cu), block(512);
+    const dim3 grid(c->opt_stream == 2 ? 2u : c->n_cu), block(512);   // 2: small products cross tile boundaries too
 #define GO(WN, ...) hipLaunchKernelGGL((k_split_stream<(WN == 8 ? 64 : 32), K / (WN == 8 ? 64 : 32), WN, __VA_ARGS__>), grid, block, 0, c->stream, s)
     if (a.a_mode == 4) {
         if (a.Npad == 256 && !a.store) GO(8, 4, 0, 0, false, false);

@@ -18,7 +18,7 @@ MIX = {"edge_add": 0.4, "edge_del": 0.25, "feat": 0.2, "vadd": 0.08, "vdel": 0.0
 SHAPES = [("sage_mean", (75, 190, 190, 23), "f32", False), ("gcn_wsum", (75, 190, 190, 23), "f32", True), ("gin_sum", (33, 256, 200, 129), "f32", False),
           ("sage_mean", (129, 65, 128, 40), "f32", False), ("gcn_sum", (17, 100, 70), "f32", False), ("gat", (100, 256, 129, 47), "f32", False),
           ("gcn_max", (31, 255, 97), "f32", False), ("sage_mean", (100, 256, 256, 47), "bf16", False), ("gcn_sum", (66, 250, 33), "bf16", False),
-          ("gcn_sum", (100, 256, 100), "bf16", False)]
+          ("gcn_sum", (100, 256, 100), "bf16", False), ("gcn_sum", (65, 201, 33), "bf16", False), ("sage_mean", (33, 129, 47), "bf16", False)]
 
 
 @pytest.mark.parametrize("kind,widths,store,weighted", SHAPES)
