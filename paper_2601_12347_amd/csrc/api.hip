@@ -8,6 +8,7 @@
 #include "transform_args.h"
 
 #include <chrono>
+#include <cmath>
 #include <cstring>
 #include <new>
 
@@ -498,6 +499,14 @@ static ripple_status grow_staging(ripple_ctx *c, uint32_t n_ops, uint32_t n_feat
     return RIPPLE_OK;
 }
 
+// A matrix whose numbers are all below 2^-40 is lifted by 2^64 before it is split into bf16 parts (see PARTS_LIFT)
+static float weight_lift(const float *w, size_t n) {
+    float most = 0.0f;
+    for (size_t i = 0; i < n; ++i)
+        if (std::isfinite(w[i])) most = std::max(most, std::fabs(w[i]));
+    return most < std::ldexp(1.0f, -40) ? std::ldexp(1.0f, 64) : 1.0f;
+}
+
 extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, const ripple_layer_desc *layers) {
     if (!c) return RIPPLE_EINVAL;
     if (c->state != 1) return fail(c, RIPPLE_ESTATE, "load_model needs a context fresh from init_graph");
@@ -534,6 +543,8 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         ly.act_out = s.act_out;
         ly.eps = s.eps;
         uint32_t n0 = s.d_hidden ? s.d_hidden : s.d_out;
+        ly.lift0 = weight_lift(s.W0, (size_t)ly.K * n0);
+        ly.lift1 = s.d_hidden ? weight_lift(s.W1, (size_t)s.d_hidden * s.d_out) : 1.0f;
         ly.K0pad = rp_round_up(ly.K, 32);
         ly.N0pad = pad_n(n0);
         RP_TRY(upload_padded(c, s.W0, s.b0, ly.K, n0, ly.K0pad, ly.N0pad, &ly.W0, &ly.b0, &ly.W0q));
@@ -600,23 +611,24 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         struct Part {
             const float *w;
             uint32_t K, Npad;
+            float lift;
             unsigned short **out;
         };
         std::vector<Part> parts;
-        auto add = [&](const float *w, uint32_t K, uint32_t Npad, unsigned short **out) {
+        auto add = [&](const float *w, uint32_t K, uint32_t Npad, float lift, unsigned short **out) {
             if (!w) return;
             b.add(out, rp_weight_parts_size(K, Npad));
-            parts.push_back({w, K, Npad, out});
+            parts.push_back({w, K, Npad, lift, out});
         };
         for (uint32_t l = 0; l < n_layers; ++l) {
             LayerDev &ly = c->layers[l];
-            add(ly.W0, ly.K, ly.N0pad, &ly.W0p);   // all rows: a product with W_self alone zeroes its rows from d_in on
-            if (ly.Wn != ly.W0) add(ly.Wn, ly.d_in, ly.N0pad, &ly.Wnp);
-            add(ly.W1, ly.d_hidden, ly.N1pad, &ly.W1p);
-            add(ly.Wc, ly.d_in, 128u, &ly.Wcp);
+            add(ly.W0, ly.K, ly.N0pad, ly.lift0, &ly.W0p);   // all rows: a product with W_self alone zeroes its rows from d_in on
+            if (ly.Wn != ly.W0) add(ly.Wn, ly.d_in, ly.N0pad, ly.lift0, &ly.Wnp);
+            add(ly.W1, ly.d_hidden, ly.N1pad, ly.lift1, &ly.W1p);
+            add(ly.Wc, ly.d_in, 128u, ly.lift0, &ly.Wcp);
         }
         if (b.n) RP_TRY(block_alloc(c, b, &c->part_block, false));
-        for (const Part &p : parts) rp_launch_weight_parts(c, p.w, p.K, p.Npad, *p.out);
+        for (const Part &p : parts) rp_launch_weight_parts(c, p.w, p.K, p.Npad, p.lift, *p.out);
         for (uint32_t l = 0; l < n_layers; ++l)
             if (c->layers[l].Wn == c->layers[l].W0) c->layers[l].Wnp = c->layers[l].W0p;
     }

@@ -107,6 +107,7 @@ struct LayerDev {
     float *W0q, *Wnq, *W1q, *Wcq;
     // ... and as three bf16 parts each, in the order k_split_stream takes them (W0p: all K rows); Wnp may alias W0p
     unsigned short *W0p, *Wnp, *W1p, *Wcp;
+    float lift0, lift1;                       // the powers of two that W0 (and what is cut out of it) and W1 are multiplied by first
 };
 
 // pieces of up to SMALL_OPS operations without vertex deletions: the Apply step in three launches (k_small_validate)

@@ -101,6 +101,10 @@ __device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
     f.y = b;
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));     // to nearest even
 }
+// The parts of a number below 2^-109 would reach into bf16's subnormal numbers and lose bits (rows of 1e-36: sums off by 2.5e-5 of their
+// norm, fp32 products by 1.3e-7). So the rows are multiplied by PARTS_LIFT before they are split, and matrices of such numbers by a power of
+// two of their own (wp_lift), and the sums are brought back: exact both ways. Sums of 2^110 and more (1e33) run over and are made again.
+#define PARTS_LIFT 131072.0f                                // 2^17
 // four numbers as PL bf16 numbers each, four to eight bytes per part
 template <int PL>
 __device__ __forceinline__ void split_parts(floatx4 x, uintx2 (&part)[PL]) {

@@ -289,6 +289,7 @@ static TArgs base_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const ui
     a.wt_ld = ly.K0pad;
     a.Wp = ly.W0p;
     a.wp_k = rp_round_up(ly.K, 128);
+    a.wp_lift = ly.lift0;
     a.bias = ly.b0;
     a.K = ly.K;
     a.Kpad = ly.K0pad;
@@ -812,6 +813,7 @@ __global__ __launch_bounds__(256, (WAVES_N == 4 ? 3 : 2)) void k_transform_split
     const uint32_t n0 = blockIdx.y * BN, col = n0 + wn * 32 + (lane & 31);
     const uintx4 *Wp = (const uintx4 *)a.Wp + (size_t)(lane >> 5) * a.Npad + col;    // eight k of the lane's column
     const size_t part = (size_t)(a.wp_k / 8u) * a.Npad, step = 2u * a.Npad;
+    const float down = 1.0f / ((PL == 3 ? PARTS_LIFT : 1.0f) * a.wp_lift);   // (see PARTS_LIFT)
 
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const uint32_t row0 = tile * BM;
@@ -868,7 +870,8 @@ __global__ __launch_bounds__(256, (WAVES_N == 4 ? 3 : 2)) void k_transform_split
                 floatx4 q = (floatx4)(0.0f);
                 if constexpr (TWO) q = rq[s][i];
                 uintx2 parts[PL];
-                split_parts<PL>(finish_raw<MODE, STORE>(a, ra[s][i], q, k0 + c4a, s_scale[r]), parts);
+                const floatx4 x = finish_raw<MODE, STORE>(a, ra[s][i], q, k0 + c4a, s_scale[r]);
+                split_parts<PL>(PL == 3 ? x * PARTS_LIFT : x, parts);
 #pragma unroll
                 for (int p = 0; p < PL; ++p) *(uintx2 *)&As[s & 1][p][r][c4a] = parts[p];
             }
@@ -904,7 +907,7 @@ __global__ __launch_bounds__(256, (WAVES_N == 4 ? 3 : 2)) void k_transform_split
         bool bad = false;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            acc[0][0][r] += cor[r];
+            acc[0][0][r] = (acc[0][0][r] + cor[r]) * down;
             bad |= !__builtin_isfinite(acc[0][0][r]);
         }
         if (__builtin_expect(__any(bad && col < a.N), 0)) {
@@ -1145,6 +1148,7 @@ void rp_launch_transform(ripple_ctx *c, uint32_t l, const uint32_t *list, const 
     s2.Wt = nullptr;
     s2.Wp = ly.W1p;
     s2.wp_k = rp_round_up(ly.d_hidden, 128);
+    s2.wp_lift = ly.lift1;
     s2.bias = ly.b1;
     s2.K = ly.d_hidden;
     s2.Kpad = ly.K1pad;

@@ -24,6 +24,7 @@ struct TArgs {
     uint32_t wt_ld;                // its row stride
     const unsigned short *Wp;      // W as three bf16 parts in the order the matrix cores take them (k_split_stream), or null
     uint32_t wp_k;                 // its rows (a multiple of 128, never below Kpad)
+    float wp_lift;                 // a power of two: the parts are those of W times it
     uint32_t K, Kpad, N, Npad;
     int act;
     int out_mode;                  // 0 write act(z) to tmp_out[slot] | 1 update H, emit delta | 2 write to tmp_out[vertex]
@@ -52,7 +53,7 @@ struct TArgs {
 bool rp_launch_stream(ripple_ctx *c, const TArgs &a, uint32_t rows_hint);
 // a weight matrix [K x Npad] in that order: numbers it takes, and the launch that makes it
 size_t rp_weight_parts_size(uint32_t K, uint32_t Npad);
-void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t Npad, unsigned short *out);
+void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t Npad, float lift, unsigned short *out);
 
 // transform.hip: the arguments of the products of a layer's previous embedding (see the launchers of the same names)
 TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d, bool bootstrap);

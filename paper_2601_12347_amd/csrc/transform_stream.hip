@@ -87,6 +87,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     const uint32_t colb = ocol * 4u;
     const uint32_t wvo = ((lane >> 5) * a.Npad + col) * 16u;                  // weights: eight k of one column
     const float bias = a.bias[col];                        // (padded)
+    const float up = PL == 3 ? PARTS_LIFT : 1.0f, down = 1.0f / (up * a.wp_lift), eps_up = a.one_plus_eps * up;   // (see PARTS_LIFT)
     constexpr uint32_t XB = STORE && MODE != 3 ? 2u : 4u;  // bytes of a gathered number
     const uint32_t k_last = (a.K - 1u) & ~3u;              // first k of a row's last group of four
     const uint32_t kstep = 2u * a.Npad * 16u;              // bytes of the weights of 16 k
@@ -104,7 +105,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     for (int i = 0; i < NA; ++i) {
         v_cur[i] = a.list[slot_of(tile, i)];
         v_nxt[i] = a.list[slot_of(tile + gridDim.x, i)];
-        if constexpr (SCALE) sc_cur[i] = row_scale(v_cur[i]);
+        if constexpr (SCALE) sc_cur[i] = row_scale(v_cur[i]) * (TWO ? up : down);
         if (c4a == 0) {                                    // nothing is parked yet: its rows only have to be valid
             s_row[1][r_own + RPP * i] = (OUT == 0 && a.out_mode == 0) ? 0u : v_cur[i];
             if (MODE == 0) s_scale[1][r_own + RPP * i] = 1.0f;
@@ -134,7 +135,8 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
             part[0].x = w0;
             part[0].y = w1;
         } else {
-            if constexpr (TWO) x = x * a.one_plus_eps + rq[buf][i] * sc;
+            if constexpr (TWO) x = x * eps_up + rq[buf][i] * sc;
+            else x = x * up;
             x.x = k < a.K ? x.x : 0.0f;                    // padding, and what was read past the row's end
             x.y = k + 1u < a.K ? x.y : 0.0f;
             x.z = k + 2u < a.K ? x.z : 0.0f;
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             z[j] = done[c >> 2][(c & 3) * 4 + j];
-            if (MODE == 0) z[j] *= s_scale[buf][chunk_row(c, j)];
+            z[j] *= MODE == 0 ? s_scale[buf][chunk_row(c, j)] : down;
             bad |= !__builtin_isfinite(z[j]);
         }
         if (__builtin_expect(__any(bad && stored), 0)) {                      // see above
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
                     }
                 if constexpr (SCALE)
 #pragma unroll
-                    for (int i = 0; i < NA; ++i) sc_nxt[i] = row_scale(v_nxt[i]);
+                    for (int i = 0; i < NA; ++i) sc_nxt[i] = row_scale(v_nxt[i]) * (TWO ? up : down);
                 if (KS == 2)
 #pragma unroll
                     for (int i = 0; i < NA; ++i) load_x(0, i, tile_n, v_nxt[i], 0);
@@ -314,8 +316,8 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     }
 }
 
-// The weights as the kernel takes them: three parts, each [Kp / 8][Npad][8] bf16, zero rows from K on
-__global__ void k_weight_parts(const float *w, uint32_t K, uint32_t Kp, uint32_t Npad, unsigned short *out) {
+// The weights, times `lift`, as the kernel takes them: three parts, each [Kp / 8][Npad][8] bf16, zero rows from K on
+__global__ void k_weight_parts(const float *w, uint32_t K, uint32_t Kp, uint32_t Npad, float lift, unsigned short *out) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= Kp / 8u * Npad) return;
     const uint32_t n = i % Npad, k8 = i / Npad * 8u;
@@ -323,7 +325,7 @@ __global__ void k_weight_parts(const float *w, uint32_t K, uint32_t Kp, uint32_t
 #pragma unroll
     for (uint32_t t = 0; t < 8u; ++t) {
         const uint32_t k = k8 + t;
-        const float f = k < K ? w[(size_t)k * Npad + n] : 0.0f;
+        const float f = k < K ? w[(size_t)k * Npad + n] * lift : 0.0f;
         x[t >> 2][t & 3u] = f;
     }
     uintx2 lo[3], hi[3];
@@ -341,9 +343,9 @@ __global__ void k_weight_parts(const float *w, uint32_t K, uint32_t Kp, uint32_t
 }
 
 size_t rp_weight_parts_size(uint32_t K, uint32_t Npad) { return (size_t)3 * rp_round_up(K, 128) * Npad; }
-void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t Npad, unsigned short *out) {
+void rp_launch_weight_parts(ripple_ctx *c, const float *w, uint32_t K, uint32_t Npad, float lift, unsigned short *out) {
     const uint32_t kp = rp_round_up(K, 128);
-    hipLaunchKernelGGL(k_weight_parts, dim3(rp_div_up(kp / 8u * Npad, 256)), dim3(256), 0, c->stream, w, K, kp, Npad, out);
+    hipLaunchKernelGGL(k_weight_parts, dim3(rp_div_up(kp / 8u * Npad, 256)), dim3(256), 0, c->stream, w, K, kp, Npad, lift, out);
 }
 
 // K: 128 or 256, the rows of the weights' parts. Slices of 64 k where the tile has 64 rows; tiles of 128 and 256 rows have no room for

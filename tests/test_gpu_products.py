@@ -113,3 +113,31 @@ def test_split_products_of_wide_rows(kind, widths, self_cache, project_first):
             pair.check_aggregates()
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("rows,weights", [(1e-33, 1.0), (1e-36, 1.0), (1.0, 1e-33), (1.0, 1e-36), (1e-20, 1e-16), (1e20, 1e-13)])
+@pytest.mark.parametrize("way", ["stream", "tiles"])
+def test_parts_of_tiny_numbers(way, rows, weights):
+    """Rows or weights near the smallest normal number: their parts keep all bits, in both kernels that split. Bound as for rows of any magnitude
+    (sums of 1e-37 are themselves rounded at 1e-45, 1e-8 of them)."""
+    widths, n = (100, 200), 400
+    feats = (ri.features(n, 100, 284) * np.float32(rows)).astype(np.float32)
+    src, dst, _, _ = ri.chung_lu_graph(n, 3000, 2.1, 0.03, 281)
+    model = ri.make_model("sage_mean", widths, 285)
+    for layer in model:
+        layer["b0"] = np.zeros_like(layer["b0"])
+        layer["W0"] = (layer["W0"] * np.float32(weights)).astype(np.float32)
+    errs = {}
+    for kernel in (way, "fp32"):
+        pair = Pair(n, n, src, dst, feats, model, split=kernel == "tiles")
+        try:
+            rp.ripple_set_option(pair.ctx, rp.OPT_STREAM_TRANSFORM, 2 if kernel == "stream" else 0)
+            rp.ripple_full_infer(pair.ctx)
+            want = oracle.full_recompute(pair.ora, model)[1]
+            got = rp.ripple_get_embeddings(pair.ctx, 1, widths[1], n_rows=n).astype(np.float64)
+            scale = np.abs(want).max()
+            errs[kernel] = np.linalg.norm((got - want) / scale) / np.linalg.norm(want / scale)
+        finally:
+            pair.close()
+    print("rows %g weights %g %s: error against 64 bits %.2e, fp32 products %.2e" % (rows, weights, way, errs[way], errs["fp32"]), flush=True)
+    assert errs[way] <= max(1.1 * errs["fp32"], 1.5e-7)
