@@ -121,15 +121,25 @@ __device__ __forceinline__ void split_parts(floatx4 x, uintx2 (&part)[PL]) {
     }
 }
 
-// element k of the row in slot `slot` as the product takes it
+// A block of 32 rows by 32 columns on the fp32 matrix cores, straight from memory: for the blocks whose sums of parts are not finite. slot, v,
+// scale: of row lane % 32 of the block; col: this lane's column (of the padded matrix). Eight k per step: the lower half of the wavefront
+// has the first four, product i takes number i of both halves. The sums lie as those of any 32 x 32 product do.
 template <int MODE, int STORE>
-__device__ __forceinline__ float row_number(const TArgs &a, uint32_t slot, uint32_t v, uint32_t k, float scale) {
-    if (MODE == 0) return a.X[(size_t)v * a.d_in + k] * scale;
-    if (MODE == 3) return a.tmp_in[(size_t)slot * a.tmp_ld + k];
-    if (MODE == 1 && k >= a.d_in) return a.X[(size_t)v * a.d_in + (k - a.d_in)] * scale;
-    const float h = rp_load_h(a.Hprev, STORE, (size_t)v * a.d_in + k);
-    if (MODE == 2) return h * a.one_plus_eps + a.X[(size_t)v * a.d_in + k] * scale;
-    return h;
+__device__ __forceinline__ floatx16 fp32_block(const TArgs &a, uint32_t slot, uint32_t v, float scale, uint32_t col, int lane) {
+    const floatx4 *Wq = (const floatx4 *)a.Wq;
+    floatx16 sum;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[r] = 0.0f;
+#pragma unroll 4
+    for (uint32_t k0 = 0; k0 < a.Kpad; k0 += 8u) {
+        const uint32_t k = k0 + 4u * ((uint32_t)lane >> 5);
+        floatx4 p, q = (floatx4)(0.0f), w = Wq[(size_t)(k >> 2) * a.Npad + col];
+        fetch_raw<MODE, STORE>(a, v, slot, k, p, q);
+        const floatx4 x = finish_raw<MODE, STORE>(a, p, q, k, scale);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], k + i < a.K ? w[i] : 0.0f, sum, 0, 0, 0);
+    }
+    return sum;
 }
 
 // ---------------------------------------------------------------------------------

@@ -793,8 +793,10 @@ static void launch_bf16(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
 // products) and the workgroups that share a compute unit's matrix cores: six bf16 products take 3/8 of the fp32 products' time.
 // 256 -> 256 against the same tiles of fp32 products (launch included): 10 K rows with a cached row 20.6 -> 15.8 us, 35 K rows 40 -> 31 (23 for
 // the bytes alone), without it 18.4 -> 12.7 and 22 -> 16.8; both products of an MLP on 10 K rows 37 -> 31 and 26 -> 18.
+// Three workgroups per compute unit where a row number comes from one place; those that add two up hold both for four slices, and with the
+// registers of a third workgroup 15 of them were spilled: two workgroups.
 template <int WAVES_M, int WAVES_N, int STAGES, int MODE, int STORE>
-__global__ __launch_bounds__(256, (WAVES_N == 4 ? 3 : 2)) void k_transform_split(TArgs a) {
+__global__ __launch_bounds__(256, (WAVES_N == 4 && MODE != 2 && !(MODE == 1 && STORE) ? 3 : 2)) void k_transform_split(TArgs a) {
     constexpr int BM = WAVES_M * 32, BN = WAVES_N * 32;
     constexpr int NA = BM / 32;                            // groups of four numbers per thread and slice
     constexpr bool TWO = (MODE == 2) || (MODE == 1 && STORE == 1);
@@ -911,15 +913,10 @@ __global__ __launch_bounds__(256, (WAVES_N == 4 ? 3 : 2)) void k_transform_split
             bad |= !__builtin_isfinite(acc[0][0][r]);
         }
         if (__builtin_expect(__any(bad && col < a.N), 0)) {
+            const uint32_t lr = wm * 32 + (lane & 31);
+            const floatx16 sum = fp32_block<MODE, STORE>(a, min(row0 + lr, count - 1u), s_vtx[lr], s_scale[lr], col, lane);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t lr = wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), slot = row0 + lr;
-                if (__builtin_isfinite(acc[0][0][r]) || col >= a.N || slot >= count) continue;
-                float t = 0.0f;
-#pragma unroll 1
-                for (uint32_t k = 0; k < a.K; ++k) t = __builtin_fmaf(row_number<MODE, STORE>(a, slot, s_vtx[lr], k, s_scale[lr]), a.W[(size_t)k * a.Npad + col], t);
-                acc[0][0][r] = t;
-            }
+            for (int r = 0; r < 16; ++r) acc[0][0][r] = __builtin_isfinite(acc[0][0][r]) ? acc[0][0][r] : sum[r];
         }
         epilogue_staged<1, 1, BM, BN, STORE != 0>(a, acc, (float *)smem, s_vtx, s_scale, row0, count, n0, wm, wn, tid);
     }

@@ -19,8 +19,9 @@
 // wavefronts that only fetch and eight that only multiply 1.6, products of 16 x 16 x 32 no difference.
 // Rows stored in bf16 are exact as they are: three products.
 // What a sum of finite products cannot show: infinities and NaNs of the rows or the weights, and numbers that bf16 rounds to
-// infinity, leave a sum that is not finite (x1 = x - x0 is a NaN then). Such an element is computed again from fp32 products, one
-// after the other.
+// infinity, leave a sum that is not finite (x1 = x - x0 is a NaN then). Such an element is stored as a NaN, beside it the old value, and made
+// again on the fp32 matrix cores once the wavefront has no tile left: in the loop it would cost registers that the loop does not have
+// (the parked tile's sums and the next tile's are all live there).
 //
 // A workgroup of eight wavefronts per compute unit is persistent and owns tiles of BM rows by all N columns; a wavefront has 64 rows
 // by 32 columns of one. No part of a tile waits for memory on its own:
@@ -40,6 +41,55 @@ struct StreamArgs {
     uint32_t o2_row, o2_bytes;     // tmp_out2
 };
 
+// Sums that were not finite (see above): a wavefront goes over its blocks of 32 x 32 once more, and those that hold a NaN are multiplied again as
+// fp32 numbers. A lane looks at the elements it has stored itself; where the sum was finite after all and only what it was added to was
+// not, the same NaN comes out. Bootstrap of 169 K rows, 128 -> 256 -> 256 -> 40, SAGE: 1.06 ms with finite features, 1.32 with a NaN at the
+// largest hub, 2.6 with an infinity in every row; with the products made one after the other where the sum was finished 1.68 and 28 ms, and
+// 1 to 14 registers spilled in most of the shapes.
+template <int BM, int TM, int WN, int MODE, int STORE, int OUT, bool ADD, bool DELTA>
+__device__ __forceinline__ void blocks_again(const StreamArgs &sa) {
+    const TArgs &a = sa.t;
+    const uint32_t count = *a.count_ptr, n_tiles = (count + BM - 1) / BM, lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, wn = wave % WN, wm = wave / WN;
+    const uint32_t col = wn * 32u + (lane & 31u);
+    const bool second = OUT == 0 && a.split_col && wn * 32u >= a.split_col;
+    const uint32_t ocol = second ? col - a.split_col : col, ld = OUT == 1 ? a.N : (second ? a.tmp_out2_ld : a.tmp_out_ld);
+    const uint32_t lim = OUT == 0 && a.split_col ? (second ? a.N - a.split_col : a.N1) : a.N;
+    float *out = OUT == 1 ? (float *)a.Hout : (second ? a.tmp_out2 : a.tmp_out);
+    const float bias = a.bias[col];
+#pragma unroll 1
+    for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
+#pragma unroll 1
+        for (uint32_t i = 0; i < (uint32_t)TM; ++i) {
+            const uint32_t row0 = tile * BM + (wm * TM + i) * 32u;
+            size_t at[16];                                 // where this lane's elements lie; not stored: `there` clear
+            uint32_t there = 0, nans = 0;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t slot = row0 + (uint32_t)(r >> 2) * 8u + (lane >> 5) * 4u + (r & 3), s = min(slot, count - 1u);
+                at[r] = (size_t)(OUT == 0 && a.out_mode == 0 ? s : a.list[s]) * ld + min(ocol, lim - 1u);
+                there |= (slot < count && ocol < lim ? 1u : 0u) << r;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float z = out[at[r]];
+                nans |= (z != z ? 1u : 0u) << r;
+            }
+            nans &= there;
+            if (!__any(nans != 0u)) continue;
+            const uint32_t slot = min(row0 + (lane & 31u), count - 1u), v = a.list[slot], deg = a.mean ? a.in_meta[v].y : 1u;
+            const floatx16 sum = fp32_block<MODE, STORE>(a, slot, v, 1.0f / (float)(deg > 1u ? deg : 1u), col, (int)lane);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (!(nans >> r & 1u)) continue;
+                float z = sum[r] + bias;
+                if (ADD) z += a.addend[at[r]];
+                if (a.act == RIPPLE_ACT_RELU) z = z > 0.0f ? z : 0.0f;
+                out[at[r]] = z;
+                if (DELTA && !a.d_old) a.D[at[r]] = z - a.D[at[r]];   // the old value is there
+            }
+        }
+}
+
 // SW: k per slice, KS slices (K <= SW KS); WN: wavefronts side by side (32 WN columns); MODE, STORE: see fetch_raw (MODE 0, 2, 3, 4).
 // OUT 0: the product goes to tmp_out (and tmp_out2). 1: H is updated; ADD: plus an unscaled cached row, DELTA: the delta row is written too.
 template <int SW, int KS, int WN, int MODE, int STORE, int OUT, bool ADD, bool DELTA>
@@ -55,6 +105,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     constexpr bool TWO = MODE == 2;
     static_assert(EVERY >= 1 && STEPS % BQ == 0 && NC % LEAD == 0, "schedule");
     __shared__ __attribute__((aligned(16))) unsigned short As[2][PL][BM][LD];
+    __shared__ uint32_t s_again[8];                        // a wavefront has stored NaNs in place of sums that have to be made again
     __shared__ uint32_t s_row[2][BM];                      // output row of every slot of the tile
     __shared__ float s_scale[MODE == 0 ? 2 : 1][MODE == 0 ? BM : 1];
 
@@ -65,6 +116,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     uint32_t tile = blockIdx.x;
     if (tile >= n_tiles) return;
 
+    if (tid < 8) s_again[tid] = 0;
     constexpr uint32_t RSRC3 = 0x00020000u, NOWHERE = 0xFFFFF000u;        // beyond every array: nothing is stored there
     const uint32_t plane = a.wp_k * a.Npad * 2u;           // bytes of one part of the weights
     const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void *)a.Wp, 0, 3u * plane, RSRC3);
@@ -177,7 +229,7 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][r] = cor[i][r] = done[i][r] = 0.0f;
-    uint32_t prev_tile = 0, prev_rows = 0;                 // the parked tile and its valid rows (0: nothing parked)
+    uint32_t prev_rows = 0;                                // the parked tile's valid rows (0: nothing parked)
     int par = 0;                                           // s_row / s_scale [par]: the current tile, [par ^ 1]: the parked one
     float pa[LEAD][4], po[LEAD][4];                        // cached-row and old values of the chunks in flight
 #pragma unroll
@@ -196,34 +248,30 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
         }
     };
     auto finish_chunk = [&](int c, int buf) {
-        float z[4];
+        float sum[4];
+        uint32_t off[4];
         bool bad = false;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            z[j] = done[c >> 2][(c & 3) * 4 + j];
-            z[j] *= MODE == 0 ? s_scale[buf][chunk_row(c, j)] : down;
-            bad |= !__builtin_isfinite(z[j]);
+            const uint32_t lr = chunk_row(c, j);
+            off[j] = stored && lr < prev_rows ? s_row[buf][lr] * out_row + colb : NOWHERE;
+            sum[j] = done[c >> 2][(c & 3) * 4 + j];
+            if constexpr (MODE == 0) sum[j] *= s_scale[buf][lr];
+            else sum[j] *= down;
+            bad |= !__builtin_isfinite(sum[j]);
+            float z = sum[j] + bias + (ADD ? pa[c % LEAD][j] : 0.0f);
+            if (a.act == RIPPLE_ACT_RELU) z = z > 0.0f ? z : 0.0f;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(z), ores, off[j], 0, 0);
+            if (DELTA) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a.d_old ? po[c % LEAD][j] : z - po[c % LEAD][j]), dres, off[j], 0, 0);
         }
-        if (__builtin_expect(__any(bad && stored), 0)) {                      // see above
+        if (__builtin_expect(__any(bad), 0)) {             // (see blocks_again)
+            s_again[wave] = 1u;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t slot = prev_tile * BM + chunk_row(c, j);
-                if (__builtin_isfinite(z[j]) || !stored || chunk_row(c, j) >= prev_rows) continue;
-                const uint32_t v = a.list[slot];
-                const float sc = (MODE == 0 || MODE == 2) ? row_scale(v) : 1.0f;
-                float t = 0.0f;
-#pragma unroll 1
-                for (uint32_t k = 0; k < a.K; ++k) t = __builtin_fmaf(row_number<MODE, STORE>(a, slot, v, k, sc), a.W[(size_t)k * a.Npad + col], t);
-                z[j] = t;
+                if (__builtin_isfinite(sum[j])) continue;
+                __builtin_amdgcn_raw_buffer_store_b32(0x7FC00000u, ores, off[j], 0, 0);
+                if (DELTA) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(po[c % LEAD][j]), dres, off[j], 0, 0);
             }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            z[j] += bias + (ADD ? pa[c % LEAD][j] : 0.0f);
-            if (a.act == RIPPLE_ACT_RELU) z[j] = z[j] > 0.0f ? z[j] : 0.0f;
-            const uint32_t lr = chunk_row(c, j), off = stored && lr < prev_rows ? s_row[buf][lr] * out_row + colb : NOWHERE;
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(z[j]), ores, off, 0, 0);
-            if (DELTA) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(a.d_old ? po[c % LEAD][j] : z[j] - po[c % LEAD][j]), dres, off, 0, 0);
         }
     };
 
@@ -296,7 +344,6 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
                 done[i][r] = acc[i][r] + cor[i][r];
                 acc[i][r] = cor[i][r] = 0.0f;
             }
-        prev_tile = tile;
         prev_rows = min((uint32_t)BM, count - tile * BM);
         par ^= 1;
 #pragma unroll
@@ -313,6 +360,11 @@ __global__ __launch_bounds__(512, 2) void k_split_stream(StreamArgs sa) {
     for (int c = 0; c < NC; ++c) {
         finish_chunk(c, par ^ 1);
         if ((ADD || DELTA) && c + LEAD < NC) request_chunk(c + LEAD, par ^ 1);
+    }
+    if (s_again[wave]) {
+        auto *args = __builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));                     // read again from memory: nothing of this is kept during the loop
+        blocks_again<BM, TM, WN, MODE, STORE, OUT, ADD, DELTA>(*(const StreamArgs *)args);
     }
 }
 
