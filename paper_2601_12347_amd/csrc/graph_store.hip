@@ -780,7 +780,7 @@ __device__ __forceinline__ void apply_op(const MutArgs &a, uint32_t i) {
         const uint32_t si = a.hole_in[op.v] + a.dead_in[op.v] + a.rank_in[i], so = a.hole_out[op.u] + a.dead_out[op.u] + a.rank_out[i];
         if (a.in_w) alpha = __uint_as_float(op.feat_row);   // weighted graphs: EDGE_ADD carries the weight's bits there
         a.seg_id[so] = op.v;
-        a.seg_x[so] = __float_as_uint(alpha);
+        if (a.out_w) a.seg_x[so] = __float_as_uint(alpha);
         a.seg_id[si] = op.u;
         a.seg_x[si] = __float_as_uint(alpha);
         list_changed(a, s, op.u, op.v, alpha, 1.0f);

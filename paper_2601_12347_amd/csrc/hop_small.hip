@@ -15,7 +15,7 @@ struct HopArgs {
     const uint32_t *list, *count_ptr, *eoff;       // A_{l-1}
     const uint2 *out_meta;
     const uint32_t *out_pool;
-    const float *out_w;                            // weights beside the out-rows (weighted sums; else null: a kernel of its own costs its loading at first use)
+    const float *out_w;                            // weights beside the out-rows (WT: weighted sums; else null)
     SparseArgs sp;
     const float *D;                                // rows to push, or null
     uint32_t ldd, d;
@@ -26,7 +26,7 @@ struct HopArgs {
     TArgs g;                                       // (g.W null: no product)
 };
 
-template <int NJ, int STORE>
+template <int NJ, int STORE, int WT>
 __global__ __launch_bounds__(256) void k_hop_small(HopArgs a) {
     const uint32_t wave = threadIdx.x >> 6;
     if (blockIdx.x < a.nb_walk) {
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void k_hop_small(HopArgs a) {
         enter_roots(a.list, a.count_ptr, a.sp, gw, nw);
     } else if (blockIdx.x < a.nb_walk + a.nb_push) {
         if (blockIdx.x == a.nb_walk && threadIdx.x == 0 && a.count_ptr[1]) a.ctr->hop_mode[a.l] = 1u + RP_HOP_PUSH;
-        push_edges<NJ, 0, 2>(a.list, a.count_ptr, a.eoff, a.D, nullptr, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X,
+        push_edges<NJ, 0, WT>(a.list, a.count_ptr, a.eoff, a.D, nullptr, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X,
                               (blockIdx.x - a.nb_walk) * 4u + wave, a.nb_push * 4u);
     } else {
         wave_gemm<4, STORE>(a.g, (blockIdx.x - a.nb_walk - a.nb_push) * 4u + wave, (gridDim.x - a.nb_walk - a.nb_push) * 4u);
@@ -43,10 +43,10 @@ __global__ __launch_bounds__(256) void k_hop_small(HopArgs a) {
 }
 
 // messages of a project-first layer (PD: projected rows, T: what has been sent)
-template <int NJ>
+template <int NJ, int WT>
 __global__ __launch_bounds__(256) void k_push_projected(HopArgs a, const float *PD, const float *T, int packed) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.count_ptr[1]) a.ctr->hop_mode[a.l] = 1u + RP_HOP_PUSH;
-    push_edges<NJ, 2, 2>(a.list, a.count_ptr, a.eoff, PD, T, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, blockIdx.x * 4u + (threadIdx.x >> 6),
+    push_edges<NJ, 2, WT>(a.list, a.count_ptr, a.eoff, PD, T, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, blockIdx.x * 4u + (threadIdx.x >> 6),
                           gridDim.x * 4u, packed != 0);
 }
 
@@ -95,8 +95,10 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
     const dim3 grid(a.nb_walk + a.nb_push + nb_gemm), block(256);
 #define HOP_CASE(NJ)                                                                                    \
     do {                                                                                                \
-        if (c->store) hipLaunchKernelGGL((k_hop_small<NJ, 1>), grid, block, 0, c->stream, a);           \
-        else hipLaunchKernelGGL((k_hop_small<NJ, 0>), grid, block, 0, c->stream, a);                    \
+        if (a.out_w && c->store) hipLaunchKernelGGL((k_hop_small<NJ, 1, 1>), grid, block, 0, c->stream, a); \
+        else if (a.out_w) hipLaunchKernelGGL((k_hop_small<NJ, 0, 1>), grid, block, 0, c->stream, a);    \
+        else if (c->store) hipLaunchKernelGGL((k_hop_small<NJ, 1, 0>), grid, block, 0, c->stream, a);   \
+        else hipLaunchKernelGGL((k_hop_small<NJ, 0, 0>), grid, block, 0, c->stream, a);                 \
     } while (0)
     if (a.d <= 64) HOP_CASE(1);
     else if (a.d <= 128) HOP_CASE(2);
@@ -105,7 +107,11 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
     else HOP_CASE(16);
 #undef HOP_CASE
     if (!ly.proj) return;
-#define PUSH_CASE(NJ) hipLaunchKernelGGL((k_push_projected<NJ>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, (int)ly.packed)
+#define PUSH_CASE(NJ)                                                                                                                     \
+    do {                                                                                                                                  \
+        if (a.out_w) hipLaunchKernelGGL((k_push_projected<NJ, 1>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, (int)ly.packed);   \
+        else hipLaunchKernelGGL((k_push_projected<NJ, 0>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, (int)ly.packed);           \
+    } while (0)
     if (a.d <= 64) PUSH_CASE(1);
     else if (a.d <= 128) PUSH_CASE(2);
     else if (a.d <= 256) PUSH_CASE(4);

@@ -18,7 +18,7 @@ __device__ __forceinline__ float rp_message(float m, bool packed) {
 // PK = 1 (NJ = 1 only): the message rows are packed 128-byte lines (D points at them). PK = 2: project-first layers of small
 // hops, where no kernel has made the messages: D holds the sources' projected rows and T what they have sent; the message
 // is made here, for every edge again (rp_message), and T is brought up to date by a later kernel.
-// WT = 1: a message is multiplied by its edge's weight, 2: if out_w is given (out_w, parallel to out_pool: 4 bytes per edge, kept so that weighted sums need not
+// WT = 1: a message is multiplied by its edge's weight (out_w, parallel to out_pool: 4 bytes per edge, kept so that weighted sums need not
 // walk every in-row of A_l for a few thousand messages: hop 1 of 1,777 updates on 31 M edges 283 -> 15 us, the whole batch 2.22 -> 1.67 ms;
 // 13 updates on 43 M edges 0.69 -> 0.23).
 template <int NJ, int PK, int WT>
@@ -26,7 +26,6 @@ __device__ __forceinline__ void push_edges(const uint32_t *list, const uint32_t 
                                            const float *T_sent, uint32_t ldd, uint32_t d, const uint2 *out_meta,
                                            const uint32_t *out_pool, const float *out_w, float *X, uint32_t gw, uint32_t nw, bool packed = false) {
     constexpr int G = (NJ <= 2) ? 8 : (NJ <= 4 ? 4 : (NJ <= 8 ? 2 : 1));   // edges per round
-    const bool weighted = WT == 1 || (WT == 2 && out_w);
     const uint32_t count = *count_ptr;
     if (count == 0) return;
     const int lane = rp_lane();
@@ -51,7 +50,7 @@ __device__ __forceinline__ void push_edges(const uint32_t *list, const uint32_t 
             pos = out_meta[my_u].x + (e - eoff[my_i]);
         }
         const uint32_t my_v = out_pool[pos];
-        const float my_w = weighted ? out_w[pos] : 1.0f;
+        const float my_w = WT ? out_w[pos] : 1.0f;
         const int n_here = (int)(e1 - e0);
         // G edges per round: their sources' delta rows are requested together (consecutive edges mostly share
         // the source: the repeats are cache hits), then the additions go out
@@ -93,7 +92,7 @@ __device__ __forceinline__ void push_edges(const uint32_t *list, const uint32_t 
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 if (k0 + g < n_here) {
-                    if (weighted) {
+                    if (WT) {
                         const float wk = __shfl(my_w, k0 + g);
 #pragma unroll
                         for (int j = 0; j < NJ; ++j) dreg[g][j] *= wk;
