@@ -231,6 +231,10 @@ struct ripple_ctx {
     float *pair_w = nullptr, *pair_w_sorted = nullptr;  // weighted graphs: the edges' weights, beside them
     uint32_t *pair_cnt = nullptr;                       // (zero between hops)
     uint32_t pair_cap = 0;                              // messages a listed hop may have; there is room for twice as many
+    struct ListOver {                                   // hop l's last list that had a bucket run over (room 0: none since)
+        uint32_t m = 0, room = 0, wait = 0;             // its messages, the entries a bucket had room for, batches until the next try
+    } list_over[RIPPLE_MAX_LAYERS + 1];
+    uint32_t list_room[RIPPLE_MAX_LAYERS + 1] = {0};    // what a bucket has room for in the batch in progress
     int opt_sorted = 1;                                 // 0 never, 1 where the last batch says it pays, 2 wherever it can be
     uint32_t last_n_ops = 0;                            // operations of the last single-piece batch    // candidates of the last batch's max / min hops (a size hint)
     bool last_from_rep = false;

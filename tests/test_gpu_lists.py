@@ -126,3 +126,59 @@ def test_weights_of_a_long_out_row(gone):
         pair.check_graph()
     finally:
         pair.close()
+
+
+def _feature(pair, rng, v):
+    ops = np.array([(OP_FEAT_UPDATE, v, 0, 0)], np.uint32)
+    res, _, _ = pair.step(ops, rng.standard_normal((1, pair.widths[0])).astype(np.float32))
+    print(" vertex", v, "hop modes", list(res.hop_mode[1:pair.L + 1]), "messages", list(res.messages[1:pair.L + 1]), flush=True)
+    return res
+
+
+def test_a_bucket_that_ran_over_is_remembered():
+    """Vertex 0 sends 3,580 messages to two sinks at hop 2 (their bucket has room for about 150), vertex 5 some 3,200 all over the graph. After
+    vertex 0's batch hops of at least half its size are pulled without a list; after a small one lists are tried again."""
+    n, rng = 3400, np.random.default_rng(17)
+    mid, other = np.arange(10, 1800), np.arange(1800, 3390)
+    src = np.concatenate([np.zeros(len(mid), np.int64), np.repeat(mid, 2), np.full(len(other), 5), np.repeat(other, 2), [7], [8]])
+    dst = np.concatenate([mid, np.tile([2, 3], len(mid)), other, rng.integers(10, n, 2 * len(other)), [8], [9]])
+    keep = np.unique(src * n + dst)
+    src, dst = (keep // n).astype(np.uint32), (keep % n).astype(np.uint32)
+    pair = Pair(n, n + 8, src, dst, ri.features(n, 8, 412), ri.make_model("gcn_sum", (8, 24, 40, 6), 411), project_first=False)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SORTED_MESSAGES, 2)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SPARSE_FRONTIER, 0)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SCATTER_MODE, 2)
+    print("case bucket remembered", flush=True)
+    try:
+        big = _feature(pair, rng, 0)
+        wide = _feature(pair, rng, 5)
+        assert big.hop_mode[2] == 2 and wide.messages[2] >= big.messages[2] // 2
+        assert wide.hop_mode[2] == 2
+        small = _feature(pair, rng, 7)
+        assert small.messages[2] < big.messages[2] // 2
+        assert _feature(pair, rng, 5).hop_mode[2] == 4
+        pair.check_aggregates()
+    finally:
+        pair.close()
+
+
+def test_a_bucket_that_runs_over_where_the_hop_is_pushed():
+    """3,000 messages of two numbers to a sink with 7,000 in-neighbours: the list has no room for them in one bucket, and a pull would read more
+    than a push sends."""
+    n, k, rng = 8000, 3000, np.random.default_rng(19)
+    mid, more = np.arange(10, 10 + k), np.arange(3100, 7100)
+    src = np.concatenate([np.zeros(k, np.int64), mid, more, rng.integers(3100, n, 24000)])
+    dst = np.concatenate([mid, np.full(k, 2), np.full(len(more), 2), rng.integers(3100, n, 24000)])
+    keep = np.unique(src * n + dst)
+    src, dst = (keep // n).astype(np.uint32), (keep % n).astype(np.uint32)
+    pair = Pair(n, n + 8, src, dst, ri.features(n, 8, 422), ri.make_model("gcn_sum", (8, 2, 6), 421), project_first=False)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SORTED_MESSAGES, 2)
+    rp.ripple_set_option(pair.ctx, rp.OPT_SPARSE_FRONTIER, 0)
+    print("case bucket over, pushed", flush=True)
+    try:
+        for _ in range(3):
+            res = _feature(pair, rng, 0)
+            assert res.messages[2] >= k and res.hop_mode[2] == 1
+        pair.check_aggregates()
+    finally:
+        pair.close()
