@@ -709,7 +709,9 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         RP_TRY(dev_alloc(c, &c->side_v, entries, false));
         RP_TRY(dev_alloc(c, &c->side_acc, entries * xmax, false));
     }
-    if (!c->opt_deterministic) {
+    bool listed = false;                                 // some hop from the second on is one of sums
+    for (uint32_t l = 2; l <= c->L; ++l) listed |= !rp_layer_mono(c, l) && !rp_layer_attn(c, l);
+    if (listed && !c->opt_deterministic && rp_lists_allowed(c)) {
         // (destination, source) pairs of a hop's messages: room for twice a quarter of the edge capacity, at most 2^26 (a hop with
         // more messages than that quarter is pulled, pushed or discovers)
         c->pair_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(c->pool_cap / 4, 1u << 14), 1u << 25);
@@ -1114,7 +1116,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         // the hop would be pushed (small sets differ more, depending on the hubs they meet). The kernels make sure on the device that
         // the list is only used if this batch's messages fit and it still pays; else the hop is pulled or pushed.
         uint32_t pair_cap = 0;
-        if (l >= 2 && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3 && c->n_cap <= RP_LIST_BUCKETS * RP_LIST_IDS) {
+        if (l >= 2 && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3) {
             const uint64_t m = c->last_m[l];
             const bool pulls = c->opt_scatter == 2 || m * c->xw[l] * 4ull * (unsigned)c->opt_pull_ratio >= 8ull * c->last_isum[l];
             if (c->opt_sorted == 2) pair_cap = c->pair_cap;

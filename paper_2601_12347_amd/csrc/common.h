@@ -284,6 +284,8 @@ static inline bool rp_layer_attn(const ripple_ctx *c, uint32_t l) {
 static inline uint32_t rp_div_up(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
 static inline uint32_t rp_round_up(uint32_t a, uint32_t b) { return (a + b - 1) / b * b; }
 
+static inline bool rp_lists_allowed(const ripple_ctx *c) { return c->n_cap <= RP_LIST_BUCKETS * RP_LIST_IDS; }   // (pair_cap stays 0 else)
+
 // ---- device helpers -----------------------------------------------------------------
 #ifdef __HIPCC__
 __device__ __forceinline__ int rp_lane() { return threadIdx.x & 63; }

@@ -2,6 +2,7 @@
 round, buckets that run over; and the weights beside the out-rows that pushed and listed messages are multiplied by. (Rows of other widths: test_gpu_updates.py, sorted messages.)"""
 import numpy as np
 import pytest
+import torch
 
 import paper_2601_12347_amd as rp
 import ripple_inputs as ri
@@ -182,3 +183,23 @@ def test_a_bucket_that_runs_over_where_the_hop_is_pushed():
         pair.check_aggregates()
     finally:
         pair.close()
+
+
+def test_no_room_for_lists_where_there_are_none():
+    """Graphs of more than 2^25 vertices have no lists, and nothing is allocated for them. Two layers of one column take 70 bytes per vertex: rows,
+    sums and changes 24, three lists with two prefixes each 36, list and prefix of the live vertices 8, marks and bitmaps 2. (Room for the lists
+    of the smallest pool such a graph can have: 24 bytes per vertex more.)"""
+    print("case memory of a large graph", flush=True)
+    n_cap = (1 << 25) + 64
+    src, dst = np.arange(0, 60, dtype=np.uint32), np.arange(1, 61, dtype=np.uint32)
+    ctx = rp.ripple_init_graph(64, n_cap, src, dst, ri.features(64, 1, 432), edge_capacity=100_000)
+    try:
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        rp.ripple_load_model(ctx, ri.make_model("gcn_sum", (1, 1, 1), 431))
+        torch.cuda.synchronize()
+        taken = before - torch.cuda.mem_get_info()[0]
+        print("  bytes per vertex %.1f" % (taken / n_cap), flush=True)
+        assert taken < 76 * n_cap
+    finally:
+        rp.ripple_destroy(ctx)
