@@ -709,6 +709,8 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         RP_TRY(dev_alloc(c, &c->side_v, entries, false));
         RP_TRY(dev_alloc(c, &c->side_acc, entries * xmax, false));
     }
+    bool weighted = false;
+    for (uint32_t l = 1; l <= c->L; ++l) weighted |= c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
     bool listed = false;                                 // some hop from the second on is one of sums
     for (uint32_t l = 2; l <= c->L; ++l) listed |= !rp_layer_mono(c, l) && !rp_layer_attn(c, l);
     if (listed && !c->opt_deterministic && rp_lists_allowed(c)) {
@@ -718,7 +720,7 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         Block b;
         b.add(&c->pairs, 2 * (size_t)c->pair_cap);
         b.add(&c->pair_sorted, c->pair_cap);
-        if (c->out_w) {                                  // ... and the edges' weights
+        if (weighted) {                                  // ... and the edges' weights
             b.add(&c->pair_w, 2 * (size_t)c->pair_cap);
             b.add(&c->pair_w_sorted, c->pair_cap);
         }
@@ -748,6 +750,10 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
     c->bm_vadd = bmall + (size_t)(c->L + 2) * c->n_words;
     RP_TRY(grow_scratch(c, PIN_OPS, 0));
     RP_HIP(c, hipStreamSynchronize(c->stream));
+    if (!weighted && c->out_w) {                         // no layer sends weighted messages: given back, and a new weight need not be looked up
+        hipFree(c->out_w);                               // in the out-row either
+        c->out_w = nullptr;
+    }
     c->state = 2;
     return RIPPLE_OK;
 }

@@ -134,7 +134,8 @@ struct ripple_ctx {
     uint2 *out_meta = nullptr, *in_meta = nullptr;      // {start, len} per vertex
     uint32_t *out_capv = nullptr, *in_capv = nullptr;   // row capacity
     uint32_t *out_pool = nullptr, *in_pool = nullptr;
-    float *in_w = nullptr, *out_w = nullptr;            // edge weights, parallel to in_pool and to out_pool (weighted graphs only)
+    float *in_w = nullptr, *out_w = nullptr;            // edge weights, parallel to in_pool and to out_pool (weighted graphs; out_w: from
+                                                        // load_model on only with a weighted-sum layer)
     uint32_t *alive = nullptr;                          // bitmap
     uint32_t *vstate = nullptr;                         // VS_* bits, zero between batches
     uint32_t *pend_out = nullptr, *pend_in = nullptr;   // appended this batch

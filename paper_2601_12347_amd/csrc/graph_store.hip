@@ -479,7 +479,8 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
             if (is_add) {                                   // absent from the shorter of the two rows
                 if (mo.y <= mi.y) po = find_part<W>(ro, mo.y, op.v, wave);
                 else po = find_part<W>(ri, mi.y, op.u, wave);
-            } else if (!is_edge && !a.in_w) {               // EDGE_REWEIGHT (else like a deletion: the edge must exist in both rows)
+            } else if (!is_edge && !a.out_w) {              // EDGE_REWEIGHT where only the in-row holds the weight (with weights in both rows: like a deletion)
+                if (a.in_w) pi = find_part<W>(ri, mi.y, op.u, wave);
             } else if (W == 1) {
                 po = find_part<1>(ro, mo.y, op.v, 0);
                 if (po >= 0) pi = find_part<1>(ri, mi.y, op.u, 0);
@@ -497,6 +498,7 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
             pi = s_pos[1];
         }
         if (ok && is_add) st = po < 0 ? 1u : 0u;
+        else if (ok && !is_edge && !a.out_w) st = pi >= 0 ? 1u : 0u;
         else if (ok) {
             st = (po >= 0 && pi >= 0) ? 1u : 0u;
             if (first && (po >= 0) != (pi >= 0)) a.ctr->error = 3;     // the two adjacencies disagree
@@ -855,7 +857,7 @@ __global__ __launch_bounds__(256) void k_edges(MutArgs a, uint32_t tb, uint32_t 
         }
         if (op.kind == RIPPLE_EDGE_REWEIGHT && lane == 0) {  // the weighted sums of the sink gain (alpha_new - alpha_old) h_u
             *wp = given;
-            a.out_w[a.out_meta[op.u].x + a.pos_out[i]] = given;
+            if (a.out_w) a.out_w[a.out_meta[op.u].x + a.pos_out[i]] = given;
             list_changed(a, atomicAdd(&a.ctr->n_struct, 1u), op.u, op.v, weighted, 0.0f);
         }
     }

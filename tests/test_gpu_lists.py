@@ -203,3 +203,46 @@ def test_no_room_for_lists_where_there_are_none():
         assert taken < 76 * n_cap
     finally:
         rp.ripple_destroy(ctx)
+
+
+def test_weights_beside_the_out_rows_only_for_weighted_sums():
+    """A weighted graph whose model has no weighted sum keeps the weights beside the in-rows alone: 4 bytes per entry of a pool, where weighted sums
+    take 4 more and 12 for a quarter of the entries (lists of messages)."""
+    src, dst, _, _ = ri.chung_lu_graph(700, 6000, 2.1, 0.03, 441)
+    weights = ri.edge_weights(len(src), 442)
+    free = {}
+    for kind, w in (("gcn_sum", None), ("gcn_sum", weights), ("gcn_wsum", weights)):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        args = dict(edge_capacity=30_000_000)
+        feats = ri.features(700, 12, 443)
+        ctx = rp.ripple_init_graph(700, 700, src, dst, feats, **args) if w is None else rp.ripple_init_graph_weighted(700, 700, src, dst, w, feats, **args)
+        try:
+            rp.ripple_load_model(ctx, ri.make_model(kind, (12, 20, 6), 444))
+            torch.cuda.synchronize()
+            free[kind, w is not None] = before - torch.cuda.mem_get_info()[0]
+        finally:
+            rp.ripple_destroy(ctx)
+    one, all_of_it = (free[k, True] - free["gcn_sum", False] for k in ("gcn_sum", "gcn_wsum"))
+    print("case memory of weights", one, all_of_it, flush=True)
+    assert one > 0 and abs(one / all_of_it - 4 / 11) < 0.05
+
+
+@pytest.mark.parametrize("kind", ["gcn_sum", "sage_mean", "gcn_max", "gat"])
+def test_new_weights_where_no_layer_uses_them(kind):
+    """Accepted where the edge exists, rejected where it does not, and kept: nothing but the graph's weights changes."""
+    print("case unused weights", kind, flush=True)
+    pair, graph = make_pair(n=700, e=6000, d0=12, kind=kind, widths=(12, 20, 6), seed=451, slack=128, weighted=True, edge_capacity=7000)
+    stream = make_stream(pair, graph, MIXW, 453, weighted=True)
+    try:
+        for b, bs in enumerate([1, 30, 300, 900]):
+            print(" batch", b, bs, flush=True)
+            ops, payload, _ = stream.next_batch(bs)
+            pair.step(ops, payload)
+        u, v = np.divmod(np.flatnonzero(~np.isin(np.arange(700 * 700), pair.ora.edges()[0] * 700 + pair.ora.edges()[1])), 700)
+        pick = np.random.default_rng(454).choice(len(u), 20, replace=False)
+        res, rec, _ = pair.step(np.array([(OP_EDGE_REWEIGHT, u[i], v[i], 0x3F800000) for i in pick], np.uint32), None)
+        assert res.n_applied == 0
+        pair.check_graph()
+    finally:
+        pair.close()
