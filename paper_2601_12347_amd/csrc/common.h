@@ -484,7 +484,13 @@ __device__ __forceinline__ int rp_hop_mode(const DevCtr *ctr, uint32_t l, uint32
 // A hop is taken from the list of its messages instead when the list was made (M fits the `cap` entries the host expected, no bucket
 // has run over) and it pays (force: whenever the list was made). M: out-edges of A_{l-1}. In place of a pull: writing a message down and
 // putting it in its place costs about what RP_LIST_FACTOR tests of an in-neighbour cost, and the launches what RP_LIST_FIXED of them cost. In
-// place of a push: the M * d float atomics take longer from RP_LIST_NUMBERS on.
+// place of a push: the M * d float atomics take longer from RP_LIST_NUMBERS on. All kernels of the hop but what both ways share, us:
+//   pushed / listed, 31 M edges: 256 columns, 20 * 2^20 numbers 81 / 90, 32 127 / 96; 128 columns, 7.7 45 / 71, 21 87 / 77; 64 columns, 13 61 / 72, 19
+//   83 / 74; 47 packed, 10 62 / 70, 15 88 / 72; 20 columns, 8.7 68 / 81, 15 105 / 105. 7 M edges: 256 columns, 20 98 / 126, 66 269 / 183; 64 columns, 18
+//   101 / 107, 36 182 / 140.
+//   pulled / listed, 64 columns: 2.1 M entries for 16 K messages 122 / 86, 1.4 M for 5 K 25 / 59; 30 M for 4.6 M 472 / 409; 128 columns, 30 M for
+//   4.5 M 545 / 536; 256 columns, 29 M for 2.0 M 582 / 430, 2.0 M for 13 K 37 / 103, 2.8 M for 40 K 163 / 109.
+// (Hops with more messages than an eighth of the edges discover: fewer than 6.5 entries per message, where both take as long, are rare.)
 #define RP_LIST_FACTOR 4ull
 #define RP_LIST_FIXED (2ull << 20)
 #define RP_LIST_NUMBERS (16ull << 20)

@@ -151,14 +151,12 @@ __device__ __forceinline__ floatx16 fp32_block(const TArgs &a, uint32_t slot, ui
 // wavefront waits for its own loads only; rows and weights are requested five steps of 16 k ahead. A lane holds four
 // consecutive k of its row (one 16-byte load), which the four products of a step take one each, so a step's k are
 // numbered lane group first: k = 4 * (lane / 16) + i for product i; the weights lie in that order in a.Wq (k by fours).
-// What bounds more rows is the L2, 32 KB per block at a K of 256. Measured (256 -> 256, launch included): 64 rows 7.0 us,
-// 1,024 rows 7.5, 2,048 rows 10.6, 3,000 rows 14.0; the 32 x 128 tiles take 11.0, 11.0, 11.4 and 11.7. So: up to two
-// wavefronts per SIMD.
-#define WAVE_GEMM_MAX 2048u
+// What bounds more rows is the L2, 32 KB per block at a K of 256, and that a SIMD's second wavefront starts behind its first.
 template <int MODE, int STORE>
 __device__ __forceinline__ void wave_gemm(const TArgs &a, uint32_t gw, uint32_t nw) {
     constexpr int STAGES = 6;
-    constexpr bool TWO = (MODE == 2) || (MODE == 1 && STORE == 1);
+    static_assert(MODE != 2, "sums of two rows go through the tiles");
+    constexpr bool TWO = MODE == 1 && STORE == 1;
     const uint32_t count = *a.count_ptr;
     const int lane = (int)(threadIdx.x & 63u);
     const uint32_t sub = (uint32_t)lane & 15u, grp = (uint32_t)lane >> 4;
@@ -238,3 +236,12 @@ __device__ __forceinline__ void wave_gemm(const TArgs &a, uint32_t gw, uint32_t 
 }
 // wavefronts (= 16 x 16 blocks) that `rows` rows take
 static inline uint32_t wave_gemm_waves(const TArgs &a, uint32_t rows) { return rp_div_up(rows ? rows : 1u, 16u) * rp_div_up(a.N, 16u); }
+// Within a launch that has other work too (k_hop_small) a launch is saved as well: up to two wavefronts per SIMD.
+#define WAVE_GEMM_MAX 2048u
+// On its own, against the tiles of k_transform_split (kernel time, wavefront each / tiles, us): 256 -> 256, 64 rows 7.0 / 9.5, 1,024 rows (a
+// wavefront per SIMD) 7.4 / 10.1, 1,536 rows 10.2 / 10.4, 2,048 rows 10.4 / 10.4, 3,072 rows 13.8 / 10.8; both products of 256 -> 47,
+// 2,048 rows (0.9 per SIMD) 7.5 / 9.5, 3,072 rows (1.3) 11.0 / 9.6, from bf16 rows 11.5 / 7.9; 256 -> 47, 4,096 rows (0.8) 7.4 / 9.6, 6,144 rows
+// (1.1) 10.9 / 10.0. With a K of 100 a second round is shorter: 100 -> 256, 2,048 rows 7.2 / 8.0, 3,072 rows 8.8 / 8.2; 100 -> 60, 8,192
+// rows (2) 6.7 / 7.1, 12,288 rows 8.2 / 7.6. So: a wavefront per SIMD, two up to a K of 128. Rows that are added up from two places
+// take it longer than the tiles at any number: 256 -> 256, 16 rows 10.8 / 7.2, 1,024 rows 10.0 / 8.3.
+static inline bool wave_gemm_pays(const TArgs &a, uint32_t rows) { return a.a_mode != 2 && wave_gemm_waves(a, rows) <= (a.K <= 128u ? 2048u : 1024u); }

@@ -930,11 +930,15 @@ __global__ __launch_bounds__(256) void k_transform_wave(TArgs a) {
 // Few rows: a product per wavefront (wave_gemm); more: tiles. Every matrix has its parts (wp_k >= Kpad: no read leaves them).
 template <int MODE, int STORE>
 static void launch_fast(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
-    if (a.Wq && !c->opt_split && wave_gemm_waves(a, rows_hint) <= WAVE_GEMM_MAX) {
-        // wavefronts for half as many rows again as expected; a set that turns out larger still finds every SIMD busy
-        const uint32_t waves = std::max(wave_gemm_waves(a, rows_hint + rows_hint / 2u), c->n_cu * 4);
-        hipLaunchKernelGGL((k_transform_wave<MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
-    } else if (a.Npad % 128 == 0) {
+    if constexpr (MODE != 2) {                             // (never pays)
+        if (!c->opt_split && wave_gemm_pays(a, rows_hint)) {
+            // wavefronts for half as many rows again as expected; a set that turns out larger still finds every SIMD busy
+            const uint32_t waves = std::max(wave_gemm_waves(a, rows_hint + rows_hint / 2u), c->n_cu * 4);
+            hipLaunchKernelGGL((k_transform_wave<MODE, STORE>), dim3(rp_div_up(waves, 4)), dim3(256), 0, c->stream, a);
+            return;
+        }
+    }
+    if (a.Npad % 128 == 0) {
         hipLaunchKernelGGL((k_transform_split<1, 4, 4, MODE, STORE>), dim3(tile_grid(c, rows_hint, 32, c->n_cu * 2), a.Npad / 128), dim3(256), 0, c->stream, a);
     } else {
         hipLaunchKernelGGL((k_transform_split<2, 2, 4, MODE, STORE>), dim3(tile_grid(c, rows_hint, 64, c->n_cu * 2), a.Npad / 64), dim3(256), 0, c->stream, a);

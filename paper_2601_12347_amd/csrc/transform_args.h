@@ -18,7 +18,7 @@ struct TArgs {
     const float *tmp_in;
     uint32_t tmp_ld;
     const float *W;                // [Kpad x Npad], zero padded
-    const float *Wq;               // the same with k by fours, [Kpad / 4][Npad][4] (wave_gemm), or null
+    const float *Wq;               // the same with k by fours, [Kpad / 4][Npad][4] (wave_gemm, fp32_block)
     const float *bias;             // [Npad]
     const __hip_bfloat16 *Wt;      // bf16 copy of W, transposed [Npad x Kpad] (k contiguous), or null
     uint32_t wt_ld;                // its row stride

@@ -14,7 +14,8 @@
 // (persistent workgroups for 256 -> 256, 32 x 128 tiles otherwise) -> now: 1.5 M rows 256 -> 256 with a cached row 1.66 -> 1.35 ms
 // (4.6 GB moved), 612 K rows 0.68 -> 0.53, without it 0.84 -> 0.46, 100 -> 256 0.49 -> 0.32 and 0.55 -> 0.38, both products of 256 -> 47
 // 1.5 M rows 0.73 -> 0.71 and 612 K 0.28 -> 0.27; 1.5 M bf16 rows 256 -> 47 0.53 -> 0.29. fp32 rows to at most 64 columns stay with the
-// tiles of fp32 products: 0.107 ms there, 0.139 here for 427 K rows 190 -> 23 (the tile of 256 rows leaves no registers).
+// tiles of k_transform_split: tiles / this kernel, 256 -> 47, 65,536 rows 27.7 / 29.6 us, 98,304 rows 39.3 / 44.1, 131,072 rows 50.2 / 46.8, 262,144
+// rows 103 / 83 (not taken: the bootstrap and the largest hops of such a layer would gain).
 // Other shapes of the same kernel: two workgroups of four wavefronts without a parked tile 1.50 ms for the first of these, four
 // wavefronts that only fetch and eight that only multiply 1.6, products of 16 x 16 x 32 no difference.
 // Rows stored in bf16 are exact as they are: three products.
@@ -434,8 +435,13 @@ static bool launch_k(ripple_ctx *c, const StreamArgs &s) {
     return true;
 }
 
-// Enough rows for every persistent workgroup to see two tiles: about 20 us go by before the first tile is out, in which the tiles of
-// fp32 products finish 12 K rows (1.6 us per thousand of 256 -> 256; here 0.8). RIPPLE_OPT_STREAM_TRANSFORM = 2: any number.
+// Enough rows for every persistent workgroup to see two tiles (of 64 rows at 256 padded columns, 128 at 128, 256 at 64): about 14 to 19 us go by
+// before the first tile is out, whatever the number of rows, and where only some workgroups have a second tile the others wait. Kernel
+// time, tiles of k_transform_split / this kernel, us: 256 -> 256, 8,192 rows 13.2 / 16.7, 16,384 rows (one tile each) 23.7 / 18.9, 24,576 rows
+// 30.8 / 28.6, 32,768 rows (two) 39.0 / 31.3; with a cached row 24.8 / 21.7, 31.8 / 33.7 and 40.2 / 36.0; GIN sums 26.3 / 22.8, 37.1 / 34.2 and
+// 47.0 / 36.0; both products of 256 -> 47, 49,152 rows (one and a half) 32.6 / 35.7, 65,536 rows (two) 41.4 / 38.1, from bf16 rows 26.6 / 26.6 and
+// 33.4 / 27.8; 256 -> 47 from bf16 rows, 98,304 rows 27.0 / 29.3, 131,072 rows (two) 33.9 / 30.9. (One tile each would be 10 to 20 % faster
+// here too, but a set a little larger than the previous batch's would be slower.) RIPPLE_OPT_STREAM_TRANSFORM = 2: any number.
 #define STREAM_MIN_TILES 2u
 bool rp_launch_stream(ripple_ctx *c, const TArgs &a, uint32_t rows_hint) {
     if (!c->opt_stream || !a.Wp || a.K > 256u || a.Npad > 256u || a.Npad < 64u) return false;
