@@ -239,9 +239,13 @@ static inline uint32_t wave_gemm_waves(const TArgs &a, uint32_t rows) { return r
 // Within a launch that has other work too (k_hop_small) a launch is saved as well: up to two wavefronts per SIMD.
 #define WAVE_GEMM_MAX 2048u
 // On its own, against the tiles of k_transform_split (kernel time, wavefront each / tiles, us): 256 -> 256, 64 rows 7.0 / 9.5, 1,024 rows (a
-// wavefront per SIMD) 7.4 / 10.1, 1,536 rows 10.2 / 10.4, 2,048 rows 10.4 / 10.4, 3,072 rows 13.8 / 10.8; both products of 256 -> 47,
-// 2,048 rows (0.9 per SIMD) 7.5 / 9.5, 3,072 rows (1.3) 11.0 / 9.6, from bf16 rows 11.5 / 7.9; 256 -> 47, 4,096 rows (0.8) 7.4 / 9.6, 6,144 rows
-// (1.1) 10.9 / 10.0. With a K of 100 a second round is shorter: 100 -> 256, 2,048 rows 7.2 / 8.0, 3,072 rows 8.8 / 8.2; 100 -> 60, 8,192
-// rows (2) 6.7 / 7.1, 12,288 rows 8.2 / 7.6. So: a wavefront per SIMD, two up to a K of 128. Rows that are added up from two places
-// take it longer than the tiles at any number: 256 -> 256, 16 rows 10.8 / 7.2, 1,024 rows 10.0 / 8.3.
-static inline bool wave_gemm_pays(const TArgs &a, uint32_t rows) { return a.a_mode != 2 && wave_gemm_waves(a, rows) <= (a.K <= 128u ? 2048u : 1024u); }
+// wavefront per SIMD) 7.4 / 10.1, 1,536 rows 10.2 / 10.4, 2,048 rows 10.4 / 10.4, 3,072 rows 13.8 / 10.8; 100 -> 256, 2,048 rows 7.2 / 8.0, 3,072
+// rows 8.8 / 8.2; both products of 256 -> 47, 2,048 rows (0.9 per SIMD) 7.5 / 9.5, 3,072 rows (1.3) 11.0 / 9.6, from bf16 rows 7.6 / 8.0 and 11.5 /
+// 7.9; 100 -> 60, 8,192 rows (2) 6.7 / 7.1, 12,288 rows 8.2 / 7.6. So: up to two wavefronts per SIMD, one with bf16 rows. (fp32 rows are nearly
+// even between one and two, and the number expected is the previous batch's: on 1.2 M edges sets differ by a factor of two from batch
+// to batch, and where a limit of one took the tiles they were slower: 12.2 us against 11.3 for 100 updates, 10.7 against 9.2 for 100 of a
+// max layer's narrow products.) Rows that are added up from two places take a wavefront each longer at any number: 256 -> 256, 16 rows
+// 10.8 / 7.2, 1,024 rows 10.0 / 8.3.
+static inline bool wave_gemm_pays(const TArgs &a, uint32_t rows) {
+    return a.a_mode != 2 && wave_gemm_waves(a, rows) <= (a.store && a.a_mode == 4 ? 1024u : 2048u);
+}
