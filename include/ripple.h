@@ -164,7 +164,7 @@ typedef enum {
                                      3 discover from hop 2 on (one scan of all in-rows gathers the messages and finds A_l) */
     RIPPLE_OPT_PULL_RATIO = 2,    /* auto mode pulls when messages * row_bytes * ratio >= 8 * scanned in-edges (default 1) */
     RIPPLE_OPT_BF16_MFMA = 4,     /* 0/1 (default 1): with bf16 storage, multiply on the bf16 matrix cores (fp32 accumulation);
-                                     0 keeps the fp32 matrix path on bf16-rounded inputs */
+                                     0 multiplies the bf16 rows, and sums of them, as fp32 numbers (see RIPPLE_OPT_SPLIT_MFMA) */
     RIPPLE_OPT_PROJECT_FIRST = 3, /* 0/1 (default 1), before load_model: layers with one linear map and d_out <= d_in/2
                                      cache sum_u H[u] W_neigh instead of sum_u H[u] and scatter d_out-wide messages */
     RIPPLE_OPT_SELF_CACHE = 5,    /* 0/1 (default 1), before load_model: layers that concatenate the vertex's own embedding
@@ -185,12 +185,17 @@ typedef enum {
                                      8 bytes, so that a number is off by at most 2^-19 of the largest of its three. What the
                                      rounding takes from a message is carried into the sender's next one: the cached
                                      aggregates stay the exact sum of what was sent and nothing accumulates. */
-    RIPPLE_OPT_STREAM_TRANSFORM = 11, /* 0/1/2 (default 1): products of many rows (from 32,768 on; widths of up to 256) run in persistent
-                                     workgroups that write a finished tile while the next one is being multiplied, every
-                                     fp32 number as three bf16 parts on the bf16 matrix cores (closer to 64-bit sums than a
-                                     chain of fp32 products); 0 keeps the kernels of one tile per workgroup
-                                     (the same parts) and of one product per wavefront (fp32 products); 2 takes the streaming kernel whatever the number
-                                     of rows, in two workgroups (for tests). */
+    RIPPLE_OPT_STREAM_TRANSFORM = 11, /* 0/1/2 (default 1): products of many rows run in persistent workgroups that write a finished tile while
+                                     the next one is being multiplied, every fp32 number as three bf16 parts on the bf16 matrix cores
+                                     (closer to 64-bit sums than a chain of fp32 products): from two tiles per compute unit on,
+                                     with 256 of them 32,768 rows where the matrix has 129 to 256 columns, 65,536 rows with 65 to 128 (a
+                                     layer's two products side by side count as these) and 131,072 with up to 64. Not for rows or
+                                     matrices wider than 256, arrays of 4 GB, [own | aggregate] rows whose self term is not cached,
+                                     matrices of up to 64 columns with fp32 rows and of more than 128 with bf16 rows, and
+                                     two-stage updates whose widths are not 129 to 256. 0 keeps the kernels of one tile per workgroup
+                                     (the same parts) and of one product per wavefront (fp32 products); 2 takes the streaming kernel
+                                     whatever the number of rows, in two workgroups (for tests; products made inside the launch of
+                                     a small hop stay there). */
     RIPPLE_OPT_SORTED_MESSAGES = 12, /* 0/1/2 (default 1): a hop that would be pulled while few of the scanned in-row entries
                                       carry a message, or pushed with many numbers to add, is scattered from the list of its
                                       messages instead, which the out-edge walk writes down by destination; 1 where the previous
@@ -201,7 +206,7 @@ typedef enum {
                                      the graph and the batches alone (no float atomics: in-rows keep a reproducible order,
                                      hops are gathered along them, rows that several wavefronts read are finished in
                                      wavefront order, changed edges are sorted), so that two runs over the same
-                                     operations on the same device model give the same bits. About 1.5x the time
+                                     operations on the same device model give the same bits. About 1.6x the time
                                      on a large graph. (Without it, two bootstraps of one stored graph do too, and max / min
                                      rows; sums of messages agree up to rounding order.)
                                      Sum and mean layers only. */

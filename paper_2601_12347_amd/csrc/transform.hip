@@ -982,7 +982,7 @@ TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uin
     a.mean = 0;
     a.W = ly.Wn;
     a.Wq = ly.Wnq;
-    a.Wt = nullptr;                                // messages are differences of such products: fp32 path also for bf16 rows
+    a.Wt = nullptr;                                // messages are differences of such products: fp32 weights (in parts) also for bf16 rows
     a.Wp = ly.Wnp;
     a.wp_k = rp_round_up(ly.d_in, 128);
     a.bias = ly.bzero;
