@@ -10,7 +10,9 @@
 // Against 64-bit sums the rows are closer than a chain of fp32 products: 2-norm of the error over that of the result, K = 256,
 // normal / rectified rows: 8.5e-8 / 6.6e-8 (fp32 matrix cores 2.9e-7 / 2.0e-7; K = 32: 3.9e-8 against 1.0e-7; K = 96 and 128 in between).
 // What bounds it: six products of a bf16 rate of 1.7 to 2.1 PFLOP/s (dense matrix products of numbers that are not zero lower the clock;
-// 2.4 with zeros) and memory, about as much each; fp32 products reach 138 TFLOP/s, 3/8 of that in the end. Measured, fp32 products
+// 2.4 with zeros) and memory, neither at its limit: 1.5 M rows 256 -> 256 with a cached row keep the matrix cores busy 42 % of the cycles, at
+// 2.0 GHz, and move 3.6 TB/s, because a compute unit's one workgroup converts, stores and waits at its slices' barriers in between; fp32
+// products reach 138 TFLOP/s, 3/8 of that in the end. Measured, fp32 products
 // (persistent workgroups for 256 -> 256, 32 x 128 tiles otherwise) -> now: 1.5 M rows 256 -> 256 with a cached row 1.66 -> 1.35 ms
 // (4.6 GB moved), 612 K rows 0.68 -> 0.53, without it 0.84 -> 0.46, 100 -> 256 0.49 -> 0.32 and 0.55 -> 0.38, both products of 256 -> 47
 // 1.5 M rows 0.73 -> 0.71 and 612 K 0.28 -> 0.27; 1.5 M bf16 rows 256 -> 47 0.53 -> 0.29. fp32 rows to at most 64 columns stay with the
