@@ -172,7 +172,7 @@ typedef enum {
     RIPPLE_OPT_SPLIT_MFMA = 7,    /* 0/1 (default 0), before load_model: the dense products of fp32 numbers run on the bf16 matrix cores
                                      with every operand as three bf16 numbers and the six largest of the nine partial
                                      products kept (what is dropped is below 2^-24 of a product) whatever the number of
-                                     rows; 0: from some thousand rows on, where it is the faster way */
+                                     rows; 0: where it is the faster way (GIN sums; other rows from some thousand on) */
     RIPPLE_OPT_SPARSE_FRONTIER = 8, /* 0/1 (default 1): a hop whose set was small in the previous batch enters vertices into
                                      its list as they are marked instead of scanning the whole bitmap afterwards */
     RIPPLE_OPT_ROW_SEGMENTS = 9,  /* >= 0 (default: what the graph's edge capacity can need, at most 262144): max / min and attention
