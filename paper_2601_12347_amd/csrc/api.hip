@@ -78,12 +78,13 @@ __global__ void k_store_rows(const float *src, void *dst, size_t n, int store) {
 // 0.54 ms for 2.45 M rows of 47; now 0.26.)
 typedef float gfloatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t guintx2u __attribute__((ext_vector_type(2), aligned(2)));
+// groups of four numbers i0, i0 + stride, ... of rows ids[0 .. n_rows) (no ids: first .. first + n_rows - 1)
 template <int STORE>
-__global__ __launch_bounds__(256) void k_gather_rows(const void *M, uint32_t d, const uint32_t *ids, uint32_t first,
-                                                     size_t n_rows, uint32_t n_cap, float *out, HostFlag done) {
+__device__ __forceinline__ void gather_groups(const void *M, uint32_t d, const uint32_t *ids, uint32_t first, size_t n_rows, uint32_t n_cap, float *out,
+                                              size_t i0, size_t stride) {
     const uint32_t groups = (d + 3u) / 4u;                   // of four numbers; a row's last one may be short
-    const size_t total = n_rows * groups, stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
+    const size_t total = n_rows * groups;
+    for (size_t i = i0; i < total; i += stride) {
         const size_t r = total <= 0xFFFFFFFFull ? (size_t)((uint32_t)i / groups) : i / groups;
         const uint32_t col = (uint32_t)(i - r * groups) * 4u;
         const uint32_t id = ids ? ids[r] : (uint32_t)(first + r);
@@ -109,6 +110,51 @@ __global__ __launch_bounds__(256) void k_gather_rows(const void *M, uint32_t d, 
             if (col + 2u < d) o[2] = v.z;
         }
     }
+}
+template <int STORE>
+__global__ __launch_bounds__(256) void k_gather_rows(const void *M, uint32_t d, const uint32_t *ids, uint32_t first,
+                                                     size_t n_rows, uint32_t n_cap, float *out, HostFlag done) {
+    gather_groups<STORE>(M, d, ids, first, n_rows, n_cap, out, (size_t)blockIdx.x * 256u + threadIdx.x, (size_t)gridDim.x * 256u);
+    report_done(done, gridDim.x);
+}
+
+// The same into pinned memory in pieces of `piece` rows, each at the front of READ_FLOATS numbers of its own; when piece p is there, `seq` goes to the word
+// 64 * p bytes behind `flags`. Teams of PIECE_WGS workgroups take the pieces in turn (their 16,384 threads a piece's groups of four at once), so that one
+// piece is on its way while the other team waits for its own to have arrived. `arrived`: a counter per piece, zero between launches.
+#define PIECE_WGS 64u
+#define PIECE_TEAMS 2u
+template <int STORE>
+__global__ __launch_bounds__(256) void k_gather_pieces(const void *M, uint32_t d, const uint32_t *ids, uint32_t first, uint32_t n_rows, uint32_t piece, uint32_t n_cap,
+                                                       float *out, uint32_t *flags, uint32_t seq, uint32_t *arrived) {
+    const uint32_t team = blockIdx.x / PIECE_WGS, wg = blockIdx.x % PIECE_WGS, n_pieces = (n_rows + piece - 1u) / piece;
+    for (uint32_t p = team; p < n_pieces; p += PIECE_TEAMS) {
+        const uint32_t r0 = p * piece;
+        gather_groups<STORE>(M, d, ids ? ids + r0 : nullptr, first + r0, min(piece, n_rows - r0), n_cap, out + (size_t)p * READ_FLOATS, wg * 256u + threadIdx.x, PIECE_WGS * 256u);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wavefront's stores have been performed
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __threadfence_system();
+            if (atomicAdd(&arrived[p], 1u) == PIECE_WGS - 1u) {
+                arrived[p] = 0;
+                __hip_atomic_store(flags + 16u * p, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+    }
+}
+
+// Numbers (or any 4-byte words) from one place to another, four per thread and load, four loads under way: whole tables on the device, and operations
+// that are handed over on the device to the host. `from` and `to` start at multiples of four bytes.
+__global__ __launch_bounds__(256) void k_copy_numbers(const float *from, float *to, size_t n, HostFlag done) {
+    const size_t stride = (size_t)gridDim.x * 1024u, quads = n / 4u;
+    for (size_t q0 = (size_t)blockIdx.x * 1024u + threadIdx.x; q0 < quads; q0 += stride) {
+        gfloatx4u v[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) v[k] = *(const gfloatx4u *)(from + 4u * min(q0 + 256u * k, quads - 1u));
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            if (q0 + 256u * k < quads) *(gfloatx4u *)(to + 4u * (q0 + 256u * k)) = v[k];
+    }
+    if (blockIdx.x == 0 && threadIdx.x < n % 4u) to[quads * 4u + threadIdx.x] = from[quads * 4u + threadIdx.x];
     report_done(done, gridDim.x);
 }
 
@@ -201,11 +247,12 @@ static ripple_status block_alloc(ripple_ctx *c, const Block &b, uint8_t **base, 
     return RIPPLE_OK;
 }
 
-// Small transfers to the host go through pinned memory that the kernel itself writes (and reads ids from): a kernel and one
-// wait, where a copy to pageable memory costs a second launch and a second wait. Larger ones are left to the copy
-// engine, which is faster once the transfer itself counts (0.13 against 0.03 ms at half a megabyte).
-#define IO_PIN_IDS 32768u
-#define IO_PIN_FLOATS 65536u
+// What the host reads goes through pinned memory that the kernels write themselves (and read ids from). Rows leave in pieces of at most
+// READ_FLOATS numbers: one launch writes up to READ_PIECES of them one after the other and says so after each, and while it writes the next ones the
+// host copies; reads of more pieces take the two halves in turn. A read so takes little more than the slower of the two (kernels write to the host
+// at 50 GB/s, a copy out of the pinned memory runs at 30 to 42). Rows of 47 numbers by ids, the runtime's copy to pageable memory / this, us: 66 K
+// numbers 40 / 26, 235 K 67 / 59, 1.2 M 304 / 187, 9.4 M 2,249 / 1,407; 4 x 40 K to 4 x 300 K numbers behind a batch 76 to 319 / 43 to 186.
+#define IO_PIN_IDS 131072u
 // operations and feature rows of a batch that the pinned block has room for; larger batches get staging of their own
 #define PIN_OPS 6144u
 #define PIN_ROWS 1024u
@@ -219,19 +266,20 @@ HostFlag rp_host_flag(ripple_ctx *c) { return HostFlag{c->pub_flag, ++c->pub_seq
 // stream, which goes over every launch since the last one (a batch of twenty launches: 63 against 90 us). What takes longer than
 // the limit gets the stream wait, which also is what reports a device error.
 #define WAIT_SPIN_US 2000.0
-ripple_status rp_wait_flag(ripple_ctx *c) {
+static ripple_status wait_word(ripple_ctx *c, const uint32_t *word, uint32_t value) {
     RP_HIP(c, hipGetLastError());
     const auto t0 = std::chrono::steady_clock::now();
-    for (uint32_t k = 0; __atomic_load_n(c->pub_flag, __ATOMIC_ACQUIRE) != c->pub_seq; ++k) {
+    for (uint32_t k = 0; __atomic_load_n(word, __ATOMIC_ACQUIRE) != value; ++k) {
         __builtin_ia32_pause();
         if ((k & 255u) == 255u && std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() > WAIT_SPIN_US) {
             RP_HIP(c, hipStreamSynchronize(c->stream));
             break;
         }
     }
-    if (__atomic_load_n(c->pub_flag, __ATOMIC_ACQUIRE) != c->pub_seq) return fail(c, RIPPLE_EDEVICE, "a kernel did not report its end");
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) != value) return fail(c, RIPPLE_EDEVICE, "a kernel did not report its end");
     return RIPPLE_OK;
 }
+ripple_status rp_wait_flag(ripple_ctx *c) { return wait_word(c, c->pub_flag, c->pub_seq); }
 
 static size_t elem_size(const ripple_ctx *c) { return c->store ? 2 : 4; }
 
@@ -298,11 +346,11 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
         RP_TRY(dev_alloc(c, &c->in_w, (size_t)pool_cap, false));
         RP_TRY(dev_alloc(c, &c->out_w, (size_t)pool_cap, false));
     }
-    {   // pinned memory, in one allocation (200 to 300 us each, whatever the size): counters, the flag, read-back, and the staging of
-        // ordinary batches
-        const size_t ctr_at = 0, flag_at = (sizeof(DevCtr) + 63) & ~(size_t)63, io_at = flag_at + 64;
-        const size_t made_at = io_at + (16 + IO_PIN_IDS + IO_PIN_FLOATS) * 4, ops_at = made_at + SMALL_OPS * 4, rows_at = ops_at + PIN_OPS * sizeof(ripple_update);
-        c->pin_bytes = rows_at + (size_t)PIN_ROWS * d0 * 4;
+    {   // pinned memory, in one allocation (200 to 300 us each, whatever the size): counters, the flag, the staging of ordinary batches, read-back.
+        // The room for rows comes last: what every batch uses lies close together (with 4 MB in between, the first batch took 10 to 50 us longer)
+        const size_t ctr_at = 0, flag_at = (sizeof(DevCtr) + 63) & ~(size_t)63, piece_at = flag_at + 64, made_at = piece_at + 2 * READ_PIECES * 64;
+        const size_t ops_at = made_at + SMALL_OPS * 4, rows_at = ops_at + PIN_OPS * sizeof(ripple_update), io_at = rows_at + (size_t)PIN_ROWS * d0 * 4;
+        c->pin_bytes = io_at + (16 + IO_PIN_IDS + 2 * READ_PIECES * READ_FLOATS) * 4;
         RP_HIP(c, hipHostMalloc((void **)&c->pin_block, c->pin_bytes, hipHostMallocDefault));
         c->ctr_host = (DevCtr *)(c->pin_block + ctr_at);
         c->pub_flag = (uint32_t *)(c->pin_block + flag_at);
@@ -314,6 +362,8 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
         c->feat_cap = PIN_ROWS;
         memset(c->ctr_host, 0, sizeof(DevCtr));
         *c->pub_flag = 0;
+        c->read_flag = (uint32_t *)(c->pin_block + piece_at);
+        memset(c->read_flag, 0, 2 * READ_PIECES * 64);
     }
     {   // features
         void *h0 = nullptr;
@@ -1218,7 +1268,15 @@ extern "C" ripple_status ripple_apply_updates(ripple_ctx *c, const ripple_update
     RP_TRY(grow_staging(c, n_ops, rows_on_host ? n_feat_rows : 0u));
     // operations are needed on the host (validation, conflict analysis)
     const ripple_update *hops = ops;
-    if (n_ops && is_device_ptr(c, ops)) {
+    const Place ops_place = n_ops ? place_of(c, ops) : ON_HOST;
+    if (ops_place == OWN_GPU) {                            // by a kernel that reports its end: the runtime's copy and the wait for the stream take 15 us more
+        const uint32_t gb = rp_div_up(n_ops, 256 * 4);
+        const HostFlag done = gb <= REPORT_WGS ? rp_host_flag(c) : HostFlag{nullptr, 0u, nullptr};
+        hipLaunchKernelGGL(k_copy_numbers, dim3(gb), dim3(256), 0, s, (const float *)ops, (float *)c->ops_pin, (size_t)n_ops * 4, done);
+        if (!done.flag) rp_launch_report(c);
+        RP_TRY(rp_wait_flag(c));
+        hops = c->ops_pin;
+    } else if (ops_place == FAR_GPU) {
         RP_HIP(c, hipMemcpyAsync(c->ops_pin, ops, (size_t)n_ops * sizeof(ripple_update), hipMemcpyDeviceToHost, s));
         RP_HIP(c, hipStreamSynchronize(s));
         hops = c->ops_pin;
@@ -1401,7 +1459,14 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
     }
     const Place place = place_of(c, out);
     const size_t total = (size_t)n_ids * d;
-    if (!ids && !store && (place != ON_HOST || total > IO_PIN_FLOATS)) {   // contiguous float32 rows: plain copy
+    if (!ids && !store && place != ON_HOST) {                // contiguous float32 rows
+        if (place == OWN_GPU) {                              // (4.6 M numbers 26 us with the runtime's copy and the wait for the stream, 14 so)
+            const uint32_t gb = (uint32_t)std::min<size_t>((total + 4095) / 4096, c->n_cu * 8);
+            const HostFlag done = gb <= REPORT_WGS ? rp_host_flag(c) : HostFlag{nullptr, 0u, nullptr};
+            hipLaunchKernelGGL(k_copy_numbers, dim3(gb), dim3(256), 0, s, (const float *)M, out, total, done);
+            if (!done.flag) rp_launch_report(c);
+            return rp_wait_flag(c);
+        }
         RP_HIP(c, hipMemcpyAsync(out, M, total * 4, hipMemcpyDefault, s));
         RP_HIP(c, hipStreamSynchronize(s));
         return RIPPLE_OK;
@@ -1418,11 +1483,33 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
         launch(0, n_ids, out, true);
         return rp_wait_flag(c);
     }
-    if (place == ON_HOST && total <= IO_PIN_FLOATS) {
-        float *rows = (float *)(c->io_pin + 16 + IO_PIN_IDS);
-        launch(0, n_ids, rows, true);
-        RP_TRY(rp_wait_flag(c));
-        memcpy(out, rows, total * 4);
+    if (place == ON_HOST) {
+        float *pinned = (float *)(c->io_pin + 16 + IO_PIN_IDS);
+        if (total <= READ_FLOATS) {
+            launch(0, n_ids, pinned, true);
+            RP_TRY(rp_wait_flag(c));
+            memcpy(out, pinned, total * 4);
+            return RIPPLE_OK;
+        }
+        const uint32_t piece = READ_FLOATS / d, half = piece * READ_PIECES;          // rows (of at most 1,024 numbers)
+        uint32_t seq[2];
+        auto fill = [&](uint32_t k) {                       // rows k * half .. into half k % 2
+            const uint32_t r0 = k * half, rows = std::min(half, n_ids - r0), h = k % 2u;
+            seq[h] = ++c->read_seq;
+            const auto kernel = store ? k_gather_pieces<1> : k_gather_pieces<0>;
+            hipLaunchKernelGGL(kernel, dim3(PIECE_WGS * std::min(PIECE_TEAMS, rp_div_up(rows, piece))), dim3(256), 0, s, M, d, ids_d ? ids_d + r0 : nullptr, r0, rows, piece, c->n_cap,
+                               pinned + (size_t)h * READ_PIECES * READ_FLOATS, c->read_flag + h * READ_PIECES * 16u, seq[h], c->ctr->piece_done);
+        };
+        const uint32_t n_halves = rp_div_up(n_ids, half);
+        for (uint32_t k = 0; k < std::min(n_halves, 2u); ++k) fill(k);
+        for (uint32_t k = 0; k < n_halves; ++k) {
+            const uint32_t h = k % 2u;
+            for (uint32_t p = 0, r = k * half; p < READ_PIECES && r < n_ids; ++p, r += piece) {
+                RP_TRY(wait_word(c, c->read_flag + (h * READ_PIECES + p) * 16u, seq[h]));
+                memcpy(out + (size_t)r * d, pinned + (size_t)(h * READ_PIECES + p) * READ_FLOATS, (size_t)std::min(piece, n_ids - r) * d * 4);
+            }
+            if (k + 2u < n_halves) fill(k + 2u);
+        }
         return RIPPLE_OK;
     }
     const size_t chunk_rows = std::max<size_t>(1, ((size_t)64 << 20) / d);
@@ -1437,7 +1524,7 @@ static ripple_status gather_rows(ripple_ctx *c, const void *M, int store, uint32
     for (size_t r0 = 0; r0 < n_ids; r0 += chunk_rows) {
         size_t rows = std::min<size_t>(chunk_rows, n_ids - r0);
         launch(r0, rows, c->gather_d, false);
-        RP_HIP(c, hipMemcpyAsync(out + r0 * d, c->gather_d, rows * d * 4, hipMemcpyDefault, s));   // the host's or another GPU's
+        RP_HIP(c, hipMemcpyAsync(out + r0 * d, c->gather_d, rows * d * 4, hipMemcpyDefault, s));   // another GPU's
         RP_HIP(c, hipStreamSynchronize(s));
     }
     return RIPPLE_OK;

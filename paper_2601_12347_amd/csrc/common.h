@@ -24,6 +24,9 @@
 #define EXP_OUT 1u                   // (w -> y): erase w from y's in-row
 #define EXP_IN 2u                    // (x -> w): erase w from x's out-row
 
+#define READ_PIECES 8u               // pieces of rows that one launch writes to the host, of at most READ_FLOATS numbers each
+#define READ_FLOATS 65536u
+
 struct DevCtr {                      // device-resident counters, one instance per context
     // kept from batch to batch
     unsigned long long n_edges;
@@ -32,6 +35,7 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t error;                           // sticky consistency error seen by a kernel
     uint32_t blocks_done;                     // workgroups of a kernel with a last-workgroup part that have finished (0 between launches)
     uint32_t n_all;                           // live vertices listed for a discovering hop
+    uint32_t piece_done[READ_PIECES];         // workgroups that have written their part of a piece that the host reads (0 between launches)
     // from here on: zero when a batch begins (k_publish clears them once it has handed them to the host)
     struct Set {
         uint32_t a;                           // |A_l|
@@ -202,6 +206,8 @@ struct ripple_ctx {
     DevCtr *ctr_host = nullptr;                         // pinned mirror, written by k_publish
     uint32_t *pub_flag = nullptr;                       // pinned: number of the last k_publish that has finished
     uint32_t pub_seq = 0;
+    uint32_t *read_flag = nullptr;                      // pinned: number of the last launch that has written this piece, 16 words per piece
+    uint32_t read_seq = 0;
     hipEvent_t idle = nullptr;                          // recorded behind the launches of a call that promises a synchronised stream
     bool ctr_dirty = false;                             // the per-batch counters are not zero (something ran after k_publish)
     ripple_update *ops_pin = nullptr;                   // pinned staging for ops
@@ -366,13 +372,17 @@ __device__ __forceinline__ uint32_t rp_count_le(uint32_t b, uint32_t e) {
     return lo;
 }
 
-// true in the last of n workgroups to get here (all of what the others wrote is then visible); called by whole workgroups
+// true in the last of n workgroups to get here (all of what the others wrote is then visible; SYSTEM: to the host as well); called by whole
+// workgroups. One wavefront of a workgroup passes the fence for all: it writes back the L2, and a fence in each of them made a launch of 64 workgroups
+// that reports its end take 12.6 us until the host sees it (8.7 with one; a launch and k_report behind it 9.4).
+template <bool SYSTEM = false>
 __device__ __forceinline__ bool last_workgroup(DevCtr *ctr, uint32_t n) {
     __shared__ uint32_t s_last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wavefront's stores and atomics have been performed: a barrier alone does not wait for them
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
+        if (SYSTEM) __threadfence_system();                 // results may lie in the host's memory
+        else __threadfence();
         s_last = atomicAdd(&ctr->blocks_done, 1u) == n - 1u ? 1u : 0u;
         if (s_last) ctr->blocks_done = 0;
     }
@@ -382,9 +392,9 @@ __device__ __forceinline__ bool last_workgroup(DevCtr *ctr, uint32_t n) {
     return true;
 }
 // The same for a launch whose results the host waits for by looking at *flag (pinned memory) instead of waiting for the stream: the
-// last workgroup stores `seq` there. flag null: nothing is reported. For launches of at most REPORT_WGS workgroups (each costs about
-// 60 ns, one after the other); after larger ones k_report does it.
-#define REPORT_WGS 24u
+// last workgroup stores `seq` there. flag null: nothing is reported. For launches of at most REPORT_WGS workgroups (each costs about 16 ns, one after
+// the other: up to 96 of them take as long as k_report or less); after larger ones k_report does it.
+#define REPORT_WGS 96u
 struct HostFlag {
     uint32_t *flag;
     uint32_t seq;
@@ -392,8 +402,7 @@ struct HostFlag {
 };
 __device__ __forceinline__ void report_done(const HostFlag &h, uint32_t n) {
     if (!h.flag) return;
-    __threadfence_system();                                 // results may lie in the host's memory
-    if (last_workgroup(h.ctr, n) && threadIdx.x == 0) __hip_atomic_store(h.flag, h.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (last_workgroup<true>(h.ctr, n) && threadIdx.x == 0) __hip_atomic_store(h.flag, h.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- packed messages ------------------------------------------------------------------
