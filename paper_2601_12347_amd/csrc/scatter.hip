@@ -106,9 +106,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
-    // delta rows gathered per round trip; the weighted one-column kernel takes 12 so that it stays
-    // within 64 registers (eight waves per SIMD), which matters more here than the deeper round
-    constexpr int G = (NJ >= 8) ? 2 : (WT && NJ == 1) ? 12 : 16 / NJ;
+    constexpr int G = (NJ >= 8) ? 2 : 16 / NJ;              // delta rows gathered per round trip
     constexpr int T = PULL_CHUNK / 64;                      // in-edges examined per lane and chunk
     const int lane = rp_lane();
     const uint32_t d = a.d;
@@ -391,7 +389,7 @@ __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
     if (made) list_clear(a);
     if (!used) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_SORTED;
-    constexpr int G = (NJ >= 8) ? 2 : (NJ == 4 ? 4 : 8 / NJ);   // message rows per round trip (and up to as many destination rows)
+    constexpr int G = (NJ >= 8) ? 2 : 4;                    // message rows per round trip (and up to as many destination rows)
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     const int lane = rp_lane();
     const uint32_t d = a.d;
@@ -481,11 +479,52 @@ __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
 // (the atomic units take about three cycles per lane, so the number of such rows, not of instructions, is what
 // counts). The destination and the partial sums carry over from chunk to chunk: a wavefront adds to a row once,
 // however many chunks the row's in-edges span.
-#define PULL4_QUADS 4                                       // quads (16 rows) in flight per wavefront
+// Rows of up to 64 floats (not packed) are taken the same way, four columns per lane: 16, 8 or 4 lanes per row and 4, 8 or 16
+// rows at a time. F names the form: 0 packed, else the lanes per row of floats.
+//   a lane per column and a row per instruction, before: @@
+template <int F>
+struct RowForm {
+    static constexpr int LANES = F ? F : 16;                // per row
+    static constexpr int ROWS = 64 / LANES;                 // per load instruction
+    static constexpr int LOADS = F == 4 ? 2 : 4;            // in flight per wavefront
+    static constexpr int V = F ? 4 : 3;                     // columns per lane: 4 sub .. 4 sub + 3 (packed: sub, 16 + sub, 32 + sub)
+};
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));   // (rows of floats begin at any multiple of four bytes)
+// The groups' partial sums added up; what comes back is the column that this lane sends to memory (row_column), one per row of 16 lanes. Every
+// step halves what a lane still has to add, and none goes through LDS: lanes 8 and 4 apart by rotations within a row, then two rows' columns
+// trade places and are added (permlane16_swap and permlane32_swap: odd rows of the first operand, or its upper half, against even rows, or
+// the lower half, of the second). With two or three shuffles per column in their place a sum of a few messages cost more than its gathers.
+__device__ __forceinline__ float swap_add16(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);   // rows 0 and 2: x over the two rows, rows 1 and 3: y
+}
+__device__ __forceinline__ float swap_add32(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);   // lower half: x over both halves, upper half: y
+}
+template <int F>
+__device__ __forceinline__ float rows_sum(float (&acc)[RowForm<F>::V]) {
+    constexpr int V = RowForm<F>::V, LANES = RowForm<F>::LANES;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        if (LANES <= 8) acc[j] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc[j]), 0x128, 0xf, 0xf, false));   // row_ror:8
+        if (LANES <= 4) acc[j] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc[j]), 0x124, 0xf, 0xf, false));   // row_ror:4
+    }
+    const float s = swap_add32(swap_add16(acc[0], acc[1]), swap_add16(acc[2], acc[V - 1]));   // (V = 3: the fourth row's is not used)
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[j] = 0.0f;
+    return s;
+}
+template <int F>
+__device__ __forceinline__ uint32_t row_column(uint32_t lane) {    // (beyond any row: nothing to send)
+    const uint32_t row = lane >> 4, sub = lane & 15u;
+    if (row >= (uint32_t)RowForm<F>::V || sub >= (uint32_t)RowForm<F>::LANES) return 0xFFFFFFFFu;
+    return F ? 4u * sub + row : 16u * row + sub;
+}
 #define PULL4_PAD 0xFFFFFFFEu                               // destination of the entries that fill a chunk's last round
-template <int DISC, int WT, int DET>
+template <int F, int DISC, int WT, int DET>
 __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
-    static_assert(!DET || (!DISC && !WT), "the deterministic form pulls into A_l, unweighted");
+    static_assert(!DET || (!DISC && !WT && !F), "the deterministic form pulls into A_l, unweighted, packed rows");
     if (!DET && rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL)) return;
     if (!DET && !DISC && pull_is_listed(a)) return;
     const uint32_t count = *a.count_ptr;
@@ -493,14 +532,15 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
     constexpr int T = PULL_CHUNK / 64;
     constexpr uint32_t NONE = 0xFFFFFFFFu;
-    constexpr uint32_t LIST = PULL_CHUNK + 4 * PULL4_QUADS; // a round always reads 4 PULL4_QUADS entries
-    // per dirty in-edge: (byte offset of the source's message row, destination); what the inner loop needs per quad
-    // is then one 8-byte LDS read and one addition in front of the row's load
+    constexpr int LANES = RowForm<F>::LANES, ROWS = RowForm<F>::ROWS, LOADS = RowForm<F>::LOADS, V = RowForm<F>::V;
+    constexpr uint32_t LIST = PULL_CHUNK + ROWS * LOADS;    // a round always reads ROWS * LOADS entries
+    // per dirty in-edge: (packed: byte offset of the source's message row, else the source; destination); what the inner loop needs per
+    // load is then one 8-byte LDS read and one addition (rows of floats: a multiplication as well) in front of it
     __shared__ uint2 s_e[4][LIST];
     __shared__ float s_w[WT ? 4 : 1][WT ? LIST : 1];
     __shared__ uint8_t s_r[DET ? 4 : 1][DET ? LIST : 1];        // DET: the entry's destination is recomputed
     const int lane = rp_lane(), wave = threadIdx.x >> 6;
-    const uint32_t grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
+    const uint32_t grp = (uint32_t)lane / LANES, sub = (uint32_t)lane & (LANES - 1u);
     const uint32_t d = a.d;
     const uint32_t total = a.ioff[count];
     const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
@@ -523,11 +563,14 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     // message rows through a buffer descriptor: 32-bit byte offsets (row offset from LDS + this lane's chunk)
     const __amdgpu_buffer_rsrc_t mres = __builtin_amdgcn_make_buffer_rsrc((void *)a.D, 0, a.msg_bytes, 0x00020000u);
     const uint32_t sub8 = 8u * sub;
-    const uint32_t my_col = 16u * grp + sub;                // the column this lane sends to memory
-    const bool sends = grp < 3u && my_col < d;
+    const float *frow = a.D + (4u * sub < d ? 4u * sub : 0u);   // rows of floats: lanes beyond the row repeat its first columns
+    const uint32_t my_col = row_column<F>((uint32_t)lane);        // the column this lane sends to memory
+    const bool sends = my_col < d;
     uint32_t cur = NONE;                                    // destination being summed (the same in all lanes)
     bool cur_rec = false;                                   // ... and whether it is recomputed (DET)
-    float acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;            // this group's partial sums of columns sub, 16 + sub, 32 + sub
+    float acc[V];                                           // this group's partial sums
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[j] = 0.0f;
     PullScan<T, WT> scan;
     scan.begin(a, count, c_begin, lane);
     uint32_t v_head = NONE, v_tail = NONE;                  // DET: see k_scatter_pull
@@ -537,13 +580,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
         v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * PULL_CHUNK) - 1u)];
     }
     auto flush = [&]() {
-        acc0 += __shfl_xor(acc0, 16);
-        acc1 += __shfl_xor(acc1, 16);
-        acc2 += __shfl_xor(acc2, 16);
-        acc0 += __shfl_xor(acc0, 32);
-        acc1 += __shfl_xor(acc1, 32);
-        acc2 += __shfl_xor(acc2, 32);
-        const float mine = grp == 0u ? acc0 : (grp == 1u ? acc1 : acc2);
+        const float mine = rows_sum<F>(acc);
         if (!DET) {
             if (sends && mine != 0.0f) unsafeAtomicAdd(&a.X[(size_t)cur * d + my_col], mine);
             if (DISC && lane == 0) atomicOr(&a.bm_cur[cur >> 5], 1u << (cur & 31));
@@ -555,7 +592,6 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
             float *x = &a.X[(size_t)cur * d + my_col];
             *x = cur_rec ? mine : *x + mine;
         }
-        acc0 = acc1 = acc2 = 0.0f;
     };
     for (;;) {
     for (uint32_t c = c_begin; c < c_end; ++c) {
@@ -576,14 +612,14 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
             const unsigned long long mask = __ballot(dirty[t]);
             const uint32_t pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
             if (dirty[t]) {
-                s_e[wave][pos] = make_uint2(my_u[t] << 7, my_v[t]);
+                s_e[wave][pos] = make_uint2(F ? my_u[t] : my_u[t] << 7, my_v[t]);
                 if (WT) s_w[wave][pos] = my_w[t];
                 if (DET) s_r[wave][pos] = rec ? 1 : 0;
             }
             n += (uint32_t)__popcll(mask);
         }
         // the entries a round reads past the list's end: row 0 (valid memory), a destination that never matches
-        if (lane < 4 * PULL4_QUADS) {
+        if (lane < ROWS * LOADS) {
             s_e[wave][n + lane] = make_uint2(0u, PULL4_PAD);
             if (WT) s_w[wave][n + lane] = 0.0f;
             if (DET) s_r[DET ? wave : 0][DET ? n + lane : 0] = 0;
@@ -593,20 +629,20 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const uint32_t n_quads = (n + 3u) >> 2;
-        for (uint32_t k0 = 0; k0 < n_quads; k0 += PULL4_QUADS) {
-            uint2 ent[PULL4_QUADS];
-            float wk[PULL4_QUADS];
-            uint2 ch[PULL4_QUADS];
-            bool rk[PULL4_QUADS];
-            float tv[DET ? PULL4_QUADS : 1][3];              // DET: the three columns of a recomputed row's source
+        for (uint32_t k0 = 0; k0 < n; k0 += ROWS * LOADS) {
+            uint2 ent[LOADS];
+            uint2 ch[LOADS];
+            floatx4u fr[F ? LOADS : 1];
+            bool rk[LOADS];
+            float tv[DET ? LOADS : 1][3];                    // DET: the three columns of a recomputed row's source
 #pragma unroll
-            for (int r = 0; r < PULL4_QUADS; ++r) {
-                const uint32_t idx = 4u * (k0 + r) + grp;
+            for (int r = 0; r < LOADS; ++r) {
+                const uint32_t idx = k0 + ROWS * r + grp;
                 ent[r] = s_e[wave][idx];
-                if (WT) wk[r] = s_w[wave][idx];
                 rk[r] = DET && s_r[DET ? wave : 0][DET ? idx : 0] != 0;
-                if (DET && rk[r]) {
+                if constexpr (F != 0) {
+                    fr[r] = *(const floatx4u *)(frow + (size_t)ent[r].x * a.ldd);
+                } else if (DET && rk[r]) {
                     const float *t = a.R + (size_t)(ent[r].x >> 7) * d;
                     tv[DET ? r : 0][0] = t[sub];
                     tv[DET ? r : 0][1] = t[16u + sub];
@@ -618,40 +654,44 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
                 }
             }
 #pragma unroll
-            for (int r = 0; r < PULL4_QUADS; ++r) {
-                const uint32_t k = k0 + r;
-                if (k < n_quads) {
-                    // the three columns as (integer, as a float) x (the chunk's power of two): one fused
+            for (int r = 0; r < LOADS; ++r) {
+                if (k0 + ROWS * r < n) {
+                    // packed: the three columns as (integer, as a float) x (the chunk's power of two): one fused
                     // multiply-add per column takes them into the sums (the product is exact)
-                    float q0, q1, q2, f;
-                    rp_msg_decode_parts(ch[r], q0, q1, q2, f);
-                    if (DET && rk[r]) {
-                        q0 = tv[DET ? r : 0][0];
-                        q1 = tv[DET ? r : 0][1];
-                        q2 = tv[DET ? r : 0][2];
-                        f = 1.0f;
-                    }
-                    if (WT) f *= wk[r];                      // a power of two times the weight: exact
-                    if (!__any(ent[r].y != cur)) {           // the whole quad goes on
-                        acc0 = __builtin_fmaf(q0, f, acc0);
-                        acc1 = __builtin_fmaf(q1, f, acc1);
-                        acc2 = __builtin_fmaf(q2, f, acc2);
-                    } else {                                 // entry by entry (they are sorted by destination)
+                    float q[V], f = 1.0f;
+                    const float wk = WT ? s_w[wave][k0 + ROWS * r + grp] : 1.0f;   // (read again here: registers)
+                    if constexpr (F != 0) {
 #pragma unroll
-                        for (uint32_t g = 0; g < 4u; ++g) {
-                            const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)ent[r].y, 16 * (int)g);
-                            if (vg != PULL4_PAD) {
-                                if (vg != cur) {
-                                    if (cur != NONE) flush();
-                                    cur = vg;
-                                    if (DET) cur_rec = __builtin_amdgcn_readlane((int)rk[r], 16 * (int)g) != 0;
-                                }
-                                if (grp == g) {
-                                    acc0 = __builtin_fmaf(q0, f, acc0);
-                                    acc1 = __builtin_fmaf(q1, f, acc1);
-                                    acc2 = __builtin_fmaf(q2, f, acc2);
-                                }
+                        for (int j = 0; j < V; ++j) q[j] = fr[r][j];
+                        f = wk;
+                    } else {
+                        rp_msg_decode_parts(ch[r], q[0], q[1], q[2], f);
+                        if (DET && rk[r]) {
+#pragma unroll
+                            for (int j = 0; j < V; ++j) q[j] = tv[DET ? r : 0][j];
+                            f = 1.0f;
+                        }
+                        if (WT) f *= wk;                     // a power of two times the weight: exact
+                    }
+                    auto add = [&]() {
+#pragma unroll
+                        for (int j = 0; j < V; ++j) acc[j] = (F && !WT) ? acc[j] + q[j] : __builtin_fmaf(q[j], f, acc[j]);
+                    };
+                    if (!__any(ent[r].y != cur)) {           // all of them go on
+                        add();
+                    } else {                                 // destination by destination (they are in order)
+                        unsigned long long left = __ballot(ent[r].y != PULL4_PAD);
+                        while (left) {
+                            const int first = __ffsll((long long)left) - 1;
+                            const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)ent[r].y, first);
+                            if (vg != cur) {
+                                if (cur != NONE) flush();
+                                cur = vg;
+                                if (DET) cur_rec = __builtin_amdgcn_readlane((int)rk[r], first) != 0;
                             }
+                            const bool same = ent[r].y == vg;
+                            if (same) add();
+                            left &= ~__ballot(same);
                         }
                     }
                 }
@@ -686,9 +726,9 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
         for (; run < a.side_runs; run += nw) a.side_v[2 * run] = a.side_v[2 * run + 1] = NONE;
 }
 
-// The list of a hop's messages (see k_scatter_list) where they are packed rows: four at a time, 16 lanes each, like k_scatter_pull4. The
+// The list of a hop's messages (see k_scatter_list) where they are packed rows or rows of up to 64 floats: several at a time, like k_scatter_pull4. The
 // destination's row, if no other run has pairs of it, is read with its first message and stored with the sum.
-template <int WT>
+template <int F, int WT>
 __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
     uint32_t M;
     bool made;
@@ -697,33 +737,30 @@ __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
     if (!used) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_SORTED;
     constexpr uint32_t NONE = 0xFFFFFFFFu;
+    constexpr int LANES = RowForm<F>::LANES, ROWS = RowForm<F>::ROWS, LOADS = RowForm<F>::LOADS, V = RowForm<F>::V;
     const int lane = rp_lane();
-    const uint32_t d = a.d, grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
+    const uint32_t d = a.d, grp = (uint32_t)lane / LANES, sub = (uint32_t)lane & (LANES - 1u);
     const uint32_t n_chunks = (M + 63u) / 64u;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t per = (n_chunks + nw - 1) / nw;
     const uint32_t c_begin = min(n_chunks, gw * per), c_end = min(n_chunks, c_begin + per);
     if (c_begin >= c_end) return;
     const __amdgpu_buffer_rsrc_t mres = __builtin_amdgcn_make_buffer_rsrc((void *)a.D, 0, a.msg_bytes, 0x00020000u);
-    const uint32_t my_col = 16u * grp + sub;                // the column this lane sends to memory
-    const bool sends = grp < 3u && my_col < d, has2 = 32u + sub < d;
+    const uint32_t col0 = 4u * sub < d ? 4u * sub : 0u;      // rows of floats: lanes beyond the row repeat its first columns
+    const uint32_t my_col = row_column<F>((uint32_t)lane);        // the column this lane sends to memory
+    const bool sends = my_col < d, has2 = 32u + sub < d;
     const uint32_t v_first = a.sorted[c_begin * 64u].x, v_last = a.sorted[min(M, c_end * 64u) - 1u].x;
     uint32_t cur = NONE;
-    float acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;            // this group's partial sums of columns sub, 16 + sub, 32 + sub
+    float acc[V];                                           // this group's partial sums
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[j] = 0.0f;
     auto flush = [&]() {
-        acc0 += __shfl_xor(acc0, 16);
-        acc1 += __shfl_xor(acc1, 16);
-        acc2 += __shfl_xor(acc2, 16);
-        acc0 += __shfl_xor(acc0, 32);
-        acc1 += __shfl_xor(acc1, 32);
-        acc2 += __shfl_xor(acc2, 32);
-        const float mine = grp == 0u ? acc0 : (grp == 1u ? acc1 : acc2);
+        const float mine = rows_sum<F>(acc);
         if (sends) {
             float *x = &a.X[(size_t)cur * d + my_col];
             if (cur != v_first && cur != v_last) *x = mine;
             else if (mine != 0.0f) unsafeAtomicAdd(x, mine);
         }
-        acc0 = acc1 = acc2 = 0.0f;
     };
     uint32_t e = c_begin * 64u + lane;
     uint2 nx = (e < M) ? a.sorted[e] : make_uint2(PULL4_PAD, 0u);
@@ -741,49 +778,61 @@ __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
         left = lane == 0 ? before : left;
         const uint32_t first = my.x != left && my.x != v_first && my.x != v_last && my.x != PULL4_PAD ? 1u : 0u;
         before = (uint32_t)__shfl((int)my.x, 63);
-        for (uint32_t k0 = 0; k0 < n; k0 += 4u * PULL4_QUADS) {
-            uint32_t v[PULL4_QUADS];
-            uint2 ch[PULL4_QUADS];
-            float x[PULL4_QUADS][3], wk[PULL4_QUADS];
+        for (uint32_t k0 = 0; k0 < n; k0 += ROWS * LOADS) {
+            uint32_t v[LOADS];
+            uint2 ch[LOADS];
+            floatx4u fr[F ? LOADS : 1];
+            float x[LOADS][V], wk[LOADS];
 #pragma unroll
-            for (int r = 0; r < PULL4_QUADS; ++r) {
-                const int idx = (int)(k0 + 4u * r + grp);    // below 64; past the list's end: row 0, no destination
+            for (int r = 0; r < LOADS; ++r) {
+                const int idx = (int)(k0 + ROWS * r + grp);  // below 64; past the list's end: row 0, no destination
                 const uint32_t u = (uint32_t)__shfl((int)my.y, idx);
                 v[r] = (uint32_t)__shfl((int)my.x, idx);
                 wk[r] = WT ? __shfl(my_w, idx) : 1.0f;
                 const bool own = __shfl((int)first, idx) != 0;
-                const uintx2 w2 = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(mres, (u << 7) + 8u * sub, 0, 0));
-                ch[r] = make_uint2(w2.x, w2.y);
-                const float *xr = a.X + (size_t)v[r] * d + sub;
-                x[r][0] = own ? xr[0] : 0.0f;
-                x[r][1] = own ? xr[16] : 0.0f;
-                x[r][2] = own && has2 ? xr[32] : 0.0f;
+                if constexpr (F != 0) {
+                    fr[r] = *(const floatx4u *)(a.D + (size_t)u * a.ldd + col0);
+                    floatx4u old = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if (own) old = *(const floatx4u *)(a.X + (size_t)v[r] * d + col0);
+#pragma unroll
+                    for (int j = 0; j < V; ++j) x[r][j] = old[j];
+                } else {
+                    const uintx2 w2 = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(mres, (u << 7) + 8u * sub, 0, 0));
+                    ch[r] = make_uint2(w2.x, w2.y);
+                    const float *xr = a.X + (size_t)v[r] * d + sub;
+                    x[r][0] = own ? xr[0] : 0.0f;
+                    x[r][1] = own ? xr[16] : 0.0f;
+                    x[r][2] = own && has2 ? xr[32] : 0.0f;
+                }
             }
 #pragma unroll
-            for (int r = 0; r < PULL4_QUADS; ++r) {
-                if (k0 + 4u * r >= n) continue;
-                float q0, q1, q2, f;
-                rp_msg_decode_parts(ch[r], q0, q1, q2, f);
-                if (WT) f *= wk[r];                          // a power of two times the weight: exact
-                if (!__any(v[r] != cur)) {                   // the whole quad goes on
-                    acc0 = __builtin_fmaf(q0, f, acc0);
-                    acc1 = __builtin_fmaf(q1, f, acc1);
-                    acc2 = __builtin_fmaf(q2, f, acc2);
-                } else {                                     // pair by pair
+            for (int r = 0; r < LOADS; ++r) {
+                if (k0 + ROWS * r >= n) continue;
+                float q[V], f;
+                if constexpr (F != 0) {
 #pragma unroll
-                    for (uint32_t g = 0; g < 4u; ++g) {
-                        const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)v[r], 16 * (int)g);
-                        if (vg != PULL4_PAD) {
-                            if (vg != cur) {
-                                if (cur != NONE) flush();
-                                cur = vg;
-                            }
-                            if (grp == g) {                  // (x is zero but for an unshared destination's first message)
-                                acc0 += __builtin_fmaf(q0, f, x[r][0]);
-                                acc1 += __builtin_fmaf(q1, f, x[r][1]);
-                                acc2 += __builtin_fmaf(q2, f, x[r][2]);
-                            }
+                    for (int j = 0; j < V; ++j) q[j] = fr[r][j];
+                    f = wk[r];
+                } else {
+                    rp_msg_decode_parts(ch[r], q[0], q[1], q[2], f);
+                    if (WT) f *= wk[r];                      // a power of two times the weight: exact
+                }
+                if (!__any(v[r] != cur)) {                   // all of them go on
+#pragma unroll
+                    for (int j = 0; j < V; ++j) acc[j] = __builtin_fmaf(q[j], f, acc[j]);
+                } else {                                     // destination by destination
+                    unsigned long long left = __ballot(v[r] != PULL4_PAD);
+                    while (left) {
+                        const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)v[r], __ffsll((long long)left) - 1);
+                        if (vg != cur) {
+                            if (cur != NONE) flush();
+                            cur = vg;
                         }
+                        const bool same = v[r] == vg;
+                        if (same)                            // (x is zero but for an unshared destination's first message)
+#pragma unroll
+                            for (int j = 0; j < V; ++j) acc[j] += __builtin_fmaf(q[j], f, x[r][j]);
+                        left &= ~__ballot(same);
                     }
                 }
             }
@@ -904,17 +953,23 @@ void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow
         else if (wt) hipLaunchKernelGGL((k_scatter_pull<NJ, 0, 1, 0>), grid, block, 0, c->stream, a);         \
         else hipLaunchKernelGGL((k_scatter_pull<NJ, 0, 0, 0>), grid, block, 0, c->stream, a);                 \
     } while (0)
-    if (packed) {
-        if (discover && wt) hipLaunchKernelGGL((k_scatter_pull4<1, 1, 0>), grid, block, 0, c->stream, a);
-        else if (discover) hipLaunchKernelGGL((k_scatter_pull4<1, 0, 0>), grid, block, 0, c->stream, a);
-        else if (wt) hipLaunchKernelGGL((k_scatter_pull4<0, 1, 0>), grid, block, 0, c->stream, a);
-        else hipLaunchKernelGGL((k_scatter_pull4<0, 0, 0>), grid, block, 0, c->stream, a);
-    } else if (a.d <= 64) PULL_CASE(1);
+#define PULL4_CASE(F)                                                                                      \
+    do {                                                                                                   \
+        if (discover && wt) hipLaunchKernelGGL((k_scatter_pull4<F, 1, 1, 0>), grid, block, 0, c->stream, a);  \
+        else if (discover) hipLaunchKernelGGL((k_scatter_pull4<F, 1, 0, 0>), grid, block, 0, c->stream, a);   \
+        else if (wt) hipLaunchKernelGGL((k_scatter_pull4<F, 0, 1, 0>), grid, block, 0, c->stream, a);         \
+        else hipLaunchKernelGGL((k_scatter_pull4<F, 0, 0, 0>), grid, block, 0, c->stream, a);                 \
+    } while (0)
+    if (packed) PULL4_CASE(0);
+    else if (a.d <= 16) PULL4_CASE(4);
+    else if (a.d <= 32) PULL4_CASE(8);
+    else if (a.d <= 64) PULL4_CASE(16);
     else if (a.d <= 128) PULL_CASE(2);
     else if (a.d <= 256) PULL_CASE(4);
     else if (a.d <= 512) PULL_CASE(8);
     else PULL_CASE(16);
 #undef PULL_CASE
+#undef PULL4_CASE
 }
 
 // About a thousand messages per bucket, so that a workgroup takes most of them in one round, and at most RP_LIST_IDS vertices (graphs of more
@@ -963,14 +1018,21 @@ void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t
         if (wt) hipLaunchKernelGGL((k_scatter_list<NJ, 1>), grid, block, 0, c->stream, a);        \
         else hipLaunchKernelGGL((k_scatter_list<NJ, 0>), grid, block, 0, c->stream, a);           \
     } while (0)
-    if (packed && wt) hipLaunchKernelGGL(k_scatter_list4<1>, grid, block, 0, c->stream, a);
-    else if (packed) hipLaunchKernelGGL(k_scatter_list4<0>, grid, block, 0, c->stream, a);
-    else if (a.d <= 64) LIST_CASE(1);
+#define LIST4_CASE(F)                                                                             \
+    do {                                                                                          \
+        if (wt) hipLaunchKernelGGL((k_scatter_list4<F, 1>), grid, block, 0, c->stream, a);        \
+        else hipLaunchKernelGGL((k_scatter_list4<F, 0>), grid, block, 0, c->stream, a);           \
+    } while (0)
+    if (packed) LIST4_CASE(0);
+    else if (a.d <= 16) LIST4_CASE(4);
+    else if (a.d <= 32) LIST4_CASE(8);
+    else if (a.d <= 64) LIST4_CASE(16);
     else if (a.d <= 128) LIST_CASE(2);
     else if (a.d <= 256) LIST_CASE(4);
     else if (a.d <= 512) LIST_CASE(8);
     else LIST_CASE(16);
 #undef LIST_CASE
+#undef LIST4_CASE
 }
 
 // Deterministic mode: the hop is pulled into A_l (bootstrap: into every live vertex, all of them recomputed;
@@ -1008,7 +1070,7 @@ void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
     dim3 grid(c->n_cu * 8), block(256);
     a.side_runs = c->side_runs;
     const uint32_t n_entries = 2u * c->side_runs;           // two per run
-    if (packed) hipLaunchKernelGGL((k_scatter_pull4<0, 0, 1>), grid, block, 0, c->stream, a);
+    if (packed) hipLaunchKernelGGL((k_scatter_pull4<0, 0, 0, 1>), grid, block, 0, c->stream, a);
     else if (a.d <= 64) hipLaunchKernelGGL((k_scatter_pull<1, 0, 0, 1>), grid, block, 0, c->stream, a);
     else if (a.d <= 128) hipLaunchKernelGGL((k_scatter_pull<2, 0, 0, 1>), grid, block, 0, c->stream, a);
     else if (a.d <= 256) hipLaunchKernelGGL((k_scatter_pull<4, 0, 0, 1>), grid, block, 0, c->stream, a);
