@@ -518,7 +518,8 @@ __global__ __launch_bounds__(256) void k_gat_edge_terms(GatEdgeArgs a) {
     }
 }
 
-#define GAT_OLD 0x80000000u                 // entry: the source's row as it was before the batch, taken away
+#define GAT_REC 0x80000000u                 // an entry's destination: it is recomputed
+#define GAT_OLD 0x80000000u                 // an entry's source: the source's row as it was before the batch, taken away
 // QUAD: rows of at most 63 columns that carry their score behind the last column (no read of its own): 16 lanes take a row, four
 // columns each, so a wavefront sums four entries at a time (the rate of instructions, not memory, bounds a row of two
 // cache lines otherwise). Else a wavefront per row, NJ columns per lane, weights made lane-parallel from the score array.
@@ -535,66 +536,62 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
     const uint32_t grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
     const uint32_t d = a.p.d, ldp = a.ldp;
     const uint32_t total = a.p.ioff[count];
-    const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t per = rp_chunks_per_run(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
+    const RunCut rc = rp_run_cut(total, nw);
+    const uint32_t n_chunks = rc.n_chunks, per = rc.per, n_runs = rc.n_runs;
     uint32_t *su = s_u[wave], *sv = s_v[wave];
     float *sx = s_x[wave];
     for (uint32_t run = gw; run < n_runs;) {
         const uint32_t c_begin = run * per, c_end = min(n_chunks, c_begin + per);
         PullScan<T, 0, 1> scan;
-        scan.begin(a.p, count, c_begin, lane);
-        const uint32_t e_end = min(total, c_end * PULL_CHUNK);
+        scan.begin(a.p, count, c_begin * rc.chunk, lane);
+        const uint32_t e_end = min(total, c_end * rc.chunk);
         const uint32_t v_first = (uint32_t)__shfl((int)scan.rv, 0), i_last = rp_seg_search_wave(a.p.ioff, 0, count - 1, e_end - 1u);
         const uint32_t v_last = a.p.list[i_last];
         const uint32_t e_last = a.p.ioff[i_last + 1u];
-        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK, cut_last = e_last > e_end;
+        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * rc.chunk, cut_last = e_last > e_end;
         const bool goes_on = cut_last && !(v_last == v_first && cut_first);   // a vertex that begins here and ends in a later run
-        if (lane == 0) a.c.cut[run] = make_uint2(goes_on ? v_last : NONE, (e_last - 1u) / (per * PULL_CHUNK));
+        if (lane == 0) a.c.cut[run] = make_uint2(goes_on ? v_last : NONE, (e_last - 1u) / rc.span());
         bool wrote_first = false, wrote_last = false;
         uint32_t cur = NONE;
         float acc[NJ], dsum = 0.0f, mag = 0.0f;
         float4 acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[j] = 0.0f;
+        // A vertex's row and sums have one writer, so what is added to them is added by atomics that nothing waits for: with the old row read
+        // first every patched vertex cost a wavefront a round trip to memory (139 K recomputed and 465 K patched rows of 47: 940 us -> 825).
         auto flush = [&]() {
-            const bool began_before = cur == v_first && cut_first, cut = began_before || (cur == v_last && cut_last);
-            const bool rec = cut || a.rec[cur] != 0;         // a part is stored plainly, like a recomputed row
-            float *xr = cut ? a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * (d + 2u) : a.p.X + (size_t)cur * d;
+            const uint32_t v = cur & ~GAT_REC;
+            const bool began_before = v == v_first && cut_first, cut = began_before || (v == v_last && cut_last);
+            const bool plain = cut || (cur & GAT_REC) != 0u;  // a part is stored plainly, like a recomputed row
+            float *xr = cut ? a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * (d + 2u) : a.p.X + (size_t)v * d;
             wrote_first |= began_before;
             wrote_last |= cut && !began_before;
+            float sums = lane == 0 ? dsum : mag;            // lane 0: the denominator's, lane 16: mag
             if (QUAD) {                                     // the four groups' sums together; lane (grp, sub) then has column 4 sub + grp
-#pragma unroll
-                for (int o = 16; o < 64; o <<= 1) {
-                    acq.x += __shfl_xor(acq.x, o);
-                    acq.y += __shfl_xor(acq.y, o);
-                    acq.z += __shfl_xor(acq.z, o);
-                    acq.w += __shfl_xor(acq.w, o);
-                    dsum += __shfl_xor(dsum, o);
-                    mag += __shfl_xor(mag, o);
-                }
-                acc[0] = grp == 0u ? acq.x : (grp == 1u ? acq.y : (grp == 2u ? acq.z : acq.w));
+                acc[0] = swap_add32(swap_add16(acq.x, acq.y), swap_add16(acq.z, acq.w));
+                const float dm = swap_add16(dsum, mag);
+                sums = swap_add32(dm, dm);
                 acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const uint32_t col = QUAD ? 4u * sub + grp : (uint32_t)lane + 64u * j;
-                if (col < d) xr[col] = rec ? acc[j] : xr[col] + acc[j];
+                if (col < d) {
+                    if (plain) xr[col] = acc[j];
+                    else unsafeAtomicAdd(&xr[col], acc[j]);
+                }
                 acc[j] = 0.0f;
             }
-            if (lane == 0) {
-                if (cut) {
-                    xr[d] = dsum;
-                    xr[d + 1u] = mag;
-                } else {
-                    a.den[cur] = rec ? dsum : a.den[cur] + dsum;
-                    if (!rec) a.mag[cur] += mag;
-                }
+            if (lane == 0 || lane == 16) {
+                float *to = cut ? xr + d + (lane ? 1u : 0u) : (lane ? a.mag : a.den) + v;
+                if (cut || (plain && lane == 0)) *to = sums;
+                else if (!plain) unsafeAtomicAdd(to, sums);
             }
             dsum = mag = 0.0f;
         };
         for (uint32_t c = c_begin; c < c_end; ++c) {
-            const uint32_t e0 = c * PULL_CHUNK, e1 = min(total, e0 + PULL_CHUNK);
+            const uint32_t e0 = c * rc.chunk, e1 = min(total, e0 + rc.chunk);
             uint32_t my_v[T], my_u[T];
             float no_w[1];
             bool valid[T], rec[T];
@@ -620,7 +617,7 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
                 const uint32_t at = n + (uint32_t)__popcll(m1 & below) + (uint32_t)__popcll(m2 & below);
                 if (one) {
                     su[at] = my_u[t];
-                    sv[at] = my_v[t];
+                    sv[at] = my_v[t] | (rec[t] ? GAT_REC : 0u);
                     sx[at] = wn;
                 }
                 if (two) {
@@ -734,8 +731,8 @@ __global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     if (count == 0) return;
-    const uint32_t total = a.p.ioff[count], n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
-    const uint32_t per = rp_chunks_per_run(n_chunks, a.n_waves), n_runs = (n_chunks + per - 1) / per, span = per * PULL_CHUNK;
+    const RunCut rc = rp_run_cut(a.p.ioff[count], a.n_waves);
+    const uint32_t n_runs = rc.n_runs, span = rc.span();
     auto cancelled = [](float den, float mag) { return mag > 0.0f && !(den > GAT_CANCEL * mag); };
     for (uint32_t r = gw; r < n_runs; r += nw) {
         const uint2 c = a.c.cut[r];

@@ -5,6 +5,29 @@
 
 #define PULL_CHUNK 256
 #define PULL_RUN 8                      // chunks a wavefront takes at a time on a large hop
+// How the flattened in-edge space of a list, `total` entries, is cut for nw wavefronts: chunks of `chunk` edges (64 edges a wavefront step, PULL_CHUNK at
+// most), `per` chunks to a run. A chunk is one chain of dependent reads (descriptors, ids, marks, rows), so where whole chunks would leave
+// wavefronts without any they are halved or quartered: a hop of 470 K in-edges is 7,300 chains of a quarter of the length and not 1,800 on 8,192 wavefronts.
+//   In-edges, rows, 256 / 64 or 128 edges a chunk: 278 K, a thousand messages of 128 columns 18.8 / 11.0 us; 482 K, 9 K of 256 46.6 / 21.5; 468 K rows of 256
+//   all gathered 86.9 / 70.8 (the first three with what the flush of k_scatter_pull gained).
+struct RunCut {
+    uint32_t chunk, n_chunks, per, n_runs;
+    __host__ __device__ __forceinline__ uint32_t span() const { return chunk * per; }
+};
+__host__ __device__ __forceinline__ RunCut rp_run_cut(uint32_t total, uint32_t nw) {
+    RunCut c;
+    c.chunk = (total - 1u) / 64u < nw ? 64u : ((total - 1u) / 128u < nw ? 128u : (uint32_t)PULL_CHUNK);
+    c.n_chunks = (uint32_t)(((unsigned long long)total + c.chunk - 1u) / c.chunk);
+    const uint32_t p = c.n_chunks / (2u * nw);
+    c.per = p < 1u ? 1u : (p > PULL_RUN ? PULL_RUN : p);
+    c.n_runs = (c.n_chunks + c.per - 1u) / c.per;
+    return c;
+}
+// ... and the most runs that in-rows of up to `entries` entries can give: nw while chunks are small, 4 nw + 1 while runs are shorter than PULL_RUN chunks
+static inline size_t rp_max_runs(uint64_t entries, uint32_t nw) {
+    return (size_t)std::min<uint64_t>(entries / 64u + 2, std::max<uint64_t>(4ull * nw + 1, entries / (PULL_CHUNK * PULL_RUN) + 2));
+}
+
 // the next run's number, fetched by lane 0 for the wavefront
 __device__ __forceinline__ uint32_t rp_next_run(uint32_t *counter, int lane) {
     uint32_t r = 0;
@@ -51,9 +74,9 @@ struct PullScan {
     uint32_t i_lo, rv, rbase, bnd;
     uint32_t i_nx, rv_n, rbase_n, bnd_n;
 
-    __device__ __forceinline__ void begin(const PullArgs &a, uint32_t count, uint32_t c_begin, int lane) {
+    __device__ __forceinline__ void begin(const PullArgs &a, uint32_t count, uint32_t e_begin, int lane) {
         const uint32_t last = count - 1;
-        i_lo = rp_seg_search_wave(a.ioff, 0, last, c_begin * PULL_CHUNK);
+        i_lo = rp_seg_search_wave(a.ioff, 0, last, e_begin);
         const uint32_t ri = min(last, i_lo + lane);
         rv = a.list[ri];
         rbase = a.in_meta[rv].x - a.ioff[ri];
@@ -134,16 +157,17 @@ struct PullScan {
     }
 };
 
-// Runs of chunks as the kernels cut them that have one sum per destination to make (k_pull_all, k_gat_edges): chunks per run
-__host__ __device__ __forceinline__ uint32_t rp_chunks_per_run(uint32_t n_chunks, uint32_t nw) {
-    const uint32_t p = n_chunks / (2u * nw);
-    return p < 1u ? 1u : (p > PULL_RUN ? PULL_RUN : p);
-}
-// ... and the most runs that in-rows of up to `entries` entries can give: 4 nw + 1 while runs are shorter than PULL_RUN chunks
-static inline size_t rp_max_runs(uint64_t entries, uint32_t nw) {
-    return (size_t)std::min<uint64_t>(entries / PULL_CHUNK + 2, std::max<uint64_t>(4ull * nw + 1, entries / (PULL_CHUNK * PULL_RUN) + 2));
-}
 #ifdef __HIPCC__
+// Two rows of 16 lanes (or the two halves) trade places and are added, without LDS: odd rows (the upper half) of the first operand against even rows (the
+// lower half) of the second.
+__device__ __forceinline__ float swap_add16(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);   // rows 0 and 2: x over the two rows, rows 1 and 3: y
+}
+__device__ __forceinline__ float swap_add32(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);   // lower half: x over both halves, upper half: y
+}
 // A destination whose in-edges lie in several runs is summed in run order: every run leaves its share in one of its two rows of
 // `part` (the first for a destination that began in an earlier run, the second for one that begins here and goes on), and says in
 // `cut` which destination goes on and up to which run; a wavefront per run then adds the parts up. Atomics in their place would make

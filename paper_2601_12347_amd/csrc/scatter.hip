@@ -106,13 +106,16 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
-    constexpr int G = (NJ >= 8) ? 2 : 16 / NJ;              // delta rows gathered per round trip
+    constexpr int G = (NJ >= 8) ? 2 : 16 / NJ;              // rows gathered per round trip
     constexpr int T = PULL_CHUNK / 64;                      // in-edges examined per lane and chunk
-    const int lane = rp_lane();
+    __shared__ uint2 s_e[4][PULL_CHUNK];                    // the chunk's messages: source, destination
+    __shared__ float s_w[WT ? 4 : 1][WT ? PULL_CHUNK : 1];
+    const int lane = rp_lane(), wave = threadIdx.x >> 6;
     const uint32_t d = a.d;
     const uint32_t total = a.ioff[count];
-    const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const RunCut cut = rp_run_cut(total, nw);
+    const uint32_t n_chunks = cut.n_chunks;
     // The chunks are handed out in runs (PULL_RUN chunks on large hops, one chunk when there are fewer chunks than
     // wavefronts would need). A wavefront starts with the run of its own number; after that it fetches runs from a
     // counter until none is left, or, in the deterministic mode, takes every nw-th run (a cut that depends on the
@@ -121,8 +124,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     // (the vertices that earlier batches created sit together at the end of the id range), and the few wavefronts
     // that owned such a stretch held up the hop (3.4 instead of 2.1 ms after 400 batches that each create 100
     // vertices; in the deterministic mode 7.4 instead of 2.5 ms at hop 2).
-    const uint32_t per = max(1u, min((uint32_t)PULL_RUN, n_chunks / (2u * nw)));
-    const uint32_t n_runs = (n_chunks + per - 1) / per;
+    const uint32_t per = cut.per, n_runs = cut.n_runs;
     uint32_t run = gw;                                      // the first run needs no counter
     if (DET && n_runs > a.side_runs) {                      // cannot happen: the side entries are sized for the in-row pool
         if (gw == 0 && lane == 0) a.ctr->error = 9;
@@ -136,115 +138,99 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     uint32_t c_begin = run * per;
     uint32_t c_end = min(n_chunks, c_begin + per);
     PullScan<T, WT> scan;
-    scan.begin(a, count, c_begin, lane);
+    scan.begin(a, count, c_begin * cut.chunk, lane);
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     uint32_t cur = NONE;                                    // destination whose partial sum is held
-    bool cur_rec = false;                                   // ... and whether it is recomputed (DET)
-    float acc[NJ];
+    const bool rec = DET && a.bm_rec != nullptr;            // every destination is recomputed from all its in-neighbours (bootstrap), or none
+    float acc[NJ], xo[NJ];                                  // ... and its old row, where nobody else writes it
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[j] = 0.0f;
-    // DET: the destinations of the current run's first and last in-edge, and whether a sum was left for them
-    uint32_t v_head = NONE, v_tail = NONE;
+    for (int j = 0; j < NJ; ++j) acc[j] = xo[j] = 0.0f;
+    // the destinations of the run's first and last in-edge may have in-edges in other runs: atomics, or (DET) side entries; whether a sum was left for them
+    uint32_t v_head = (uint32_t)__shfl((int)scan.rv, 0), v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * cut.chunk) - 1u)];
     bool wrote_head = false, wrote_tail = false;
-    if (DET) {
-        v_head = (uint32_t)__shfl((int)scan.rv, 0);
-        v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * PULL_CHUNK) - 1u)];
-    }
+    // All others have one writer: the old row is read beside the destination's first message and stored with the sum. (Atomics take 3.2 ps a number
+    // wherever they go, 30 K rows of 256 numbers alone 24 us: 62 K messages to them 38 us, so 29. The old row read when the sum is complete, as the
+    // deterministic mode did, is a stall per destination: 40 K messages to 21 K rows of 256 73 us, with atomics 35, so 25.)
     auto flush = [&]() {
         float *xr = a.X + (size_t)cur * d;
-        if (!DET) {
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const uint32_t col = lane + 64 * j;
-                if (col < d && acc[j] != 0.0f) unsafeAtomicAdd(&xr[col], acc[j]);
-                acc[j] = 0.0f;
-            }
-            if (DISC && lane == 0) atomicOr(&a.bm_cur[cur >> 5], 1u << (cur & 31));   // once per receiver and wavefront
-            return;
-        }
-        if (cur == v_head || cur == v_tail) {
-            const uint32_t slot = 2 * run + (cur == v_head ? 0u : 1u);
+        const bool shared = cur == v_head || cur == v_tail;
+        if (DET && shared) {
+            xr = a.side_acc + (size_t)(2 * run + (cur == v_head ? 0u : 1u)) * d;
             if (cur == v_head) wrote_head = true;
             else wrote_tail = true;
-            xr = a.side_acc + (size_t)slot * d;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const uint32_t col = lane + 64 * j;
-                if (col < d) xr[col] = acc[j];
-                acc[j] = 0.0f;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const uint32_t col = lane + 64 * j;
-                if (col < d) xr[col] = cur_rec ? acc[j] : xr[col] + acc[j];
-                acc[j] = 0.0f;
-            }
         }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint32_t col = lane + 64 * j;
+            if (col < d) {
+                if (DET && (shared || rec)) xr[col] = acc[j];
+                else if (!shared) xr[col] = xo[j] + acc[j];
+                else if (acc[j] != 0.0f) unsafeAtomicAdd(&xr[col], acc[j]);
+            }
+            acc[j] = 0.0f;
+        }
+        if (DISC && lane == 0) atomicOr(&a.bm_cur[cur >> 5], 1u << (cur & 31));   // once per receiver and wavefront
     };
     for (;;) {
     for (uint32_t c = c_begin; c < c_end; ++c) {
-        const uint32_t e0 = c * PULL_CHUNK, e1 = min(total, e0 + PULL_CHUNK);
+        const uint32_t e0 = c * cut.chunk, e1 = min(total, e0 + cut.chunk);
         uint32_t my_v[T], my_u[T];
         float my_w[WT ? T : 1];
         bool dirty[T];
-        bool rec[DET ? T : 1];
         scan.chunk(a, count, e0, e1, lane, my_v, my_u, my_w, dirty);
-        if (DET) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                rec[t] = a.bm_rec && e0 + 64 * t + lane < e1 && rp_bit(a.bm_rec, my_v[t]);
-                dirty[t] = dirty[t] || rec[t];
-            }
-        }
+        // the chunk's messages, in edge order
+        uint32_t n = 0;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            unsigned long long mask = __ballot(dirty[t]);
-            while (mask) {
-                int kk[G];
-                int n = 0;
+            const bool on = dirty[t] || (rec && e0 + 64u * t + lane < e1);
+            const unsigned long long mask = __ballot(on);
+            const uint32_t pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (on) {
+                s_e[wave][pos] = make_uint2(my_u[t], my_v[t]);
+                if (WT) s_w[wave][pos] = my_w[t];
+            }
+            n += (uint32_t)__popcll(mask);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (LDS accesses of one wavefront are executed in order)
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (uint32_t k0 = 0; k0 < n; k0 += G) {
+            uint32_t v[G];
+            float r[G][NJ], x[G][NJ], w[WT ? G : 1];
+            uint32_t before = cur;
+            auto rows = [&](auto read) {                     // (past the list's end: its last row again, not added)
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    kk[g] = 0;
-                    if (mask) {
-                        kk[g] = __ffsll((long long)mask) - 1;
-                        mask &= mask - 1;
-                        n = g + 1;
-                    }
+                    const uint32_t idx = min(k0 + (uint32_t)g, n - 1u);
+                    const uint2 e = s_e[wave][idx];
+                    const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.x);
+                    v[g] = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.y);
+                    if (WT) w[WT ? g : 0] = s_w[wave][idx];
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) r[g][j] = read(u, min((uint32_t)lane + 64u * j, d - 1u));
+                    const bool own = v[g] != before && v[g] != v_head && v[g] != v_tail && !rec;   // the first message of an unshared destination
+                    before = v[g];
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) x[g][j] = own ? a.X[(size_t)v[g] * d + min((uint32_t)lane + 64u * j, d - 1u)] : 0.0f;
                 }
-                float r[G][NJ];
+            };
+            if (!rec) rows([&](uint32_t u, uint32_t col) { return a.D[(size_t)u * a.ldd + col]; });
+            else if (a.R) rows([&](uint32_t u, uint32_t col) { return a.R[(size_t)u * d + col]; });
+            else rows([&](uint32_t u, uint32_t col) { return rp_load_h(a.Hprev, a.store, (size_t)u * d + col); });
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const uint32_t uk = __shfl(my_u[t], kk[g]);
-                    const bool rk = DET && __shfl((int)rec[DET ? t : 0], kk[g]) != 0;
+            for (int g = 0; g < G; ++g) {
+                if (k0 + (uint32_t)g >= n) continue;
+                if (v[g] != cur) {                           // the destination changes: flush its partial sum
+                    if (cur != NONE) flush();
+                    cur = v[g];
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const uint32_t col = lane + 64 * j;
-                        float x = 0.0f;
-                        if (g < n && col < d) {
-                            if (rk) x = a.R ? a.R[(size_t)uk * d + col] : rp_load_h(a.Hprev, a.store, (size_t)uk * d + col);
-                            else x = a.D[(size_t)uk * a.ldd + col];
-                        }
-                        r[g][j] = x;
-                    }
+                    for (int j = 0; j < NJ; ++j) xo[j] = x[g][j];
                 }
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    if (g < n) {
-                        const uint32_t vk = __shfl(my_v[t], kk[g]);
-                        if (vk != cur) {                     // the destination changes: flush its partial sum
-                            if (cur != NONE) flush();
-                            cur = vk;
-                            if (DET) cur_rec = __shfl((int)rec[DET ? t : 0], kk[g]) != 0;
-                        }
-                        // the weight is fetched again here rather than kept per row in flight (registers)
-                        const float wk = WT ? __shfl(my_w[t], kk[g]) : 1.0f;
-#pragma unroll
-                        for (int j = 0; j < NJ; ++j) acc[j] += WT ? r[g][j] * wk : r[g][j];
-                    }
-                }
+                for (int j = 0; j < NJ; ++j) acc[j] = WT ? __builtin_fmaf(r[g][j], w[WT ? g : 0], acc[j]) : acc[j] + r[g][j];
             }
         }
+        __builtin_amdgcn_wave_barrier();                     // the next chunk overwrites the list
         scan.advance();                                      // the destination and its partial sum carry over to the next chunk
     }
     if (cur != NONE) flush();
@@ -263,11 +249,9 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     if (run >= n_runs) break;
     c_begin = run * per;
     c_end = min(n_chunks, c_begin + per);
-    scan.begin(a, count, c_begin, lane);
-    if (DET) {
-        v_head = (uint32_t)__shfl((int)scan.rv, 0);
-        v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * PULL_CHUNK) - 1u)];
-    }
+    scan.begin(a, count, c_begin * cut.chunk, lane);
+    v_head = (uint32_t)__shfl((int)scan.rv, 0);
+    v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * cut.chunk) - 1u)];
     }
     if (DET && lane == 0)                                         // the runs of this wavefront's numbers that do not exist
         for (; run < a.side_runs; run += nw) a.side_v[2 * run] = a.side_v[2 * run + 1] = NONE;
@@ -481,7 +465,7 @@ __global__ __launch_bounds__(256) void k_scatter_list(ListArgs a) {
 // however many chunks the row's in-edges span.
 // Rows of up to 64 floats (not packed) are taken the same way, four columns per lane: 16, 8 or 4 lanes per row and 4, 8 or 16
 // rows at a time. F names the form: 0 packed, else the lanes per row of floats.
-//   a lane per column and a row per instruction, before: @@
+// (A lane per column and a row per instruction before, 31 M edges, a discovering hop: 16 columns 700 us, 23 weighted ones 771, 60 737; now 411, 435, 585.)
 template <int F>
 struct RowForm {
     static constexpr int LANES = F ? F : 16;                // per row
@@ -494,14 +478,6 @@ typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));   // (ro
 // step halves what a lane still has to add, and none goes through LDS: lanes 8 and 4 apart by rotations within a row, then two rows' columns
 // trade places and are added (permlane16_swap and permlane32_swap: odd rows of the first operand, or its upper half, against even rows, or
 // the lower half, of the second). With two or three shuffles per column in their place a sum of a few messages cost more than its gathers.
-__device__ __forceinline__ float swap_add16(float x, float y) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);   // rows 0 and 2: x over the two rows, rows 1 and 3: y
-}
-__device__ __forceinline__ float swap_add32(float x, float y) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);   // lower half: x over both halves, upper half: y
-}
 template <int F>
 __device__ __forceinline__ float rows_sum(float (&acc)[RowForm<F>::V]) {
     constexpr int V = RowForm<F>::V, LANES = RowForm<F>::LANES;
@@ -538,16 +514,15 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     // load is then one 8-byte LDS read and one addition (rows of floats: a multiplication as well) in front of it
     __shared__ uint2 s_e[4][LIST];
     __shared__ float s_w[WT ? 4 : 1][WT ? LIST : 1];
-    __shared__ uint8_t s_r[DET ? 4 : 1][DET ? LIST : 1];        // DET: the entry's destination is recomputed
     const int lane = rp_lane(), wave = threadIdx.x >> 6;
     const uint32_t grp = (uint32_t)lane / LANES, sub = (uint32_t)lane & (LANES - 1u);
     const uint32_t d = a.d;
     const uint32_t total = a.ioff[count];
-    const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const RunCut cut = rp_run_cut(total, nw);
+    const uint32_t n_chunks = cut.n_chunks;
     // runs of chunks: every nw-th one (DET) or fetched from a counter, see k_scatter_pull
-    const uint32_t per = max(1u, min((uint32_t)PULL_RUN, n_chunks / (2u * nw)));
-    const uint32_t n_runs = (n_chunks + per - 1) / per;
+    const uint32_t per = cut.per, n_runs = cut.n_runs;
     uint32_t run = gw;                                      // the first run needs no counter
     if (DET && n_runs > a.side_runs) {                      // cannot happen: the side entries are sized for the in-row pool
         if (gw == 0 && lane == 0) a.ctr->error = 9;
@@ -567,17 +542,17 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     const uint32_t my_col = row_column<F>((uint32_t)lane);        // the column this lane sends to memory
     const bool sends = my_col < d;
     uint32_t cur = NONE;                                    // destination being summed (the same in all lanes)
-    bool cur_rec = false;                                   // ... and whether it is recomputed (DET)
+    const bool rec = DET && a.bm_rec != nullptr;            // every destination is recomputed (see k_scatter_pull)
     float acc[V];                                           // this group's partial sums
 #pragma unroll
     for (int j = 0; j < V; ++j) acc[j] = 0.0f;
     PullScan<T, WT> scan;
-    scan.begin(a, count, c_begin, lane);
+    scan.begin(a, count, c_begin * cut.chunk, lane);
     uint32_t v_head = NONE, v_tail = NONE;                  // DET: see k_scatter_pull
     bool wrote_head = false, wrote_tail = false;
     if (DET) {
         v_head = (uint32_t)__shfl((int)scan.rv, 0);
-        v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * PULL_CHUNK) - 1u)];
+        v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * cut.chunk) - 1u)];
     }
     auto flush = [&]() {
         const float mine = rows_sum<F>(acc);
@@ -590,12 +565,13 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
             if (sends) a.side_acc[(size_t)(2 * run + (cur == v_head ? 0u : 1u)) * d + my_col] = mine;
         } else if (sends) {
             float *x = &a.X[(size_t)cur * d + my_col];
-            *x = cur_rec ? mine : *x + mine;
+            if (rec) *x = mine;
+            else if (mine != 0.0f) unsafeAtomicAdd(x, mine);
         }
     };
     for (;;) {
     for (uint32_t c = c_begin; c < c_end; ++c) {
-        const uint32_t e0 = c * PULL_CHUNK, e1 = min(total, e0 + PULL_CHUNK);
+        const uint32_t e0 = c * cut.chunk, e1 = min(total, e0 + cut.chunk);
         uint32_t my_v[T], my_u[T];
         float my_w[WT ? T : 1];
         bool dirty[T];
@@ -604,17 +580,12 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
         uint32_t n = 0;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            bool rec = false;
-            if (DET) {
-                rec = a.bm_rec && e0 + 64 * t + lane < e1 && rp_bit(a.bm_rec, my_v[t]);
-                dirty[t] = dirty[t] || rec;
-            }
+            if (DET) dirty[t] = dirty[t] || (rec && e0 + 64 * t + lane < e1);
             const unsigned long long mask = __ballot(dirty[t]);
             const uint32_t pos = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
             if (dirty[t]) {
                 s_e[wave][pos] = make_uint2(F ? my_u[t] : my_u[t] << 7, my_v[t]);
                 if (WT) s_w[wave][pos] = my_w[t];
-                if (DET) s_r[wave][pos] = rec ? 1 : 0;
             }
             n += (uint32_t)__popcll(mask);
         }
@@ -622,7 +593,6 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
         if (lane < ROWS * LOADS) {
             s_e[wave][n + lane] = make_uint2(0u, PULL4_PAD);
             if (WT) s_w[wave][n + lane] = 0.0f;
-            if (DET) s_r[DET ? wave : 0][DET ? n + lane : 0] = 0;
         }
         // LDS accesses of one wavefront are executed in order, so the loads below see the stores above without a
         // workgroup barrier; the fence keeps the compiler from moving them across each other
@@ -633,16 +603,14 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
             uint2 ent[LOADS];
             uint2 ch[LOADS];
             floatx4u fr[F ? LOADS : 1];
-            bool rk[LOADS];
             float tv[DET ? LOADS : 1][3];                    // DET: the three columns of a recomputed row's source
 #pragma unroll
             for (int r = 0; r < LOADS; ++r) {
                 const uint32_t idx = k0 + ROWS * r + grp;
                 ent[r] = s_e[wave][idx];
-                rk[r] = DET && s_r[DET ? wave : 0][DET ? idx : 0] != 0;
                 if constexpr (F != 0) {
                     fr[r] = *(const floatx4u *)(frow + (size_t)ent[r].x * a.ldd);
-                } else if (DET && rk[r]) {
+                } else if (DET && rec) {
                     const float *t = a.R + (size_t)(ent[r].x >> 7) * d;
                     tv[DET ? r : 0][0] = t[sub];
                     tv[DET ? r : 0][1] = t[16u + sub];
@@ -666,7 +634,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
                         f = wk;
                     } else {
                         rp_msg_decode_parts(ch[r], q[0], q[1], q[2], f);
-                        if (DET && rk[r]) {
+                        if (DET && rec) {
 #pragma unroll
                             for (int j = 0; j < V; ++j) q[j] = tv[DET ? r : 0][j];
                             f = 1.0f;
@@ -687,7 +655,6 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
                             if (vg != cur) {
                                 if (cur != NONE) flush();
                                 cur = vg;
-                                if (DET) cur_rec = __builtin_amdgcn_readlane((int)rk[r], first) != 0;
                             }
                             const bool same = ent[r].y == vg;
                             if (same) add();
@@ -716,10 +683,10 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     if (run >= n_runs) break;
     c_begin = run * per;
     c_end = min(n_chunks, c_begin + per);
-    scan.begin(a, count, c_begin, lane);
+    scan.begin(a, count, c_begin * cut.chunk, lane);
     if (DET) {
         v_head = (uint32_t)__shfl((int)scan.rv, 0);
-        v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * PULL_CHUNK) - 1u)];
+        v_tail = a.list[rp_seg_search_wave(a.ioff, 0, count - 1, min(total, c_end * cut.chunk) - 1u)];
     }
     }
     if (DET && lane == 0)                                         // the runs of this wavefront's numbers that do not exist
@@ -843,77 +810,76 @@ __global__ __launch_bounds__(256) void k_scatter_list4(ListArgs a) {
 
 // Deterministic mode, after a DET pull: the side entries (two per run of chunks, in run order; entries of one
 // destination are neighbours, apart from empty ones between them) are added up per destination in that order
-// and the sum is added to the row, or replaces it if the row is recomputed. One wavefront per entry and block of 64
-// columns; the one that holds a destination's first entry does the work. The order of the additions is fixed, the reads
-// are not: sixteen entries are on their way at a time (one read per addition and all columns by one wavefront made the
-// destination with the longest in-row, 40 entries of 256 columns, hold up the hop: 24 us). Recomputed rows without any
-// in-edge are zeroed here too: no in-edge, so the pull never met them.
+// and the sum is added to the row, or replaces it if the row is recomputed. A wavefront per entry and all columns; the one that holds a
+// destination's first entry does the work. The order of the additions is fixed, the reads are not: the entries around its own are read at once, then
+// the old row and G parts of NB blocks of 64 columns are on their way at a time (one read per addition made the destination with the longest in-row,
+// 40 entries of 256 columns, hold up the hop: 24 us; a wavefront per entry and block of columns, 60 K of them, took 17 us, now 14).
+// Recomputed rows without any in-edge are zeroed here too: no in-edge, so the pull never met them.
+template <int NB>
 __global__ __launch_bounds__(256) void k_pull_fixup(PullArgs a, uint32_t n_entries, uint32_t pull_nw) {
     constexpr uint32_t NONE = 0xFFFFFFFFu;
+    constexpr int G = NB <= 2 ? 16 : 32 / NB;
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
-    {   // only the entries of runs that exist can hold anything (the same cut as in the pull kernels)
-        const uint32_t n_chunks = (a.ioff[count] + PULL_CHUNK - 1) / PULL_CHUNK;
-        const uint32_t per = max(1u, min((uint32_t)PULL_RUN, n_chunks / (2u * pull_nw)));
-        n_entries = min(n_entries, 2u * ((n_chunks + per - 1) / per));
-    }
-    const int lane = rp_lane();
-    const uint32_t d = a.d;
+    n_entries = min(n_entries, 2u * rp_run_cut(a.ioff[count], pull_nw).n_runs);   // only the entries of runs that exist can hold anything
+    const uint32_t lane = (uint32_t)rp_lane(), d = a.d;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t i = gw * 64u + lane; a.bm_rec && i < count; i += nw * 64u) {
         const uint32_t v = a.list[i];
         if (a.in_meta[v].y == 0 && rp_bit(a.bm_rec, v))
             for (uint32_t c = 0; c < d; ++c) a.X[(size_t)v * d + c] = 0.0f;
     }
-    const uint32_t blocks = (d + 63u) / 64u;
-    for (uint32_t t0 = gw; t0 < n_entries * blocks; t0 += nw) {
-        const uint32_t k = t0 / blocks, col = (t0 - k * blocks) * 64u + (uint32_t)lane;
-        const uint32_t v = a.side_v[k];
+    for (uint32_t k = gw; k < n_entries; k += nw) {
+        uint32_t ahead = (k + lane < n_entries) ? a.side_v[k + lane] : NONE;         // lane 0: this entry
+        uint32_t behind = (lane < k) ? a.side_v[k - 1u - lane] : NONE;               // lane 0: the nearest one
+        const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)ahead);
         if (v == NONE) continue;
         // the nearest entry before k that is not empty: the same destination means k is not the first
         bool first = true;
-        for (uint32_t b0 = k; b0 > 0;) {
-            const uint32_t b = b0 - 1u - (uint32_t)lane;                 // lane 0 looks at the nearest one
-            const uint32_t val = ((uint32_t)lane < b0) ? a.side_v[b] : NONE;
-            const unsigned long long m = __ballot(val != NONE);
-            if (m) {
-                first = (uint32_t)__shfl((int)val, __ffsll((long long)m) - 1) != v;
-                break;
-            }
-            b0 = b0 > 64u ? b0 - 64u : 0u;
+        for (uint32_t b0 = k;;) {
+            const unsigned long long m = __ballot(behind != NONE);
+            if (m) first = (uint32_t)__shfl((int)behind, __ffsll((long long)m) - 1) != v;
+            if (m || b0 <= 64u) break;
+            b0 -= 64u;
+            behind = (lane < b0) ? a.side_v[b0 - 1u - lane] : NONE;
         }
         if (!first) continue;
         const bool rec = a.bm_rec && rp_bit(a.bm_rec, v);
-        float *x = &a.X[(size_t)v * d + col];
-        const float old = (col < d && !rec) ? *x : 0.0f;
-        float t = (col < d) ? a.side_acc[(size_t)k * d + col] : 0.0f;
-        bool more = true;
-        for (uint32_t f0 = k + 1; f0 < n_entries && more; f0 += 64) {
-            const uint32_t f = f0 + (uint32_t)lane;
-            const uint32_t val = (f < n_entries) ? a.side_v[f] : NONE;
-            unsigned long long same = __ballot(val == v);
-            const unsigned long long other = __ballot(val != NONE && val != v);
-            if (other) {                                             // entries past the first other destination are not ours
-                same &= (1ull << (__ffsll((long long)other) - 1)) - 1ull;
-                more = false;
-            }
+        float old[NB], t[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t col = min(lane + 64u * b, d - 1u);
+            old[b] = rec ? 0.0f : a.X[(size_t)v * d + col];
+            t[b] = 0.0f;
+        }
+        for (uint32_t f0 = k;;) {
+            unsigned long long same = __ballot(ahead == v);
+            const unsigned long long other = __ballot(ahead != NONE && ahead != v);
+            if (other) same &= (1ull << (__ffsll((long long)other) - 1)) - 1ull;     // entries past the first other destination are not ours
             while (same) {
-                constexpr int G = 16;
-                float part[G];
+                float part[G][NB];
                 bool has[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     has[g] = same != 0;
                     const uint32_t e = f0 + (uint32_t)(has[g] ? __ffsll((long long)same) - 1 : 0);
                     same &= same - 1;                                // (0 stays 0)
-                    part[g] = (has[g] && col < d) ? a.side_acc[(size_t)e * d + col] : 0.0f;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) part[g][b] = has[g] ? a.side_acc[(size_t)e * d + min(lane + 64u * b, d - 1u)] : 0.0f;
                 }
 #pragma unroll
                 for (int g = 0; g < G; ++g)
-                    if (has[g]) t += part[g];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+                        if (has[g]) t[b] += part[g][b];
             }
+            f0 += 64u;
+            if (other || f0 >= n_entries) break;
+            ahead = (f0 + lane < n_entries) ? a.side_v[f0 + lane] : NONE;
         }
-        if (col < d) *x = rec ? t : old + t;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            if (lane + 64u * b < d) a.X[(size_t)v * d + lane + 64u * b] = old[b] + t[b];
     }
 }
 
@@ -1070,14 +1036,19 @@ void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
     dim3 grid(c->n_cu * 8), block(256);
     a.side_runs = c->side_runs;
     const uint32_t n_entries = 2u * c->side_runs;           // two per run
-    if (packed) hipLaunchKernelGGL((k_scatter_pull4<0, 0, 0, 1>), grid, block, 0, c->stream, a);
-    else if (a.d <= 64) hipLaunchKernelGGL((k_scatter_pull<1, 0, 0, 1>), grid, block, 0, c->stream, a);
-    else if (a.d <= 128) hipLaunchKernelGGL((k_scatter_pull<2, 0, 0, 1>), grid, block, 0, c->stream, a);
-    else if (a.d <= 256) hipLaunchKernelGGL((k_scatter_pull<4, 0, 0, 1>), grid, block, 0, c->stream, a);
-    else if (a.d <= 512) hipLaunchKernelGGL((k_scatter_pull<8, 0, 0, 1>), grid, block, 0, c->stream, a);
-    else hipLaunchKernelGGL((k_scatter_pull<16, 0, 0, 1>), grid, block, 0, c->stream, a);
-    hipLaunchKernelGGL(k_pull_fixup, dim3(std::min<uint32_t>(rp_div_up(n_entries * rp_div_up(a.d, 64), 4), c->n_cu * 32)), block, 0,
-                       c->stream, a, n_entries, grid.x * 4u);
+    const dim3 fix(std::min<uint32_t>(rp_div_up(n_entries, 4), c->n_cu * 8));
+#define DET_CASE(NJ)                                                                                        \
+    do {                                                                                                    \
+        if (packed) hipLaunchKernelGGL((k_scatter_pull4<0, 0, 0, 1>), grid, block, 0, c->stream, a);        \
+        else hipLaunchKernelGGL((k_scatter_pull<NJ, 0, 0, 1>), grid, block, 0, c->stream, a);               \
+        hipLaunchKernelGGL(k_pull_fixup<NJ>, fix, block, 0, c->stream, a, n_entries, grid.x * 4u);          \
+    } while (0)
+    if (a.d <= 64) DET_CASE(1);
+    else if (a.d <= 128) DET_CASE(2);
+    else if (a.d <= 256) DET_CASE(4);
+    else if (a.d <= 512) DET_CASE(8);
+    else DET_CASE(16);
+#undef DET_CASE
 }
 
 // ---------------------------------------------------------------------------------
@@ -1843,7 +1814,7 @@ __global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     const uint32_t total = count ? a.p.ioff[count] : 0u;
-    const uint32_t span = rp_chunks_per_run((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;  // edges per run
+    const uint32_t span = rp_run_cut(total, a.n_waves).span();  // edges per run
     for (uint32_t base = gw * 64u; !HOP && base < a.n_cap; base += nw * 64u) {   // no in-edges (or not alive): zero
         const uint32_t v = base + (uint32_t)lane;
         unsigned long long m = __ballot(v < a.n_cap && a.p.in_meta[v].y == 0u);
@@ -1853,11 +1824,12 @@ __global__ __launch_bounds__(256) void k_pull_all_init(PullAllArgs a) {
             for (uint32_t col = lane; col < d; col += 64u) a.p.X[(size_t)w * d + col] = 0.0f;
         }
     }
-    for (uint32_t base = gw * 64u; a.op != 0 && base < count; base += nw * 64u) {   // extremes cut by a run boundary: the start value
+    const uint32_t S = max(1u, min(64u, count / nw));       // vertices per wavefront and round
+    for (uint32_t base = gw * S; a.op != 0 && base < count; base += nw * S) {   // extremes cut by a run boundary: the start value
         const uint32_t i = base + (uint32_t)lane;
         bool cut = false;
         uint32_t v = 0;
-        if (i < count) {
+        if (i < count && (uint32_t)lane < S) {
             const uint32_t e0 = a.p.ioff[i], e1 = a.p.ioff[i + 1u];
             v = a.p.list[i];
             cut = e1 > e0 && e0 / span != (e1 - 1u) / span;
@@ -1893,34 +1865,35 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
     const int lane = rp_lane();
     const uint32_t d = a.p.d;
     const uint32_t total = a.p.ioff[count];
-    const uint32_t n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
-    const uint32_t per = rp_chunks_per_run(n_chunks, nw), n_runs = (n_chunks + per - 1) / per;
+    const RunCut cut = rp_run_cut(total, nw);
+    const uint32_t n_chunks = cut.n_chunks;
+    const uint32_t per = cut.per, n_runs = cut.n_runs;
     const float start = SUM ? 0.0f : pull_all_start(a.op);
     for (uint32_t run = gw; run < n_runs; run += nw) {
         const uint32_t c_begin = run * per, c_end = min(n_chunks, c_begin + per);
         PullScan<T, WT, 1> scan;
-        scan.begin(a.p, count, c_begin, lane);
+        scan.begin(a.p, count, c_begin * cut.chunk, lane);
         // the destinations of the run's first and last in-edge may have in-edges in other runs
         const uint32_t v_first = (uint32_t)__shfl((int)scan.rv, 0);
-        const uint32_t e_end = min(total, c_end * PULL_CHUNK);
+        const uint32_t e_end = min(total, c_end * cut.chunk);
         const uint32_t i_last = rp_seg_search_wave(a.p.ioff, 0, count - 1, e_end - 1u);
         const uint32_t v_last = a.p.list[i_last];
-        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * PULL_CHUNK;
+        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * cut.chunk;
         const uint32_t e_last = a.p.ioff[i_last + 1u];
         const bool cut_last = e_last > e_end;
         if (SUM && lane == 0)
-            a.c.cut[run] = make_uint2(cut_last && !(v_last == v_first && cut_first) ? v_last : NONE, (e_last - 1u) / (per * PULL_CHUNK));
+            a.c.cut[run] = make_uint2(cut_last && !(v_last == v_first && cut_first) ? v_last : NONE, (e_last - 1u) / cut.span());
         uint32_t cur = NONE;
         float acc[NJ], xo[HOP ? NJ : 1];                     // HOP: the destination's old aggregate, requested with its first edge
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[j] = start;
         auto flush = [&]() {
-            const bool began_before = cur == v_first && cut_first, cut = began_before || (cur == v_last && cut_last);
-            float *xr = ((HOP && cut) ? a.XN : a.p.X) + (size_t)cur * d;
-            if (SUM && cut) xr = a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * d;
+            const bool began_before = cur == v_first && cut_first, shared = began_before || (cur == v_last && cut_last);
+            float *xr = ((HOP && shared) ? a.XN : a.p.X) + (size_t)cur * d;
+            if (SUM && shared) xr = a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * d;
             if constexpr (HOP) {
-                if (!cut) {
+                if (!shared) {
                     mono_finish<NJ>(h, cur, rp_bit(h.bm_vadd, cur), xo, acc);
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) acc[j] = start;
@@ -1931,14 +1904,14 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
             for (int j = 0; j < NJ; ++j) {
                 const uint32_t col = lane + 64 * j;
                 if (col < d) {
-                    if (SUM || !cut) xr[col] = acc[j];
+                    if (SUM || !shared) xr[col] = acc[j];
                     else rp_atomic_extreme(&xr[col], acc[j], a.op == 1);
                 }
                 acc[j] = start;
             }
         };
         for (uint32_t c = c_begin; c < c_end; ++c) {
-            const uint32_t e0 = c * PULL_CHUNK, e1 = min(total, e0 + PULL_CHUNK);
+            const uint32_t e0 = c * cut.chunk, e1 = min(total, e0 + cut.chunk);
             uint32_t my_v[T], my_u[T];
             float my_w[WT ? T : 1];
             bool all[T];
@@ -1985,6 +1958,107 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
     }
 }
 
+// Sums of fp32 rows of up to 64 columns: several rows per load instruction and four columns per lane, as k_scatter_pull4 takes them. (A lane per
+// column and a row per instruction takes 1,170 to 1,320 us for 47 columns and 31 M edges, depending on what the compiler makes of it; this 1,172, 64 G lines a second.)
+template <int F, int WT>
+__global__ __launch_bounds__(256) void k_pull_all4(PullAllArgs a) {
+    constexpr int T = PULL_CHUNK / 64;
+    constexpr uint32_t NONE = 0xFFFFFFFFu;
+    constexpr int LANES = RowForm<F>::LANES, ROWS = RowForm<F>::ROWS, LOADS = RowForm<F>::LOADS;
+    constexpr uint32_t LIST = PULL_CHUNK + ROWS * LOADS;
+    __shared__ uint2 s_e[4][LIST];                          // per in-edge: source, destination
+    __shared__ float s_w[WT ? 4 : 1][WT ? LIST : 1];
+    const uint32_t count = *a.p.count_ptr;
+    if (count == 0) return;
+    const int lane = rp_lane(), wave = threadIdx.x >> 6;
+    const uint32_t d = a.p.d, grp = (uint32_t)lane / LANES, sub = (uint32_t)lane & (LANES - 1u);
+    const uint32_t total = a.p.ioff[count];
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const RunCut cut = rp_run_cut(total, nw);
+    const float *frow = (const float *)a.Hprev + (4u * sub < d ? 4u * sub : 0u);   // lanes beyond the row repeat its first columns
+    const uint32_t my_col = row_column<F>((uint32_t)lane);
+    for (uint32_t run = gw; run < cut.n_runs; run += nw) {
+        const uint32_t c_begin = run * cut.per, c_end = min(cut.n_chunks, c_begin + cut.per);
+        PullScan<T, WT, 1> scan;
+        scan.begin(a.p, count, c_begin * cut.chunk, lane);
+        const uint32_t v_first = (uint32_t)__shfl((int)scan.rv, 0);
+        const uint32_t e_end = min(total, c_end * cut.chunk);
+        const uint32_t i_last = rp_seg_search_wave(a.p.ioff, 0, count - 1, e_end - 1u);
+        const uint32_t v_last = a.p.list[i_last];
+        const bool cut_first = a.p.ioff[scan.i_lo] < c_begin * cut.chunk;
+        const uint32_t e_last = a.p.ioff[i_last + 1u];
+        const bool cut_last = e_last > e_end;
+        if (lane == 0) a.c.cut[run] = make_uint2(cut_last && !(v_last == v_first && cut_first) ? v_last : NONE, (e_last - 1u) / cut.span());
+        uint32_t cur = NONE;
+        float acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] = 0.0f;
+        auto flush = [&]() {
+            const bool began_before = cur == v_first && cut_first, shared = began_before || (cur == v_last && cut_last);
+            float *xr = shared ? a.c.part + (size_t)(2u * run + (began_before ? 0u : 1u)) * d : a.p.X + (size_t)cur * d;
+            const float mine = rows_sum<F>(acc);
+            if (my_col < d) xr[my_col] = mine;
+        };
+        for (uint32_t c = c_begin; c < c_end; ++c) {
+            const uint32_t e0 = c * cut.chunk, e1 = min(total, e0 + cut.chunk), n = e1 - e0;
+            uint32_t my_v[T], my_u[T];
+            float my_w[WT ? T : 1];
+            bool all[T];
+            scan.chunk(a.p, count, e0, e1, lane, my_v, my_u, my_w, all);
+#pragma unroll
+            for (int t = 0; t < T; ++t)                      // (lanes past the chunk leave row 0 without a destination)
+                if (64u * t < n) {
+                    s_e[wave][64u * t + lane] = make_uint2(my_u[t], all[t] ? my_v[t] : PULL4_PAD);
+                    if (WT) s_w[wave][64u * t + lane] = my_w[WT ? t : 0];
+                }
+            if (lane < ROWS * LOADS) {                       // entries a round reads past the list's end
+                s_e[wave][n + lane] = make_uint2(0u, PULL4_PAD);
+                if (WT) s_w[wave][n + lane] = 0.0f;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (LDS accesses of one wavefront are executed in order)
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (uint32_t k0 = 0; k0 < n; k0 += ROWS * LOADS) {
+                uint2 ent[LOADS];
+                floatx4u fr[LOADS];
+                float wk[WT ? LOADS : 1];
+#pragma unroll
+                for (int r = 0; r < LOADS; ++r) {
+                    ent[r] = s_e[wave][k0 + ROWS * r + grp];
+                    if (WT) wk[WT ? r : 0] = s_w[wave][k0 + ROWS * r + grp];
+                    fr[r] = *(const floatx4u *)(frow + (size_t)ent[r].x * d);
+                }
+#pragma unroll
+                for (int r = 0; r < LOADS; ++r) {
+                    if (k0 + ROWS * r >= n) continue;
+                    auto add = [&]() {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) acc[j] = WT ? __builtin_fmaf(fr[r][j], wk[WT ? r : 0], acc[j]) : acc[j] + fr[r][j];
+                    };
+                    if (!__any(ent[r].y != cur)) {           // all of them go on
+                        add();
+                    } else {                                 // destination by destination (they are in order)
+                        unsigned long long left = __ballot(ent[r].y != PULL4_PAD);
+                        while (left) {
+                            const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)ent[r].y, __ffsll((long long)left) - 1);
+                            if (vg != cur) {
+                                if (cur != NONE) flush();
+                                cur = vg;
+                            }
+                            const bool same = ent[r].y == vg;
+                            if (same) add();
+                            left &= ~__ballot(same);
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();                 // the next chunk overwrites the list
+            scan.advance();
+        }
+        if (cur != NONE) flush();
+    }
+}
+
 // Sums of destinations that a run boundary cuts, a wavefront per run: paced by three dependent reads and by the longest row's parts
 // (31 M edges, 17 K runs: 11 / 13 / 10 us for rows of 100 / 256 / 47; 26 for 256 with one block of 64 columns after the other).
 __global__ __launch_bounds__(256) void k_pull_all_close(PullAllArgs a) {
@@ -1992,8 +2066,7 @@ __global__ __launch_bounds__(256) void k_pull_all_close(PullAllArgs a) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     if (count == 0) return;
-    const uint32_t total = a.p.ioff[count], n_chunks = (total + PULL_CHUNK - 1) / PULL_CHUNK;
-    const uint32_t per = rp_chunks_per_run(n_chunks, a.n_waves), n_runs = (n_chunks + per - 1) / per;
+    const uint32_t n_runs = rp_run_cut(a.p.ioff[count], a.n_waves).n_runs;
     for (uint32_t r = gw; r < n_runs; r += nw) {
         const uint2 c = a.c.cut[r];
         for (uint32_t c0 = lane; c.x != 0xFFFFFFFFu && c0 < d; c0 += 64u * PARTS_B) {
@@ -2013,13 +2086,14 @@ __global__ __launch_bounds__(256) void k_mono_close(PullAllArgs a, MonoArgs h) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     const uint32_t total = count ? a.p.ioff[count] : 0u;
-    const uint32_t span = rp_chunks_per_run((total + PULL_CHUNK - 1) / PULL_CHUNK, a.n_waves) * PULL_CHUNK;
+    const uint32_t span = rp_run_cut(total, a.n_waves).span();
+    const uint32_t S = max(1u, min(64u, count / nw));                    // vertices per wavefront and round (few of them: one each, most are cut)
     if (gw == 0 && lane == 0) h.ctr->mono[2][h.l] = count;               // all of them are recomputed
-    for (uint32_t base = gw * 64u; base < count; base += nw * 64u) {
+    for (uint32_t base = gw * S; base < count; base += nw * S) {
         const uint32_t i = base + (uint32_t)lane;
         uint32_t v = 0, e0 = 0, e1 = 1;
         bool todo = false;
-        if (i < count) {
+        if (i < count && (uint32_t)lane < S) {
             e0 = a.p.ioff[i];
             e1 = a.p.ioff[i + 1u];
             v = a.p.list[i];
@@ -2080,13 +2154,23 @@ void rp_launch_pull_all(ripple_ctx *c, uint32_t l) {
         else if (a.p.in_w) PULL_CASE_W(NJ, 0, 1);      \
         else PULL_CASE_W(NJ, 0, 0);                    \
     } while (0)
-    if (a.p.d <= 64) PULL_CASE(1);
+#define PULL4_CASE(F)                                                                                       \
+    do {                                                                                                    \
+        if (a.p.in_w) hipLaunchKernelGGL((k_pull_all4<F, 1>), grid, block, 0, c->stream, a);                \
+        else hipLaunchKernelGGL((k_pull_all4<F, 0>), grid, block, 0, c->stream, a);                         \
+    } while (0)
+    const bool quads = a.op == 0 && !store;
+    if (quads && a.p.d <= 16) PULL4_CASE(4);
+    else if (quads && a.p.d <= 32) PULL4_CASE(8);
+    else if (quads && a.p.d <= 64) PULL4_CASE(16);
+    else if (a.p.d <= 64) PULL_CASE(1);
     else if (a.p.d <= 128) PULL_CASE(2);
     else if (a.p.d <= 256) PULL_CASE(4);
     else if (a.p.d <= 512) PULL_CASE(8);
     else PULL_CASE(16);
 #undef PULL_CASE
 #undef PULL_CASE_W
+#undef PULL4_CASE
     if (a.op == 0) hipLaunchKernelGGL(k_pull_all_close, dim3(c->n_cu * 16), block, 0, c->stream, a);
 }
 
