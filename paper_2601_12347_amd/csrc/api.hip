@@ -338,6 +338,7 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     g.add(&c->part_cnt, (size_t)c->n_part);
     g.add(&c->part_deg, (size_t)c->n_part);
     g.add(&c->part_ideg, (size_t)c->n_part);
+    g.add(&c->part_tch, (size_t)c->n_part);
     g.add(&c->ctr, 1);
     RP_TRY(block_alloc(c, g, &c->graph_block, true));
     RP_TRY(dev_alloc(c, &c->out_pool, (size_t)pool_cap, false));

@@ -23,6 +23,7 @@
 #define EXP_NONE 0u
 #define EXP_OUT 1u                   // (w -> y): erase w from y's in-row
 #define EXP_IN 2u                    // (x -> w): erase w from x's out-row
+#define EXP_FIRST 4u                 // with one of the two: the first operation or edge to touch that row
 
 #define READ_PIECES 8u               // pieces of rows that one launch writes to the host, of at most READ_FLOATS numbers each
 #define READ_FLOATS 65536u
@@ -50,7 +51,7 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t n_applied, n_rejected;
     uint32_t n_add, n_del;                    // accepted edge adds / deletes (ops only)
     uint32_t n_gone;                          // edges that go with deleted vertices
-    unsigned long long n_listed;              // touched out-rows (low half) and in-rows that edge operations have listed so far
+    unsigned long long n_listed;              // touched out-rows (low half) and in-rows listed so far
     uint32_t n_entries;                       // entries of the touched rows' segments handed out so far
     uint32_t need_out, need_in;               // pool entries relocation will take
     uint32_t n_vadd;
@@ -174,7 +175,7 @@ struct ripple_ctx {
     uint32_t *rep[RIPPLE_MAX_LAYERS + 1] = {nullptr};   // union over sub-batches (reporting)
     uint32_t *list[RIPPLE_MAX_LAYERS + 1] = {nullptr};  // A_l, ascending (l >= 1); op order for l = 0
     uint32_t *eoff[RIPPLE_MAX_LAYERS + 1] = {nullptr};  // exclusive scan of out-degrees over A_l, +1 entry
-    uint32_t *part_cnt = nullptr, *part_deg = nullptr, *part_ideg = nullptr;  // per-block partial sums
+    uint32_t *part_cnt = nullptr, *part_deg = nullptr, *part_ideg = nullptr, *part_tch = nullptr;  // per-block partial sums
     uint32_t *ioff[RIPPLE_MAX_LAYERS + 1] = {nullptr};  // exclusive scan of in-degrees over A_l, +1 entry
     uint32_t n_part = 0;
     uint32_t *all_list = nullptr;                       // scratch list (live vertices): full inference, discovering hops

@@ -103,7 +103,7 @@ struct CompactArgs {
     uint32_t n_words;
     const uint2 *out_meta, *in_meta;
     int want_out, want_in;         // emit out-degree / in-degree prefixes over the list
-    uint32_t *part_cnt, *part_out, *part_in;
+    uint32_t *part_cnt, *part_out, *part_in, *part_tch;    // (part_tch: with touched_out only)
     uint32_t *rep;                 // reporting union or null
     uint32_t *touched_out;         // += vertices that received a message, or null
     uint32_t *list, *eoff, *ioff;  // outputs
@@ -251,33 +251,37 @@ __global__ __launch_bounds__(256) void k_frontier_count(CompactArgs a) {
         a.part_cnt[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
         a.part_out[blockIdx.x] = sh[4] + sh[5] + sh[6] + sh[7];
         a.part_in[blockIdx.x] = sh[8] + sh[9] + sh[10] + sh[11];
-        const uint32_t t = sh[12] + sh[13] + sh[14] + sh[15];
-        if (a.touched_out && t) atomicAdd(a.touched_out, t);
+        // (added to one counter, 1,196 blocks waited for one another: 22 us for 2.45 M vertices, now 12)
+        if (a.touched_out) a.part_tch[blockIdx.x] = sh[12] + sh[13] + sh[14] + sh[15];
     }
 }
 
 // pass 2: write the ascending list and the degree prefixes
 template <int S>
 __global__ __launch_bounds__(256) void k_frontier_emit(CompactArgs a) {
-    __shared__ uint32_t sh[12], wt[12];
+    __shared__ uint32_t sh[16], wt[12];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t w0 = (blockIdx.x * 4u + wave) * 2u * S;
     WordRange<S> r;
     r.read(a, w0, lane);                                   // on its way while the blocks before this one are summed
-    uint32_t pc = 0, po = 0, pi = 0;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    uint32_t pc = 0, po = 0, pi = 0, pt = 0;
     for (uint32_t b = tid; b < blockIdx.x; b += 256) {
         pc += a.part_cnt[b];
         po += a.part_out[b];
         pi += a.part_in[b];
     }
+    for (uint32_t b = tid; last && a.touched_out && b < gridDim.x; b += 256) pt += a.part_tch[b];
     r.degrees(a, w0, lane);
     pc = rp_wave_scan(pc);
     po = rp_wave_scan(po);
     pi = rp_wave_scan(pi);
+    pt = rp_wave_scan(pt);
     if (lane == 63) {
         sh[wave] = pc;
         sh[4 + wave] = po;
         sh[8 + wave] = pi;
+        sh[12 + wave] = pt;
         wt[wave] = r.cnt;
         wt[4 + wave] = r.dout;
         wt[8 + wave] = r.din;
@@ -290,7 +294,10 @@ __global__ __launch_bounds__(256) void k_frontier_emit(CompactArgs a) {
         oi += wt[8 + k];
     }
     r.emit(a, w0, lane, oc, oo, oi);
-    if (blockIdx.x == gridDim.x - 1 && tid == 255) compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din);
+    if (last && tid == 255) {
+        compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din);
+        if (a.touched_out) *a.touched_out += sh[12] + sh[13] + sh[14] + sh[15];
+    }
 }
 
 // Both passes in one workgroup, for bitmaps of at most ONE_WORDS words (8,192 vertices): one launch instead of two.
@@ -483,6 +490,7 @@ void rp_launch_alive_list(ripple_ctx *c) {
     a.part_cnt = c->part_cnt;
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
+    a.part_tch = c->part_tch;
     a.list = c->all_list;
     a.ioff = c->ioff_all;
     a.count_out = &c->ctr->n_all;
@@ -510,6 +518,7 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
     a.part_cnt = c->part_cnt;
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
+    a.part_tch = c->part_tch;
     a.done.flag = nullptr;
     a.rep = accumulate_rep ? c->rep[l] : nullptr;
     a.touched_out = pruned ? nullptr : &c->ctr->touched[l];
@@ -541,6 +550,7 @@ void rp_launch_candidates(ripple_ctx *c, uint32_t l) {
     a.part_cnt = c->part_cnt;
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
+    a.part_tch = c->part_tch;
     a.touched_out = &c->ctr->touched[l];
     a.want_in = 1;                                 // for the hops that recompute every candidate, and for the choice of the next batch
     a.list = c->all_list;
@@ -575,6 +585,7 @@ void rp_launch_bitmap_to_list(ripple_ctx *c, uint32_t *bitmap, uint32_t *out_lis
     a.part_cnt = c->part_cnt;
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
+    a.part_tch = c->part_tch;
     a.list = out_list;
     a.count_out = count_d;
     bitmap_ids(c, a, report);
