@@ -1169,19 +1169,17 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         }
         // A hop that the last batch moved a good many messages at without discovering its set is taken from the list of them
         // (k_scatter_list) where that pays: in place of a pull through in-rows that hold enough entries, or of a push of enough numbers.
-        // The out-edge walk writes the list; a quarter more messages than the last batch had are expected, four times as many where
-        // the hop would be pushed (small sets differ more, depending on the hubs they meet). The kernels make sure on the device that
-        // the list is only used if this batch's messages fit and it still pays; else the hop is pulled or pushed.
+        // The out-edge walk writes the list, whatever there is room for: batches differ by the hubs they meet, and one that is pulled because it has
+        // more messages than the last one costs more than the walk (100 updates on the dense graph that meet a hub, hop 3: 165 us of walk and 1,115 pulled, 210 and 460 listed).
+        // The kernels make sure on the device that the list is only used if it still pays; else the hop is pulled or pushed.
         uint32_t pair_cap = 0;
         if (l >= 2 && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3) {
             const uint64_t m = c->last_m[l];
             const bool pulls = c->opt_scatter == 2 || m * c->xw[l] * 4ull * (unsigned)c->opt_pull_ratio >= 8ull * c->last_isum[l];
             if (c->opt_sorted == 2) pair_cap = c->pair_cap;
-            else if (c->hints_valid && m && c->last_hop_mode[l] != 1u + RP_HOP_DISCOVER &&
-                     (pulls ? rp_list_pays_pull(m, c->last_isum[l]) : m * c->xw[l] >= RP_LIST_NUMBERS)) {
-                const uint64_t want = ((pulls ? m + m / 4 : 4 * m) + 4096) & ~4095ull;
-                if (pulls ? want <= c->pair_cap : m <= c->pair_cap) pair_cap = (uint32_t)std::min<uint64_t>(want, c->pair_cap);
-            }
+            else if (c->hints_valid && m && m <= c->pair_cap && c->last_hop_mode[l] != 1u + RP_HOP_DISCOVER &&
+                     (pulls ? rp_list_pays_pull(m, c->last_isum[l]) : m * c->xw[l] >= RP_LIST_NUMBERS))
+                pair_cap = c->pair_cap;
             if (pair_cap && list_runs_over(c, l, pair_cap)) pair_cap = 0;
         }
         if (sparse) rp_launch_frontier_sparse(c, l, layer_self(c, l), l < c->L);
