@@ -450,9 +450,11 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
         if (SMALL) st = rp_bit(a.alive, op.u) ? 0u : 1u;   // (small pieces delete no vertices)
     } else {
         bool ok = true;
+        const uint2 mo = a.out_meta[op.u], mi = a.in_meta[op.v];
+        const bool live[2] = {rp_bit(a.alive, op.u), rp_bit(a.alive, op.v)};
         for (int side = 0; side < 2; ++side) {              // alive, or (edges) created by this piece
             const uint32_t w = side ? op.v : op.u;
-            if (rp_bit(a.alive, w)) continue;
+            if (live[side]) continue;
             bool created = false;
             if (!SMALL) {
                 created = is_edge && (a.vstate[w] & VS_ADDING);
@@ -463,7 +465,6 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
             ok = ok && created;
         }
         if (ok) {                                           // the same for all wavefronts
-            const uint2 mo = a.out_meta[op.u], mi = a.in_meta[op.v];
             const uint32_t *ro = a.out_pool + mo.x, *ri = a.in_pool + mi.x;
             const uint32_t half = W / 2;
             if (is_add) {                                   // absent from the shorter of the two rows
@@ -505,55 +506,82 @@ __device__ __forceinline__ void validate_op(const MutArgs &a, uint32_t i, const 
     if (W > 1) __syncthreads();                             // (s_pos is set anew)
 }
 
-// the edges of the vertices that the piece deletes, a wavefront per vertex
-__device__ __forceinline__ void list_expanded(const MutArgs &a, uint32_t gw, uint32_t nw) {
+#define EXPAND_OPS 16u
+// The edges of the vertices that the piece deletes, a workgroup per 16 operations: it takes the vertices among them one after the other, all its
+// wavefronts together, 1,024 entries of a row at a time. (A wavefront per vertex, 64 entries at a time: 100 deleted vertices on the dense
+// graph, some with thousands of in-edges, held k_validate up for 142 us, now 104.)
+__device__ __forceinline__ void list_expanded(const MutArgs &a, uint32_t bid, uint32_t nb, uint32_t *s_base) {
     if (a.ctr->need_exp > a.exp_cap) return;                // no room: the piece will not be committed
+    constexpr int U = 4;
     const int lane = rp_lane();
-    for (uint32_t i = gw; i < a.n_ops; i += nw) {
-        const ripple_update op = a.ops[i];
-        if (op.kind != RIPPLE_VERTEX_DEL || !a.status[i]) continue;
-        const uint32_t w = op.u;
-        const uint2 mo = a.out_meta[w], mi = a.in_meta[w];
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&a.ctr->n_exp, mo.y + mi.y);
-        base = __shfl(base, 0);
-        uint32_t gone = mo.y;                               // every out-edge disappears
-        for (uint32_t j = lane; j < mo.y; j += 64) {
-            const uint32_t y = a.out_pool[mo.x + j];
-            a.exp_kind[base + j] = (a.vstate[y] & VS_DYING) ? EXP_NONE : EXP_OUT;
-            a.exp_a[base + j] = w;
-            a.exp_b[base + j] = y;
-        }
-        for (uint32_t j0 = 0; j0 < mi.y; j0 += 64) {
-            const uint32_t j = j0 + lane;
-            const bool valid = j < mi.y;
-            const uint32_t x = valid ? a.in_pool[mi.x + j] : 0u;
-            const bool keep = valid && !(a.vstate[x] & VS_DYING);   // edges between two dying vertices count once
-            if (valid) {
-                a.exp_kind[base + mo.y + j] = keep ? EXP_IN : EXP_NONE;
-                a.exp_a[base + mo.y + j] = x;
-                a.exp_b[base + mo.y + j] = w;
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t i0 = bid * EXPAND_OPS; i0 < a.n_ops; i0 += nb * EXPAND_OPS) {
+        const uint32_t i = i0 + (uint32_t)lane, ic = min(i, a.n_ops - 1u);   // (the same operations in all wavefronts)
+        const ripple_update op = a.ops[ic];
+        const uint32_t st = a.status[ic];
+        unsigned long long left = __ballot(lane < (int)EXPAND_OPS && i < a.n_ops && op.kind == RIPPLE_VERTEX_DEL && st != 0u);
+        for (; left; left &= left - 1ull) {
+            const uint32_t w = (uint32_t)__shfl((int)op.u, __ffsll((long long)left) - 1);
+            const uint2 mo = a.out_meta[w], mi = a.in_meta[w];
+            __syncthreads();
+            if (tid == 0) *s_base = atomicAdd(&a.ctr->n_exp, mo.y + mi.y);
+            __syncthreads();
+            const uint32_t base = *s_base;
+            for (uint32_t j0 = tid; j0 < mo.y; j0 += 256u * U) {
+                uint32_t y[U], st[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) y[t] = a.out_pool[mo.x + min(j0 + 256u * t, mo.y - 1u)];
+#pragma unroll
+                for (int t = 0; t < U; ++t) st[t] = a.vstate[y[t]];
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const uint32_t j = j0 + 256u * t;
+                    if (j >= mo.y) continue;
+                    a.exp_kind[base + j] = (st[t] & VS_DYING) ? EXP_NONE : EXP_OUT;
+                    a.exp_a[base + j] = w;
+                    a.exp_b[base + j] = y[t];
+                }
             }
-            gone += (uint32_t)__popcll(__ballot(keep));
+            uint32_t gone = 0;
+            for (uint32_t j0 = tid; j0 < mi.y; j0 += 256u * U) {
+                uint32_t x[U], st[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) x[t] = a.in_pool[mi.x + min(j0 + 256u * t, mi.y - 1u)];
+#pragma unroll
+                for (int t = 0; t < U; ++t) st[t] = a.vstate[x[t]];
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const uint32_t j = j0 + 256u * t;
+                    if (j >= mi.y) continue;
+                    const bool keep = !(st[t] & VS_DYING);  // edges between two dying vertices count once
+                    a.exp_kind[base + mo.y + j] = keep ? EXP_IN : EXP_NONE;
+                    a.exp_a[base + mo.y + j] = x[t];
+                    a.exp_b[base + mo.y + j] = w;
+                    gone += keep ? 1u : 0u;
+                }
+            }
+            gone = (uint32_t)__builtin_amdgcn_readlane((int)rp_wave_scan(gone), 63);
+            if (tid == 0) gone += mo.y;                      // every out-edge disappears
+            if (lane == 0 && gone) atomicAdd(&a.ctr->n_gone, gone);
         }
-        if (lane == 0) atomicAdd(&a.ctr->n_gone, gone);
     }
 }
 
-// The first nb workgroups judge operations, the others list the edges of deleted vertices. A workgroup per operation (W = 4) while
+// The first nd workgroups list the edges of deleted vertices, the others judge operations. A workgroup per operation (W = 4) while
 // all of them are resident at once, a wavefront per operation above that. Averages of 40 to 60 launches, W = 4 and 1: 1,000
 // operations on 1.2 M edges 10.0 and 11.1 us (single launches differ by 2.5), 1,777 on 31 M edges 16.2 and 21.4 (0.7), 10,000 on
 // 124 M edges 53.6 and 34.7 (0.4).
 #define WORKGROUP_OPS 2048u
 template <int W>
-__global__ __launch_bounds__(256) void k_validate(MutArgs a, uint32_t nb) {
+__global__ __launch_bounds__(256) void k_validate(MutArgs a, uint32_t nd) {
     __shared__ int s_pos[2];
-    const uint32_t wave = threadIdx.x >> 6;
-    if (blockIdx.x >= nb) {
-        list_expanded(a, (blockIdx.x - nb) * 4u + wave, (gridDim.x - nb) * 4u);
+    __shared__ uint32_t s_base;
+    if (blockIdx.x < nd) {
+        list_expanded(a, blockIdx.x, nd, &s_base);
         return;
     }
-    for (uint32_t i = W == 1 ? blockIdx.x * 4u + wave : blockIdx.x; i < a.n_ops; i += W == 1 ? nb * 4u : nb)
+    const uint32_t b = blockIdx.x - nd, nb = gridDim.x - nd;
+    for (uint32_t i = W == 1 ? b * 4u + (threadIdx.x >> 6) : b; i < a.n_ops; i += W == 1 ? nb * 4u : nb)
         validate_op<W, 0>(a, i, a.ops[i], s_pos);
 }
 
@@ -619,10 +647,8 @@ __device__ __forceinline__ void measure(const MutArgs &a, const ripple_update *o
         }
     } else if (j < a.n_ops) {
         f = a.op_touch[j];
-        if (f) {
-            u = ops[j].u;
-            v = ops[j].v;
-        }
+        u = ops[j].u;                                       // (v: of edge operations)
+        v = ops[j].v;
     }
     const unsigned long long mo = __ballot((f & 4u) != 0), mi = __ballot((f & 8u) != 0);
     uint32_t eo = 0, ei = 0, no = 0, ni = 0;
@@ -707,9 +733,16 @@ __global__ __launch_bounds__(256) void k_small_validate(MutArgs a, const ripple_
 // what its in-neighbours have sent (T), so a changed edge adds or removes T[u] itself.
 __device__ __forceinline__ void struct_term(const MutArgs &a, uint32_t u, uint32_t v, uint32_t l, float sg, int lane) {
     const uint32_t w = a.T[l] ? a.xw[l] : a.d[l - 1];
-    for (uint32_t c = lane; c < w; c += 64) {
-        const float val = a.T[l] ? a.T[l][(size_t)u * w + c] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + c);
-        if (val != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * w + c], sg * val);
+    for (uint32_t c = lane; c < w; c += 256) {              // four reads on their way, then the additions
+        float val[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const size_t at = (size_t)u * w + min(c + 64u * t, w - 1u);
+            val[t] = a.T[l] ? a.T[l][at] : rp_load_h(a.H[l - 1], a.store, at);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (c + 64u * t < w && val[t] != 0.0f) unsafeAtomicAdd(&a.X[l][(size_t)v * w + c + 64u * t], sg * val[t]);
     }
 }
 // layers whose rows with a changed in-edge are recomputed have no such terms, and the deterministic mode orders them (k_det_terms)
@@ -728,11 +761,13 @@ __device__ __forceinline__ void list_changed(const MutArgs &a, uint32_t s, uint3
 // One operation per thread: tombstones, the rows' segments, the list of changed edges, A_0 with its out-degree prefix
 __device__ __forceinline__ void apply_op(const MutArgs &a, uint32_t i) {
     const bool in_range = i < a.n_ops;
-    const ripple_update op = in_range ? a.ops[i] : ripple_update{99u, 0u, 0u, 0u};
+    const uint32_t ic = min(i, a.n_ops - 1u), judged = a.status[ic], stop = a.ctr->abort_flag;
+    ripple_update op = a.ops[ic];
+    if (!in_range) op = ripple_update{99u, 0u, 0u, 0u};
     if (op.kind == RIPPLE_VERTEX_ADD || op.kind == RIPPLE_VERTEX_DEL) atomicAnd(&a.vstate[op.u], ~(VS_ADDING | VS_DYING));
-    if (a.ctr->abort_flag) return;
+    if (stop) return;
     const int lane = rp_lane();
-    const bool acc = in_range && a.status[i] != 0;
+    const bool acc = in_range && judged != 0;
     const unsigned long long ma = __ballot(acc), mr = __ballot(in_range && !acc);
     if (lane == 0) {
         if (ma) atomicAdd(&a.ctr->n_applied, (uint32_t)__popcll(ma));
@@ -801,12 +836,12 @@ __device__ __forceinline__ void apply_expanded(const MutArgs &a, uint32_t gw, ui
         }
     }
     if (a.det) return;
-    for (uint32_t e = gw; e < n; e += nw) {
-        if ((a.exp_kind[e] & ~EXP_FIRST) != EXP_OUT) continue;
+    for (unsigned long long t = gw; t < (unsigned long long)n * a.L; t += nw) {      // a wavefront per edge and layer
+        const uint32_t e = (uint32_t)(t / a.L), l = (uint32_t)(t - (unsigned long long)e * a.L) + 1u;
+        if ((a.exp_kind[e] & ~EXP_FIRST) != EXP_OUT || !has_terms(a, l)) continue;
         const uint32_t x = a.exp_a[e], y = a.exp_b[e];
-        const float alpha = a.in_w ? a.in_w[a.in_meta[y].x + a.exp_pos[e]] : 1.0f;
-        for (uint32_t l = 1; l <= a.L; ++l)
-            if (has_terms(a, l)) struct_term(a, x, y, l, ((a.wsum_mask >> l) & 1u) ? -alpha : -1.0f, lane);
+        const float alpha = (a.in_w && ((a.wsum_mask >> l) & 1u)) ? a.in_w[a.in_meta[y].x + a.exp_pos[e]] : 1.0f;
+        struct_term(a, x, y, l, -alpha, lane);
     }
 }
 
@@ -823,13 +858,14 @@ __global__ __launch_bounds__(256) void k_edges(MutArgs a, uint32_t tb, uint32_t 
         apply_expanded(a, (blockIdx.x - tb - sb) * 4u + wave, (gridDim.x - tb - sb) * 4u);
         return;
     }
-    if (a.ctr->abort_flag) return;
+    const uint32_t stop = a.ctr->abort_flag;
     const int lane = rp_lane();
     const uint32_t per = a.in_w ? 1u : a.L;
     for (unsigned long long t = (blockIdx.x - tb) * 4u + wave; t < (unsigned long long)a.n_ops * per; t += sb * 4u) {
         const uint32_t i = (uint32_t)(t / per), l = (uint32_t)(t - (unsigned long long)i * per) + 1u;
-        if (!a.status[i]) continue;
+        const uint32_t st = a.status[i];                    // (requested together, like all that does not depend on one another here)
         const ripple_update op = a.ops[i];
+        if (!st || stop) continue;
         if (op.kind != RIPPLE_EDGE_ADD && op.kind != RIPPLE_EDGE_DEL && op.kind != RIPPLE_EDGE_REWEIGHT) continue;
         const float unit = op.kind == RIPPLE_EDGE_ADD ? 1.0f : (op.kind == RIPPLE_EDGE_DEL ? -1.0f : 0.0f);
         if (!a.in_w) {                                      // nothing is re-weighted, all layers see +1 / -1
@@ -1359,11 +1395,11 @@ void rp_launch_mutate(ripple_ctx *c, const ripple_update *src, uint32_t n_ops, b
         else hipLaunchKernelGGL(k_small_validate<1>, grid, dim3(256), 0, s, a, src, c->ops_d, nb, c->bm[0], words);
     } else {
         const bool wide = n_ops <= WORKGROUP_OPS;
-        const uint32_t nb = wide ? n_ops : std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu * 32), nd = has_vertex_del ? std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu) : 0u;
+        const uint32_t nb = wide ? n_ops : std::min<uint32_t>(rp_div_up(n_ops, 4), c->n_cu * 32), nd = has_vertex_del ? std::min<uint32_t>(rp_div_up(n_ops, EXPAND_OPS), c->n_cu * 4) : 0u;
         hipLaunchKernelGGL(k_stage, dim3(std::min<uint32_t>(rp_div_up(std::max(words, n_ops), 256), c->n_cu * 4)), dim3(256), 0, s, a, src,
                            c->ops_d, c->bm[0], words);
-        if (wide) hipLaunchKernelGGL(k_validate<4>, dim3(nb + nd), dim3(256), 0, s, a, nb);
-        else hipLaunchKernelGGL(k_validate<1>, dim3(nb + nd), dim3(256), 0, s, a, nb);
+        if (wide) hipLaunchKernelGGL(k_validate<4>, dim3(nb + nd), dim3(256), 0, s, a, nd);
+        else hipLaunchKernelGGL(k_validate<1>, dim3(nb + nd), dim3(256), 0, s, a, nd);
         if (has_vertex_del) hipLaunchKernelGGL(k_find_expanded, dim3(big), dim3(256), 0, s, a);
         hipLaunchKernelGGL(k_measure, dim3(has_vertex_del ? SMALL_WGS : std::min<uint32_t>(tb, SMALL_WGS)), dim3(256), 0, s, a);
     }
