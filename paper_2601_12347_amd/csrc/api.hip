@@ -1183,7 +1183,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             if (pair_cap && list_runs_over(c, l, pair_cap)) pair_cap = 0;
         }
         if (sparse) rp_launch_frontier_sparse(c, l, layer_self(c, l), l < c->L);
-        else rp_launch_frontier_mark(c, l, may_disc, pair_cap);
+        else if (!may_disc || pair_cap) rp_launch_frontier_mark(c, l, may_disc, pair_cap);   // (else by the launch that discovers or marks)
         rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
         const bool both = rp_has_project_both(c, l);
         if (c->layers[l - 1].proj) {                   // what travels is already multiplied by W_neigh
@@ -1200,7 +1200,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         }
         if (may_disc) {                                // scatters and marks A_l in one scan of all in-rows
             t = rp_timer_begin(c);
-            rp_launch_scatter_pull(c, l, true, true);
+            rp_launch_scatter_pull(c, l, true, true, 0, !pair_cap);
             rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l, false);
         }
         if (!sparse) {
@@ -1209,9 +1209,9 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_timer_end(c, t, RIPPLE_PH_COMPACT, (int)l);
         }
         t = rp_timer_begin(c);
-        if (c->opt_scatter < 2 || !may_pull) rp_launch_scatter_push(c, l, may_pull, may_disc, pair_cap);
+        if (!may_pull) rp_launch_scatter_push(c, l, pair_cap);
         if (pair_cap) rp_launch_scatter_list(c, l, may_disc, pair_cap);
-        if (may_pull) rp_launch_scatter_pull(c, l, false, may_disc, pair_cap);
+        if (may_pull) rp_launch_scatter_pull(c, l, false, may_disc, pair_cap, c->opt_scatter < 2);
         rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);
         t = rp_timer_begin(c);
         rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));

@@ -37,9 +37,9 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term);
 void rp_launch_small_addend(ripple_ctx *c, uint32_t l, bool emit_delta);   // transform.hip
 
 // scatter.hip
-void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc, uint32_t pair_cap = 0);
+void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, uint32_t pair_cap = 0);
 void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap);
-void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow_disc, uint32_t pair_cap = 0);
+void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow_disc, uint32_t pair_cap, bool others);
 // buckets of the lists of a hop of about `messages` messages: a bucket is the vertices that agree in id >> shift
 struct ListCut {
     uint32_t n, shift, room;                             // buckets, their width, entries each has room for

@@ -56,6 +56,13 @@ struct PullArgs {
     const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
     uint32_t sorted_cap;           // entries the host sorted (0: no list was made)
     int sorted_force;
+    // the same hop pushed (DISC = 0), or its set marked (DISC = 1), by the same launch where the hop turns out not to be this kernel's
+    int others;
+    const uint32_t *out_list, *out_eoff;   // A_{l-1} and its out-degree prefix
+    const uint2 *out_meta;
+    const uint32_t *out_pool;
+    const float *out_w;
+    uint8_t *mk;
     // deterministic variants only
     const uint32_t *bm_rec;        // destinations that are recomputed from all their in-neighbours (bootstrap inference), or null
     const void *Hprev;             // what a recomputed row sums: rows of H^{l-1} (storage format `store`) ...

@@ -15,6 +15,7 @@
 #include "kernels.h"
 #include "pull_scan.h"
 #include "push.h"
+#include "walk.h"
 
 
 
@@ -24,11 +25,9 @@ template <int NJ, int PK, int WT>
 __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, const uint32_t *count_ptr,
                                                       const uint32_t *eoff, const float *D, uint32_t ldd, uint32_t d,
                                                       const uint2 *out_meta, const uint32_t *out_pool, const float *out_w, float *X,
-                                                      DevCtr *ctr, uint32_t l, int may_pull, int mode, int ratio, int allow_disc,
-                                                      uint32_t list_cap, int list_force) {
-    const int hm = rp_hop_mode(ctr, l, d, mode, ratio, allow_disc);
-    if (hm == RP_HOP_DISCOVER || (may_pull && hm == RP_HOP_PULL)) return;
+                                                      DevCtr *ctr, uint32_t l, int mode, int ratio, uint32_t list_cap, int list_force) {
     if (list_cap) {
+        const int hm = rp_hop_mode(ctr, l, d, mode, ratio, 0);
         const uint32_t cp = *count_ptr;
         if (rp_hop_listed(ctr, l, d, cp ? count_ptr[1] : 0u, list_cap, list_force, hm)) return;
     }
@@ -37,7 +36,8 @@ __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, cons
                        (gridDim.x * blockDim.x) >> 6);
 }
 
-void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow_disc, uint32_t pair_cap) {
+// (hops that may be pulled: rp_launch_scatter_pull)
+void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, uint32_t pair_cap) {
     const bool proj = c->layers[l - 1].proj != 0;           // project-first: messages are already d_out wide
     const uint32_t d = c->xw[l];
     const bool packed = proj && c->layers[l - 1].packed;
@@ -47,8 +47,8 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
     const bool wt = c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
 #define PUSH_CASE_WT(NJ, PK, WT)                                                                                   \
     hipLaunchKernelGGL((k_scatter_push<NJ, PK, WT>), grid, block, 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,     \
-                       c->eoff[l - 1], D, ldd, d, c->out_meta, c->out_pool, c->out_w, c->X[l], c->ctr, l, may_pull ? 1 : 0,  \
-                       c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0, pair_cap, c->opt_sorted == 2 ? 1 : 0)
+                       c->eoff[l - 1], D, ldd, d, c->out_meta, c->out_pool, c->out_w, c->X[l], c->ctr, l,  \
+                       c->opt_scatter, c->opt_pull_ratio, pair_cap, c->opt_sorted == 2 ? 1 : 0)
 #define PUSH_CASE_PK(NJ, PK)                     \
     do {                                         \
         if (wt) PUSH_CASE_WT(NJ, PK, 1);         \
@@ -92,17 +92,36 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, bool may_pull, bool allow
 // message, and the sum replaces the row. The hop is always pulled.
 //
 // WT = 1: every message is multiplied by its edge's weight (weighted sum, m = alpha (h - h_old), Sec. 3.3.3)
-__device__ __forceinline__ bool pull_is_listed(const PullArgs &a) {
+__device__ __forceinline__ bool pull_is_listed(const PullArgs &a, int hop_mode) {
     if (!a.sorted_cap) return false;
     const uint32_t cp = *a.m_count;
-    return rp_hop_listed(a.ctr, a.l, a.d, cp ? a.m_count[1] : 0u, a.sorted_cap, a.sorted_force, RP_HOP_PULL);
+    return rp_hop_listed(a.ctr, a.l, a.d, cp ? a.m_count[1] : 0u, a.sorted_cap, a.sorted_force, hop_mode);
+}
+// Whether the hop is pulled (DISC = 0) or discovered by the launch that asks. If not, and nothing else has been launched for it, the launch pushes the
+// hop's messages (rows of NJ times 64 columns, PK: packed), or marks its set: a launch of its own that turns out to have nothing to do takes 7 us.
+template <int NJ, int PK, int DISC, int WT>
+__device__ __forceinline__ bool pull_or_others(const PullArgs &a) {
+    const int hm = rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc);
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    if (DISC) {
+        if (hm == RP_HOP_DISCOVER) return true;
+        if (a.others) frontier_walk<false>(a.out_list, a.m_count, a.out_eoff, a.out_meta, a.out_pool, a.mk, SparseArgs(), gw, nw);
+        return false;
+    }
+    if (hm == RP_HOP_DISCOVER || pull_is_listed(a, hm)) return false;
+    if (hm == RP_HOP_PULL) return true;
+    if (a.others) {
+        if (*a.m_count && blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_PUSH;
+        push_edges<NJ, PK, WT>(a.out_list, a.m_count, a.out_eoff, a.D, nullptr, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, gw, nw);
+    }
+    return false;
 }
 
 template <int NJ, int DISC, int WT, int DET>
 __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
     static_assert(!DET || (!DISC && !WT), "the deterministic form pulls into A_l, unweighted");
-    if (!DET && rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL)) return;
-    if (!DET && !DISC && pull_is_listed(a)) return;
+    if constexpr (!DET)
+        if (!pull_or_others<NJ, 0, DISC, WT>(a)) return;
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
@@ -501,8 +520,8 @@ __device__ __forceinline__ uint32_t row_column(uint32_t lane) {    // (beyond an
 template <int F, int DISC, int WT, int DET>
 __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
     static_assert(!DET || (!DISC && !WT && !F), "the deterministic form pulls into A_l, unweighted, packed rows");
-    if (!DET && rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc) != (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL)) return;
-    if (!DET && !DISC && pull_is_listed(a)) return;
+    if constexpr (!DET)
+        if (!pull_or_others<1, F ? 0 : 1, DISC, WT>(a)) return;
     const uint32_t count = *a.count_ptr;
     if (count == 0) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + (DISC ? RP_HOP_DISCOVER : RP_HOP_PULL);
@@ -885,8 +904,15 @@ __global__ __launch_bounds__(256) void k_pull_fixup(PullArgs a, uint32_t n_entri
 
 // discover = false: pull into A_l (the hop's list). true: scan every live vertex (c->all_list and
 // c->ioff_all must have been produced by rp_launch_alive_list) and mark the receivers in bm[l].
-void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow_disc, uint32_t pair_cap) {
+// others: nothing else is launched to push the hop (discover = false), or to mark its set (true).
+void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow_disc, uint32_t pair_cap, bool others) {
     PullArgs a;
+    a.others = others ? 1 : 0;
+    a.out_list = c->list[l - 1];
+    a.out_eoff = c->eoff[l - 1];
+    a.out_meta = c->out_meta;
+    a.out_pool = c->out_pool;
+    a.mk = c->mk;
     a.m_count = &c->ctr->set[l - 1].a;
     a.sorted_cap = discover ? 0u : pair_cap;
     a.sorted_force = c->opt_sorted == 2;
@@ -912,6 +938,7 @@ void rp_launch_scatter_pull(ripple_ctx *c, uint32_t l, bool discover, bool allow
     dim3 grid(c->n_cu * 8), block(256);
     const bool wt = c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
     a.in_w = wt ? c->in_w : nullptr;
+    a.out_w = wt ? c->out_w : nullptr;
 #define PULL_CASE(NJ)                                                                                      \
     do {                                                                                                   \
         if (discover && wt) hipLaunchKernelGGL((k_scatter_pull<NJ, 1, 1, 0>), grid, block, 0, c->stream, a);  \
@@ -1006,7 +1033,7 @@ void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t
 // one wavefront had in-edges of are finished.
 void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
     const LayerDev &ly = c->layers[l - 1];
-    PullArgs a;
+    PullArgs a = {};
     a.m_count = nullptr;
     a.sorted_cap = 0;
     a.sorted_force = 0;
