@@ -613,16 +613,16 @@ __global__ __launch_bounds__(256) void k_find_expanded(MutArgs a) {
 
 // whether the batch may be committed at all
 __device__ __forceinline__ uint32_t decide(const MutArgs &a) {
-    const volatile DevCtr *c = a.ctr;
-    const uint32_t need_out = c->need_out, need_in = c->need_in;
+    const volatile DevCtr *c = a.ctr;                       // (all of it requested at once: one round trip and not five)
+    const uint32_t need_out = c->need_out, need_in = c->need_in, out_top = c->out_top, in_top = c->in_top;
+    const uint32_t n_add = c->n_add, n_del = c->n_del, need_exp = c->need_exp, error = c->error;
+    const unsigned long long n_edges = c->n_edges;
+    const unsigned long long changed = (unsigned long long)n_add + n_del + need_exp;
     uint32_t flag = 0;
-    if ((unsigned long long)c->out_top + need_out > a.pool_cap || (unsigned long long)c->in_top + need_in > a.pool_cap)
-        flag |= 1u;
-    if (c->n_edges + c->n_add > a.e_cap + c->n_del) flag |= 2u;
-    if (c->need_exp > a.exp_cap || (unsigned long long)c->n_add + c->n_del + c->need_exp > a.struct_cap ||
-        (unsigned long long)c->n_add + c->n_del + c->need_exp > a.touch_cap)
-        flag |= 4u;
-    if (c->error) flag |= 8u;
+    if ((unsigned long long)out_top + need_out > a.pool_cap || (unsigned long long)in_top + need_in > a.pool_cap) flag |= 1u;
+    if (n_edges + n_add > a.e_cap + n_del) flag |= 2u;
+    if (need_exp > a.exp_cap || changed > a.struct_cap || changed > a.touch_cap) flag |= 4u;
+    if (error) flag |= 8u;
     return flag;
 }
 
@@ -653,14 +653,14 @@ __device__ __forceinline__ void measure(const MutArgs &a, const ripple_update *o
     const unsigned long long mo = __ballot((f & 4u) != 0), mi = __ballot((f & 8u) != 0);
     uint32_t eo = 0, ei = 0, no = 0, ni = 0;
     if (f & 4u) {
-        const uint32_t pend = a.pend_out[u], dead = a.dead_out[u], need = a.out_meta[u].y - dead + pend;
+        const uint32_t pend = a.pend_out[u], dead = a.dead_out[u], need = a.out_meta[u].y - dead + pend, cap = a.out_capv[u];
         eo = dead + pend;
-        if (pend && need > a.out_capv[u]) no = rp_row_cap(need);
+        if (pend && need > cap) no = rp_row_cap(need);
     }
     if (f & 8u) {
-        const uint32_t pend = a.pend_in[v], dead = a.dead_in[v], need = a.in_meta[v].y - dead + pend;
+        const uint32_t pend = a.pend_in[v], dead = a.dead_in[v], need = a.in_meta[v].y - dead + pend, cap = a.in_capv[v];
         ei = dead + pend;
-        if (pend && need > a.in_capv[v]) ni = rp_row_cap(need);
+        if (pend && need > cap) ni = rp_row_cap(need);
     }
     const uint32_t incl = rp_wave_scan(eo + ei), sum_no = rp_wave_scan(no), sum_ni = rp_wave_scan(ni);
     const uint32_t adds = (uint32_t)__popcll(__ballot((f & 3u) == 3u)), dels = (uint32_t)__popcll(__ballot((f & 3u) == 1u));

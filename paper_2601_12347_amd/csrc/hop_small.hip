@@ -71,7 +71,7 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
     a.D = ly.proj ? nullptr : c->D[(l - 1) & 1];
     a.ldd = ly.proj ? c->pd_ld : a.d;
     a.nb_walk = std::min(16u + msgs / 128u, c->n_cu);
-    const uint32_t nb_push = std::min(8u + msgs / 48u, c->n_cu * 4);
+    const uint32_t nb_push = std::min(8u + msgs / (msgs <= 2048u ? 16u : 48u), c->n_cu * 4);
     a.nb_push = ly.proj ? 0u : nb_push;
     const bool both = rp_has_project_both(c, l);
     uint32_t nb_gemm = 0;

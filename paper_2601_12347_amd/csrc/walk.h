@@ -39,8 +39,14 @@ struct SparseArgs {
 template <int T>
 __device__ __forceinline__ void sparse_enter_many(const SparseArgs &s, const uint32_t *v, bool from_edge) {
     bool live[T], fresh[T], lng[T];
+    uint32_t d_out[T], d_in[T];                             // requested beside the live bits, whether or not the vertex turns out to be new
 #pragma unroll
-    for (int t = 0; t < T; ++t) live[t] = v[t] != 0xFFFFFFFFu && rp_bit(s.alive, v[t]);
+    for (int t = 0; t < T; ++t) {
+        const bool some = v[t] != 0xFFFFFFFFu;
+        live[t] = some && rp_bit(s.alive, v[t]);
+        d_out[t] = (some && s.eoff) ? s.out_meta[v[t]].y : 0u;
+        d_in[t] = (some && (s.eoff || s.long_list)) ? s.in_meta[v[t]].y : 0u;
+    }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         fresh[t] = false;
@@ -50,7 +56,7 @@ __device__ __forceinline__ void sparse_enter_many(const SparseArgs &s, const uin
         }
     }
 #pragma unroll
-    for (int t = 0; t < T; ++t) lng[t] = fresh[t] && s.long_list && s.in_meta[v[t]].y > s.long_min;
+    for (int t = 0; t < T; ++t) lng[t] = fresh[t] && s.long_list && d_in[t] > s.long_min;
     unsigned long long mask[T], lmask[T];
     uint32_t total = 0, ltotal = 0;
 #pragma unroll
@@ -67,8 +73,8 @@ __device__ __forceinline__ void sparse_enter_many(const SparseArgs &s, const uin
         uint32_t off[T], run = 0, din = 0;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            off[t] = fresh[t] ? s.out_meta[v[t]].y : 0u;
-            din += fresh[t] ? s.in_meta[v[t]].y : 0u;
+            off[t] = fresh[t] ? d_out[t] : 0u;
+            din += fresh[t] ? d_in[t] : 0u;
         }
 #pragma unroll
         for (int t = 0; t < T; ++t) {
