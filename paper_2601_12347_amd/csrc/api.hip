@@ -762,8 +762,8 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
     }
     bool weighted = false;
     for (uint32_t l = 1; l <= c->L; ++l) weighted |= c->layers[l - 1].agg == RIPPLE_AGG_WSUM;
-    bool listed = false;                                 // some hop from the second on is one of sums
-    for (uint32_t l = 2; l <= c->L; ++l) listed |= !rp_layer_mono(c, l) && !rp_layer_attn(c, l);
+    bool listed = false;                                 // some hop from the second on is one of sums or attention
+    for (uint32_t l = 2; l <= c->L; ++l) listed |= !rp_layer_mono(c, l);
     if (listed && !c->opt_deterministic && rp_lists_allowed(c)) {
         // (destination, source) pairs of a hop's messages: room for twice a quarter of the edge capacity, at most 2^26 (a hop with
         // more messages than that quarter is pulled, pushed or discovers)
@@ -1122,20 +1122,27 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             rp_launch_gat_scores(c, l, c->list[l - 1], &c->ctr->set[l - 1].a);
             rp_timer_end(c, t, RIPPLE_PH_OTHER, (int)l);
             const bool listed = small_frontier(c, l, n, multi);
+            uint32_t pair_cap = 0;
             if (listed) {
                 t = rp_timer_begin(c);
                 rp_launch_frontier_sparse(c, l, true, l < c->L, RP_MONO_LISTED_LONG);
                 rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
             } else {
+                // messages listed as they are marked, where the last batch says that this pays (the kernels decide)
+                if (l >= 2 && c->pair_cap && c->opt_sorted) {
+                    const uint64_t m = c->last_m[l], e = c->ctr_host->n_edges, nv = std::max(1u, c->ctr_host->n_alive);
+                    if (c->opt_sorted == 2 || (c->hints_valid && RP_GAT_LIST_SHARE * m <= e && rp_list_pays_pull(m, m * (e / nv)))) pair_cap = c->pair_cap;
+                    if (pair_cap && list_runs_over(c, l, pair_cap)) pair_cap = 0;
+                }
                 t = rp_timer_begin(c);
-                rp_launch_frontier_mark(c, l, false);
+                rp_launch_frontier_mark(c, l, false, pair_cap);
                 rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
                 t = rp_timer_begin(c);
-                rp_launch_frontier_compact(c, l, true, l < c->L, true, multi);
+                rp_launch_frontier_compact(c, l, true, l < c->L, true, multi, false, pair_cap);
                 rp_timer_end(c, t, RIPPLE_PH_COMPACT, (int)l);
             }
             t = rp_timer_begin(c);
-            rp_launch_gat_scatter(c, l, false, listed);
+            rp_launch_gat_scatter(c, l, false, listed, pair_cap);
             rp_timer_end(c, t, RIPPLE_PH_SCATTER, (int)l);
             t = rp_timer_begin(c);
             rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));

@@ -482,11 +482,11 @@ __global__ __launch_bounds__(256) void k_gat_prepare(GatEdgeArgs a) {
         uint32_t v = 0;
         if (i < count) {
             v = a.p.list[i];
-            const uint32_t e0 = a.p.ioff[i], e1 = a.p.ioff[i + 1u];
-            const bool rec = a.all || rp_bit(a.p.bm_prev, v) || rp_bit(a.bm_vadd, v) || (rp_bit(a.bm_sink, v) && e1 - e0 <= a.long_min);
+            const uint32_t deg = a.p.in_meta[v].y;
+            const bool rec = a.all || rp_gat_recomputes(a.p.bm_prev, a.bm_sink, a.bm_vadd, a.p.in_meta, a.long_min, v);
             a.rec[v] = rec ? 1 : 0;
             a.mag[v] = 0.0f;
-            zero = rec && e1 == e0;                         // no run meets it
+            zero = rec && deg == 0u;                        // no run meets it
             if (zero) a.den[v] = 0.0f;
         }
         unsigned long long m = __ballot(zero);
@@ -723,6 +723,155 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
     }
 }
 
+// The messages of vertices that are not recomputed, from their list in order of destination (k_frontier_list, k_list_order): the old row taken away and
+// the new one added per changed in-neighbour, a sum per destination, added to its row by atomics. In place of testing all in-neighbours
+// of those vertices for the few that changed (rp_gat_list_made): 209 K messages of 256 columns to 135 K of them, with 14 M in-neighbours, k_gat_edges 405 -> 285
+// us (650 -> 412 for twice the recomputed vertices) and 84 here; with atomics for every row 130.
+template <int NJ, bool QUAD>
+__global__ __launch_bounds__(256) void k_gat_list(GatEdgeArgs a, const uint2 *sorted, uint32_t cap, int force, uint32_t *cnt, uint32_t n_cnt) {
+    const uint32_t M = a.p.ctr->set[a.p.l - 1u].a ? a.p.ctr->set[a.p.l - 1u].m : 0u;
+    if (!rp_gat_list_made(a.p.ctr, M, cap, force)) return;
+    {   // the buckets' counts for the next hop that is listed
+        const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+        if (i < n_cnt) cnt[i] = 0;
+    }
+    if (a.p.ctr->pair_over[a.p.l]) return;
+    constexpr uint32_t NONE = 0xFFFFFFFFu;
+    constexpr int G = QUAD ? 4 : (NJ >= 8 ? 1 : 8 / NJ);    // quads / messages in flight, two rows each
+    const uint32_t n_pairs = a.p.ctr->pairs[a.p.l];
+    const int lane = rp_lane();
+    const uint32_t d = a.p.d, ldp = a.ldp, grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
+    const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
+    const uint32_t unit = n_pairs / 64u < nw ? 16u : 64u;   // pairs at a time: fewer where whole wavefronts would leave others without any
+    const uint32_t n_chunks = (n_pairs + unit - 1u) / unit, per = (n_chunks + nw - 1u) / nw;
+    const uint32_t c_begin = min(n_chunks, gw * per), c_end = min(n_chunks, c_begin + per);
+    if (c_begin >= c_end) return;
+    // destinations of the run's first and last pair may have pairs in a neighbour's run; all others have one writer, whose old row is read with the first message
+    const uint32_t v_first = sorted[c_begin * unit].x, v_last = sorted[min(n_pairs, c_end * unit) - 1u].x;
+    uint32_t cur = NONE;
+    float xo[NJ];                                           // the old row (QUAD: of the lane's own column, in acc's layout)
+    float acc[NJ], dsum = 0.0f, mag = 0.0f;
+    float4 acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[j] = xo[j] = 0.0f;
+    auto flush = [&]() {
+        float sums = lane == 0 ? dsum : mag;                // lane 0: the denominator's, lane 16: mag
+        if (QUAD) {
+            acc[0] = swap_add32(swap_add16(acq.x, acq.y), swap_add16(acq.z, acq.w));
+            const float dm = swap_add16(dsum, mag);
+            sums = swap_add32(dm, dm);
+            acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint32_t col = QUAD ? 4u * sub + grp : (uint32_t)lane + 64u * j;
+            if (col < d) {
+                float *x = &a.p.X[(size_t)cur * d + col];
+                if (!QUAD && cur != v_first && cur != v_last) *x = xo[j] + acc[j];
+                else unsafeAtomicAdd(x, acc[j]);
+            }
+            acc[j] = 0.0f;
+        }
+        if (lane == 0 || lane == 16) unsafeAtomicAdd((lane ? a.mag : a.den) + cur, sums);
+        dsum = mag = 0.0f;
+    };
+    for (uint32_t c = c_begin; c < c_end; ++c) {
+        const uint32_t e = c * unit + (uint32_t)lane, n = min(unit, n_pairs - c * unit);
+        const bool in = (uint32_t)lane < n;
+        const uint2 my = in ? sorted[e] : make_uint2(NONE, 0u);
+        const float t_v = in ? a.sdst[my.x] : 0.0f;
+        if constexpr (QUAD) {
+            for (uint32_t k0 = 0; k0 < n; k0 += 4u * G) {
+                uint32_t v[G];
+                float tv[G];
+                float4 rn[G], ro[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int idx = (int)(k0 + 4u * g + grp); // below 64; past the list's end: row 0, no destination
+                    const size_t at = (size_t)(uint32_t)__shfl((int)my.y, idx) * ldp + 4u * sub;
+                    v[g] = (uint32_t)__shfl((int)my.x, idx);
+                    tv[g] = __shfl(t_v, idx);
+                    const bool col = 4u * sub < ldp;
+                    rn[g] = col ? *(const float4 *)(a.P + at) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    ro[g] = col && v[g] != NONE ? *(const float4 *)(a.Pold + at) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    if (k0 + 4u * g >= n) continue;
+                    const uint32_t r = d & 3u;
+                    const int from = (int)(16u * grp + d / 4u);   // the rows' scores sit in lane d / 4
+                    const float wn = gat_weight(__shfl(r == 0u ? rn[g].x : (r == 1u ? rn[g].y : (r == 2u ? rn[g].z : rn[g].w)), from), tv[g]);
+                    const float wo = gat_weight(__shfl(r == 0u ? ro[g].x : (r == 1u ? ro[g].y : (r == 2u ? ro[g].z : ro[g].w)), from), tv[g]);
+                    auto add = [&]() {
+                        acq.x += wn * rn[g].x - wo * ro[g].x;
+                        acq.y += wn * rn[g].y - wo * ro[g].y;
+                        acq.z += wn * rn[g].z - wo * ro[g].z;
+                        acq.w += wn * rn[g].w - wo * ro[g].w;
+                        dsum += wn - wo;
+                        mag += wn + wo;
+                    };
+                    if (!__any(v[g] != cur)) {
+                        add();
+                    } else {                                // destination by destination (they are in order)
+                        unsigned long long left = __ballot(v[g] != NONE);
+                        while (left) {
+                            const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)v[g], __ffsll((long long)left) - 1);
+                            if (vg != cur) {
+                                if (cur != NONE) flush();
+                                cur = vg;
+                            }
+                            const bool same = v[g] == vg;
+                            if (same) add();
+                            left &= ~__ballot(same);
+                        }
+                    }
+                }
+            }
+        } else {
+            const float my_n = in ? gat_weight(a.ssrc[my.y], t_v) : 0.0f, my_o = in ? gat_weight(a.sold[my.y], t_v) : 0.0f;
+            for (uint32_t k0 = 0; k0 < n; k0 += G) {
+                float rn[G][NJ], ro[G][NJ], x[G][NJ];
+                uint32_t before = cur;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int kk = (int)min(k0 + (uint32_t)g, n - 1u);
+                    const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)my.y, kk), v = (uint32_t)__builtin_amdgcn_readlane((int)my.x, kk);
+                    const bool own = v != before && v != v_first && v != v_last;
+                    before = v;
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+                        const size_t at = (size_t)u * ldp + min((uint32_t)lane + 64u * j, d - 1u);
+                        rn[g][j] = a.P[at];
+                        ro[g][j] = a.Pold[at];
+                        x[g][j] = own ? a.p.X[(size_t)v * d + min((uint32_t)lane + 64u * j, d - 1u)] : 0.0f;
+                    }
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int k = (int)(k0 + (uint32_t)g);
+                    if (k >= (int)n) continue;
+                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)my.x, k);
+                    const float wn = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(my_n), k));
+                    const float wo = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(my_o), k));
+                    if (v != cur) {
+                        if (cur != NONE) flush();
+                        cur = v;
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) xo[j] = x[g][j];
+                    }
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) acc[j] += wn * rn[g][j] - wo * ro[g][j];
+                    dsum += wn - wo;
+                    mag += wn + wo;
+                }
+            }
+        }
+    }
+    if (cur != NONE) flush();
+}
+
+uint32_t rp_gat_long_min(const ripple_ctx *c) { return c->in_w ? 0xFFFFFFFFu : GAT_LONG; }
+
 // Vertices that a run boundary cuts: their parts added up, a wavefront per run (22 us for 256 columns and 12 K runs, 13 for 47 and
 // 17 K). Then (hops) every patched denominator that has cancelled is queued: of the cut vertices by the wavefront that has just
 // finished it, of the others, which this launch does not write, by a thread each.
@@ -773,7 +922,7 @@ __global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
 // bootstrap: every live vertex (c->all_list, its in-degree prefix in c->ioff_all, count in ctr->n_all) is recomputed.
 // listed: a small hop, whose vertices (and the long rows among them) were listed while they were marked: a wavefront or a
 // workgroup per row in one launch, which is paced by the longest chain of reads; all other hops are cut over edges.
-void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool listed) {
+void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool listed, uint32_t pair_cap) {
     const LayerDev &ly = c->layers[l - 1];
     GatArgs a;
     a.list = c->list[l];
@@ -855,7 +1004,7 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool liste
     e.mag = c->gat_mag;
     e.rec = c->gat_rec;
     e.all = bootstrap ? 1 : 0;
-    e.long_min = c->in_w ? 0xFFFFFFFFu : GAT_LONG;
+    e.long_min = rp_gat_long_min(c);
     e.n_waves = c->n_cu * 8 * 4;
     e.queue = c->all_list;
     e.queue_count = &c->ctr->n_long[l];
@@ -866,11 +1015,16 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool liste
     e.struct_cap = a.struct_cap;
     hipLaunchKernelGGL(k_gat_prepare, grid, block, 0, c->stream, e);
     if (e.struct_cap) hipLaunchKernelGGL(k_gat_edge_terms, dim3(c->n_cu * 2), block, 0, c->stream, e);
+    const uint32_t n_cnt = pair_cap ? rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap).n : 0u;
     b.all = 1;                                           // rows whose patch has cancelled: read once more
     b.split_min = 0xFFFFFFFFu;
 #define GAT_CASE(NJ, QUAD, TEAM)                                                                                              \
     do {                                                                                                                      \
         hipLaunchKernelGGL((k_gat_edges<NJ, QUAD>), grid, block, 0, c->stream, e);                                            \
+        if (pair_cap) {                                                                                                       \
+            rp_launch_list_order(c, l, pair_cap);                                                                             \
+            hipLaunchKernelGGL((k_gat_list<NJ, QUAD>), grid, block, 0, c->stream, e, c->pair_sorted, pair_cap, c->opt_sorted == 2, c->pair_cnt, n_cnt); \
+        }                                                                                                                     \
         hipLaunchKernelGGL(k_gat_close, dim3(c->n_cu * 16), block, 0, c->stream, e);                                                     \
         if (bootstrap) break;                                                                                                 \
         hipLaunchKernelGGL((k_gat_scatter_long<NJ, TEAM>), dim3(c->n_cu), dim3(TEAM * 64), 0, c->stream, b);                  \

@@ -65,6 +65,7 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t range_rows;                      // attention layers: rows updated from sums that were not finite
     uint32_t pull_next[RIPPLE_MAX_LAYERS + 1];// pull scatter of hop l: runs of chunks handed out so far
     uint32_t pair_over[RIPPLE_MAX_LAYERS + 1];// a bucket of hop l's messages had no room for all of its own
+    uint32_t pairs[RIPPLE_MAX_LAYERS + 1];    // attention hops: messages in the list (those of vertices that are not recomputed)
 };
 // buckets of a hop's messages: at most this many, each of at most this many consecutive vertices
 #define RP_LIST_BUCKETS 8192u
@@ -509,6 +510,27 @@ __device__ __forceinline__ bool rp_hop_listed(const DevCtr *ctr, uint32_t l, uin
     if (!cap || M == 0 || M > cap || ctr->pair_over[l] || hop_mode == RP_HOP_DISCOVER) return false;
     if (force) return true;
     return hop_mode == RP_HOP_PULL ? RP_LIST_FACTOR * M + RP_LIST_FIXED <= ctr->isum[l] : (unsigned long long)M * d >= RP_LIST_NUMBERS;
+}
+
+// An attention hop: its vertices that are recomputed read whole in-rows, the others take a message per changed in-neighbour. Those messages are found by
+// testing every in-neighbour, or taken from a list that the out-edge walk writes, where that pays by the same measure (a set reached along M edges has
+// about M mean in-degrees of in-neighbours, at most all edges). Decided before the set is known, from M alone: all of the hop's kernels agree.
+// Not where M is more than a 64th of the edges: the messages' rows, two each, are then most of the work either way. 3 M messages of 47 columns out of 7 M
+// walked edges of 31 M: walk and hop 865 us, listed 1,020 (walk 122, order 24, recomputed vertices 682, messages 190).
+#define RP_GAT_LIST_SHARE 64ull
+__device__ __forceinline__ bool rp_gat_list_made(const DevCtr *ctr, uint32_t M, uint32_t cap, int force) {
+    if (!cap || M == 0 || M > cap) return false;
+    if (force) return true;
+    const unsigned long long e = ctr->n_edges, n = ctr->n_alive ? ctr->n_alive : 1u;
+    return RP_GAT_LIST_SHARE * M <= e && RP_LIST_FACTOR * M + RP_LIST_FIXED <= M * (e / n);
+}
+__device__ __forceinline__ bool rp_gat_listed(const DevCtr *ctr, uint32_t l, uint32_t cap, int force) {
+    return cap && !ctr->pair_over[l] && rp_gat_list_made(ctr, ctr->set[l - 1].a ? ctr->set[l - 1].m : 0u, cap, force);
+}
+// a vertex of the hop's set is recomputed from all its in-neighbours
+__device__ __forceinline__ bool rp_gat_recomputes(const uint32_t *bm_prev, const uint32_t *bm_sink, const uint32_t *bm_vadd, const uint2 *in_meta, uint32_t long_min, uint32_t v) {
+    const uint32_t w = v >> 5, b = v & 31u, is = bm_prev[w] | bm_vadd[w], sink = bm_sink[w];    // (read together)
+    return ((is >> b) & 1u) || (((sink >> b) & 1u) && in_meta[v].y <= long_min);
 }
 
 // position of `target` in row[0..len), searched by one wavefront; -1 when absent. Rows begin at multiples of four entries and

@@ -17,6 +17,8 @@
 // In place of a list in edge order and a radix sort of it (4.6 M pairs: 0.09 ms for the walk, 0.24 for the sort and its launches; here 0.117
 // for the walk and 0.036 for k_list_order).
 #define LIST_C 4
+// up to here a tile is a quarter of that: most compute units would have none (220 K walked edges of an attention hop 64 us / 21, 140 K of a sum 30 / 13; 2 M 38 / 38)
+#define LIST_SMALL (1u << 20)
 struct ListWalk {
     uint2 *pairs;
     const float *out_w;            // weighted sums: weights beside the out-rows, and where they go beside the pairs
@@ -24,30 +26,44 @@ struct ListWalk {
     uint32_t *cnt;
     ListCut cut;
     uint32_t cap;
+    // attention hops: messages to vertices that are recomputed anyway are not listed
+    int attn, force;
+    const uint32_t *bm_prev, *bm_sink, *bm_vadd;
+    const uint2 *in_meta;
+    uint32_t long_min;
 };
-template <int WT>
-__global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff, const uint2 *out_meta,
-                                                        const uint32_t *out_pool, uint8_t *mk, DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio,
-                                                        int allow_disc, ListWalk w) {
-    if (allow_disc && rp_hop_mode(ctr, l, d, mode, ratio, allow_disc) == RP_HOP_DISCOVER) return;
+// the tiles of a list walk, C chunks of 256 edges to a wavefront
+template <int C, int WT>
+__device__ __forceinline__ void list_tiles(const uint32_t *list, uint32_t count, uint32_t M, const uint32_t *eoff, const uint2 *out_meta,
+                                           const uint32_t *out_pool, uint8_t *mk, DevCtr *ctr, uint32_t l, const ListWalk &w, uint32_t *s_at) {
     constexpr uint32_t NONE = 0xFFFFFFFFu, FULL = 0xFF000000u;
-    __shared__ uint32_t s_at[RP_LIST_BUCKETS];              // per bucket: this tile's pairs, then where the next one goes
-    const uint32_t count = *count_ptr, wave = threadIdx.x >> 6;
-    const uint32_t M = count ? count_ptr[1] : 0u;
-    if (M == 0 || M > w.cap) {
-        frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), blockIdx.x * 16u + wave, gridDim.x * 16u);
-        return;
-    }
-    constexpr uint32_t TILE = 16u * LIST_C;                 // chunks of a workgroup
+    constexpr uint32_t TILE = 16u * C;                      // chunks of a workgroup
+    const uint32_t wave = threadIdx.x >> 6;
     const uint32_t n_tiles = (M + TILE * MARK_CHUNK - 1) / (TILE * MARK_CHUNK);
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         for (uint32_t b = threadIdx.x; b < w.cut.n; b += 1024u) s_at[b] = 0;
-        uint32_t v[4 * LIST_C], u[4 * LIST_C];
-        float wt[WT ? 4 * LIST_C : 1];
-        walk_collect<LIST_C, WT>(list, count, M, eoff, out_meta, out_pool, w.out_w, tile * TILE + wave * LIST_C, v, u, wt);
+        uint32_t v[4 * C], u[4 * C];
+        float wt[WT ? 4 * C : 1];
+        walk_collect<C, WT>(list, count, M, eoff, out_meta, out_pool, w.out_w, tile * TILE + wave * C, v, u, wt);
+        if (w.attn) {
+            uint32_t is[4 * C], sink[4 * C];                // all of them on their way together
+#pragma unroll
+            for (int t = 0; t < 4 * C; ++t) {
+                const uint32_t at = v[t] == NONE ? 0u : v[t] >> 5;
+                is[t] = w.bm_prev[at] | w.bm_vadd[at];
+                sink[t] = w.bm_sink[at];
+            }
+#pragma unroll
+            for (int t = 0; t < 4 * C; ++t) {
+                const uint32_t x = v[t], b = x & 31u;
+                if (x == NONE) continue;
+                mk[x] = 1;
+                if (((is[t] >> b) & 1u) || (((sink[t] >> b) & 1u) && w.in_meta[x].y <= w.long_min)) v[t] = NONE;
+            }
+        }
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < 4 * LIST_C; ++t)
+        for (int t = 0; t < 4 * C; ++t)
             if (v[t] != NONE) {
                 mk[v[t]] = 1;
                 atomicAdd(&s_at[v[t] >> w.cut.shift], 1u);
@@ -63,7 +79,7 @@ __global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, co
         }
         __syncthreads();
 #pragma unroll
-        for (int t = 0; t < 4 * LIST_C; ++t)
+        for (int t = 0; t < 4 * C; ++t)
             if (v[t] != NONE) {
                 const uint32_t at = atomicAdd(&s_at[v[t] >> w.cut.shift], 1u);
                 if (at < FULL) {
@@ -73,6 +89,22 @@ __global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, co
             }
         __syncthreads();
     }
+}
+
+template <int WT>
+__global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff, const uint2 *out_meta,
+                                                        const uint32_t *out_pool, uint8_t *mk, DevCtr *ctr, uint32_t l, uint32_t d, int mode, int ratio,
+                                                        int allow_disc, ListWalk w) {
+    if (allow_disc && rp_hop_mode(ctr, l, d, mode, ratio, allow_disc) == RP_HOP_DISCOVER) return;
+    __shared__ uint32_t s_at[RP_LIST_BUCKETS];              // per bucket: this tile's pairs, then where the next one goes
+    const uint32_t count = *count_ptr, wave = threadIdx.x >> 6;
+    const uint32_t M = count ? count_ptr[1] : 0u;
+    if (w.attn ? !rp_gat_list_made(ctr, M, w.cap, w.force) : (M == 0 || M > w.cap)) {
+        frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), blockIdx.x * 16u + wave, gridDim.x * 16u);
+        return;
+    }
+    if (M <= LIST_SMALL) list_tiles<1, WT>(list, count, M, eoff, out_meta, out_pool, mk, ctr, l, w, s_at);
+    else list_tiles<LIST_C, WT>(list, count, M, eoff, out_meta, out_pool, mk, ctr, l, w, s_at);
 }
 
 __global__ __launch_bounds__(256) void k_frontier_mark(const uint32_t *list, const uint32_t *count_ptr,
@@ -110,6 +142,10 @@ struct CompactArgs {
     uint32_t *count_out, *msgs_out, *isum_out;
     uint32_t list_cap;             // entries the list has room for (positions beyond are counted, not written)
     HostFlag done;                 // k_bitmap_ids only
+    // attention hops whose messages are listed (rp_gat_listed): the in-degree prefix is that of the vertices that are recomputed alone
+    const DevCtr *gat;             // null: any other compaction
+    uint32_t gat_l, gat_cap, gat_long;
+    int gat_force;
 };
 
 // Compaction of a bitmap into its ascending list. A wavefront takes two bitmap words at a time, a lane being a vertex:
@@ -179,11 +215,19 @@ struct WordRange {
             for (int s = 0; s < S; ++s) o[s] = i[s] = 0u;
             return;
         }
+        const bool some = a.gat && rp_gat_listed(a.gat, a.gat_l, a.gat_cap, a.gat_force);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const uint32_t v = (w0 + 2u * s) * 32u + (uint32_t)lane;
             o[s] = (a.want_out && on[s]) ? a.out_meta[v].y : 0u;
             i[s] = (a.want_in && on[s]) ? a.in_meta[v].y : 0u;
+        }
+        if (some) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const uint32_t v = (w0 + 2u * s) * 32u + (uint32_t)lane;
+                if (on[s] && !rp_gat_recomputes(a.bm_prev, a.bm_sink, a.bm_vadd, a.in_meta, a.gat_long, v)) i[s] = 0u;
+            }
         }
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -464,7 +508,8 @@ __global__ __launch_bounds__(1024) void k_list_eoff(const uint32_t *list, const 
 
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     if (pair_cap) {
-        const ListWalk w = {c->pairs, c->out_w, c->pair_w, c->pair_cnt, rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap), pair_cap};
+        const ListWalk w = {c->pairs, c->out_w, c->pair_w, c->pair_cnt, rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap), pair_cap,
+                            rp_layer_attn(c, l) ? 1 : 0, c->opt_sorted == 2, c->bm[l - 1], c->bm_sink, c->bm_vadd, c->in_meta, rp_gat_long_min(c)};
         const auto kernel = c->layers[l - 1].agg == RIPPLE_AGG_WSUM ? k_frontier_list<1> : k_frontier_list<0>;
         hipLaunchKernelGGL(kernel, dim3(c->n_cu * 2), dim3(1024), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->eoff[l - 1],
                            c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0, w);
@@ -502,8 +547,13 @@ void rp_launch_alive_list(ripple_ctx *c) {
 // pruned: bm[l] already is the hop's final set (max / min layers: candidates whose aggregate did not
 // change have been taken out again), so neither marks nor S are merged into it
 void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool want_out, bool want_in,
-                                bool accumulate_rep, bool pruned) {
+                                bool accumulate_rep, bool pruned, uint32_t gat_cap) {
     CompactArgs a;
+    a.gat = gat_cap ? c->ctr : nullptr;
+    a.gat_l = l;
+    a.gat_cap = gat_cap;
+    a.gat_long = rp_gat_long_min(c);
+    a.gat_force = c->opt_sorted == 2;
     a.bm = c->bm[l];
     a.mk = pruned ? nullptr : c->mk;
     a.bm_prev = self_term ? c->bm[l - 1] : nullptr;

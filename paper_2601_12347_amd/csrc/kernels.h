@@ -22,7 +22,7 @@ ripple_status rp_stable_sort_pairs(ripple_ctx *c, const uint32_t *keys_in, uint3
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap = 0);
 void rp_launch_alive_list(ripple_ctx *c);
 void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool want_out, bool want_in,
-                                bool accumulate_rep, bool pruned = false);
+                                bool accumulate_rep, bool pruned = false, uint32_t gat_cap = 0);
 void rp_launch_candidates(ripple_ctx *c, uint32_t l);
 void rp_launch_candidates_sparse(ripple_ctx *c, uint32_t l, bool self_term, uint32_t long_min);
 void rp_launch_list_offsets(ripple_ctx *c, uint32_t l, bool want_out);
@@ -46,12 +46,14 @@ struct ListCut {
 };
 ListCut rp_list_cut(const ripple_ctx *c, uint32_t messages);
 void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap);
+void rp_launch_list_order(ripple_ctx *c, uint32_t l, uint32_t pair_cap);   // attention hops
 void rp_launch_pull_all(ripple_ctx *c, uint32_t l);
 void rp_launch_messages(ripple_ctx *c, uint32_t l);
 void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr, bool listed);
 
 // attention.hip
-void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool prequeued = false);
+void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool prequeued = false, uint32_t pair_cap = 0);
+uint32_t rp_gat_long_min(const ripple_ctx *c);               // a sink of changed edges with at most this many in-neighbours recomputes
 void rp_launch_gat_save(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d);
 void rp_launch_gat_scores(ripple_ctx *c, uint32_t l, const uint32_t *list, const uint32_t *count_d);
 

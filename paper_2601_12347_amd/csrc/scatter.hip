@@ -304,12 +304,17 @@ struct ListArgs {
     DevCtr *ctr;
     uint32_t l;
     int mode, ratio, allow_disc;
+    int attn;                      // an attention hop (rp_gat_listed)
 };
 
 // Whether the hop was listed at all (M: its messages), and whether the list is what moves them
 __device__ __forceinline__ bool list_is_used(const ListArgs &a, uint32_t &M, bool &made) {
     const uint32_t cp = *a.m_count;
     M = cp ? a.m_count[1] : 0u;
+    if (a.attn) {
+        made = rp_gat_list_made(a.ctr, M, a.cap, a.force);
+        return made && !a.ctr->pair_over[a.l];
+    }
     const int hm = rp_hop_mode(a.ctr, a.l, a.d, a.mode, a.ratio, a.allow_disc);
     made = M > 0 && M <= a.cap && hm != RP_HOP_DISCOVER;
     return rp_hop_listed(a.ctr, a.l, a.d, M, a.cap, a.force, hm);
@@ -352,6 +357,7 @@ __global__ __launch_bounds__(256) void k_list_order(ListArgs a) {
     }
     __syncthreads();
     uint32_t at = s_before[0] + s_before[1] + s_before[2] + s_before[3] + incl - mine;
+    if (a.attn && bucket == gridDim.x - 1u && tid == 0) a.ctr->pairs[a.l] = s_before[0] + s_before[1] + s_before[2] + s_before[3] + n;
     for (uint32_t w = 0; w < (tid >> 6); ++w) at += s_sum[w];
     for (uint32_t i = i0; i < i1; ++i) {
         const uint32_t n_i = s_at[i];
@@ -979,10 +985,24 @@ ListCut rp_list_cut(const ripple_ctx *c, uint32_t messages) {
 }
 
 // From the list that k_frontier_list has made (the same pair_cap): nothing happens if it was not made or does not pay.
+void rp_launch_list_order(ripple_ctx *c, uint32_t l, uint32_t pair_cap) {
+    ListArgs a = {};
+    a.attn = 1;
+    a.pairs = c->pairs;
+    a.sorted = c->pair_sorted;
+    a.cnt = c->pair_cnt;
+    a.cut = rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap);
+    a.m_count = &c->ctr->set[l - 1].a;
+    a.cap = pair_cap;
+    a.force = c->opt_sorted == 2;
+    a.ctr = c->ctr;
+    a.l = l;
+    hipLaunchKernelGGL(k_list_order<0>, dim3(a.cut.n), dim3(256), 0, c->stream, a);
+}
 void rp_launch_scatter_list(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     const LayerDev &ly = c->layers[l - 1];
     const bool packed = ly.proj && ly.packed;
-    ListArgs a;
+    ListArgs a = {};
     a.pairs = c->pairs;
     a.sorted = c->pair_sorted;
     a.cnt = c->pair_cnt;
