@@ -1176,8 +1176,8 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         }
         // A hop that the last batch moved a good many messages at without discovering its set is taken from the list of them
         // (k_scatter_list) where that pays: in place of a pull through in-rows that hold enough entries, or of a push of enough numbers.
-        // The out-edge walk writes the list, whatever there is room for: batches differ by the hubs they meet, and one that is pulled because it has
-        // more messages than the last one costs more than the walk (100 updates on the dense graph that meet a hub, hop 3: 165 us of walk and 1,115 pulled, 210 and 460 listed).
+        // The out-edge walk writes the list, of up to eight times the last batch's messages: batches differ by the hubs they meet, and one that is pulled
+        // because it has more than was expected costs more than the walk (100 updates on the dense graph that meet a hub, hop 3: 165 us of walk and 1,115 pulled, 210 and 460 listed).
         // The kernels make sure on the device that the list is only used if it still pays; else the hop is pulled or pushed.
         uint32_t pair_cap = 0;
         if (l >= 2 && !sparse && c->pair_cap && c->opt_sorted && c->opt_scatter != 1 && c->opt_scatter != 3) {
@@ -1186,7 +1186,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             if (c->opt_sorted == 2) pair_cap = c->pair_cap;
             else if (c->hints_valid && m && m <= c->pair_cap && c->last_hop_mode[l] != 1u + RP_HOP_DISCOVER &&
                      (pulls ? rp_list_pays_pull(m, c->last_isum[l]) : m * c->xw[l] >= RP_LIST_NUMBERS))
-                pair_cap = c->pair_cap;
+                pair_cap = (uint32_t)std::min<uint64_t>(8 * m + 4096, c->pair_cap);
             if (pair_cap && list_runs_over(c, l, pair_cap)) pair_cap = 0;
         }
         if (sparse) rp_launch_frontier_sparse(c, l, layer_self(c, l), l < c->L);
