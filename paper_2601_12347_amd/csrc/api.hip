@@ -694,7 +694,10 @@ extern "C" ripple_status ripple_load_model(ripple_ctx *c, uint32_t n_layers, con
         RP_TRY(dev_alloc(c, &c->X[l], n * c->xw[l], true));
         if (c->layers[l - 1].selfc) RP_TRY(dev_alloc(c, &c->layers[l - 1].PS, n * c->d[l], true));
         if (c->layers[l - 1].proj) {
-            RP_TRY(dev_alloc(c, &c->layers[l - 1].T, n * c->d[l], true));
+            {
+                c->layers[l - 1].ldt = c->d[l] > 16u && c->d[l] <= 32u ? 32u : rp_round_up(c->d[l], 16);
+                RP_TRY(dev_alloc(c, &c->layers[l - 1].T, n * c->layers[l - 1].ldt, true));
+            }
             // packed rows are addressed with 32-bit byte offsets (vertex id * 128): below 2^25 vertices
             c->layers[l - 1].packed = (c->opt_pack && n < (1u << 25)) ? rp_msg_packed(c->d[l]) : 0u;
         }

@@ -342,6 +342,7 @@ struct MutArgs {
     void *H[RIPPLE_MAX_LAYERS + 1];
     float *X[RIPPLE_MAX_LAYERS + 1];
     float *T[RIPPLE_MAX_LAYERS + 1];             // project-first layers: what every vertex has sent so far (xw[l] floats per vertex), else null
+    uint32_t ldt[RIPPLE_MAX_LAYERS + 1];         // its row stride
     uint32_t mono_mask;                          // bit l: layer l takes max / min or attention (no structural terms)
     uint32_t wsum_mask;                          // bit l: layer l aggregates with the edge weights
     int d0_old;                                  // layer 1 does: D0 receives the old feature row instead of the difference
@@ -737,8 +738,8 @@ __device__ __forceinline__ void struct_term(const MutArgs &a, uint32_t u, uint32
         float val[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const size_t at = (size_t)u * w + min(c + 64u * t, w - 1u);
-            val[t] = a.T[l] ? a.T[l][at] : rp_load_h(a.H[l - 1], a.store, at);
+            const uint32_t col = min(c + 64u * t, w - 1u);
+            val[t] = a.T[l] ? a.T[l][(size_t)u * a.ldt[l] + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -1041,7 +1042,7 @@ __global__ __launch_bounds__(256) void k_det_terms(MutArgs a) {
                             if (k0 + (uint32_t)g >= cnt) continue;
                             const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(k0 + (uint32_t)g)), u = id & ~DET_ADD;
                             sg[g] = (id & DET_ADD) ? 1.0f : -1.0f;
-                            if (col < w) val[g] = Tl ? Tl[(size_t)u * w + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
+                            if (col < w) val[g] = Tl ? Tl[(size_t)u * a.ldt[l] + col] : rp_load_h(a.H[l - 1], a.store, (size_t)u * w + col);
                         }
 #pragma unroll
                         for (int g = 0; g < G; ++g)
@@ -1104,7 +1105,7 @@ __device__ __forceinline__ void apply_vertices(const MutArgs &a, uint32_t gw, ui
                     uint32_t dp = a.xw[l];
                     for (uint32_t c = lane; c < dp; c += 64) a.X[l][(size_t)w * dp + c] = 0.0f;
                     if (a.T[l])                            // a vertex created under this id later has sent nothing yet
-                        for (uint32_t c = lane; c < dp; c += 64) a.T[l][(size_t)w * dp + c] = 0.0f;
+                        for (uint32_t c = lane; c < dp; c += 64) a.T[l][(size_t)w * a.ldt[l] + c] = 0.0f;
                 }
             }
             if (lane == 0) {
@@ -1354,6 +1355,7 @@ static MutArgs make_args(ripple_ctx *c, uint32_t n_ops) {
         a.H[l] = c->H[l];
         a.X[l] = c->X[l];
         a.T[l] = (l >= 1 && l <= c->L && c->layers[l - 1].proj) ? c->layers[l - 1].T : nullptr;
+        a.ldt[l] = a.T[l] ? c->layers[l - 1].ldt : 0u;
     }
     a.mono_mask = 0;
     a.wsum_mask = 0;

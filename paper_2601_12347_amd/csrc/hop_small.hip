@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void k_hop_small(HopArgs a) {
         enter_roots(a.list, a.count_ptr, a.sp, gw, nw);
     } else if (blockIdx.x < a.nb_walk + a.nb_push) {
         if (blockIdx.x == a.nb_walk && threadIdx.x == 0 && a.count_ptr[1]) a.ctr->hop_mode[a.l] = 1u + RP_HOP_PUSH;
-        push_edges<NJ, 0, WT>(a.list, a.count_ptr, a.eoff, a.D, nullptr, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X,
+        push_edges<NJ, 0, WT>(a.list, a.count_ptr, a.eoff, a.D, nullptr, 0u, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X,
                               (blockIdx.x - a.nb_walk) * 4u + wave, a.nb_push * 4u);
     } else {
         wave_gemm<4, STORE>(a.g, (blockIdx.x - a.nb_walk - a.nb_push) * 4u + wave, (gridDim.x - a.nb_walk - a.nb_push) * 4u);
@@ -44,9 +44,9 @@ __global__ __launch_bounds__(256) void k_hop_small(HopArgs a) {
 
 // messages of a project-first layer (PD: projected rows, T: what has been sent)
 template <int NJ, int WT>
-__global__ __launch_bounds__(256) void k_push_projected(HopArgs a, const float *PD, const float *T, int packed) {
+__global__ __launch_bounds__(256) void k_push_projected(HopArgs a, const float *PD, const float *T, uint32_t ldt, int packed) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.count_ptr[1]) a.ctr->hop_mode[a.l] = 1u + RP_HOP_PUSH;
-    push_edges<NJ, 2, WT>(a.list, a.count_ptr, a.eoff, PD, T, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, blockIdx.x * 4u + (threadIdx.x >> 6),
+    push_edges<NJ, 2, WT>(a.list, a.count_ptr, a.eoff, PD, T, ldt, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, blockIdx.x * 4u + (threadIdx.x >> 6),
                           gridDim.x * 4u, packed != 0);
 }
 
@@ -109,8 +109,8 @@ void rp_launch_hop_small(ripple_ctx *c, uint32_t l, bool self_term) {
     if (!ly.proj) return;
 #define PUSH_CASE(NJ)                                                                                                                     \
     do {                                                                                                                                  \
-        if (a.out_w) hipLaunchKernelGGL((k_push_projected<NJ, 1>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, (int)ly.packed);   \
-        else hipLaunchKernelGGL((k_push_projected<NJ, 0>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, (int)ly.packed);           \
+        if (a.out_w) hipLaunchKernelGGL((k_push_projected<NJ, 1>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, ly.ldt, (int)ly.packed);   \
+        else hipLaunchKernelGGL((k_push_projected<NJ, 0>), dim3(nb_push), block, 0, c->stream, a, c->PD, ly.T, ly.ldt, (int)ly.packed);           \
     } while (0)
     if (a.d <= 64) PUSH_CASE(1);
     else if (a.d <= 128) PUSH_CASE(2);

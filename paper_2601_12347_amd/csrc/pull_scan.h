@@ -66,7 +66,8 @@ struct PullArgs {
     // deterministic variants only
     const uint32_t *bm_rec;        // destinations that are recomputed from all their in-neighbours (bootstrap inference), or null
     const void *Hprev;             // what a recomputed row sums: rows of H^{l-1} (storage format `store`) ...
-    const float *R;                // ... or, for a project-first layer, of T (what every vertex has sent so far); stride d
+    const float *R;                // ... or, for a project-first layer, of T (what every vertex has sent so far)
+    uint32_t ldr;                  // its row stride (H: d)
     int store;
     uint32_t side_runs;            // runs the side entries have room for (two entries per run)
     uint32_t *side_v;              // per run: the destinations of its first and last in-edge, if it has sums for them

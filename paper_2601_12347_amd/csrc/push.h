@@ -23,7 +23,7 @@ __device__ __forceinline__ float rp_message(float m, bool packed) {
 // 13 updates on 43 M edges 0.69 -> 0.23).
 template <int NJ, int PK, int WT>
 __device__ __forceinline__ void push_edges(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff, const float *D,
-                                           const float *T_sent, uint32_t ldd, uint32_t d, const uint2 *out_meta,
+                                           const float *T_sent, uint32_t ldt, uint32_t ldd, uint32_t d, const uint2 *out_meta,
                                            const uint32_t *out_pool, const float *out_w, float *X, uint32_t gw, uint32_t nw, bool packed = false) {
     constexpr int G = (NJ <= 2) ? 8 : (NJ <= 4 ? 4 : (NJ <= 8 ? 2 : 1));   // edges per round
     const uint32_t count = *count_ptr;
@@ -80,7 +80,7 @@ __device__ __forceinline__ void push_edges(const uint32_t *list, const uint32_t 
                     for (int j = 0; j < NJ; ++j) {
                         const uint32_t col = lane + 64 * j;
                         dreg[g][j] = (col < d) ? D[(size_t)uk * ldd + col] : 0.0f;
-                        if (PK == 2) sent[g][j] = (col < d) ? T_sent[(size_t)uk * d + col] : 0.0f;
+                        if (PK == 2) sent[g][j] = (col < d) ? T_sent[(size_t)uk * ldt + col] : 0.0f;
                     }
                 }
                 if constexpr (PK == 2) {

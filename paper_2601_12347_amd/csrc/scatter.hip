@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void k_scatter_push(const uint32_t *list, cons
         if (rp_hop_listed(ctr, l, d, cp ? count_ptr[1] : 0u, list_cap, list_force, hm)) return;
     }
     if (*count_ptr && blockIdx.x == 0 && threadIdx.x == 0) ctr->hop_mode[l] = 1u + RP_HOP_PUSH;
-    push_edges<NJ, PK, WT>(list, count_ptr, eoff, D, nullptr, ldd, d, out_meta, out_pool, out_w, X, (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
+    push_edges<NJ, PK, WT>(list, count_ptr, eoff, D, nullptr, 0u, ldd, d, out_meta, out_pool, out_w, X, (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
                        (gridDim.x * blockDim.x) >> 6);
 }
 
@@ -112,7 +112,7 @@ __device__ __forceinline__ bool pull_or_others(const PullArgs &a) {
     if (hm == RP_HOP_PULL) return true;
     if (a.others) {
         if (*a.m_count && blockIdx.x == 0 && threadIdx.x == 0) a.ctr->hop_mode[a.l] = 1u + RP_HOP_PUSH;
-        push_edges<NJ, PK, WT>(a.out_list, a.m_count, a.out_eoff, a.D, nullptr, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, gw, nw);
+        push_edges<NJ, PK, WT>(a.out_list, a.m_count, a.out_eoff, a.D, nullptr, 0u, a.ldd, a.d, a.out_meta, a.out_pool, a.out_w, a.X, gw, nw);
     }
     return false;
 }
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull(PullArgs a) {
                 }
             };
             if (!rec) rows([&](uint32_t u, uint32_t col) { return a.D[(size_t)u * a.ldd + col]; });
-            else if (a.R) rows([&](uint32_t u, uint32_t col) { return a.R[(size_t)u * d + col]; });
+            else if (a.R) rows([&](uint32_t u, uint32_t col) { return a.R[(size_t)u * a.ldr + col]; });
             else rows([&](uint32_t u, uint32_t col) { return rp_load_h(a.Hprev, a.store, (size_t)u * d + col); });
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(256) void k_scatter_pull4(PullArgs a) {
                 if constexpr (F != 0) {
                     fr[r] = *(const floatx4u *)(frow + (size_t)ent[r].x * a.ldd);
                 } else if (DET && rec) {
-                    const float *t = a.R + (size_t)(ent[r].x >> 7) * d;
+                    const float *t = a.R + (size_t)(ent[r].x >> 7) * a.ldr;
                     tv[DET ? r : 0][0] = t[sub];
                     tv[DET ? r : 0][1] = t[16u + sub];
                     tv[DET ? r : 0][2] = (32u + sub < d) ? t[32u + sub] : 0.0f;
@@ -1077,6 +1077,7 @@ void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
     a.bm_rec = bootstrap ? c->alive : nullptr;              // bootstrap: every listed vertex is recomputed; batches: none is
     a.Hprev = c->H[l - 1];
     a.R = ly.proj ? ly.T : nullptr;
+    a.ldr = ly.ldt;
     a.store = c->store;
     a.side_v = c->side_v;
     a.side_acc = c->side_acc;
@@ -1107,7 +1108,7 @@ void rp_launch_scatter_pull_det(ripple_ctx *c, uint32_t l, bool bootstrap) {
 // rounding took away is part of u's next message). 16 lanes per row, three columns (c, 16 + c, 32 + c) each for
 // packed rows; four rows per wavefront and step, two steps in flight.
 __global__ __launch_bounds__(256) void k_messages(const uint32_t *list, const uint32_t *count_ptr, float *PD, uint32_t ldd,
-                                                  float *T, uint32_t d, uint32_t packed, uint32_t *MSG) {
+                                                  float *T, uint32_t ldt, uint32_t d, uint32_t packed, uint32_t *MSG) {
     const uint32_t count = *count_ptr;
     const uint32_t lane = (uint32_t)rp_lane();
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
@@ -1122,13 +1123,13 @@ __global__ __launch_bounds__(256) void k_messages(const uint32_t *list, const ui
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     p[r] = PD[(size_t)u[r] * ldd + col];
-                    t[r] = T[(size_t)u[r] * d + col];
+                    t[r] = T[(size_t)u[r] * ldt + col];
                 }
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     if (s0 + r >= count) continue;
                     PD[(size_t)u[r] * ldd + col] = p[r] - t[r];
-                    T[(size_t)u[r] * d + col] = p[r];
+                    T[(size_t)u[r] * ldt + col] = p[r];
                 }
             }
         }
@@ -1145,7 +1146,7 @@ __global__ __launch_bounds__(256) void k_messages(const uint32_t *list, const ui
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const float *pr = PD + (size_t)u[r] * ldd;
-            const float *tr = T + (size_t)u[r] * d;
+            const float *tr = T + (size_t)u[r] * ldt;
             p[r][0] = pr[sub];
             t[r][0] = tr[sub];
             p[r][1] = has1 ? pr[16u + sub] : 0.0f;
@@ -1159,7 +1160,7 @@ __global__ __launch_bounds__(256) void k_messages(const uint32_t *list, const ui
             float v0, v1, v2;
             const uint2 ch = rp_msg_encode(p[r][0] - t[r][0], p[r][1] - t[r][1], p[r][2] - t[r][2], v0, v1, v2);
             *(uint2 *)(MSG + (size_t)u[r] * RP_MSG_WORDS + 2u * sub) = ch;
-            float *tr = T + (size_t)u[r] * d;
+            float *tr = T + (size_t)u[r] * ldt;
             tr[sub] = t[r][0] + v0;
             if (has1) tr[16u + sub] = t[r][1] + v1;
             if (has2) tr[32u + sub] = t[r][2] + v2;
@@ -1172,7 +1173,7 @@ void rp_launch_messages(ripple_ctx *c, uint32_t l) {
     const uint32_t hint = rp_rows_hint(c, l - 1);
     const uint32_t grid = std::max<uint32_t>(1u, std::min<uint32_t>(c->n_cu * 8, rp_div_up(hint, 4 * 8) + 1));
     hipLaunchKernelGGL(k_messages, dim3(grid), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->PD, c->pd_ld,
-                       ly.T, c->xw[l], ly.packed, c->MSG);
+                       ly.T, ly.ldt, c->xw[l], ly.packed, c->MSG);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1845,6 +1846,7 @@ void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr
 struct PullAllArgs {
     PullArgs p;                    // list (live vertices or candidates), count_ptr, ioff, in_meta, in_pool, in_w, d, X
     const void *Hprev;
+    uint32_t ldh;                  // its row stride
     int op;
     uint32_t n_cap;
     float *XN;                     // candidates: rows that a run boundary cuts [vertex x d]
@@ -1974,7 +1976,7 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
 #pragma unroll
                         for (int j = 0; j < NJ; ++j) {
                             const uint32_t col = min((uint32_t)lane + 64u * j, d - 1u);
-                            r[g][j] = rp_load_h(a.Hprev, STORE, (size_t)uk * d + col);
+                            r[g][j] = rp_load_h(a.Hprev, STORE, (size_t)uk * a.ldh + col);
                         }
                     }
 #pragma unroll
@@ -2006,7 +2008,7 @@ __global__ __launch_bounds__(256) void k_pull_all(PullAllArgs a, MonoArgs h) {
 }
 
 // Sums of fp32 rows of up to 64 columns: several rows per load instruction and four columns per lane, as k_scatter_pull4 takes them. (A lane per
-// column and a row per instruction takes 1,170 to 1,320 us for 47 columns and 31 M edges, depending on what the compiler makes of it; this 1,172, 64 G lines a second.)
+// column and a row per instruction takes 1,170 to 1,320 us for 47 columns and 31 M edges, depending on what the compiler makes of it; this 1,172, 64 G lines a second, and 950 with padded rows.)
 template <int F, int WT>
 __global__ __launch_bounds__(256) void k_pull_all4(PullAllArgs a) {
     constexpr int T = PULL_CHUNK / 64;
@@ -2073,7 +2075,7 @@ __global__ __launch_bounds__(256) void k_pull_all4(PullAllArgs a) {
                 for (int r = 0; r < LOADS; ++r) {
                     ent[r] = s_e[wave][k0 + ROWS * r + grp];
                     if (WT) wk[WT ? r : 0] = s_w[wave][k0 + ROWS * r + grp];
-                    fr[r] = *(const floatx4u *)(frow + (size_t)ent[r].x * d);
+                    fr[r] = *(const floatx4u *)(frow + (size_t)ent[r].x * a.ldh);
                 }
 #pragma unroll
                 for (int r = 0; r < LOADS; ++r) {
@@ -2176,6 +2178,7 @@ static PullAllArgs pull_all_args(ripple_ctx *c, uint32_t l) {
     a.p.d = c->xw[l];
     a.p.X = c->X[l];
     a.Hprev = proj ? (const void *)c->layers[l - 1].T : c->H[l - 1];
+    a.ldh = proj ? c->layers[l - 1].ldt : a.p.d;
     a.op = c->layers[l - 1].agg == RIPPLE_AGG_MAX ? 1 : (c->layers[l - 1].agg == RIPPLE_AGG_MIN ? 2 : 0);
     a.n_cap = c->n_cap;
     a.n_waves = c->n_cu * 8 * 4;

@@ -478,7 +478,7 @@ __global__ __launch_bounds__(256) void k_transform_addend_flat(TArgs a) {
 // Small hops of a project-first layer: the row update, and (the workgroups from nb on) T brought up to date with the messages
 // that push_edges<.., 2> has sent: T += m, element by element as rp_message made it.
 __global__ __launch_bounds__(256) void k_small_addend(TArgs a, uint32_t nb, const uint32_t *src_list, const uint32_t *src_count,
-                                                      const float *PD, uint32_t ldd, float *T, int packed) {
+                                                      const float *PD, uint32_t ldd, float *T, uint32_t ldt, int packed) {
     if (blockIdx.x < nb) {
         if (a.store) addend_only_rows<true>(a, blockIdx.x * 4u + (threadIdx.x >> 6), nb * 4u);
         else addend_only_rows<false>(a, blockIdx.x * 4u + (threadIdx.x >> 6), nb * 4u);
@@ -489,9 +489,9 @@ __global__ __launch_bounds__(256) void k_small_addend(TArgs a, uint32_t nb, cons
         const uint32_t u = src_list[i];
         for (uint32_t c0 = 0; c0 < a.N; c0 += 64u) {
             const uint32_t col = c0 + lane;
-            const float p = col < a.N ? PD[(size_t)u * ldd + col] : 0.0f, t = col < a.N ? T[(size_t)u * a.N + col] : 0.0f;
+            const float p = col < a.N ? PD[(size_t)u * ldd + col] : 0.0f, t = col < a.N ? T[(size_t)u * ldt + col] : 0.0f;
             const float m = rp_message(p - t, packed != 0);
-            if (col < a.N) T[(size_t)u * a.N + col] = packed ? t + m : p;
+            if (col < a.N) T[(size_t)u * ldt + col] = packed ? t + m : p;
         }
     }
 }
@@ -507,7 +507,7 @@ void rp_launch_small_addend(ripple_ctx *c, uint32_t l, bool emit_delta) {
     const uint32_t nb = std::min(rp_div_up(c->last_a[l] + c->last_a[l] / 2u + 32u, 32), c->n_cu * 8);
     const uint32_t nt = std::min(rp_div_up(c->last_a[l - 1] + c->last_a[l - 1] / 2u + 4u, 4), c->n_cu * 4);
     hipLaunchKernelGGL(k_small_addend, dim3(nb + nt), dim3(256), 0, c->stream, a, nb, c->list[l - 1], &c->ctr->set[l - 1].a, c->PD, c->pd_ld,
-                       ly.T, (int)ly.packed);
+                       ly.T, ly.ldt, (int)ly.packed);
 }
 
 // Many rows: every lane busy, whatever the row width. (Fewer: the launch is what counts.)
@@ -990,7 +990,7 @@ TArgs rp_project_args(ripple_ctx *c, uint32_t l, const uint32_t *list, const uin
     a.Kpad = rp_round_up(ly.d_in, 32);
     a.act = RIPPLE_ACT_NONE;
     a.tmp_out = bootstrap ? ly.T : c->PD;
-    a.tmp_out_ld = bootstrap ? ly.d_out : c->pd_ld;
+    a.tmp_out_ld = bootstrap ? ly.ldt : c->pd_ld;
     a.Hout = nullptr;
     a.out_mode = 2;
     a.a_mode = 4;
@@ -1029,7 +1029,7 @@ TArgs rp_project_both_args(ripple_ctx *c, uint32_t l, const uint32_t *list, cons
     a.split_col = 64;
     a.N1 = ly.d_out;
     a.tmp_out2 = bootstrap ? ly.T : c->PD;
-    a.tmp_out2_ld = bootstrap ? ly.d_out : c->pd_ld;
+    a.tmp_out2_ld = bootstrap ? ly.ldt : c->pd_ld;
     return a;
 }
 
