@@ -740,7 +740,8 @@ void rp_launch_candidates_sparse(ripple_ctx *c, uint32_t l, bool self_term, uint
 // straight into bm[l] and list[l] (unordered), then the degree prefixes over that list. Two launches
 // instead of the walk plus a scan of the whole bitmap.
 // long_min > 0 (attention hops): vertices with more in-neighbours than that are also queued in c->all_list
-// (count in ctr->n_long[l], zero since the batch began) for the workgroup role of the aggregation kernel.
+// (count in ctr->n_long[l], zero since the batch began) for the workgroup role of the aggregation kernel. Nothing reads an in-degree prefix there, and the
+// out-degrees' is written along with the list: no second launch (9 us for 1,400 vertices, 20 for 4,300).
 void rp_launch_frontier_sparse(ripple_ctx *c, uint32_t l, bool self_term, bool want_out, uint32_t long_min) {
     SparseArgs sp = rp_sparse_args(c, l, c->list[l], &c->ctr->set[l].a, self_term);
     if (long_min) {
@@ -748,10 +749,11 @@ void rp_launch_frontier_sparse(ripple_ctx *c, uint32_t l, bool self_term, bool w
         sp.long_list = c->all_list;
         sp.long_count = &c->ctr->n_long[l];
         sp.long_dup = 1;
+        if (want_out) sp.eoff = c->eoff[l];
     }
     hipLaunchKernelGGL(k_frontier_sparse, dim3(c->n_cu), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,
                        c->eoff[l - 1], c->out_meta, c->out_pool, sp);
-    rp_launch_list_offsets(c, l, want_out);
+    if (!long_min) rp_launch_list_offsets(c, l, want_out);
 }
 
 // degree prefixes over the (unordered) list of hop l

@@ -69,7 +69,7 @@ void rp_launch_scatter_push(ripple_ctx *c, uint32_t l, uint32_t pair_cap) {
 // ---------------------------------------------------------------------------------
 // pull: segmented reduction over in-rows, keeping only the sources that are in A_{l-1}
 // ---------------------------------------------------------------------------------
-// The flattened in-edge space of the listed destinations is cut into 256-edge chunks and every
+// The flattened in-edge space of the listed destinations is cut into chunks of up to 256 edges (rp_run_cut) and every
 // wavefront takes a contiguous run of chunks, so the row of a chunk's first edge follows from the
 // previous chunk instead of a search over the whole list. The 64 rows after that one (vertex, pool
 // position, first edge) sit in registers, one per lane; an edge finds its row with shuffles. The next

@@ -16,7 +16,7 @@ struct SparseArgs {
     uint32_t *bm;                  // the hop's bitmap (zero on entry)
     const uint32_t *alive;
     uint32_t *list, *count;        // the hop's list and its length (zero on entry)
-    // with eoff: the degree prefix over the list is written along with it. `count` is a DevCtr::Set: one 64-bit addition
+    // with eoff (all entered vertices are appended then, long_dup): the degree prefix over the list is written along with it. `count` is a DevCtr::Set: one 64-bit addition
     // reserves list positions and the stretch of the out-edge space that goes with them, so the prefix is in list order
     uint32_t *eoff;
     const uint2 *out_meta;
@@ -86,10 +86,12 @@ __device__ __forceinline__ void sparse_enter_many(const SparseArgs &s, const uin
         unsigned long long at = 0;
         if (lane == 0) {
             at = atomicAdd((unsigned long long *)s.count, ((unsigned long long)run << 32) | total);
+            if (ltotal) lbase = atomicAdd(s.long_count, ltotal);
             if (from_edge && s.touched) atomicAdd(s.touched, total);
             atomicAdd(s.isum, din);
         }
         base = __shfl((uint32_t)at, 0);
+        lbase = __shfl(lbase, 0);
         const uint32_t e = __shfl((uint32_t)(at >> 32), 0);
         const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
@@ -99,7 +101,9 @@ __device__ __forceinline__ void sparse_enter_many(const SparseArgs &s, const uin
                 s.list[p] = v[t];
                 s.eoff[p] = e + off[t];
             }
+            if (lng[t]) s.long_list[lbase + (uint32_t)__popcll(lmask[t] & below)] = v[t];
             base += (uint32_t)__popcll(mask[t]);
+            lbase += (uint32_t)__popcll(lmask[t]);
         }
         return;
     }
