@@ -339,6 +339,7 @@ static ripple_status init_graph(ripple_ctx **out, uint32_t n_vertices, uint32_t 
     g.add(&c->part_deg, (size_t)c->n_part);
     g.add(&c->part_ideg, (size_t)c->n_part);
     g.add(&c->part_tch, (size_t)c->n_part);
+    g.add(&c->part_rec, (size_t)c->n_part);
     g.add(&c->ctr, 1);
     RP_TRY(block_alloc(c, g, &c->graph_block, true));
     RP_TRY(dev_alloc(c, &c->out_pool, (size_t)pool_cap, false));
@@ -1150,7 +1151,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
             t = rp_timer_begin(c);
             rp_launch_transform(c, l, c->list[l], &c->ctr->set[l].a, next_reads_delta(c, l));
             rp_timer_end(c, t, RIPPLE_PH_TRANSFORM, (int)l);
-            have_all = false;                          // the long-row queue went through the live-vertex list's buffer
+            have_all = false;                          // the long-row queue and the recomputed vertices went through the live-vertex list's buffers
             continue;
         }
         // hop 1 always pushes: hop-0 rows are in operation order, not ranked by vertex id. Where the

@@ -470,7 +470,18 @@ struct GatEdgeArgs {
     const uint32_t *st_src, *st_dst, *n_struct;
     const float *st_sign;
     uint32_t struct_cap;
+    // where the messages of the other vertices are listed (rp_gat_listed): the recomputed vertices that have in-edges, and p.ioff is over them
+    const uint32_t *rec_list, *rec_count;
+    uint32_t list_cap;             // 0: never listed
+    int list_force;
 };
+// the vertices whose in-edges the hop reads, over which p.ioff is
+__device__ __forceinline__ bool gat_rows(const GatEdgeArgs &a, const uint32_t *&list, uint32_t &count) {
+    const bool listed = rp_gat_listed(a.p.ctr, a.p.l, a.list_cap, a.list_force);
+    list = listed ? a.rec_list : a.p.list;
+    count = listed ? *a.rec_count : *a.p.count_ptr;
+    return listed;
+}
 
 __global__ __launch_bounds__(256) void k_gat_prepare(GatEdgeArgs a) {
     const int lane = rp_lane();
@@ -530,7 +541,8 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
     constexpr uint32_t NONE = 0xFFFFFFFFu, PAD = 0x7FFFFFFEu, ITEMS = 2u * PULL_CHUNK + 16u;
     __shared__ uint32_t s_u[4][ITEMS], s_v[4][ITEMS];
     __shared__ float s_x[4][ITEMS];                         // QUAD: the destination's score; else the entry's weight
-    const uint32_t count = *a.p.count_ptr;
+    uint32_t count;
+    gat_rows(a, a.p.list, count);
     if (count == 0) return;
     const int lane = rp_lane(), wave = threadIdx.x >> 6;
     const uint32_t grp = (uint32_t)lane >> 4, sub = (uint32_t)lane & 15u;
@@ -880,7 +892,10 @@ __global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
     const uint32_t gw = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nw = (gridDim.x * blockDim.x) >> 6;
     const uint32_t count = *a.p.count_ptr, d = a.p.d;
     if (count == 0) return;
-    const RunCut rc = rp_run_cut(a.p.ioff[count], a.n_waves);
+    const uint32_t *rows;
+    uint32_t n_rows;
+    const bool listed = gat_rows(a, rows, n_rows);
+    const RunCut rc = rp_run_cut(a.p.ioff[n_rows], a.n_waves);
     const uint32_t n_runs = rc.n_runs, span = rc.span();
     auto cancelled = [](float den, float mag) { return mag > 0.0f && !(den > GAT_CANCEL * mag); };
     for (uint32_t r = gw; r < n_runs; r += nw) {
@@ -913,7 +928,7 @@ __global__ __launch_bounds__(256) void k_gat_close(GatEdgeArgs a) {
         if (lane == 0 && !a.all && !rec && cancelled(den, mag)) a.queue[atomicAdd(a.queue_count, 1u)] = v;
     }
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; !a.all && i < count; i += gridDim.x * blockDim.x) {
-        const uint32_t v = a.p.list[i], e0 = a.p.ioff[i], e1 = a.p.ioff[i + 1u];
+        const uint32_t v = a.p.list[i], e0 = listed ? 0u : a.p.ioff[i], e1 = listed ? 0u : a.p.ioff[i + 1u];
         if (a.rec[v] || (e1 > e0 && e0 / span != (e1 - 1u) / span)) continue;
         if (cancelled(a.den[v], a.mag[v])) a.queue[atomicAdd(a.queue_count, 1u)] = v;
     }
@@ -1013,6 +1028,10 @@ void rp_launch_gat_scatter(ripple_ctx *c, uint32_t l, bool bootstrap, bool liste
     e.st_sign = c->st_unit;
     e.n_struct = &c->ctr->n_struct;
     e.struct_cap = a.struct_cap;
+    e.rec_list = c->ioff_all;
+    e.rec_count = &c->ctr->n_rec;
+    e.list_cap = pair_cap;
+    e.list_force = c->opt_sorted == 2;
     hipLaunchKernelGGL(k_gat_prepare, grid, block, 0, c->stream, e);
     if (e.struct_cap) hipLaunchKernelGGL(k_gat_edge_terms, dim3(c->n_cu * 2), block, 0, c->stream, e);
     const uint32_t n_cnt = pair_cap ? rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap).n : 0u;

@@ -36,12 +36,13 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t error;                           // sticky consistency error seen by a kernel
     uint32_t blocks_done;                     // workgroups of a kernel with a last-workgroup part that have finished (0 between launches)
     uint32_t n_all;                           // live vertices listed for a discovering hop
+    uint32_t n_rec;                           // vertices with in-edges that the last listed attention hop recomputes
     uint32_t piece_done[READ_PIECES];         // workgroups that have written their part of a piece that the host reads (0 between launches)
     // from here on: zero when a batch begins (k_publish clears them once it has handed them to the host)
-    struct Set {
+    struct alignas(8) Set {
         uint32_t a;                           // |A_l|
         uint32_t m;                           // out-edges of A_l: messages into layer l + 1
-    } set[RIPPLE_MAX_LAYERS + 1];             // (eight bytes, so that small hops add to both at once)
+    } set[RIPPLE_MAX_LAYERS + 1];             // (eight bytes at a multiple of eight, so that small hops add to both at once)
     uint32_t touched[RIPPLE_MAX_LAYERS + 1];  // distinct live destinations of those edges
     uint32_t isum[RIPPLE_MAX_LAYERS + 1];     // sum of in-degrees over A_l
     uint32_t n_struct;
@@ -179,7 +180,7 @@ struct ripple_ctx {
     uint32_t *rep[RIPPLE_MAX_LAYERS + 1] = {nullptr};   // union over sub-batches (reporting)
     uint32_t *list[RIPPLE_MAX_LAYERS + 1] = {nullptr};  // A_l, ascending (l >= 1); op order for l = 0
     uint32_t *eoff[RIPPLE_MAX_LAYERS + 1] = {nullptr};  // exclusive scan of out-degrees over A_l, +1 entry
-    uint32_t *part_cnt = nullptr, *part_deg = nullptr, *part_ideg = nullptr, *part_tch = nullptr;  // per-block partial sums
+    uint32_t *part_cnt = nullptr, *part_deg = nullptr, *part_ideg = nullptr, *part_tch = nullptr, *part_rec = nullptr;  // per-block partial sums
     uint32_t *ioff[RIPPLE_MAX_LAYERS + 1] = {nullptr};  // exclusive scan of in-degrees over A_l, +1 entry
     uint32_t n_part = 0;
     uint32_t *all_list = nullptr;                       // scratch list (live vertices): full inference, discovering hops

@@ -135,17 +135,20 @@ struct CompactArgs {
     uint32_t n_words;
     const uint2 *out_meta, *in_meta;
     int want_out, want_in;         // emit out-degree / in-degree prefixes over the list
-    uint32_t *part_cnt, *part_out, *part_in, *part_tch;    // (part_tch: with touched_out only)
+    uint32_t *part_cnt, *part_out, *part_in, *part_tch, *part_rec;    // (part_tch: with touched_out only, part_rec: with gat)
     uint32_t *rep;                 // reporting union or null
     uint32_t *touched_out;         // += vertices that received a message, or null
     uint32_t *list, *eoff, *ioff;  // outputs
     uint32_t *count_out, *msgs_out, *isum_out;
     uint32_t list_cap;             // entries the list has room for (positions beyond are counted, not written)
     HostFlag done;                 // k_bitmap_ids only
-    // attention hops whose messages are listed (rp_gat_listed): the in-degree prefix is that of the vertices that are recomputed alone
+    // Attention hops whose messages are listed (rp_gat_listed): the vertices that are recomputed and have in-edges get a list of their own, and the
+    // in-degree prefix is over that one. (With the prefix over the whole list, zero for the others, the wavefront whose edges lay on both sides of
+    // 400 K vertices that are not recomputed went over those alone: a batch of 0.23 ms took 9.8.)
     const DevCtr *gat;             // null: any other compaction
     uint32_t gat_l, gat_cap, gat_long;
     int gat_force;
+    uint32_t *rec_list, *rec_count;
 };
 
 // Compaction of a bitmap into its ascending list. A wavefront takes two bitmap words at a time, a lane being a vertex:
@@ -158,6 +161,8 @@ struct WordRange {
     bool on[S];                    // this lane's vertex of step s is in the set
     uint32_t o[S], i[S];           // its degrees (0 where not wanted or not in the set)
     uint32_t cnt, tch, dout, din;  // the wavefront's totals
+    bool some;                     // a listed attention hop: i[s] is zero but for vertices that are recomputed
+    uint32_t nrec;                 // ... and how many those are
 
     static __device__ __forceinline__ uint32_t word(uint32_t w0, int s, int lane) { return w0 + 2u * s + ((uint32_t)lane >> 5); }
 
@@ -209,13 +214,14 @@ struct WordRange {
         }
     }
     __device__ __forceinline__ void degrees(const CompactArgs &a, uint32_t w0, int lane) {
-        dout = din = 0;
+        dout = din = nrec = 0;
+        some = false;
         if (!(a.want_out | a.want_in)) {
 #pragma unroll
             for (int s = 0; s < S; ++s) o[s] = i[s] = 0u;
             return;
         }
-        const bool some = a.gat && rp_gat_listed(a.gat, a.gat_l, a.gat_cap, a.gat_force);
+        some = a.gat && rp_gat_listed(a.gat, a.gat_l, a.gat_cap, a.gat_force);
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const uint32_t v = (w0 + 2u * s) * 32u + (uint32_t)lane;
@@ -227,6 +233,7 @@ struct WordRange {
             for (int s = 0; s < S; ++s) {
                 const uint32_t v = (w0 + 2u * s) * 32u + (uint32_t)lane;
                 if (on[s] && !rp_gat_recomputes(a.bm_prev, a.bm_sink, a.bm_vadd, a.in_meta, a.gat_long, v)) i[s] = 0u;
+                nrec += (uint32_t)__popcll(__ballot(i[s] != 0u));
             }
         }
 #pragma unroll
@@ -237,8 +244,8 @@ struct WordRange {
         dout = (uint32_t)__builtin_amdgcn_readlane((int)rp_wave_scan(dout), 63);
         din = (uint32_t)__builtin_amdgcn_readlane((int)rp_wave_scan(din), 63);
     }
-    // list entries and prefixes, from position oc and running sums oo, oi on
-    __device__ __forceinline__ void emit(const CompactArgs &a, uint32_t w0, int lane, uint32_t oc, uint32_t oo, uint32_t oi) const {
+    // list entries and prefixes, from position oc and running sums oo, oi on (some: the list of recomputed vertices from position orec on)
+    __device__ __forceinline__ void emit(const CompactArgs &a, uint32_t w0, int lane, uint32_t oc, uint32_t oo, uint32_t oi, uint32_t orec) const {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const unsigned long long mask = __ballot(on[s]);
@@ -254,21 +261,32 @@ struct WordRange {
             }
             if (a.want_in) {
                 const uint32_t x = rp_wave_scan(i[s]);
-                if (put) a.ioff[pos] = oi + x - i[s];
+                if (some) {
+                    const unsigned long long mr = __ballot(i[s] != 0u);
+                    const uint32_t at = orec + __builtin_amdgcn_mbcnt_hi((uint32_t)(mr >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mr, 0u));
+                    if (i[s]) {
+                        a.rec_list[at] = (w0 + 2u * s) * 32u + (uint32_t)lane;
+                        a.ioff[at] = oi + x - i[s];
+                    }
+                    orec += (uint32_t)__popcll(mr);
+                } else if (put) {
+                    a.ioff[pos] = oi + x - i[s];
+                }
                 oi += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
             }
         }
     }
 };
 
-__device__ __forceinline__ void compact_totals(const CompactArgs &a, uint32_t oc, uint32_t oo, uint32_t oi) {
+__device__ __forceinline__ void compact_totals(const CompactArgs &a, uint32_t oc, uint32_t oo, uint32_t oi, bool some, uint32_t orec) {
     *a.count_out = oc;
+    if (some) *a.rec_count = orec;
     if (a.want_out) {
         a.eoff[oc] = oo;
         if (a.msgs_out) *a.msgs_out = oo;
     }
     if (a.want_in) {
-        a.ioff[oc] = oi;
+        a.ioff[some ? orec : oc] = oi;
         if (a.isum_out) *a.isum_out = oi;
     }
 }
@@ -278,7 +296,7 @@ __device__ __forceinline__ void compact_totals(const CompactArgs &a, uint32_t oc
 // (optionally) their degrees per block of 8 S words
 template <int S>
 __global__ __launch_bounds__(256) void k_frontier_count(CompactArgs a) {
-    __shared__ uint32_t sh[16];
+    __shared__ uint32_t sh[20];
     const int lane = rp_lane(), wave = threadIdx.x >> 6;
     const uint32_t w0 = (blockIdx.x * 4u + wave) * 2u * S;
     WordRange<S> r;
@@ -289,6 +307,7 @@ __global__ __launch_bounds__(256) void k_frontier_count(CompactArgs a) {
         sh[4 + wave] = r.dout;
         sh[8 + wave] = r.din;
         sh[12 + wave] = r.tch;
+        sh[16 + wave] = r.nrec;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -297,19 +316,20 @@ __global__ __launch_bounds__(256) void k_frontier_count(CompactArgs a) {
         a.part_in[blockIdx.x] = sh[8] + sh[9] + sh[10] + sh[11];
         // (added to one counter, 1,196 blocks waited for one another: 22 us for 2.45 M vertices, now 12)
         if (a.touched_out) a.part_tch[blockIdx.x] = sh[12] + sh[13] + sh[14] + sh[15];
+        if (r.some) a.part_rec[blockIdx.x] = sh[16] + sh[17] + sh[18] + sh[19];
     }
 }
 
 // pass 2: write the ascending list and the degree prefixes
 template <int S>
 __global__ __launch_bounds__(256) void k_frontier_emit(CompactArgs a) {
-    __shared__ uint32_t sh[16], wt[12];
+    __shared__ uint32_t sh[20], wt[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t w0 = (blockIdx.x * 4u + wave) * 2u * S;
     WordRange<S> r;
     r.read(a, w0, lane);                                   // on its way while the blocks before this one are summed
     const bool last = blockIdx.x == gridDim.x - 1;
-    uint32_t pc = 0, po = 0, pi = 0, pt = 0;
+    uint32_t pc = 0, po = 0, pi = 0, pt = 0, pr = 0;
     for (uint32_t b = tid; b < blockIdx.x; b += 256) {
         pc += a.part_cnt[b];
         po += a.part_out[b];
@@ -317,29 +337,34 @@ __global__ __launch_bounds__(256) void k_frontier_emit(CompactArgs a) {
     }
     for (uint32_t b = tid; last && a.touched_out && b < gridDim.x; b += 256) pt += a.part_tch[b];
     r.degrees(a, w0, lane);
+    for (uint32_t b = tid; r.some && b < blockIdx.x; b += 256) pr += a.part_rec[b];
     pc = rp_wave_scan(pc);
     po = rp_wave_scan(po);
     pi = rp_wave_scan(pi);
     pt = rp_wave_scan(pt);
+    if (r.some) pr = rp_wave_scan(pr);
     if (lane == 63) {
         sh[wave] = pc;
         sh[4 + wave] = po;
         sh[8 + wave] = pi;
         sh[12 + wave] = pt;
+        sh[16 + wave] = pr;
         wt[wave] = r.cnt;
         wt[4 + wave] = r.dout;
         wt[8 + wave] = r.din;
+        wt[12 + wave] = r.nrec;
     }
     __syncthreads();
-    uint32_t oc = sh[0] + sh[1] + sh[2] + sh[3], oo = sh[4] + sh[5] + sh[6] + sh[7], oi = sh[8] + sh[9] + sh[10] + sh[11];
+    uint32_t oc = sh[0] + sh[1] + sh[2] + sh[3], oo = sh[4] + sh[5] + sh[6] + sh[7], oi = sh[8] + sh[9] + sh[10] + sh[11], orec = sh[16] + sh[17] + sh[18] + sh[19];
     for (int k = 0; k < wave; ++k) {
         oc += wt[k];
         oo += wt[4 + k];
         oi += wt[8 + k];
+        orec += wt[12 + k];
     }
-    r.emit(a, w0, lane, oc, oo, oi);
+    r.emit(a, w0, lane, oc, oo, oi, orec);
     if (last && tid == 255) {
-        compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din);
+        compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din, r.some, orec + r.nrec);
         if (a.touched_out) *a.touched_out += sh[12] + sh[13] + sh[14] + sh[15];
     }
 }
@@ -348,7 +373,7 @@ __global__ __launch_bounds__(256) void k_frontier_emit(CompactArgs a) {
 #define ONE_STEPS 8
 #define ONE_WORDS (16u * 2u * ONE_STEPS)
 __global__ __launch_bounds__(1024) void k_frontier_compact_one(CompactArgs a) {
-    __shared__ uint32_t wt[16 * 4];
+    __shared__ uint32_t wt[16 * 5];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t w0 = (uint32_t)wave * 2u * ONE_STEPS;
     WordRange<ONE_STEPS> r;
@@ -359,17 +384,19 @@ __global__ __launch_bounds__(1024) void k_frontier_compact_one(CompactArgs a) {
         wt[16 + wave] = r.dout;
         wt[32 + wave] = r.din;
         wt[48 + wave] = r.tch;
+        wt[64 + wave] = r.nrec;
     }
     __syncthreads();
-    uint32_t oc = 0, oo = 0, oi = 0;
+    uint32_t oc = 0, oo = 0, oi = 0, orec = 0;
     for (int k = 0; k < wave; ++k) {
         oc += wt[k];
         oo += wt[16 + k];
         oi += wt[32 + k];
+        orec += wt[64 + k];
     }
-    r.emit(a, w0, lane, oc, oo, oi);
+    r.emit(a, w0, lane, oc, oo, oi, orec);
     if (tid == 1023) {
-        compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din);
+        compact_totals(a, oc + r.cnt, oo + r.dout, oi + r.din, r.some, orec + r.nrec);
         uint32_t t = 0;
         for (int k = 0; k < 16; ++k) t += wt[48 + k];
         if (a.touched_out && t) atomicAdd(a.touched_out, t);
@@ -403,7 +430,8 @@ __global__ __launch_bounds__(256) void k_bitmap_ids(CompactArgs a) {
     for (int k = 0; k < wave; ++k) oc += wt[k];
 #pragma unroll
     for (int s = 0; s < S; ++s) r.o[s] = r.i[s] = 0u;
-    r.emit(a, w0, lane, oc, 0u, 0u);
+    r.some = false;
+    r.emit(a, w0, lane, oc, 0u, 0u, 0u);
     if (blockIdx.x == gridDim.x - 1 && tid == 255) *a.count_out = oc + r.cnt;
     report_done(a.done, gridDim.x);
 }
@@ -554,6 +582,8 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
     a.gat_cap = gat_cap;
     a.gat_long = rp_gat_long_min(c);
     a.gat_force = c->opt_sorted == 2;
+    a.rec_list = c->ioff_all;                      // (the live vertices' prefix is made anew behind an attention hop)
+    a.rec_count = &c->ctr->n_rec;
     a.bm = c->bm[l];
     a.mk = pruned ? nullptr : c->mk;
     a.bm_prev = self_term ? c->bm[l - 1] : nullptr;
@@ -569,6 +599,7 @@ void rp_launch_frontier_compact(ripple_ctx *c, uint32_t l, bool self_term, bool 
     a.part_out = c->part_deg;
     a.part_in = c->part_ideg;
     a.part_tch = c->part_tch;
+    a.part_rec = c->part_rec;
     a.done.flag = nullptr;
     a.rep = accumulate_rep ? c->rep[l] : nullptr;
     a.touched_out = pruned ? nullptr : &c->ctr->touched[l];
