@@ -200,8 +200,12 @@ typedef enum {
                                       carry a message, or pushed with many numbers to add, is scattered from the list of its
                                       messages instead, which the out-edge walk writes down by destination; 1 where the previous
                                       batch's counts say so, 2 at every hop from the second on that does not discover (tests), 0
-                                      never. Same results up to the order of the sums. Not used in the deterministic mode and on
-                                      graphs of more than 2^25 vertices. */
+                                      never. Attention hops list the messages of vertices that are not recomputed, where they are
+                                      at most a 64th of the edges (2: whatever their number). Same results up to the order of the
+                                      sums. Not used in the deterministic mode and on graphs of more than 2^25 vertices. Models with
+                                      such a hop from the second layer on take 24 bytes of device memory per message there is room
+                                      for at ripple_load_model: a quarter of the pools' entries, at most 2^25, weighted graphs 12
+                                      bytes more each; a sixteenth where the only such hops are attention. */
     RIPPLE_OPT_DETERMINISTIC = 6  /* 0/1 (default 0), before load_model: every sum is taken in an order that is a function of
                                      the graph and the batches alone (no float atomics: in-rows keep a reproducible order,
                                      hops are gathered along them, rows that several wavefronts read are finished in
