@@ -95,10 +95,8 @@ struct LayerDev {
     // is m = H[u] W_neigh - T[u] in the form it travels in (rounded to 19-bit block floating point when
     // the row is packed into one 128-byte line) and T[u] += m: what rounding takes away from one message is part
     // of the next, so nothing accumulates. Changed edges add or remove T[u] itself.
-    // Its rows begin at multiples of 64 bytes: every in-edge of the bootstrap gathers one, and a row of 47 numbers at any multiple of four bytes touches
-    // 2.4 lines on average, a padded one two (31 M edges: 1,172 us / 950).
     float *T;
-    uint32_t ldt;                             // row stride of T
+    uint32_t ldt;                             // row stride of T (sent_row_stride)
     uint32_t packed;                          // 0: messages travel as fp32 rows of PD; 1: as packed rows of MSG
     float *Wn;                                // neighbour weights padded to [roundup(d_in,32) x N0pad] (may alias W0)
     float *bzero;                             // N0pad zeros

@@ -29,3 +29,13 @@ def test_lists_of_attention_messages_take_what_they_can_hold():
     took = _load_bytes(1000, 8, "gat", (8, 8, 8), 1 << 26)
     print("  MB:", took / 1e6, flush=True)
     assert took <= 200e6
+
+
+def test_rows_of_narrow_layers_are_not_padded():
+    """A layer that is handled project-first keeps three tables of its output's width per vertex (H, the aggregate, what has been sent): 16 columns take
+    42 numbers per vertex more than 2 do."""
+    print("case memory of narrow rows", flush=True)
+    n = 2_000_000
+    took = {d: _load_bytes(n, 32, "gcn_sum", (32, d), 1000) for d in (2, 16)}
+    print("  MB:", {d: b / 1e6 for d, b in took.items()}, flush=True)
+    assert took[16] - took[2] >= 0.95 * 42 * 4 * n
