@@ -137,8 +137,9 @@ typedef struct {
     /* sum, mean and weighted-sum layers: how hop l moved its messages (Sec. 3.5 compares the costs): 1 pushed
      * along the out-edges of A_{l-1}, 2 pulled through the in-rows of A_l, 3 one scan of all in-rows that also
      * found A_l, 4 gathered from the list of the hop's messages sorted by destination (RIPPLE_OPT_SORTED_MESSAGES);
-     * 0 where no such kernel ran (no messages, other aggregators, deterministic mode). A batch that
-     * was cut into pieces reports its last piece. */
+     * 0 where no such kernel ran (no messages, other aggregators, deterministic mode). Attention layers: 4 where the
+     * messages of vertices that are not recomputed were taken from such a list, else 0. A batch that was cut into
+     * pieces reports its last piece. */
     uint32_t hop_mode[RIPPLE_MAX_LAYERS + 1];
     /* operations of the batch, counted from its start, that took effect: n_ops on success; on a capacity or
      * device error in a batch that had to be cut into pieces, the end of the last piece that went through */
@@ -204,8 +205,8 @@ typedef enum {
                                       at most a 64th of the edges (2: whatever their number). Same results up to the order of the
                                       sums. Not used in the deterministic mode and on graphs of more than 2^25 vertices. Models with
                                       such a hop from the second layer on take 24 bytes of device memory per message there is room
-                                      for at ripple_load_model: a quarter of the pools' entries, at most 2^25, weighted graphs 12
-                                      bytes more each; a sixteenth where the only such hops are attention. */
+                                      for at ripple_load_model, 36 with weighted sums: a quarter of the pools' entries, at most 2^25; a
+                                      sixteenth where the only such hops are attention. */
     RIPPLE_OPT_DETERMINISTIC = 6  /* 0/1 (default 0), before load_model: every sum is taken in an order that is a function of
                                      the graph and the batches alone (no float atomics: in-rows keep a reproducible order,
                                      hops are gathered along them, rows that several wavefronts read are finished in

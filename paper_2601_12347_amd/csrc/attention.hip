@@ -736,9 +736,10 @@ __global__ __launch_bounds__(256) void k_gat_edges(GatEdgeArgs a) {
 }
 
 // The messages of vertices that are not recomputed, from their list in order of destination (k_frontier_list, k_list_order): the old row taken away and
-// the new one added per changed in-neighbour, a sum per destination, added to its row by atomics. In place of testing all in-neighbours
-// of those vertices for the few that changed (rp_gat_list_made): 209 K messages of 256 columns to 135 K of them, with 14 M in-neighbours, k_gat_edges 405 -> 285
-// us (650 -> 412 for twice the recomputed vertices) and 84 here; with atomics for every row 130.
+// the new one added per changed in-neighbour, a sum per destination. Rows of more than 63 columns whose pairs all lie in one wavefront's run have no other
+// writer: their old row is read with the first message and stored with the sum. Narrow rows, and those at a run's ends, are added to by atomics. In
+// place of testing all in-neighbours of those vertices for the few that changed (rp_gat_list_made): 209 K messages of 256 columns to 135 K of them,
+// with 14 M in-neighbours, k_gat_edges 405 -> 285 us (650 -> 412 for twice the recomputed vertices) and 84 here; with atomics for every row 130.
 template <int NJ, bool QUAD>
 __global__ __launch_bounds__(256) void k_gat_list(GatEdgeArgs a, const uint2 *sorted, uint32_t cap, int force, uint32_t *cnt, uint32_t n_cnt) {
     const uint32_t M = a.p.ctr->set[a.p.l - 1u].a ? a.p.ctr->set[a.p.l - 1u].m : 0u;
@@ -748,6 +749,7 @@ __global__ __launch_bounds__(256) void k_gat_list(GatEdgeArgs a, const uint2 *so
         if (i < n_cnt) cnt[i] = 0;
     }
     if (a.p.ctr->pair_over[a.p.l]) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.p.ctr->hop_mode[a.p.l] = 1u + RP_HOP_SORTED;
     constexpr uint32_t NONE = 0xFFFFFFFFu;
     constexpr int G = QUAD ? 4 : (NJ >= 8 ? 1 : 8 / NJ);    // quads / messages in flight, two rows each
     const uint32_t n_pairs = a.p.ctr->pairs[a.p.l];
@@ -758,10 +760,10 @@ __global__ __launch_bounds__(256) void k_gat_list(GatEdgeArgs a, const uint2 *so
     const uint32_t n_chunks = (n_pairs + unit - 1u) / unit, per = (n_chunks + nw - 1u) / nw;
     const uint32_t c_begin = min(n_chunks, gw * per), c_end = min(n_chunks, c_begin + per);
     if (c_begin >= c_end) return;
-    // destinations of the run's first and last pair may have pairs in a neighbour's run; all others have one writer, whose old row is read with the first message
+    // destinations of the run's first and last pair may have pairs in a neighbour's run; all others have one writer
     const uint32_t v_first = sorted[c_begin * unit].x, v_last = sorted[min(n_pairs, c_end * unit) - 1u].x;
     uint32_t cur = NONE;
-    float xo[NJ];                                           // the old row (QUAD: of the lane's own column, in acc's layout)
+    float xo[NJ];                                           // the old row (not QUAD)
     float acc[NJ], dsum = 0.0f, mag = 0.0f;
     float4 acq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll

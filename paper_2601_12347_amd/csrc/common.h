@@ -62,7 +62,7 @@ struct DevCtr {                      // device-resident counters, one instance p
     uint32_t n_big[RIPPLE_MAX_LAYERS + 1];    // very long in-rows whose recomputation was split into segments
     uint32_t n_seg[RIPPLE_MAX_LAYERS + 1];    // segments queued for them
     uint32_t mono[3][RIPPLE_MAX_LAYERS + 1];  // max / min hops: candidates left unchanged / raised from the messages / recomputed
-    uint32_t hop_mode[RIPPLE_MAX_LAYERS + 1]; // 1 + RP_HOP_* of the scatter kernel that moved hop l's messages (0: none ran)
+    uint32_t hop_mode[RIPPLE_MAX_LAYERS + 1]; // 1 + RP_HOP_* of the scatter kernel that moved hop l's messages (0: none ran, attention hops: no list)
     uint32_t range_rows;                      // attention layers: rows updated from sums that were not finite
     uint32_t pull_next[RIPPLE_MAX_LAYERS + 1];// pull scatter of hop l: runs of chunks handed out so far
     uint32_t pair_over[RIPPLE_MAX_LAYERS + 1];// a bucket of hop l's messages had no room for all of its own

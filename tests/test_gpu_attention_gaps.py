@@ -46,7 +46,7 @@ def test_few_recomputed_vertices_far_apart(n, spread):
                 t0 = time.perf_counter()
                 res = rp.ripple_apply_updates(ctx, np.array([(ri.OP_FEAT_UPDATE, 0, 0, 0)], np.uint32), row)
                 best = min(best, time.perf_counter() - t0)
-                assert list(res.affected[:3]) == [1, 2 + spread, n]
+                assert list(res.affected[:3]) == [1, 2 + spread, n] and res.hop_mode[2] == (4 if mode else 0)
             times[mode], rows[mode] = best, rp.ripple_get_embeddings(ctx, 2, widths[2], n_rows=n)
         finally:
             rp.ripple_destroy(ctx)
