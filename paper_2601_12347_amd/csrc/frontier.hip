@@ -107,11 +107,8 @@ __global__ __launch_bounds__(1024) void k_frontier_list(const uint32_t *list, co
     else list_tiles<LIST_C, WT>(list, count, M, eoff, out_meta, out_pool, mk, ctr, l, w, s_at);
 }
 
-__global__ __launch_bounds__(256) void k_frontier_mark(const uint32_t *list, const uint32_t *count_ptr,
-                                                       const uint32_t *eoff, const uint2 *out_meta,
-                                                       const uint32_t *out_pool, uint8_t *mk, const DevCtr *ctr,
-                                                       uint32_t l, uint32_t d, int mode, int ratio, int allow_disc) {
-    if (allow_disc && rp_hop_mode(ctr, l, d, mode, ratio, allow_disc) == RP_HOP_DISCOVER) return;
+__global__ __launch_bounds__(256) void k_frontier_mark(const uint32_t *list, const uint32_t *count_ptr, const uint32_t *eoff, const uint2 *out_meta,
+                                                       const uint32_t *out_pool, uint8_t *mk) {
     frontier_walk<false>(list, count_ptr, eoff, out_meta, out_pool, mk, SparseArgs(), (blockIdx.x * blockDim.x + threadIdx.x) >> 6,
                          (gridDim.x * blockDim.x) >> 6);
 }
@@ -534,6 +531,7 @@ __global__ __launch_bounds__(1024) void k_list_eoff(const uint32_t *list, const 
     }
 }
 
+// allow_disc: the hop may discover its set (pair_cap > 0 then: without a list the launch that discovers marks)
 void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_t pair_cap) {
     if (pair_cap) {
         const ListWalk w = {c->pairs, c->out_w, c->pair_w, c->pair_cnt, rp_list_cut(c, c->last_m[l] ? c->last_m[l] : pair_cap), pair_cap,
@@ -543,9 +541,8 @@ void rp_launch_frontier_mark(ripple_ctx *c, uint32_t l, bool allow_disc, uint32_
                            c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], c->opt_scatter, c->opt_pull_ratio, allow_disc ? 1 : 0, w);
         return;
     }
-    hipLaunchKernelGGL(k_frontier_mark, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a,
-                       c->eoff[l - 1], c->out_meta, c->out_pool, c->mk, c->ctr, l, c->xw[l], c->opt_scatter,
-                       c->opt_pull_ratio, allow_disc ? 1 : 0);
+    hipLaunchKernelGGL(k_frontier_mark, dim3(c->n_cu * 8), dim3(256), 0, c->stream, c->list[l - 1], &c->ctr->set[l - 1].a, c->eoff[l - 1],
+                       c->out_meta, c->out_pool, c->mk);
 }
 
 // all live vertices, ascending, in c->all_list (count in ctr->n_all) with the exclusive scan of

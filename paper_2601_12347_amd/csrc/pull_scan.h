@@ -6,10 +6,15 @@
 #define PULL_CHUNK 256
 #define PULL_RUN 8                      // chunks a wavefront takes at a time on a large hop
 // How the flattened in-edge space of a list, `total` entries, is cut for nw wavefronts: chunks of `chunk` edges (64 edges a wavefront step, PULL_CHUNK at
-// most), `per` chunks to a run. A chunk is one chain of dependent reads (descriptors, ids, marks, rows), so where whole chunks would leave
-// wavefronts without any they are halved or quartered: a hop of 470 K in-edges is 7,300 chains of a quarter of the length and not 1,800 on 8,192 wavefronts.
+// most), `per` chunks to a run. A chunk is one chain of dependent reads (descriptors, ids, marks, rows), so hops of few in-edges are cut into halves or
+// quarters of a chunk as long as every wavefront still gets at most one: up to 64 nw in-edges (0.5 M on 8,192 wavefronts) chunks of 64, up to 128 nw (1.05 M) chunks of
+// 128. A hop of 470 K in-edges is 7,300 chains of a quarter of the length and not 1,800.
 //   In-edges, rows, 256 / 64 or 128 edges a chunk: 278 K, a thousand messages of 128 columns 18.8 / 11.0 us; 482 K, 9 K of 256 46.6 / 21.5; 468 K rows of 256
 //   all gathered 86.9 / 70.8 (the first three with what the flush of k_scatter_pull gained).
+// Not further: above that, from 1.05 M to 2.1 M in-edges, up to half of the wavefronts have no chunk of 256, but with more chunks than wavefronts
+// every wavefront asks the counter for another run, one after the other. Two-layer batches and bootstraps, limits as they are / twice as high, us:
+// 1.1 M in-edges, sums of 128 columns 316 / 385, of 60 222 / 304, attention's bootstrap 272 / 416, deterministic (no counter) 372 / 383; 2.05 M 402 / 511,
+// 276 / 418, 354 / 607, 459 / 484.
 struct RunCut {
     uint32_t chunk, n_chunks, per, n_runs;
     __host__ __device__ __forceinline__ uint32_t span() const { return chunk * per; }
@@ -52,7 +57,7 @@ struct PullArgs {
     DevCtr *ctr;
     uint32_t l;
     int mode, ratio, allow_disc;
-    // the hop's messages may have been listed and sorted instead (rp_hop_sorted): then the pull leaves the hop alone
+    // the hop's messages may have been listed and sorted instead (rp_hop_listed): then the pull leaves the hop alone
     const uint32_t *m_count;       // |A_{l-1}| and, in the next word, the number of messages
     uint32_t sorted_cap;           // entries the host sorted (0: no list was made)
     int sorted_force;

@@ -1838,8 +1838,9 @@ void rp_launch_scatter_mono(ripple_ctx *c, uint32_t l, const uint32_t *count_ptr
 // k_pull_all_close: a bootstrap of the same graph gives the same bits every time. Extremes do not depend on an order and are
 // combined with atomics, onto the start value that k_pull_all_init puts there (together with the zeros of vertices without
 // in-edges). One wavefront per row, one row in flight, is what this replaces: 34.0 / 15.6 / 8.3 ms for rows of 256 / 100 / 47
-// floats over 31 M edges, most of it spent waiting for the few wavefronts with the longest rows; now 4.3 / 2.0 / 1.25 ms (7.4, 6.2
-// and 4.7 TB/s of rows), 4.7 / 2.2 / 1.3 while sums and extremes were told apart in the inner loop.
+// floats over 31 M edges, most of it spent waiting for the few wavefronts with the longest rows; now 4.3 / 2.0 ms for 256 / 100 (7.4 and
+// 6.2 TB/s of rows), 4.7 / 2.2 while sums and extremes were told apart in the inner loop. Sums of fp32 rows of up to 64 columns go through k_pull_all4
+// (47 floats 0.95 ms, 1.2 here).
 // The same cut serves the hops of max / min layers whose candidates are all recomputed (mono_direct): a candidate's new
 // aggregate is compared with the old one when it is complete, stored if it differs and taken out of the hop's set if not;
 // what a run boundary cuts is put together in XN and finished by k_mono_close.
