@@ -50,7 +50,9 @@ def algorithmic_work(st, model, widths, store, L, layer_info, n_edges=0):
                   aggregate read and written once;
     frontier(l):  index pairs + column ids of the walked out-rows, the list written; not priced
                   where the hop discovered A_l while scattering (messages * 8 >= edges, the
-                  library's own rule), since no frontier kernel runs there;
+                  library's own rule), since no frontier kernel runs there, nor (main) where a
+                  batch had the walk in the launch that would have discovered A_l: scatter(l)
+                  holds its time then;
     transform(l): per dirty row the gathered input row, old H read, new H and delta written;
                   flops 2*K*d_out per row (plus the hidden stage for two-stage updates). For
                   project-first layers the projection of the hop's deltas (a_{l-1} rows) is
@@ -305,7 +307,7 @@ def main():
     for (ph, l), w in work.items():
         ms = st.ms[phase_idx[ph]][l] + (st.ms[6][l] if ph == "transform" else 0.0)   # 6: projection of the deltas
         n_launch = st.launches[phase_idx[ph]][l]
-        if not n_launch or ms <= 0:
+        if not n_launch or ms <= 0 or (ph == "frontier" and n_launch < st.batches):
             continue
         ent = {"ms_per_launch": ms / n_launch, "launches": int(n_launch),
                "GBps": w["bytes"] / (ms * 1e-3) / 1e9, "hbm_frac": w["bytes"] / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS}

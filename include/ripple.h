@@ -146,7 +146,10 @@ typedef struct {
     uint32_t n_ops_done;
 } ripple_batch_result;
 
-/* Accumulated per-kernel-class timing and work counters (RIPPLE_OPT_TIMING). */
+/* Accumulated per-kernel-class timing and work counters (RIPPLE_OPT_TIMING). FRONTIER is the out-edge walk that marks a hop's set
+ * (with the list of its vertices or messages where it writes one; the smallest hops of sums push in the same launch). A hop that may discover
+ * its set without that walk (hop_mode 3) has the walk, if it turns out to need one, in the launch that would have discovered: its time is part of
+ * SCATTER then, and no FRONTIER launch is counted for the batch. */
 #define RIPPLE_N_PHASES 8
 enum { RIPPLE_PH_INGEST = 0, RIPPLE_PH_STRUCT = 1, RIPPLE_PH_FRONTIER = 2, RIPPLE_PH_SCATTER = 3,
        RIPPLE_PH_COMPACT = 4, RIPPLE_PH_TRANSFORM = 5, RIPPLE_PH_OTHER = 6, RIPPLE_PH_TOTAL = 7 };

@@ -1216,7 +1216,7 @@ static void enqueue_piece(ripple_ctx *c, const SubBatch &sb, bool multi) {
         }
         if (sparse) rp_launch_frontier_sparse(c, l, layer_self(c, l), l < c->L);
         else if (!may_disc || pair_cap) rp_launch_frontier_mark(c, l, may_disc, pair_cap);   // (else by the launch that discovers or marks)
-        rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l);
+        rp_timer_end(c, t, RIPPLE_PH_FRONTIER, (int)l, !may_disc || pair_cap);
         const bool both = rp_has_project_both(c, l);
         if (c->layers[l - 1].proj) {                   // what travels is already multiplied by W_neigh
             t = rp_timer_begin(c);
