@@ -517,8 +517,17 @@ __device__ __forceinline__ bool rp_hop_listed(const DevCtr *ctr, uint32_t l, uin
 // An attention hop: its vertices that are recomputed read whole in-rows, the others take a message per changed in-neighbour. Those messages are found by
 // testing every in-neighbour, or taken from a list that the out-edge walk writes, where that pays by the same measure (a set reached along M edges has
 // about M mean in-degrees of in-neighbours, at most all edges). Decided before the set is known, from M alone: all of the hop's kernels agree.
-// Not where M is more than a 64th of the edges: the messages' rows, two each, are then most of the work either way. 3 M messages of 47 columns out of 7 M
-// walked edges of 31 M: walk and hop 865 us, listed 1,020 (walk 122, order 24, recomputed vertices 682, messages 190).
+// Not where M is more than a 64th of the edges: the messages' rows, two each, are then most of the work either way. Walk, compaction and scatter of a second
+// hop, us, in-rows tested / messages listed, 0.6 M vertices and 31 M edges:
+//   edges per message   47 columns     128 columns      256 columns
+//         657           336 / 142      386 / 187        448 / 287
+//         138           382 / 347      545 / 418        781 / 657
+//          67           436 / 467      671 / 574      1,051 / 930
+//          31           529 / 610      890 / 807      1,458 / 1,370
+//          10           767 / 825    1,487 / 1,440    2,703 / 2,613
+// Rows of up to 63 columns cross at about 100 edges per message, wider ones gain 3 to 9 % up to six times as many messages as the limit lets them have: one limit
+// for both. On 0.4 M vertices and 4 M edges, where the second condition (a mean in-degree of ten) never lists, nothing is lost: 47 to 650 edges per message,
+// 47 to 256 columns 60 to 222 us, listed 85 to 244.
 #define RP_GAT_LIST_SHARE 64ull
 __device__ __forceinline__ bool rp_gat_list_made(const DevCtr *ctr, uint32_t M, uint32_t cap, int force) {
     if (!cap || M == 0 || M > cap) return false;
